@@ -173,10 +173,11 @@ struct Ctx {
   // whole iterations in one launch for small logistic workloads, cada_logreg_small.hip
   int small;
   size_t small_lds;
+  int small_groups, small_dts;   // its row groups and whether the stored innovation / gradient stays in LDS
   int small_plain_launch;    // launch it as an ordinary grid (profilers that cannot trace cooperative dispatches)
   uint32_t *small_bar;       // the whole-step kernel's barrier words in the workspace
   uint32_t small_seq;        // its value after everything enqueued so far
-  void *small_args;          // room in the workspace for this context's launch-invariant arguments (replica launches)
+  void *small_args;          // room in the workspace for this context's launch-invariant arguments (launches of several steps)
   void *small_args_host;     // their host copy (owned by the context)
   // full-data evaluation scratch (cada_eval)
   double *eval_part;         // [M][kEvalBlocks][2] per-block sums of (loss, correct)

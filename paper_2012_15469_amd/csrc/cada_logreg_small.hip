@@ -1,24 +1,49 @@
 // Whole iterations of Algorithm 1 in one kernel launch, for logistic workloads so small that a
 // step is bound by launch and dependency latency rather than by memory (tens of workers, a few
-// hundred coordinates): four dependent launches per step cost 35-40 us, the arithmetic well
-// under one.  One workgroup per worker, launched cooperatively; n_steps iterations per launch
-// with ONE grid-wide barrier each:
+// hundred coordinates): four dependent launches per step cost 20-40 us, the arithmetic well
+// under one.  One workgroup per worker:
 //   phase A (workgroup m = worker m): both minibatch gradients in the difference form of
 //     cada_logreg.hip, the rule's left-hand side, the right-hand side from the ring, the
 //     decision, tau, the stored/fresh pointer swap, the trace           [S1-S4 of the step]
 //   -- barrier --
 //   phase B (EVERY workgroup, all coordinates): aggregate of the stored gradients, the server
 //     update, the squared step                                          [S5-S7]
-// Every workgroup keeps the server's vectors (iterate, moments, snapshot) in its LDS and applies the same update
+// Launches of several steps (k_small, launched cooperatively, ONE grid-wide barrier per iteration): every workgroup
+// keeps the server's vectors (iterate, moments, snapshot) in its LDS and applies the same update
 // to them, in the same order, so all copies stay bit for bit equal and the next phase A needs neither a second
 // barrier nor the iterate from memory; workgroup (j / 256) mod M writes coordinate j's results to memory for
-// the world outside and for the reference points theta^{k - tau}, tau >= 1, which are read a barrier later at
-// the earliest.  What a fast workgroup writes in phase A of step k + 1 while a slow one is still in phase B of
+// the world outside.  What a fast workgroup writes in phase A of step k + 1 while a slow one is still in phase B of
 // step k never is what the slow one reads: the fresh gradient goes to the row that is not the stored one, and
 // the decisions of step k are published in slot k mod 2 of an array of their own.
-// The barrier is that array: a workgroup's word carries the step's tag, its publication releases (writes back) and a
-// workgroup that has seen every word of the step acquires (invalidates) the XCD-local caches.  Every wait is bounded:
-// a wait that exceeds the bound sets bit 1 of the error flags and the workgroup stops waiting.
+// The barrier is that array.  Workgroup m publishes the word {tag of the step, its worker's buffer selector after the
+// decision} in slot (step parity, m); a workgroup has passed the barrier when the first wavefront, one lane per worker,
+// has seen this step's tag in every word -- and then it holds every decision, which a counter plus a separate array cost
+// a memory round trip more.  (Two slots per worker: a workgroup can be one step ahead of another at most, so the word
+// that a slow workgroup still waits for is not overwritten.  A tag is never 0, the value of a fresh workspace.)
+// Every wait is bounded: one that exceeds the bound sets bit 1 of the error flags and the workgroup stops waiting.
+//
+// A launch of one step (k_small_one, cada_step): nothing has to wait for another workgroup.  The one that finishes
+// phase A last (a counter in the workspace that also collects the decisions) runs phase B alone, with the same
+// operations in the same order, so a step ends bit for bit where it ends inside a longer launch.  Without a
+// wait among workgroups the launch needs no cooperative dispatch, whose queue hand-over costs more than the step.
+//
+// What bounds a step is a chain of dependent trips: rows in LDS -> products -> residuals -> gradient -> its stores
+// acknowledged -> word published -> words polled -> M rows of gradients -> update.  The kernel is built to shorten it:
+//   - eight wavefronts, so that the products of 32 rows are one pass of four rows each and the gradient's rows are
+//     split over the threads that have no column of their own; the sums over the lanes of a wavefront's rows are formed
+//     together, halving the number of values at each exchange (row_sums);
+//   - what one workgroup writes for the others (gradient rows, words) goes through to the coherence point and is read
+//     past the XCD's cache (device-scope accesses) instead of a write-back and an invalidation of the whole
+//     cache on each side of the barrier;
+//   - the stored innovation (CADA1) or gradient (LAG) of the worker, its reference point and the ring stay in LDS,
+//     the right-hand side is formed by a wavefront under the products, the next step's rows are asked for while the
+//     others arrive (LDS-direct loads into buffers that are free by then);
+//   - four workgroup barriers per step, which wait for LDS only; the wait for the gradient's stores is the one exception.
+// Measured (before: 256 threads, whole-cache release and acquire per step, a cooperative launch for a single step too):
+// one step per call, M = 10, B = 10, p = 54: 34.6 -> 11.5 us (of 8.8 us in the kernel: indices 1.6, rows and vectors 1.1,
+// products 1.0, gradient 1.4, count 1.1, rows of the aggregate 1.5, update 0.9; the phases' code comes from memory each
+// time); twenty steps per call, M = 20, B = 32, p = 784 (CADA1): 18.2 -> 11.9 us per step; ten runs of the first
+// workload side by side: 12.1 -> 7.2 us per step.
 #include <cstring>
 #include <new>
 #include <type_traits>
@@ -27,370 +52,438 @@
 
 namespace cada {
 
+constexpr int S_NT = 512, S_NW = S_NT / kWave;      // threads and wavefronts of a workgroup
+
+// What does not change from launch to launch; kept in the context's workspace for the launches of several steps.
 struct SmallArgs {
   DevState s;
+  uint32_t *bar;             // [64]: counter of a single-step launch (first 8 bytes); then [2][M] words {tag, selector} of the last two steps
+  uint32_t spin_limit;
+  int ps;                    // floats from one row to the next in LDS: p rounded up to a multiple of 4
+  int groups;                // row groups of the gradient pass (1, 2, 4, 8), each of all columns
+  int dts;                   // the worker's stored innovation (CADA1) or gradient (LAG, always) is kept in LDS
+};
+static_assert(sizeof(SmallArgs) <= kSmallArgsBytes && sizeof(SmallArgs) % 8 == 0, "room kept in the workspace");
+
+// What does: schedules, iteration, tag of the first step.
+struct SmallVar {
   const int32_t *idx;        // [n_steps][M][B]
   const uint8_t *replay;     // [n_steps][M] or nullptr
-  int64_t n_steps;
-  uint32_t *bar;             // barrier words: [64 unused][2][M] {tag, selector} of the last two steps
-  uint32_t bar_base;         // sequence number of this launch's first step (monotone over the life of the context)
-  uint32_t spin_limit;
-};
-static_assert(sizeof(SmallArgs) <= kSmallArgsBytes, "room kept in the workspace for a replica launch");
-
-// One launch serves one run (its arguments by value) or several independent runs (blockIdx.y
-// picks the run).  A run's arguments that do not change from launch to launch (where its state
-// lies) are kept in its own workspace, written once when the context is set up; what changes
-// (schedules, iteration, barrier count) travels by value with the launch.
-struct SmallVar {
-  const int32_t *idx;
-  const uint8_t *replay;
   int64_t k;
-  uint32_t bar_base;
+  uint32_t bar_base;         // sequence number of this launch's first step (monotone over the life of the context)
 };
+// Several independent runs (blockIdx.y picks the run) or one.
 struct SmallLaunch {
-  SmallArgs one;
   const SmallArgs *rep[CADA_MAX_REPLICAS];
   SmallVar var[CADA_MAX_REPLICAS];
   int64_t n_steps;
-  int n_rep;                 // 0: `one`
 };
 static_assert(sizeof(SmallLaunch) <= 4096, "kernel arguments");
 
 __device__ __forceinline__ float sigmoid_s(float a) { return 1.0f / (1.0f + expf(-a)); }
 
-// The barrier of a step is also how the decisions travel.  Workgroup m publishes the word {tag of the step, its
-// worker's buffer selector after the decision} with a release, in slot (step parity, m) of an array in the workspace; a
-// workgroup has passed the barrier when the first wavefront, one lane per worker, has seen this step's tag in every
-// word -- and then it holds every decision, which a counter plus a separate array cost a memory round trip more.
-// (Two slots per worker: a workgroup can be one step ahead of another at most, so the word that a slow workgroup
-// still waits for is not overwritten.  A tag is never 0, the value of a fresh workspace.)
-// `while_waiting` runs between this workgroup's publication and its wait: loads issued there are under way while
-// the others arrive.  dk_s[M] (LDS) receives the selectors; the function ends with a workgroup barrier.
-template <typename F>
-__device__ __forceinline__ void decision_barrier(const SmallArgs &a, uint32_t *words /* [M] of this parity */, int M, int m, uint32_t tag, int sel,
-                                                 unsigned char *dk_s, bool &dead, F while_waiting) {
-  __syncthreads();                      // every thread's stores have reached the L2 (the barrier waits for them) ...
-  // ... and the publication releases at agent scope: it writes the L2's dirty lines back before the word changes
-  if (threadIdx.x == 0) __hip_atomic_store(words + m, (tag << 1) | (uint32_t)sel, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-  while_waiting();
-  if (threadIdx.x < kWave) {
-    const int lane = threadIdx.x;
-    for (int m0 = 0; m0 < M; m0 += kWave) {
-      const int mm = m0 + lane;
-      uint32_t v = 0, spins = 0;
-      // (relaxed polls: the fence below is the acquire, once, instead of a cache invalidation per poll)
-      for (;;) {
-        if (mm < M) v = __hip_atomic_load(words + mm, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const bool ok = mm >= M || (v >> 1) == tag;
-        if (dead || __all(ok)) break;
-        if (++spins > a.spin_limit) { dead = true; if (lane == 0) atomicOr(a.s.err, 2u); break; }    // (the whole wavefront: spins is uniform)
-        __builtin_amdgcn_s_sleep(2);
-      }
-      if (mm < M) dk_s[mm] = (unsigned char)(v & 1u);
-    }
+typedef float v4s __attribute__((ext_vector_type(4)));
+typedef float v4u __attribute__((ext_vector_type(4), aligned(4)));     // four floats at any 4-byte aligned address
+
+// Four floats to / from the coherence point of the device (see above): buffer accesses with the device-scope bit (sc1), since
+// device-scope accesses exist in the language for four bytes only.  What lies past the buffer's end reads as zero.
+constexpr int kFar = 16;
+typedef uint32_t u4s __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t far_buffer(float *p, int64_t floats) {
+  return __builtin_amdgcn_make_buffer_rsrc(p, 0, (int)(floats * 4), 0x00020000);
+}
+__device__ __forceinline__ void store_far(__amdgpu_buffer_rsrc_t r, uint32_t byte_off, uint32_t row_off, v4s x) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4s, x), r, byte_off, row_off, kFar);
+}
+__device__ __forceinline__ v4s load_far(__amdgpu_buffer_rsrc_t r, uint32_t byte_off, uint32_t row_off) {
+  return __builtin_bit_cast(v4s, __builtin_amdgcn_raw_buffer_load_b128(r, byte_off, row_off, kFar));
+}
+// One LDS-direct load: lane l's 16 (4) bytes at `src` go to LDS byte `dst` + 16 l (4 l).  Written out so that no wait is
+// placed before an unrelated LDS access; whoever uses the data waits for vmcnt(0) and a barrier.
+template <int BYTES>
+__device__ __forceinline__ void lds_direct(const float *src, const float *dst) {
+  const uint32_t off = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(const __attribute__((address_space(3))) float *)dst);
+  if constexpr (BYTES == 16) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(off), "v"(src) : "memory");
+  else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" :: "s"(off), "v"(src) : "memory");
+}
+// every memory operation of this wavefront has completed, then the workgroup meets
+__device__ __forceinline__ void full_sync() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+template <int CTRL>
+__device__ __forceinline__ float dpp_of(float x) { return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, true)); }
+
+// Sums over the 64 lanes of N = 4 or 8 values at once.  Exchanges across lane ^ 1 and lane ^ 2 (and lane ^ 32 for N = 8)
+// halve the number of values, so the whole takes about 17 (27) instructions instead of N times twenty.
+// Lane l receives the sum of value (l & 3), for N = 8 of value (l & 3) + 4 (l / 32).
+template <int N>
+__device__ __forceinline__ float row_sums(const float (&v)[N], int lane) {
+  const bool o1 = lane & 1, o2 = lane & 2;
+  float a[N / 2], b[N / 4];
+#pragma unroll
+  for (int i = 0; i < N / 2; ++i) a[i] = (o1 ? v[2 * i + 1] : v[2 * i]) + dpp_of<0xB1>(o1 ? v[2 * i] : v[2 * i + 1]);
+#pragma unroll
+  for (int i = 0; i < N / 4; ++i) {
+    b[i] = (o2 ? a[2 * i + 1] : a[2 * i]) + dpp_of<0x4E>(o2 ? a[2 * i] : a[2 * i + 1]);
+    b[i] = dpp_add<0x124>(b[i]);
+    b[i] = dpp_add<0x128>(b[i]);
   }
-  __syncthreads();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");   // acquire: drop stale cached lines
+  // rows of 16 lanes: halves of the wavefront, then pairs of rows
+  const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(b[0]), __float_as_uint(b[N / 4 - 1]), false, false);
+  const float c = __uint_as_float(h[0]) + __uint_as_float(h[1]);
+  const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(c), __float_as_uint(c), false, false);
+  return __uint_as_float(q[0]) + __uint_as_float(q[1]);
 }
 
-// grid = M workgroups of kBlock threads; dynamic LDS: the server's vectors and theta - theta_ref (7 p floats), r, dr,
-// row offsets (B each) and the worker's whole minibatch (B p floats): the rows are fetched once, with every
-// load independent of the others, and both passes over them run from LDS
-__global__ __launch_bounds__(kBlock) void k_small(const SmallLaunch launch) {
+// Dynamic LDS, in floats: x [B][ps]; theta, theta_lo, h, vhat, theta - theta_ref [5][ps]; CADA: reference point [2][ps];
+// dts: [2][ps]; parts of the gradient pass [groups - 1][2][ps]; r, dr [2][B rounded up to 4]; next rows [B].
+__host__ __device__ inline size_t small_floats(int ps, int B, int rule, int groups, int dts) {
+  const bool cada = rule == CADA_RULE_CADA1 || rule == CADA_RULE_CADA2;
+  return (size_t)B * ps + (size_t)(5 + (cada ? 2 : 0) + (dts ? 2 : 0) + 2 * (groups - 1)) * ps + 2 * (size_t)((B + 3) & ~3) + B;
+}
+
+template <bool ONE>
+__device__ __forceinline__ void small_body(const SmallArgs &a, const uint32_t *state /* a.s in memory */, const SmallVar &v, int64_t n_steps) {
   extern __shared__ __align__(16) unsigned char small_smem[];
-  SmallArgs a = launch.n_rep ? *launch.rep[blockIdx.y] : launch.one;
-  if (launch.n_rep) {
-    const SmallVar &v = launch.var[blockIdx.y];
-    a.idx = v.idx; a.replay = v.replay; a.s.k = v.k; a.bar_base = v.bar_base; a.n_steps = launch.n_steps;
-  }
-  DevState s = a.s;
-  const int p = (int)s.p, B = s.B, M = s.M;
-  float *th_s = reinterpret_cast<float *>(small_smem);     // [p] theta, [p] theta_lo, [p] h, [p] vhat: this workgroup's copies
-  float *tl_s = th_s + p, *h_s = tl_s + p, *vh_s = h_s + p;
-  float *sn_s = vh_s + p, *snl_s = sn_s + p;               // [p] each: CADA1's snapshot
-  float *d_s = snl_s + p;                                  // [p] theta - theta_ref
-  float *r_s = d_s + p;                                    // [B]
-  float *dr_s = r_s + B;                                   // [B]
-  long long *row_s = reinterpret_cast<long long *>(dr_s + B + ((7 * p + 2 * B) & 1));   // [B], 8-byte aligned
-  long long *row_n = row_s + B;                            // [B] rows of the NEXT step's minibatch (row numbers)
-  const size_t x_off = ((size_t)(reinterpret_cast<unsigned char *>(row_n + B) - small_smem) + 15) & ~(size_t)15;
-  float *x_s = reinterpret_cast<float *>(small_smem + x_off);        // [B][p] the minibatch, 16-byte aligned
-  // rows and columns are moved four floats at a time when every row starts on a 16-byte boundary
-  const bool v4 = (p & 3) == 0 && (reinterpret_cast<uintptr_t>(s.X) & 15) == 0;
-  __shared__ float red[4];
-  __shared__ double redd[kBlock];
-  __shared__ float bcast[2];
+  const DevState &s = a.s;
+  const int p = (int)s.p, ps = a.ps, B = s.B, M = s.M, B4 = (s.B + 3) & ~3, nq = ps >> 2, rule = s.rule;
+  const bool cada = rule == CADA_RULE_CADA1 || rule == CADA_RULE_CADA2, lds_stored = a.dts != 0;
+  float *x_s = reinterpret_cast<float *>(small_smem);      // [B][ps] the minibatch
+  float *th_s = x_s + (size_t)B * ps, *tl_s = th_s + ps, *h_s = tl_s + ps, *vh_s = h_s + ps;   // this workgroup's copies
+  float *d_s = vh_s + ps;                                  // theta - theta_ref
+  float *rf_s = d_s + ps, *rfl_s = rf_s + ps;              // the reference point (CADA rules)
+  float *dt_s = d_s + (cada ? 3 : 1) * ps;                 // [2][ps] indexed like the store in memory
+  float *part_s = dt_s + (lds_stored ? 2 : 0) * ps;        // [groups - 1][2][ps]
+  float *r_s = part_s + 2 * (a.groups - 1) * ps, *dr_s = r_s + B4;      // [B4] residuals (before: labels) and differences
+  int32_t *row_n = reinterpret_cast<int32_t *>(dr_s + B4);              // [B] rows of the minibatch to fetch next
+  __shared__ float red_l[S_NW], red_q[S_NW];   // per wavefront: left-hand side, squared step
+  __shared__ double rhs_s;
+  __shared__ float newest_s;
+  __shared__ unsigned long long last_s;
   __shared__ float ring_s[CADA_MAX_DMAX];      // the squared steps, kept up to date by every workgroup for itself
   __shared__ unsigned char dk_s[256];          // the workers' buffer selectors after this step's decisions (M <= CUs <= 256)
 
+  // Where the state lies, for what is touched once per step: read from LDS when it is needed.  Kept in scalar registers,
+  // of which there are 100, the pointers pushed each other out all over the kernel.
+  __shared__ DevState at;
+
   const int m = blockIdx.x, nb = gridDim.x;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t mp = (int64_t)M * s.p;
   const float invB = 1.0f / (float)B;
   bool dead = false;
-  // What only this workgroup changes during the launch -- its worker's delay and buffer selector -- and what every
-  // workgroup can keep up to date by itself -- the ring of squared steps -- is read from memory once: a step is a
-  // chain of dependent memory round trips, and each one taken off it is a microsecond.
   int32_t tau_m = s.tau[m];
   int cur = s.sel[m];
   const int64_t base = s.row_off[m], n_m = s.row_off[m + 1] - base;
-  for (int j = tid; j < s.d_max; j += kBlock) ring_s[j] = s.ring[j];
-  for (int j = tid; j < p; j += kBlock) {
-    th_s[j] = s.theta[j]; tl_s[j] = s.theta_lo[j]; h_s[j] = s.h[j]; vh_s[j] = s.vhat[j];
-    if (s.rule == CADA_RULE_CADA1) { sn_s[j] = s.snap[j]; snl_s[j] = s.snap_lo[j]; }
-  }
-  uint32_t *dec = a.bar + 64;                  // [2][M] {tag, selector after the decision} of step k in slot k mod 2
-  // the squared step of the iteration before this launch: partial sums that the launch before (or cada_set_state) left
-  float newest_c = 0.f;
-  {
-    double acc = 0.0;
-    if (s.k > 0)
-      for (int i = tid; i < s.n_ring_part; i += kBlock) acc += (double)s.ring_part[i];
-    redd[tid] = acc;
-    __syncthreads();
-    for (int o = kBlock / 2; o > 0; o >>= 1) {
-      if (tid < o) redd[tid] += redd[tid + o];
-      __syncthreads();
-    }
-    newest_c = (float)redd[0];
-  }
-
-  // The next step's rows and labels are asked for while this workgroup waits at the barrier (LDS-direct loads: no
-  // registers, and the buffers they land in are free by then), so only the first step of a launch fetches its own.
-  bool have_rows = false;
-  constexpr int NW = kBlock / kWave, RB = 8;
-  for (int64_t step = 0; step < a.n_steps; ++step) {
-    const int64_t k = s.k + step;
-    const bool more = step + 1 < a.n_steps;
-    // ------------------------------------------------------------ phase A
-    if (s.rule == CADA_RULE_CADA2) {           // theta^{k - tau}: written a barrier ago at the latest (tau >= 1)
-      const RefPtr ref = theta_ref_at(s, tau_m, k);
-      for (int j = tid; j < p; j += kBlock) d_s[j] = (th_s[j] - ref.hi[j]) + (tl_s[j] - ref.lo[j]);
-    } else if (s.rule == CADA_RULE_CADA1) {
-      for (int j = tid; j < p; j += kBlock) d_s[j] = (th_s[j] - sn_s[j]) + (tl_s[j] - snl_s[j]);
-    } else {
-      for (int j = tid; j < p; j += kBlock) d_s[j] = 0.f;
-    }
-    const int32_t *idx = a.idx + (step * M + m) * (int64_t)B;
-    for (int b = tid; b < B; b += kBlock) {
-      if (!have_rows) {
-        int64_t r = idx[b];
-        if (r < 0 || r >= n_m) { atomicOr(s.err, 1u); r = r < 0 ? 0 : n_m - 1; }
-        row_s[b] = (base + r) * s.p;
-      }
-      if (more) {
-        int64_t r = idx[(int64_t)M * B + b];
-        if (r < 0 || r >= n_m) { atomicOr(s.err, 1u); r = r < 0 ? 0 : n_m - 1; }
-        row_n[b] = base + r;
-      }
-    }
-    __syncthreads();
-    // the rows: wavefront w fetches rows w, w+4, ..., eight rows at a time so that eight loads per
-    // lane are in flight (no division per element; every load independent of the others)
-    if (!have_rows) {
-    for (int b0 = w; b0 < B; b0 += NW * RB) {
-      const float *src[RB];
-#pragma unroll
-      for (int q = 0; q < RB; ++q) src[q] = s.X + row_s[min(b0 + NW * q, B - 1)];      // (a row past the end repeats the last one and is dropped)
-      if (v4) {
-#pragma unroll 2
-        for (int j = lane * 4; j < p; j += 4 * kWave) {
-          float4 v[RB];
-#pragma unroll
-          for (int q = 0; q < RB; ++q) v[q] = *reinterpret_cast<const float4 *>(src[q] + j);
-#pragma unroll
-          for (int q = 0; q < RB; ++q)
-            if (b0 + NW * q < B) *reinterpret_cast<float4 *>(x_s + (b0 + NW * q) * p + j) = v[q];
-        }
+  const int32_t *idx = v.idx + (int64_t)m * B;
+  const bool x16 = (p & 3) == 0 && (reinterpret_cast<uintptr_t>(s.X) & 15) == 0;
+  auto put_row = [&](int b, int64_t r) __attribute__((always_inline)) {
+    if (r < 0 || r >= n_m) { atomicOr(s.err, 1u); r = r < 0 ? 0 : n_m - 1; }
+    row_n[b] = (int32_t)r;
+  };
+  // asks for the rows and labels row_n names; wavefronts w0 .. S_NW - 1 share them
+  auto fetch = [&](int w0) __attribute__((always_inline)) {
+    const int n = S_NW - w0;
+    for (int b = w - w0; b < B; b += n) {
+      const float *src = s.X + (base + __builtin_amdgcn_readfirstlane(row_n[b])) * s.p;
+      float *dst = x_s + (size_t)b * ps;
+      if (x16) {
+        for (int j0 = 0; j0 < p; j0 += 4 * kWave)
+          if (j0 + lane * 4 < p) lds_direct<16>(src + j0 + lane * 4, dst + j0);
       } else {
-#pragma unroll 2
-        for (int j = lane; j < p; j += kWave) {
-          float v[RB];
-#pragma unroll
-          for (int q = 0; q < RB; ++q) v[q] = src[q][j];
-#pragma unroll
-          for (int q = 0; q < RB; ++q)
-            if (b0 + NW * q < B) x_s[(b0 + NW * q) * p + j] = v[q];
-        }
+        for (int j0 = 0; j0 < p; j0 += kWave)
+          if (j0 + lane < p) lds_direct<4>(src + j0 + lane, dst + j0);
       }
     }
-    if (tid < B) r_s[tid] = static_cast<const float *>(s.y)[row_s[tid] / s.p];     // the labels, for now
-    for (int b = kBlock + tid; b < B; b += kBlock) r_s[b] = static_cast<const float *>(s.y)[row_s[b] / s.p];
+    for (int b0 = (w - w0) * kWave; b0 < B; b0 += n * kWave)
+      if (b0 + lane < B) lds_direct<4>(static_cast<const float *>(s.y) + base + row_n[b0 + lane], r_s + b0);
+  };
+  // Everything the start needs is asked for before anything is waited for; only the rows depend on their indices.
+  const RefPtr ref = theta_ref_at(s, tau_m, v.k);
+  const float *stored = (rule == CADA_RULE_CADA1 ? s.dtl : s.gbuf) + (int64_t)cur * mp + (int64_t)m * s.p;
+  const int32_t idx0 = tid < B ? idx[tid] : 0;
+  const uint32_t state0 = tid < (int)(sizeof(DevState) / 4) ? state[tid] : 0u;
+  const float ring0 = tid < s.d_max ? s.ring[tid] : 0.f, part0 = tid == 0 && v.k > 0 ? s.ring_part[0] : 0.f;   // (part0: the squared step of the iteration before this launch)
+  auto put_vectors = [&](int j, float th, float tl, float hh, float vh, float rf, float rl, float st) __attribute__((always_inline)) {
+    th_s[j] = th; tl_s[j] = tl; h_s[j] = hh; vh_s[j] = vh;
+    d_s[j] = cada ? (th - rf) + (tl - rl) : 0.f;
+    if (cada) { rf_s[j] = rf; rfl_s[j] = rl; }
+    if (lds_stored) { dt_s[cur * ps + j] = st; dt_s[(cur ^ 1) * ps + j] = 0.f; }
+  };
+  const int j0 = min(tid, p - 1);
+  const float th0 = s.theta[j0], tl0 = s.theta_lo[j0], h0 = s.h[j0], vh0 = s.vhat[j0];
+  const float rf0 = cada ? ref.hi[j0] : 0.f, rl0 = cada ? ref.lo[j0] : 0.f, st0 = lds_stored ? stored[j0] : 0.f;
+  if (tid < B) put_row(tid, idx0);
+  for (int b = tid + S_NT; b < B; b += S_NT) put_row(b, idx[b]);
+  lds_sync();
+  fetch(0);
+  // under the rows' latency: the vectors, the ring, zeros in the padding (x, r, dr)
+  if (tid < (int)(sizeof(DevState) / 4)) reinterpret_cast<uint32_t *>(&at)[tid] = state0;
+  if (tid < s.d_max) ring_s[tid] = ring0;
+  for (int j = tid + S_NT; j < s.d_max; j += S_NT) ring_s[j] = s.ring[j];
+  if (tid < S_NW) red_q[tid] = part0;
+  if (tid < p) put_vectors(tid, th0, tl0, h0, vh0, rf0, rl0, st0);
+  for (int j = tid + S_NT; j < p; j += S_NT)
+    put_vectors(j, s.theta[j], s.theta_lo[j], s.h[j], s.vhat[j], cada ? ref.hi[j] : 0.f, cada ? ref.lo[j] : 0.f, lds_stored ? stored[j] : 0.f);
+  if (tid < ps - p) put_vectors(p + tid, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f);
+  for (int i = tid; i < B * (ps - p); i += S_NT) x_s[(i / (ps - p)) * ps + p + i % (ps - p)] = 0.f;
+  if (tid < B4 - B) { r_s[B + tid] = 0.f; dr_s[B + tid] = 0.f; }
+  uint32_t *dec = a.bar + 64;
+  const __amdgpu_buffer_rsrc_t store = far_buffer(s.gbuf, 2 * mp);
+  // gradient pass: with several row groups thread tid has column quad tid % nq and the rows of group tid / nq
+  const int G = a.groups, Bg = G > 1 ? ((B + G - 1) / G + 3) & ~3 : B4;
+  const int gg = G > 1 ? tid / nq : 0, c_first = tid - gg * nq;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+
+  for (int64_t step = 0; step < n_steps; ++step) {
+    const int64_t k = v.k + step;
+    const bool more = !ONE && step + 1 < n_steps;
+    lds_sync();            // (the wavefronts waited for the rows before they came here)
+    int32_t nidx = 0;
+    if (more && tid < B) nidx = idx[(step + 1) * (int64_t)M * B + tid];
+    // right-hand side: the squared step of iteration k-1 is this workgroup's own sum of the step before
+    if (tid == S_NT - kWave) {
+      float newest = red_q[0];
+#pragma unroll
+      for (int i = 1; i < S_NW; ++i) newest += red_q[i];
+      if (k > 0) ring_s[(k - 1) % s.d_max] = newest;
+      double sum = 0.0;
+#pragma unroll 4
+      for (int j = 0; j < s.d_max; ++j) sum += (double)ring_s[j];
+      rhs_s = (s.c / (double)s.d_max) * sum;
+      newest_s = newest;
     }
-    __syncthreads();
-    // rows over the wavefronts, RP at a time per wavefront (their 2 RP reductions overlap; RP = 8 for more than 16
-    // rows, so that 32 rows are one pass): z = x.theta, dz = x.d, then the residual and its difference
+    // ------------------------------------------------------------ phase A
+    // rows over the wavefronts, RP at a time: z = x.theta, dz = x.d, then the residual and its difference
     auto products = [&](auto RPc) __attribute__((always_inline)) {
       constexpr int RP = decltype(RPc)::value;
-      for (int b0 = w; b0 < B; b0 += RP * NW) {
+      for (int b0 = w; b0 < B; b0 += RP * S_NW) {
+        float zd[2 * RP];
         const float *x[RP];
-        float z[RP], dz[RP];
 #pragma unroll
-        for (int q = 0; q < RP; ++q) { z[q] = 0.f; dz[q] = 0.f; x[q] = x_s + min(b0 + q * NW, B - 1) * p; }   // (a row past the end repeats the last one and is dropped)
-        if (v4) {
-          for (int j = lane * 4; j < p; j += 4 * kWave) {
-            const float4 th = *reinterpret_cast<const float4 *>(th_s + j), dd = *reinterpret_cast<const float4 *>(d_s + j);
+        for (int q = 0; q < RP; ++q) { zd[2 * q] = zd[2 * q + 1] = 0.f; x[q] = x_s + min(b0 + q * S_NW, B - 1) * ps; }   // (a row past the end repeats the last one and is dropped)
+#pragma unroll 2
+        for (int j = lane * 4; j < ps; j += 4 * kWave) {
+          const float4 th = *reinterpret_cast<const float4 *>(th_s + j), dd = *reinterpret_cast<const float4 *>(d_s + j);
 #pragma unroll
-            for (int q = 0; q < RP; ++q) {
-              const float4 xv = *reinterpret_cast<const float4 *>(x[q] + j);
-              z[q] = fmaf(xv.x, th.x, z[q]); z[q] = fmaf(xv.y, th.y, z[q]); z[q] = fmaf(xv.z, th.z, z[q]); z[q] = fmaf(xv.w, th.w, z[q]);
-              dz[q] = fmaf(xv.x, dd.x, dz[q]); dz[q] = fmaf(xv.y, dd.y, dz[q]); dz[q] = fmaf(xv.z, dd.z, dz[q]); dz[q] = fmaf(xv.w, dd.w, dz[q]);
-            }
-          }
-        } else {
-          for (int j = lane; j < p; j += kWave) {
-            const float th = th_s[j], dd = d_s[j];
-#pragma unroll
-            for (int q = 0; q < RP; ++q) {
-              const float xv = x[q][j];
-              z[q] = fmaf(xv, th, z[q]);
-              dz[q] = fmaf(xv, dd, dz[q]);
-            }
+          for (int q = 0; q < RP; ++q) {
+            const float4 xv = *reinterpret_cast<const float4 *>(x[q] + j);
+            zd[2 * q] = fmaf(xv.x, th.x, zd[2 * q]); zd[2 * q] = fmaf(xv.y, th.y, zd[2 * q]);
+            zd[2 * q] = fmaf(xv.z, th.z, zd[2 * q]); zd[2 * q] = fmaf(xv.w, th.w, zd[2 * q]);
+            zd[2 * q + 1] = fmaf(xv.x, dd.x, zd[2 * q + 1]); zd[2 * q + 1] = fmaf(xv.y, dd.y, zd[2 * q + 1]);
+            zd[2 * q + 1] = fmaf(xv.z, dd.z, zd[2 * q + 1]); zd[2 * q + 1] = fmaf(xv.w, dd.w, zd[2 * q + 1]);
           }
         }
-#pragma unroll
-        for (int q = 0; q < RP; ++q) { z[q] = wave_sum_dpp(z[q]); dz[q] = wave_sum_dpp(dz[q]); }
-        {   // lane q takes row q of the RP (every lane holds all the sums): the exponentials of RP rows side by side
-          float zq = z[0], dq = dz[0];
-#pragma unroll
-          for (int q = 1; q < RP; ++q) { zq = lane == q ? z[q] : zq; dq = lane == q ? dz[q] : dq; }
-          const int b = b0 + lane * NW;
-          if (lane < RP && b < B) {
-            const float y = r_s[b];
-            const float aa = -y * zq, bb = aa + y * dq;
-            const float sa = sigmoid_s(aa);
-            r_s[b] = -y * sa * invB;
-            dr_s[b] = y * sa * sigmoid_s(-bb) * expm1f(y * dq) * invB;
-          }
+        // value 2 q of a lane is z of row q, value 2 q + 1 its dz: even lanes hold z, odd lanes dz, of the row below
+        const float mine = row_sums<2 * RP>(zd, lane), other = dpp_of<0xB1>(mine);
+        const bool odd = lane & 1;
+        const int b = b0 + S_NW * (((lane >> 1) & 1) + (RP == 4 ? 2 * (lane >> 5) : 0));
+        const float z = odd ? other : mine, dz = odd ? mine : other;
+        const float y = r_s[min(b, B - 1)];
+        const float aa = -y * z, bb = aa + y * dz;
+        const float sg = sigmoid_s(odd ? -bb : aa);            // even lanes sigma(aa), odd lanes sigma(-bb)
+        const float so = dpp_of<0xB1>(sg), em = expm1f(y * dz);
+        if ((lane & (RP == 4 ? 0x1d : 0x3d)) == 0 && b < B) {
+          r_s[b] = -y * sg * invB;
+          dr_s[b] = y * sg * so * em * invB;
         }
       }
     };
-    if (B > 16) products(std::integral_constant<int, 8>{}); else products(std::integral_constant<int, 4>{});
-    __syncthreads();
-    // columns over the threads: fresh gradient, innovation, the rule's left-hand side
-    float *gf = s.gbuf + (int64_t)(1 - cur) * mp + (int64_t)m * s.p;
-    const float *gs = s.gbuf + (int64_t)cur * mp + (int64_t)m * s.p;
+    if (B > 2 * S_NW) products(std::integral_constant<int, 4>{}); else products(std::integral_constant<int, 2>{});
+    lds_sync();
+    // columns over the threads, four each: fresh gradient, innovation, the rule's left-hand side
+    const uint32_t gf_off = (uint32_t)(((int64_t)(1 - cur) * mp + (int64_t)m * s.p) * 4);
     float sq = 0.f;
-    if (v4) {
-      for (int j = tid * 4; j < p; j += 4 * kBlock) {
-        float g[4] = {0.f, 0.f, 0.f, 0.f}, iv[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 8
-        for (int b = 0; b < B; ++b) {
-          const float4 xv = *reinterpret_cast<const float4 *>(x_s + b * p + j);
-          const float rb = r_s[b], db = dr_s[b];
-          g[0] = fmaf(rb, xv.x, g[0]); g[1] = fmaf(rb, xv.y, g[1]); g[2] = fmaf(rb, xv.z, g[2]); g[3] = fmaf(rb, xv.w, g[3]);
-          iv[0] = fmaf(db, xv.x, iv[0]); iv[1] = fmaf(db, xv.y, iv[1]); iv[2] = fmaf(db, xv.z, iv[2]); iv[3] = fmaf(db, xv.w, iv[3]);
-        }
-        float st[4] = {0.f, 0.f, 0.f, 0.f};
-        const int64_t o = (int64_t)m * s.p + j;
-        if (s.rule == CADA_RULE_CADA1) {
-          const float4 t = *reinterpret_cast<const float4 *>(s.dtl + (int64_t)cur * mp + o);
-          st[0] = t.x; st[1] = t.y; st[2] = t.z; st[3] = t.w;
-        } else if (s.rule != CADA_RULE_CADA2) {
-          const float4 t = *reinterpret_cast<const float4 *>(gs + j);
-          st[0] = t.x; st[1] = t.y; st[2] = t.z; st[3] = t.w;
-        }
+    auto accumulate = [&](int j, v4s &g, v4s &iv) __attribute__((always_inline)) {      // this thread's rows of columns j .. j + 3
+      const int b1 = min(B, (gg + 1) * Bg);
+#pragma unroll 2
+      for (int b = gg * Bg; b < b1; b += 4) {
+        const float4 r4 = *reinterpret_cast<const float4 *>(r_s + b), d4 = *reinterpret_cast<const float4 *>(dr_s + b);   // (zero past B)
+        const float rr[4] = {r4.x, r4.y, r4.z, r4.w}, dd[4] = {d4.x, d4.y, d4.z, d4.w};
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          g[q] = fmaf(s.lam, th_s[j + q], g[q]);
-          iv[q] = fmaf(s.lam, d_s[j + q], iv[q]);
-          float lhs_term = iv[q];
-          if (s.rule == CADA_RULE_CADA1) lhs_term = iv[q] - st[q];
-          else if (s.rule != CADA_RULE_CADA2) lhs_term = g[q] - st[q];          // condition (LAGrule): against the stored gradient
-          sq = fmaf(lhs_term, lhs_term, sq);
+        for (int e = 0; e < 4; ++e) {
+          const v4s xv = *reinterpret_cast<const v4s *>(x_s + min(b + e, B - 1) * ps + j);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) { g[u] = fmaf(rr[e], xv[u], g[u]); iv[u] = fmaf(dd[e], xv[u], iv[u]); }
         }
-        if (s.rule == CADA_RULE_CADA1) *reinterpret_cast<float4 *>(s.dtl + (int64_t)(1 - cur) * mp + o) = make_float4(iv[0], iv[1], iv[2], iv[3]);
-        *reinterpret_cast<float4 *>(gf + j) = make_float4(g[0], g[1], g[2], g[3]);
       }
-    } else
-    for (int j = tid; j < p; j += kBlock) {
-      float g = 0.f, iv = 0.f;
-      for (int b = 0; b < B; ++b) {
-        const float xv = x_s[b * p + j];
-        g = fmaf(r_s[b], xv, g);
-        iv = fmaf(dr_s[b], xv, iv);
+    };
+    auto finish = [&](int j, v4s g, v4s iv) __attribute__((always_inline)) {
+      const int64_t o = (int64_t)m * s.p + j;
+      v4s st = {0.f, 0.f, 0.f, 0.f};
+      if (rule != CADA_RULE_CADA2) {
+        if (lds_stored) {
+          st = *reinterpret_cast<const v4s *>(dt_s + cur * ps + j);
+        } else {
+          const float *q = (rule == CADA_RULE_CADA1 ? s.dtl : s.gbuf) + (int64_t)cur * mp + o;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) if (j + e < p) st[e] = q[e];
+        }
       }
-      g = fmaf(s.lam, th_s[j], g);
-      iv = fmaf(s.lam, d_s[j], iv);
-      float lhs_term = iv;
-      if (s.rule == CADA_RULE_CADA1) {
-        const int64_t o = (int64_t)m * s.p + j;
-        s.dtl[(int64_t)(1 - cur) * mp + o] = iv;
-        lhs_term = iv - s.dtl[(int64_t)cur * mp + o];
-      } else if (s.rule != CADA_RULE_CADA2) {
-        lhs_term = g - gs[j];                 // condition (LAGrule): against the stored gradient
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        g[e] = fmaf(s.lam, th_s[j + e], g[e]);
+        iv[e] = fmaf(s.lam, d_s[j + e], iv[e]);
+        float lhs_term = iv[e];
+        if (rule == CADA_RULE_CADA1) lhs_term = iv[e] - st[e];
+        else if (rule != CADA_RULE_CADA2) lhs_term = g[e] - st[e];          // condition (LAGrule): against the stored gradient
+        sq = fmaf(lhs_term, lhs_term, sq);                                   // (the padding past p is zero throughout)
       }
-      gf[j] = g;
-      sq = fmaf(lhs_term, lhs_term, sq);
-    }
-    const float lhs = block_sum_lds(sq, red);
-    // right-hand side: the squared step of iteration k-1 is this workgroup's own sum of the step before
-    if (tid == 0) {
-      const int last = k > 0 ? (int)((k - 1) % s.d_max) : -1;
-      const float newest = newest_c;
-      double sum = 0.0;
-      if (last >= 0) ring_s[last] = newest;
-      for (int j = 0; j < s.d_max; ++j) sum += (double)ring_s[j];
-      const double rhs = (s.c / (double)s.d_max) * sum;
-      const int32_t tau = tau_m;
-      const bool own = (s.rule == CADA_RULE_ALWAYS) || ((double)lhs > rhs) || (tau >= s.D);
-      bool up = own;
-      const uint8_t *replay = a.replay ? a.replay + step * M : nullptr;
-      if (replay != nullptr && replay[m] != CADA_REPLAY_FREE) up = replay[m] != 0;
-      if (k < s.trace_steps) {
-        const int64_t o = k * M + m;
-        s.t_mask[o] = up ? 1 : 0;
-        s.t_own[o] = own ? 1 : 0;
-        s.t_lhs[o] = lhs;
-        s.t_tau[o] = tau;
-        if (m == 0) s.t_rhs[k] = (float)rhs;
-      }
-      s.lhs[m] = lhs;
-      s.mask[m] = up ? 1 : 0;
-      if (up) {
-        s.tau[m] = 1;
-        s.sel[m] = cur ^ 1;
-        atomicAdd(reinterpret_cast<unsigned long long *>(s.uploads), 1ull);
+      if (j + 4 <= p) {
+        store_far(store, (uint32_t)j * 4u, gf_off, g);
+        if (rule == CADA_RULE_CADA1) *reinterpret_cast<v4u *>(s.dtl + (int64_t)(1 - cur) * mp + o) = iv;
       } else {
-        s.tau[m] = tau + 1;
-        if (s.rule == CADA_RULE_CADA2 && tau >= s.D) atomicOr(s.err, 8u);   // (a replay mask outlasting the retained iterates)
+        for (int e = 0; j + e < p; ++e) {
+          __hip_atomic_store(s.gbuf + (int64_t)(1 - cur) * mp + o + e, g[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if (rule == CADA_RULE_CADA1) s.dtl[(int64_t)(1 - cur) * mp + o + e] = iv[e];
+        }
       }
-      bcast[0] = newest;
-      bcast[1] = up ? 1.f : 0.f;
+      if (lds_stored) *reinterpret_cast<v4s *>(dt_s + (cur ^ 1) * ps + j) = rule == CADA_RULE_CADA1 ? iv : g;
+    };
+    if (G > 1) {             // (nq G <= S_NT: one quad per thread)
+      v4s g = {0.f, 0.f, 0.f, 0.f}, iv = {0.f, 0.f, 0.f, 0.f};
+      const int j = c_first * 4;
+      if (gg < G) accumulate(j, g, iv);
+      if (gg > 0 && gg < G) {
+        *reinterpret_cast<v4s *>(part_s + (gg - 1) * 2 * ps + j) = g;
+        *reinterpret_cast<v4s *>(part_s + (gg - 1) * 2 * ps + ps + j) = iv;
+      }
+      lds_sync();
+      if (gg == 0) {
+        for (int q = 0; q < G - 1; ++q) {
+          g += *reinterpret_cast<const v4s *>(part_s + q * 2 * ps + j);
+          iv += *reinterpret_cast<const v4s *>(part_s + q * 2 * ps + ps + j);
+        }
+        finish(j, g, iv);
+      }
+    } else {
+      for (int j = tid * 4; j < ps; j += 4 * S_NT) {
+        v4s g = {0.f, 0.f, 0.f, 0.f}, iv = {0.f, 0.f, 0.f, 0.f};
+        accumulate(j, g, iv);
+        finish(j, g, iv);
+      }
+    }
+    sq = wave_sum_dpp(sq);
+    if (lane == 0) red_l[w] = sq;
+    if (more) {
+      if (tid < B) put_row(tid, nidx);
+      for (int b = tid + S_NT; b < B; b += S_NT) put_row(b, idx[(step + 1) * (int64_t)M * B + b]);
+    }
+    full_sync();           // the gradient's stores have reached the coherence point
+    if (w == 0) {
+      // the decision, by every lane of the first wavefront alike
+      float lhs = red_l[0];
+#pragma unroll
+      for (int i = 1; i < S_NW; ++i) lhs += red_l[i];
+      const double rhs = rhs_s;
+      const bool own = (rule == CADA_RULE_ALWAYS) || ((double)lhs > rhs) || (tau_m >= s.D);
+      bool up = own;
+      const uint8_t *replay = v.replay ? v.replay + step * M : nullptr;
+      if (replay != nullptr && replay[m] != CADA_REPLAY_FREE) up = replay[m] != 0;
+      const int sel = up ? cur ^ 1 : cur;
+      if constexpr (ONE) {
+        // who is last?  Up to 56 workers the decisions travel with the count.
+        unsigned long long *cnt = reinterpret_cast<unsigned long long *>(a.bar);
+        if (lane == 0) {
+          unsigned long long inc = 1ull << 56;
+          if (M <= 56) {
+            inc |= (unsigned long long)sel << m;
+          } else {
+            __hip_atomic_store(at.sel + m, sel, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+          }
+          // (counts past 255 wrap: M <= 256, and the last of 256 sees 255 before it adds)
+          const unsigned long long seen = __hip_atomic_fetch_add(cnt, inc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          last_s = (seen >> 56) == (unsigned long long)(M - 1) ? ((seen + inc) & ((1ull << 56) - 1)) | (1ull << 63) : 0ull;
+        }
+      } else {
+        const uint32_t tag = ((v.bar_base + (uint32_t)step) & 0x3fffffffu) + 1u;      // (bar_base advances by n_steps M >= n_steps per launch)
+        uint32_t *words = dec + (k & 1) * M;
+        if (lane == 0) __hip_atomic_store(words + m, (tag << 1) | (uint32_t)sel, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int m0 = 0; m0 < M; m0 += kWave) {
+          const int mm = m0 + lane;
+          uint32_t word = 0, spins = 0;
+          for (;;) {
+            if (mm < M) word = __hip_atomic_load(words + mm, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const bool ok = mm >= M || (word >> 1) == tag;
+            if (dead || __all(ok)) break;
+            if (++spins > a.spin_limit) { dead = true; if (lane == 0) atomicOr(at.err, 2u); break; }    // (the whole wavefront: spins is uniform)
+            __builtin_amdgcn_s_sleep(1);
+          }
+          if (mm < M) dk_s[mm] = mm == m ? (unsigned char)sel : (unsigned char)(word & 1u);
+        }
+      }
+      if (lane == 0) {      // the books (after the publication, which nothing should delay)
+        if (k < at.trace_steps) {
+          const int64_t o = k * M + m;
+          at.t_mask[o] = up ? 1 : 0;
+          at.t_own[o] = own ? 1 : 0;
+          at.t_lhs[o] = lhs;
+          at.t_tau[o] = tau_m;
+          if (m == 0) at.t_rhs[k] = (float)rhs;
+        }
+        at.lhs[m] = lhs;
+        at.mask[m] = up ? 1 : 0;
+        at.tau[m] = up ? 1 : tau_m + 1;
+        if (!ONE || M <= 56) at.sel[m] = sel;
+        if (up) atomicAdd(reinterpret_cast<unsigned long long *>(at.uploads), 1ull);
+        else if (rule == CADA_RULE_CADA2 && tau_m >= s.D) atomicOr(at.err, 8u);   // (a replay mask outlasting the retained iterates)
+      }
+    } else if (more) {
+      fetch(1);            // (x_s and r_s were last read by the gradient pass)
     }
     lds_sync();
-    if (bcast[1] != 0.f) { tau_m = 1; cur ^= 1; } else tau_m += 1;
-    const uint32_t tag = ((a.bar_base + (uint32_t)step) & 0x3fffffffu) + 1u;      // (bar_base advances by n_steps M >= n_steps per launch)
-    decision_barrier(a, dec + (k & 1) * M, M, m, tag, cur, dk_s, dead, [&]() __attribute__((always_inline)) {
-      if (!more) return;
-      // (x_s and r_s were last read by the gradient pass, several workgroup barriers ago)
-      for (int b = w; b < B; b += NW) {
-        const float *src = s.X + row_n[b] * s.p;
-        float *dst = x_s + (size_t)b * p;
-        if (v4) {
-          for (int j0 = 0; j0 < p; j0 += 4 * kWave)
-            if (j0 + lane * 4 < p) __builtin_amdgcn_global_load_lds(src + j0 + lane * 4, (__attribute__((address_space(3))) void *)(dst + j0), 16, 0, 0);
-        } else {
-          for (int j0 = 0; j0 < p; j0 += kWave)
-            if (j0 + lane < p) __builtin_amdgcn_global_load_lds(src + j0 + lane, (__attribute__((address_space(3))) void *)(dst + j0), 4, 0, 0);
-        }
-      }
-      for (int b0 = w * kWave; b0 < B; b0 += NW * kWave)
-        if (b0 + lane < B)
-          __builtin_amdgcn_global_load_lds(static_cast<const float *>(s.y) + row_n[b0 + lane],
-                                           (__attribute__((address_space(3))) void *)(r_s + b0), 4, 0, 0);
-    });
-    have_rows = more;
+    if constexpr (ONE) {
+      const unsigned long long last = last_s;
+      if (last == 0ull) return;
+      if (tid == 0) __hip_atomic_store(reinterpret_cast<unsigned long long *>(a.bar), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      for (int mm = tid; mm < M; mm += S_NT)
+        dk_s[mm] = M <= 56 ? (unsigned char)((last >> mm) & 1) : (unsigned char)__hip_atomic_load(at.sel + mm, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      lds_sync();
+    }
+    const bool up_m = (int)dk_s[m] != cur;
+    if (up_m) { tau_m = 1; cur ^= 1; } else tau_m += 1;
     // ------------------------------------------------------------ phase B
-    if (m == 0 && tid == 0 && k > 0) s.ring[(k - 1) % s.d_max] = bcast[0];   // (for the world outside: every workgroup has its own copy)
+    if ((ONE || m == 0) && tid == 0 && k > 0) at.ring[(k - 1) % s.d_max] = newest_s;   // (for the world outside: every workgroup has its own copy)
     float sqs = 0.f;
     const float alpha = stepsize(s, k);
-    const unsigned char *dk = dk_s;
-    const bool snap_now = s.rule == CADA_RULE_CADA1 && (k + 1) % s.D == 0;
-    // one coordinate: this workgroup's copies of the server's vectors, and its share of the results in memory
-    auto update = [&](int j, float nab) __attribute__((always_inline)) {
-      nab = nab / (float)M;
+    const bool snap_now = rule == CADA_RULE_CADA1 && (k + 1) % s.D == 0;
+    // the decisions as bits of scalar registers, 64 workers each (M <= 256)
+    unsigned long long sel64[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) sel64[i] = 64 * i < M ? __ballot(dk_s[64 * i + lane] != 0) : 0ull;
+    const uint32_t mp4 = (uint32_t)mp * 4u, p4 = (uint32_t)p * 4u;
+    for (int j = tid * 4; j < ps; j += 4 * S_NT) {
+      // The aggregate: the sum over the workers in their order, NG rows asked for before the first is added.  A quad that
+      // reaches past p reads up to three floats of what follows the row and drops them.
+      v4s nab = {0.f, 0.f, 0.f, 0.f};
+      auto aggregate = [&](auto NGc) __attribute__((always_inline)) {
+        constexpr int NG = decltype(NGc)::value;
+        for (int m0 = 0; m0 < M; m0 += NG) {
+          const unsigned long long s64 = m0 < 64 ? sel64[0] : m0 < 128 ? sel64[1] : m0 < 192 ? sel64[2] : sel64[3];
+          uint32_t bits = __builtin_amdgcn_readfirstlane((uint32_t)(s64 >> (m0 & 63)));
+          asm volatile("" : "+s"(bits));       // (the rows' offsets are formed here, not kept in registers across the loop)
+          v4s g[NG];
+#pragma unroll
+          for (int q = 0; q < NG; ++q) {
+            const int qq = min(q, M - 1 - m0);       // (past the last worker: its row again, dropped)
+            g[q] = load_far(store, (uint32_t)j * 4u, ((bits >> qq) & 1u) * mp4 + (uint32_t)(m0 + qq) * p4);
+          }
+#pragma unroll
+          for (int q = 0; q < NG; ++q)
+            if (m0 + q < M) nab += g[q];
+        }
+      };
+      if (M <= 8) aggregate(std::integral_constant<int, 8>{});
+      else if (M <= 16) aggregate(std::integral_constant<int, 16>{});
+      else aggregate(std::integral_constant<int, 32>{});
+      *reinterpret_cast<v4s *>(d_s + j) = nab;               // (theta - theta_ref has been used: the sums take its place for a moment)
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // (the next minibatch, asked for before, is in LDS too)
+    lds_sync();
+    // The update, one coordinate per thread: four per thread, as the aggregate has them, are four square roots and eight divisions one after
+    // the other, and four times the code, which the first step of a launch fetches from memory.
+    for (int j = tid; j < p; j += S_NT) {
+      const float nab = d_s[j] / (float)M;
       float hh = h_s[j], vh = vh_s[j], vv = vh, stp;
       if (s.server_sgd) {
         stp = alpha * nab;
@@ -401,75 +494,76 @@ __global__ __launch_bounds__(kBlock) void k_small(const SmallLaunch launch) {
         stp = alpha * hh / sqrtf(s.eps + vh);
       }
       // (theta, theta_lo) - step in two-float arithmetic (TwoSum, then renormalise)
-      const float t0 = th_s[j], ms = -stp;
+      const float t0 = th_s[j], l0 = tl_s[j], ms = -stp;
       const float sum = t0 + ms;
       const float bb = sum - t0;
       const float er = (t0 - (sum - bb)) + (ms - bb);
-      const float lo = tl_s[j] + er;
+      const float lo = l0 + er;
       const float th = sum + lo, tl = lo - (th - sum);
+      sqs = fmaf(stp, stp, sqs);
       h_s[j] = hh; vh_s[j] = vh; th_s[j] = th; tl_s[j] = tl;
-      if (snap_now) { sn_s[j] = th; snl_s[j] = tl; }
-      if ((j / kBlock) % nb == m) {
-        s.nabla[j] = nab; s.h[j] = hh; s.v[j] = vv; s.vhat[j] = vh; s.theta[j] = th; s.theta_lo[j] = tl;
-        if (s.rule == CADA_RULE_CADA2) {
-          s.hist[((k + 1) % s.R) * s.p + j] = th;
-          s.hist_lo[((k + 1) % s.R) * s.p + j] = tl;
+      if (cada) {
+        float rf = rf_s[j], rl = rfl_s[j];
+        if (rule == CADA_RULE_CADA2 ? up_m : snap_now) {     // CADA2: theta^k is the next reference point; CADA1: theta^{k+1} the snapshot
+          rf = rule == CADA_RULE_CADA2 ? t0 : th; rl = rule == CADA_RULE_CADA2 ? l0 : tl;
+          rf_s[j] = rf; rfl_s[j] = rl;
+        }
+        d_s[j] = (th - rf) + (tl - rl);
+      } else {
+        d_s[j] = 0.f;
+      }
+      if (ONE || (j / 256) % nb == m) {
+        at.nabla[j] = nab; at.h[j] = hh; at.v[j] = vv; at.vhat[j] = vh; at.theta[j] = th; at.theta_lo[j] = tl;
+        if (rule == CADA_RULE_CADA2) {      // (read by other workgroups of this launch below)
+          const int64_t o = ((k + 1) % s.R) * s.p + j;
+          __hip_atomic_store(at.hist + o, th, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          __hip_atomic_store(at.hist_lo + o, tl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         } else if (snap_now) {
-          s.snap[j] = th;
-          s.snap_lo[j] = tl;
+          at.snap[j] = th; at.snap_lo[j] = tl;
         }
       }
-      sqs = fmaf(stp, stp, sqs);
-    };
-    // The aggregate: every load of a thread is independent of the others (the selectors are one cheap read for all),
-    // four coordinates per 16-byte load where the rows allow it; the sum runs over the workers in their order.
-    if (v4) {
-      // (NG workers' rows asked for before the first is added: the sum is a chain of memory round trips otherwise;
-      // 16 at a time, 32 when there are more workers than 16)
-      auto aggregate = [&](auto NGc) __attribute__((always_inline)) {
-        constexpr int NG = decltype(NGc)::value;
-        for (int j = tid * 4; j < p; j += 4 * kBlock) {
-          float4 nab = make_float4(0.f, 0.f, 0.f, 0.f);
-          for (int m0 = 0; m0 < M; m0 += NG) {
-            float4 g[NG];
-#pragma unroll
-            for (int q = 0; q < NG; ++q) {
-              const int mm = min(m0 + q, M - 1);
-              g[q] = *reinterpret_cast<const float4 *>(s.gbuf + (int64_t)dk[mm] * mp + (int64_t)mm * s.p + j);
-            }
-#pragma unroll
-            for (int q = 0; q < NG; ++q)
-              if (m0 + q < M) { nab.x += g[q].x; nab.y += g[q].y; nab.z += g[q].z; nab.w += g[q].w; }
-          }
-          update(j, nab.x); update(j + 1, nab.y); update(j + 2, nab.z); update(j + 3, nab.w);
-        }
-      };
-      if (M > 16) aggregate(std::integral_constant<int, 32>{}); else aggregate(std::integral_constant<int, 16>{});
-    } else {
-      auto aggregate = [&](auto NGc) __attribute__((always_inline)) {
-        constexpr int NG = decltype(NGc)::value;
-        for (int j = tid; j < p; j += kBlock) {
-          float nab = 0.f;
-          for (int m0 = 0; m0 < M; m0 += NG) {
-            float g[NG];
-#pragma unroll
-            for (int q = 0; q < NG; ++q) {
-              const int mm = min(m0 + q, M - 1);
-              g[q] = s.gbuf[(int64_t)dk[mm] * mp + (int64_t)mm * s.p + j];
-            }
-#pragma unroll
-            for (int q = 0; q < NG; ++q)
-              if (m0 + q < M) nab += g[q];
-          }
-          update(j, nab);
-        }
-      };
-      if (M > 16) aggregate(std::integral_constant<int, 32>{}); else aggregate(std::integral_constant<int, 16>{});
     }
-    newest_c = block_sum_lds(sqs, red);          // (ends with a workgroup barrier: the next phase A sees the new copies)
-    if (tid == 0) s.ring_part[m] = m == 0 ? newest_c : 0.f;     // what a later launch, or reading the state out, adds up
+    for (int j = p + tid; j < ps; j += S_NT) d_s[j] = 0.f;   // (the padding keeps its zeros)
+    sqs = wave_sum_dpp(sqs);
+    if (lane == 0) red_q[w] = sqs;
+    if (more && rule == CADA_RULE_CADA2 && tau_m > s.D) {
+      // only a replay mask does this: the worker's reference point has left the retained iterates and the
+      // oldest of them, theta^{k + 1 - D}, stands for it (written D steps ago; with D = 1 by the step before)
+      full_sync();
+      const RefPtr ref = theta_ref_at(at, tau_m, k + 1);
+      for (int j = tid; j < p; j += S_NT) {
+        const float rf = __hip_atomic_load(ref.hi + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const float rl = __hip_atomic_load(ref.lo + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        rf_s[j] = rf; rfl_s[j] = rl;
+        d_s[j] = (th_s[j] - rf) + (tl_s[j] - rl);
+      }
+    }
+  }
+  // what a later launch, or reading the state out, adds up (the other entries of ring_part stay zero)
+  lds_sync();
+  if (tid == 0 && (ONE || m == 0)) {
+    float newest = red_q[0];
+#pragma unroll
+    for (int i = 1; i < S_NW; ++i) newest += red_q[i];
+    at.ring_part[0] = newest;
   }
 }
+
+// grid (M, runs)
+__global__ __launch_bounds__(S_NT) void k_small(const SmallLaunch launch) {
+  // (constant address space: scalar loads, so that the compiler knows the values to be the same in all lanes)
+  constexpr int n = sizeof(SmallArgs) / 8;
+  const auto *src = (const __attribute__((address_space(4))) uint64_t *)(uintptr_t)launch.rep[blockIdx.y];
+  uint64_t words[n];
+#pragma unroll
+  for (int i = 0; i < n; ++i) words[i] = src[i];
+  SmallArgs a;
+  __builtin_memcpy(&a, words, sizeof(a));
+  small_body<false>(a, reinterpret_cast<const uint32_t *>(&launch.rep[blockIdx.y]->s), launch.var[blockIdx.y], launch.n_steps);
+}
+
+// grid M
+__global__ __launch_bounds__(S_NT) void k_small_one(const SmallArgs a, const SmallVar v) { small_body<true>(a, reinterpret_cast<const uint32_t *>(&a.s), v, 1); }
 
 // Whether the multi-step kernel serves this configuration; sets the ring-partial count it uses.
 bool small_plan(Ctx *c, const cada_config *cfg) {
@@ -487,12 +581,22 @@ bool small_plan(Ctx *c, const cada_config *cfg) {
   if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess || !coop) return false;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) return false;
   if (M > cus) return false;
-  c->small_lds = (size_t)(7 * p + 2 * B + 1) * sizeof(float) + (size_t)2 * B * sizeof(long long) + 16 + (size_t)B * p * sizeof(float);
-  if (c->small_lds > 150 * 1024) return false;      // the minibatch of a worker and the server's vectors must fit in LDS
-  if (hipFuncSetAttribute(reinterpret_cast<const void *>(k_small), hipFuncAttributeMaxDynamicSharedMemorySize, (int)c->small_lds) != hipSuccess) {
-    (void)hipGetLastError();
-    return false;
-  }
+  const int ps = (int)((p + 3) / 4 * 4);
+  // the minibatch of a worker and the server's vectors must fit in LDS ...
+  constexpr size_t kRoom = 154 * 1024;
+  if (small_floats(ps, B, cfg->rule, 1, 0) * sizeof(float) > kRoom) return false;
+  // ... the stored innovation or gradient where it also does, and the parts of as many row groups of the gradient pass as
+  // threads are left for (of at least eight rows each)
+  c->small_dts = cfg->rule != CADA_RULE_CADA2 && small_floats(ps, B, cfg->rule, 1, 1) * sizeof(float) <= kRoom ? 1 : 0;
+  c->small_groups = 8;
+  while (c->small_groups > 1 && (ps / 4 * c->small_groups > S_NT || (B + c->small_groups - 1) / c->small_groups < 8 ||
+                                 small_floats(ps, B, cfg->rule, c->small_groups, c->small_dts) * sizeof(float) > kRoom)) c->small_groups /= 2;
+  c->small_lds = small_floats(ps, B, cfg->rule, c->small_groups, c->small_dts) * sizeof(float);
+  for (const void *fn : {reinterpret_cast<const void *>(k_small), reinterpret_cast<const void *>(k_small_one)})
+    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRoom) != hipSuccess) {
+      (void)hipGetLastError();
+      return false;
+    }
   c->small = 1;
   c->small_plain_launch = cfg->plain_launch != 0 ? 1 : 0;
   return true;
@@ -500,20 +604,18 @@ bool small_plan(Ctx *c, const cada_config *cfg) {
 
 constexpr uint32_t kSmallSpinLimit = 4000000u;
 
-static SmallArgs small_args_of(Ctx *c, const int32_t *idx, const uint8_t *replay, int64_t n_steps) {
+static SmallArgs small_args_of(Ctx *c) {
   SmallArgs a;
   a.s = c->s;
-  a.s.k = c->k;
-  a.idx = idx;
-  a.replay = replay;
-  a.n_steps = n_steps;
   a.bar = c->small_bar;
-  a.bar_base = c->small_seq;
   a.spin_limit = kSmallSpinLimit;
+  a.ps = (int)((c->s.p + 3) / 4 * 4);
+  a.groups = c->small_groups;
+  a.dts = c->small_dts;
   return a;
 }
 
-// Writes the launch-invariant arguments of this context into its workspace (for replica launches).
+// Writes the launch-invariant arguments of this context into its workspace (for the launches of several steps).
 // The source is host memory that lives as long as the context.
 int small_publish_args(Ctx *c) {
   if (!c->small) return CADA_OK;
@@ -521,7 +623,7 @@ int small_publish_args(Ctx *c) {
     c->small_args_host = new (std::nothrow) unsigned char[sizeof(SmallArgs)];
     if (!c->small_args_host) { set_error("out of host memory"); return CADA_EINVAL; }
   }
-  const SmallArgs a = small_args_of(c, nullptr, nullptr, 0);
+  const SmallArgs a = small_args_of(c);
   memcpy(c->small_args_host, &a, sizeof(a));
   const hipError_t e = hipMemcpyAsync(c->small_args, c->small_args_host, sizeof(SmallArgs), hipMemcpyHostToDevice, c->stream);
   if (e != hipSuccess) { set_error("copy of launch arguments failed: %s", hipGetErrorString(e)); return CADA_EHIP; }
@@ -542,7 +644,6 @@ int small_steps_replicas(Ctx *const *cs, int n, const int32_t *const *idx, const
   }
   if ((int64_t)n * c0->s.M > cus) { set_error("n_replicas x M = %lld workgroups exceed the %d CUs that must hold them at once", (long long)n * c0->s.M, cus); return CADA_EINVAL; }
   SmallLaunch l{};
-  l.n_rep = n;
   l.n_steps = n_steps;
   for (int r = 0; r < n; ++r) {
     l.rep[r] = static_cast<const SmallArgs *>(cs[r]->small_args);
@@ -550,7 +651,7 @@ int small_steps_replicas(Ctx *const *cs, int n, const int32_t *const *idx, const
   }
   void *args[] = {&l};
   prof_mark(c0);
-  const hipError_t e = hipLaunchCooperativeKernel(reinterpret_cast<const void *>(k_small), dim3((unsigned)c0->s.M, (unsigned)n), dim3(kBlock), args,
+  const hipError_t e = hipLaunchCooperativeKernel(reinterpret_cast<const void *>(k_small), dim3((unsigned)c0->s.M, (unsigned)n), dim3(S_NT), args,
                                                   (unsigned)c0->small_lds, c0->stream);
   prof_mark(c0);
   if (e != hipSuccess) {
@@ -563,16 +664,27 @@ int small_steps_replicas(Ctx *const *cs, int n, const int32_t *const *idx, const
 }
 
 int small_steps(Ctx *c, const int32_t *idx, const uint8_t *replay, int64_t n_steps) {
+  if (n_steps == 1) {
+    prof_mark(c);
+    hipLaunchKernelGGL(k_small_one, dim3((unsigned)c->s.M), dim3(S_NT), c->small_lds, c->stream, small_args_of(c),
+                       SmallVar{idx, replay, c->k, 0u});
+    prof_mark(c);
+    const hipError_t e1 = hipGetLastError();
+    if (e1 != hipSuccess) { set_error("single-step logistic launch failed: %s", hipGetErrorString(e1)); return CADA_EHIP; }
+    return CADA_OK;
+  }
   SmallLaunch l{};
-  l.one = small_args_of(c, idx, replay, n_steps);
+  l.n_steps = n_steps;
+  l.rep[0] = static_cast<const SmallArgs *>(c->small_args);
+  l.var[0] = SmallVar{idx, replay, c->k, c->small_seq};
   void *args[] = {&l};
   prof_mark(c);
   hipError_t e;
-  if (c->small_plain_launch) {      // (at most as many workgroups of 256 threads as CUs: all resident at once on an idle device)
-    hipLaunchKernelGGL(k_small, dim3((unsigned)c->s.M), dim3(kBlock), c->small_lds, c->stream, l);
+  if (c->small_plain_launch) {      // (at most as many workgroups as CUs: all resident at once on an idle device)
+    hipLaunchKernelGGL(k_small, dim3((unsigned)c->s.M), dim3(S_NT), c->small_lds, c->stream, l);
     e = hipGetLastError();
   } else {
-    e = hipLaunchCooperativeKernel(reinterpret_cast<const void *>(k_small), dim3((unsigned)c->s.M), dim3(kBlock), args,
+    e = hipLaunchCooperativeKernel(reinterpret_cast<const void *>(k_small), dim3((unsigned)c->s.M), dim3(S_NT), args,
                                    (unsigned)c->small_lds, c->stream);
   }
   prof_mark(c);
