@@ -157,13 +157,16 @@ void carve_common(Carver &w, const cada_config *cfg, const Geometry &g, DevState
   int32_t *eval_idx = w.take<int32_t>(M * (size_t)cfg->B);
   float *zpart = nullptr;
   unsigned long long *post = nullptr;
-  float *tail = nullptr;
+  float *tail = nullptr, *rows_part = nullptr;
+  uint32_t *rows_count = nullptr;
   uint32_t *small_bar = nullptr;
   unsigned char *small_args = nullptr;
   if (cfg->model == CADA_MODEL_LOGREG) {
     zpart = w.take<float>(M * (size_t)cfg->B * (size_t)g.n_col_chunks * 2);
     post = w.take<unsigned long long>(kFusedPostWords);
     if (cfg->p >= 8192 && cfg->p % 4 == 0) tail = w.take<float>(kFusedTailFloatsPerP * (size_t)cfg->p);   // (shapes the single-pass kernel serves)
+    rows_part = w.take<float>(rows_part_floats(cfg));
+    rows_count = w.take<uint32_t>(1 + M);
     small_bar = w.take<uint32_t>(64 + 2 * M);      // (a cache line kept free,) then the tagged decision words of the last two steps [2][M]
     small_args = w.take<unsigned char>(kSmallArgsBytes);
   }
@@ -171,6 +174,8 @@ void carve_common(Carver &w, const cada_config *cfg, const Geometry &g, DevState
   c->fused_post = post;
   c->fused_tail = tail;
   c->eval_part = eval_part; c->eval_acc = eval_acc; c->eval_idx = eval_idx;
+  c->rows_part = rows_part;
+  c->rows_count = rows_count;
   c->small_bar = small_bar;
   c->small_args = small_args;
   s->theta = theta; s->theta_lo = theta_lo; s->hist_lo = hist_lo; s->snap_lo = snap_lo; s->h = h; s->v = v; s->vhat = vhat; s->nabla = nabla;
@@ -377,7 +382,9 @@ int cada_init(const cada_config *cfg, const float *theta0, cada_ctx **out) {
     if (cfg->path == CADA_PATH_WHOLE_STEPS && small_plan(c, cfg)) s.n_ring_part = cfg->M;
     else if (cfg->path != CADA_PATH_TWO_PASS && fused_plan(c, cfg)) s.n_lhs_part = kFusedWaves * c->fused_Q;
     else if (cfg->path == CADA_PATH_AUTO && small_plan(c, cfg)) s.n_ring_part = cfg->M;
-    if (c->small) {
+    if (!c->small && !c->fused && rows_plan(c, cfg)) {
+      c->n_phases = c->rows_server ? 1 : 2; c->phase_names[0] = "logreg_rows"; c->phase_names[1] = "server_update";
+    } else if (c->small) {
       c->n_phases = 1; c->phase_names[0] = "logreg_whole_steps";
     } else if (c->fused && c->fused_tail_f > 0) {
       c->n_phases = 4; c->phase_names[0] = "logreg_single_pass"; c->phase_names[1] = "logreg_split_round_sum";
@@ -442,6 +449,11 @@ int cada_step(cada_ctx *ctx, const int32_t *idx, const uint8_t *replay) {
     const int rs = small_steps(c, idx, replay, 1);
     if (rs == CADA_OK) c->k += 1;
     return rs;
+  }
+  if (c->rows) {
+    const int rr = logreg_step_rows(c, idx, replay);
+    if (rr == CADA_OK) c->k += 1;
+    return rr;
   }
   int rc = (c->model != CADA_MODEL_LOGREG) ? mlp_gradients(c, idx)
            : (c->fused ? logreg_gradients_fused(c, idx) : logreg_gradients(c, idx));

@@ -132,6 +132,21 @@ __device__ __forceinline__ float wave_sum_dpp(float v) {
   return (r0 + r1) + (r2 + r3);
 }
 
+template <int CTRL>
+__device__ __forceinline__ double dpp_add_f64(double x) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xF, 0xF, true), hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xF, 0xF, true);
+  return x + __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double lane_f64(double x, int lane) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, x);
+  return __builtin_bit_cast(double, ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane));
+}
+__device__ __forceinline__ double wave_sum_f64(double v) {
+  v = dpp_add_f64<0xB1>(v); v = dpp_add_f64<0x4E>(v); v = dpp_add_f64<0x124>(v); v = dpp_add_f64<0x128>(v);
+  return (lane_f64(v, 0) + lane_f64(v, 16)) + (lane_f64(v, 32) + lane_f64(v, 48));
+}
+
 // Workgroup barrier for data that is exchanged through LDS: it waits for this wavefront's LDS operations only, not, as
 // __syncthreads() does, for the acknowledgement of every global store issued before it (a microsecond each time).
 // Data that a thread loaded from memory and passes on through LDS is waited for where it is written to LDS.
@@ -146,7 +161,86 @@ __device__ __forceinline__ float block_sum_lds(float x, float *red /* [4] LDS */
   return (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-struct LogregLaunch;   // defined in cada_logreg.hip
+template <int CTRL>
+__device__ __forceinline__ float dpp_of(float x) { return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, true)); }
+
+// Sums over the 64 lanes of N = 4, 8 or 16 values at once.  Exchanges across lane ^ 1 and lane ^ 2 (N >= 8: and between the halves of
+// the wavefront; N = 16: and between neighbouring rows of 16 lanes) halve the number of values, so that the
+// whole takes about 17, 27 or 47 instructions instead of N times twenty.  Lane l receives the sum of value
+// row_sums_index(l); row_sums_lane(v) is one lane that holds value v, row_sums_owner() the lanes that hold each value once.
+template <int N>
+__device__ __forceinline__ float row_sums(const float (&v)[N], int lane) {
+  static_assert(N == 4 || N == 8 || N == 16, "");
+  const bool o1 = lane & 1, o2 = lane & 2;
+  float a[N / 2], b[N / 4];
+#pragma unroll
+  for (int i = 0; i < N / 2; ++i) a[i] = (o1 ? v[2 * i + 1] : v[2 * i]) + dpp_of<0xB1>(o1 ? v[2 * i] : v[2 * i + 1]);
+#pragma unroll
+  for (int i = 0; i < N / 4; ++i) {
+    b[i] = (o2 ? a[2 * i + 1] : a[2 * i]) + dpp_of<0x4E>(o2 ? a[2 * i] : a[2 * i + 1]);
+    b[i] = dpp_add<0x124>(b[i]);
+    b[i] = dpp_add<0x128>(b[i]);
+  }
+  // the swap leaves (x.low, y.low) and (x.high, y.high): their sum is x's in the lower and y's in the upper lanes
+  auto halves = [](float x, float y) __attribute__((always_inline)) {
+    const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return __uint_as_float(h[0]) + __uint_as_float(h[1]);
+  };
+  auto rows = [](float x, float y) __attribute__((always_inline)) {
+    const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return __uint_as_float(q[0]) + __uint_as_float(q[1]);
+  };
+  if constexpr (N == 4) { const float c = halves(b[0], b[0]); return rows(c, c); }
+  else if constexpr (N == 8) { const float c = halves(b[0], b[1]); return rows(c, c); }
+  else return rows(halves(b[0], b[1]), halves(b[2], b[3]));
+}
+template <int N> __host__ __device__ constexpr int row_sums_index(int lane) {
+  return (lane & 3) + (N >= 8 ? 4 * (lane >> 5) : 0) + (N == 16 ? 8 * ((lane >> 4) & 1) : 0);
+}
+template <int N> __host__ __device__ constexpr int row_sums_lane(int v) { return (v & 3) + ((v & 4) ? 32 : 0) + ((v & 8) ? 16 : 0); }
+template <int N> __host__ __device__ constexpr bool row_sums_owner(int lane) { return (lane & ((N < 16 ? 16 : 0) | (N < 8 ? 32 : 0) | 12)) == 0; }
+
+typedef float v4s __attribute__((ext_vector_type(4)));
+typedef float v4u __attribute__((ext_vector_type(4), aligned(4)));     // four floats at any 4-byte aligned address
+
+// Four floats to / from the coherence point of the device, past the XCD's own cache: buffer accesses with the device-scope bit (sc1), since
+// device-scope accesses exist in the language for four bytes only.  What lies past the buffer's end reads as zero.
+constexpr int kFar = 16;
+typedef uint32_t u4s __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t far_buffer(float *p, int64_t floats) {
+  return __builtin_amdgcn_make_buffer_rsrc(p, 0, (int)(floats * 4), 0x00020000);
+}
+__device__ __forceinline__ void store_far(__amdgpu_buffer_rsrc_t r, uint32_t byte_off, uint32_t row_off, v4s x) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4s, x), r, byte_off, row_off, kFar);
+}
+__device__ __forceinline__ v4s load_far(__amdgpu_buffer_rsrc_t r, uint32_t byte_off, uint32_t row_off) {
+  return __builtin_bit_cast(v4s, __builtin_amdgcn_raw_buffer_load_b128(r, byte_off, row_off, kFar));
+}
+// One coordinate of the server update, equations (CADA-1)-(CADA-3) or the plain SGD step: new h, vhat, v, theta (two floats);
+// returns the step.  beta*x + (1-beta)*y is written x + (1-beta)*(y - x): float32(0.999) is off by 1.3e-8 relative, which compounds
+// to 1e-5 over the ~1000-step memory of vhat, whereas float32(1-beta) enters only linearly.
+__device__ __forceinline__ float server_coordinate(const DevState &s, float alpha, float nab, float &h, float &vh, float &v, float &th, float &tl) {
+  const float vo = vh;
+  float step;
+  v = vo;
+  if (s.server_sgd) {          // theta <- theta - alpha * nabla; h, v, vhat keep their zeros
+    step = alpha * nab;
+  } else {
+    h = fmaf(s.omb1, nab - h, h);
+    v = fmaf(s.omb2, nab * nab - vo, vo);
+    vh = fmaxf(v, vo);
+    step = alpha * h / sqrtf(s.eps + vh);
+  }
+  // (theta, theta_lo) - step in two-float arithmetic (TwoSum, then renormalise)
+  const float a = th, ms = -step;
+  const float sum = a + ms;
+  const float bb = sum - a;
+  const float err = (a - (sum - bb)) + (ms - bb);
+  const float lo = tl + err;
+  th = sum + lo;
+  tl = lo - (th - sum);
+  return step;
+}
 
 // Host context.
 struct Ctx {
@@ -179,6 +273,11 @@ struct Ctx {
   uint32_t small_seq;        // its value after everything enqueued so far
   void *small_args;          // room in the workspace for this context's launch-invariant arguments (launches of several steps)
   void *small_args_host;     // their host copy (owned by the context)
+  // one or two launches per step for rows of up to 8192 columns, cada_logreg_rows.hip
+  int rows, rows_shares, rows_per_share, rows_server;
+  size_t rows_lds;
+  float *rows_part;          // sums of the shares of a worker's rows
+  uint32_t *rows_count;      // [1 + M] counters
   // full-data evaluation scratch (cada_eval)
   double *eval_part;         // [M][kEvalBlocks][2] per-block sums of (loss, correct)
   double *eval_acc;          // [M][2]
@@ -199,6 +298,10 @@ void prof_mark(Ctx *c);
 int logreg_gradients(Ctx *c, const int32_t *idx);
 bool fused_plan(Ctx *c, const cada_config *cfg);
 int logreg_gradients_fused(Ctx *c, const int32_t *idx);
+bool rows_serves(const cada_config *cfg);
+size_t rows_part_floats(const cada_config *cfg);
+bool rows_plan(Ctx *c, const cada_config *cfg);
+int logreg_step_rows(Ctx *c, const int32_t *idx, const uint8_t *replay);   // gradients, rule and server
 int small_steps(Ctx *c, const int32_t *idx, const uint8_t *replay, int64_t n_steps);
 int small_steps_replicas(Ctx *const *cs, int n, const int32_t *const *idx, const uint8_t *const *replay, int64_t n_steps);
 constexpr size_t kSmallArgsBytes = 1024;    // >= sizeof(SmallArgs), checked where it is defined
@@ -224,5 +327,6 @@ int mlp_init_state(Ctx *c, const float *theta0);
 void mlp_free(Ctx *c);
 // S3: rule, mask, tau.  S5-S7: aggregate, AMSGrad, ring push.
 int rule_and_server(Ctx *c, const uint8_t *replay);
+int server_step(Ctx *c);                    // S5-S7 alone (the rule has been evaluated)
 
 }  // namespace cada

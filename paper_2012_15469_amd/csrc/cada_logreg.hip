@@ -10,6 +10,7 @@
 // The difference of the two gradients is formed from d and dr directly: subtracting two
 // float32 gradients of nearby points would lose the digits the rule's comparison needs.
 //
+// This file: two streaming passes, for rows wider than cada_logreg_rows.hip and cada_logreg_fused.hip serve, or when asked for.
 // Pass 1 (k_dots) streams the B gathered rows once for z and dz; pass 2 (k_grad) streams
 // them again for g and innov, column-parallel, and reduces |innov|^2 (CADA2) or
 // |innov - stored innovation|^2 (CADA1) per block in a fixed order.

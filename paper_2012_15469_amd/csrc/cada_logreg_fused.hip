@@ -712,7 +712,7 @@ bool fused_plan(Ctx *c, const cada_config *cfg) {
   c->fused = 0;
   const int64_t p = cfg->p;
   const int B = cfg->B, M = cfg->M;
-  if (c->vec != 4 || p < 8192) return false;
+  if (c->vec != 4 || p < 8192 || (p == 8192 && cfg->path != CADA_PATH_SINGLE_PASS)) return false;    // (8192 columns: cada_logreg_rows.hip)
   int dev = 0, coop = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess) return false;
   if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess || !coop) return false;

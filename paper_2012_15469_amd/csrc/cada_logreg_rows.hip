@@ -1,0 +1,470 @@
+// Dual minibatch gradient, rule and (small states) server update of the logistic model for rows that one workgroup can
+// hold in its registers (p <= 8192): a step is ONE launch, or two where the state is too large for one workgroup's server
+// phase, and the rows cross the memory bus once.
+//
+// Workgroup (g, m) takes a share of worker m's minibatch rows.  The rows of a share are read into registers, many at a
+// time; z = x.theta and dz = x.d are summed over the lanes, turned into the residual and its difference (formulas as in
+// cada_logreg.hip), and the same registers are accumulated into the gradient and the innovation: no second pass.
+//   p <= 1024: a wavefront holds whole rows (WC = 1), the eight wavefronts work on rows of their own and add their sums up
+//     through LDS at the end: no workgroup barrier per row;
+//   p <= 8192: a row lies across the eight wavefronts (WC = 8), which exchange their parts of z, dz through LDS, one barrier per
+//     batch of rows, with the next batch's loads in flight across it.
+// Nothing waits for another workgroup: whoever finishes last continues.  The last workgroup of a worker adds the shares'
+// sums up in their order, forms the fresh gradient and the left-hand side; the last of those runs the rule for
+// all workers, and, where M p is small, the server update.  The partial sums, gradients and left-hand sides that are passed on
+// inside the launch are written and read at device scope (past the XCD's cache).
+//
+// Why: the path replaces four to five dependent launches (two passes over the rows, [left-hand side of the LAG rule],
+// rule, server), each about 5 us of fetching arguments, code and first operands for well under 1 us of work.
+// Measured per step, against those launches: M = 10, p = 784, B = 60: 23.8 -> 16.2 us (15.5 in the kernel: operands and indices 3.3,
+// rows 2.9, share's sums 2.6, gradient 1.5, count 0.7, rule 1.0, aggregate 2.1, update 1.3); M = 10, p = 22, B = 92, LAG:
+// 23.8 -> 13.2 us; M = 100, B = 256, p = 4000 (410 MB of rows): 147 -> 87 us; p = 8192: 308 -> 164 us (5.1 TB/s).
+#include "cada_internal.h"
+
+namespace cada {
+
+constexpr int R_NT = 512, R_NW = R_NT / kWave;
+constexpr int kRowsFusedServer = 12288, kRowsFusedWorkers = 32;      // M p and M up to here: the last workgroup also runs the server update
+
+struct RowsArgs {
+  DevState s;
+  const int32_t *idx;        // [M][B]
+  const uint8_t *replay;     // [M] or nullptr
+  float *part;               // [M][shares][2][p rounded up to 4] sums of the shares (shares > 1)
+  uint32_t *count;           // [1 + M]: workers done; shares done of each worker (zero between launches)
+  int shares;                // workgroups per worker
+  int rows;                  // rows per share
+  int server;                // run the server update in this launch
+};
+
+__device__ __forceinline__ float sigmoid_r(float a) { return 1.0f / (1.0f + expf(-a)); }
+__device__ __forceinline__ void put_far(float *p, float x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ float get_far(const float *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// Counts this workgroup in and says whether it is the last of n; called by all its threads, whose stores have then reached
+// the coherence point.  The last one resets the counter for the next launch.
+__device__ __forceinline__ bool last_of(uint32_t *count, uint32_t n, uint32_t *flag /* LDS */) {
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  if (threadIdx.x == 0) {
+    const uint32_t seen = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *flag = seen + 1 == n;
+    if (seen + 1 == n) __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  lds_sync();
+  return *flag != 0;
+}
+
+// CW: 16-byte pieces of a row per lane; WC: wavefronts a row lies across; RB: rows per batch.
+// dynamic LDS: row offsets int64 [rows], labels [rows] (rounded up to four rows), sums [R_NW / WC][2][p]
+template <int CW, int WC, int RB>
+__global__ __launch_bounds__(R_NT) void k_rows(const RowsArgs a) {
+  extern __shared__ __align__(16) unsigned char rows_smem[];
+  const DevState &s = a.s;
+  const int p = (int)s.p, ps = (p + 3) & ~3, M = s.M, m = blockIdx.y, share = blockIdx.x, rule = s.rule;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int64_t *off_s = reinterpret_cast<int64_t *>(rows_smem);
+  float *y_s = reinterpret_cast<float *>(off_s + ((a.rows + 3) & ~3));
+  float *sum_s = y_s + ((a.rows + 3) & ~3);             // [R_NW / WC][2][p rounded up to 4]
+  __shared__ float red_s[2][R_NW][2 * RB], red_l[R_NW];
+  __shared__ uint32_t flag_s, up_s;
+  constexpr int NV = 2 * RB;
+  static_assert(NV == 4 || NV == 8 || NV == 16, "row_sums");
+
+  const int r0 = share * a.rows, nr = min(a.rows, s.B - r0);        // this share's rows
+  const int64_t base = s.row_off[m], n_m = s.row_off[m + 1] - base;
+  const int64_t mp = (int64_t)M * s.p;
+  const RefPtr ref = theta_ref(s, m, s.k);
+  // this lane's columns: CW quads; the quad that would reach past p is moved back to end at p, `dup` of its columns belong
+  // to the quad before (weight zero here, not stored from here); a quad beyond p has dup >= 4
+  int jb[CW], dup[CW];
+  float th[CW][4], dd[CW][4], g[CW][4], iv[CW][4];
+#pragma unroll
+  for (int i = 0; i < CW; ++i) {
+    const int j = (((WC == 1 ? 0 : w) * CW + i) * kWave + lane) * 4;
+    jb[i] = min(j, p - 4);
+    dup[i] = j - jb[i];
+  }
+  // theta and theta - theta_ref at j .. j + 3 (up to three floats past p: of what follows in the workspace)
+  auto diff_at = [&](int j, v4u &t4, v4s &d4) __attribute__((always_inline)) {
+    t4 = *reinterpret_cast<const v4u *>(s.theta + j);
+    const v4u l4 = *reinterpret_cast<const v4u *>(s.theta_lo + j), rh = *reinterpret_cast<const v4u *>(ref.hi + j), rl = *reinterpret_cast<const v4u *>(ref.lo + j);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) d4[e] = (t4[e] - rh[e]) + (l4[e] - rl[e]);
+  };
+  // What the end of the launch needs and nobody changes before it is asked for here, so that its latency passes under the rows'.
+  int32_t tau0 = 0, sel0 = 0, rep0 = CADA_REPLAY_FREE;          // of worker tid
+  if (tid < M) {
+    tau0 = s.tau[tid]; sel0 = s.sel[tid];
+    if (a.replay != nullptr) rep0 = a.replay[tid];
+  }
+  const float ring0 = lane < s.d_max ? s.ring[lane] : 0.f, part0 = lane < s.n_ring_part ? s.ring_part[lane] : 0.f;   // (n_ring_part <= 32)
+  auto row_of = [&](int b, int32_t r0_) __attribute__((always_inline)) {
+    int64_t r = r0_;
+    if (r < 0 || r >= n_m) { atomicOr(s.err, 1u); r = r < 0 ? 0 : n_m - 1; }
+    off_s[b] = (base + r) * s.p;
+    return base + r;
+  };
+  const int32_t *idx = a.idx + (int64_t)m * s.B + r0;
+  int64_t row0 = 0;
+  const int32_t idx0 = tid < nr ? idx[tid] : 0;
+  if constexpr (WC == 1) {
+    // (every wavefront needs all of theta and the difference: fetched once for the workgroup, through the room of the sums)
+    float *d_s = sum_s + ps;
+    if (tid * 4 < ps) {                                // (p <= 1024: one quad per thread)
+      v4u t4; v4s d4;
+      diff_at(tid * 4, t4, d4);
+      *reinterpret_cast<v4s *>(sum_s + tid * 4) = t4;
+      *reinterpret_cast<v4s *>(d_s + tid * 4) = d4;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < CW; ++i) {
+      v4u t4; v4s d4;
+      diff_at(jb[i], t4, d4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { th[i][e] = e >= dup[i] ? t4[e] : 0.f; dd[i][e] = e >= dup[i] ? d4[e] : 0.f; }
+    }
+  }
+  if (tid < nr) row0 = row_of(tid, idx0);
+  for (int b = tid + R_NT; b < nr; b += R_NT) y_s[b] = static_cast<const float *>(s.y)[row_of(b, idx[b])];
+  lds_sync();
+
+  const float invB = 1.0f / (float)s.B;
+  constexpr int NG = R_NW / WC;                        // row groups: group q takes rows q, q + NG, ...
+  const int grp = WC == 1 ? w : 0;
+  v4u x[2][RB][CW];
+  auto load = [&](v4u (&xb)[RB][CW], int b0) __attribute__((always_inline)) {      // rows b0, b0 + NG, ... (past the end: the last row, with weight zero)
+#pragma unroll
+    for (int q = 0; q < RB; ++q) {
+      const int64_t o = off_s[min(b0 + q * NG, nr - 1)];
+      const float *row = s.X + (((int64_t)__builtin_amdgcn_readfirstlane((uint32_t)(o >> 32)) << 32) | __builtin_amdgcn_readfirstlane((uint32_t)o));
+#pragma unroll
+      for (int i = 0; i < CW; ++i) xb[q][i] = *reinterpret_cast<const v4u *>(row + jb[i]);
+    }
+  };
+  auto work = [&](v4u (&xb)[RB][CW], int b0, int it) __attribute__((always_inline)) {
+    float zd[NV];
+#pragma unroll
+    for (int q = 0; q < RB; ++q) {
+      zd[2 * q] = zd[2 * q + 1] = 0.f;
+#pragma unroll
+      for (int i = 0; i < CW; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { zd[2 * q] = fmaf(xb[q][i][e], th[i][e], zd[2 * q]); zd[2 * q + 1] = fmaf(xb[q][i][e], dd[i][e], zd[2 * q + 1]); }
+    }
+    float mine = row_sums<NV>(zd, lane);               // lane holds value v(lane): z of row v / 2 in even, dz in odd lanes
+    const int v = row_sums_index<NV>(lane);
+    if constexpr (WC > 1) {
+      if (row_sums_owner<NV>(lane)) red_s[it & 1][w][v] = mine;
+      lds_sync();
+      mine = 0.f;
+#pragma unroll
+      for (int i = 0; i < R_NW; ++i) mine += red_s[it & 1][i][v];
+    }
+    const float other = dpp_of<0xB1>(mine);
+    const bool odd = lane & 1;
+    const int b = b0 + (v >> 1) * NG;
+    const float z = odd ? other : mine, dz = odd ? mine : other;
+    const float y = y_s[min(b, nr - 1)];
+    const float aa = -y * z, bb = aa + y * dz;
+    const float sg = sigmoid_r(odd ? -bb : aa);        // even lanes sigma(aa), odd lanes sigma(-bb)
+    const float so = dpp_of<0xB1>(sg), em = expm1f(y * dz);
+    float r = b < nr ? (odd ? y * so * sg * em * invB : -y * sg * invB) : 0.f;      // even lanes r, odd lanes dr
+#pragma unroll
+    for (int q = 0; q < RB; ++q) {
+      const float rr = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(r), row_sums_lane<NV>(2 * q)));
+      const float dr = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(r), row_sums_lane<NV>(2 * q + 1)));
+#pragma unroll
+      for (int i = 0; i < CW; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { g[i][e] = fmaf(rr, xb[q][i][e], g[i][e]); iv[i][e] = fmaf(dr, xb[q][i][e], iv[i][e]); }
+    }
+  };
+  const int64_t k = s.k;
+  const int last = k > 0 ? (int)((k - 1) % s.d_max) : -1;
+  double rhs;
+  float newest;
+  {
+    int b = grp, it = 0;
+    if (b < nr) load(x[0], b);
+    const float label = tid < nr ? static_cast<const float *>(s.y)[row0] : 0.f;
+    // right-hand side of the rule, by every wavefront alike while its rows are on their way: the squared step of the iteration before is the sum of its blocks' parts
+    newest = k > 0 ? (float)wave_sum_f64((double)part0) : 0.f;
+    double ring_sum = lane == last ? (double)newest : (double)ring0;
+    for (int j = lane + kWave; j < s.d_max; j += kWave) ring_sum += (double)(j == last ? newest : s.ring[j]);
+    ring_sum = wave_sum_f64(ring_sum);
+    rhs = (s.c / (double)s.d_max) * ring_sum;
+#pragma unroll
+    for (int i = 0; i < CW; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if constexpr (WC == 1) {
+          th[i][e] = e >= dup[i] ? sum_s[jb[i] + e] : 0.f;
+          dd[i][e] = e >= dup[i] ? sum_s[ps + jb[i] + e] : 0.f;
+        }
+        g[i][e] = iv[i][e] = 0.f;
+      }
+    if (tid < nr) y_s[tid] = label;
+    lds_sync();
+    while (b < nr) {                                   // (WC > 1: the same trip count in every wavefront)
+      if (b + RB * NG < nr) load(x[1], b + RB * NG);
+      work(x[0], b, it);
+      b += RB * NG; ++it;
+      if (b >= nr) break;
+      if (b + RB * NG < nr) load(x[0], b + RB * NG);
+      work(x[1], b, it);
+      b += RB * NG; ++it;
+    }
+  }
+  // the sums over the share: through LDS, four columns per thread from here on.  (The last quad may reach past p: it reads
+  // up to three floats of what follows an array in the workspace and drops them.)
+#pragma unroll
+  for (int i = 0; i < CW; ++i)
+    if (dup[i] == 0) {
+      *reinterpret_cast<v4s *>(sum_s + (grp * 2) * ps + jb[i]) = v4s{g[i][0], g[i][1], g[i][2], g[i][3]};
+      *reinterpret_cast<v4s *>(sum_s + (grp * 2 + 1) * ps + jb[i]) = v4s{iv[i][0], iv[i][1], iv[i][2], iv[i][3]};
+    } else {
+#pragma unroll
+      for (int e = 1; e < 4; ++e)
+        if (e >= dup[i]) { sum_s[(grp * 2) * ps + jb[i] + e] = g[i][e]; sum_s[(grp * 2 + 1) * ps + jb[i] + e] = iv[i][e]; }
+    }
+  lds_sync();
+  auto share_sums = [&](int j, v4s &gs, v4s &is) __attribute__((always_inline)) {
+    gs = is = v4s{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int q = 0; q < NG; ++q) { gs += *reinterpret_cast<const v4s *>(sum_s + q * 2 * ps + j); is += *reinterpret_cast<const v4s *>(sum_s + (q * 2 + 1) * ps + j); }
+  };
+  const __amdgpu_buffer_rsrc_t part = far_buffer(a.part + (int64_t)m * a.shares * 2 * ps, (int64_t)a.shares * 2 * ps);
+  if (a.shares > 1) {
+    for (int j = tid * 4; j < ps; j += R_NT * 4) {
+      v4s gs, is;
+      share_sums(j, gs, is);
+      store_far(part, (uint32_t)j * 4u, (uint32_t)(share * 2 * ps) * 4u, gs);
+      store_far(part, (uint32_t)j * 4u, (uint32_t)((share * 2 + 1) * ps) * 4u, is);
+    }
+    if (!last_of(a.count + 1 + m, (uint32_t)a.shares, &flag_s)) return;
+  }
+  const int cur = s.sel[m];
+  const __amdgpu_buffer_rsrc_t fresh = far_buffer(s.gbuf + (int64_t)(1 - cur) * mp + (int64_t)m * s.p, s.p);
+  float sq = 0.f;
+  for (int j = tid * 4; j < ps; j += R_NT * 4) {
+    const int64_t o = (int64_t)m * s.p + j, of = (int64_t)(1 - cur) * mp + o, oc = (int64_t)cur * mp + o;
+    const v4u t4 = *reinterpret_cast<const v4u *>(s.theta + j), l4 = *reinterpret_cast<const v4u *>(s.theta_lo + j);
+    const v4u rh = *reinterpret_cast<const v4u *>(ref.hi + j), rl = *reinterpret_cast<const v4u *>(ref.lo + j);
+    v4u st = {0.f, 0.f, 0.f, 0.f};                     // CADA1: the stored innovation; LAG, always: the stored gradient
+    if (rule == CADA_RULE_CADA1) st = *reinterpret_cast<const v4u *>(s.dtl + oc);
+    else if (rule != CADA_RULE_CADA2) st = *reinterpret_cast<const v4u *>(s.gbuf + oc);
+    v4s gs, is;
+    if (a.shares > 1) {
+      gs = is = v4s{0.f, 0.f, 0.f, 0.f};
+      for (int q0 = 0; q0 < a.shares; q0 += 4) {
+        v4s x[4], y[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {                  // (past the last share: reads as zero)
+          x[q] = load_far(part, (uint32_t)j * 4u, (uint32_t)((q0 + q) * 2 * ps) * 4u);
+          y[q] = load_far(part, (uint32_t)j * 4u, (uint32_t)(((q0 + q) * 2 + 1) * ps) * 4u);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) { gs += x[q]; is += y[q]; }
+      }
+    } else {
+      share_sums(j, gs, is);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      gs[e] = fmaf(s.lam, t4[e], gs[e]);
+      is[e] = fmaf(s.lam, (t4[e] - rh[e]) + (l4[e] - rl[e]), is[e]);
+      const float term = rule == CADA_RULE_CADA2 ? is[e] : (rule == CADA_RULE_CADA1 ? is[e] : gs[e]) - st[e];
+      if (j + e < p) sq = fmaf(term, term, sq);
+    }
+    if (j + 4 <= p) {
+      store_far(fresh, (uint32_t)j * 4u, 0u, gs);
+      if (rule == CADA_RULE_CADA1) *reinterpret_cast<v4u *>(s.dtl + of) = is;
+    } else {
+      for (int e = 0; j + e < p; ++e) {
+        put_far(s.gbuf + of + e, gs[e]);
+        if (rule == CADA_RULE_CADA1) s.dtl[of + e] = is[e];
+      }
+    }
+  }
+  sq = wave_sum_dpp(sq);
+  if (lane == 0) red_l[w] = sq;
+  lds_sync();
+  if (tid == 0) {
+    float l = red_l[0];
+#pragma unroll
+    for (int i = 1; i < R_NW; ++i) l += red_l[i];
+    put_far(s.lhs + m, l);
+    up_s = 0u;
+  }
+  if (!last_of(a.count, (uint32_t)M, &flag_s)) return;
+
+  // ---- the rule for all workers (last workgroup of the launch)
+  uint32_t ups = 0;
+  uint8_t *sel_s = reinterpret_cast<uint8_t *>(rows_smem);       // [M], in place of what came before (every wavefront is past it)
+  for (int mm = tid; mm < M; mm += R_NT) {
+    const float lhs = get_far(s.lhs + mm);
+    const int32_t tau = mm == tid ? tau0 : s.tau[mm], was = mm == tid ? sel0 : s.sel[mm];
+    const int32_t replay = mm == tid ? rep0 : a.replay != nullptr ? (int32_t)a.replay[mm] : CADA_REPLAY_FREE;
+    const bool own = (rule == CADA_RULE_ALWAYS) || ((double)lhs > rhs) || (tau >= s.D);
+    bool up = own;
+    if (replay != CADA_REPLAY_FREE) up = replay != 0;
+    if (k < s.trace_steps) {
+      const int64_t o = k * M + mm;
+      s.t_mask[o] = up ? 1 : 0;
+      s.t_own[o] = own ? 1 : 0;
+      s.t_lhs[o] = lhs;
+      s.t_tau[o] = tau;
+    }
+    s.mask[mm] = up ? 1 : 0;
+    s.tau[mm] = up ? 1 : tau + 1;
+    const int sel = up ? was ^ 1 : was;    // an upload: the fresh row becomes the stored one
+    if (a.server) sel_s[mm] = (uint8_t)sel;
+    if (up) { s.sel[mm] = sel; ++ups; }
+    else if (rule == CADA_RULE_CADA2 && tau >= s.D) atomicOr(s.err, 8u);   // (only a replay mask can do this)
+  }
+  if (ups) atomicAdd(&up_s, ups);
+  // the server's operands, asked for before the rows of the aggregate
+  float h0[2], vh0[2], th0[2], tl0[2];
+  if (a.server) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int j = min(tid + u * R_NT, p - 1);
+      h0[u] = s.h[j]; vh0[u] = s.vhat[j]; th0[u] = s.theta[j]; tl0[u] = s.theta_lo[j];
+    }
+  }
+  lds_sync();
+  if (tid == 0) {
+    atomicAdd(reinterpret_cast<unsigned long long *>(s.uploads), (unsigned long long)up_s);
+    s.n_up[k & 1] = up_s;
+    if (last >= 0) s.ring[last] = newest;
+    if (k < s.trace_steps) s.t_rhs[k] = (float)rhs;
+  }
+  if (!a.server) return;
+
+  // ---- the server update: sums of four coordinates per thread, then one coordinate per thread (as in cada_logreg_small.hip)
+  float *nab_s = reinterpret_cast<float *>(rows_smem + ((M + 15) & ~15));      // [p rounded up to 4]
+  const __amdgpu_buffer_rsrc_t store = far_buffer(s.gbuf, 2 * mp);      // (M p <= kRowsFusedServer)
+  for (int j = tid * 4; j < ps; j += R_NT * 4) {
+    v4s nab = {0.f, 0.f, 0.f, 0.f};
+    for (int m0 = 0; m0 < M; m0 += 16) {               // sixteen rows asked for before the first is added
+      v4s v[16];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        const int mm = min(m0 + q, M - 1);
+        v[q] = load_far(store, (uint32_t)j * 4u, __builtin_amdgcn_readfirstlane((uint32_t)(((int64_t)sel_s[mm] * mp + (int64_t)mm * s.p) * 4)));
+      }
+#pragma unroll
+      for (int q = 0; q < 16; ++q)
+        if (m0 + q < M) nab += v[q];
+    }
+    *reinterpret_cast<v4s *>(nab_s + j) = nab;
+  }
+  lds_sync();
+  float sqs = 0.f;
+  for (int j = tid; j < p; j += R_NT) {
+    const float nab = nab_s[j] / (float)M;
+    const int u = j < 2 * R_NT ? j / R_NT : 2;
+    float hh, vh, vv, t, tl;
+    if (u == 0) { hh = h0[0]; vh = vh0[0]; t = th0[0]; tl = tl0[0]; }
+    else if (u == 1) { hh = h0[1]; vh = vh0[1]; t = th0[1]; tl = tl0[1]; }
+    else { hh = s.h[j]; vh = s.vhat[j]; t = s.theta[j]; tl = s.theta_lo[j]; }
+    const float step = server_coordinate(s, s.alpha, nab, hh, vh, vv, t, tl);
+    sqs = fmaf(step, step, sqs);
+    s.nabla[j] = nab; s.h[j] = hh; s.v[j] = vv; s.vhat[j] = vh; s.theta[j] = t; s.theta_lo[j] = tl;
+    if (rule == CADA_RULE_CADA2) {
+      s.hist[((k + 1) % s.R) * s.ps + j] = t;
+      s.hist_lo[((k + 1) % s.R) * s.ps + j] = tl;
+    } else if (rule == CADA_RULE_CADA1 && (k + 1) % s.D == 0) {
+      s.snap[j] = t;
+      s.snap_lo[j] = tl;
+    }
+  }
+  sqs = wave_sum_dpp(sqs);
+  lds_sync();                                          // (red_l has been read)
+  if (lane == 0) red_l[w] = sqs;
+  lds_sync();
+  if (tid < s.n_ring_part) {
+    float l = red_l[0];
+#pragma unroll
+    for (int i = 1; i < R_NW; ++i) l += red_l[i];
+    s.ring_part[tid] = tid == 0 ? l : 0.f;
+  }
+}
+
+namespace {
+using RowsKernel = void (*)(const RowsArgs);
+// the variant for rows of p columns: pieces per lane, wavefronts per row, rows per batch
+RowsKernel rows_kernel(int64_t p, int *wc) {
+  *wc = p <= 1024 ? 1 : 8;
+  if (p <= 256) return k_rows<1, 1, 8>;
+  if (p <= 512) return k_rows<2, 1, 4>;
+  if (p <= 1024) return k_rows<4, 1, 4>;
+  if (p <= 2048) return k_rows<1, 8, 8>;
+  if (p <= 4096) return k_rows<2, 8, 4>;
+  return k_rows<4, 8, 2>;
+}
+}  // namespace
+
+// Rows per share and shares per worker: as many shares as give every CU a workgroup, while a share keeps the rows of one batch of its
+// eight wavefronts (p <= 1024) or ten rows (each wavefront then has a part of every row) and 32 KB, at most eight.  Measured, us per step with
+// 1, 2, 4, 8, 16 shares: M = 10, B = 200, p = 784: 25, 21, 19, 18, 19; M = 64, B = 128, p = 784: 23, 21.5, 21, 30, 51;
+// M = 100, B = 256, p = 4000: 133, 90, 93, 111, 138; M = 10, B = 64, p = 4000: 33.5, 26.5, 22, 22 (two-pass kernels: 27, 32, 147, 25).
+static void rows_split(int M, int B, int64_t p, int *shares, int *rows) {
+  const int least = p <= 1024 ? 24 : 10;
+  const int n = max(1, min(min(8, (int)((int64_t)B * p / 8192)), min(256 / M, B / least)));
+  *rows = (B + n - 1) / n;
+  *shares = (B + *rows - 1) / *rows;
+}
+
+bool rows_serves(const cada_config *cfg) {
+  return cfg->model == CADA_MODEL_LOGREG && cfg->path != CADA_PATH_TWO_PASS && cfg->p >= 4 && cfg->p <= 8192;
+}
+size_t rows_part_floats(const cada_config *cfg) {
+  if (!rows_serves(cfg)) return 0;
+  int shares, rows;
+  rows_split(cfg->M, cfg->B, cfg->p, &shares, &rows);
+  return shares > 1 ? (size_t)cfg->M * shares * 2 * (size_t)((cfg->p + 3) / 4 * 4) : 0;
+}
+
+bool rows_plan(Ctx *c, const cada_config *cfg) {
+  c->rows = 0;
+  if (!rows_serves(cfg)) return false;
+  rows_split(cfg->M, cfg->B, cfg->p, &c->rows_shares, &c->rows_per_share);
+  c->rows_server = cfg->M <= kRowsFusedWorkers && (int64_t)cfg->M * cfg->p <= kRowsFusedServer;
+  int wc;
+  const RowsKernel fn = rows_kernel(cfg->p, &wc);
+  const size_t ps = (size_t)((cfg->p + 3) / 4 * 4), server = (size_t)((cfg->M + 15) & ~15) + ps * sizeof(float);
+  c->rows_lds = (size_t)((c->rows_per_share + 3) & ~3) * 12 + (size_t)(R_NW / wc) * 2 * ps * sizeof(float);
+  if (c->rows_server && c->rows_lds < server) c->rows_lds = server;
+  if (hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  c->rows = 1;
+  return true;
+}
+
+int logreg_step_rows(Ctx *c, const int32_t *idx, const uint8_t *replay) {
+  RowsArgs a;
+  a.s = c->s;
+  a.s.k = c->k;
+  a.s.alpha = stepsize(a.s, c->k);
+  a.idx = idx;
+  a.replay = replay;
+  a.part = c->rows_part;
+  a.count = c->rows_count;
+  a.shares = c->rows_shares;
+  a.rows = c->rows_per_share;
+  a.server = c->rows_server;
+  int wc;
+  prof_mark(c);
+  hipLaunchKernelGGL(rows_kernel(c->s.p, &wc), dim3((unsigned)a.shares, (unsigned)c->s.M), dim3(R_NT), c->rows_lds, c->stream, a);
+  prof_mark(c);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) { set_error("logistic step launch failed: %s", hipGetErrorString(e)); return CADA_EHIP; }
+  if (a.server) { c->force_resum = 0; return CADA_OK; }
+  return server_step(c);
+}
+
+}  // namespace cada

@@ -82,22 +82,6 @@ static_assert(sizeof(SmallLaunch) <= 4096, "kernel arguments");
 
 __device__ __forceinline__ float sigmoid_s(float a) { return 1.0f / (1.0f + expf(-a)); }
 
-typedef float v4s __attribute__((ext_vector_type(4)));
-typedef float v4u __attribute__((ext_vector_type(4), aligned(4)));     // four floats at any 4-byte aligned address
-
-// Four floats to / from the coherence point of the device (see above): buffer accesses with the device-scope bit (sc1), since
-// device-scope accesses exist in the language for four bytes only.  What lies past the buffer's end reads as zero.
-constexpr int kFar = 16;
-typedef uint32_t u4s __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t far_buffer(float *p, int64_t floats) {
-  return __builtin_amdgcn_make_buffer_rsrc(p, 0, (int)(floats * 4), 0x00020000);
-}
-__device__ __forceinline__ void store_far(__amdgpu_buffer_rsrc_t r, uint32_t byte_off, uint32_t row_off, v4s x) {
-  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4s, x), r, byte_off, row_off, kFar);
-}
-__device__ __forceinline__ v4s load_far(__amdgpu_buffer_rsrc_t r, uint32_t byte_off, uint32_t row_off) {
-  return __builtin_bit_cast(v4s, __builtin_amdgcn_raw_buffer_load_b128(r, byte_off, row_off, kFar));
-}
 // One LDS-direct load: lane l's 16 (4) bytes at `src` go to LDS byte `dst` + 16 l (4 l).  Written out so that no wait is
 // placed before an unrelated LDS access; whoever uses the data waits for vmcnt(0) and a barrier.
 template <int BYTES>
@@ -108,31 +92,6 @@ __device__ __forceinline__ void lds_direct(const float *src, const float *dst) {
 }
 // every memory operation of this wavefront has completed, then the workgroup meets
 __device__ __forceinline__ void full_sync() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
-template <int CTRL>
-__device__ __forceinline__ float dpp_of(float x) { return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, true)); }
-
-// Sums over the 64 lanes of N = 4 or 8 values at once.  Exchanges across lane ^ 1 and lane ^ 2 (and lane ^ 32 for N = 8)
-// halve the number of values, so the whole takes about 17 (27) instructions instead of N times twenty.
-// Lane l receives the sum of value (l & 3), for N = 8 of value (l & 3) + 4 (l / 32).
-template <int N>
-__device__ __forceinline__ float row_sums(const float (&v)[N], int lane) {
-  const bool o1 = lane & 1, o2 = lane & 2;
-  float a[N / 2], b[N / 4];
-#pragma unroll
-  for (int i = 0; i < N / 2; ++i) a[i] = (o1 ? v[2 * i + 1] : v[2 * i]) + dpp_of<0xB1>(o1 ? v[2 * i] : v[2 * i + 1]);
-#pragma unroll
-  for (int i = 0; i < N / 4; ++i) {
-    b[i] = (o2 ? a[2 * i + 1] : a[2 * i]) + dpp_of<0x4E>(o2 ? a[2 * i] : a[2 * i + 1]);
-    b[i] = dpp_add<0x124>(b[i]);
-    b[i] = dpp_add<0x128>(b[i]);
-  }
-  // rows of 16 lanes: halves of the wavefront, then pairs of rows
-  const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(b[0]), __float_as_uint(b[N / 4 - 1]), false, false);
-  const float c = __uint_as_float(h[0]) + __uint_as_float(h[1]);
-  const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(c), __float_as_uint(c), false, false);
-  return __uint_as_float(q[0]) + __uint_as_float(q[1]);
-}
 
 // Dynamic LDS, in floats: x [B][ps]; theta, theta_lo, h, vhat, theta - theta_ref [5][ps]; CADA: reference point [2][ps];
 // dts: [2][ps]; parts of the gradient pass [groups - 1][2][ps]; r, dr [2][B rounded up to 4]; next rows [B].
@@ -276,13 +235,13 @@ __device__ __forceinline__ void small_body(const SmallArgs &a, const uint32_t *s
         // value 2 q of a lane is z of row q, value 2 q + 1 its dz: even lanes hold z, odd lanes dz, of the row below
         const float mine = row_sums<2 * RP>(zd, lane), other = dpp_of<0xB1>(mine);
         const bool odd = lane & 1;
-        const int b = b0 + S_NW * (((lane >> 1) & 1) + (RP == 4 ? 2 * (lane >> 5) : 0));
+        const int b = b0 + S_NW * (row_sums_index<2 * RP>(lane) >> 1);
         const float z = odd ? other : mine, dz = odd ? mine : other;
         const float y = r_s[min(b, B - 1)];
         const float aa = -y * z, bb = aa + y * dz;
         const float sg = sigmoid_s(odd ? -bb : aa);            // even lanes sigma(aa), odd lanes sigma(-bb)
         const float so = dpp_of<0xB1>(sg), em = expm1f(y * dz);
-        if ((lane & (RP == 4 ? 0x1d : 0x3d)) == 0 && b < B) {
+        if (row_sums_owner<2 * RP>(lane) && !odd && b < B) {
           r_s[b] = -y * sg * invB;
           dr_s[b] = y * sg * so * em * invB;
         }
@@ -484,22 +443,8 @@ __device__ __forceinline__ void small_body(const SmallArgs &a, const uint32_t *s
     // the other, and four times the code, which the first step of a launch fetches from memory.
     for (int j = tid; j < p; j += S_NT) {
       const float nab = d_s[j] / (float)M;
-      float hh = h_s[j], vh = vh_s[j], vv = vh, stp;
-      if (s.server_sgd) {
-        stp = alpha * nab;
-      } else {
-        hh = fmaf(s.omb1, nab - hh, hh);
-        vv = fmaf(s.omb2, nab * nab - vh, vh);
-        vh = fmaxf(vv, vh);
-        stp = alpha * hh / sqrtf(s.eps + vh);
-      }
-      // (theta, theta_lo) - step in two-float arithmetic (TwoSum, then renormalise)
-      const float t0 = th_s[j], l0 = tl_s[j], ms = -stp;
-      const float sum = t0 + ms;
-      const float bb = sum - t0;
-      const float er = (t0 - (sum - bb)) + (ms - bb);
-      const float lo = l0 + er;
-      const float th = sum + lo, tl = lo - (th - sum);
+      float hh = h_s[j], vh = vh_s[j], vv, th = th_s[j], tl = tl_s[j];
+      const float t0 = th, l0 = tl, stp = server_coordinate(s, alpha, nab, hh, vh, vv, th, tl);
       sqs = fmaf(stp, stp, sqs);
       h_s[j] = hh; vh_s[j] = vh; th_s[j] = th; tl_s[j] = tl;
       if (cada) {
@@ -571,10 +516,10 @@ bool small_plan(Ctx *c, const cada_config *cfg) {
   const int64_t p = cfg->p;
   const int B = cfg->B, M = cfg->M;
   if (p >= 8192) return false;
-  // Measured against the two-pass kernels (four launches, about 21 us at best): 9 us against 20 us for M = 10, B = 10,
-  // p = 54; 18 against 21 us for M = 20, B = 32, p = 784; 23 against 26 us with M = 64; but 33 against 31 us with M = 128,
-  // 58 against 37 us for M = 200 tiny workers (the server phase and the barrier grow with the workers) and 29 against
-  // 28 us for B = 100 rows of p = 256: the path is taken by itself up to 64 workers of up to 64 rows.
+  // Measured against the rows path (cada_logreg_rows.hip), us per step of a 16-step run here / of a single step here / there: M = 10, B = 10,
+  // p = 54: 7 / 11.5 / 13; M = 20, B = 32, p = 784: 12 / 17 / 15; M = 64: 15 / 20 / 17; but M = 128: 21 / 26 / 19, M = 200 tiny workers 19 / 23 / 22 (the
+  // server phase and the barrier grow with the workers), B = 100 rows of p = 54: 12 / 17 / 13, B = 300: 24 / 28 / 17 (one CU
+  // has all rows of a worker): the path is taken by itself up to 64 workers of up to 64 rows.
   if (cfg->path != CADA_PATH_WHOLE_STEPS && (M > 64 || B > 64)) return false;
   int dev = 0, coop = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess) return false;

@@ -245,30 +245,9 @@ __global__ __launch_bounds__(kBlock) void k_server(const DevState s) {
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
     nab[v] = prev[v] + ((part[0][v][lane] + part[1][v][lane]) + (part[2][v][lane] + part[3][v][lane])) / fM;
-    // beta*x + (1-beta)*y written as x + (1-beta)*(y - x): float32(0.999) is off by 1.3e-8
-    // relative, which compounds to 1e-5 over the ~1000-step memory of vhat, whereas
-    // float32(1-beta) enters only linearly
-    const float ho = hh[v];
-    const float vo = vh[v];
-    float step;
-    if (s.server_sgd) {          // theta <- theta - alpha * nabla; h, v, vhat keep their zeros
-      vv[v] = vo;
-      step = s.alpha * nab[v];
-    } else {
-      hh[v] = fmaf(s.omb1, nab[v] - ho, ho);
-      vv[v] = fmaf(s.omb2, nab[v] * nab[v] - vo, vo);
-      vh[v] = fmaxf(vv[v], vo);
-      step = s.alpha * hh[v] / sqrtf(s.eps + vh[v]);
-    }
-    if (VEC == 4 && coord(v) >= s.p) step = 0.f;   // (a coordinate of the 16-byte padding past p stays as it is, also with eps = 0)
-    // (theta, theta_lo) - step in two-float arithmetic (TwoSum, then renormalise)
-    const float a = th[v], ms = -step;
-    const float sum = a + ms;
-    const float bb = sum - a;
-    const float err = (a - (sum - bb)) + (ms - bb);
-    const float lo = tl[v] + err;
-    th[v] = sum + lo;
-    tl[v] = lo - (th[v] - sum);
+    const float to = th[v], lo = tl[v];
+    const float step = server_coordinate(s, s.alpha, nab[v], hh[v], vh[v], vv[v], th[v], tl[v]);
+    if (VEC == 4 && coord(v) >= s.p) { th[v] = to; tl[v] = lo; }   // (a coordinate of the 16-byte padding past p stays as it is, also with eps = 0)
     if (coord(v) < s.p) sq = fmaf(step, step, sq);
   }
   put(s.nabla, nab); put(s.h, hh); put(s.v, vv); put(s.vhat, vh); put(s.theta, th); put(s.theta_lo, tl);
@@ -283,29 +262,37 @@ __global__ __launch_bounds__(kBlock) void k_server(const DevState s) {
   if (lane == 0) s.ring_part[blockIdx.x] = tot;
 }
 
-int rule_and_server(Ctx *c, const uint8_t *replay) {
+int server_step(Ctx *c) {
   DevState s = c->s;
   s.k = c->k;
   s.alpha = stepsize(s, s.k);
   s.resum = (c->force_resum || s.k % s.D == 0) ? 1 : 0;
-  if (s.rule == CADA_RULE_LAG || s.rule == CADA_RULE_ALWAYS) {   // (the always-upload rule only records it)
-    const int nb = (int)min((int64_t)s.n_lhs_part, (s.p + 4 * kBlock - 1) / (4 * kBlock));
-    hipLaunchKernelGGL(k_lag_lhs, dim3((unsigned)max(nb, 1), (unsigned)s.M), dim3(kBlock), 0, c->stream, s);
-  }
-  hipLaunchKernelGGL(k_rule, dim3((unsigned)((s.M + 3) / 4)), dim3(kBlock), 0, c->stream, s, replay);
-  prof_mark(c);
   if (c->vec == 4)
     hipLaunchKernelGGL(k_server<4>, dim3(s.n_ring_part), dim3(kBlock), 0, c->stream, s);
   else
     hipLaunchKernelGGL(k_server<1>, dim3(s.n_ring_part), dim3(kBlock), 0, c->stream, s);
   prof_mark(c);
   const hipError_t e = hipGetLastError();
-  if (e != hipSuccess) {
-    set_error("rule/server launch failed: %s", hipGetErrorString(e));
-    return CADA_EHIP;
-  }
+  if (e != hipSuccess) { set_error("server launch failed: %s", hipGetErrorString(e)); return CADA_EHIP; }
   c->force_resum = 0;
   return CADA_OK;
+}
+
+int rule_and_server(Ctx *c, const uint8_t *replay) {
+  DevState s = c->s;
+  s.k = c->k;
+  if (s.rule == CADA_RULE_LAG || s.rule == CADA_RULE_ALWAYS) {   // (the always-upload rule only records it)
+    const int nb = (int)min((int64_t)s.n_lhs_part, (s.p + 4 * kBlock - 1) / (4 * kBlock));
+    hipLaunchKernelGGL(k_lag_lhs, dim3((unsigned)max(nb, 1), (unsigned)s.M), dim3(kBlock), 0, c->stream, s);
+  }
+  hipLaunchKernelGGL(k_rule, dim3((unsigned)((s.M + 3) / 4)), dim3(kBlock), 0, c->stream, s, replay);
+  prof_mark(c);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) {
+    set_error("rule launch failed: %s", hipGetErrorString(e));
+    return CADA_EHIP;
+  }
+  return server_step(c);
 }
 
 int ring_finalize(Ctx *c) {

@@ -1,0 +1,42 @@
+"""The logistic step of one or two launches (cada_logreg_rows.hip) against the oracle, at the edges of its variants:
+pieces per lane and wavefronts per row change at 256, 512, 1024, 2048 and 4096 columns, the last quad of a row may overlap
+its neighbour, a worker's rows are split into shares from 64 rows and 256 KB on, and small states take the
+server update into the launch."""
+import numpy as np
+import pytest
+
+from cada_synth import configs, generators
+
+from common import check_protocol, upload
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("p,M,B,rule", [
+    (4, 3, 70, 2), (5, 70, 9, 1), (22, 10, 92, 3), (255, 3, 65, 2), (256, 66, 8, 1), (257, 3, 129, 2), (513, 5, 66, 1),
+    (784, 10, 60, 2), (1024, 4, 300, 2), (1025, 4, 300, 1), (1027, 3, 67, 0), (2048, 40, 40, 1), (2049, 3, 130, 2), (4097, 9, 64, 1),
+    (8191, 5, 150, 2), (8192, 3, 33, 1)])
+def test_rows_path(p, M, B, rule):
+    lag = rule == configs.RULE_LAG
+    cfg = configs.CFG1.scaled(name="rows", layer_dims=(p,), M=M, N_m=B + 40, B=B, K=24, D=6, rule=rule, c=0.5 if p < 100 else 2e-3,
+                              alpha=0.005, server=1 if lag else 0)
+    prob = generators.make_problem(cfg)
+    prob.X *= np.float32(1.0 / np.sqrt(p))           # (rows of norm about one, so that the decisions mix)
+    dev, sched = upload(prob), generators.make_schedule(cfg)
+    stats, o, tr, rep = check_protocol(cfg, prob, dev, sched, 1e-4, lhs_rtol=1e-4, expect_phase="logreg_rows")
+    print(p, M, B, rule, stats, tr["mask"].mean())
+    assert stats["stored_rel_l2"] < 1e-5
+
+
+def test_rows_path_flags_and_repeats():
+    """An index out of range is clamped and flagged; two runs agree bit for bit."""
+    from common import run_library
+    cfg = configs.CFG1.scaled(name="rows", layer_dims=(300,), M=3, N_m=200, B=100, K=6)
+    prob = generators.make_problem(cfg)
+    dev, sched = upload(prob), generators.make_schedule(cfg)
+    bad = sched.copy(); bad[3, 2, 70] = cfg.N_m + 5
+    fixed = sched.copy(); fixed[3, 2, 70] = cfg.N_m - 1
+    out, ref = run_library(cfg, dev, bad, expect_phase="logreg_rows"), run_library(cfg, dev, fixed)
+    assert out["error_flags"][0] == 1 and ref["error_flags"][0] == 0
+    for name in ("theta", "h", "vhat", "stored", "trace_lhs"):
+        assert np.array_equal(out[name], ref[name]), name
