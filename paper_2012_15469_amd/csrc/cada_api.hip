@@ -154,28 +154,23 @@ void carve_common(Carver &w, const cada_config *cfg, const Geometry &g, DevState
   float *t_lhs = w.take<float>(T * M), *t_rhs = w.take<float>(T);
   int32_t *t_tau = w.take<int32_t>(T * M);
   double *eval_part = w.take<double>(M * (size_t)kEvalBlocks * 2), *eval_acc = w.take<double>(M * 2);
-  int32_t *eval_idx = w.take<int32_t>(M * (size_t)cfg->B);
+  (void)w.take<int32_t>(M * (size_t)cfg->B);          // (not used any more; the room keeps the layout of saved checkpoint blocks)
   float *zpart = nullptr;
   unsigned long long *post = nullptr;
-  float *tail = nullptr, *rows_part = nullptr;
-  uint32_t *rows_count = nullptr;
+  float *tail = nullptr;
   uint32_t *small_bar = nullptr;
   unsigned char *small_args = nullptr;
   if (cfg->model == CADA_MODEL_LOGREG) {
     zpart = w.take<float>(M * (size_t)cfg->B * (size_t)g.n_col_chunks * 2);
     post = w.take<unsigned long long>(kFusedPostWords);
     if (cfg->p >= 8192 && cfg->p % 4 == 0) tail = w.take<float>(kFusedTailFloatsPerP * (size_t)cfg->p);   // (shapes the single-pass kernel serves)
-    rows_part = w.take<float>(rows_part_floats(cfg));
-    rows_count = w.take<uint32_t>(1 + M);
     small_bar = w.take<uint32_t>(64 + 2 * M);      // (a cache line kept free,) then the tagged decision words of the last two steps [2][M]
     small_args = w.take<unsigned char>(kSmallArgsBytes);
   }
   if (!s) return;
   c->fused_post = post;
   c->fused_tail = tail;
-  c->eval_part = eval_part; c->eval_acc = eval_acc; c->eval_idx = eval_idx;
-  c->rows_part = rows_part;
-  c->rows_count = rows_count;
+  c->eval_part = eval_part; c->eval_acc = eval_acc;
   c->small_bar = small_bar;
   c->small_args = small_args;
   s->theta = theta; s->theta_lo = theta_lo; s->hist_lo = hist_lo; s->snap_lo = snap_lo; s->h = h; s->v = v; s->vhat = vhat; s->nabla = nabla;
@@ -187,6 +182,22 @@ void carve_common(Carver &w, const cada_config *cfg, const Geometry &g, DevState
   s->t_mask = t_mask; s->t_own = t_own; s->t_lhs = t_lhs; s->t_rhs = t_rhs; s->t_tau = t_tau;
   s->trace_steps = cfg->trace_steps;
   c->zpart = zpart;
+}
+
+// Bytes of the state, which a checkpoint block holds.  Behind it lies scratch that holds nothing from one call to the next.
+size_t state_bytes(const cada_config *cfg, const Geometry &g) {
+  Carver w{nullptr};
+  carve_common(w, cfg, g, nullptr, nullptr);
+  if (cfg->model != CADA_MODEL_MLP) return w.off;
+  const size_t extra = mlp_workspace_bytes(cfg, g.total_rows);
+  return extra == 0 ? 0 : w.off + extra;
+}
+void carve_logreg_scratch(Carver &w, const cada_config *cfg, Ctx *c) {
+  float *rows_part = w.take<float>(rows_part_floats(cfg));
+  uint32_t *rows_count = w.take<uint32_t>(1 + (size_t)cfg->M);      // (zero between launches)
+  if (!c) return;
+  c->rows_part = rows_part;
+  c->rows_count = rows_count;
 }
 
 __global__ void k_fill_i32(int32_t *p, int32_t v, int64_t n) {
@@ -320,15 +331,12 @@ const char *cada_last_error(void) { return g_err; }
 size_t cada_workspace_bytes(const cada_config *cfg) {
   Geometry g;
   if (!check_config(cfg, &g) || !store_supported(cfg)) return 0;
-  Carver w{nullptr};
-  carve_common(w, cfg, g, nullptr, nullptr);
-  size_t total = w.off;
-  if (cfg->model == CADA_MODEL_MLP) {
-    const size_t extra = mlp_workspace_bytes(cfg, g.total_rows);
-    if (extra == 0) return 0;
-    total += extra;
-  }
-  return total;
+  const size_t state = state_bytes(cfg, g);
+  if (state == 0) return 0;
+  if (cfg->model == CADA_MODEL_MLP) return state + mlp_scratch_bytes(cfg, g.total_rows);
+  Carver w{nullptr, state};
+  carve_logreg_scratch(w, cfg, nullptr);
+  return w.off;
 }
 
 int cada_init(const cada_config *cfg, const float *theta0, cada_ctx **out) {
@@ -362,13 +370,17 @@ int cada_init(const cada_config *cfg, const float *theta0, cada_ctx **out) {
   c->vec = g.vec;
   c->n_col_chunks = g.n_col_chunks;
   c->chunk_cols = g.chunk_cols;
-  c->ws_bytes = need;
+  c->state_bytes = state_bytes(cfg, g);
   c->ring_cap = g.ring_cap;
   c->force_resum = 1;
   c->ws_base = cfg->workspace;
   c->logreg_group = cfg->two_pass_group > 0 ? cfg->two_pass_group : 0;
   Carver w{static_cast<char *>(cfg->workspace)};
   carve_common(w, cfg, g, &s, c);
+  if (cfg->model == CADA_MODEL_LOGREG) {
+    Carver scratch{static_cast<char *>(cfg->workspace), c->state_bytes};
+    carve_logreg_scratch(scratch, cfg, c);
+  }
   s.X = cfg->X; s.y = cfg->y;
   s.M = cfg->M; s.B = cfg->B; s.d_max = cfg->d_max; s.D = cfg->D; s.R = cfg->D + 1; s.rule = cfg->rule; s.server_sgd = cfg->server == CADA_SERVER_SGD;
   s.n_lhs_part = g.n_lhs_part; s.n_ring_part = g.n_ring_part;
@@ -397,8 +409,7 @@ int cada_init(const cada_config *cfg, const float *theta0, cada_ctx **out) {
     }
   }
   if (cfg->model == CADA_MODEL_MLP) {
-    size_t off = w.off;
-    const int rc = mlp_plan(c, cfg, static_cast<char *>(cfg->workspace), &off, g.total_rows);
+    const int rc = mlp_plan(c, cfg, static_cast<char *>(cfg->workspace), w.off, c->state_bytes, g.total_rows);
     if (rc != CADA_OK) { delete h; return rc; }
   }
 
@@ -577,8 +588,8 @@ int cada_eval_noalloc(cada_ctx *ctx, double *out) {
 }
 
 namespace {
-struct CheckpointHeader {          // in front of the workspace image
-  uint64_t magic, ws_bytes;
+struct CheckpointHeader {          // in front of the image of the workspace's state
+  uint64_t magic, state_bytes;
   int64_t k, p;
   int32_t M, B, rule, model, D, d_max, server_sgd;
   uint32_t fused_seq, small_seq;
@@ -590,7 +601,7 @@ constexpr size_t kCheckpointHeaderBytes = 128;
 
 CheckpointHeader header_of(const Ctx *c) {
   CheckpointHeader h{};
-  h.magic = kCheckpointMagic; h.ws_bytes = c->ws_bytes; h.k = c->k; h.p = c->s.p;
+  h.magic = kCheckpointMagic; h.state_bytes = c->state_bytes; h.k = c->k; h.p = c->s.p;
   h.M = c->s.M; h.B = c->s.B; h.rule = c->s.rule; h.model = c->model; h.D = c->s.D; h.d_max = c->s.d_max;
   h.server_sgd = c->s.server_sgd; h.fused_seq = c->fused_seq; h.small_seq = c->small_seq;
   h.force_resum = c->force_resum;
@@ -598,13 +609,13 @@ CheckpointHeader header_of(const Ctx *c) {
 }
 }  // namespace
 
-size_t cada_checkpoint_bytes(cada_ctx *ctx) { return ctx ? kCheckpointHeaderBytes + ctx->c.ws_bytes : 0; }
+size_t cada_checkpoint_bytes(cada_ctx *ctx) { return ctx ? kCheckpointHeaderBytes + ctx->c.state_bytes : 0; }
 
 int cada_checkpoint_save(cada_ctx *ctx, void *dst) {
   if (!ctx || !dst) { set_error("ctx/dst is NULL"); return CADA_EINVAL; }
   Ctx *c = &ctx->c;
   const CheckpointHeader h = header_of(c);
-  HIP_TRY(hipMemcpyAsync(static_cast<char *>(dst) + kCheckpointHeaderBytes, c->ws_base, c->ws_bytes, hipMemcpyDeviceToDevice, c->stream));
+  HIP_TRY(hipMemcpyAsync(static_cast<char *>(dst) + kCheckpointHeaderBytes, c->ws_base, c->state_bytes, hipMemcpyDeviceToDevice, c->stream));
   HIP_TRY(hipMemcpyAsync(dst, &h, sizeof(h), hipMemcpyHostToDevice, c->stream));
   HIP_TRY(hipStreamSynchronize(c->stream));     // h lives on this frame
   return CADA_OK;
@@ -618,12 +629,12 @@ int cada_checkpoint_load(cada_ctx *ctx, const void *src) {
   HIP_TRY(hipStreamSynchronize(c->stream));
   const CheckpointHeader mine = header_of(c);
   if (h.magic != kCheckpointMagic) { set_error("not a checkpoint block"); return CADA_EINVAL; }
-  if (h.ws_bytes != mine.ws_bytes || h.p != mine.p || h.M != mine.M || h.B != mine.B || h.rule != mine.rule ||
+  if (h.state_bytes != mine.state_bytes || h.p != mine.p || h.M != mine.M || h.B != mine.B || h.rule != mine.rule ||
       h.model != mine.model || h.D != mine.D || h.d_max != mine.d_max || h.server_sgd != mine.server_sgd) {
     set_error("checkpoint was saved with a different configuration");
     return CADA_EINVAL;
   }
-  HIP_TRY(hipMemcpyAsync(c->ws_base, static_cast<const char *>(src) + kCheckpointHeaderBytes, c->ws_bytes, hipMemcpyDeviceToDevice, c->stream));
+  HIP_TRY(hipMemcpyAsync(c->ws_base, static_cast<const char *>(src) + kCheckpointHeaderBytes, c->state_bytes, hipMemcpyDeviceToDevice, c->stream));
   HIP_TRY(hipStreamSynchronize(c->stream));
   c->k = h.k;
   c->fused_seq = h.fused_seq;

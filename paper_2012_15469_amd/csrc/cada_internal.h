@@ -249,7 +249,7 @@ struct Ctx {
   int64_t k;                 // steps enqueued
   int32_t model, gemm_dtype, n_layers;
   int32_t dims[CADA_MAX_LAYERS + 1];
-  size_t ws_bytes;
+  size_t state_bytes;        // the part of the workspace that a checkpoint holds
   void *ws_base;             // the caller's workspace
   // logistic launch geometry
   int vec;                   // 4 if rows can be read as float4, else 1
@@ -281,7 +281,6 @@ struct Ctx {
   // full-data evaluation scratch (cada_eval)
   double *eval_part;         // [M][kEvalBlocks][2] per-block sums of (loss, correct)
   double *eval_acc;          // [M][2]
-  int32_t *eval_idx;         // [M][B] row ids of one evaluation chunk (MLP)
   int logreg_group;          // workers per launch pair of the logistic gradient kernels (0 = all)
   int force_resum;           // the stored aggregate does not belong to the state (first step, after cada_set_state)
   void *mlp;                 // MLP plan (cada_mlp.hip), or nullptr
@@ -322,7 +321,8 @@ int eval_scratch_init();                        // looks that array's address up
 void eval_finish(Ctx *c, double *out, int with_reg);   // out = mean over the workers of eval_acc (+ regulariser)
 constexpr int kEvalBlocks = 512;      // blocks per worker of the logistic evaluation kernel
 size_t mlp_workspace_bytes(const cada_config *cfg, const int64_t total_rows);
-int mlp_plan(Ctx *c, const cada_config *cfg, char *base, size_t *offset, int64_t total_rows);
+size_t mlp_scratch_bytes(const cada_config *cfg, const int64_t total_rows);      // behind the state: nothing a checkpoint holds
+int mlp_plan(Ctx *c, const cada_config *cfg, char *base, size_t offset, size_t scratch, int64_t total_rows);
 int mlp_init_state(Ctx *c, const float *theta0);
 void mlp_free(Ctx *c);
 // S3: rule, mask, tau.  S5-S7: aggregate, AMSGrad, ring push.

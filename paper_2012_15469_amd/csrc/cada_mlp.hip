@@ -46,62 +46,21 @@
 #include <cstdlib>
 #include <new>
 
-#include "cada_internal.h"
+#include "cada_mlp.h"
 
 namespace cada {
 
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
-typedef uint16_t bf16_t;   // storage type
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));   // four floats at any 4-byte aligned address
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // 16 bytes in flight (a native vector: stays in registers)
-typedef uint32_t u32x2u __attribute__((ext_vector_type(2), aligned(4)));   // four bf16 values at any 4-byte aligned address
-
-static inline int64_t P8(int64_t x) { return (x + 7) / 8 * 8; }
-
-constexpr int BM = 128, BN = 128, BK = 32;
-constexpr int TILE = 128 * BK;                    // bf16 elements of one chunk (8 KB)
-constexpr int kMaxSlots = 4;
-
-// Operand layout.  Every bf16 tensor a contraction reads is stored in chunks of 128 rows x 32
-// contraction indices, each chunk 8 KB of consecutive memory, the chunks of a 128-row tile one
-// after the other: element (r, k) of a tensor with kt chunks per row tile lies at
-//     ((r / 128) * kt + k / 32) * 4096 + (r % 128) * 32 + k % 32.
-// A tile step of the contraction then reads whole 128-byte lines only.  With rows stored one
-// after the other a step reads a 64-byte piece of each of 128 rows, and the vector L1, which
-// works line by line, delivers those at half the rate (measured from L2: 27 against 51 B/clk
-// per CU), which made the loads, not the MFMAs, the longest phase of a step.  Rows and indices
-// beyond a tensor's extent, up to whole chunks, exist in memory and stay zero: nothing is
-// clamped or masked on the way in.
-__host__ __device__ __forceinline__ int64_t tm(int64_t r, int64_t k, int64_t kt) {
-  return (((r >> 7) * kt + (k >> 5)) << 12) + ((r & 127) << 5) + (k & 31);
-}
-static inline int tiles128(int64_t x) { return (int)((x + 127) / 128); }
-// chunks per 128-row tile of a tensor with x contraction indices: whole groups of four, so that a
-// 128-unit tile of the weight-gradient contractions (which take units as output rows) finds all its
-// four chunks; the padding stays zero
-static inline int chunks32(int64_t x) { return 4 * (int)((x + 127) / 128); }
-
-// In LDS a chunk keeps its 8 KB (row r at byte 64 r, no padding); the four 16-byte pieces of a row
-// are stored in the order q ^ ((r >> 2) & 3).  A fragment read takes one piece of each of 32
-// consecutive rows; rows 4 apart lie 256 bytes = one pass over the 64 banks apart, and with this
-// order the same piece of 16 consecutive rows covers every bank once.
-__device__ __forceinline__ int lds_piece(int piece) {   // piece = 4 row + q  ->  position (16-byte units)
-  return piece ^ ((piece >> 4) & 3);
-}
-
-enum { EPI_FWD_HIDDEN = 0, EPI_STORE2 = 1, EPI_DW = 2, EPI_DA = 3, EPI_LOSS = 4 };
+enum { EPI_FWD_HIDDEN = 0, EPI_DW = 2, EPI_DA = 3, EPI_LOSS = 4 };
 
 // LDS: a ring of 8 KB slots (one chunk each); behind it a buffer per multiplying wavefront for the
 // way out: 32 rows x 64 floats for the weight gradients, 8 KB for the bf16 tensors of the forward
-// and activation-gradient variants (the logits of the last layer are stored directly).  The pitch of
+// and activation-gradient variants.  The pitch of
 // 72 floats puts the two half-wavefronts of an accumulator store (rows 4 apart) into different
 // halves of the banks.
 constexpr int kDwPitch = 72;
-constexpr int mm5_slots(int epi) { return epi == EPI_STORE2 ? 19 : 15; }
+constexpr int kMm5Slots = 15;
 constexpr size_t mm5_lds_bytes(int epi) {
-  return (size_t)mm5_slots(epi) * TILE * sizeof(bf16_t) +
-         (epi == EPI_DW ? 4 * 32 * kDwPitch * sizeof(float) : epi == EPI_STORE2 ? 0 : 4 * 8192);
+  return (size_t)kMm5Slots * TILE * sizeof(bf16_t) + (epi == EPI_DW ? 4 * 32 * kDwPitch * sizeof(float) : 4 * 8192);
 }
 
 // Up to four tensors that share the row index of one side of the product.
@@ -127,8 +86,6 @@ struct Mm5Args {
   int64_t kto;
   uint64_t *maskbits;                   // ReLU mask bits [workers][row tiles][column tiles][256 lanes][2]: written by EPI_FWD_HIDDEN, read by EPI_DA
   float *dbpart, *ddbpart;              // EPI_DA: [M_workers][2 x row tiles][N], one partial sum per 64-row band
-  // EPI_STORE2
-  float *c1, *c2;                       // [Rp][N]
   // EPI_DW
   int64_t offW;
   int lhs_slot0;
@@ -209,7 +166,7 @@ template <int EPI, int NA, int NB, bool HAS_D>
 __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   bf16_t *lds = reinterpret_cast<bf16_t *>(smem_raw);
-  constexpr int NS = NA + NB, NSLOT = mm5_slots(EPI);
+  constexpr int NS = NA + NB, NSLOT = kMm5Slots;
   constexpr bool TR = EPI == EPI_DW;          // operands are (row, unit) tensors read across the rows
   static_assert(NSLOT >= 2 * NS, "the ring must hold two tile steps");
   const DevState &s = g.s;
@@ -364,22 +321,7 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
   const int rbase = m0 + wy * 64 + 4 * (lane >> 5);
   const int cbase = n0 + wx * 64 + (lane & 31);
   const int64_t rp0 = (int64_t)wk * g.Bp;            // first padded row of this worker
-  if constexpr (EPI == EPI_STORE2) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int col = cbase + j * 32;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int row = rbase + i * 32 + 8 * (r >> 2) + (r & 3);
-          if (row < g.M && col < g.N) {
-            g.c1[(rp0 + row) * g.N + col] = acc1[i][j][r];
-            g.c2[(rp0 + row) * g.N + col] = acc2[i][j][r];
-          }
-        }
-      }
-  } else if constexpr (EPI == EPI_FWD_HIDDEN || EPI == EPI_DA) {
+  if constexpr (EPI == EPI_FWD_HIDDEN || EPI == EPI_DA) {
     // Forward: bias, ReLU of both evaluations.  Activation gradient: ReLU masks of the layer
     // below, bias-gradient partial sums.  Both: the result split into hi/lo, its difference and
     // its reference value, each written as a (row, column) tensor.
@@ -632,7 +574,7 @@ __device__ __forceinline__ float group16_sum(float x) {
 // global memory (a fragment is 16 consecutive bytes of a chunk row) and add their partial accumulators up
 // through LDS in a fixed order.  grid (ceil(M / 32), workers), 64 nw threads, 8 KB of dynamic LDS per
 // wavefront (EPI_DW: 14 KB).
-// EPI_STORE2: logits (evaluation); EPI_LOSS: the logits stay in the workgroup, whose epilogue is the loss (the signals
+// EPI_LOSS: the logits stay in the workgroup, whose epilogue is the loss (the signals
 // the backward contractions read, and per-block sums for the bias gradient); EPI_DW: weight gradient, innovation, its
 // squared norm (slot lhs_slot0 + row band), and (one more workgroup) the last layer's bias gradient from those sums.
 // The weight gradient sums over the worker's rows: its operands are (row, unit) tensors, a step's part of
@@ -882,17 +824,12 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
     for (int ww = 0; ww < nw; ++ww) v += red[((ww * 2 + a) * 16 + r) * 64 + ln];
     const int row = m0 + 8 * (r >> 2) + 4 * (ln >> 5) + (r & 3), col = ln & 31;
     if (row < g.M && col < g.N) {
-      if constexpr (EPI == EPI_STORE2) {
-        const int64_t o = ((int64_t)wk * g.Bp + row) * g.N + col;
-        if (a == 0) g.c1[o] = v; else g.c2[o] = v;
+      const int64_t o = (int64_t)row * g.N + col;
+      if (a == 0) {
+        if (gf16) gf16[o] = f2bf(v); else gf[o] = v;
       } else {
-        const int64_t o = (int64_t)row * g.N + col;
-        if (a == 0) {
-          if (gf16) gf16[o] = f2bf(v); else gf[o] = v;
-        } else {
-          if (cada1) { ivf[o] = f2bf(v); v -= bf2f(ivs[o]); }
-          sq = fmaf(v, v, sq);
-        }
+        if (cada1) { ivf[o] = f2bf(v); v -= bf2f(ivs[o]); }
+        sq = fmaf(v, v, sq);
       }
     }
   }
@@ -912,31 +849,6 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
 // ------------------------------------------------------------------------------------------
 // plan
 // ------------------------------------------------------------------------------------------
-struct MlpPlan {
-  int L, M, B, Bp, rule, RT;
-  int64_t Rp;                     // M * Bp padded rows per step (Bp a multiple of 128: a worker's rows start a tile)
-  int64_t total_rows;             // rows of X
-  int64_t max_rows_per_worker;
-  int d[CADA_MAX_LAYERS + 1];
-  int64_t offW[CADA_MAX_LAYERS], offb[CADA_MAX_LAYERS];   // offsets into theta, index l-1
-  int64_t kta[CADA_MAX_LAYERS + 1];                       // chunks32(d_l): chunks per tile of (row, d_l) tensors
-  int64_t wt_off[CADA_MAX_LAYERS], wt_total;              // W_l^T (d_l, d_{l-1}), index l-1
-  int64_t wn_off[CADA_MAX_LAYERS], wn_total;              // W_l   (d_{l-1}, d_l), l >= 2
-  int lhs_w_slot[CADA_MAX_LAYERS], lhs_b_slot[CADA_MAX_LAYERS];
-  int nW;                                                 // delta-weight copies: 1 (CADA1) or M (CADA2)
-  bf16_t *Xh, *Xl; int64_t ldx;                           // all features, rows one after the other [total_rows][ldx]
-  bf16_t *XGh, *XGl;                                      // gathered minibatch, (padded row, feature)
-  int64_t *grow;
-  bf16_t *WTh, *WTl, *dWT, *WNh, *WNl, *dWN;
-  bf16_t *Ah[CADA_MAX_LAYERS], *Al[CADA_MAX_LAYERS], *dA[CADA_MAX_LAYERS], *Aref[CADA_MAX_LAYERS];   // hidden l, (row, unit)
-  bf16_t *Gh[CADA_MAX_LAYERS + 1], *Gl[CADA_MAX_LAYERS + 1], *dG[CADA_MAX_LAYERS + 1], *Gref[CADA_MAX_LAYERS + 1];       // layer l >= 1, (row, unit)
-  float *ZL, *dZL;                                        // logits [Rp][C]
-  uint64_t *maskbits[CADA_MAX_LAYERS];                    // hidden l: ReLU mask bits per tile and lane
-  int32_t *rep;                                           // CADA2: first worker with the same reference point [M]
-  float *dbpart, *ddbpart;                                // [M][2 RT][max hidden width]
-  float *lastb;                                           // [M][Bp / 32][32][2]: last layer, sums of G and dG per block of 32 rows
-};
-
 namespace {
 constexpr size_t kAlignB = 256;
 struct Carve {
@@ -957,9 +869,6 @@ void layout(MlpPlan &P, const cada_config *cfg, int64_t total_rows, Carve &w) {
   P.Bp = P.RT * 128;
   P.Rp = (int64_t)cfg->M * P.Bp;
   P.total_rows = total_rows;
-  P.max_rows_per_worker = 0;
-  for (int m = 0; m < cfg->M; ++m)
-    if (cfg->n_samples[m] > P.max_rows_per_worker) P.max_rows_per_worker = cfg->n_samples[m];
   for (int l = 0; l <= P.L; ++l) { P.d[l] = cfg->layer_dims[l]; P.kta[l] = chunks32(P.d[l]); }
   int64_t o = 0, wt = 0, wn = 0;
   int slot = 0, maxh = 1;
@@ -994,8 +903,8 @@ void layout(MlpPlan &P, const cada_config *cfg, int64_t total_rows, Carve &w) {
     P.Gh[l] = w.take<bf16_t>(n); P.Gl[l] = w.take<bf16_t>(n); P.dG[l] = w.take<bf16_t>(n);
     P.Gref[l] = l >= 2 ? w.take<bf16_t>(n) : nullptr;       // (the first layer has no propagated difference to pair it with)
   }
-  P.ZL = w.take<float>(Rp * P.d[P.L]);
-  P.dZL = w.take<float>(Rp * P.d[P.L]);
+  (void)w.take<float>(Rp * P.d[P.L]);             // (not used any more; the room keeps the layout of saved checkpoint blocks)
+  (void)w.take<float>(Rp * P.d[P.L]);
   P.dbpart = w.take<float>((size_t)cfg->M * 2 * P.RT * maxh);
   P.ddbpart = w.take<float>((size_t)cfg->M * 2 * P.RT * maxh);
   P.lastb = w.take<float>((size_t)cfg->M * (P.Bp / 32) * 32 * 2);
@@ -1029,13 +938,20 @@ size_t mlp_workspace_bytes(const cada_config *cfg, const int64_t total_rows) {
   return w.off + kAlignB;
 }
 
-int mlp_plan(Ctx *c, const cada_config *cfg, char *base, size_t *offset, int64_t total_rows) {
+size_t mlp_scratch_bytes(const cada_config *cfg, const int64_t total_rows) {
+  MlpPlan P;
+  Carve w{nullptr, 0};
+  layout(P, cfg, total_rows, w);
+  return mlp_eval_bytes(P) + kAlignB;
+}
+
+int mlp_plan(Ctx *c, const cada_config *cfg, char *base, size_t offset, size_t scratch, int64_t total_rows) {
   if (mlp_workspace_bytes(cfg, total_rows) == 0) return CADA_EUNSUPPORTED;
   MlpPlan *P = new (std::nothrow) MlpPlan();
   if (!P) { set_error("out of host memory"); return CADA_EINVAL; }
-  Carve w{base, (*offset + kAlignB - 1) / kAlignB * kAlignB};
+  Carve w{base, (offset + kAlignB - 1) / kAlignB * kAlignB};
   layout(*P, cfg, total_rows, w);
-  *offset = w.off;
+  P->eval = base + (scratch + kAlignB - 1) / kAlignB * kAlignB;
   c->mlp = P;
   c->n_phases = 3;
   c->phase_names[0] = "mlp_gradients"; c->phase_names[1] = "rule"; c->phase_names[2] = "server_update";
@@ -1286,7 +1202,7 @@ template <int EPI, int NA, int NB, bool HAS_D> int launch_skinny_as(Ctx *c, cons
 template <int EPI> int launch_mm5(Ctx *c, Mm5Args &g, int workers) {
   g.workers = workers;
   const bool has_d = g.a_d >= 0;
-  if constexpr (EPI == EPI_STORE2 || EPI == EPI_DW || EPI == EPI_LOSS) {
+  if constexpr (EPI == EPI_DW || EPI == EPI_LOSS) {
     if (g.N <= 32) {            // at most 32 output columns (the last layer)
       for (int i = 1; i < g.A.n; ++i)
         if (g.A.kt[i] != g.A.kt[0]) { set_error("internal: A tensors with different chunk counts"); return CADA_EUNSUPPORTED; }
@@ -1346,15 +1262,12 @@ Mm5Args blank(const DevState &s, const MlpPlan &P) {
 int mlp_init_state(Ctx *c, const float *) {
   MlpPlan &P = *static_cast<MlpPlan *>(c->mlp);
   hipError_t e = hipSuccess;
+  if (const int rc = mlp_eval_init(c)) return rc;
   e = mm5_allow_lds<EPI_FWD_HIDDEN, 2, 3, false>();
   if (e == hipSuccess) e = mm5_allow_lds<EPI_FWD_HIDDEN, 4, 3, true>();
-  if (e == hipSuccess) e = mm5_allow_lds<EPI_STORE2, 2, 3, false>();
-  if (e == hipSuccess) e = mm5_allow_lds<EPI_STORE2, 4, 3, true>();
   if (e == hipSuccess) e = mm5_allow_lds<EPI_DW, 2, 3, false>();
   if (e == hipSuccess) e = mm5_allow_lds<EPI_DW, 3, 4, true>();
   if (e == hipSuccess) e = mm5_allow_lds<EPI_DA, 4, 3, true>();
-  if (e == hipSuccess) e = skinny_allow_lds<EPI_STORE2, 2, 3, false>();
-  if (e == hipSuccess) e = skinny_allow_lds<EPI_STORE2, 4, 3, true>();
   if (e == hipSuccess) e = skinny_allow_lds<EPI_LOSS, 2, 3, false>();
   if (e == hipSuccess) e = skinny_allow_lds<EPI_LOSS, 4, 3, true>();
   if (e == hipSuccess) e = skinny_allow_lds<EPI_DW, 2, 3, false>();
@@ -1367,39 +1280,41 @@ int mlp_init_state(Ctx *c, const float *) {
   return CADA_OK;
 }
 
-// Gathers the minibatch rows, prepares the bf16 weights and runs the forward contractions:
-// leaves the activations of every layer and the logits (without bias) of the last one.
-// with_loss: the last layer's launch also evaluates the loss (training step); else it leaves the logits (evaluation).
-static int mlp_forward(Ctx *c, MlpPlan &P, const DevState &s, const int32_t *idx, bool with_loss) {
-  hipStream_t st = c->stream;
+// The bf16 copies of the weights, and with idx the minibatch's rows and the differences to the reference points.
+static void stage(Ctx *c, const MlpPlan &P, const DevState &s, const int32_t *idx) {
+  const int L = P.L, M = P.M, B = P.B;
+  StageArgs sa;
+  sa.s = s;
+  sa.Xh = P.Xh; sa.Xl = P.Xl; sa.ldx = P.ldx; sa.idx = idx; sa.grow = P.grow;
+  sa.XGh = P.XGh; sa.XGl = P.XGl;
+  sa.d0 = P.d[0]; sa.B = B; sa.Bp = P.Bp; sa.ktx = P.kta[0];
+  sa.gx = (int)((P.ldx + 63) / 64); sa.gy = (B + 63) / 64;
+  sa.n_layers = L; sa.nz = idx ? P.nW + 1 : 1; sa.wt_total = P.wt_total; sa.wn_total = P.wn_total; sa.rep = P.rule == CADA_RULE_CADA2 ? P.rep : nullptr;
+  uint64_t nblk = idx ? (uint64_t)sa.gx * sa.gy * M : 0;
+  sa.first[0] = 0;
+  for (int l = 1; l <= L; ++l) {
+    PrepLayer &pl = sa.layer[l - 1];
+    pl.WTh = P.WTh + P.wt_off[l - 1]; pl.WTl = P.WTl + P.wt_off[l - 1]; pl.dWT = P.dWT + P.wt_off[l - 1];
+    pl.WNh = P.WNh + P.wn_off[l - 1]; pl.WNl = P.WNl + P.wn_off[l - 1]; pl.dWN = P.dWN + P.wn_off[l - 1];
+    pl.offW = P.offW[l - 1];
+    pl.din = P.d[l - 1]; pl.dout = P.d[l]; pl.ktt = P.kta[l - 1]; pl.ktn = P.kta[l]; pl.want_n = idx && l >= 2;
+    pl.gx = (pl.dout + 63) / 64; pl.gy = (pl.din + 63) / 64;
+    sa.first[l] = (uint32_t)nblk;
+    nblk += (uint64_t)pl.gx * pl.gy * sa.nz;
+  }
+  for (int l = L + 1; l < CADA_MAX_LAYERS + 2; ++l) sa.first[l] = (uint32_t)nblk;
+  hipLaunchKernelGGL(k_stage, dim3((unsigned)nblk), dim3(kBlock), 0, c->stream, sa);
+}
+
+void mlp_stage_weights(Ctx *c) { stage(c, *static_cast<MlpPlan *>(c->mlp), c->s, nullptr); }
+
+// Gathers the minibatch rows, prepares the bf16 weights and runs the forward contractions, whose last one evaluates the loss.
+static int mlp_forward(Ctx *c, MlpPlan &P, const DevState &s, const int32_t *idx) {
   const int L = P.L, M = P.M, B = P.B, Bp = P.Bp;
   const bool per_worker = (P.rule == CADA_RULE_CADA2);
   const int64_t dwt_stride = per_worker ? P.wt_total : 0;
   int32_t *rep = per_worker ? P.rep : nullptr;
-  {
-    StageArgs sa;
-    sa.s = s;
-    sa.Xh = P.Xh; sa.Xl = P.Xl; sa.ldx = P.ldx; sa.idx = idx; sa.grow = P.grow;
-    sa.XGh = P.XGh; sa.XGl = P.XGl;
-    sa.d0 = P.d[0]; sa.B = B; sa.Bp = Bp; sa.ktx = P.kta[0];
-    sa.gx = (int)((P.ldx + 63) / 64); sa.gy = (B + 63) / 64;
-    sa.n_layers = L; sa.nz = P.nW + 1; sa.wt_total = P.wt_total; sa.wn_total = P.wn_total; sa.rep = rep;
-    uint64_t nblk = (uint64_t)sa.gx * sa.gy * M;
-    sa.first[0] = 0;
-    for (int l = 1; l <= L; ++l) {
-      PrepLayer &pl = sa.layer[l - 1];
-      pl.WTh = P.WTh + P.wt_off[l - 1]; pl.WTl = P.WTl + P.wt_off[l - 1]; pl.dWT = P.dWT + P.wt_off[l - 1];
-      pl.WNh = P.WNh + P.wn_off[l - 1]; pl.WNl = P.WNl + P.wn_off[l - 1]; pl.dWN = P.dWN + P.wn_off[l - 1];
-      pl.offW = P.offW[l - 1];
-      pl.din = P.d[l - 1]; pl.dout = P.d[l]; pl.ktt = P.kta[l - 1]; pl.ktn = P.kta[l]; pl.want_n = l >= 2;
-      pl.gx = (pl.dout + 63) / 64; pl.gy = (pl.din + 63) / 64;
-      sa.first[l] = (uint32_t)nblk;
-      nblk += (uint64_t)pl.gx * pl.gy * sa.nz;
-    }
-    sa.first[L + 1] = (uint32_t)nblk;
-    for (int l = L + 2; l < CADA_MAX_LAYERS + 2; ++l) sa.first[l] = (uint32_t)nblk;
-    hipLaunchKernelGGL(k_stage, dim3((unsigned)nblk), dim3(kBlock), 0, st, sa);
-  }
+  stage(c, P, s, idx);
 
   // ---- forward: worker m owns padded rows [m*Bp, m*Bp + B)
   for (int l = 1; l <= L; ++l) {
@@ -1426,14 +1341,11 @@ static int mlp_forward(Ctx *c, MlpPlan &P, const DevState &s, const int32_t *idx
       g.o_h = P.Ah[l]; g.o_l = P.Al[l]; g.o_d = P.dA[l]; g.o_r = P.Aref[l];
       g.maskbits = P.maskbits[l];
       if (const int rc = launch_mm5<EPI_FWD_HIDDEN>(c, g, M)) return rc;
-    } else if (with_loss) {
+    } else {
       g.offb = P.offb[L - 1]; g.kto = P.kta[L];
       g.o_h = P.Gh[L]; g.o_l = P.Gl[L]; g.o_d = P.dG[L]; g.o_r = P.Gref[L];     // (Gref: null for a single-layer network)
       g.grow = P.grow; g.lastb = P.lastb; g.nrb = Bp / 32;
       if (const int rc = launch_mm5<EPI_LOSS>(c, g, M)) return rc;
-    } else {
-      g.c1 = P.ZL; g.c2 = P.dZL;
-      if (const int rc = launch_mm5<EPI_STORE2>(c, g, M)) return rc;
     }
   }
   return CADA_OK;
@@ -1449,7 +1361,7 @@ int mlp_gradients(Ctx *c, const int32_t *idx) {
   const int64_t dwn_stride = per_worker ? P.wn_total : 0;
 
   prof_mark(c);
-  if (const int rc = mlp_forward(c, P, s, idx, true)) return rc;
+  if (const int rc = mlp_forward(c, P, s, idx)) return rc;
 
   // ---- backward
   for (int l = L; l >= 1; --l) {
@@ -1507,91 +1419,6 @@ int mlp_gradients(Ctx *c, const int32_t *idx) {
     set_error("MLP gradient launch failed: %s", hipGetErrorString(e));
     return CADA_EHIP;
   }
-  return CADA_OK;
-}
-
-
-// ------------------------------------------------------------------------------------------
-// Evaluation on all the data (not part of an iteration).
-// idx[m][b] = min(chunk*B + b, N_m - 1): the rows of one evaluation chunk (the tail repeats the
-// last row; those copies are not counted)
-__global__ void k_eval_idx(const DevState s, int32_t *idx, int chunk) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (int64_t)s.M * s.B) return;
-  const int m = (int)(i / s.B), b = (int)(i % s.B);
-  const int64_t n = s.row_off[m + 1] - s.row_off[m];
-  const int64_t r = (int64_t)chunk * s.B + b;
-  idx[i] = (int32_t)(r < n ? r : n - 1);
-}
-
-// Softmax cross-entropy and top-1 hits of the chunk's valid rows, added to acc[m] (sums, not yet
-// means).  One block per worker, so consecutive chunks add in a fixed order.
-__global__ __launch_bounds__(kBlock) void k_eval_chunk(const DevState s, const float *Z, const int64_t *grow, int64_t offb, int C, int Bp,
-                                                      int chunk, double *acc) {
-  constexpr int MAXC = 32;
-  __shared__ double red[kBlock][2];
-  const int m = blockIdx.x;
-  const int64_t n = s.row_off[m + 1] - s.row_off[m];
-  const int64_t left = n - (int64_t)chunk * s.B;
-  const int valid = (int)(left < 0 ? 0 : (left > s.B ? s.B : left));
-  const int32_t *yv = static_cast<const int32_t *>(s.y);
-  double loss = 0.0, hits = 0.0;
-  for (int b = threadIdx.x; b < valid; b += kBlock) {
-    const int64_t r = (int64_t)m * Bp + b;
-    const int label = yv[grow[r]];
-    float zmax = -INFINITY, zl = 0.f;
-    int arg = 0;
-    float z[MAXC];
-#pragma unroll
-    for (int c = 0; c < MAXC; ++c)
-      if (c < C) {
-        z[c] = Z[r * C + c] + s.theta[offb + c];
-        if (z[c] > zmax) { zmax = z[c]; arg = c; }
-        if (c == label) zl = z[c];
-      }
-    float den = 0.f;
-#pragma unroll
-    for (int c = 0; c < MAXC; ++c) if (c < C) den += expf(z[c] - zmax);
-    loss += (double)(zmax + logf(den) - zl);
-    hits += arg == label ? 1.0 : 0.0;
-  }
-  red[threadIdx.x][0] = loss; red[threadIdx.x][1] = hits;
-  __syncthreads();
-  for (int o = kBlock / 2; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) { red[threadIdx.x][0] += red[threadIdx.x + o][0]; red[threadIdx.x][1] += red[threadIdx.x + o][1]; }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) { acc[2 * m] += red[0][0]; acc[2 * m + 1] += red[0][1]; }
-}
-
-__global__ void k_eval_means(const DevState s, double *acc) {
-  const int m = blockIdx.x * blockDim.x + threadIdx.x;
-  if (m >= s.M) return;
-  const double n = (double)(s.row_off[m + 1] - s.row_off[m]);
-  acc[2 * m] /= n;
-  acc[2 * m + 1] /= n;
-}
-
-int mlp_eval(Ctx *c, double *out) {
-  MlpPlan &P = *static_cast<MlpPlan *>(c->mlp);
-  DevState s = c->s;
-  s.k = c->k;
-  hipStream_t st = c->stream;
-  if (P.d[P.L] > 32) { set_error("evaluation supports at most 32 classes"); return CADA_EINVAL; }
-  hipError_t e = hipMemsetAsync(c->eval_acc, 0, (size_t)P.M * 2 * sizeof(double), st);
-  if (e != hipSuccess) { set_error("hipMemsetAsync failed: %s", hipGetErrorString(e)); return CADA_EHIP; }
-  const int64_t nmax = P.max_rows_per_worker;
-  const int chunks = (int)((nmax + P.B - 1) / P.B);
-  const unsigned nb = (unsigned)(((int64_t)P.M * P.B + 255) / 256);
-  for (int ch = 0; ch < chunks; ++ch) {
-    hipLaunchKernelGGL(k_eval_idx, dim3(nb), dim3(256), 0, st, s, c->eval_idx, ch);
-    if (const int rc = mlp_forward(c, P, s, c->eval_idx, false)) return rc;
-    hipLaunchKernelGGL(k_eval_chunk, dim3((unsigned)P.M), dim3(kBlock), 0, st, s, P.ZL, P.grow, P.offb[P.L - 1], P.d[P.L], P.Bp, ch, c->eval_acc);
-  }
-  hipLaunchKernelGGL(k_eval_means, dim3((unsigned)((P.M + 63) / 64)), dim3(64), 0, st, s, c->eval_acc);
-  eval_finish(c, out, 0);
-  e = hipGetLastError();
-  if (e != hipSuccess) { set_error("evaluation launch failed: %s", hipGetErrorString(e)); return CADA_EHIP; }
   return CADA_OK;
 }
 

@@ -1,0 +1,406 @@
+// Objective and accuracy of the MLP on all the data (not part of an iteration): one launch takes every row of X through
+// all layers and leaves each row's loss and hit, a second adds them up per worker.
+//
+// The rows of all workers lie one after the other, so the data is one matrix.  A workgroup takes RT = 64 NR of its rows at a
+// time through the network: for every tile of UT = 128 NU units it sums W X^T over the inputs (split operands, three bf16 MFMA
+// products, float32 accumulators as in cada_mlp.hip), eight wavefronts of 32 NU units x 32 NR rows (4 x 2).  The weights are the
+// A operand, so a lane of the result holds ONE row and groups of four consecutive units: after bias and ReLU
+// these registers are, as they are, the operand of the last layer's product (whose sum over the units may take them in any order, as
+// long as the weights follow it).  With one hidden layer nothing but the row's loss leaves the chip; deeper networks
+// pass activations on through rows of scratch that belong to the workgroup (L2-resident, never read by another).
+// Operands go straight to LDS, one step of 32 inputs ahead of the products, over the boundaries of unit and row tiles.
+//
+// What bounds it: the MFMA issue (three products per weight and row; without any loads the launch below takes 630 us), then the
+// latency of the rows' loads (740 us when the rows lie in the L2).  It replaced a loop over chunks of M x B rows, each with five
+// launches that also staged the minibatch, the weights and their differences and evaluated the reference point.
+// Measured: 784-512-10 on 384000 rows 3.48 -> 0.90 ms (0.31 TFLOP, executed threefold: 1.04 PFLOP/s);
+// small minibatches, whose chunks were small too, 10.8 ms -> 73 us.
+#include <cstdlib>
+
+#include "cada_mlp.h"
+
+namespace cada {
+
+struct EvalLayer {
+  const bf16_t *Wh, *Wl;     // (out, in) chunks
+  int64_t kt;                // chunks per 128-unit tile
+  int64_t offb;
+  int nk, N;                 // steps of 32 inputs, units
+};
+
+struct EvalArgs {
+  DevState s;
+  const bf16_t *Xh, *Xl;     // [rows][ldx]
+  int64_t ldx, rows;
+  const bf16_t *zeros;       // 16 bytes of zeros
+  EvalLayer layer[CADA_MAX_LAYERS];
+  int L, C;
+  bf16_t *act[2][2];         // [layer parity][hi, lo]: activations [workgroup][RT][lda] (L >= 3)
+  int64_t lda;
+  float2 *rowval;            // [rows] (loss, hit)
+};
+
+// 16 bytes per lane straight to LDS (consecutive in lane order from byte `lds` on).  The compiler does not count these loads; the
+// step's barrier waits for them.
+__device__ __forceinline__ void to_lds(const bf16_t *g, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory");
+}
+__device__ __forceinline__ void to_lds(const bf16_t *base, uint32_t off, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory");
+}
+
+// HID: hidden layers (2: two or more)
+template <int NR, int NU, int HID>
+__global__ __launch_bounds__(512) void k_eval_net(const EvalArgs a) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  constexpr int RT = 64 * NR, UT = 128 * NU;
+  constexpr int STAGE = (RT + UT) * 128;                    // bytes: X hi, lo [RT][32], W hi, lo [UT][32]
+  float *logit_s = reinterpret_cast<float *>(smem_raw + 2 * STAGE);      // [RT][32], class c of row r at c ^ (r % 32)
+  const DevState &s = a.s;
+  const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int wu = w & 3, wr = w >> 2;                        // this wavefront's units and rows
+  const int half = lane >> 5, l32 = lane & 31;
+  const int ntiles = (int)((a.rows + RT - 1) / RT);
+  const int nhid = HID < 2 ? 1 : a.L - 1;                   // products in the steps below (no hidden layer: the logits are their result)
+  // A loading instruction fills 16 rows of 32 values of a tile: the lane at position `lane` fetches the piece that lds_piece puts there
+  const int piece = lds_piece(lane), prow = piece >> 2, pq = piece & 3;
+
+  // Loading cursor: (row tile, layer, unit tile, step).  Row addresses are a scalar plus this lane's part: rows past the last
+  // one are read as well (from what follows X's copies in the workspace: at least 256 rows of gathered ones) and dropped.
+  int ltile = blockIdx.x, ll = 0, lct = 0, lk = 0;
+  EvalLayer le = a.layer[0];
+  const bf16_t *src[2];                                     // hi, lo: first row of the tile
+  int64_t sld = 0;
+  uint32_t xoff = 0;
+  auto set_source = [&]() __attribute__((always_inline)) {
+    const bool first = HID < 2 || ll == 0;
+    sld = first ? a.ldx : a.lda;
+    xoff = (uint32_t)(prow * (int)sld + pq * 8) * 2u;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      src[h] = first ? (h ? a.Xl : a.Xh) + (int64_t)ltile * RT * sld : a.act[(ll - 1) & 1][h] + (int64_t)blockIdx.x * RT * sld;
+  };
+  auto load_step = [&](int buf) __attribute__((always_inline)) {
+    const uint32_t base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem_raw + (uint32_t)buf * STAGE;
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+      const int id = w * NR + i, lo = id >= 4 * NR, blk = id & (4 * NR - 1);
+      const bf16_t *row = (lo ? src[1] : src[0]) + (int64_t)(blk * 16) * sld + lk * 32;
+      if ((int64_t)lk * 32 + 32 > sld) {                    // rows of X end at a multiple of 8 values: zeros from there on
+        const bf16_t *g = lk * 32 + pq * 8 < (int)sld ? reinterpret_cast<const bf16_t *>(reinterpret_cast<const char *>(row) + xoff) : a.zeros;
+        to_lds(g, base + (uint32_t)id * 1024u);
+      } else {
+        to_lds(row, xoff, base + (uint32_t)id * 1024u);
+      }
+    }
+    const int last = (le.N + 127) / 128 - 1;
+#pragma unroll
+    for (int i = 0; i < 2 * NU; ++i) {
+      const int id = w * 2 * NU + i, lo = id >= 8 * NU, blk = id & (8 * NU - 1);
+      const int ut = min(lct * NU + (blk >> 3), last);      // (units past the last tile: any finite values)
+      to_lds((lo ? le.Wl : le.Wh) + (((int64_t)ut * le.kt + lk) << 12) + ((blk & 7) << 9), (uint32_t)piece * 16u, base + (uint32_t)(RT * 128 + id * 1024));
+    }
+  };
+  // next step; returns false where it is the first of a layer whose input is still being formed, or past the end
+  auto advance = [&](bool &done) __attribute__((always_inline)) -> bool {
+    if (++lk < le.nk) return true;
+    lk = 0;
+    if (++lct * UT < le.N) return true;
+    lct = 0;
+    if constexpr (HID == 2) {
+      if (++ll < nhid) { le = a.layer[ll]; set_source(); return false; }
+      ll = 0;
+      le = a.layer[0];
+    }
+    ltile += gridDim.x;
+    if (ltile >= ntiles) { done = true; return false; }
+    set_source();
+    return true;
+  };
+  auto landed = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+
+  if (ltile >= ntiles) return;
+  bool done = false;
+  int buf = 0;
+  set_source();
+  load_step(0);
+  landed();
+  for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    const int64_t r0 = (int64_t)tile * RT;
+    for (int l = 0; l < nhid; ++l) {
+      const EvalLayer e = a.layer[l];
+      for (int u0 = 0; u0 < e.N; u0 += UT) {
+        f32x16 acc[NU][NR];
+#pragma unroll
+        for (int i = 0; i < NU; ++i)
+#pragma unroll
+          for (int j = 0; j < NR; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+        bool ready = true;
+        for (int k = 0; k < e.nk; ++k) {
+          ready = advance(done);
+          if (ready) load_step(buf ^ 1);
+          const bf16_t *st = reinterpret_cast<const bf16_t *>(smem_raw + buf * STAGE);
+          const bf16_t *sx = st + (wr * 32 * NR) * 32, *sw = st + RT * 64 + (wu * 32 * NU) * 32;
+          const int fro = lds_piece(l32 * 4 + half) * 8;
+#pragma unroll
+          for (int ks = 0; ks < 32; ks += 16) {
+            bf16x8 wh[NU], wl[NU], xh[NR], xl[NR];
+#pragma unroll
+            for (int j = 0; j < NR; ++j) {
+              xh[j] = *reinterpret_cast<const bf16x8 *>(sx + j * 1024 + (fro ^ ks));
+              xl[j] = *reinterpret_cast<const bf16x8 *>(sx + RT * 32 + j * 1024 + (fro ^ ks));
+            }
+#pragma unroll
+            for (int i = 0; i < NU; ++i) {
+              wh[i] = *reinterpret_cast<const bf16x8 *>(sw + i * 1024 + (fro ^ ks));
+              wl[i] = *reinterpret_cast<const bf16x8 *>(sw + UT * 32 + i * 1024 + (fro ^ ks));
+            }
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+#pragma unroll
+              for (int i = 0; i < NU; ++i)
+#pragma unroll
+                for (int j = 0; j < NR; ++j)
+                  acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q == 1 ? wl[i] : wh[i], q == 0 ? xl[j] : xh[j], acc[i][j], 0, 0, 0);
+          }
+          landed();
+          buf ^= 1;
+        }
+        // accumulator element r of (i, j): unit ub + 32 i + 8 (r / 4) + r % 4, row 32 NR wr + 32 j + lane % 32
+        const int ub = u0 + wu * 32 * NU + 4 * half;
+        const int rl = wr * 32 * NR + l32;
+        if constexpr (HID == 0) {
+          if (wu == 0) {
+#pragma unroll
+            for (int j = 0; j < NR; ++j)
+#pragma unroll
+              for (int r = 0; r < 16; ++r) logit_s[(rl + 32 * j) * 32 + ((8 * (r >> 2) + 4 * half + (r & 3)) ^ l32)] = acc[0][j][r];
+          }
+          lds_sync();
+        } else {
+          // (one block of 32 units after the other: the registers hold the accumulators and the logits, but no more than
+          // one block's biases and weights)
+          float bias[16];
+          const __amdgpu_buffer_rsrc_t bias_buf = __builtin_amdgcn_make_buffer_rsrc(s.theta + e.offb, 0, e.N * 4, 0x00020000);
+          auto load_bias = [&](int i) __attribute__((always_inline)) {
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+              const int u = ub + 32 * i + 8 * g;
+              const v4s b4 = __builtin_bit_cast(v4s, __builtin_amdgcn_raw_buffer_load_b128(bias_buf, u * 4, 0, 0));      // (zero past the last unit)
+#pragma unroll
+              for (int q = 0; q < 4; ++q) bias[4 * g + q] = u + q < e.N ? b4[q] : -INFINITY;                    // (no such unit: its value is zero)
+            }
+          };
+          auto value = [&](int i, int j, int r) __attribute__((always_inline)) {
+            return fmaxf(acc[i][j][r] + bias[r], 0.f);
+          };
+          if (HID == 2 && l + 1 < nhid) {
+            bf16_t *dh = a.act[l & 1][0] + ((int64_t)blockIdx.x * RT + rl) * a.lda + ub, *dl = a.act[l & 1][1] + ((int64_t)blockIdx.x * RT + rl) * a.lda + ub;
+            const int ld = a.layer[l + 1].nk * 32;          // (the next layer's steps read whole groups of 32)
+#pragma unroll
+            for (int i = 0; i < NU; ++i) {
+              load_bias(i);
+#pragma unroll
+              for (int j = 0; j < NR; ++j)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                  float x[4];
+#pragma unroll
+                  for (int q = 0; q < 4; ++q) x[q] = value(i, j, 4 * g + q);
+                  uint2 hi, lo;
+                  hi.x = f2bf_pk(x[0], x[1]); hi.y = f2bf_pk(x[2], x[3]);
+                  lo.x = f2bf_pk(x[0] - __uint_as_float(hi.x << 16), x[1] - __uint_as_float(hi.x & 0xffff0000u));
+                  lo.y = f2bf_pk(x[2] - __uint_as_float(hi.y << 16), x[3] - __uint_as_float(hi.y & 0xffff0000u));
+                  if (ub + 32 * i + 8 * g < ld) {
+                    *reinterpret_cast<uint2 *>(dh + (int64_t)(32 * j) * a.lda + 32 * i + 8 * g) = hi;
+                    *reinterpret_cast<uint2 *>(dl + (int64_t)(32 * j) * a.lda + 32 * i + 8 * g) = lo;
+                  }
+                }
+            }
+          } else {
+            // the last layer's part from these units, from registers to registers: operand slots 8 half .. 8 half + 7 of a
+            // product over 16 units hold units {0-3, 8-11} + 4 half, and the weights are read in that order
+            const bf16_t *Vh = a.layer[a.L - 1].Wh, *Vl = a.layer[a.L - 1].Wl;
+            const int vkt = (int)a.layer[a.L - 1].kt;
+            f32x16 lg[NR];
+#pragma unroll
+            for (int j = 0; j < NR; ++j)
+#pragma unroll
+              for (int r = 0; r < 16; ++r) lg[j][r] = 0.f;
+#pragma unroll
+            for (int i = 0; i < NU; ++i) {
+              load_bias(i);
+              bf16x8 vh[2], vl[2];
+              const int64_t o = ((int64_t)min((ub + 32 * i) >> 5, vkt - 1) << 12) + l32 * 32 + 4 * half;
+#pragma unroll
+              for (int q = 0; q < 2; ++q) {
+                const uint2 h0 = *reinterpret_cast<const uint2 *>(Vh + o + 16 * q), h1 = *reinterpret_cast<const uint2 *>(Vh + o + 16 * q + 8);
+                const uint2 l0 = *reinterpret_cast<const uint2 *>(Vl + o + 16 * q), l1 = *reinterpret_cast<const uint2 *>(Vl + o + 16 * q + 8);
+                vh[q] = __builtin_bit_cast(bf16x8, u32x4{h0.x, h0.y, h1.x, h1.y});
+                vl[q] = __builtin_bit_cast(bf16x8, u32x4{l0.x, l0.y, l1.x, l1.y});
+              }
+#pragma unroll
+              for (int j = 0; j < NR; ++j) {
+                __builtin_amdgcn_sched_barrier(0);           // (conversions of one block at a time: registers)
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                  uint32_t hi[4], lo[4];
+#pragma unroll
+                  for (int b = 0; b < 4; ++b) {
+                    const float x0 = value(i, j, 8 * q + 2 * b), x1 = value(i, j, 8 * q + 2 * b + 1);
+                    hi[b] = f2bf_pk(x0, x1);
+                    lo[b] = f2bf_pk(x0 - __uint_as_float(hi[b] << 16), x1 - __uint_as_float(hi[b] & 0xffff0000u));
+                  }
+                  const bf16x8 ah = __builtin_bit_cast(bf16x8, u32x4{hi[0], hi[1], hi[2], hi[3]}), al = __builtin_bit_cast(bf16x8, u32x4{lo[0], lo[1], lo[2], lo[3]});
+                  lg[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vh[q], al, lg[j], 0, 0, 0);
+                  lg[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vl[q], ah, lg[j], 0, 0, 0);
+                  lg[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vh[q], ah, lg[j], 0, 0, 0);
+                }
+              }
+            }
+            // added up over the four wavefronts of the same rows, one after the other
+            if (u0 == 0) {
+              for (int i = t; i < RT * 32; i += 512) logit_s[i] = 0.f;
+              lds_sync();
+            }
+            for (int q = 0; q < 4; ++q) {
+              if (wu == q) {
+#pragma unroll
+                for (int j = 0; j < NR; ++j)
+#pragma unroll
+                  for (int r = 0; r < 16; ++r) {
+                    logit_s[(rl + 32 * j) * 32 + ((8 * (r >> 2) + 4 * half + (r & 3)) ^ l32)] += lg[j][r];
+                  }
+              }
+              lds_sync();
+            }
+          }
+        }
+        if (HID == 2 && !ready && !done) {       // the next layer reads what this one has just written
+          landed();
+          load_step(buf);
+          landed();
+        }
+      }
+    }
+    if (t < RT && r0 + t < a.rows) {
+      const int64_t r = r0 + t;
+      const int label = static_cast<const int32_t *>(s.y)[r];
+      const float *bl = s.theta + a.layer[a.L - 1].offb;
+      auto z = [&](int c) __attribute__((always_inline)) { return logit_s[t * 32 + (c ^ (t & 31))] + bl[c]; };
+      float zmax = -INFINITY, zl = 0.f;
+      int arg = 0;
+      for (int c = 0; c < a.C; ++c) {
+        const float x = z(c);
+        if (x > zmax) { zmax = x; arg = c; }
+        if (c == label) zl = x;
+      }
+      float den = 0.f;
+      for (int c = 0; c < a.C; ++c) den += expf(z(c) - zmax);
+      a.rowval[r] = make_float2(zmax + logf(den) - zl, arg == label ? 1.f : 0.f);
+    }
+    // (the next write of the logits is a barrier away)
+  }
+}
+
+// acc[m] = (mean loss, mean accuracy) of worker m's rows, added up in a fixed order.  One block per worker.
+__global__ __launch_bounds__(1024) void k_eval_sums(const DevState s, const float2 *rowval, double *acc) {
+  __shared__ double red[1024][2];
+  const int m = blockIdx.x, t = threadIdx.x;
+  const int64_t r0 = s.row_off[m], n = s.row_off[m + 1] - r0;
+  double loss = 0.0, hits = 0.0;
+  for (int64_t r = t; r < n; r += 1024) { const float2 v = rowval[r0 + r]; loss += (double)v.x; hits += (double)v.y; }
+  red[t][0] = loss; red[t][1] = hits;
+  __syncthreads();
+  for (int o = 512; o > 0; o >>= 1) {
+    if (t < o) { red[t][0] += red[t + o][0]; red[t][1] += red[t + o][1]; }
+    __syncthreads();
+  }
+  if (t < 2) acc[2 * m + t] = red[0][t] / (double)n;
+}
+
+namespace {
+using EvalKernel = void (*)(const EvalArgs);
+constexpr int kEvalGroups = 256;        // workgroups of a launch (one per CU) at most
+constexpr int eval_lds(int NR, int NU) { return 2 * (64 * NR + 128 * NU) * 128 + 64 * NR * 128; }
+template <int NU, int HID> EvalKernel eval_kernel_of(int NR) { return NR == 4 ? k_eval_net<4, NU, HID> : NR == 2 ? k_eval_net<2, NU, HID> : k_eval_net<1, NU, HID>; }
+EvalKernel eval_kernel(int NR, int NU, int L) {
+  if (L == 1) return eval_kernel_of<1, 0>(NR);             // (at most 32 classes)
+  if (L == 2) return NU == 2 ? eval_kernel_of<2, 1>(NR) : eval_kernel_of<1, 1>(NR);
+  if (NU == 2) return NR == 2 ? k_eval_net<2, 2, 2> : k_eval_net<1, 2, 2>;      // (256 x 256 would spill registers)
+  return eval_kernel_of<1, 2>(NR);
+}
+
+// Rows (64 NR) and units (128 NU) of a tile.  In cycles of a step a wavefront pair issues 2 x 3 x 2 x 32 per 32 x 32 block; 256 units
+// x 64 rows and 128 units x any rows wait for their operands instead (8 KB per 64 rows and 128 units at some 40 bytes per clock).  The
+// choice minimises rounds of tiles over the CUs times the time of a tile.
+void eval_tile(const MlpPlan &P, int *nr, int *nu) {
+  int64_t best = INT64_MAX;
+  for (int u = 1; u <= (P.L > 1 ? 2 : 1); ++u)
+    for (int r = 1; r <= (P.L > 2 && u == 2 ? 2 : 4); r *= 2) {
+      const int64_t tiles = (P.total_rows + 64 * r - 1) / (64 * r), rounds = (tiles + kEvalGroups - 1) / kEvalGroups;
+      int64_t per = 2000;      // end of a tile
+      for (int l = 1; l <= (P.L > 1 ? P.L - 1 : 1); ++l) {
+        const int64_t step = max(384 * u * r, 8192 * (u + 1 + r) / 40 + 200), ut = (P.d[l] + 128 * u - 1) / (128 * u);
+        per += ut * ((P.d[l - 1] + 31) / 32 * step + 2500);
+      }
+      if (rounds * per < best) { best = rounds * per; *nr = r; *nu = u; }
+    }
+}
+int64_t eval_groups(const MlpPlan &P, int nr) { return min((P.total_rows + 64 * nr - 1) / (64 * nr), (int64_t)kEvalGroups); }
+int64_t eval_lda(const MlpPlan &P) {     // values per row of the activations that pass through memory (0: none do)
+  int64_t w = 0;
+  for (int l = 1; l <= P.L - 2; ++l) w = max(w, (int64_t)(P.d[l] + 31) / 32 * 32);
+  return w;
+}
+}  // namespace
+
+// Scratch of the evaluation, behind everything else in the workspace.
+size_t mlp_eval_bytes(const MlpPlan &P) {
+  int nr, nu;
+  eval_tile(P, &nr, &nu);
+  const size_t row = ((size_t)P.total_rows * sizeof(float2) + 255) / 256 * 256;
+  return row + (size_t)eval_groups(P, nr) * 64 * nr * eval_lda(P) * sizeof(bf16_t) * 2 * (P.L > 3 ? 2 : 1);
+}
+
+int mlp_eval_init(Ctx *c) {
+  const MlpPlan &P = *static_cast<MlpPlan *>(c->mlp);
+  int nr, nu;
+  eval_tile(P, &nr, &nu);
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(eval_kernel(nr, nu, P.L)), hipFuncAttributeMaxDynamicSharedMemorySize, eval_lds(nr, nu));
+  if (e != hipSuccess) { set_error("hipFuncSetAttribute(LDS size) failed: %s", hipGetErrorString(e)); return CADA_EHIP; }
+  return CADA_OK;
+}
+
+int mlp_eval(Ctx *c, double *out) {
+  const MlpPlan &P = *static_cast<MlpPlan *>(c->mlp);
+  int nr, nu;
+  eval_tile(P, &nr, &nu);
+  EvalArgs a;
+  a.s = c->s;
+  a.s.k = c->k;
+  a.Xh = P.Xh; a.Xl = P.Xl; a.ldx = P.ldx; a.rows = P.total_rows;
+  a.zeros = P.XGh + tm(0, P.ldx, P.kta[0]);      // (columns from ldx on; not read where a row fills its chunks)
+  a.L = P.L; a.C = P.d[P.L];
+  for (int l = 0; l < P.L; ++l) {
+    a.layer[l].Wh = P.WTh + P.wt_off[l]; a.layer[l].Wl = P.WTl + P.wt_off[l]; a.layer[l].kt = P.kta[l];
+    a.layer[l].offb = P.offb[l]; a.layer[l].nk = (P.d[l] + 31) / 32; a.layer[l].N = P.d[l + 1];
+  }
+  a.rowval = reinterpret_cast<float2 *>(P.eval);
+  a.lda = eval_lda(P);
+  const int64_t groups = eval_groups(P, nr), n = groups * 64 * nr * a.lda;
+  bf16_t *act = reinterpret_cast<bf16_t *>(P.eval + ((size_t)P.total_rows * sizeof(float2) + 255) / 256 * 256);
+  for (int i = 0; i < 4; ++i) a.act[i >> 1][i & 1] = act + (P.L > 3 ? i : (i & 1)) * n;
+  mlp_stage_weights(c);
+  hipLaunchKernelGGL(eval_kernel(nr, nu, P.L), dim3((unsigned)groups), dim3(512), eval_lds(nr, nu), c->stream, a);
+  hipLaunchKernelGGL(k_eval_sums, dim3((unsigned)P.M), dim3(1024), 0, c->stream, a.s, a.rowval, c->eval_acc);
+  eval_finish(c, out, 0);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) { set_error("evaluation launch failed: %s", hipGetErrorString(e)); return CADA_EHIP; }
+  return CADA_OK;
+}
+
+}  // namespace cada

@@ -49,3 +49,33 @@ def test_objective_and_accuracy_match_oracle(cfg, tol):
     # the run continues unharmed after an evaluation
     eng.step(to_dev(sched[0].astype(np.int32)))
     torch.cuda.synchronize()
+
+
+# Networks at the edges of the evaluation kernel's tiles: depths 1 to 4, units on both sides of its 128- and 256-unit tiles, few and
+# many rows (64 to 256 per tile), inputs that end inside a group of 32.  The products' split operands (16 significant bits each)
+# leave about 1e-5 of a logit; the objective averages over rows.
+NETS = [((40, 10), 3, 77), ((41, 32), 2, 35001), ((61, 100, 7), 5, 333), ((61, 128, 7), 4, 9001), ((40, 257, 32), 2, 2100), ((39, 256, 2), 2, 20011),
+        ((24, 300, 10), 3, 33000), ((24, 130, 300, 40, 5), 3, 111), ((100, 260, 150, 5), 3, 9001), ((17, 96, 64, 3), 2, 18000),
+        ((41, 32), 2, 15000), ((61, 128, 7), 2, 15000), ((40, 257, 9), 2, 14000), ((24, 96, 64, 3), 2, 15000), ((24, 96, 64, 3), 2, 500)]
+
+
+@pytest.mark.parametrize("dims,M,n", NETS, ids=lambda v: "-".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_network_evaluation_at_tile_edges(dims, M, n):
+    cfg = configs.CFG4.scaled(name="net", layer_dims=dims, M=M, N_m=n, B=8, K=2, D=4)
+    prob = generators.make_problem(cfg)
+    X, y, th0 = upload(prob)
+    got = Cada.from_config(cfg, X, y, th0).evaluate().cpu().numpy()
+    z = prob.X.astype(np.float64)
+    at = 0
+    for l, (a, b) in enumerate(zip(dims, dims[1:])):
+        W, bias = prob.theta0[at:at + a * b].astype(np.float64).reshape(a, b), prob.theta0[at + a * b:at + a * b + b].astype(np.float64)
+        at += a * b + b
+        z = z @ W + bias
+        if l + 2 < len(dims):
+            z = np.maximum(z, 0.0)
+    top = z.max(axis=1, keepdims=True)
+    loss = (top[:, 0] + np.log(np.exp(z - top).sum(axis=1)) - z[np.arange(len(z)), prob.y.astype(np.int64)]).mean()
+    hits = (z.argmax(axis=1) == prob.y).mean()
+    print(dims, got, loss, hits)
+    assert abs(got[0] - loss) <= 2e-5 * abs(loss)
+    assert abs(got[1] - hits) <= 2.0 / (M * n) + 1e-4      # rows whose two best classes differ by rounding
