@@ -194,7 +194,7 @@ size_t state_bytes(const cada_config *cfg, const Geometry &g) {
 }
 void carve_logreg_scratch(Carver &w, const cada_config *cfg, Ctx *c) {
   float *rows_part = w.take<float>(rows_part_floats(cfg));
-  uint32_t *rows_count = w.take<uint32_t>(1 + (size_t)cfg->M);      // (zero between launches)
+  uint32_t *rows_count = w.take<uint32_t>(kCountWords * (1 + (size_t)cfg->M));      // (zero between launches)
   if (!c) return;
   c->rows_part = rows_part;
   c->rows_count = rows_count;
@@ -392,10 +392,11 @@ int cada_init(const cada_config *cfg, const float *theta0, cada_ctx **out) {
   if (cfg->model == CADA_MODEL_LOGREG) {
     // the requested path first; a request that the shape does not allow falls back to the others
     if (cfg->path == CADA_PATH_WHOLE_STEPS && small_plan(c, cfg)) s.n_ring_part = cfg->M;
-    else if (cfg->path != CADA_PATH_TWO_PASS && fused_plan(c, cfg)) s.n_lhs_part = kFusedWaves * c->fused_Q;
+    else if (cfg->path != CADA_PATH_TWO_PASS && !(cfg->path == CADA_PATH_AUTO && cfg->p <= kRowsWidest) && fused_plan(c, cfg)) s.n_lhs_part = kFusedWaves * c->fused_Q;
     else if (cfg->path == CADA_PATH_AUTO && small_plan(c, cfg)) s.n_ring_part = cfg->M;
     if (!c->small && !c->fused && rows_plan(c, cfg)) {
       c->n_phases = c->rows_server ? 1 : 2; c->phase_names[0] = "logreg_rows"; c->phase_names[1] = "server_update";
+      if (c->rows == 2) s.n_lhs_part = (int)((cfg->p + 1023) / 1024);
     } else if (c->small) {
       c->n_phases = 1; c->phase_names[0] = "logreg_whole_steps";
     } else if (c->fused && c->fused_tail_f > 0) {

@@ -164,20 +164,22 @@ __device__ __forceinline__ float block_sum_lds(float x, float *red /* [4] LDS */
 template <int CTRL>
 __device__ __forceinline__ float dpp_of(float x) { return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, true)); }
 
-// Sums over the 64 lanes of N = 4, 8 or 16 values at once.  Exchanges across lane ^ 1 and lane ^ 2 (N >= 8: and between the halves of
+// Sums over the 64 lanes of N = 2, 4, 8 or 16 values at once.  Exchanges across lane ^ 1 and lane ^ 2 (N >= 8: and between the halves of
 // the wavefront; N = 16: and between neighbouring rows of 16 lanes) halve the number of values, so that the
 // whole takes about 17, 27 or 47 instructions instead of N times twenty.  Lane l receives the sum of value
 // row_sums_index(l); row_sums_lane(v) is one lane that holds value v, row_sums_owner() the lanes that hold each value once.
 template <int N>
 __device__ __forceinline__ float row_sums(const float (&v)[N], int lane) {
-  static_assert(N == 4 || N == 8 || N == 16, "");
+  static_assert(N == 2 || N == 4 || N == 8 || N == 16, "");
   const bool o1 = lane & 1, o2 = lane & 2;
-  float a[N / 2], b[N / 4];
+  constexpr int NB = N == 2 ? 1 : N / 4;
+  float a[N / 2], b[NB];
 #pragma unroll
   for (int i = 0; i < N / 2; ++i) a[i] = (o1 ? v[2 * i + 1] : v[2 * i]) + dpp_of<0xB1>(o1 ? v[2 * i] : v[2 * i + 1]);
 #pragma unroll
-  for (int i = 0; i < N / 4; ++i) {
-    b[i] = (o2 ? a[2 * i + 1] : a[2 * i]) + dpp_of<0x4E>(o2 ? a[2 * i] : a[2 * i + 1]);
+  for (int i = 0; i < NB; ++i) {
+    if constexpr (N == 2) b[i] = dpp_add<0x4E>(a[i]);
+    else b[i] = (o2 ? a[2 * i + 1] : a[2 * i]) + dpp_of<0x4E>(o2 ? a[2 * i] : a[2 * i + 1]);
     b[i] = dpp_add<0x124>(b[i]);
     b[i] = dpp_add<0x128>(b[i]);
   }
@@ -190,15 +192,15 @@ __device__ __forceinline__ float row_sums(const float (&v)[N], int lane) {
     const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
     return __uint_as_float(q[0]) + __uint_as_float(q[1]);
   };
-  if constexpr (N == 4) { const float c = halves(b[0], b[0]); return rows(c, c); }
+  if constexpr (N <= 4) { const float c = halves(b[0], b[0]); return rows(c, c); }
   else if constexpr (N == 8) { const float c = halves(b[0], b[1]); return rows(c, c); }
   else return rows(halves(b[0], b[1]), halves(b[2], b[3]));
 }
 template <int N> __host__ __device__ constexpr int row_sums_index(int lane) {
-  return (lane & 3) + (N >= 8 ? 4 * (lane >> 5) : 0) + (N == 16 ? 8 * ((lane >> 4) & 1) : 0);
+  return (lane & (N == 2 ? 1 : 3)) + (N >= 8 ? 4 * (lane >> 5) : 0) + (N == 16 ? 8 * ((lane >> 4) & 1) : 0);
 }
 template <int N> __host__ __device__ constexpr int row_sums_lane(int v) { return (v & 3) + ((v & 4) ? 32 : 0) + ((v & 8) ? 16 : 0); }
-template <int N> __host__ __device__ constexpr bool row_sums_owner(int lane) { return (lane & ((N < 16 ? 16 : 0) | (N < 8 ? 32 : 0) | 12)) == 0; }
+template <int N> __host__ __device__ constexpr bool row_sums_owner(int lane) { return (lane & ((N < 16 ? 16 : 0) | (N < 8 ? 32 : 0) | 12 | (N < 4 ? 2 : 0))) == 0; }
 
 typedef float v4s __attribute__((ext_vector_type(4)));
 typedef float v4u __attribute__((ext_vector_type(4), aligned(4)));     // four floats at any 4-byte aligned address
@@ -242,6 +244,8 @@ __device__ __forceinline__ float server_coordinate(const DevState &s, float alph
   return step;
 }
 
+constexpr int kCountWords = 32;      // a counter that workgroups count in has a 128-byte line of its own
+
 // Host context.
 struct Ctx {
   DevState s;
@@ -274,10 +278,10 @@ struct Ctx {
   void *small_args;          // room in the workspace for this context's launch-invariant arguments (launches of several steps)
   void *small_args_host;     // their host copy (owned by the context)
   // one or two launches per step for rows of up to 8192 columns, cada_logreg_rows.hip
-  int rows, rows_shares, rows_per_share, rows_server;
+  int rows, rows_shares, rows_per_share, rows_per_worker, rows_server;      // (rows: 1, or 2 for more than 8192 columns)
   size_t rows_lds;
   float *rows_part;          // sums of the shares of a worker's rows
-  uint32_t *rows_count;      // [1 + M] counters
+  uint32_t *rows_count;      // [1 + M] counters, kCountWords apart
   // full-data evaluation scratch (cada_eval)
   double *eval_part;         // [M][kEvalBlocks][2] per-block sums of (loss, correct)
   double *eval_acc;          // [M][2]
@@ -297,6 +301,7 @@ void prof_mark(Ctx *c);
 int logreg_gradients(Ctx *c, const int32_t *idx);
 bool fused_plan(Ctx *c, const cada_config *cfg);
 int logreg_gradients_fused(Ctx *c, const int32_t *idx);
+constexpr int64_t kRowsWidest = 10 * 2048;          // columns of the widest row that a workgroup's registers hold
 bool rows_serves(const cada_config *cfg);
 size_t rows_part_floats(const cada_config *cfg);
 bool rows_plan(Ctx *c, const cada_config *cfg);

@@ -14,12 +14,14 @@
 // all workers, and, where M p is small, the server update.  The partial sums, gradients and left-hand sides that are passed on
 // inside the launch are written and read at device scope (past the XCD's cache).
 //
+// Wider rows, up to 20480 columns: k_rows_wide and k_rows_sum below, two launches and the server's.
+//
 // Why: the path replaces four to five dependent launches (two passes over the rows, [left-hand side of the LAG rule],
 // rule, server), each about 5 us of fetching arguments, code and first operands for well under 1 us of work.
 // Measured per step, against those launches: M = 10, p = 784, B = 60: 23.8 -> 16.2 us (15.5 in the kernel: operands and indices 3.3,
 // rows 2.9, share's sums 2.6, gradient 1.5, count 0.7, rule 1.0, aggregate 2.1, update 1.3); M = 10, p = 22, B = 92, LAG:
 // 23.8 -> 13.2 us; M = 100, B = 256, p = 4000 (410 MB of rows): 147 -> 87 us; p = 8192: 308 -> 164 us (5.1 TB/s).
-#include "cada_internal.h"
+#include "cada_rule.h"
 
 namespace cada {
 
@@ -31,28 +33,14 @@ struct RowsArgs {
   const int32_t *idx;        // [M][B]
   const uint8_t *replay;     // [M] or nullptr
   float *part;               // [M][shares][2][p rounded up to 4] sums of the shares (shares > 1)
-  uint32_t *count;           // [1 + M]: workers done; shares done of each worker (zero between launches)
+  uint32_t *count;           // [1 + M], kCountWords apart: workers done; shares done of each worker (zero between launches)
   int shares;                // workgroups per worker
-  int rows;                  // rows per share
+  int rows;                  // rows per share (at most)
+  int per;                   // k_rows_wide: shares of every worker, or 0
   int server;                // run the server update in this launch
 };
 
 __device__ __forceinline__ float sigmoid_r(float a) { return 1.0f / (1.0f + expf(-a)); }
-__device__ __forceinline__ void put_far(float *p, float x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ float get_far(const float *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-
-// Counts this workgroup in and says whether it is the last of n; called by all its threads, whose stores have then reached
-// the coherence point.  The last one resets the counter for the next launch.
-__device__ __forceinline__ bool last_of(uint32_t *count, uint32_t n, uint32_t *flag /* LDS */) {
-  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-  if (threadIdx.x == 0) {
-    const uint32_t seen = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    *flag = seen + 1 == n;
-    if (seen + 1 == n) __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-  lds_sync();
-  return *flag != 0;
-}
 
 // CW: 16-byte pieces of a row per lane; WC: wavefronts a row lies across; RB: rows per batch.
 // dynamic LDS: row offsets int64 [rows], labels [rows] (rounded up to four rows), sums [R_NW / WC][2][p]
@@ -242,7 +230,7 @@ __global__ __launch_bounds__(R_NT) void k_rows(const RowsArgs a) {
       store_far(part, (uint32_t)j * 4u, (uint32_t)(share * 2 * ps) * 4u, gs);
       store_far(part, (uint32_t)j * 4u, (uint32_t)((share * 2 + 1) * ps) * 4u, is);
     }
-    if (!last_of(a.count + 1 + m, (uint32_t)a.shares, &flag_s)) return;
+    if (!last_of(a.count + kCountWords * (1 + m), (uint32_t)a.shares, &flag_s)) return;
   }
   const int cur = s.sel[m];
   const __amdgpu_buffer_rsrc_t fresh = far_buffer(s.gbuf + (int64_t)(1 - cur) * mp + (int64_t)m * s.p, s.p);
@@ -392,6 +380,222 @@ __global__ __launch_bounds__(R_NT) void k_rows(const RowsArgs a) {
   }
 }
 
+// First row (of all workers' rows in order) of share c, and the share that holds row f; `per` shares for every worker, or (0) all rows
+// cut evenly into n shares.
+__device__ __forceinline__ int wide_first(const RowsArgs &a, int c) {
+  if (a.per) { const int m = c / a.per; return m * a.s.B + (int)((int64_t)(c - m * a.per) * a.s.B / a.per); }
+  return (int)((int64_t)c * a.s.M * a.s.B / a.shares);
+}
+__device__ __forceinline__ int wide_share(const RowsArgs &a, int f) {
+  if (a.per) { const int m = f / a.s.B; return m * a.per + (int)((((int64_t)(f - m * a.s.B) + 1) * a.per - 1) / a.s.B); }
+  return (int)((((int64_t)f + 1) * a.shares - 1) / ((int64_t)a.s.M * a.s.B));
+}
+
+// Rows of more than 8192 columns: a workgroup still takes whole rows (z and dz need no other workgroup, hence no cooperative launch and
+// no exchange, which cost the cluster kernel of cada_logreg_fused.hip some 50 us per step whatever the size), CW quads of each per lane.
+// What bounds it: HBM, at 4.2-5.3 TB/s, and 8 us of operands and sums at the two ends.  Measured per step, two passes or the cluster
+// kernel before: M = 37, B = 75, p = 20001, CADA1: 117 -> 79 us; p = 20000: 114 -> 77; M = 8, B = 256, p = 8196: 117 -> 39;
+// M = 100, B = 256, p = 20000 (2 GB of rows): 391 -> 387.  Rows without the non-temporal hint: 81, 79, 39, 433.
+// All workers' rows, one after the other, are cut into one share per workgroup (wide_split); a share that crosses from one worker to
+// the next starts new sums there.  The sums of workgroup c for worker m go to slot c + m (from one such pair to the next either c or m
+// is one more), and k_rows_sum adds a worker's slots up, one block per 1024 columns.  RB rows are worked on together with the next RB in flight.
+// DL: theta - theta_ref lies in LDS (the registers of 512 threads hold four vectors of 20480 columns and the rows in flight, not
+// five).  SEG: shares may meet several workers (up to 14336 columns: the loop over them costs wider rows registers, 51 -> 59 us).
+// dynamic LDS: row offsets int64 [rows], labels [rows] (rounded up to four rows), with DL theta - theta_ref [CW][512] quads
+template <int CW, int RB, bool DL, bool SEG>
+__global__ __launch_bounds__(R_NT) void k_rows_wide(const RowsArgs a) {
+  extern __shared__ __align__(16) unsigned char rows_smem[];
+  const DevState &s = a.s;
+  const int p = (int)s.p, ps = (p + 3) & ~3;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int64_t *off_s = reinterpret_cast<int64_t *>(rows_smem);
+  float *y_s = reinterpret_cast<float *>(off_s + ((a.rows + 3) & ~3));
+  v4s *d_s = reinterpret_cast<v4s *>(y_s + ((a.rows + 3) & ~3));
+  constexpr int NV = 2 * RB;
+  __shared__ float red_s[2][R_NW][NV];
+
+  const int f0 = wide_first(a, blockIdx.x), nr = wide_first(a, blockIdx.x + 1) - f0;        // this share's rows
+  for (int b = tid; b < nr; b += R_NT) {
+    const int m = (f0 + b) / s.B;
+    const int64_t base = s.row_off[m], n_m = s.row_off[m + 1] - base;
+    int64_t r = a.idx[f0 + b];
+    if (r < 0 || r >= n_m) { atomicOr(s.err, 1u); r = r < 0 ? 0 : n_m - 1; }
+    off_s[b] = (base + r) * s.p;
+    y_s[b] = static_cast<const float *>(s.y)[base + r];
+  }
+  lds_sync();
+  // columns as in k_rows: the quad that would reach past p ends at p, its first `dup` columns belong to the quad before
+  int j0 = (w * CW * kWave + lane) * 4;
+  uint32_t jb[CW];                                     // byte offsets
+  auto quad = [](const float *x, uint32_t off) __attribute__((always_inline)) { return *reinterpret_cast<const v4u *>(reinterpret_cast<const char *>(x) + off); };
+  float th[CW][4], dd[DL ? 1 : CW][4], g[CW][4], iv[CW][4];
+  v4u x[2][RB][CW];
+#pragma unroll
+  for (int i = 0; i < CW; ++i) {
+    jb[i] = (uint32_t)min(j0 + i * (4 * kWave), p - 4) * 4u;
+    const v4u t4 = quad(s.theta, jb[i]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) th[i][e] = t4[e];      // (zero in the columns of another quad: see below)
+  }
+  int seg = 0, end;                                    // rows of the worker that is worked on
+  auto load = [&](v4u (&xb)[RB][CW], int b0) __attribute__((always_inline)) {      // rows b0 .. b0 + RB - 1 (past the end: theta, with weight zero)
+#pragma unroll
+    for (int q = 0; q < RB; ++q) {
+      const int64_t o = off_s[min(b0 + q, end - 1)];
+      const float *row = s.X + (((int64_t)__builtin_amdgcn_readfirstlane((uint32_t)(o >> 32)) << 32) | __builtin_amdgcn_readfirstlane((uint32_t)o));
+      if (b0 + q >= end) row = s.theta;
+#pragma unroll
+      for (int i = 0; i < CW; ++i) xb[q][i] = __builtin_nontemporal_load(reinterpret_cast<const v4u *>(reinterpret_cast<const char *>(row) + jb[i]));
+    }
+  };
+  const float invB = 1.0f / (float)s.B;
+  auto work = [&](v4u (&xb)[RB][CW], int b0, int it) __attribute__((always_inline)) {
+    float zd[NV];
+#pragma unroll
+    for (int q = 0; q < NV; ++q) zd[q] = 0.f;
+#pragma unroll
+    for (int i = 0; i < CW; ++i) {
+      v4s d4;
+      if constexpr (DL) d4 = d_s[i * R_NT + tid];
+      else d4 = v4s{dd[i][0], dd[i][1], dd[i][2], dd[i][3]};
+#pragma unroll
+      for (int q = 0; q < RB; ++q)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { zd[2 * q] = fmaf(xb[q][i][e], th[i][e], zd[2 * q]); zd[2 * q + 1] = fmaf(xb[q][i][e], d4[e], zd[2 * q + 1]); }
+    }
+    float mine = row_sums<NV>(zd, lane);
+    const int v = row_sums_index<NV>(lane);
+    if (row_sums_owner<NV>(lane)) red_s[it & 1][w][v] = mine;
+    lds_sync();
+    mine = 0.f;
+#pragma unroll
+    for (int i = 0; i < R_NW; ++i) mine += red_s[it & 1][i][v];
+    const float other = dpp_of<0xB1>(mine);
+    const bool odd = lane & 1;
+    const int b = b0 + (v >> 1);
+    const float z = odd ? other : mine, dz = odd ? mine : other;
+    const float y = y_s[min(b, end - 1)];
+    const float aa = -y * z, bb = aa + y * dz;
+    const float sg = sigmoid_r(odd ? -bb : aa);        // even lanes sigma(aa), odd lanes sigma(-bb)
+    const float so = dpp_of<0xB1>(sg), em = expm1f(y * dz);
+    const float r = b < end ? (odd ? y * so * sg * em * invB : -y * sg * invB) : 0.f;      // even lanes r, odd lanes dr
+#pragma unroll
+    for (int q = 0; q < RB; ++q) {
+      const float rr = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(r), row_sums_lane<NV>(2 * q)));
+      const float dr = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(r), row_sums_lane<NV>(2 * q + 1)));
+#pragma unroll
+      for (int i = 0; i < CW; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { g[i][e] = fmaf(rr, xb[q][i][e], g[i][e]); iv[i][e] = fmaf(dr, xb[q][i][e], iv[i][e]); }
+    }
+  };
+  int it = 0;
+  do {
+    if constexpr (SEG) asm volatile("" : "+v"(j0));    // (what follows from it is formed here each time: registers)
+    const int m = (f0 + seg) / s.B;
+    end = min(nr, (m + 1) * s.B - f0);
+    const RefPtr ref = theta_ref(s, m, s.k);
+    load(x[0], seg);
+#pragma unroll
+    for (int i = 0; i < CW; ++i) {
+      if (SEG && i == (CW + 1) / 2) asm volatile("" ::: "memory");      // (half of the operands at a time: registers)
+      const v4u l4 = quad(s.theta_lo, jb[i]), rh = quad(ref.hi, jb[i]), rl = quad(ref.lo, jb[i]);
+      const int dup = j0 + i * (4 * kWave) - (int)(jb[i] >> 2);
+      v4s d4;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        d4[e] = e >= dup ? (th[i][e] - rh[e]) + (l4[e] - rl[e]) : 0.f;
+        if (e < dup) th[i][e] = 0.f;
+        if constexpr (!DL) dd[i][e] = d4[e];
+        g[i][e] = iv[i][e] = 0.f;
+      }
+      if constexpr (DL) d_s[i * R_NT + tid] = d4;              // (read back by this lane only)
+    }
+    // (no branch around the loads past the end: their registers then stay in place)
+    for (int b = seg; b < end; b += 2 * RB, it += 2) {
+      load(x[1], b + RB);
+      work(x[0], b, it);
+      if (b + RB >= end) break;
+      load(x[0], b + 2 * RB);
+      work(x[1], b + RB, it + 1);
+    }
+    float *pg = a.part + (int64_t)((int)blockIdx.x + m) * 2 * ps;
+#pragma unroll
+    for (int i = 0; i < CW; ++i) {
+      const int dup = j0 + i * (4 * kWave) - (int)(jb[i] >> 2);
+      float *q = reinterpret_cast<float *>(reinterpret_cast<char *>(pg) + jb[i]);
+      if (dup == 0) {
+        *reinterpret_cast<v4s *>(q) = v4s{g[i][0], g[i][1], g[i][2], g[i][3]};
+        *reinterpret_cast<v4s *>(q + ps) = v4s{iv[i][0], iv[i][1], iv[i][2], iv[i][3]};
+      } else {
+#pragma unroll
+        for (int e = 1; e < 4; ++e)
+          if (e >= dup) { q[e] = g[i][e]; q[ps + e] = iv[i][e]; }
+      }
+    }
+    seg = end;
+  } while (SEG && seg < nr);
+}
+
+// Adds up the shares of every worker in their order, adds the regulariser's terms, stores the fresh gradient (CADA1: and the fresh
+// innovation) and the left-hand side's partial sums; the block that finishes last runs the rule.  grid (ceil(p / 1024), M): four
+// columns per thread.  (The last quad may reach past p: it reads up to three floats of what follows in the workspace and drops them.)
+__global__ __launch_bounds__(kBlock) void k_rows_sum(const RowsArgs a) {
+  __shared__ float red[4];
+  __shared__ double red_d[4];
+  __shared__ uint32_t flag, cnt;
+  const DevState &s = a.s;
+  const int p = (int)s.p, ps = (p + 3) & ~3, m = blockIdx.y, rule = s.rule;
+  const int64_t mp = (int64_t)s.M * s.p;
+  const int j = (blockIdx.x * kBlock + threadIdx.x) * 4;
+  float sq = 0.f;
+  if (j < ps) {
+    const RefPtr ref = theta_ref(s, m, s.k);
+    const int cur = s.sel[m];
+    const int64_t o = (int64_t)m * s.p + j, of = (int64_t)(1 - cur) * mp + o, oc = (int64_t)cur * mp + o;
+    const v4u t4 = *reinterpret_cast<const v4u *>(s.theta + j), l4 = *reinterpret_cast<const v4u *>(s.theta_lo + j);
+    const v4u rh = *reinterpret_cast<const v4u *>(ref.hi + j), rl = *reinterpret_cast<const v4u *>(ref.lo + j);
+    v4u st = {0.f, 0.f, 0.f, 0.f};                     // CADA1: the stored innovation; LAG, always: the stored gradient
+    if (rule == CADA_RULE_CADA1) st = *reinterpret_cast<const v4u *>(s.dtl + oc);
+    else if (rule != CADA_RULE_CADA2) st = *reinterpret_cast<const v4u *>(s.gbuf + oc);
+    const int c0 = wide_share(a, m * s.B), shares = wide_share(a, (m + 1) * s.B - 1) - c0 + 1;
+    const float *pg = a.part + (int64_t)(c0 + m) * 2 * ps + j;
+    v4s gs = {0.f, 0.f, 0.f, 0.f}, is = gs;
+    for (int q0 = 0; q0 < shares; q0 += 8) {         // eight shares asked for before the first is added
+      v4s x[8], y[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const float *f = pg + (int64_t)min(q0 + q, shares - 1) * 2 * ps;
+        x[q] = *reinterpret_cast<const v4s *>(f);
+        y[q] = *reinterpret_cast<const v4s *>(f + ps);
+      }
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+        if (q0 + q < shares) { gs += x[q]; is += y[q]; }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      gs[e] = fmaf(s.lam, t4[e], gs[e]);
+      is[e] = fmaf(s.lam, (t4[e] - rh[e]) + (l4[e] - rl[e]), is[e]);
+      const float term = rule == CADA_RULE_CADA2 ? is[e] : (rule == CADA_RULE_CADA1 ? is[e] : gs[e]) - st[e];
+      if (j + e < p) sq = fmaf(term, term, sq);
+    }
+    if (j + 4 <= p) {
+      *reinterpret_cast<v4u *>(s.gbuf + of) = gs;
+      if (rule == CADA_RULE_CADA1) *reinterpret_cast<v4u *>(s.dtl + of) = is;
+    } else {
+      for (int e = 0; j + e < p; ++e) {
+        s.gbuf[of + e] = gs[e];
+        if (rule == CADA_RULE_CADA1) s.dtl[of + e] = is[e];
+      }
+    }
+  }
+  sq = block_sum_lds(sq, red);
+  if (threadIdx.x == 0) put_far(s.lhs_part + (int64_t)m * s.n_lhs_part + blockIdx.x, sq);
+  // (counted per worker first: a counter takes one arrival at a time)
+  if (last_of(a.count + kCountWords * (1 + m), gridDim.x, &flag) && last_of(a.count, gridDim.y, &flag)) rule_all<kBlock>(s, a.replay, red_d, &cnt);
+}
+
 namespace {
 using RowsKernel = void (*)(const RowsArgs);
 // the variant for rows of p columns: pieces per lane, wavefronts per row, rows per batch
@@ -403,6 +607,14 @@ RowsKernel rows_kernel(int64_t p, int *wc) {
   if (p <= 2048) return k_rows<1, 8, 8>;
   if (p <= 4096) return k_rows<2, 8, 4>;
   return k_rows<4, 8, 2>;
+}
+RowsKernel wide_kernel(int64_t p) {
+  if (p <= 5 * 2048) return k_rows_wide<5, 2, false, true>;
+  if (p <= 6 * 2048) return k_rows_wide<6, 2, false, true>;
+  if (p <= 7 * 2048) return k_rows_wide<7, 1, false, true>;
+  if (p <= 8 * 2048) return k_rows_wide<8, 1, true, false>;
+  if (p <= 9 * 2048) return k_rows_wide<9, 1, true, false>;
+  return k_rows_wide<10, 1, true, false>;
 }
 }  // namespace
 
@@ -417,31 +629,66 @@ static void rows_split(int M, int B, int64_t p, int *shares, int *rows) {
   *shares = (B + *rows - 1) / *rows;
 }
 
+// Rows of more than 8192 columns.  A workgroup fills a CU; the operands of a worker and the sums' way out cost it about as much as three
+// rows, and fifty workgroups' sums cost the whole launch another.  So many shares for every worker as make the rounds of CUs
+// cheapest, or, up to kWideEven columns and where it is less, all rows cut evenly over the CUs, although a share then may meet two
+// workers.  Measured, us per step with a share count per worker and cut evenly: M = 37, B = 75, p = 20001: 77, 92;
+// M = 100, B = 256, p = 10000: 220, 217; M = 100, B = 100, p = 8196: 113, 105.
+// (A share's row offsets and labels lie in LDS: 2048 rows at most.)
+constexpr int64_t kWideEven = 7 * 2048;
+static void wide_split(int M, int B, int64_t p, int *shares, int *rows, int *per) {
+  const int64_t T = (int64_t)M * B;
+  int64_t best = INT64_MAX;
+  for (int n = (B + 2047) / 2048; n <= 32 && n <= B; ++n) {
+    const int r = (B + n - 1) / n;
+    const int64_t cost = 50 * (((int64_t)M * n + 255) / 256) * (r + 3) + (int64_t)M * n;
+    if (cost < best) { best = cost; *shares = M * n; *rows = r; *per = n; }
+  }
+  const int64_t even = max(min((int64_t)256, T), (T + 2047) / 2048), most = (T + even - 1) / even;
+  if (p <= kWideEven && 50 * ((even + 255) / 256) * (most + 6) + even < best) { *shares = (int)even; *rows = (int)most; *per = 0; }
+}
+
 bool rows_serves(const cada_config *cfg) {
-  return cfg->model == CADA_MODEL_LOGREG && cfg->path != CADA_PATH_TWO_PASS && cfg->p >= 4 && cfg->p <= 8192;
+  return cfg->model == CADA_MODEL_LOGREG && cfg->path != CADA_PATH_TWO_PASS && cfg->p >= 4 && cfg->p <= kRowsWidest &&
+         (cfg->p <= 8192 || (int64_t)cfg->M * cfg->B < (1ll << 31) - 1);
 }
 size_t rows_part_floats(const cada_config *cfg) {
   if (!rows_serves(cfg)) return 0;
-  int shares, rows;
+  int shares, rows, per;
+  const size_t ps = (size_t)((cfg->p + 3) / 4 * 4);
+  if (cfg->p > 8192) {
+    wide_split(cfg->M, cfg->B, cfg->p, &shares, &rows, &per);
+    return (size_t)(cfg->M + shares) * 2 * ps;
+  }
   rows_split(cfg->M, cfg->B, cfg->p, &shares, &rows);
-  return shares > 1 ? (size_t)cfg->M * shares * 2 * (size_t)((cfg->p + 3) / 4 * 4) : 0;
+  return shares > 1 ? (size_t)cfg->M * shares * 2 * ps : 0;
 }
 
 bool rows_plan(Ctx *c, const cada_config *cfg) {
   c->rows = 0;
   if (!rows_serves(cfg)) return false;
-  rows_split(cfg->M, cfg->B, cfg->p, &c->rows_shares, &c->rows_per_share);
-  c->rows_server = cfg->M <= kRowsFusedWorkers && (int64_t)cfg->M * cfg->p <= kRowsFusedServer;
+  const bool wide = cfg->p > 8192;
+  const size_t ps = (size_t)((cfg->p + 3) / 4 * 4);
   int wc;
-  const RowsKernel fn = rows_kernel(cfg->p, &wc);
-  const size_t ps = (size_t)((cfg->p + 3) / 4 * 4), server = (size_t)((cfg->M + 15) & ~15) + ps * sizeof(float);
-  c->rows_lds = (size_t)((c->rows_per_share + 3) & ~3) * 12 + (size_t)(R_NW / wc) * 2 * ps * sizeof(float);
-  if (c->rows_server && c->rows_lds < server) c->rows_lds = server;
+  RowsKernel fn;
+  if (wide) {
+    wide_split(cfg->M, cfg->B, cfg->p, &c->rows_shares, &c->rows_per_share, &c->rows_per_worker);
+    c->rows_server = 0;
+    fn = wide_kernel(cfg->p);
+    c->rows_lds = (size_t)((c->rows_per_share + 3) & ~3) * 12 + (cfg->p > 7 * 2048 ? (size_t)((cfg->p + 2047) / 2048) * R_NT * sizeof(v4s) : 0);
+  } else {
+    rows_split(cfg->M, cfg->B, cfg->p, &c->rows_shares, &c->rows_per_share);
+    c->rows_server = cfg->M <= kRowsFusedWorkers && (int64_t)cfg->M * cfg->p <= kRowsFusedServer;
+    fn = rows_kernel(cfg->p, &wc);
+    const size_t server = (size_t)((cfg->M + 15) & ~15) + ps * sizeof(float);
+    c->rows_lds = (size_t)((c->rows_per_share + 3) & ~3) * 12 + (size_t)(R_NW / wc) * 2 * ps * sizeof(float);
+    if (c->rows_server && c->rows_lds < server) c->rows_lds = server;
+  }
   if (hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024) != hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
-  c->rows = 1;
+  c->rows = wide ? 2 : 1;
   return true;
 }
 
@@ -456,10 +703,13 @@ int logreg_step_rows(Ctx *c, const int32_t *idx, const uint8_t *replay) {
   a.count = c->rows_count;
   a.shares = c->rows_shares;
   a.rows = c->rows_per_share;
+  a.per = c->rows_per_worker;
   a.server = c->rows_server;
   int wc;
   prof_mark(c);
-  hipLaunchKernelGGL(rows_kernel(c->s.p, &wc), dim3((unsigned)a.shares, (unsigned)c->s.M), dim3(R_NT), c->rows_lds, c->stream, a);
+  hipLaunchKernelGGL(c->rows == 2 ? wide_kernel(c->s.p) : rows_kernel(c->s.p, &wc), dim3((unsigned)a.shares, c->rows == 2 ? 1u : (unsigned)c->s.M), dim3(R_NT), c->rows_lds, c->stream, a);
+  if (c->rows == 2)
+    hipLaunchKernelGGL(k_rows_sum, dim3((unsigned)((c->s.p + 1023) / 1024), (unsigned)c->s.M), dim3(kBlock), 0, c->stream, a);
   prof_mark(c);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) { set_error("logistic step launch failed: %s", hipGetErrorString(e)); return CADA_EHIP; }

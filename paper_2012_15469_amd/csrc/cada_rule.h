@@ -1,0 +1,101 @@
+// The rule's decisions for all workers, by the workgroup of a gradient kernel that finishes last: a launch of its own costs about
+// 5 us for under 1 us of work.
+#pragma once
+
+#include "cada_internal.h"
+
+namespace cada {
+
+__device__ __forceinline__ void put_far(float *p, float x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ float get_far(const float *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// Counts this workgroup in and says whether it is the last of n; called by all its threads, whose stores have then reached
+// the coherence point.  The last one resets the counter for the next launch.
+__device__ __forceinline__ bool last_of(uint32_t *count, uint32_t n, uint32_t *flag /* LDS */) {
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  if (threadIdx.x == 0) {
+    const uint32_t seen = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *flag = seen + 1 == n;
+    if (seen + 1 == n) __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  lds_sync();
+  return *flag != 0;
+}
+
+// S3 of the step, by the NT threads of one workgroup: right-hand side, left-hand sides from their partial sums (written
+// before by put_far, or by an earlier launch), decisions, tau, pointer swap, trace.  red: LDS [NT / 64]; cnt: LDS.
+// The wavefronts take workers in turn; sums are in double and in a fixed order.
+template <int NT>
+__device__ __forceinline__ void rule_all(const DevState &s, const uint8_t *replay, double *red, uint32_t *cnt) {
+  constexpr int NW = NT / kWave;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int64_t k = s.k;
+  const int last = k > 0 ? (int)((k - 1) % s.d_max) : -1;
+  // squared step of the iteration before: the sum of its blocks' parts
+  double acc = 0.0;
+  if (k > 0)
+    for (int i0 = tid; i0 < s.n_ring_part; i0 += 16 * NT) {
+      float v[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) { const int i = i0 + u * NT; v[u] = s.ring_part[min(i, s.n_ring_part - 1)]; if (i >= s.n_ring_part) v[u] = 0.f; }
+#pragma unroll
+      for (int u = 0; u < 16; ++u) acc += (double)v[u];
+    }
+  acc = wave_sum_f64(acc);
+  if (lane == 0) red[w] = acc;
+  if (tid == 0) *cnt = 0u;
+  lds_sync();
+  double sum = 0.0;
+#pragma unroll
+  for (int i = 0; i < NW; ++i) sum += red[i];
+  const float newest = (float)sum;
+  sum = 0.0;
+  for (int j = lane; j < s.d_max; j += kWave) sum += (double)(j == last ? newest : s.ring[j]);
+  const double rhs = (s.c / (double)s.d_max) * wave_sum_f64(sum);
+  const bool tr = k < s.trace_steps;
+  for (int m = w; m < s.M; m += NW) {
+    double lhs = 0.0;
+    const float *lp = s.lhs_part + (int64_t)m * s.n_lhs_part;
+    for (int t0 = lane; t0 < s.n_lhs_part; t0 += 16 * kWave) {       // sixteen loads in flight
+      float v[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) { const int t = t0 + u * kWave; v[u] = get_far(lp + min(t, s.n_lhs_part - 1)); if (t >= s.n_lhs_part) v[u] = 0.f; }
+#pragma unroll
+      for (int u = 0; u < 16; ++u) lhs += (double)v[u];
+    }
+    lhs = wave_sum_f64(lhs);
+    if (lane == 0) {
+      const int32_t tau = s.tau[m];
+      const bool own = (s.rule == CADA_RULE_ALWAYS) || (lhs > rhs) || (tau >= s.D);
+      bool up = own;
+      if (replay != nullptr && replay[m] != CADA_REPLAY_FREE) up = replay[m] != 0;
+      if (tr) {
+        const int64_t o = k * s.M + m;
+        s.t_mask[o] = up ? 1 : 0;
+        s.t_own[o] = own ? 1 : 0;
+        s.t_lhs[o] = (float)lhs;
+        s.t_tau[o] = tau;
+      }
+      s.lhs[m] = (float)lhs;
+      s.mask[m] = up ? 1 : 0;
+      s.tau[m] = up ? 1 : tau + 1;
+      if (up) {
+        s.sel[m] ^= 1;       // the fresh row becomes the stored one
+        atomicAdd(cnt, 1u);
+      } else if (s.rule == CADA_RULE_CADA2 && tau >= s.D) {
+        // (only a replay mask can do this: the reference point theta^{k+1-(tau+1)} leaves the D+1 retained iterates)
+        atomicOr(s.err, 8u);
+      }
+    }
+  }
+  lds_sync();
+  if (tid == 0) {
+    const uint32_t n = *cnt;
+    atomicAdd(reinterpret_cast<unsigned long long *>(s.uploads), (unsigned long long)n);
+    s.n_up[k & 1] = n;
+    if (last >= 0) s.ring[last] = newest;
+    if (tr) s.t_rhs[k] = (float)rhs;
+  }
+}
+
+}  // namespace cada

@@ -28,6 +28,14 @@ def test_rows_path(p, M, B, rule):
     assert stats["stored_rel_l2"] < 1e-5
 
 
+# more than 8192 columns: five to ten quads per lane, the last ones with theta - theta_ref in LDS; shares of one row and of many
+@pytest.mark.parametrize("p,M,B,rule", [
+    (8193, 3, 33, 1), (8196, 5, 64, 2), (10240, 2, 7, 2), (10243, 4, 50, 1), (12290, 3, 40, 3), (14336, 70, 6, 2), (14337, 3, 61, 2),
+    (16385, 9, 30, 1), (18433, 3, 45, 0), (20001, 6, 75, 1), (20478, 3, 100, 2), (20480, 2, 1, 1)])
+def test_wide_rows_path(p, M, B, rule):
+    test_rows_path(p, M, B, rule)
+
+
 def test_rows_path_flags_and_repeats():
     """An index out of range is clamped and flagged; two runs agree bit for bit."""
     from common import run_library
