@@ -397,8 +397,8 @@ __device__ __forceinline__ int wide_share(const RowsArgs &a, int f) {
 // kernel before: M = 37, B = 75, p = 20001, CADA1: 117 -> 79 us; p = 20000: 114 -> 77; M = 8, B = 256, p = 8196: 117 -> 39;
 // M = 100, B = 256, p = 20000 (2 GB of rows): 391 -> 387.  Rows without the non-temporal hint: 81, 79, 39, 433.
 // All workers' rows, one after the other, are cut into one share per workgroup (wide_split); a share that crosses from one worker to
-// the next starts new sums there.  The sums of workgroup c for worker m go to slot c + m (from one such pair to the next either c or m
-// is one more), and k_rows_sum adds a worker's slots up, one block per 1024 columns.  RB rows are worked on together with the next RB in flight.
+// the next starts new sums there.  The sums of workgroup c for worker m go to slot c or, where shares cross workers, c + m (from one such pair to the
+// next either c or m is one more), and k_rows_sum adds a worker's slots up, one block per 1024 columns.  RB rows are worked on together with the next RB in flight.
 // DL: theta - theta_ref lies in LDS (the registers of 512 threads hold four vectors of 20480 columns and the rows in flight, not
 // five).  SEG: shares may meet several workers (up to 14336 columns: the loop over them costs wider rows registers, 51 -> 59 us).
 // dynamic LDS: row offsets int64 [rows], labels [rows] (rounded up to four rows), with DL theta - theta_ref [CW][512] quads
@@ -519,7 +519,7 @@ __global__ __launch_bounds__(R_NT) void k_rows_wide(const RowsArgs a) {
       load(x[0], b + 2 * RB);
       work(x[1], b + RB, it + 1);
     }
-    float *pg = a.part + (int64_t)((int)blockIdx.x + m) * 2 * ps;
+    float *pg = a.part + (int64_t)((int)blockIdx.x + (SEG && a.per == 0 ? m : 0)) * 2 * ps;
 #pragma unroll
     for (int i = 0; i < CW; ++i) {
       const int dup = j0 + i * (4 * kWave) - (int)(jb[i] >> 2);
@@ -542,8 +542,8 @@ __global__ __launch_bounds__(R_NT) void k_rows_wide(const RowsArgs a) {
 // columns per thread.  (The last quad may reach past p: it reads up to three floats of what follows in the workspace and drops them.)
 __global__ __launch_bounds__(kBlock) void k_rows_sum(const RowsArgs a) {
   __shared__ float red[4];
-  __shared__ double red_d[4];
-  __shared__ uint32_t flag, cnt;
+  __shared__ double rule_s[rule_lds(kBlock) / sizeof(double)];
+  __shared__ uint32_t flag;
   const DevState &s = a.s;
   const int p = (int)s.p, ps = (p + 3) & ~3, m = blockIdx.y, rule = s.rule;
   const int64_t mp = (int64_t)s.M * s.p;
@@ -559,7 +559,7 @@ __global__ __launch_bounds__(kBlock) void k_rows_sum(const RowsArgs a) {
     if (rule == CADA_RULE_CADA1) st = *reinterpret_cast<const v4u *>(s.dtl + oc);
     else if (rule != CADA_RULE_CADA2) st = *reinterpret_cast<const v4u *>(s.gbuf + oc);
     const int c0 = wide_share(a, m * s.B), shares = wide_share(a, (m + 1) * s.B - 1) - c0 + 1;
-    const float *pg = a.part + (int64_t)(c0 + m) * 2 * ps + j;
+    const float *pg = a.part + (int64_t)(c0 + (a.per == 0 ? m : 0)) * 2 * ps + j;
     v4s gs = {0.f, 0.f, 0.f, 0.f}, is = gs;
     for (int q0 = 0; q0 < shares; q0 += 8) {         // eight shares asked for before the first is added
       v4s x[8], y[8];
@@ -593,7 +593,7 @@ __global__ __launch_bounds__(kBlock) void k_rows_sum(const RowsArgs a) {
   sq = block_sum_lds(sq, red);
   if (threadIdx.x == 0) put_far(s.lhs_part + (int64_t)m * s.n_lhs_part + blockIdx.x, sq);
   // (counted per worker first: a counter takes one arrival at a time)
-  if (last_of(a.count + kCountWords * (1 + m), gridDim.x, &flag) && last_of(a.count, gridDim.y, &flag)) rule_all<kBlock>(s, a.replay, red_d, &cnt);
+  if (last_of(a.count + kCountWords * (1 + m), gridDim.x, &flag) && last_of(a.count, gridDim.y, &flag)) rule_all<kBlock>(s, a.replay, rule_s);
 }
 
 namespace {
@@ -658,7 +658,7 @@ size_t rows_part_floats(const cada_config *cfg) {
   const size_t ps = (size_t)((cfg->p + 3) / 4 * 4);
   if (cfg->p > 8192) {
     wide_split(cfg->M, cfg->B, cfg->p, &shares, &rows, &per);
-    return (size_t)(cfg->M + shares) * 2 * ps;
+    return (size_t)(shares + (per ? 0 : cfg->M)) * 2 * ps;
   }
   rows_split(cfg->M, cfg->B, cfg->p, &shares, &rows);
   return shares > 1 ? (size_t)cfg->M * shares * 2 * ps : 0;

@@ -23,11 +23,15 @@ __device__ __forceinline__ bool last_of(uint32_t *count, uint32_t n, uint32_t *f
 }
 
 // S3 of the step, by the NT threads of one workgroup: right-hand side, left-hand sides from their partial sums (written
-// before by put_far, or by an earlier launch), decisions, tau, pointer swap, trace.  red: LDS [NT / 64]; cnt: LDS.
-// The wavefronts take workers in turn; sums are in double and in a fixed order.
+// before by put_far, or by an earlier launch), decisions, tau, pointer swap, trace.  Sums are in double and in a fixed order: a
+// wavefront takes four workers at a time (sixteen loads in flight), then a thread decides for one worker.
+// lds: rule_lds(NT) bytes.
+constexpr int rule_lds(int nt) { return (nt + nt / kWave + 1) * (int)sizeof(double); }
 template <int NT>
-__device__ __forceinline__ void rule_all(const DevState &s, const uint8_t *replay, double *red, uint32_t *cnt) {
+__device__ __forceinline__ void rule_all(const DevState &s, const uint8_t *replay, void *lds) {
   constexpr int NW = NT / kWave;
+  double *lhs_s = static_cast<double *>(lds), *red = lhs_s + NT;
+  uint32_t *cnt = reinterpret_cast<uint32_t *>(red + NW);
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int64_t k = s.k;
   const int last = k > 0 ? (int)((k - 1) % s.d_max) : -1;
@@ -44,51 +48,77 @@ __device__ __forceinline__ void rule_all(const DevState &s, const uint8_t *repla
   acc = wave_sum_f64(acc);
   if (lane == 0) red[w] = acc;
   if (tid == 0) *cnt = 0u;
-  lds_sync();
-  double sum = 0.0;
-#pragma unroll
-  for (int i = 0; i < NW; ++i) sum += red[i];
-  const float newest = (float)sum;
-  sum = 0.0;
-  for (int j = lane; j < s.d_max; j += kWave) sum += (double)(j == last ? newest : s.ring[j]);
-  const double rhs = (s.c / (double)s.d_max) * wave_sum_f64(sum);
+  double rhs = 0.0;
+  float newest = 0.f;
   const bool tr = k < s.trace_steps;
-  for (int m = w; m < s.M; m += NW) {
-    double lhs = 0.0;
-    const float *lp = s.lhs_part + (int64_t)m * s.n_lhs_part;
-    for (int t0 = lane; t0 < s.n_lhs_part; t0 += 16 * kWave) {       // sixteen loads in flight
-      float v[16];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) { const int t = t0 + u * kWave; v[u] = get_far(lp + min(t, s.n_lhs_part - 1)); if (t >= s.n_lhs_part) v[u] = 0.f; }
-#pragma unroll
-      for (int u = 0; u < 16; ++u) lhs += (double)v[u];
+  for (int mb = 0; mb < s.M; mb += NT) {
+    const int mine = mb + tid, mend = min(mb + NT, s.M);
+    int32_t tau = 0, sel = 0;
+    bool forced = false, up = false;
+    if (mine < s.M) {                                  // (asked for before the left-hand sides' parts)
+      tau = s.tau[mine]; sel = s.sel[mine];
+      if (replay != nullptr) { const uint8_t r = replay[mine]; forced = r != CADA_REPLAY_FREE; up = r != 0; }
     }
-    lhs = wave_sum_f64(lhs);
-    if (lane == 0) {
-      const int32_t tau = s.tau[m];
+    for (int m0 = mb + 4 * w; m0 < mend; m0 += 4 * NW) {
+      double l[4] = {0.0, 0.0, 0.0, 0.0};
+      for (int t0 = lane; t0 < s.n_lhs_part; t0 += 4 * kWave) {
+        float v[4][4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int t = t0 + u * kWave;
+            v[q][u] = get_far(s.lhs_part + (int64_t)min(m0 + q, s.M - 1) * s.n_lhs_part + min(t, s.n_lhs_part - 1));
+            if (t >= s.n_lhs_part) v[q][u] = 0.f;
+          }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) l[q] += (double)v[q][u];
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        l[q] = wave_sum_f64(l[q]);
+        if (lane == 0 && m0 + q < mend) lhs_s[m0 + q - mb] = l[q];
+      }
+    }
+    lds_sync();
+    if (mb == 0) {
+      double sum = 0.0;
+#pragma unroll
+      for (int i = 0; i < NW; ++i) sum += red[i];
+      newest = (float)sum;
+      sum = 0.0;
+      for (int j = lane; j < s.d_max; j += kWave) sum += (double)(j == last ? newest : s.ring[j]);
+      rhs = (s.c / (double)s.d_max) * wave_sum_f64(sum);
+    }
+    uint32_t ups = 0;
+    if (mine < s.M) {
+      const double lhs = lhs_s[tid];
       const bool own = (s.rule == CADA_RULE_ALWAYS) || (lhs > rhs) || (tau >= s.D);
-      bool up = own;
-      if (replay != nullptr && replay[m] != CADA_REPLAY_FREE) up = replay[m] != 0;
+      if (!forced) up = own;
       if (tr) {
-        const int64_t o = k * s.M + m;
+        const int64_t o = k * s.M + mine;
         s.t_mask[o] = up ? 1 : 0;
         s.t_own[o] = own ? 1 : 0;
         s.t_lhs[o] = (float)lhs;
         s.t_tau[o] = tau;
       }
-      s.lhs[m] = (float)lhs;
-      s.mask[m] = up ? 1 : 0;
-      s.tau[m] = up ? 1 : tau + 1;
+      s.lhs[mine] = (float)lhs;
+      s.mask[mine] = up ? 1 : 0;
+      s.tau[mine] = up ? 1 : tau + 1;
       if (up) {
-        s.sel[m] ^= 1;       // the fresh row becomes the stored one
-        atomicAdd(cnt, 1u);
+        s.sel[mine] = sel ^ 1;       // the fresh row becomes the stored one
+        ups = 1;
       } else if (s.rule == CADA_RULE_CADA2 && tau >= s.D) {
         // (only a replay mask can do this: the reference point theta^{k+1-(tau+1)} leaves the D+1 retained iterates)
         atomicOr(s.err, 8u);
       }
     }
+    const unsigned long long votes = __ballot(ups != 0);
+    if (lane == 0 && votes) atomicAdd(cnt, (uint32_t)__popcll(votes));
+    lds_sync();
   }
-  lds_sync();
   if (tid == 0) {
     const uint32_t n = *cnt;
     atomicAdd(reinterpret_cast<unsigned long long *>(s.uploads), (unsigned long long)n);
