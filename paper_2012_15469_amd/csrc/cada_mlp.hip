@@ -89,6 +89,7 @@ struct Mm5Args {
   // EPI_DW
   int64_t offW;
   int lhs_slot0;
+  int nband;                            // k_mm5: 64-row bands of dbpart / ddbpart, of which the tiles of the first row band form the layer's bias gradient (0: not here)
   // EPI_LOSS (last layer's forward product with the loss in its epilogue; outputs o_h/o_l/o_d/o_r, bias at offb) and the
   // last layer's EPI_DW, which finishes that layer's bias gradient from the row blocks' sums
   const int64_t *grow;                  // global row of every padded minibatch row (its label)
@@ -552,6 +553,24 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
           }
       }
       asm volatile("" ::: "memory");
+    }
+    // The tiles of the first 128 units also form the layer's bias gradient and its innovation, from the sums that the
+    // activation-gradient launch left per band of 64 rows: this wavefront's 64 columns, one per lane.  (A launch of its own
+    // cost 5 us.)  Their part of the left-hand side goes with the tile's; the slots of their own stay zero.
+    if (g.nband > 0 && by == 0 && wy == 0) {
+      const int col = n0 + wx * 64 + lane;
+      if (col < g.N) {
+        const float *db = g.dbpart + (int64_t)wk * g.nband * g.N + col, *dd = g.ddbpart + (int64_t)wk * g.nband * g.N + col;
+        float gsum = 0.f, dsum = 0.f;
+        for (int i = 0; i < g.nband; ++i) { gsum += db[(int64_t)i * g.N]; dsum += dd[(int64_t)i * g.N]; }
+        put_fresh_grad(s, wk, g.offb + col, gsum);
+        if (cada1) {
+          fresh_innov(s, wk)[g.offb + col] = f2bf(dsum);
+          dsum -= bf2f(stored_innov(s, wk)[g.offb + col]);
+        }
+        sq = fmaf(dsum, dsum, sq);
+        if ((col & 255) == 0) s.lhs_part[(int64_t)wk * s.n_lhs_part + g.lhs_slot_b + (col >> 8)] = 0.f;
+      }
     }
     const float tot = wave_sum(sq);           // one partial sum of the left-hand side per wavefront and tile
     if (lane == 0) s.lhs_part[(int64_t)wk * s.n_lhs_part + g.lhs_slot0 + (by * gx + bx) * 4 + w] = tot;
@@ -1388,6 +1407,8 @@ int mlp_gradients(Ctx *c, const int32_t *idx) {
       g.offW = P.offW[l - 1]; g.lhs_slot0 = P.lhs_w_slot[l - 1];
       if (l == L) {     // the last layer's launch also finishes its bias gradient from the forward launch's row-block sums
         g.lastb = P.lastb; g.nrb = Bp / 32; g.offb = P.offb[L - 1]; g.lhs_slot_b = P.lhs_b_slot[L - 1];
+      } else if (dout > 32) {       // and the other layers' from the activation-gradient launch's sums
+        g.dbpart = P.dbpart; g.ddbpart = P.ddbpart; g.nband = 2 * P.RT; g.offb = P.offb[l - 1]; g.lhs_slot_b = P.lhs_b_slot[l - 1];
       }
       if (const int rc = launch_mm5<EPI_DW>(c, g, M)) return rc;
     }
@@ -1409,7 +1430,8 @@ int mlp_gradients(Ctx *c, const int32_t *idx) {
       g.maskbits = P.maskbits[q];
       g.dbpart = P.dbpart; g.ddbpart = P.ddbpart;
       if (const int rc = launch_mm5<EPI_DA>(c, g, M)) return rc;
-      hipLaunchKernelGGL(k_bias_finish, dim3((din + 255) / 256, M), dim3(kBlock), 0, st, s, P.dbpart, P.ddbpart, 2 * P.RT, din,
+      if (din <= 32)      // (k_skinny serves that layer's weight gradient)
+        hipLaunchKernelGGL(k_bias_finish, dim3((din + 255) / 256, M), dim3(kBlock), 0, st, s, P.dbpart, P.ddbpart, 2 * P.RT, din,
                          P.offb[q - 1], P.lhs_b_slot[q - 1]);
     }
   }
