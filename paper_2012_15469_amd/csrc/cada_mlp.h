@@ -11,7 +11,7 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 typedef uint16_t bf16_t;   // storage type
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));   // four floats at any 4-byte aligned address
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // 16 bytes in flight (a native vector: stays in registers)
-typedef uint32_t u32x2u __attribute__((ext_vector_type(2), aligned(4)));   // four bf16 values at any 4-byte aligned address
+typedef uint32_t u32x2u __attribute__((ext_vector_type(2), aligned(2)));   // four bf16 values at any address (one access: the target runs in its unaligned mode)
 
 static inline int64_t P8(int64_t x) { return (x + 7) / 8 * 8; }
 

@@ -131,6 +131,10 @@ __device__ __forceinline__ u32x4 pack8(const bf16_t (&v)[8]) {
 
 // NA, NB: tensors on the A and the B side (compile-time, so that the loads of a tile step are a
 // fixed number of instructions and the waits can count them).  HAS_D: the product Ad Bx^T is present.
+// NB == 2 (PL): the rule evaluates no second gradient (always, LAG), so there is no C2 and no difference is carried: three products
+// and four operands instead of five and seven.  (The LAG rule's left-hand side stays a launch of its own, k_lag_lhs: the stored
+// gradients read in this epilogue made it 12 us longer for the 10 us of that launch, and the server found nothing in the
+// caches, 7 -> 11 us; 617-301-150-26, 24 workers.)
 //
 // A workgroup has eight wavefronts in two roles and works through several tiles.  Wavefronts 4-7
 // move chunks from global memory straight into LDS (16-byte LDS-direct loads: no registers, no
@@ -169,6 +173,7 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
   bf16_t *lds = reinterpret_cast<bf16_t *>(smem_raw);
   constexpr int NS = NA + NB, NSLOT = kMm5Slots;
   constexpr bool TR = EPI == EPI_DW;          // operands are (row, unit) tensors read across the rows
+  constexpr bool PL = NB == 2;
   static_assert(NSLOT >= 2 * NS, "the ring must hold two tile steps");
   const DevState &s = g.s;
   const bool mover = __builtin_amdgcn_readfirstlane((int)threadIdx.x) >= kBlock;   // uniform per wavefront
@@ -274,7 +279,7 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     auto slot_of = [&](int idx) __attribute__((always_inline)) { const int p = sb + idx; return lds + ((size_t)(p >= NSLOT ? p - NSLOT : p) << 12); };
     const bf16_t *tah = slot_of(g.a_h), *tal = slot_of(g.a_l), *tad = slot_of(HAS_D ? g.a_d : 0), *tar = slot_of(NA == 4 ? g.a_r : 0);
-    const bf16_t *tbh = slot_of(NA + g.b_h), *tbl = slot_of(NA + g.b_l), *tbx = slot_of(NA + (HAS_D && NB == 4 ? g.b_x : 0)), *tbd = slot_of(NA + g.b_d);
+    const bf16_t *tbh = slot_of(NA + g.b_h), *tbl = slot_of(NA + g.b_l), *tbx = slot_of(NA + (HAS_D && NB == 4 ? g.b_x : 0)), *tbd = slot_of(PL ? NA : NA + g.b_d);
 #pragma unroll
     for (int ks = 0; ks < BK; ks += 16) {
       bf16x8 ah[2], al[2], ad[2], ar[2], bh[2], bl[2], bx_[2], bd[2];
@@ -301,7 +306,7 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
           if constexpr (NB == 4) bx_[j] = frag(tbx, wx, j);
           else bx_[j] = bh[j];
         }
-        bd[j] = frag(tbd, wx, j);
+        if constexpr (!PL) bd[j] = frag(tbd, wx, j);
       }
 #pragma unroll
       for (int i = 0; i < 2; ++i)
@@ -311,7 +316,7 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
           acc1[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[i], bl[j], acc1[i][j], 0, 0, 0);
           acc1[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[i], bh[j], acc1[i][j], 0, 0, 0);
           if constexpr (HAS_D) acc2[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ad[i], bx_[j], acc2[i][j], 0, 0, 0);
-          acc2[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ar[i], bd[j], acc2[i][j], 0, 0, 0);
+          if constexpr (!PL) acc2[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ar[i], bd[j], acc2[i][j], 0, 0, 0);
         }
     }
     sb = sb + NS >= NSLOT ? sb + NS - NSLOT : sb + NS;
@@ -339,7 +344,7 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
     auto copy_out = [&](bf16_t *const (&dst)[4], int64_t goff) __attribute__((always_inline)) {
       asm volatile("" ::: "memory");
 #pragma unroll
-      for (int b = 0; b < 4; ++b)
+      for (int b = 0; b < (PL ? 2 : 4); ++b)
         if (dst[b] != nullptr) {
 #pragma unroll
           for (int hh = 0; hh < 2; ++hh) {
@@ -370,7 +375,7 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
       for (int j = 0; j < 2; ++j) {
         const int col = min(cbase + j * 32, g.N - 1);
         bias[j] = s.theta[g.offb + col];
-        dbias[j] = delta_theta(s, ref, g.offb + col);
+        if constexpr (!PL) dbias[j] = delta_theta(s, ref, g.offb + col);
       }
     }
 #pragma unroll
@@ -393,12 +398,13 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
             x[e] = 0.f; xref[e] = 0.f;
             if (cok && row < g.M) {
               if constexpr (EPI == EPI_FWD_HIDDEN) {
-                const float z = acc1[i][j][r] + b, dz = acc2[i][j][r] + db;
-                x[e] = fmaxf(z, 0.f); xref[e] = fmaxf(z - dz, 0.f);
+                const float z = acc1[i][j][r] + b;
+                x[e] = fmaxf(z, 0.f);
+                if constexpr (!PL) xref[e] = fmaxf(z - (acc2[i][j][r] + db), 0.f);
               } else {
-                const float ga = acc1[i][j][r], dga = acc2[i][j][r];
+                const float ga = acc1[i][j][r];
                 x[e] = (bit_on >> ((i * 2 + j) * 16 + r)) & 1 ? ga : 0.f;
-                xref[e] = (bit_ref >> ((i * 2 + j) * 16 + r)) & 1 ? (ga - dga) : 0.f;
+                if constexpr (!PL) xref[e] = (bit_ref >> ((i * 2 + j) * 16 + r)) & 1 ? (ga - acc2[i][j][r]) : 0.f;
               }
             }
             sg_sum += x[e]; sd_sum += x[e] - xref[e];
@@ -410,7 +416,7 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
           if constexpr (EPI == EPI_FWD_HIDDEN) {      // (the sign of the stored, rounded value)
             const int sh = (i * 2 + j) * 16 + 2 * rp;
             bit_on |= (uint64_t)((__uint_as_float(vh << 16) > 0.f ? 1u : 0u) | (__uint_as_float(vh & 0xffff0000u) > 0.f ? 2u : 0u)) << sh;
-            bit_ref |= (uint64_t)((__uint_as_float(vr << 16) > 0.f ? 1u : 0u) | (__uint_as_float(vr & 0xffff0000u) > 0.f ? 2u : 0u)) << sh;
+            if constexpr (!PL) bit_ref |= (uint64_t)((__uint_as_float(vr << 16) > 0.f ? 1u : 0u) | (__uint_as_float(vr & 0xffff0000u) > 0.f ? 2u : 0u)) << sh;
           }
         }
         // (row, column) layout: element (rl, cl) of the quarter at 32 rl + cl
@@ -419,7 +425,7 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
           for (int r = 0; r < 16; ++r) {
             const int e = (8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * 32 + (lane & 31), sh = 16 * (r & 1);
             sg[e] = (bf16_t)(ph[r >> 1] >> sh); sg[1024 + e] = (bf16_t)(pl[r >> 1] >> sh);
-            sg[2048 + e] = (bf16_t)(pd[r >> 1] >> sh); sg[3072 + e] = (bf16_t)(pr[r >> 1] >> sh);
+            if constexpr (!PL) { sg[2048 + e] = (bf16_t)(pd[r >> 1] >> sh); sg[3072 + e] = (bf16_t)(pr[r >> 1] >> sh); }
           }
           copy_out(orow_t, tm(rp0 + wr0 + i * 32, wc0 + j * 32, g.kto));
         }
@@ -432,7 +438,7 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
         if (lane < 32 && cok) {
           const int64_t o = ((int64_t)wk * (2 * gy) + 2 * by + wy) * g.N + col;
           g.dbpart[o] = sg_sum;
-          g.ddbpart[o] = sd_sum;
+          if constexpr (!PL) g.ddbpart[o] = sd_sum;
         }
       }
     }
@@ -453,15 +459,15 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
     const bool g16 = s.gbuf16 != nullptr;
     float *gf = g16 ? nullptr : fresh_grad(s, wk) + g.offW;
     bf16_t *gf16 = g16 ? fresh_grad16(s, wk) + g.offW : nullptr;
-    const bool cada1 = s.rule == CADA_RULE_CADA1;
+    const bool cada1 = !PL && s.rule == CADA_RULE_CADA1;
     bf16_t *ivf = cada1 ? fresh_innov(s, wk) + g.offW : nullptr;
     const bf16_t *ivs = cada1 ? stored_innov(s, wk) + g.offW : nullptr;
     // row-wise pass: this lane has columns c4 .. c4+3 of the band's rows rr + 4 it, it = 0..7
     const int c4 = (lane & 15) * 4, rr = lane >> 4;
     const int colg = n0 + wx * 64 + c4;
-    // every column of this wavefront's part exists: 16-byte accesses (4-byte aligned; with stored bf16
-    // innovations or gradients their 8-byte accesses need an even offset and row length for that)
-    const bool wide = n0 + wx * 64 + 64 <= g.N && (!(cada1 || g16) || ((g.offW | (int64_t)g.N) & 1) == 0);
+    // every column of this wavefront's part exists: 16-byte accesses (8 bytes of bf16), whatever the rows' alignment; a part that
+    // overhangs the matrix goes element by element, but asks for all its stored values first, too
+    const bool wide = n0 + wx * 64 + 64 <= g.N;
     auto put_band = [&](const f32x16 (&acc)[2]) __attribute__((always_inline)) {
 #pragma unroll
       for (int j = 0; j < 2; ++j)
@@ -473,15 +479,26 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
     // (rows clamped into the matrix so that no load sits under a branch).  Gradients and innovations
     // are written once and read once per step, megabytes apart in time: non-temporal accesses.
     u32x2u old[2][8];        // four bf16 values each
-    if (cada1 && wide) {
+    if (cada1) {
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int it = 0; it < 8; ++it) {
-          const int row = min(m0 + wy * 64 + i * 32 + rr + 4 * it, g.M - 1);
-          old[i][it] = *reinterpret_cast<const u32x2u *>(ivs + (int64_t)row * g.N + colg);
+          const bf16_t *row = ivs + (int64_t)min(m0 + wy * 64 + i * 32 + rr + 4 * it, g.M - 1) * g.N;
+          if (wide) {
+            old[i][it] = *reinterpret_cast<const u32x2u *>(row + colg);
+          } else {
+            uint32_t e[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) e[q] = row[min(colg + q, g.N - 1)];
+            old[i][it].x = e[0] | (e[1] << 16); old[i][it].y = e[2] | (e[3] << 16);
+          }
         }
     }
+    auto old_of = [&](int i, int it, int e) __attribute__((always_inline)) {      // value e of old[i][it]
+      const uint32_t o = e < 2 ? old[i][it].x : old[i][it].y;
+      return __uint_as_float((e & 1) ? o & 0xffff0000u : o << 16);
+    };
     // The innovation first, the gradient last: the innovation's part waits for the loads of the stored
     // innovations (and a wait for a load also waits for every store issued before it), whereas nothing
     // in this tile waits behind the gradient's stores: they drain while the next tile's products run.
@@ -489,6 +506,7 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const int rowb = m0 + wy * 64 + i * 32 + rr;
+      if constexpr (PL) break;
       if (!cada1) {       // nothing to store or to subtract: the squared norm needs no particular order of the elements
 #pragma unroll
         for (int j = 0; j < 2; ++j)
@@ -514,15 +532,17 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
             sq = fmaf(v.x, v.x, sq); sq = fmaf(v.y, v.y, sq); sq = fmaf(v.z, v.z, sq); sq = fmaf(v.w, v.w, sq);
           }
         }
-      } else if (colg < g.N) {                 // a part that overhangs the matrix: element by element
-        for (int it = 0; it < 8 && rowb + 4 * it < g.M; ++it)
-          for (int e = 0; e < 4 && colg + e < g.N; ++e) {
-            const int64_t o = (int64_t)(rowb + 4 * it) * g.N + colg + e;
-            float iv = st[(rr + 4 * it) * SP + c4 + e];
-            ivf[o] = f2bf(iv);
-            iv -= bf2f(ivs[o]);
-            sq = fmaf(iv, iv, sq);
-          }
+      } else {                                 // a part that overhangs the matrix: element by element
+#pragma unroll
+        for (int it = 0; it < 8; ++it)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (rowb + 4 * it < g.M && colg + e < g.N) {
+              const float iv = st[(rr + 4 * it) * SP + c4 + e];
+              ivf[(int64_t)(rowb + 4 * it) * g.N + colg + e] = f2bf(iv);
+              const float d = iv - old_of(i, it, e);
+              sq = fmaf(d, d, sq);
+            }
       }
       asm volatile("" ::: "memory");
     }
@@ -544,13 +564,16 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
             }
           }
         }
-      } else if (colg < g.N) {
-        for (int it = 0; it < 8 && rowb + 4 * it < g.M; ++it)
-          for (int e = 0; e < 4 && colg + e < g.N; ++e) {
-            const int64_t o = (int64_t)(rowb + 4 * it) * g.N + colg + e;
-            const float v = st[(rr + 4 * it) * SP + c4 + e];
-            if (g16) gf16[o] = f2bf(v); else gf[o] = v;
-          }
+      } else {
+#pragma unroll
+        for (int it = 0; it < 8; ++it)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (rowb + 4 * it < g.M && colg + e < g.N) {
+              const int64_t o = (int64_t)(rowb + 4 * it) * g.N + colg + e;
+              const float v = st[(rr + 4 * it) * SP + c4 + e];
+              if (g16) gf16[o] = f2bf(v); else gf[o] = v;
+            }
       }
       asm volatile("" ::: "memory");
     }
@@ -562,7 +585,10 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
       if (col < g.N) {
         const float *db = g.dbpart + (int64_t)wk * g.nband * g.N + col, *dd = g.ddbpart + (int64_t)wk * g.nband * g.N + col;
         float gsum = 0.f, dsum = 0.f;
-        for (int i = 0; i < g.nband; ++i) { gsum += db[(int64_t)i * g.N]; dsum += dd[(int64_t)i * g.N]; }
+        for (int i = 0; i < g.nband; ++i) {
+          gsum += db[(int64_t)i * g.N];
+          if constexpr (!PL) dsum += dd[(int64_t)i * g.N];
+        }
         put_fresh_grad(s, wk, g.offb + col, gsum);
         if (cada1) {
           fresh_innov(s, wk)[g.offb + col] = f2bf(dsum);
@@ -608,6 +634,7 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
   const int nw = blockDim.x >> 6;          // wavefronts of this launch (1..8): fewer for short contractions, so that more workgroups fit a CU
   const int m0 = blockIdx.x * 32, wk = blockIdx.y;
   const int nk = (g.K + BK - 1) / BK;
+  constexpr bool PL = NB == 2;
   // this lane's fragment in a chunk: row lane % 32 of the band (A) or of the first 32 rows (B), piece lane / 32 (+ 2)
   const int64_t offa = (((int64_t)(m0 >> 7) * g.A.kt[0]) << 12) + (((m0 & 127) + (lane & 31)) << 5) + ((lane >> 5) << 3);
   const int64_t offb = ((lane & 31) << 5) + ((lane >> 5) << 3);
@@ -651,7 +678,10 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
     const int c0 = 2 * (t & 15);
 #pragma unroll
     for (int e = 0; e < 2; ++e)
-      if (c0 + e < g.N) { bz[e] = s.theta[g.offb + c0 + e]; dbz[e] = delta_theta(s, ref, g.offb + c0 + e); }
+      if (c0 + e < g.N) {
+        bz[e] = s.theta[g.offb + c0 + e];
+        if constexpr (!PL) dbz[e] = delta_theta(s, ref, g.offb + c0 + e);
+      }
     label = static_cast<const int32_t *>(s.y)[g.grow[(int64_t)wk * g.Bp + min(m0 + (t >> 4), g.M - 1)]];
   }
   if constexpr (EPI == EPI_DW) {
@@ -689,7 +719,7 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
           const bf16x8 ad = fr(2), bx = NB == 4 ? fr(NA + 2) : bh;
           acc2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ad, bx, acc2, 0, 0, 0);
         }
-        acc2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bd, acc2, 0, 0, 0);
+        if constexpr (!PL) acc2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bd, acc2, 0, 0, 0);
       }
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the fragments are in registers before the area is written again
     }
@@ -723,14 +753,14 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
         const bf16x8 ad = fr(fa[half][2]), bx = NB == 4 ? fr(fb[half][2]) : bh;
         acc2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ad, bx, acc2, 0, 0, 0);
       }
-      acc2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ar, bd, acc2, 0, 0, 0);
+      if constexpr (!PL) acc2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ar, bd, acc2, 0, 0, 0);
     }
   }
   }
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     red[((w * 2 + 0) * 16 + r) * 64 + lane] = acc1[r];
-    red[((w * 2 + 1) * 16 + r) * 64 + lane] = acc2[r];
+    if constexpr (!PL) red[((w * 2 + 1) * 16 + r) * 64 + lane] = acc2[r];
   }
   __syncthreads();
   if constexpr (EPI == EPI_LOSS) {
@@ -758,7 +788,7 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
       float zs = 0.f, ds = 0.f;
       for (int ww = 0; ww < nw; ++ww) {
         zs += red[((ww * 2 + 0) * 16 + ra) * 64 + lb + c0 + e];
-        ds += red[((ww * 2 + 1) * 16 + ra) * 64 + lb + c0 + e];
+        if constexpr (!PL) ds += red[((ww * 2 + 1) * 16 + ra) * 64 + lb + c0 + e];
       }
       z[e] = on[e] ? zs + bz[e] : -INFINITY;
       ndz[e] = on[e] ? -(ds + dbz[e]) : 0.f;
@@ -802,8 +832,8 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
     if (on[0] && live) {
       const int64_t o = tm((int64_t)wk * g.Bp + row, 0, g.kto) + c0;          // classes 0..31 lie in the row's first chunk
       *reinterpret_cast<uint32_t *>(g.o_h + o) = ph; *reinterpret_cast<uint32_t *>(g.o_l + o) = pl;
-      *reinterpret_cast<uint32_t *>(g.o_d + o) = pd;
-      if (g.o_r) *reinterpret_cast<uint32_t *>(g.o_r + o) = pr;
+      if constexpr (!PL) *reinterpret_cast<uint32_t *>(g.o_d + o) = pd;
+      if (!PL && g.o_r) *reinterpret_cast<uint32_t *>(g.o_r + o) = pr;
     }
     // sums over the tile's rows in a fixed order: the wavefront's four rows, then the wavefronts
 #pragma unroll
@@ -827,7 +857,7 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
   bf16_t *gf16 = nullptr;
   bf16_t *ivf = nullptr;
   const bf16_t *ivs = nullptr;
-  const bool cada1 = s.rule == CADA_RULE_CADA1;
+  const bool cada1 = !PL && s.rule == CADA_RULE_CADA1;
   if constexpr (EPI == EPI_DW) {
     if (s.gbuf16) gf16 = fresh_grad16(s, wk) + g.offW;
     else gf = fresh_grad(s, wk) + g.offW;
@@ -837,7 +867,7 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
     }
   }
   float sq = 0.f;
-  for (int e = t; e < 2 * 16 * 64; e += (int)blockDim.x) {       // (accumulator, r, lane)
+  for (int e = t; e < (PL ? 1 : 2) * 16 * 64; e += (int)blockDim.x) {       // (accumulator, r, lane)
     const int a = e >> 10, r = (e >> 6) & 15, ln = e & 63;
     float v = 0.f;
     for (int ww = 0; ww < nw; ++ww) v += red[((ww * 2 + a) * 16 + r) * 64 + ln];
@@ -1162,7 +1192,7 @@ __global__ __launch_bounds__(kBlock) void k_bias_finish(const DevState s, const 
     float gsum = 0.f, dsum = 0.f;
     for (int rt = 0; rt < RT; ++rt) {
       gsum += dbpart[((int64_t)m * RT + rt) * d + c];
-      dsum += ddbpart[((int64_t)m * RT + rt) * d + c];
+      if (ddbpart) dsum += ddbpart[((int64_t)m * RT + rt) * d + c];
     }
     put_fresh_grad(s, m, offb + c, gsum);
     if (s.rule == CADA_RULE_CADA1) {
@@ -1230,6 +1260,7 @@ template <int EPI> int launch_mm5(Ctx *c, Mm5Args &g, int workers) {
         set_error("internal: unexpected tensor roles");
         return CADA_EUNSUPPORTED;
       }
+      if (g.A.n == 2 && g.B.n == 2) return launch_skinny_as<EPI, 2, 2, false>(c, g);
       if (EPI == EPI_DW) {
         if (!has_d && g.A.n == 2 && g.B.n == 3) return launch_skinny_as<EPI, 2, 3, false>(c, g);
         if (has_d && g.A.n == 3 && g.B.n == 4) return launch_skinny_as<EPI, 3, 4, true>(c, g);
@@ -1253,6 +1284,7 @@ template <int EPI> int launch_mm5(Ctx *c, Mm5Args &g, int workers) {
   for (int i = 0; i < g.B.n; ++i)
     if (g.B.kt[i] < needB) { set_error("internal: B tensor with fewer chunks than the tiles walk through"); return CADA_EUNSUPPORTED; }
   if (EPI == EPI_DW && (int64_t)((g.K + BK - 1) / BK) * BK > g.Bp) { set_error("internal: more rows than a worker's padded tile"); return CADA_EUNSUPPORTED; }
+  if (g.A.n == 2 && g.B.n == 2) return launch_mm5_as<EPI, 2, 2, false>(c, g);
   if constexpr (EPI == EPI_DW) {
     if (!has_d && g.A.n == 2 && g.B.n == 3) return launch_mm5_as<EPI, 2, 3, false>(c, g);
     if (has_d && g.A.n == 3 && g.B.n == 4) return launch_mm5_as<EPI, 3, 4, true>(c, g);
@@ -1284,6 +1316,11 @@ int mlp_init_state(Ctx *c, const float *) {
   if (const int rc = mlp_eval_init(c)) return rc;
   e = mm5_allow_lds<EPI_FWD_HIDDEN, 2, 3, false>();
   if (e == hipSuccess) e = mm5_allow_lds<EPI_FWD_HIDDEN, 4, 3, true>();
+  if (e == hipSuccess) e = mm5_allow_lds<EPI_FWD_HIDDEN, 2, 2, false>();
+  if (e == hipSuccess) e = mm5_allow_lds<EPI_DA, 2, 2, false>();
+  if (e == hipSuccess) e = mm5_allow_lds<EPI_DW, 2, 2, false>();
+  if (e == hipSuccess) e = skinny_allow_lds<EPI_LOSS, 2, 2, false>();
+  if (e == hipSuccess) e = skinny_allow_lds<EPI_DW, 2, 2, false>();
   if (e == hipSuccess) e = mm5_allow_lds<EPI_DW, 2, 3, false>();
   if (e == hipSuccess) e = mm5_allow_lds<EPI_DW, 3, 4, true>();
   if (e == hipSuccess) e = mm5_allow_lds<EPI_DA, 4, 3, true>();
@@ -1299,6 +1336,9 @@ int mlp_init_state(Ctx *c, const float *) {
   return CADA_OK;
 }
 
+// The rule evaluates no second gradient.
+static bool plain_rule(const MlpPlan &P) { return P.rule == CADA_RULE_ALWAYS || P.rule == CADA_RULE_LAG; }
+
 // The bf16 copies of the weights, and with idx the minibatch's rows and the differences to the reference points.
 static void stage(Ctx *c, const MlpPlan &P, const DevState &s, const int32_t *idx) {
   const int L = P.L, M = P.M, B = P.B;
@@ -1308,7 +1348,7 @@ static void stage(Ctx *c, const MlpPlan &P, const DevState &s, const int32_t *id
   sa.XGh = P.XGh; sa.XGl = P.XGl;
   sa.d0 = P.d[0]; sa.B = B; sa.Bp = P.Bp; sa.ktx = P.kta[0];
   sa.gx = (int)((P.ldx + 63) / 64); sa.gy = (B + 63) / 64;
-  sa.n_layers = L; sa.nz = idx ? P.nW + 1 : 1; sa.wt_total = P.wt_total; sa.wn_total = P.wn_total; sa.rep = P.rule == CADA_RULE_CADA2 ? P.rep : nullptr;
+  sa.n_layers = L; sa.nz = idx && !plain_rule(P) ? P.nW + 1 : 1; sa.wt_total = P.wt_total; sa.wn_total = P.wn_total; sa.rep = P.rule == CADA_RULE_CADA2 ? P.rep : nullptr;
   uint64_t nblk = idx ? (uint64_t)sa.gx * sa.gy * M : 0;
   sa.first[0] = 0;
   for (int l = 1; l <= L; ++l) {
@@ -1330,7 +1370,7 @@ void mlp_stage_weights(Ctx *c) { stage(c, *static_cast<MlpPlan *>(c->mlp), c->s,
 // Gathers the minibatch rows, prepares the bf16 weights and runs the forward contractions, whose last one evaluates the loss.
 static int mlp_forward(Ctx *c, MlpPlan &P, const DevState &s, const int32_t *idx) {
   const int L = P.L, M = P.M, B = P.B, Bp = P.Bp;
-  const bool per_worker = (P.rule == CADA_RULE_CADA2);
+  const bool per_worker = (P.rule == CADA_RULE_CADA2), plain = plain_rule(P);
   const int64_t dwt_stride = per_worker ? P.wt_total : 0;
   int32_t *rep = per_worker ? P.rep : nullptr;
   stage(c, P, s, idx);
@@ -1347,17 +1387,20 @@ static int mlp_forward(Ctx *c, MlpPlan &P, const DevState &s, const int32_t *idx
     } else {
       const int64_t bs = (int64_t)Bp * P.kta[l - 1] * 32;
       side_add(g.A, P.Ah[l - 1], P.kta[l - 1], bs); side_add(g.A, P.Al[l - 1], P.kta[l - 1], bs);
-      side_add(g.A, P.dA[l - 1], P.kta[l - 1], bs); side_add(g.A, P.Aref[l - 1], P.kta[l - 1], bs);
-      g.a_h = 0; g.a_l = 1; g.a_d = 2; g.a_r = 3;         // dZ_l = dA W + Aref dW
+      g.a_h = 0; g.a_l = 1; g.a_r = 0;
+      if (!plain) {
+        side_add(g.A, P.dA[l - 1], P.kta[l - 1], bs); side_add(g.A, P.Aref[l - 1], P.kta[l - 1], bs);
+        g.a_d = 2; g.a_r = 3;                             // dZ_l = dA W + Aref dW
+      }
     }
     const int64_t ktt = P.kta[l - 1];
     side_add(g.B, P.WTh + P.wt_off[l - 1], ktt, 0); side_add(g.B, P.WTl + P.wt_off[l - 1], ktt, 0);
-    side_add(g.B, P.dWT + P.wt_off[l - 1], ktt, dwt_stride);
-    g.b_h = 0; g.b_l = 1; g.b_x = 0; g.b_d = 2;
+    g.b_h = 0; g.b_l = 1; g.b_x = 0; g.b_d = 1;
+    if (!plain) { side_add(g.B, P.dWT + P.wt_off[l - 1], ktt, dwt_stride); g.b_d = 2; }
     g.rep = rep;
     if (l < L) {
       g.offb = P.offb[l - 1]; g.kto = P.kta[l];
-      g.o_h = P.Ah[l]; g.o_l = P.Al[l]; g.o_d = P.dA[l]; g.o_r = P.Aref[l];
+      g.o_h = P.Ah[l]; g.o_l = P.Al[l]; g.o_d = plain ? nullptr : P.dA[l]; g.o_r = plain ? nullptr : P.Aref[l];
       g.maskbits = P.maskbits[l];
       if (const int rc = launch_mm5<EPI_FWD_HIDDEN>(c, g, M)) return rc;
     } else {
@@ -1376,7 +1419,7 @@ int mlp_gradients(Ctx *c, const int32_t *idx) {
   s.k = c->k;
   hipStream_t st = c->stream;
   const int L = P.L, M = P.M, B = P.B, Bp = P.Bp;
-  const bool per_worker = (P.rule == CADA_RULE_CADA2);
+  const bool per_worker = (P.rule == CADA_RULE_CADA2), plain = plain_rule(P);
   const int64_t dwn_stride = per_worker ? P.wn_total : 0;
 
   prof_mark(c);
@@ -1393,11 +1436,14 @@ int mlp_gradients(Ctx *c, const int32_t *idx) {
         side_add(g.A, P.XGh, P.kta[0], bsA); side_add(g.A, P.XGl, P.kta[0], bsA);
         g.a_h = 0; g.a_l = 1; g.a_r = 0;
       } else {
-        side_add(g.A, P.Ah[l - 1], P.kta[l - 1], bsA); side_add(g.A, P.Al[l - 1], P.kta[l - 1], bsA); side_add(g.A, P.dA[l - 1], P.kta[l - 1], bsA);
-        g.a_h = 0; g.a_l = 1; g.a_d = 2; g.a_r = 0;       // innov = A^T dG + dA^T Gref
+        side_add(g.A, P.Ah[l - 1], P.kta[l - 1], bsA); side_add(g.A, P.Al[l - 1], P.kta[l - 1], bsA);
+        g.a_h = 0; g.a_l = 1; g.a_r = 0;                  // innov = A^T dG + dA^T Gref
+        if (!plain) { side_add(g.A, P.dA[l - 1], P.kta[l - 1], bsA); g.a_d = 2; }
       }
       side_add(g.B, P.Gh[l], P.kta[l], bsB); side_add(g.B, P.Gl[l], P.kta[l], bsB);
-      if (l == 1) {     // no dA^T Gref term in the first layer
+      if (plain) {
+        g.b_h = 0; g.b_l = 1; g.b_d = 1;
+      } else if (l == 1) {     // no dA^T Gref term in the first layer
         side_add(g.B, P.dG[l], P.kta[l], bsB);
         g.b_h = 0; g.b_l = 1; g.b_d = 2;
       } else {
@@ -1417,21 +1463,24 @@ int mlp_gradients(Ctx *c, const int32_t *idx) {
       g.M = B; g.N = din; g.K = dout;
       const int64_t bs = (int64_t)Bp * P.kta[l] * 32;
       side_add(g.A, P.Gh[l], P.kta[l], bs); side_add(g.A, P.Gl[l], P.kta[l], bs);
-      side_add(g.A, P.dG[l], P.kta[l], bs); side_add(g.A, P.Gref[l], P.kta[l], bs);
-      g.a_h = 0; g.a_l = 1; g.a_d = 2; g.a_r = 3;         // dGA = dG W^T + Gref dW^T
+      g.a_h = 0; g.a_l = 1; g.a_r = 0;
+      if (!plain) {
+        side_add(g.A, P.dG[l], P.kta[l], bs); side_add(g.A, P.Gref[l], P.kta[l], bs);
+        g.a_d = 2; g.a_r = 3;                             // dGA = dG W^T + Gref dW^T
+      }
       const int64_t ktn = P.kta[l];
       side_add(g.B, P.WNh + P.wn_off[l - 1], ktn, 0); side_add(g.B, P.WNl + P.wn_off[l - 1], ktn, 0);
-      side_add(g.B, P.dWN + P.wn_off[l - 1], ktn, dwn_stride);
-      g.b_h = 0; g.b_l = 1; g.b_x = 0; g.b_d = 2;
+      g.b_h = 0; g.b_l = 1; g.b_x = 0; g.b_d = 1;
+      if (!plain) { side_add(g.B, P.dWN + P.wn_off[l - 1], ktn, dwn_stride); g.b_d = 2; }
       g.rep = per_worker ? P.rep : nullptr;
       const int q = l - 1;
       g.offb = P.offb[q - 1]; g.kto = P.kta[q];
-      g.o_h = P.Gh[q]; g.o_l = P.Gl[q]; g.o_d = P.dG[q]; g.o_r = P.Gref[q];     // (Gref: null for q = 1)
+      g.o_h = P.Gh[q]; g.o_l = P.Gl[q]; g.o_d = plain ? nullptr : P.dG[q]; g.o_r = plain ? nullptr : P.Gref[q];     // (Gref: null for q = 1)
       g.maskbits = P.maskbits[q];
       g.dbpart = P.dbpart; g.ddbpart = P.ddbpart;
       if (const int rc = launch_mm5<EPI_DA>(c, g, M)) return rc;
       if (din <= 32)      // (k_skinny serves that layer's weight gradient)
-        hipLaunchKernelGGL(k_bias_finish, dim3((din + 255) / 256, M), dim3(kBlock), 0, st, s, P.dbpart, P.ddbpart, 2 * P.RT, din,
+        hipLaunchKernelGGL(k_bias_finish, dim3((din + 255) / 256, M), dim3(kBlock), 0, st, s, P.dbpart, plain ? nullptr : P.ddbpart, 2 * P.RT, din,
                          P.offb[q - 1], P.lhs_b_slot[q - 1]);
     }
   }
