@@ -617,8 +617,9 @@ __device__ __forceinline__ float group16_sum(float x) {
 // 32 rows x 32 columns; its wavefronts (eight; fewer for the few steps of a weight gradient) split the
 // tile steps (wavefront w takes steps w, w + nw, ...), read their fragments straight from the chunks in
 // global memory (a fragment is 16 consecutive bytes of a chunk row) and add their partial accumulators up
-// through LDS in a fixed order.  grid (ceil(M / 32), workers), 64 nw threads, 8 KB of dynamic LDS per
-// wavefront (EPI_DW: 14 KB).
+// through LDS in a fixed order.  grid (ceil(M / 32), workers, blocks of 32 columns), 64 nw threads, 8 KB of dynamic LDS per
+// wavefront (EPI_DW: 14 KB).  EPI_FWD_HIDDEN: a hidden layer's forward product where the 128 x 128 tiles are few or mostly
+// padding (skinny_forward), with the outputs of k_mm5's.
 // EPI_LOSS: the logits stay in the workgroup, whose epilogue is the loss (the signals
 // the backward contractions read, and per-block sums for the bias gradient); EPI_DW: weight gradient, innovation, its
 // squared norm (slot lhs_slot0 + row band), and (one more workgroup) the last layer's bias gradient from those sums.
@@ -637,7 +638,9 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
   constexpr bool PL = NB == 2;
   // this lane's fragment in a chunk: row lane % 32 of the band (A) or of the first 32 rows (B), piece lane / 32 (+ 2)
   const int64_t offa = (((int64_t)(m0 >> 7) * g.A.kt[0]) << 12) + (((m0 & 127) + (lane & 31)) << 5) + ((lane >> 5) << 3);
-  const int64_t offb = ((lane & 31) << 5) + ((lane >> 5) << 3);
+  // (EPI_FWD_HIDDEN: units 32 blockIdx.z ... of the layer; else the only block of columns)
+  const int cb = EPI == EPI_FWD_HIDDEN ? (int)blockIdx.z : 0;
+  const int64_t offb = (((int64_t)(cb >> 2) * g.B.kt[0]) << 12) + ((cb & 3) << 10) + ((lane & 31) << 5) + ((lane >> 5) << 3);
   if constexpr (EPI == EPI_DW) {
     // The last layer's launch has one workgroup more than tiles: it forms that layer's bias gradient, its innovation
     // and the innovation's part of the left-hand side from the sums that the forward launch left per block of 32 rows
@@ -668,21 +671,21 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
   f32x16 acc1, acc2;
 #pragma unroll
   for (int r = 0; r < 16; ++r) { acc1[r] = 0.f; acc2[r] = 0.f; }
-  // EPI_LOSS: sixteen lanes share a row of the 32 x 32 result, each with two of the (at most 32) classes.  The
-  // biases, their differences to the reference point and the row's label are asked for here, so that their
+  // EPI_LOSS, EPI_FWD_HIDDEN: sixteen lanes share a row of the 32 x 32 result, each with two of the (at most 32) classes or units.
+  // The biases, their differences to the reference point and the row's label are asked for here, so that their
   // latency passes under the products.
   float bz[2] = {0.f, 0.f}, dbz[2] = {0.f, 0.f};
   int label = 0;
-  if constexpr (EPI == EPI_LOSS) {
+  if constexpr (EPI == EPI_LOSS || EPI == EPI_FWD_HIDDEN) {
     const RefPtr ref = theta_ref(s, wk, s.k);
-    const int c0 = 2 * (t & 15);
+    const int c0 = 32 * cb + 2 * (t & 15);
 #pragma unroll
     for (int e = 0; e < 2; ++e)
       if (c0 + e < g.N) {
         bz[e] = s.theta[g.offb + c0 + e];
         if constexpr (!PL) dbz[e] = delta_theta(s, ref, g.offb + c0 + e);
       }
-    label = static_cast<const int32_t *>(s.y)[g.grow[(int64_t)wk * g.Bp + min(m0 + (t >> 4), g.M - 1)]];
+    if constexpr (EPI == EPI_LOSS) label = static_cast<const int32_t *>(s.y)[g.grow[(int64_t)wk * g.Bp + min(m0 + (t >> 4), g.M - 1)]];
   }
   if constexpr (EPI == EPI_DW) {
     // units m0 .. m0 + 31 of the A tensors are chunk m0 / 32 of every row tile, the (at most 32) output
@@ -763,6 +766,51 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
     if constexpr (!PL) red[((w * 2 + 1) * 16 + r) * 64 + lane] = acc2[r];
   }
   __syncthreads();
+  if constexpr (EPI == EPI_FWD_HIDDEN) {
+    // bias and ReLU of both evaluations; the block is 2 KB of consecutive memory of each output tensor
+    __shared__ uint8_t pos[2][32][33];              // value at theta, at the reference point is positive
+    const int rl = t >> 4, c0 = 2 * (t & 15);
+    const int ra = 4 * (rl >> 3) + (rl & 3), lb = 32 * ((rl >> 2) & 1);      // (accumulator element of a row: as below)
+    float x[2], xref[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      float zs = bz[e], ds = dbz[e];
+      for (int ww = 0; ww < nw; ++ww) {
+        zs += red[((ww * 2 + 0) * 16 + ra) * 64 + lb + c0 + e];
+        if constexpr (!PL) ds += red[((ww * 2 + 1) * 16 + ra) * 64 + lb + c0 + e];
+      }
+      const bool live = m0 + rl < g.M && 32 * cb + c0 + e < g.N;             // (else padding: zero)
+      x[e] = live ? fmaxf(zs, 0.f) : 0.f;
+      xref[e] = live && !PL ? fmaxf(zs - ds, 0.f) : 0.f;
+    }
+    const uint32_t vh = f2bf_pk(x[0], x[1]), vr = f2bf_pk(xref[0], xref[1]);
+    const int64_t o = tm((int64_t)wk * g.Bp + m0 + rl, 32 * cb + c0, g.kto);
+    *reinterpret_cast<uint32_t *>(g.o_h + o) = vh;
+    *reinterpret_cast<uint32_t *>(g.o_l + o) = f2bf_pk(x[0] - __uint_as_float(vh << 16), x[1] - __uint_as_float(vh & 0xffff0000u));
+    if constexpr (!PL) {
+      *reinterpret_cast<uint32_t *>(g.o_d + o) = f2bf_pk(x[0] - xref[0], x[1] - xref[1]);
+      *reinterpret_cast<uint32_t *>(g.o_r + o) = vr;
+    }
+    // ReLU masks where k_mm5's activation gradient looks for them (sign of the stored, rounded values): this block is quarter
+    // (i, j) of wavefront (wy, wx) of its 128 x 128 tile, sixteen bits of each of the wavefront's lanes
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      pos[0][rl][c0 + e] = __uint_as_float(e ? vh & 0xffff0000u : vh << 16) > 0.f;
+      pos[1][rl][c0 + e] = __uint_as_float(e ? vr & 0xffff0000u : vr << 16) > 0.f;
+    }
+    __syncthreads();
+    if (t < 2 * kWave) {
+      const int ref = t >> 6;
+      uint32_t bits = 0;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) bits |= (uint32_t)pos[ref][8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)][lane & 31] << r;
+      const int by = m0 >> 7, wy = (m0 >> 6) & 1, i = (m0 >> 5) & 1, wx = (cb >> 1) & 1, j = cb & 1;
+      const int gx = (g.N + BN - 1) / BN, gy = (g.M + BM - 1) / BM;
+      uint64_t *word = g.maskbits + ((((int64_t)wk * gy + by) * gx + (cb >> 2)) * kBlock + (wy * 2 + wx) * 64 + lane) * 2 + ref;
+      reinterpret_cast<uint16_t *>(word)[i * 2 + j] = (uint16_t)bits;
+    }
+    return;
+  }
   if constexpr (EPI == EPI_LOSS) {
     // softmax cross-entropy on the tile's rows: G = (P - onehot)/B, dG = (P - Pref)/B.  With e_i = exp(-dz_i) and
     // T = sum_j P_j e_j the reference probabilities are Pref_i = P_i e_i / T, so
@@ -1243,16 +1291,26 @@ template <int EPI, int NA, int NB, bool HAS_D> hipError_t skinny_allow_lds() {
 template <int EPI, int NA, int NB, bool HAS_D> int launch_skinny_as(Ctx *c, const Mm5Args &g) {
   const int nw = skinny_waves(EPI, g.K);
   const unsigned extra = (EPI == EPI_DW && g.lastb != nullptr) ? 1u : 0u;      // (the workgroup that finishes the last layer's bias gradient)
-  hipLaunchKernelGGL((k_skinny<EPI, NA, NB, HAS_D>), dim3((unsigned)((g.M + 31) / 32) + extra, g.workers), dim3(64 * nw), skinny_lds_bytes(EPI, nw), c->stream, g);
+  hipLaunchKernelGGL((k_skinny<EPI, NA, NB, HAS_D>), dim3((unsigned)((g.M + 31) / 32) + extra, g.workers, EPI == EPI_FWD_HIDDEN ? (unsigned)((g.N + 31) / 32) : 1u), dim3(64 * nw), skinny_lds_bytes(EPI, nw), c->stream, g);
   return CADA_OK;
+}
+// Hidden layers' forward products go through k_skinny while its 32 x 32 blocks fill the chip (two workgroups per CU) at most twice
+// over, or a worker has a single block of rows (a 128 x 128 tile would then be three quarters padding).  Few tiles leave CUs
+// idle and run through the whole inner dimension one after the other, where k_skinny splits it over eight wavefronts.
+// Measured, us per step with k_skinny and with k_mm5: 784-500-10, M = 10, B = 12: 82, 103; M = 64: 149, 160; 617-301-150-26, M = 24,
+// B = 100: 160, 177; 3072-1024-1024-10, M = 16, B = 64: 468, 494; 3072-1024-10, M = 64, B = 12: 849, 889; above:
+// 784-512-10, M = 60, B = 60 (1920 blocks): 163, 157.
+constexpr int64_t kSkinnyBlocks = 1024;
+static bool skinny_forward(const Mm5Args &g, int workers) {
+  return g.M <= 32 || (int64_t)((g.M + 31) / 32) * ((g.N + 31) / 32) * workers <= kSkinnyBlocks;
 }
 // Returns CADA_OK after enqueueing the launch, CADA_EUNSUPPORTED (and launches nothing) when the
 // operands do not fit a compiled variant.
 template <int EPI> int launch_mm5(Ctx *c, Mm5Args &g, int workers) {
   g.workers = workers;
   const bool has_d = g.a_d >= 0;
-  if constexpr (EPI == EPI_DW || EPI == EPI_LOSS) {
-    if (g.N <= 32) {            // at most 32 output columns (the last layer)
+  if constexpr (EPI == EPI_DW || EPI == EPI_LOSS || EPI == EPI_FWD_HIDDEN) {
+    if (EPI == EPI_FWD_HIDDEN ? skinny_forward(g, workers) : g.N <= 32) {            // (at most 32 output columns: the last layer)
       for (int i = 1; i < g.A.n; ++i)
         if (g.A.kt[i] != g.A.kt[0]) { set_error("internal: A tensors with different chunk counts"); return CADA_EUNSUPPORTED; }
       if (g.a_h != 0 || g.a_l != 1 || (has_d && g.a_d != 2) || g.a_r != (g.A.n == 4 ? 3 : 0) || g.b_h != 0 || g.b_l != 1 ||
@@ -1319,6 +1377,9 @@ int mlp_init_state(Ctx *c, const float *) {
   if (e == hipSuccess) e = mm5_allow_lds<EPI_FWD_HIDDEN, 2, 2, false>();
   if (e == hipSuccess) e = mm5_allow_lds<EPI_DA, 2, 2, false>();
   if (e == hipSuccess) e = mm5_allow_lds<EPI_DW, 2, 2, false>();
+  if (e == hipSuccess) e = skinny_allow_lds<EPI_FWD_HIDDEN, 2, 2, false>();
+  if (e == hipSuccess) e = skinny_allow_lds<EPI_FWD_HIDDEN, 2, 3, false>();
+  if (e == hipSuccess) e = skinny_allow_lds<EPI_FWD_HIDDEN, 4, 3, true>();
   if (e == hipSuccess) e = skinny_allow_lds<EPI_LOSS, 2, 2, false>();
   if (e == hipSuccess) e = skinny_allow_lds<EPI_DW, 2, 2, false>();
   if (e == hipSuccess) e = mm5_allow_lds<EPI_DW, 2, 3, false>();

@@ -153,3 +153,22 @@ def test_reference_point_far_from_the_iterate():
     assert np.median(rel) < 1e-2 and rel.max() < 0.2
     assert np.array_equal(out["trace_own_mask"], tr["own_mask"])
     assert rel_l2(out["theta64"], o.theta) < BF16_TOL
+
+
+# Hidden layers' forward products on either side of the 32 x 32 blocks' range (one block of rows; 1024 blocks and more), odd widths
+# on both sides of 32, the rules with and without a second gradient.  Tolerances as in the reduced cases above.
+@pytest.mark.parametrize("dims,M,B,rule", [
+    ((61, 133, 10), 3, 5, 1), ((61, 133, 10), 3, 33, 2), ((77, 67, 45, 7), 4, 32, 2), ((77, 67, 31, 7), 4, 40, 0), ((45, 33, 129, 5), 3, 130, 1),
+    ((50, 515, 10), 40, 33, 2), ((50, 515, 10), 61, 20, 3), ((50, 515, 9), 21, 64, 2), ((77, 131, 67, 7), 5, 100, 3), ((40, 31, 10), 3, 50, 3)])
+def test_forward_blocks_and_odd_widths(dims, M, B, rule):
+    lag = rule == configs.RULE_LAG
+    cfg = configs.CFG4.scaled(name="blocks", layer_dims=dims, M=M, N_m=B + 60, B=B, K=12, D=5, rule=rule, c=20.0,
+                              server=configs.SERVER_SGD if lag else configs.SERVER_AMSGRAD, alpha=0.05 if lag else 0.0005)
+    prob = generators.make_problem(cfg)
+    dev, sched = upload(prob), generators.make_schedule(cfg)
+    stats, o, tr, rep = check_protocol(cfg, prob, dev, sched, 2e-2, lhs_rtol=None, own_mask_exact=False, free_margin=None)
+    big = tr["lhs"] > 1e-9 * tr["lhs"].max()
+    rel = np.abs(rep["trace_lhs"] - tr["lhs"])[big] / tr["lhs"][big]
+    print(dims, M, B, rule, stats["theta_rel_l2"], stats["stored_rel_l2"], "lhs rel median %.2e" % np.median(rel), "mask mean", tr["mask"].mean())
+    assert np.median(rel) < 1e-2 and stats["stored_rel_l2"] < 2e-2
+    assert stats["own_disagreements"] <= max(2, 0.03 * tr["mask"].size)
