@@ -465,9 +465,13 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
     // row-wise pass: this lane has columns c4 .. c4+3 of the band's rows rr + 4 it, it = 0..7
     const int c4 = (lane & 15) * 4, rr = lane >> 4;
     const int colg = n0 + wx * 64 + c4;
-    // every column of this wavefront's part exists: 16-byte accesses (8 bytes of bf16), whatever the rows' alignment; a part that
-    // overhangs the matrix goes element by element, but asks for all its stored values first, too
-    const bool wide = n0 + wx * 64 + 64 <= g.N;
+    // A lane whose four columns exist takes 16 bytes at a time (8 bytes of bf16), whatever the rows' alignment; the lane at the
+    // matrix's edge that has fewer (`some`) goes element by element, but asks for all its stored values first, too.  (Whole
+    // wavefronts used to go element by element where their 64 columns overhang the matrix, one dependent read after the
+    // other with CADA1: 784-500-10, M = 30, B = 12: 148 -> 109 us per step.  Blocks of 32 x 128 with a wavefront per 32 columns were
+    // 2-6 % faster for odd widths and 5 % slower where a tile has more than four steps.)
+    const bool full = colg + 4 <= g.N, some = colg < g.N && !full;
+    const int colv = min(colg, g.N - 4);                     // (more than 32 columns)
     auto put_band = [&](const f32x16 (&acc)[2]) __attribute__((always_inline)) {
 #pragma unroll
       for (int j = 0; j < 2; ++j)
@@ -485,9 +489,8 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
 #pragma unroll
         for (int it = 0; it < 8; ++it) {
           const bf16_t *row = ivs + (int64_t)min(m0 + wy * 64 + i * 32 + rr + 4 * it, g.M - 1) * g.N;
-          if (wide) {
-            old[i][it] = *reinterpret_cast<const u32x2u *>(row + colg);
-          } else {
+          old[i][it] = *reinterpret_cast<const u32x2u *>(row + colv);
+          if (some) {
             uint32_t e[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) e[q] = row[min(colg + q, g.N - 1)];
@@ -519,7 +522,7 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
         continue;
       }
       put_band(acc2[i]);
-      if (wide) {
+      if (full) {
 #pragma unroll
         for (int it = 0; it < 8; ++it) {
           f32x4u v = *reinterpret_cast<const f32x4u *>(st + (rr + 4 * it) * SP + c4);
@@ -532,7 +535,7 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
             sq = fmaf(v.x, v.x, sq); sq = fmaf(v.y, v.y, sq); sq = fmaf(v.z, v.z, sq); sq = fmaf(v.w, v.w, sq);
           }
         }
-      } else {                                 // a part that overhangs the matrix: element by element
+      } else if (some) {
 #pragma unroll
         for (int it = 0; it < 8; ++it)
 #pragma unroll
@@ -550,7 +553,7 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
     for (int i = 0; i < 2; ++i) {
       const int rowb = m0 + wy * 64 + i * 32 + rr;
       put_band(acc1[i]);
-      if (wide) {
+      if (full) {
 #pragma unroll
         for (int it = 0; it < 8; ++it) {
           const f32x4u v = *reinterpret_cast<const f32x4u *>(st + (rr + 4 * it) * SP + c4);
@@ -564,7 +567,7 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
             }
           }
         }
-      } else {
+      } else if (some) {
 #pragma unroll
         for (int it = 0; it < 8; ++it)
 #pragma unroll
