@@ -490,13 +490,19 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
         for (int it = 0; it < 8; ++it) {
           const bf16_t *row = ivs + (int64_t)min(m0 + wy * 64 + i * 32 + rr + 4 * it, g.M - 1) * g.N;
           old[i][it] = *reinterpret_cast<const u32x2u *>(row + colv);
-          if (some) {
+        }
+      if (n0 + wx * 64 + 64 > g.N && (g.N & 3) != 0) {       // (uniform: no branch among the loads of the other tiles)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int it = 0; it < 8; ++it) {
+            const bf16_t *row = ivs + (int64_t)min(m0 + wy * 64 + i * 32 + rr + 4 * it, g.M - 1) * g.N;
             uint32_t e[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) e[q] = row[min(colg + q, g.N - 1)];
-            old[i][it].x = e[0] | (e[1] << 16); old[i][it].y = e[2] | (e[3] << 16);
+            if (some) { old[i][it].x = e[0] | (e[1] << 16); old[i][it].y = e[2] | (e[3] << 16); }
           }
-        }
+      }
     }
     auto old_of = [&](int i, int it, int e) __attribute__((always_inline)) {      // value e of old[i][it]
       const uint32_t o = e < 2 ? old[i][it].x : old[i][it].y;
