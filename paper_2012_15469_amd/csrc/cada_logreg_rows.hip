@@ -21,6 +21,7 @@
 // Measured per step, against those launches: M = 10, p = 784, B = 60: 23.8 -> 16.2 us (15.5 in the kernel: operands and indices 3.3,
 // rows 2.9, share's sums 2.6, gradient 1.5, count 0.7, rule 1.0, aggregate 2.1, update 1.3); M = 10, p = 22, B = 92, LAG:
 // 23.8 -> 13.2 us; M = 100, B = 256, p = 4000 (410 MB of rows): 147 -> 87 us; p = 8192: 308 -> 164 us (5.1 TB/s).
+#include "cada_rows_split.h"
 #include "cada_rule.h"
 
 namespace cada {
@@ -32,12 +33,12 @@ struct RowsArgs {
   DevState s;
   const int32_t *idx;        // [M][B]
   const uint8_t *replay;     // [M] or nullptr
-  float *part;               // [M][shares][2][p rounded up to 4] sums of the shares (shares > 1)
-  uint32_t *count;           // [1 + M], kCountWords apart: workers done; shares done of each worker (zero between launches)
-  int shares;                // workgroups per worker
+  float *part;               // sums of the shares: k_rows [M][shares][2][p rounded up to 4] (shares > 1), k_rows_wide [wide_slots][2][the same]
+  uint32_t *count;           // [1 + M], kCountWords apart: workers done; shares (k_rows_sum: blocks) done of each worker (zero between launches)
+  int shares;                // k_rows: workgroups per worker
   int rows;                  // rows per share (at most)
-  int per;                   // k_rows_wide: shares of every worker, or 0
-  int server;                // run the server update in this launch
+  int server;                // k_rows: run the server update in this launch
+  WideSplit wide;            // k_rows_wide, k_rows_sum
 };
 
 __device__ __forceinline__ float sigmoid_r(float a) { return 1.0f / (1.0f + expf(-a)); }
@@ -380,25 +381,13 @@ __global__ __launch_bounds__(R_NT) void k_rows(const RowsArgs a) {
   }
 }
 
-// First row (of all workers' rows in order) of share c, and the share that holds row f; `per` shares for every worker, or (0) all rows
-// cut evenly into n shares.
-__device__ __forceinline__ int wide_first(const RowsArgs &a, int c) {
-  if (a.per) { const int m = c / a.per; return m * a.s.B + (int)((int64_t)(c - m * a.per) * a.s.B / a.per); }
-  return (int)((int64_t)c * a.s.M * a.s.B / a.shares);
-}
-__device__ __forceinline__ int wide_share(const RowsArgs &a, int f) {
-  if (a.per) { const int m = f / a.s.B; return m * a.per + (int)((((int64_t)(f - m * a.s.B) + 1) * a.per - 1) / a.s.B); }
-  return (int)((((int64_t)f + 1) * a.shares - 1) / ((int64_t)a.s.M * a.s.B));
-}
-
 // Rows of more than 8192 columns: a workgroup still takes whole rows (z and dz need no other workgroup, hence no cooperative launch and
 // no exchange, which cost the cluster kernel of cada_logreg_fused.hip some 50 us per step whatever the size), CW quads of each per lane.
 // What bounds it: HBM, at 4.2-5.3 TB/s, and 8 us of operands and sums at the two ends.  Measured per step, two passes or the cluster
 // kernel before: M = 37, B = 75, p = 20001, CADA1: 117 -> 79 us; p = 20000: 114 -> 77; M = 8, B = 256, p = 8196: 117 -> 39;
 // M = 100, B = 256, p = 20000 (2 GB of rows): 391 -> 387.  Rows without the non-temporal hint: 81, 79, 39, 433.
 // All workers' rows, one after the other, are cut into one share per workgroup (wide_split); a share that crosses from one worker to
-// the next starts new sums there.  The sums of workgroup c for worker m go to slot c or, where shares cross workers, c + m (from one such pair to the
-// next either c or m is one more), and k_rows_sum adds a worker's slots up, one block per 1024 columns.  RB rows are worked on together with the next RB in flight.
+// the next starts new sums there (wide_slot), and k_rows_sum adds a worker's slots up, one block per 1024 columns.  RB rows are worked on together with the next RB in flight.
 // DL: theta - theta_ref lies in LDS (the registers of 512 threads hold four vectors of 20480 columns and the rows in flight, not
 // five).  SEG: shares may meet several workers (up to 14336 columns: the loop over them costs wider rows registers, 51 -> 59 us).
 // dynamic LDS: row offsets int64 [rows], labels [rows] (rounded up to four rows), with DL theta - theta_ref [CW][512] quads
@@ -414,7 +403,7 @@ __global__ __launch_bounds__(R_NT) void k_rows_wide(const RowsArgs a) {
   constexpr int NV = 2 * RB;
   __shared__ float red_s[2][R_NW][NV];
 
-  const int f0 = wide_first(a, blockIdx.x), nr = wide_first(a, blockIdx.x + 1) - f0;        // this share's rows
+  const int f0 = wide_first(a.wide, blockIdx.x), nr = wide_first(a.wide, blockIdx.x + 1) - f0;        // this share's rows
   for (int b = tid; b < nr; b += R_NT) {
     const int m = (f0 + b) / s.B;
     const int64_t base = s.row_off[m], n_m = s.row_off[m + 1] - base;
@@ -519,7 +508,7 @@ __global__ __launch_bounds__(R_NT) void k_rows_wide(const RowsArgs a) {
       load(x[0], b + 2 * RB);
       work(x[1], b + RB, it + 1);
     }
-    float *pg = a.part + (int64_t)((int)blockIdx.x + (SEG && a.per == 0 ? m : 0)) * 2 * ps;
+    float *pg = a.part + (int64_t)(SEG ? wide_slot(a.wide, blockIdx.x, m) : (int)blockIdx.x) * 2 * ps;
 #pragma unroll
     for (int i = 0; i < CW; ++i) {
       const int dup = j0 + i * (4 * kWave) - (int)(jb[i] >> 2);
@@ -534,6 +523,8 @@ __global__ __launch_bounds__(R_NT) void k_rows_wide(const RowsArgs a) {
       }
     }
     seg = end;
+    // (the next worker's first rows may use the exchange buffer of this one's last ones, which a slower wavefront still reads)
+    if (SEG && seg < nr) lds_sync();
   } while (SEG && seg < nr);
 }
 
@@ -558,8 +549,8 @@ __global__ __launch_bounds__(kBlock) void k_rows_sum(const RowsArgs a) {
     v4u st = {0.f, 0.f, 0.f, 0.f};                     // CADA1: the stored innovation; LAG, always: the stored gradient
     if (rule == CADA_RULE_CADA1) st = *reinterpret_cast<const v4u *>(s.dtl + oc);
     else if (rule != CADA_RULE_CADA2) st = *reinterpret_cast<const v4u *>(s.gbuf + oc);
-    const int c0 = wide_share(a, m * s.B), shares = wide_share(a, (m + 1) * s.B - 1) - c0 + 1;
-    const float *pg = a.part + (int64_t)(c0 + (a.per == 0 ? m : 0)) * 2 * ps + j;
+    const int c0 = wide_share(a.wide, m * s.B), shares = wide_share(a.wide, (m + 1) * s.B - 1) - c0 + 1;
+    const float *pg = a.part + (int64_t)wide_slot(a.wide, c0, m) * 2 * ps + j;
     v4s gs = {0.f, 0.f, 0.f, 0.f}, is = gs;
     for (int q0 = 0; q0 < shares; q0 += 8) {         // eight shares asked for before the first is added
       v4s x[8], y[8];
@@ -629,37 +620,15 @@ static void rows_split(int M, int B, int64_t p, int *shares, int *rows) {
   *shares = (B + *rows - 1) / *rows;
 }
 
-// Rows of more than 8192 columns.  A workgroup fills a CU; the operands of a worker and the sums' way out cost it about as much as three
-// rows, and fifty workgroups' sums cost the whole launch another.  So many shares for every worker as make the rounds of CUs
-// cheapest, or, up to kWideEven columns and where it is less, all rows cut evenly over the CUs, although a share then may meet two
-// workers.  Measured, us per step with a share count per worker and cut evenly: M = 37, B = 75, p = 20001: 77, 92;
-// M = 100, B = 256, p = 10000: 220, 217; M = 100, B = 100, p = 8196: 113, 105.
-// (A share's row offsets and labels lie in LDS: 2048 rows at most.)
-constexpr int64_t kWideEven = 7 * 2048;
-static void wide_split(int M, int B, int64_t p, int *shares, int *rows, int *per) {
-  const int64_t T = (int64_t)M * B;
-  int64_t best = INT64_MAX;
-  for (int n = (B + 2047) / 2048; n <= 32 && n <= B; ++n) {
-    const int r = (B + n - 1) / n;
-    const int64_t cost = 50 * (((int64_t)M * n + 255) / 256) * (r + 3) + (int64_t)M * n;
-    if (cost < best) { best = cost; *shares = M * n; *rows = r; *per = n; }
-  }
-  const int64_t even = max(min((int64_t)256, T), (T + 2047) / 2048), most = (T + even - 1) / even;
-  if (p <= kWideEven && 50 * ((even + 255) / 256) * (most + 6) + even < best) { *shares = (int)even; *rows = (int)most; *per = 0; }
-}
-
 bool rows_serves(const cada_config *cfg) {
   return cfg->model == CADA_MODEL_LOGREG && cfg->path != CADA_PATH_TWO_PASS && cfg->p >= 4 && cfg->p <= kRowsWidest &&
          (cfg->p <= 8192 || (int64_t)cfg->M * cfg->B < (1ll << 31) - 1);
 }
 size_t rows_part_floats(const cada_config *cfg) {
   if (!rows_serves(cfg)) return 0;
-  int shares, rows, per;
+  int shares, rows;
   const size_t ps = (size_t)((cfg->p + 3) / 4 * 4);
-  if (cfg->p > 8192) {
-    wide_split(cfg->M, cfg->B, cfg->p, &shares, &rows, &per);
-    return (size_t)(shares + (per ? 0 : cfg->M)) * 2 * ps;
-  }
+  if (cfg->p > 8192) return (size_t)wide_slots(wide_split(cfg->M, cfg->B, cfg->p)) * 2 * ps;
   rows_split(cfg->M, cfg->B, cfg->p, &shares, &rows);
   return shares > 1 ? (size_t)cfg->M * shares * 2 * ps : 0;
 }
@@ -672,7 +641,8 @@ bool rows_plan(Ctx *c, const cada_config *cfg) {
   int wc;
   RowsKernel fn;
   if (wide) {
-    wide_split(cfg->M, cfg->B, cfg->p, &c->rows_shares, &c->rows_per_share, &c->rows_per_worker);
+    const WideSplit w = wide_split(cfg->M, cfg->B, cfg->p);
+    c->rows_shares = w.shares; c->rows_per_share = w.rows; c->rows_per_worker = w.per;
     c->rows_server = 0;
     fn = wide_kernel(cfg->p);
     c->rows_lds = (size_t)((c->rows_per_share + 3) & ~3) * 12 + (cfg->p > 7 * 2048 ? (size_t)((cfg->p + 2047) / 2048) * R_NT * sizeof(v4s) : 0);
@@ -703,7 +673,7 @@ int logreg_step_rows(Ctx *c, const int32_t *idx, const uint8_t *replay) {
   a.count = c->rows_count;
   a.shares = c->rows_shares;
   a.rows = c->rows_per_share;
-  a.per = c->rows_per_worker;
+  a.wide = WideSplit{c->s.M, c->s.B, c->rows_shares, c->rows_per_share, c->rows_per_worker};
   a.server = c->rows_server;
   int wc;
   prof_mark(c);

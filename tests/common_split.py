@@ -1,0 +1,46 @@
+"""csrc/cada_rows_split.h for tests: compiled with the host compiler, called through ctypes."""
+import ctypes as C
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+# (p, M, B, rule) whose rows are cut evenly, so that shares meet several workers: five, six and seven quads per lane
+SHARED_WORKERS = [(8196, 129, 13, 2), (8199, 137, 15, 1), (8193, 600, 2, 2), (10240, 129, 14, 3), (10241, 131, 13, 1), (12288, 133, 14, 2),
+                  (12289, 129, 13, 1), (14335, 129, 13, 2), (14336, 300, 1, 1)]
+
+_SRC = """
+#include "cada_rows_split.h"
+using namespace cada;
+extern "C" {
+void split(int M, int B, long p, int *out) { const WideSplit w = wide_split(M, B, p); out[0] = w.shares; out[1] = w.rows; out[2] = w.per; out[3] = wide_slots(w); }
+int first(const WideSplit *w, int c) { return wide_first(*w, c); }
+int share(const WideSplit *w, int f) { return wide_share(*w, f); }
+int slot(const WideSplit *w, int c, int m) { return wide_slot(*w, c, m); }
+}
+"""
+
+
+class _W(C.Structure):
+    _fields_ = [(n, C.c_int) for n in ("M", "B", "shares", "rows", "per")]
+
+
+def compile_split(tmp):
+    src, lib = os.path.join(str(tmp), "split.cc"), os.path.join(str(tmp), "split.so")
+    with open(src, "w") as f:
+        f.write(_SRC)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", os.path.join(ROOT, "paper_2012_15469_amd", "csrc"), "-o", lib, src], check=True)
+    dll = C.CDLL(lib)
+
+    class Split:
+        def __init__(self, M, B, p):
+            out = (C.c_int * 4)()
+            dll.split(M, B, C.c_long(p), out)
+            self.shares, self.rows, self.per, self.slots = out
+            self._w = _W(M, B, self.shares, self.rows, self.per)
+
+        def first(self, c): return dll.first(C.byref(self._w), c)
+        def share(self, f): return dll.share(C.byref(self._w), f)
+        def slot(self, c, m): return dll.slot(C.byref(self._w), c, m)
+
+    return Split

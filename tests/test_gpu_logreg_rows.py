@@ -8,6 +8,7 @@ import pytest
 from cada_synth import configs, generators
 
 from common import check_protocol, upload
+from common_split import SHARED_WORKERS
 
 pytestmark = pytest.mark.gpu
 
@@ -16,9 +17,9 @@ pytestmark = pytest.mark.gpu
     (4, 3, 70, 2), (5, 70, 9, 1), (22, 10, 92, 3), (255, 3, 65, 2), (256, 66, 8, 1), (257, 3, 129, 2), (513, 5, 66, 1),
     (784, 10, 60, 2), (1024, 4, 300, 2), (1025, 4, 300, 1), (1027, 3, 67, 0), (2048, 40, 40, 1), (2049, 3, 130, 2), (4097, 9, 64, 1),
     (8191, 5, 150, 2), (8192, 3, 33, 1)])
-def test_rows_path(p, M, B, rule):
+def test_rows_path(p, M, B, rule, K=24, spare=40):
     lag = rule == configs.RULE_LAG
-    cfg = configs.CFG1.scaled(name="rows", layer_dims=(p,), M=M, N_m=B + 40, B=B, K=24, D=6, rule=rule, c=0.5 if p < 100 else 2e-3,
+    cfg = configs.CFG1.scaled(name="rows", layer_dims=(p,), M=M, N_m=B + spare, B=B, K=K, D=6, rule=rule, c=0.5 if p < 100 else 2e-3,
                               alpha=0.005, server=1 if lag else 0)
     prob = generators.make_problem(cfg)
     prob.X *= np.float32(1.0 / np.sqrt(p))           # (rows of norm about one, so that the decisions mix)
@@ -34,6 +35,13 @@ def test_rows_path(p, M, B, rule):
     (16385, 9, 30, 1), (18433, 3, 45, 0), (20001, 6, 75, 1), (20478, 3, 100, 2), (20480, 2, 1, 1)])
 def test_wide_rows_path(p, M, B, rule):
     test_rows_path(p, M, B, rule)
+
+
+@pytest.mark.parametrize("p,M,B,rule", SHARED_WORKERS)
+def test_wide_rows_path_shares_of_several_workers(p, M, B, rule):
+    # (LAG: samples enough that no minibatch is drawn twice running.  Its left-hand side |g - g_stored|^2 has no digits where both gradients
+    # are over the same rows: 5e-14 for |g|^2 = 0.25 is a difference of 5e-7 |g| between float32 vectors of 6e-8 |g| rounding each.)
+    test_rows_path(p, M, B, rule, K=8, spare=40 if rule == configs.RULE_LAG else 3)
 
 
 def test_rows_path_flags_and_repeats():
