@@ -106,8 +106,9 @@ bool check_config(const cada_config *cfg, Geometry *g) {
   g->n_col_chunks = (int)((cfg->p + g->chunk_cols - 1) / g->chunk_cols);
   const int64_t per_block = (int64_t)kBlock * g->vec;
   g->n_lhs_part = (int)((cfg->p + per_block - 1) / per_block);
-  // server kernel: one block per 256 coordinates, see cada_server.hip (the multi-step kernel of
-  // cada_logreg_small.hip writes one partial per worker instead: room for either)
+  // Server kernel: one block per 256 coordinates, see cada_server.hip.  The kernels of cada_logreg_small.hip and cada_logreg_rows.hip that
+  // run the server themselves write the whole into the first part and clear the others, so that a
+  // checkpoint block means the same on every path.  (ring_cap: what the array has room for, as in saved blocks.)
   g->n_ring_part = (int)((cfg->p + 255) / 256);
   g->ring_cap = g->n_ring_part > cfg->M ? g->n_ring_part : cfg->M;
   if (cfg->model == CADA_MODEL_MLP) g->n_lhs_part = mlp_lhs_slots(cfg);
@@ -391,9 +392,9 @@ int cada_init(const cada_config *cfg, const float *theta0, cada_ctx **out) {
   s.eps = (float)cfg->eps; s.lam = (float)cfg->lambda_l2; s.c = cfg->c;
   if (cfg->model == CADA_MODEL_LOGREG) {
     // the requested path first; a request that the shape does not allow falls back to the others
-    if (cfg->path == CADA_PATH_WHOLE_STEPS && small_plan(c, cfg)) s.n_ring_part = cfg->M;
-    else if (cfg->path != CADA_PATH_TWO_PASS && !(cfg->path == CADA_PATH_AUTO && cfg->p <= kRowsWidest) && fused_plan(c, cfg)) s.n_lhs_part = kFusedWaves * c->fused_Q;
-    else if (cfg->path == CADA_PATH_AUTO && small_plan(c, cfg)) s.n_ring_part = cfg->M;
+    if (cfg->path == CADA_PATH_WHOLE_STEPS) small_plan(c, cfg);
+    if (!c->small && cfg->path != CADA_PATH_TWO_PASS && !(cfg->path == CADA_PATH_AUTO && cfg->p <= kRowsWidest) && fused_plan(c, cfg)) s.n_lhs_part = kFusedWaves * c->fused_Q;
+    else if (cfg->path == CADA_PATH_AUTO) small_plan(c, cfg);
     if (!c->small && !c->fused && rows_plan(c, cfg)) {
       c->n_phases = c->rows_server ? 1 : 2; c->phase_names[0] = "logreg_rows"; c->phase_names[1] = "server_update";
       if (c->rows == 2) s.n_lhs_part = (int)((cfg->p + 1023) / 1024);

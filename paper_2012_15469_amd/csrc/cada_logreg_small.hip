@@ -161,7 +161,8 @@ __device__ __forceinline__ void small_body(const SmallArgs &a, const uint32_t *s
   const float *stored = (rule == CADA_RULE_CADA1 ? s.dtl : s.gbuf) + (int64_t)cur * mp + (int64_t)m * s.p;
   const int32_t idx0 = tid < B ? idx[tid] : 0;
   const uint32_t state0 = tid < (int)(sizeof(DevState) / 4) ? state[tid] : 0u;
-  const float ring0 = tid < s.d_max ? s.ring[tid] : 0.f, part0 = tid == 0 && v.k > 0 ? s.ring_part[0] : 0.f;   // (part0: the squared step of the iteration before this launch)
+  // (part0: the squared step of the iteration before this launch, in the parts that a server launch or this kernel left)
+  const float ring0 = tid < s.d_max ? s.ring[tid] : 0.f, part0 = v.k > 0 && tid < s.n_ring_part ? s.ring_part[tid] : 0.f;
   auto put_vectors = [&](int j, float th, float tl, float hh, float vh, float rf, float rl, float st) __attribute__((always_inline)) {
     th_s[j] = th; tl_s[j] = tl; h_s[j] = hh; vh_s[j] = vh;
     d_s[j] = cada ? (th - rf) + (tl - rl) : 0.f;
@@ -179,7 +180,10 @@ __device__ __forceinline__ void small_body(const SmallArgs &a, const uint32_t *s
   if (tid < (int)(sizeof(DevState) / 4)) reinterpret_cast<uint32_t *>(&at)[tid] = state0;
   if (tid < s.d_max) ring_s[tid] = ring0;
   for (int j = tid + S_NT; j < s.d_max; j += S_NT) ring_s[j] = s.ring[j];
-  if (tid < S_NW) red_q[tid] = part0;
+  if (w == 0) {          // (n_ring_part = ceil(p / 256) <= 32)
+    const float before = (float)wave_sum_f64((double)part0);
+    if (tid < S_NW) red_q[tid] = tid == 0 ? before : 0.f;
+  }
   if (tid < p) put_vectors(tid, th0, tl0, h0, vh0, rf0, rl0, st0);
   for (int j = tid + S_NT; j < p; j += S_NT)
     put_vectors(j, s.theta[j], s.theta_lo[j], s.h[j], s.vhat[j], cada ? ref.hi[j] : 0.f, cada ? ref.lo[j] : 0.f, lds_stored ? stored[j] : 0.f);
@@ -484,13 +488,13 @@ __device__ __forceinline__ void small_body(const SmallArgs &a, const uint32_t *s
       }
     }
   }
-  // what a later launch, or reading the state out, adds up (the other entries of ring_part stay zero)
+  // what a later launch, or reading the state out, adds up
   lds_sync();
-  if (tid == 0 && (ONE || m == 0)) {
+  if (tid < s.n_ring_part && (ONE || m == 0)) {
     float newest = red_q[0];
 #pragma unroll
     for (int i = 1; i < S_NW; ++i) newest += red_q[i];
-    at.ring_part[0] = newest;
+    at.ring_part[tid] = tid == 0 ? newest : 0.f;
   }
 }
 
@@ -510,7 +514,7 @@ __global__ __launch_bounds__(S_NT) void k_small(const SmallLaunch launch) {
 // grid M
 __global__ __launch_bounds__(S_NT) void k_small_one(const SmallArgs a, const SmallVar v) { small_body<true>(a, reinterpret_cast<const uint32_t *>(&a.s), v, 1); }
 
-// Whether the multi-step kernel serves this configuration; sets the ring-partial count it uses.
+// Whether the multi-step kernel serves this configuration.
 bool small_plan(Ctx *c, const cada_config *cfg) {
   c->small = 0;
   const int64_t p = cfg->p;

@@ -70,3 +70,37 @@ def test_block_of_another_configuration_is_refused():
     with pytest.raises(CadaError):
         a.restore(torch.zeros_like(block))
     a.restore(block)            # a valid block still loads afterwards
+
+
+@pytest.mark.parametrize("M,B", [(3, 20), (20, 20), (3, 1)])
+@pytest.mark.parametrize("save,load", [(a, b) for a in ("two_pass", "rows", "whole") for b in ("two_pass", "rows", "whole") if a != b])
+def test_block_of_another_path(save, load, M, B):
+    """The path is no part of a block.  The newest squared step is kept in parts that each path cuts in its own way (p = 784 are four
+    server blocks; M = 3 is fewer, M = 20 more, and too much state for a server inside the rows kernel): a run that goes on on
+    another path forms the right-hand sides that the saving context forms, and both report the same ring."""
+    from paper_2012_15469_amd import binding
+    from paper_2012_15469_amd.binding import cada_profile_phase_names
+    paths = {"two_pass": (binding.PATH_TWO_PASS, "logreg_two_pass"), "rows": (binding.PATH_SINGLE_PASS, "logreg_rows"),
+             "whole": (binding.PATH_WHOLE_STEPS, "logreg_whole_steps")}      # (a single pass starts at 8192 columns: the rows kernel before that)
+    cfg = configs.CFG2.scaled(K=14, N_m=50, M=M, B=B, D=5)
+    K1, prob = 6, generators.make_problem(cfg)
+    X, y, th0 = upload(prob)
+    sched = to_dev(generators.make_schedule(cfg).astype(np.int32))
+    engines = {}
+    for name in (save, load):
+        engines[name] = Cada.from_config(cfg, X, y, th0, trace_steps=cfg.K, path=paths[name][0])
+        assert paths[name][1] in cada_profile_phase_names(engines[name].ctx)
+    for k in range(K1):
+        engines[save].step(sched[k])
+    engines[load].restore(engines[save].checkpoint())
+    want, _ = _final(engines[save])
+    got, _ = _final(engines[load])
+    assert np.array_equal(got["ring"], want["ring"])      # the same parts, added up by the same kernel
+    for k in range(K1, cfg.K):
+        for name in (save, load):
+            engines[name].step(sched[k], torch.ones(M, dtype=torch.uint8, device="cuda"))
+    want, _ = _final(engines[save])
+    got, _ = _final(engines[load])
+    # (float32 sums of 784 terms in another order, over eight steps: 1e-6; a missing part is a quarter of the newest term)
+    assert np.allclose(got["trace_rhs"], want["trace_rhs"], rtol=1e-5, atol=0)
+    assert np.allclose(got["ring"], want["ring"], rtol=1e-5, atol=0)
