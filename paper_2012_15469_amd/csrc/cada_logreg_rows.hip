@@ -54,7 +54,8 @@ __global__ __launch_bounds__(R_NT) void k_rows(const RowsArgs a) {
   int64_t *off_s = reinterpret_cast<int64_t *>(rows_smem);
   float *y_s = reinterpret_cast<float *>(off_s + ((a.rows + 3) & ~3));
   float *sum_s = y_s + ((a.rows + 3) & ~3);             // [R_NW / WC][2][p rounded up to 4]
-  __shared__ float red_s[2][R_NW][2 * RB], red_l[R_NW];
+  __shared__ float red_s[2][R_NW][2 * RB];
+  __shared__ double red_l[R_NW];
   __shared__ uint32_t flag_s, up_s;
   constexpr int NV = 2 * RB;
   static_assert(NV == 4 || NV == 8 || NV == 16, "row_sums");
@@ -235,7 +236,7 @@ __global__ __launch_bounds__(R_NT) void k_rows(const RowsArgs a) {
   }
   const int cur = s.sel[m];
   const __amdgpu_buffer_rsrc_t fresh = far_buffer(s.gbuf + (int64_t)(1 - cur) * mp + (int64_t)m * s.p, s.p);
-  float sq = 0.f;
+  double sq = 0.0;                                     // (four terms at a time in float32, their sums in double: the rule compares in double)
   for (int j = tid * 4; j < ps; j += R_NT * 4) {
     const int64_t o = (int64_t)m * s.p + j, of = (int64_t)(1 - cur) * mp + o, oc = (int64_t)cur * mp + o;
     const v4u t4 = *reinterpret_cast<const v4u *>(s.theta + j), l4 = *reinterpret_cast<const v4u *>(s.theta_lo + j);
@@ -259,13 +260,15 @@ __global__ __launch_bounds__(R_NT) void k_rows(const RowsArgs a) {
     } else {
       share_sums(j, gs, is);
     }
+    float sq4 = 0.f;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       gs[e] = fmaf(s.lam, t4[e], gs[e]);
       is[e] = fmaf(s.lam, (t4[e] - rh[e]) + (l4[e] - rl[e]), is[e]);
       const float term = rule == CADA_RULE_CADA2 ? is[e] : (rule == CADA_RULE_CADA1 ? is[e] : gs[e]) - st[e];
-      if (j + e < p) sq = fmaf(term, term, sq);
+      if (j + e < p) sq4 = fmaf(term, term, sq4);
     }
+    sq += (double)sq4;
     if (j + 4 <= p) {
       store_far(fresh, (uint32_t)j * 4u, 0u, gs);
       if (rule == CADA_RULE_CADA1) *reinterpret_cast<v4u *>(s.dtl + of) = is;
@@ -276,14 +279,15 @@ __global__ __launch_bounds__(R_NT) void k_rows(const RowsArgs a) {
       }
     }
   }
-  sq = wave_sum_dpp(sq);
+  sq = wave_sum_f64(sq);
   if (lane == 0) red_l[w] = sq;
   lds_sync();
+  double *lhs_far = reinterpret_cast<double *>(s.lhs_part);      // [M] (room for eight floats per worker at least)
   if (tid == 0) {
-    float l = red_l[0];
+    double l = red_l[0];
 #pragma unroll
     for (int i = 1; i < R_NW; ++i) l += red_l[i];
-    put_far(s.lhs + m, l);
+    put_far(lhs_far + m, l);
     up_s = 0u;
   }
   if (!last_of(a.count, (uint32_t)M, &flag_s)) return;
@@ -292,19 +296,20 @@ __global__ __launch_bounds__(R_NT) void k_rows(const RowsArgs a) {
   uint32_t ups = 0;
   uint8_t *sel_s = reinterpret_cast<uint8_t *>(rows_smem);       // [M], in place of what came before (every wavefront is past it)
   for (int mm = tid; mm < M; mm += R_NT) {
-    const float lhs = get_far(s.lhs + mm);
+    const double lhs = get_far(lhs_far + mm);
     const int32_t tau = mm == tid ? tau0 : s.tau[mm], was = mm == tid ? sel0 : s.sel[mm];
     const int32_t replay = mm == tid ? rep0 : a.replay != nullptr ? (int32_t)a.replay[mm] : CADA_REPLAY_FREE;
-    const bool own = (rule == CADA_RULE_ALWAYS) || ((double)lhs > rhs) || (tau >= s.D);
+    const bool own = (rule == CADA_RULE_ALWAYS) || (lhs > rhs) || (tau >= s.D);
     bool up = own;
     if (replay != CADA_REPLAY_FREE) up = replay != 0;
     if (k < s.trace_steps) {
       const int64_t o = k * M + mm;
       s.t_mask[o] = up ? 1 : 0;
       s.t_own[o] = own ? 1 : 0;
-      s.t_lhs[o] = lhs;
+      s.t_lhs[o] = (float)lhs;
       s.t_tau[o] = tau;
     }
+    s.lhs[mm] = (float)lhs;
     s.mask[mm] = up ? 1 : 0;
     s.tau[mm] = up ? 1 : tau + 1;
     const int sel = up ? was ^ 1 : was;    // an upload: the fresh row becomes the stored one
@@ -350,7 +355,7 @@ __global__ __launch_bounds__(R_NT) void k_rows(const RowsArgs a) {
     *reinterpret_cast<v4s *>(nab_s + j) = nab;
   }
   lds_sync();
-  float sqs = 0.f;
+  double sqs = 0.0;
   for (int j = tid; j < p; j += R_NT) {
     const float nab = nab_s[j] / (float)M;
     const int u = j < 2 * R_NT ? j / R_NT : 2;
@@ -359,7 +364,7 @@ __global__ __launch_bounds__(R_NT) void k_rows(const RowsArgs a) {
     else if (u == 1) { hh = h0[1]; vh = vh0[1]; t = th0[1]; tl = tl0[1]; }
     else { hh = s.h[j]; vh = s.vhat[j]; t = s.theta[j]; tl = s.theta_lo[j]; }
     const float step = server_coordinate(s, s.alpha, nab, hh, vh, vv, t, tl);
-    sqs = fmaf(step, step, sqs);
+    sqs = fma((double)step, (double)step, sqs);
     s.nabla[j] = nab; s.h[j] = hh; s.v[j] = vv; s.vhat[j] = vh; s.theta[j] = t; s.theta_lo[j] = tl;
     if (rule == CADA_RULE_CADA2) {
       s.hist[((k + 1) % s.R) * s.ps + j] = t;
@@ -369,15 +374,15 @@ __global__ __launch_bounds__(R_NT) void k_rows(const RowsArgs a) {
       s.snap_lo[j] = tl;
     }
   }
-  sqs = wave_sum_dpp(sqs);
+  sqs = wave_sum_f64(sqs);
   lds_sync();                                          // (red_l has been read)
   if (lane == 0) red_l[w] = sqs;
   lds_sync();
   if (tid < s.n_ring_part) {
-    float l = red_l[0];
+    double l = red_l[0];
 #pragma unroll
     for (int i = 1; i < R_NW; ++i) l += red_l[i];
-    s.ring_part[tid] = tid == 0 ? l : 0.f;
+    s.ring_part[tid] = tid == 0 ? (float)l : 0.f;
   }
 }
 

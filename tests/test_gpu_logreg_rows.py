@@ -4,8 +4,10 @@ its neighbour, a worker's rows are split into shares from 64 rows and 256 KB on,
 server update into the launch."""
 import numpy as np
 import pytest
+import torch
 
 from cada_synth import configs, generators
+from paper_2012_15469_amd import binding
 
 from common import check_protocol, upload
 from common_split import SHARED_WORKERS
@@ -56,3 +58,27 @@ def test_rows_path_flags_and_repeats():
     assert out["error_flags"][0] == 1 and ref["error_flags"][0] == 0
     for name in ("theta", "h", "vhat", "stored", "trace_lhs"):
         assert np.array_equal(out[name], ref[name]), name
+
+
+@pytest.mark.parametrize("p,M,big,small", [(8192, 3, 2048, 2.0 ** -10), (2048, 1, 512, 2.0 ** -11)])
+def test_sums_of_the_rule_keep_small_terms(p, M, big, small):
+    """The rule compares sums of squares in double.  All values here are powers of two: every gradient, and with alpha = 1 every step of the SGD
+    server, is exact; a float32 sum over a few of the large squares (4 or 1) and then small ones (2^-22, 2^-24: half a unit in
+    the last place) loses all of these.  Shapes: left-hand side, and (a server in the same launch) the squared step."""
+    B = 128
+    x = torch.full((p,), small, device="cuda")
+    x[:big] = 2.0
+    X = x.repeat(M * B, 1).contiguous()
+    eng = binding.Cada(model="logreg", layer_dims=[p], M=M, B=B, n_samples=[B] * M, X=X, y=torch.ones(M * B, device="cuda"),
+                       theta0=torch.zeros(p, device="cuda"), rule=3, D=50, d_max=10, c=0.5, alpha=1.0, beta1=0.9, beta2=0.999, eps=1e-8, lam=0.0,
+                       gemm_dtype="fp32", server=1, trace_steps=1)
+    assert "logreg_rows" in binding.cada_profile_phase_names(eng.ctx)
+    eng.step(torch.arange(B, dtype=torch.int32, device="cuda").repeat(M, 1).contiguous())
+    st = eng.state()
+    torch.cuda.synchronize()
+    want = np.float32(big * 1.0 + (p - big) * (0.5 * small) ** 2)
+    assert want != np.float32(big)
+    assert (st["trace_lhs"].cpu().numpy().ravel() == want).all()
+    assert st["lhs"].cpu().numpy().tolist() == [want] * M
+    assert st["ring"].cpu().numpy()[0] == want
+    eng.close()
