@@ -111,9 +111,13 @@ bool check_config(const cada_config *cfg, Geometry *g) {
   // checkpoint block means the same on every path.  (ring_cap: what the array has room for, as in saved blocks.)
   g->n_ring_part = (int)((cfg->p + 255) / 256);
   g->ring_cap = g->n_ring_part > cfg->M ? g->n_ring_part : cfg->M;
-  if (cfg->model == CADA_MODEL_MLP) g->n_lhs_part = mlp_lhs_slots(cfg);
+  int room = g->n_lhs_part;
+  if (cfg->model == CADA_MODEL_MLP) {
+    g->n_lhs_part = mlp_lhs_slots(cfg, mlp_bias_cols(cfg->rule));      // (in scratch, cada_mlp.hip; the room here keeps the layout of saved checkpoint blocks)
+    room = mlp_lhs_slots(cfg, kBiasColsState);
+  }
   const int fused_slots = kFusedWaves * (int)((cfg->p + 2047) / 2048);
-  g->lhs_cap = g->n_lhs_part > fused_slots ? g->n_lhs_part : fused_slots;
+  g->lhs_cap = room > fused_slots ? room : fused_slots;
   return true;
 }
 

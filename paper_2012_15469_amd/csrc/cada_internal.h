@@ -318,7 +318,10 @@ constexpr size_t kFusedTailFloatsPerP = 2 * 32;     // room for the parts of 32 
 constexpr size_t kFusedPostWords = 1024 * 4 * 16;   // upper bound: 1024 workgroups x 4 buffers x 16 values
 // S1+S2 for the MLP.
 int mlp_gradients(Ctx *c, const int32_t *idx);
-int mlp_lhs_slots(const cada_config *cfg);
+// Partial sums of the left-hand side, with one per so many columns of a bias innovation (the plain rules have none: k_lag_lhs uses the slots).
+constexpr int kBiasColsState = 256;
+inline int mlp_bias_cols(int rule) { return rule == CADA_RULE_CADA1 || rule == CADA_RULE_CADA2 ? 64 : kBiasColsState; }
+int mlp_lhs_slots(const cada_config *cfg, int bias_cols);
 int mlp_eval(Ctx *c, double *out);
 int logreg_eval(Ctx *c, double *out);
 int logreg_eval_noalloc(Ctx *c, double *out);   // the same kernels with their scratch in a file-scope device array

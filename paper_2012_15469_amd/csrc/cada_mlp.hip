@@ -587,13 +587,15 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
       asm volatile("" ::: "memory");
     }
     // The tiles of the first 128 units also form the layer's bias gradient and its innovation, from the sums that the
-    // activation-gradient launch left per band of 64 rows: this wavefront's 64 columns, one per lane.  (A launch of its own
-    // cost 5 us.)  Their part of the left-hand side goes with the tile's; the slots of their own stay zero.
-    if (g.nband > 0 && by == 0 && wy == 0) {
+    // activation-gradient launch left per band of 64 rows: this wavefront's 64 columns, one per lane, and a partial sum of the left-hand
+    // side of their own.  (A launch of its own cost 5 us.  One wavefront for 256 columns, with fewer partial sums: 784-500-10, B = 12:
+    // 81.1 -> 82.8 us per step, 3072-1024-1024-10: 608 -> 615.)
+    if (g.nband > 0 && by == 0 && wy == 0 && n0 + wx * 64 < g.N) {
       const int col = n0 + wx * 64 + lane;
+      float dsum = 0.f;
       if (col < g.N) {
         const float *db = g.dbpart + (int64_t)wk * g.nband * g.N + col, *dd = g.ddbpart + (int64_t)wk * g.nband * g.N + col;
-        float gsum = 0.f, dsum = 0.f;
+        float gsum = 0.f;
         for (int i = 0; i < g.nband; ++i) {
           gsum += db[(int64_t)i * g.N];
           if constexpr (!PL) dsum += dd[(int64_t)i * g.N];
@@ -603,8 +605,10 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
           fresh_innov(s, wk)[g.offb + col] = f2bf(dsum);
           dsum -= bf2f(stored_innov(s, wk)[g.offb + col]);
         }
-        sq = fmaf(dsum, dsum, sq);
-        if ((col & 255) == 0) s.lhs_part[(int64_t)wk * s.n_lhs_part + g.lhs_slot_b + (col >> 8)] = 0.f;
+      }
+      if constexpr (!PL) {
+        const float totb = wave_sum(dsum * dsum);
+        if (lane == 0) s.lhs_part[(int64_t)wk * s.n_lhs_part + g.lhs_slot_b + 2 * bx + wx] = totb;
       }
     }
     const float tot = wave_sum(sq);           // one partial sum of the left-hand side per wavefront and tile
@@ -984,7 +988,7 @@ void layout(MlpPlan &P, const cada_config *cfg, int64_t total_rows, Carve &w) {
     P.wt_off[l - 1] = wt; wt += (int64_t)tm_elems(P.d[l], P.d[l - 1]);
     P.wn_off[l - 1] = wn; if (l >= 2) wn += (int64_t)tm_elems(P.d[l - 1], P.d[l]);
     P.lhs_w_slot[l - 1] = slot; slot += 4 * tiles128(P.d[l - 1]) * tiles128(P.d[l]);
-    P.lhs_b_slot[l - 1] = slot; slot += (P.d[l] + 255) / 256;
+    P.lhs_b_slot[l - 1] = slot; slot += (P.d[l] + mlp_bias_cols(P.rule) - 1) / mlp_bias_cols(P.rule);
     if (l < P.L && P.d[l] > maxh) maxh = P.d[l];
   }
   P.wt_total = wt; P.wn_total = wn;
@@ -1019,10 +1023,10 @@ void layout(MlpPlan &P, const cada_config *cfg, int64_t total_rows, Carve &w) {
 
 // Number of partial sums of the left-hand side per worker (one per weight-gradient tile and
 // per 256 biases).
-int mlp_lhs_slots(const cada_config *cfg) {
+int mlp_lhs_slots(const cada_config *cfg, int bias_cols) {
   int slot = 0;
   for (int l = 1; l <= cfg->n_layers; ++l)
-    slot += 4 * tiles128(cfg->layer_dims[l - 1]) * tiles128(cfg->layer_dims[l]) + (cfg->layer_dims[l] + 255) / 256;
+    slot += 4 * tiles128(cfg->layer_dims[l - 1]) * tiles128(cfg->layer_dims[l]) + (cfg->layer_dims[l] + bias_cols - 1) / bias_cols;
   return slot;
 }
 
@@ -1044,11 +1048,16 @@ size_t mlp_workspace_bytes(const cada_config *cfg, const int64_t total_rows) {
   return w.off + kAlignB;
 }
 
+// The partial sums of the left-hand side, in front of the evaluation's scratch.
+static size_t lhs_bytes(const cada_config *cfg) {
+  return ((size_t)cfg->M * mlp_lhs_slots(cfg, mlp_bias_cols(cfg->rule)) * sizeof(float) + kAlignB - 1) / kAlignB * kAlignB;
+}
+
 size_t mlp_scratch_bytes(const cada_config *cfg, const int64_t total_rows) {
   MlpPlan P;
   Carve w{nullptr, 0};
   layout(P, cfg, total_rows, w);
-  return mlp_eval_bytes(P) + kAlignB;
+  return lhs_bytes(cfg) + mlp_eval_bytes(P) + kAlignB;
 }
 
 int mlp_plan(Ctx *c, const cada_config *cfg, char *base, size_t offset, size_t scratch, int64_t total_rows) {
@@ -1057,7 +1066,9 @@ int mlp_plan(Ctx *c, const cada_config *cfg, char *base, size_t offset, size_t s
   if (!P) { set_error("out of host memory"); return CADA_EINVAL; }
   Carve w{base, (offset + kAlignB - 1) / kAlignB * kAlignB};
   layout(*P, cfg, total_rows, w);
-  P->eval = base + (scratch + kAlignB - 1) / kAlignB * kAlignB;
+  scratch = (scratch + kAlignB - 1) / kAlignB * kAlignB;
+  c->s.lhs_part = reinterpret_cast<float *>(base + scratch);
+  P->eval = base + scratch + lhs_bytes(cfg);
   c->mlp = P;
   c->n_phases = 3;
   c->phase_names[0] = "mlp_gradients"; c->phase_names[1] = "rule"; c->phase_names[2] = "server_update";

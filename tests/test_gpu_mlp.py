@@ -172,3 +172,23 @@ def test_forward_blocks_and_odd_widths(dims, M, B, rule):
     print(dims, M, B, rule, stats["theta_rel_l2"], stats["stored_rel_l2"], "lhs rel median %.2e" % np.median(rel), "mask mean", tr["mask"].mean())
     assert np.median(rel) < 1e-2 and stats["stored_rel_l2"] < 2e-2
     assert stats["own_disagreements"] <= max(2, 0.03 * tr["mask"].size)
+
+
+@pytest.mark.parametrize("rule", [configs.RULE_CADA1, configs.RULE_CADA2])
+@pytest.mark.parametrize("h", [33, 64, 65, 129, 257])
+def test_left_hand_side_of_bias_innovations(h, rule):
+    """Every hidden bias counts once in the left-hand side, whichever partial sum it goes to (64 units each).  With X = 0 and a small
+    first bias the weights' innovations are next to nothing, so that four fifths of it are the first layer's biases:
+    64 of 257 units left out would change its root by 10 %.  The vectors whose norm it is are differences rounded to bf16, 2^-9 of the
+    innovation's norm, and with CADA1 less a stored one, rounded once more: norms differ by no more than that."""
+    cfg = configs.CFG4.scaled(name="bias_lhs", layer_dims=(5, h, 3), M=3, N_m=40, B=20, K=6, D=4, rule=rule)
+    prob = generators.make_problem(cfg)
+    prob.X[:] = 0.0
+    prob.theta0[5 * h:6 * h] = 1e-3
+    prob.theta0[6 * h:9 * h] *= 4.0
+    dev, sched = upload(prob), generators.make_schedule(cfg)
+    o, tr = oracle_run(cfg, prob, sched)
+    out = run_library(cfg, dev, sched, replay=tr["mask"])
+    got, want = np.sqrt(out["trace_lhs"]), np.sqrt(tr["lhs"])
+    print(h, rule, "%.1e" % (np.abs(got - want).max() / want.max()))
+    assert want[1:].min() > 0 and np.abs(got - want).max() < 2.0 ** -8 * want.max()
