@@ -400,8 +400,7 @@ int cada_init(const cada_config *cfg, const float *theta0, cada_ctx **out) {
     if (!c->small && cfg->path != CADA_PATH_TWO_PASS && !(cfg->path == CADA_PATH_AUTO && cfg->p <= kRowsWidest) && fused_plan(c, cfg)) s.n_lhs_part = kFusedWaves * c->fused_Q;
     else if (cfg->path == CADA_PATH_AUTO) small_plan(c, cfg);
     if (!c->small && !c->fused && rows_plan(c, cfg)) {
-      c->n_phases = c->rows_server ? 1 : 2; c->phase_names[0] = "logreg_rows"; c->phase_names[1] = "server_update";
-      if (c->rows == 2) s.n_lhs_part = (int)((cfg->p + 1023) / 1024);
+      // (its phases are named there)
     } else if (c->small) {
       c->n_phases = 1; c->phase_names[0] = "logreg_whole_steps";
     } else if (c->fused && c->fused_tail_f > 0) {

@@ -278,7 +278,7 @@ struct Ctx {
   void *small_args;          // room in the workspace for this context's launch-invariant arguments (launches of several steps)
   void *small_args_host;     // their host copy (owned by the context)
   // one or two launches per step for rows of up to 8192 columns, cada_logreg_rows.hip
-  int rows, rows_shares, rows_per_share, rows_per_worker, rows_server;      // (rows: 1, or 2 for more than 8192 columns, whose shares are WideSplit's)
+  int rows, rows_shares, rows_per_share, rows_per_worker, rows_tail;      // (rows: 1, or 2 for more than 8192 columns, whose shares are WideSplit's)
   size_t rows_lds;
   float *rows_part;          // sums of the shares of a worker's rows
   uint32_t *rows_count;      // [1 + M] counters, kCountWords apart
@@ -335,6 +335,7 @@ int mlp_init_state(Ctx *c, const float *theta0);
 void mlp_free(Ctx *c);
 // S3: rule, mask, tau.  S5-S7: aggregate, AMSGrad, ring push.
 int rule_and_server(Ctx *c, const uint8_t *replay);
-int server_step(Ctx *c);                    // S5-S7 alone (the rule has been evaluated)
+int rule_then_server(Ctx *c, const uint8_t *replay);      // the same, the left-hand side's partial sums being complete for every rule
+int server_step(Ctx *c);                           // S5-S7 alone (the rule has been evaluated)
 
 }  // namespace cada

@@ -27,7 +27,16 @@
 namespace cada {
 
 constexpr int R_NT = 512, R_NW = R_NT / kWave;
-constexpr int kRowsFusedServer = 12288, kRowsFusedWorkers = 32;      // M p and M up to here: the last workgroup also runs the server update
+enum { kTailNone = 0, kTailRule = 1, kTailServer = 2 };      // what the workgroup that finishes last does: nothing, the rule, the server update too
+// The server update in the launch's last workgroup saves a launch, and costs a pass over the state by one CU.  Measured, us per step with and
+// without it, B = 65: M = 10, p = 22: 12.5, 15.0; M = 32, p = 256: 14.0, 15.5; M = 32, p = 500: 14.5, 15.5; M = 48: 15.6, 16.1; M = 64: 16.8,
+// 16.7; M = 16, p = 784: 16.5, 17.1; M = 24: 18.1, 17.2; M = 16, p = 1024: 16.4, 17.0; M = 1, p = 1500: 16.5, 16.3; 3000: 22.0, 18.9; 8000: 40.7, 26.6.
+constexpr int kServerColumns = 2 * R_NT, kServerState = 16384, kServerWorkers = 32;      // p, M p and M up to here
+// The rule in the last workgroup saves a launch as well; the workgroups count themselves in one after the other for it.  Measured, us with
+// and without it: B = 65, p = 22: M = 100: 17.2, 19.9; 256: 23.3, 24.1; 400: 28.6, 30.0; 512: 32.3, 32.4; 1024: 54.9, 53.8; p = 8191, M = 512: 215, 219;
+// 1024: 414, 416.  k_rows_sum, whose blocks are many: p = 8193, M = 16, B = 8: 23.0, 23.9; 64: 32.5, 30.7; 256: 62.8, 47.5; 1024: 207, 134; p = 20480,
+// M = 16, B = 64: 49.6, 50.1; M = 64: 94.0, 91.7.
+constexpr int kRuleWorkers = 512, kWideRuleWorkers = 32;
 
 struct RowsArgs {
   DevState s;
@@ -37,7 +46,7 @@ struct RowsArgs {
   uint32_t *count;           // [1 + M], kCountWords apart: workers done; shares (k_rows_sum: blocks) done of each worker (zero between launches)
   int shares;                // k_rows: workgroups per worker
   int rows;                  // rows per share (at most)
-  int server;                // k_rows: run the server update in this launch
+  int tail;                  // kTail*
   WideSplit wide;            // k_rows_wide, k_rows_sum
 };
 
@@ -282,21 +291,24 @@ __global__ __launch_bounds__(R_NT) void k_rows(const RowsArgs a) {
   sq = wave_sum_f64(sq);
   if (lane == 0) red_l[w] = sq;
   lds_sync();
-  double *lhs_far = reinterpret_cast<double *>(s.lhs_part);      // [M] (room for eight floats per worker at least)
+  uint64_t *lhs_far = reinterpret_cast<uint64_t *>(s.lhs_part);      // [M] two floats whose sum is the left-hand side (n_lhs_part = 2; room for eight)
   if (tid == 0) {
     double l = red_l[0];
 #pragma unroll
     for (int i = 1; i < R_NW; ++i) l += red_l[i];
-    put_far(lhs_far + m, l);
+    const float hi = (float)l, lo = (float)(l - (double)hi);
+    put_far(lhs_far + m, ((uint64_t)__float_as_uint(lo) << 32) | __float_as_uint(hi));
     up_s = 0u;
   }
+  if (a.tail == kTailNone) return;
   if (!last_of(a.count, (uint32_t)M, &flag_s)) return;
 
   // ---- the rule for all workers (last workgroup of the launch)
   uint32_t ups = 0;
   uint8_t *sel_s = reinterpret_cast<uint8_t *>(rows_smem);       // [M], in place of what came before (every wavefront is past it)
   for (int mm = tid; mm < M; mm += R_NT) {
-    const double lhs = get_far(lhs_far + mm);
+    const uint64_t l2 = get_far(lhs_far + mm);
+    const double lhs = (double)__uint_as_float((uint32_t)l2) + (double)__uint_as_float((uint32_t)(l2 >> 32));
     const int32_t tau = mm == tid ? tau0 : s.tau[mm], was = mm == tid ? sel0 : s.sel[mm];
     const int32_t replay = mm == tid ? rep0 : a.replay != nullptr ? (int32_t)a.replay[mm] : CADA_REPLAY_FREE;
     const bool own = (rule == CADA_RULE_ALWAYS) || (lhs > rhs) || (tau >= s.D);
@@ -313,14 +325,14 @@ __global__ __launch_bounds__(R_NT) void k_rows(const RowsArgs a) {
     s.mask[mm] = up ? 1 : 0;
     s.tau[mm] = up ? 1 : tau + 1;
     const int sel = up ? was ^ 1 : was;    // an upload: the fresh row becomes the stored one
-    if (a.server) sel_s[mm] = (uint8_t)sel;
+    if (a.tail == kTailServer) sel_s[mm] = (uint8_t)sel;
     if (up) { s.sel[mm] = sel; ++ups; }
     else if (rule == CADA_RULE_CADA2 && tau >= s.D) atomicOr(s.err, 8u);   // (only a replay mask can do this)
   }
   if (ups) atomicAdd(&up_s, ups);
   // the server's operands, asked for before the rows of the aggregate
   float h0[2], vh0[2], th0[2], tl0[2];
-  if (a.server) {
+  if (a.tail == kTailServer) {
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       const int j = min(tid + u * R_NT, p - 1);
@@ -334,11 +346,11 @@ __global__ __launch_bounds__(R_NT) void k_rows(const RowsArgs a) {
     if (last >= 0) s.ring[last] = newest;
     if (k < s.trace_steps) s.t_rhs[k] = (float)rhs;
   }
-  if (!a.server) return;
+  if (a.tail != kTailServer) return;
 
   // ---- the server update: sums of four coordinates per thread, then one coordinate per thread (as in cada_logreg_small.hip)
   float *nab_s = reinterpret_cast<float *>(rows_smem + ((M + 15) & ~15));      // [p rounded up to 4]
-  const __amdgpu_buffer_rsrc_t store = far_buffer(s.gbuf, 2 * mp);      // (M p <= kRowsFusedServer)
+  const __amdgpu_buffer_rsrc_t store = far_buffer(s.gbuf, 2 * mp);      // (M p <= kServerState)
   for (int j = tid * 4; j < ps; j += R_NT * 4) {
     v4s nab = {0.f, 0.f, 0.f, 0.f};
     for (int m0 = 0; m0 < M; m0 += 16) {               // sixteen rows asked for before the first is added
@@ -358,11 +370,8 @@ __global__ __launch_bounds__(R_NT) void k_rows(const RowsArgs a) {
   double sqs = 0.0;
   for (int j = tid; j < p; j += R_NT) {
     const float nab = nab_s[j] / (float)M;
-    const int u = j < 2 * R_NT ? j / R_NT : 2;
-    float hh, vh, vv, t, tl;
-    if (u == 0) { hh = h0[0]; vh = vh0[0]; t = th0[0]; tl = tl0[0]; }
-    else if (u == 1) { hh = h0[1]; vh = vh0[1]; t = th0[1]; tl = tl0[1]; }
-    else { hh = s.h[j]; vh = s.vhat[j]; t = s.theta[j]; tl = s.theta_lo[j]; }
+    const bool first = j < R_NT;                         // (p <= kServerColumns)
+    float hh = first ? h0[0] : h0[1], vh = first ? vh0[0] : vh0[1], t = first ? th0[0] : th0[1], tl = first ? tl0[0] : tl0[1], vv;
     const float step = server_coordinate(s, s.alpha, nab, hh, vh, vv, t, tl);
     sqs = fma((double)step, (double)step, sqs);
     s.nabla[j] = nab; s.h[j] = hh; s.v[j] = vv; s.vhat[j] = vh; s.theta[j] = t; s.theta_lo[j] = tl;
@@ -589,6 +598,7 @@ __global__ __launch_bounds__(kBlock) void k_rows_sum(const RowsArgs a) {
   sq = block_sum_lds(sq, red);
   if (threadIdx.x == 0) put_far(s.lhs_part + (int64_t)m * s.n_lhs_part + blockIdx.x, sq);
   // (counted per worker first: a counter takes one arrival at a time)
+  if (a.tail == kTailNone) return;
   if (last_of(a.count + kCountWords * (1 + m), gridDim.x, &flag) && last_of(a.count, gridDim.y, &flag)) rule_all<kBlock>(s, a.replay, rule_s);
 }
 
@@ -644,26 +654,31 @@ bool rows_plan(Ctx *c, const cada_config *cfg) {
   const bool wide = cfg->p > 8192;
   const size_t ps = (size_t)((cfg->p + 3) / 4 * 4);
   int wc;
+  c->rows_tail = cfg->M <= (wide ? kWideRuleWorkers : kRuleWorkers) ? kTailRule : kTailNone;
   RowsKernel fn;
   if (wide) {
     const WideSplit w = wide_split(cfg->M, cfg->B, cfg->p);
     c->rows_shares = w.shares; c->rows_per_share = w.rows; c->rows_per_worker = w.per;
-    c->rows_server = 0;
     fn = wide_kernel(cfg->p);
     c->rows_lds = (size_t)((c->rows_per_share + 3) & ~3) * 12 + (cfg->p > 7 * 2048 ? (size_t)((cfg->p + 2047) / 2048) * R_NT * sizeof(v4s) : 0);
   } else {
     rows_split(cfg->M, cfg->B, cfg->p, &c->rows_shares, &c->rows_per_share);
-    c->rows_server = cfg->M <= kRowsFusedWorkers && (int64_t)cfg->M * cfg->p <= kRowsFusedServer;
+    if (cfg->p <= kServerColumns && cfg->M <= kServerWorkers && (int64_t)cfg->M * cfg->p <= kServerState) c->rows_tail = kTailServer;
     fn = rows_kernel(cfg->p, &wc);
     const size_t server = (size_t)((cfg->M + 15) & ~15) + ps * sizeof(float);
     c->rows_lds = (size_t)((c->rows_per_share + 3) & ~3) * 12 + (size_t)(R_NW / wc) * 2 * ps * sizeof(float);
-    if (c->rows_server && c->rows_lds < server) c->rows_lds = server;
+    if (c->rows_tail == kTailServer && c->rows_lds < server) c->rows_lds = server;
   }
   if (hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024) != hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
   c->rows = wide ? 2 : 1;
+  c->s.n_lhs_part = wide ? (int)((cfg->p + 1023) / 1024) : 2;
+  c->n_phases = 0;
+  c->phase_names[c->n_phases++] = "logreg_rows";
+  if (c->rows_tail == kTailNone) c->phase_names[c->n_phases++] = "rule";
+  if (c->rows_tail != kTailServer) c->phase_names[c->n_phases++] = "server_update";
   return true;
 }
 
@@ -679,7 +694,7 @@ int logreg_step_rows(Ctx *c, const int32_t *idx, const uint8_t *replay) {
   a.shares = c->rows_shares;
   a.rows = c->rows_per_share;
   a.wide = WideSplit{c->s.M, c->s.B, c->rows_shares, c->rows_per_share, c->rows_per_worker};
-  a.server = c->rows_server;
+  a.tail = c->rows_tail;
   int wc;
   prof_mark(c);
   hipLaunchKernelGGL(c->rows == 2 ? wide_kernel(c->s.p) : rows_kernel(c->s.p, &wc), dim3((unsigned)a.shares, c->rows == 2 ? 1u : (unsigned)c->s.M), dim3(R_NT), c->rows_lds, c->stream, a);
@@ -688,8 +703,8 @@ int logreg_step_rows(Ctx *c, const int32_t *idx, const uint8_t *replay) {
   prof_mark(c);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) { set_error("logistic step launch failed: %s", hipGetErrorString(e)); return CADA_EHIP; }
-  if (a.server) { c->force_resum = 0; return CADA_OK; }
-  return server_step(c);
+  if (a.tail == kTailServer) { c->force_resum = 0; return CADA_OK; }
+  return a.tail == kTailRule ? server_step(c) : rule_then_server(c, replay);
 }
 
 }  // namespace cada

@@ -278,13 +278,9 @@ int server_step(Ctx *c) {
   return CADA_OK;
 }
 
-int rule_and_server(Ctx *c, const uint8_t *replay) {
+int rule_then_server(Ctx *c, const uint8_t *replay) {
   DevState s = c->s;
   s.k = c->k;
-  if (s.rule == CADA_RULE_LAG || s.rule == CADA_RULE_ALWAYS) {   // (the always-upload rule only records it)
-    const int nb = (int)min((int64_t)s.n_lhs_part, (s.p + 4 * kBlock - 1) / (4 * kBlock));
-    hipLaunchKernelGGL(k_lag_lhs, dim3((unsigned)max(nb, 1), (unsigned)s.M), dim3(kBlock), 0, c->stream, s);
-  }
   hipLaunchKernelGGL(k_rule, dim3((unsigned)((s.M + 3) / 4)), dim3(kBlock), 0, c->stream, s, replay);
   prof_mark(c);
   const hipError_t e = hipGetLastError();
@@ -293,6 +289,16 @@ int rule_and_server(Ctx *c, const uint8_t *replay) {
     return CADA_EHIP;
   }
   return server_step(c);
+}
+
+int rule_and_server(Ctx *c, const uint8_t *replay) {
+  DevState s = c->s;
+  s.k = c->k;
+  if (s.rule == CADA_RULE_LAG || s.rule == CADA_RULE_ALWAYS) {   // (the always-upload rule only records it)
+    const int nb = (int)min((int64_t)s.n_lhs_part, (s.p + 4 * kBlock - 1) / (4 * kBlock));
+    hipLaunchKernelGGL(k_lag_lhs, dim3((unsigned)max(nb, 1), (unsigned)s.M), dim3(kBlock), 0, c->stream, s);
+  }
+  return rule_then_server(c, replay);
 }
 
 int ring_finalize(Ctx *c) {

@@ -72,11 +72,11 @@ def test_block_of_another_configuration_is_refused():
     a.restore(block)            # a valid block still loads afterwards
 
 
-@pytest.mark.parametrize("M,B", [(3, 20), (20, 20), (3, 1)])
+@pytest.mark.parametrize("M,B", [(3, 20), (24, 20), (3, 1)])
 @pytest.mark.parametrize("save,load", [(a, b) for a in ("two_pass", "rows", "whole") for b in ("two_pass", "rows", "whole") if a != b])
 def test_block_of_another_path(save, load, M, B):
     """The path is no part of a block.  The newest squared step is kept in parts that each path cuts in its own way (p = 784 are four
-    server blocks; M = 3 is fewer, M = 20 more, and too much state for a server inside the rows kernel): a run that goes on on
+    server blocks; M = 3 is fewer, M = 24 more, and too much state for a server inside the rows kernel): a run that goes on on
     another path forms the right-hand sides that the saving context forms, and both report the same ring."""
     from paper_2012_15469_amd import binding
     from paper_2012_15469_amd.binding import cada_profile_phase_names

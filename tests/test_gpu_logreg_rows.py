@@ -46,6 +46,13 @@ def test_wide_rows_path_shares_of_several_workers(p, M, B, rule):
     test_rows_path(p, M, B, rule, K=8, spare=40 if rule == configs.RULE_LAG else 3)
 
 
+# the rule in the last workgroup up to 512 (more than 8192 columns: 32) workers, in a launch of its own for more
+@pytest.mark.parametrize("p,M,B,rule", [(54, 512, 33, 2), (54, 513, 33, 1), (257, 530, 40, 3), (1025, 513, 8, 2), (2050, 513, 9, 0), (8193, 32, 5, 1), (8200, 33, 5, 2),
+                                        (10241, 40, 9, 0)])
+def test_rows_path_many_workers(p, M, B, rule):
+    test_rows_path(p, M, B, rule, K=8, spare=40 if rule == configs.RULE_LAG else 3)
+
+
 def test_rows_path_flags_and_repeats():
     """An index out of range is clamped and flagged; two runs agree bit for bit."""
     from common import run_library
@@ -60,14 +67,21 @@ def test_rows_path_flags_and_repeats():
         assert np.array_equal(out[name], ref[name]), name
 
 
-@pytest.mark.parametrize("p,M,big,small", [(8192, 3, 2048, 2.0 ** -10), (2048, 1, 512, 2.0 ** -11)])
-def test_sums_of_the_rule_keep_small_terms(p, M, big, small):
+@pytest.mark.parametrize("p,M", [(8192, 3), (1024, 1)])
+def test_sums_of_the_rule_keep_small_terms(p, M):
     """The rule compares sums of squares in double.  All values here are powers of two: every gradient, and with alpha = 1 every step of the SGD
-    server, is exact; a float32 sum over a few of the large squares (4 or 1) and then small ones (2^-22, 2^-24: half a unit in
-    the last place) loses all of these.  Shapes: left-hand side, and (a server in the same launch) the squared step."""
+    server, is exact; a float32 sum that meets a large square first and then small ones of half a unit in the last place loses these.
+    8192 columns: the left-hand side, four squares of 1 and then twelve of 2^-22 in each lane.  1024 columns and one worker: the
+    server runs in the same launch, and the squared step is 1 in the first and 2^-24 in each other wavefront's columns."""
     B = 128
-    x = torch.full((p,), small, device="cuda")
-    x[:big] = 2.0
+    x = torch.zeros(p, device="cuda")
+    if p == 8192:
+        x[:] = 2.0 ** -10
+        x[:2048] = 2.0
+    else:
+        x[64:512:64] = 2.0 ** -11
+        x[0] = 2.0
+    squares = float(((0.5 * x.double()) ** 2).sum())
     X = x.repeat(M * B, 1).contiguous()
     eng = binding.Cada(model="logreg", layer_dims=[p], M=M, B=B, n_samples=[B] * M, X=X, y=torch.ones(M * B, device="cuda"),
                        theta0=torch.zeros(p, device="cuda"), rule=3, D=50, d_max=10, c=0.5, alpha=1.0, beta1=0.9, beta2=0.999, eps=1e-8, lam=0.0,
@@ -76,8 +90,8 @@ def test_sums_of_the_rule_keep_small_terms(p, M, big, small):
     eng.step(torch.arange(B, dtype=torch.int32, device="cuda").repeat(M, 1).contiguous())
     st = eng.state()
     torch.cuda.synchronize()
-    want = np.float32(big * 1.0 + (p - big) * (0.5 * small) ** 2)
-    assert want != np.float32(big)
+    want = np.float32(squares)
+    assert want == (2048 + 6144 * 2.0 ** -22 if p == 8192 else 1 + 8 * 2.0 ** -24)
     assert (st["trace_lhs"].cpu().numpy().ravel() == want).all()
     assert st["lhs"].cpu().numpy().tolist() == [want] * M
     assert st["ring"].cpu().numpy()[0] == want
