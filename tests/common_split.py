@@ -6,8 +6,8 @@ import subprocess
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 # (p, M, B, rule) whose rows are cut evenly, so that shares meet several workers: five, six and seven quads per lane
-SHARED_WORKERS = [(8196, 129, 13, 2), (8199, 137, 15, 1), (8193, 600, 2, 2), (10240, 129, 14, 3), (10241, 131, 13, 1), (12288, 133, 14, 2),
-                  (12289, 129, 13, 1), (14335, 129, 13, 2), (14336, 300, 1, 1)]
+SHARED_WORKERS = [(8196, 129, 19, 2), (8199, 137, 21, 1), (8193, 600, 2, 2), (10240, 129, 20, 3), (10241, 131, 19, 1), (12288, 133, 20, 2),
+                  (12289, 129, 19, 1), (14335, 129, 19, 2), (14336, 300, 1, 1)]
 
 _SRC = """
 #include "cada_rows_split.h"

@@ -52,3 +52,10 @@ def test_shapes_whose_shares_meet_several_workers(split, p, M, B, rule):
             pieces.add((n + batch - 1) // batch % 2)
             f += n
     assert 1 in pieces and (0 in pieces or B < 2 * batch)
+
+
+@pytest.mark.parametrize("M,B,p,low,high", [(16, 64, 20479, 8, 12), (4, 64, 20479, 12, 24), (64, 16, 20479, 2, 4), (16, 16, 20479, 4, 6), (37, 75, 20001, 6, 6),
+                                            (1, 1024, 20479, 32, 32)])
+def test_shares_per_worker_near_the_best_measured(split, M, B, p, low, high):
+    """Counts within 4 % of the best of 1, 2, 4, 6, 8, 12, 16, 24, 32 shares per worker on the hardware."""
+    assert low <= split(M, B, p).per <= high
