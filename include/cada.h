@@ -59,8 +59,10 @@ enum { CADA_MODEL_LOGREG = 0, CADA_MODEL_MLP = 1 };
 enum {
   CADA_PATH_AUTO = 0,        /* single pass where it applies (p > 20480, a multiple of 4), whole steps for small
                                 workloads (at most 64 workers of at most 64 rows whose minibatch and the server's
-                                vectors fit one workgroup's LDS), one to three launches per step with the rows in
-                                registers for other rows of 4 to 20480 columns, two passes otherwise */
+                                vectors fit one workgroup's LDS), one to four launches per step with the rows in
+                                registers for other rows of 4 to 20480 columns where that is faster (not for many
+                                workers of few rows, nor for few workers above 4096 columns), two passes otherwise.
+                                A request below that a shape does not allow takes what the shape takes by itself */
   CADA_PATH_TWO_PASS = 1,    /* two streaming passes over the minibatch rows (any shape) */
   CADA_PATH_SINGLE_PASS = 2, /* one pass: the rows stay in registers/LDS between the two products */
   CADA_PATH_WHOLE_STEPS = 3  /* whole iterations in one launch, one workgroup per worker, whenever the shape allows it,

@@ -396,10 +396,11 @@ int cada_init(const cada_config *cfg, const float *theta0, cada_ctx **out) {
   s.eps = (float)cfg->eps; s.lam = (float)cfg->lambda_l2; s.c = cfg->c;
   if (cfg->model == CADA_MODEL_LOGREG) {
     // the requested path first; a request that the shape does not allow falls back to the others
+    const bool rows = rows_better(c, cfg);
     if (cfg->path == CADA_PATH_WHOLE_STEPS) small_plan(c, cfg);
-    if (!c->small && cfg->path != CADA_PATH_TWO_PASS && !(cfg->path == CADA_PATH_AUTO && cfg->p <= kRowsWidest) && fused_plan(c, cfg)) s.n_lhs_part = kFusedWaves * c->fused_Q;
+    if (!c->small && cfg->path != CADA_PATH_TWO_PASS && (cfg->path == CADA_PATH_SINGLE_PASS || !rows) && fused_plan(c, cfg)) s.n_lhs_part = kFusedWaves * c->fused_Q;
     else if (cfg->path == CADA_PATH_AUTO) small_plan(c, cfg);
-    if (!c->small && !c->fused && rows_plan(c, cfg)) {
+    if (rows && !c->small && !c->fused && rows_plan(c, cfg)) {
       // (its phases are named there)
     } else if (c->small) {
       c->n_phases = 1; c->phase_names[0] = "logreg_whole_steps";

@@ -304,6 +304,7 @@ int logreg_gradients_fused(Ctx *c, const int32_t *idx);
 constexpr int64_t kRowsWidest = 10 * 2048;          // columns of the widest row that a workgroup's registers hold
 bool rows_serves(const cada_config *cfg);
 size_t rows_part_floats(const cada_config *cfg);
+bool rows_better(const Ctx *c, const cada_config *cfg);      // the shape is served, and no other kernel is faster
 bool rows_plan(Ctx *c, const cada_config *cfg);
 int logreg_step_rows(Ctx *c, const int32_t *idx, const uint8_t *replay);   // gradients, rule and server
 int small_steps(Ctx *c, const int32_t *idx, const uint8_t *replay, int64_t n_steps);

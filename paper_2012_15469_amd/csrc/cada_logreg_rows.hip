@@ -624,33 +624,22 @@ RowsKernel wide_kernel(int64_t p) {
 }
 }  // namespace
 
-// Rows per share and shares per worker: as many shares as give every CU a workgroup, while a share keeps the rows of one batch of its
-// eight wavefronts (p <= 1024) or ten rows (each wavefront then has a part of every row) and 32 KB, at most eight.  Measured, us per step with
-// 1, 2, 4, 8, 16 shares: M = 10, B = 200, p = 784: 25, 21, 19, 18, 19; M = 64, B = 128, p = 784: 23, 21.5, 21, 30, 51;
-// M = 100, B = 256, p = 4000: 133, 90, 93, 111, 138; M = 10, B = 64, p = 4000: 33.5, 26.5, 22, 22 (two-pass kernels: 27, 32, 147, 25).
-static void rows_split(int M, int B, int64_t p, int *shares, int *rows) {
-  const int least = p <= 1024 ? 24 : 10;
-  const int n = max(1, min(min(8, (int)((int64_t)B * p / 8192)), min(256 / M, B / least)));
-  *rows = (B + n - 1) / n;
-  *shares = (B + *rows - 1) / *rows;
-}
-
 bool rows_serves(const cada_config *cfg) {
   return cfg->model == CADA_MODEL_LOGREG && cfg->path != CADA_PATH_TWO_PASS && cfg->p >= 4 && cfg->p <= kRowsWidest &&
          (cfg->p <= 8192 || (int64_t)cfg->M * cfg->B < (1ll << 31) - 1);
 }
 size_t rows_part_floats(const cada_config *cfg) {
   if (!rows_serves(cfg)) return 0;
-  int shares, rows;
   const size_t ps = (size_t)((cfg->p + 3) / 4 * 4);
   if (cfg->p > 8192) return (size_t)wide_slots(wide_split(cfg->M, cfg->B, cfg->p)) * 2 * ps;
-  rows_split(cfg->M, cfg->B, cfg->p, &shares, &rows);
+  const int shares = rows_split(cfg->M, cfg->B, cfg->p).shares;
   return shares > 1 ? (size_t)cfg->M * shares * 2 * ps : 0;
 }
 
+bool rows_better(const Ctx *c, const cada_config *cfg) { return rows_serves(cfg) && rows_preferred(cfg->M, cfg->B, cfg->p, c->vec); }
+
 bool rows_plan(Ctx *c, const cada_config *cfg) {
   c->rows = 0;
-  if (!rows_serves(cfg)) return false;
   const bool wide = cfg->p > 8192;
   const size_t ps = (size_t)((cfg->p + 3) / 4 * 4);
   int wc;
@@ -662,7 +651,8 @@ bool rows_plan(Ctx *c, const cada_config *cfg) {
     fn = wide_kernel(cfg->p);
     c->rows_lds = (size_t)((c->rows_per_share + 3) & ~3) * 12 + (cfg->p > 7 * 2048 ? (size_t)((cfg->p + 2047) / 2048) * R_NT * sizeof(v4s) : 0);
   } else {
-    rows_split(cfg->M, cfg->B, cfg->p, &c->rows_shares, &c->rows_per_share);
+    const RowsSplit r = rows_split(cfg->M, cfg->B, cfg->p);
+    c->rows_shares = r.shares; c->rows_per_share = r.rows;
     if (cfg->p <= kServerColumns && cfg->M <= kServerWorkers && (int64_t)cfg->M * cfg->p <= kServerState) c->rows_tail = kTailServer;
     fn = rows_kernel(cfg->p, &wc);
     const size_t server = (size_t)((cfg->M + 15) & ~15) + ps * sizeof(float);

@@ -1,11 +1,28 @@
-// How cada_logreg_rows.hip cuts the minibatch rows of more than 8192 columns into shares, one workgroup each: plain C++ without
-// device code, so that a test can go over it on the host.
+// Which logistic shapes cada_logreg_rows.hip takes by itself, and how it cuts their minibatch rows into shares, one workgroup each: plain
+// C++ without device code, so that a test can go over it on the host.
 #pragma once
 
 #include <cstdint>
 
 namespace cada {
 
+// Up to 8192 columns: rows per share and shares per worker, as many shares as give every CU a workgroup, while a share keeps the rows of one batch of its
+// eight wavefronts (p <= 1024) or ten rows (each wavefront then has a part of every row) and 32 KB, at most eight.  Measured, us per step with
+// 1, 2, 4, 8, 16 shares: M = 10, B = 200, p = 784: 25, 21, 19, 18, 19; M = 64, B = 128, p = 784: 23, 21.5, 21, 30, 51;
+// M = 100, B = 256, p = 4000: 133, 90, 93, 111, 138; M = 10, B = 64, p = 4000: 33.5, 26.5, 22, 22 (two-pass kernels: 27, 32, 147, 25).
+struct RowsSplit {
+  int shares, rows;                              // per worker; per share (at most)
+};
+constexpr RowsSplit rows_split(int M, int B, int64_t p) {
+  int64_t n = B * p / 8192 < 8 ? B * p / 8192 : 8;
+  if (n > 256 / M) n = 256 / M;
+  if (n > B / (p <= 1024 ? 24 : 10)) n = B / (p <= 1024 ? 24 : 10);
+  if (n < 1) n = 1;
+  const int rows = (int)((B + n - 1) / n);
+  return {(B + rows - 1) / rows, rows};
+}
+
+// More than 8192 columns.
 constexpr int64_t kWideEven = 7 * 2048;          // columns up to which a share may meet several workers
 constexpr int kWideRows = 2048;                  // rows of a share at most (their offsets and labels lie in LDS)
 
@@ -51,6 +68,25 @@ constexpr WideSplit wide_split(int M, int B, int64_t p) {
   const int64_t even = cus > least ? cus : least, most = (T + even - 1) / even;
   if (p <= kWideEven && kSumsOfRow * ((even + 255) / 256) * (most + 6) + even < best) { w.shares = (int)even; w.rows = (int)most; w.per = 0; }
   return w;
+}
+
+// Whether the path is taken by itself (p >= 4; vec: 4 where rows can be read 16 bytes at a time by the kernels that need that).  Not where one
+// of the kernels that it stands beside is faster; measured, us per step here / two passes over the rows:
+//   up to 1024 columns, many workers of few rows: a workgroup has eight wavefronts for one row each and the CUs take the workers in
+//     rounds.  p = 784, B = 8: M = 256: 23.5 / 24.8; 300: 31 / 27; 1024: 66 / 50; 4096: 235 / 158; but M = 1024, B = 32: 0.94 of the time;
+//   more columns: the same with some rows, p = 3000, M = 4096: B = 1: 1.24 of the time, 4: 1.09, 8: 0.91; M = 1024, B = 4: 0.99;
+//   more than 4096 columns: a wavefront's part of a row takes two loads and more, and few workgroups leave CUs idle, where the two
+//     passes cut the columns as well.  p = 6000, M = 4: B = 8: 0.86, 16: 1.05, 65: 1.09, 1024: 1.05; B = 65: M = 8 (48 workgroups): 1.04,
+//     12 (72): 0.96.  Where the two passes read 4 bytes at a time: p = 8191, M = 4: B = 65: 0.95, 256: 0.99, 512: 1.13; M = 1, B = 256: 1.18;
+//   more than 8192 columns / the single-pass kernel: p = 10240, M = 700: B = 1: 0.95, 4: 1.04, 16: 0.99; M = 4096, B = 4: 1.30; p = 20480,
+//     M = 512: B = 4: 1.00, M = 700: 1.09; two passes take as long at best (p = 20479, M = 4, B = 64: 0.95 of the time, M = 16: 1.02).
+//   8192 columns: the single-pass kernel takes 1.1 to 3.4 times as long.
+constexpr bool rows_preferred(int M, int B, int64_t p, int vec) {
+  if (p > 8192) return vec != 4 || M <= 512 || B >= 16;
+  if (p <= 1024) return M <= 256 || B >= 32;
+  if (M > 512 && B < 8) return false;
+  if (p <= 4096 || p == 8192 || M * rows_split(M, B, p).shares >= 64) return true;
+  return B <= (vec == 4 ? 10 : M > 1 ? 256 : 128);
 }
 
 }  // namespace cada

@@ -14,6 +14,8 @@ _SRC = """
 using namespace cada;
 extern "C" {
 void split(int M, int B, long p, int *out) { const WideSplit w = wide_split(M, B, p); out[0] = w.shares; out[1] = w.rows; out[2] = w.per; out[3] = wide_slots(w); }
+int preferred(int M, int B, long p, int vec) { return rows_preferred(M, B, p, vec); }
+void narrow(int M, int B, long p, int *out) { const RowsSplit r = rows_split(M, B, p); out[0] = r.shares; out[1] = r.rows; }
 int first(const WideSplit *w, int c) { return wide_first(*w, c); }
 int share(const WideSplit *w, int f) { return wide_share(*w, f); }
 int slot(const WideSplit *w, int c, int m) { return wide_slot(*w, c, m); }
@@ -43,4 +45,11 @@ def compile_split(tmp):
         def share(self, f): return dll.share(C.byref(self._w), f)
         def slot(self, c, m): return dll.slot(C.byref(self._w), c, m)
 
+    def narrow(M, B, p):
+        out = (C.c_int * 2)()
+        dll.narrow(M, B, C.c_long(p), out)
+        return tuple(out)
+
+    Split.narrow = staticmethod(narrow)
+    Split.preferred = staticmethod(lambda M, B, p, vec: bool(dll.preferred(M, B, C.c_long(p), vec)))
     return Split

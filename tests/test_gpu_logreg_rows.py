@@ -9,7 +9,7 @@ import torch
 from cada_synth import configs, generators
 from paper_2012_15469_amd import binding
 
-from common import check_protocol, upload
+from common import check_protocol, to_dev, upload
 from common_split import SHARED_WORKERS
 
 pytestmark = pytest.mark.gpu
@@ -51,6 +51,22 @@ def test_wide_rows_path_shares_of_several_workers(p, M, B, rule):
                                         (10241, 40, 9, 0)])
 def test_rows_path_many_workers(p, M, B, rule):
     test_rows_path(p, M, B, rule, K=8, spare=40 if rule == configs.RULE_LAG else 3)
+
+
+@pytest.mark.parametrize("p,M,B,path,phase", [
+    (784, 257, 8, binding.PATH_AUTO, "logreg_two_pass"), (784, 257, 8, binding.PATH_SINGLE_PASS, "logreg_two_pass"), (784, 257, 32, binding.PATH_AUTO, "logreg_rows"),
+    (6000, 2, 40, binding.PATH_AUTO, "logreg_two_pass"), (6000, 2, 10, binding.PATH_AUTO, "logreg_rows"), (8196, 513, 4, binding.PATH_AUTO, "logreg_single_pass"),
+    (8197, 513, 4, binding.PATH_AUTO, "logreg_rows"), (8196, 3, 8, binding.PATH_AUTO, "logreg_rows"), (8196, 3, 8, binding.PATH_SINGLE_PASS, "logreg_single_pass"),
+    (8196, 3, 8, binding.PATH_WHOLE_STEPS, "logreg_rows"), (8196, 3, 8, binding.PATH_TWO_PASS, "logreg_two_pass"), (54, 3, 8, binding.PATH_WHOLE_STEPS, "logreg_whole_steps")])
+def test_routes(p, M, B, path, phase):
+    """Which kernels a shape and a request take; a request that the shape does not allow takes what it would take by itself."""
+    cfg = configs.CFG1.scaled(name="route", layer_dims=(p,), M=M, N_m=B, B=B, K=2)
+    prob = generators.make_problem(cfg)
+    eng = binding.Cada.from_config(cfg, *upload(prob), path=path)
+    assert phase in binding.cada_profile_phase_names(eng.ctx)
+    eng.step(to_dev(generators.make_schedule(cfg)[0].astype(np.int32)))
+    torch.cuda.synchronize()
+    eng.close()
 
 
 def test_rows_path_flags_and_repeats():

@@ -1,4 +1,4 @@
-"""How the rows of more than 8192 columns are cut into shares (csrc/cada_rows_split.h), on the host: every row belongs to
+"""How rows are cut into shares and which shapes take that path (csrc/cada_rows_split.h), on the host: every row belongs to
 exactly one share, the sums of every pair (share, worker) have a slot of their own inside the buffer, and k_rows_sum finds a worker's."""
 import pytest
 
@@ -52,6 +52,27 @@ def test_shapes_whose_shares_meet_several_workers(split, p, M, B, rule):
             pieces.add((n + batch - 1) // batch % 2)
             f += n
     assert 1 in pieces and (0 in pieces or B < 2 * batch)
+
+
+@pytest.mark.parametrize("p", [4, 54, 257, 1024, 1025, 4096, 4097, 8192])
+def test_shares_of_narrow_rows(split, p):
+    for M in (1, 2, 3, 31, 32, 33, 64, 255, 256, 257, 1000, 65535):
+        for B in (1, 9, 10, 11, 23, 24, 25, 64, 100, 255, 4095, 4096):
+            shares, rows = split.narrow(M, B, p)
+            assert 1 <= shares <= 8 and (shares - 1) * rows < B <= shares * rows
+            assert shares == 1 or M * shares <= 256
+            # offsets and labels, then the sums: what the kernel asks for of the 150 KB of LDS it is allowed
+            assert (rows + 3) // 4 * 4 * 12 + (8 if p <= 1024 else 1) * 2 * ((p + 3) // 4 * 4) * 4 <= 150 * 1024
+
+
+@pytest.mark.parametrize("p,M,B,vec,rows", [
+    (784, 256, 1, 4, True), (784, 257, 31, 4, False), (784, 257, 32, 4, True), (1024, 300, 8, 4, False), (1025, 300, 8, 1, True),
+    (3000, 512, 1, 4, True), (3000, 513, 7, 4, False), (3000, 513, 8, 4, True),
+    (4096, 1, 64, 4, True), (4100, 1, 64, 4, False), (4100, 4, 10, 4, True), (4100, 4, 11, 4, False), (6000, 12, 65, 4, True), (6000, 8, 65, 4, False),
+    (8191, 1, 128, 1, True), (8191, 1, 129, 1, False), (8191, 2, 256, 1, True), (8191, 2, 257, 1, False), (8192, 1, 4096, 4, True),
+    (8196, 512, 1, 4, True), (8196, 513, 15, 4, False), (8196, 513, 16, 4, True), (8197, 4096, 1, 1, True)])
+def test_route(split, p, M, B, vec, rows):
+    assert split.preferred(M, B, p, vec) == rows
 
 
 @pytest.mark.parametrize("M,B,p,low,high", [(16, 64, 20479, 8, 12), (4, 64, 20479, 12, 24), (64, 16, 20479, 2, 4), (16, 16, 20479, 4, 6), (37, 75, 20001, 6, 6),
