@@ -1249,12 +1249,11 @@ __global__ __launch_bounds__(kBlock) void k_stage(const StageArgs a) {
 }
 
 // Hidden-layer bias gradient and its innovation from the per-tile partial sums of k_mm5<EPI_DA>.
-// grid (ceil(d/256), M)
-__global__ __launch_bounds__(kBlock) void k_bias_finish(const DevState s, const float *dbpart, const float *ddbpart, int RT, int d,
-                                                        int64_t offb, int lhs_slot) {
-  __shared__ float red[4];
+// grid (ceil(d / 64), M), one wavefront each
+__global__ __launch_bounds__(kWave) void k_bias_finish(const DevState s, const float *dbpart, const float *ddbpart, int RT, int d,
+                                                       int64_t offb, int lhs_slot) {
   const int m = blockIdx.y;
-  const int c = blockIdx.x * kBlock + threadIdx.x;
+  const int c = blockIdx.x * kWave + threadIdx.x;
   float sq = 0.f;
   if (c < d) {
     float gsum = 0.f, dsum = 0.f;
@@ -1269,8 +1268,8 @@ __global__ __launch_bounds__(kBlock) void k_bias_finish(const DevState s, const 
     }
     sq = dsum * dsum;
   }
-  const float tot = block_sum(sq, red);
-  if (threadIdx.x == 0) s.lhs_part[(int64_t)m * s.n_lhs_part + lhs_slot + blockIdx.x] = tot;
+  const float tot = wave_sum(sq);
+  if (ddbpart && threadIdx.x == 0) s.lhs_part[(int64_t)m * s.n_lhs_part + lhs_slot + blockIdx.x] = tot;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1494,6 +1493,15 @@ static int mlp_forward(Ctx *c, MlpPlan &P, const DevState &s, const int32_t *idx
   return CADA_OK;
 }
 
+// Whether a layer's weight-gradient launch also forms its bias gradient.  That saves a launch of 5 us, but a tile that does it waits for its own
+// stores first (some 8 us), which counts where a workgroup has several such tiles, or few workgroups have one and the others wait for them.
+// us per step inside / outside, CADA2, B = 128: 784-512-10: M = 64 (256 such tiles): 0.987, 200 (800): 1.017; 617-301-150-26:
+// M = 100 (300): 0.983; 1024-1024-32: M = 32 (256, M din = 32768): 0.992, 64: 1.016, 200: 1.049; 2000-64-5: M = 32 (32, 64000):
+// 0.989, 64: 1.012, 200: 1.035; 3072-1024-10: M = 16: 1.000, 64: 1.014.  (Up to 32 units k_skinny forms the weight gradient.)
+static bool bias_inside(int M, int din, int dout) {
+  return dout > 32 && (int64_t)M * tiles128(dout) <= 512 && (int64_t)M * din < 65536;
+}
+
 int mlp_gradients(Ctx *c, const int32_t *idx) {
   MlpPlan &P = *static_cast<MlpPlan *>(c->mlp);
   DevState s = c->s;
@@ -1534,7 +1542,7 @@ int mlp_gradients(Ctx *c, const int32_t *idx) {
       g.offW = P.offW[l - 1]; g.lhs_slot0 = P.lhs_w_slot[l - 1];
       if (l == L) {     // the last layer's launch also finishes its bias gradient from the forward launch's row-block sums
         g.lastb = P.lastb; g.nrb = Bp / 32; g.offb = P.offb[L - 1]; g.lhs_slot_b = P.lhs_b_slot[L - 1];
-      } else if (dout > 32) {       // and the other layers' from the activation-gradient launch's sums
+      } else if (bias_inside(M, din, dout)) {       // and the other layers' from the activation-gradient launch's sums
         g.dbpart = P.dbpart; g.ddbpart = P.ddbpart; g.nband = 2 * P.RT; g.offb = P.offb[l - 1]; g.lhs_slot_b = P.lhs_b_slot[l - 1];
       }
       if (const int rc = launch_mm5<EPI_DW>(c, g, M)) return rc;
@@ -1560,8 +1568,8 @@ int mlp_gradients(Ctx *c, const int32_t *idx) {
       g.maskbits = P.maskbits[q];
       g.dbpart = P.dbpart; g.ddbpart = P.ddbpart;
       if (const int rc = launch_mm5<EPI_DA>(c, g, M)) return rc;
-      if (din <= 32)      // (k_skinny serves that layer's weight gradient)
-        hipLaunchKernelGGL(k_bias_finish, dim3((din + 255) / 256, M), dim3(kBlock), 0, st, s, P.dbpart, plain ? nullptr : P.ddbpart, 2 * P.RT, din,
+      if (!bias_inside(M, P.d[q - 1], din))
+        hipLaunchKernelGGL(k_bias_finish, dim3((din + kWave - 1) / kWave, M), dim3(kWave), 0, st, s, P.dbpart, plain ? nullptr : P.ddbpart, 2 * P.RT, din,
                          P.offb[q - 1], P.lhs_b_slot[q - 1]);
     }
   }
