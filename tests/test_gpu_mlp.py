@@ -175,13 +175,14 @@ def test_forward_blocks_and_odd_widths(dims, M, B, rule):
 
 
 @pytest.mark.parametrize("rule", [configs.RULE_CADA1, configs.RULE_CADA2])
-@pytest.mark.parametrize("h", [33, 64, 65, 129, 257])
-def test_left_hand_side_of_bias_innovations(h, rule):
+@pytest.mark.parametrize("h,M", [(33, 3), (64, 3), (65, 3), (129, 3), (257, 3), (33, 513), (129, 257)])
+def test_left_hand_side_of_bias_innovations(h, M, rule):
     """Every hidden bias counts once in the left-hand side, whichever partial sum it goes to (64 units each).  With X = 0 and a small
     first bias the weights' innovations are next to nothing, so that four fifths of it are the first layer's biases:
     64 of 257 units left out would change its root by 10 %.  The vectors whose norm it is are differences rounded to bf16, 2^-9 of the
-    innovation's norm, and with CADA1 less a stored one, rounded once more: norms differ by no more than that."""
-    cfg = configs.CFG4.scaled(name="bias_lhs", layer_dims=(5, h, 3), M=3, N_m=40, B=20, K=6, D=4, rule=rule)
+    innovation's norm, and with CADA1 less a stored one, rounded once more: norms differ by no more than that.  (With the many workers of the
+    last two shapes the bias gradient is a launch of its own.)"""
+    cfg = configs.CFG4.scaled(name="bias_lhs", layer_dims=(5, h, 3), M=M, N_m=40, B=20, K=6, D=4, rule=rule)
     prob = generators.make_problem(cfg)
     prob.X[:] = 0.0
     prob.theta0[5 * h:6 * h] = 1e-3
