@@ -1,5 +1,5 @@
 // Objective and accuracy of the MLP on all the data (not part of an iteration): one launch takes every row of X through
-// all layers and leaves each row's loss and hit, a second adds them up per worker.
+// all layers and leaves each row's loss and hit, a second adds them up per worker.  (Few rows: a launch per hidden layer, see eval_plan.)
 //
 // The rows of all workers lie one after the other, so the data is one matrix.  A workgroup takes RT = 64 NR of its rows at a
 // time through the network: for every tile of UT = 128 NU units it sums W X^T over the inputs (split operands, three bf16 MFMA
@@ -38,6 +38,8 @@ struct EvalArgs {
   bf16_t *act[2][2];         // [layer parity][hi, lo]: activations [workgroup][RT][lda] (L >= 3)
   int64_t lda;
   float2 *rowval;            // [rows] (loss, hit)
+  float *zpart;              // layer by layer: [unit tile][row_pad][32] the logits' parts from each tile of the last hidden layer's units, or
+  int64_t row_pad;           //   null: this layer's activations go to act[0] by rows of X
 };
 
 // 16 bytes per lane straight to LDS (consecutive in lane order from byte `lds` on).  The compiler does not count these loads; the
@@ -49,7 +51,8 @@ __device__ __forceinline__ void to_lds(const bf16_t *base, uint32_t off, uint32_
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory");
 }
 
-// HID: hidden layers (2: two or more)
+// HID: hidden layers (2: two or more), or kByLayer: one hidden layer a launch (layer[0]; layer[1] is the next one), one tile of its units a workgroup
+constexpr int kByLayer = 3;
 template <int NR, int NU, int HID>
 __global__ __launch_bounds__(512) void k_eval_net(const EvalArgs a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -61,19 +64,19 @@ __global__ __launch_bounds__(512) void k_eval_net(const EvalArgs a) {
   const int wu = w & 3, wr = w >> 2;                        // this wavefront's units and rows
   const int half = lane >> 5, l32 = lane & 31;
   const int ntiles = (int)((a.rows + RT - 1) / RT);
-  const int nhid = HID < 2 ? 1 : a.L - 1;                   // products in the steps below (no hidden layer: the logits are their result)
+  const int nhid = HID != 2 ? 1 : a.L - 1;                   // products in the steps below (no hidden layer: the logits are their result)
   // A loading instruction fills 16 rows of 32 values of a tile: the lane at position `lane` fetches the piece that lds_piece puts there
   const int piece = lds_piece(lane), prow = piece >> 2, pq = piece & 3;
 
   // Loading cursor: (row tile, layer, unit tile, step).  Row addresses are a scalar plus this lane's part: rows past the last
   // one are read as well (from what follows X's copies in the workspace: at least 256 rows of gathered ones) and dropped.
-  int ltile = blockIdx.x, ll = 0, lct = 0, lk = 0;
+  int ltile = blockIdx.x, ll = 0, lct = HID == kByLayer ? (int)blockIdx.y : 0, lk = 0;
   EvalLayer le = a.layer[0];
   const bf16_t *src[2];                                     // hi, lo: first row of the tile
   int64_t sld = 0;
   uint32_t xoff = 0;
   auto set_source = [&]() __attribute__((always_inline)) {
-    const bool first = HID < 2 || ll == 0;
+    const bool first = HID != 2 || ll == 0;
     sld = first ? a.ldx : a.lda;
     xoff = (uint32_t)(prow * (int)sld + pq * 8) * 2u;
 #pragma unroll
@@ -105,8 +108,10 @@ __global__ __launch_bounds__(512) void k_eval_net(const EvalArgs a) {
   auto advance = [&](bool &done) __attribute__((always_inline)) -> bool {
     if (++lk < le.nk) return true;
     lk = 0;
-    if (++lct * UT < le.N) return true;
-    lct = 0;
+    if constexpr (HID != kByLayer) {
+      if (++lct * UT < le.N) return true;
+      lct = 0;
+    }
     if constexpr (HID == 2) {
       if (++ll < nhid) { le = a.layer[ll]; set_source(); return false; }
       ll = 0;
@@ -129,7 +134,8 @@ __global__ __launch_bounds__(512) void k_eval_net(const EvalArgs a) {
     const int64_t r0 = (int64_t)tile * RT;
     for (int l = 0; l < nhid; ++l) {
       const EvalLayer e = a.layer[l];
-      for (int u0 = 0; u0 < e.N; u0 += UT) {
+      const int u1 = HID == kByLayer ? (int)blockIdx.y * UT : 0, u2 = HID == kByLayer ? u1 + 1 : e.N;
+      for (int u0 = u1; u0 < u2; u0 += UT) {
         f32x16 acc[NU][NR];
 #pragma unroll
         for (int i = 0; i < NU; ++i)
@@ -197,8 +203,9 @@ __global__ __launch_bounds__(512) void k_eval_net(const EvalArgs a) {
           auto value = [&](int i, int j, int r) __attribute__((always_inline)) {
             return fmaxf(acc[i][j][r] + bias[r], 0.f);
           };
-          if (HID == 2 && l + 1 < nhid) {
-            bf16_t *dh = a.act[l & 1][0] + ((int64_t)blockIdx.x * RT + rl) * a.lda + ub, *dl = a.act[l & 1][1] + ((int64_t)blockIdx.x * RT + rl) * a.lda + ub;
+          if ((HID == 2 && l + 1 < nhid) || (HID == kByLayer && a.zpart == nullptr)) {
+            const int64_t at = ((HID == kByLayer ? r0 : (int64_t)blockIdx.x * RT) + rl) * a.lda + ub;
+            bf16_t *dh = a.act[l & 1][0] + at, *dl = a.act[l & 1][1] + at;
             const int ld = a.layer[l + 1].nk * 32;          // (the next layer's steps read whole groups of 32)
 #pragma unroll
             for (int i = 0; i < NU; ++i) {
@@ -262,7 +269,7 @@ __global__ __launch_bounds__(512) void k_eval_net(const EvalArgs a) {
               }
             }
             // added up over the four wavefronts of the same rows, one after the other
-            if (u0 == 0) {
+            if (u0 == u1) {
               for (int i = t; i < RT * 32; i += 512) logit_s[i] = 0.f;
               lds_sync();
             }
@@ -286,7 +293,10 @@ __global__ __launch_bounds__(512) void k_eval_net(const EvalArgs a) {
         }
       }
     }
-    if (t < RT && r0 + t < a.rows) {
+    if constexpr (HID == kByLayer) {
+      if (a.zpart != nullptr)
+        for (int i = t; i < RT * 32; i += 512) a.zpart[((int64_t)blockIdx.y * a.row_pad + r0) * 32 + i] = logit_s[(i & ~31) + ((i ^ (i >> 5)) & 31)];
+    } else if (t < RT && r0 + t < a.rows) {
       const int64_t r = r0 + t;
       const int label = static_cast<const int32_t *>(s.y)[r];
       const float *bl = s.theta + a.layer[a.L - 1].offb;
@@ -304,6 +314,27 @@ __global__ __launch_bounds__(512) void k_eval_net(const EvalArgs a) {
     }
     // (the next write of the logits is a barrier away)
   }
+}
+
+// A row's loss and hit from the parts of its logits, added up in order: 32 lanes a row, one a class.
+__global__ __launch_bounds__(kBlock) void k_eval_rows(const EvalArgs a, int parts) {
+  const int c = threadIdx.x & 31, half = threadIdx.x & 32;      // (two rows a wavefront)
+  const int64_t r = (int64_t)blockIdx.x * (kBlock / 32) + (threadIdx.x >> 5);
+  if (r >= a.rows) return;                                      // (whole rows of lanes)
+  const bool live = c < a.C;
+  float z = 0.f;
+  for (int i = 0; i < parts; ++i) z += a.zpart[((int64_t)i * a.row_pad + r) * 32 + c];
+  if (live) z += a.s.theta[a.layer[1].offb + c];
+  float zmax = live ? z : -INFINITY;
+#pragma unroll
+  for (int o = 16; o > 0; o >>= 1) zmax = fmaxf(zmax, __shfl_xor(zmax, o, 32));
+  const uint32_t at = (uint32_t)(__ballot(live && z == zmax) >> half);
+  const int arg = at ? __ffs(at) - 1 : 0, label = static_cast<const int32_t *>(a.s.y)[r];
+  float den = live ? expf(z - zmax) : 0.f;
+#pragma unroll
+  for (int o = 16; o > 0; o >>= 1) den += __shfl_xor(den, o, 32);
+  const float zl = __shfl(z, label & 31, 32);
+  if (c == 0) a.rowval[r] = make_float2(zmax + logf(den) - (label >= 0 && label < a.C ? zl : 0.f), arg == label ? 1.f : 0.f);
 }
 
 // acc[m] = (mean loss, mean accuracy) of worker m's rows, added up in a fixed order.  One block per worker.
@@ -327,58 +358,88 @@ using EvalKernel = void (*)(const EvalArgs);
 constexpr int kEvalGroups = 256;        // workgroups of a launch (one per CU) at most
 constexpr int eval_lds(int NR, int NU) { return 2 * (64 * NR + 128 * NU) * 128 + 64 * NR * 128; }
 template <int NU, int HID> EvalKernel eval_kernel_of(int NR) { return NR == 4 ? k_eval_net<4, NU, HID> : NR == 2 ? k_eval_net<2, NU, HID> : k_eval_net<1, NU, HID>; }
-EvalKernel eval_kernel(int NR, int NU, int L) {
-  if (L == 1) return eval_kernel_of<1, 0>(NR);             // (at most 32 classes)
-  if (L == 2) return NU == 2 ? eval_kernel_of<2, 1>(NR) : eval_kernel_of<1, 1>(NR);
-  if (NU == 2) return NR == 2 ? k_eval_net<2, 2, 2> : k_eval_net<1, 2, 2>;      // (256 x 256 would spill registers)
-  return eval_kernel_of<1, 2>(NR);
+struct EvalPlan {
+  int nr, nu;                // rows (64 nr) and units (128 nu) of a tile
+  bool by_layer;             // a launch per hidden layer
+};
+EvalKernel eval_kernel(const EvalPlan &e, int L) {
+  if (e.by_layer) {
+    if (e.nu == 2) return e.nr == 2 ? k_eval_net<2, 2, kByLayer> : k_eval_net<1, 2, kByLayer>;
+    return eval_kernel_of<1, kByLayer>(e.nr);
+  }
+  if (L == 1) return eval_kernel_of<1, 0>(e.nr);             // (at most 32 classes)
+  if (L == 2) return e.nu == 2 ? eval_kernel_of<2, 1>(e.nr) : eval_kernel_of<1, 1>(e.nr);
+  if (e.nu == 2) return e.nr == 2 ? k_eval_net<2, 2, 2> : k_eval_net<1, 2, 2>;
+  return eval_kernel_of<1, 2>(e.nr);
 }
 
-// Rows (64 NR) and units (128 NU) of a tile.  In cycles of a step a wavefront pair issues 2 x 3 x 2 x 32 per 32 x 32 block; 256 units
-// x 64 rows and 128 units x any rows wait for their operands instead (8 KB per 64 rows and 128 units at some 40 bytes per clock).  The
-// choice minimises rounds of tiles over the CUs times the time of a tile.
-void eval_tile(const MlpPlan &P, int *nr, int *nu) {
-  int64_t best = INT64_MAX;
+int64_t eval_row_tiles(const MlpPlan &P, int nr) { return (P.total_rows + 64 * nr - 1) / (64 * nr); }
+int eval_unit_tiles(const MlpPlan &P, int l, int nu) { return (int)((P.d[l] + 128 * nu - 1) / (128 * nu)); }
+
+// In cycles of a step a wavefront pair issues 2 x 3 x 2 x 32 per 32 x 32 block; 256 units
+// x 64 rows and 128 units x any rows wait for their operands instead (8 KB per 64 rows and 128 units at some 40 bytes per clock).
+int64_t eval_step(int r, int u) { return max(384 * u * r, 8192 * (u + 1 + r) / 40 + 200); }
+// One tile of 128 u units of layer l.
+int64_t eval_tile(const MlpPlan &P, int l, int r, int u) { return (P.d[l - 1] + 31) / 32 * eval_step(r, u) + 2500; }
+// Bytes of layer l's input, read once for every tile of units, over the chip's rate.
+int64_t eval_reads(const MlpPlan &P, int l, int u) { return P.total_rows * eval_unit_tiles(P, l, u) * P.d[l - 1] * 4 / 5000; }
+
+// One launch takes a row through all layers; the choice of the tile minimises rounds of tiles over the CUs times the time of a tile.  But few
+// rows leave CUs idle and pass every tile of units one after the other: there a launch per layer (some 6000 cycles each) puts the tiles
+// of units side by side.  Measured, us in one launch / by layers (and the chunks of minibatches that both replaced): 3072-1024-1024-10: 100 rows:
+// 470 / 127 (330), 6000: 470 / 195, 20000: 855 / 618; 784-512-10: 64: 64 / 37 (101), 16000: 72 / 71, 40000: 130 / 160; 1024-1024-32: 100: 134 / 43
+// (70); 100-1000-10: 20000: 57 / 71.
+EvalPlan eval_plan(const MlpPlan &P) {
+  const int hidden = P.L > 1 ? P.L - 1 : 1;
+  EvalPlan one{1, 1, false}, layers{1, 1, true};
+  int64_t best = INT64_MAX, best_layers = INT64_MAX;
   for (int u = 1; u <= (P.L > 1 ? 2 : 1); ++u)
-    for (int r = 1; r <= (P.L > 2 && u == 2 ? 2 : 4); r *= 2) {
-      const int64_t tiles = (P.total_rows + 64 * r - 1) / (64 * r), rounds = (tiles + kEvalGroups - 1) / kEvalGroups;
-      int64_t per = 2000;      // end of a tile
-      for (int l = 1; l <= (P.L > 1 ? P.L - 1 : 1); ++l) {
-        const int64_t step = max(384 * u * r, 8192 * (u + 1 + r) / 40 + 200), ut = (P.d[l] + 128 * u - 1) / (128 * u);
-        per += ut * ((P.d[l - 1] + 31) / 32 * step + 2500);
+    for (int r = 1; r <= 4; r *= 2) {
+      const int64_t tiles = eval_row_tiles(P, r);
+      int64_t per = 2000, cost = 6000 * hidden + P.total_rows * eval_unit_tiles(P, hidden, u) * 256 / 2000;      // (with the end of a tile; with the logits' parts)
+      for (int l = 1; l <= hidden; ++l) {
+        const int64_t ut = eval_unit_tiles(P, l, u), tile = eval_tile(P, l, r, u);
+        per += ut * tile;
+        cost += (tiles * ut + kEvalGroups - 1) / kEvalGroups * tile + eval_reads(P, l, u);
       }
-      if (rounds * per < best) { best = rounds * per; *nr = r; *nu = u; }
+      per *= (tiles + kEvalGroups - 1) / kEvalGroups;
+      const bool big = u == 2 && r == 4;      // (256 x 256 would spill registers except with one hidden layer)
+      if (per < best && !(big && P.L > 2)) { best = per; one = EvalPlan{r, u, false}; }
+      if (cost < best_layers && !big && tiles < kEvalGroups) { best_layers = cost; layers = EvalPlan{r, u, true}; }
     }
+  return P.L > 1 && best_layers < best + eval_reads(P, 1, one.nu) ? layers : one;
 }
-int64_t eval_groups(const MlpPlan &P, int nr) { return min((P.total_rows + 64 * nr - 1) / (64 * nr), (int64_t)kEvalGroups); }
+int64_t eval_groups(const MlpPlan &P, int nr) { return min(eval_row_tiles(P, nr), (int64_t)kEvalGroups); }
 int64_t eval_lda(const MlpPlan &P) {     // values per row of the activations that pass through memory (0: none do)
   int64_t w = 0;
   for (int l = 1; l <= P.L - 2; ++l) w = max(w, (int64_t)(P.d[l] + 31) / 32 * 32);
   return w;
 }
+int64_t eval_act_rows(const MlpPlan &P, const EvalPlan &e) { return (e.by_layer ? eval_row_tiles(P, e.nr) : eval_groups(P, e.nr)) * 64 * e.nr; }
+size_t eval_rowval_bytes(const MlpPlan &P) { return ((size_t)P.total_rows * sizeof(float2) + 255) / 256 * 256; }
+size_t eval_act_bytes(const MlpPlan &P, const EvalPlan &e) {
+  return (size_t)eval_act_rows(P, e) * eval_lda(P) * sizeof(bf16_t) * 2 * (P.L > 3 ? 2 : 1);      // (rows of 64 and groups of 32 values: a multiple of 256 bytes)
+}
 }  // namespace
 
 // Scratch of the evaluation, behind everything else in the workspace.
 size_t mlp_eval_bytes(const MlpPlan &P) {
-  int nr, nu;
-  eval_tile(P, &nr, &nu);
-  const size_t row = ((size_t)P.total_rows * sizeof(float2) + 255) / 256 * 256;
-  return row + (size_t)eval_groups(P, nr) * 64 * nr * eval_lda(P) * sizeof(bf16_t) * 2 * (P.L > 3 ? 2 : 1);
+  const EvalPlan e = eval_plan(P);
+  const size_t parts = e.by_layer ? (size_t)eval_unit_tiles(P, P.L - 1, e.nu) * eval_act_rows(P, e) * 32 * sizeof(float) : 0;
+  return eval_rowval_bytes(P) + eval_act_bytes(P, e) + parts;
 }
 
 int mlp_eval_init(Ctx *c) {
   const MlpPlan &P = *static_cast<MlpPlan *>(c->mlp);
-  int nr, nu;
-  eval_tile(P, &nr, &nu);
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(eval_kernel(nr, nu, P.L)), hipFuncAttributeMaxDynamicSharedMemorySize, eval_lds(nr, nu));
+  const EvalPlan p = eval_plan(P);
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(eval_kernel(p, P.L)), hipFuncAttributeMaxDynamicSharedMemorySize, eval_lds(p.nr, p.nu));
   if (e != hipSuccess) { set_error("hipFuncSetAttribute(LDS size) failed: %s", hipGetErrorString(e)); return CADA_EHIP; }
   return CADA_OK;
 }
 
 int mlp_eval(Ctx *c, double *out) {
   const MlpPlan &P = *static_cast<MlpPlan *>(c->mlp);
-  int nr, nu;
-  eval_tile(P, &nr, &nu);
+  const EvalPlan p = eval_plan(P);
   EvalArgs a;
   a.s = c->s;
   a.s.k = c->k;
@@ -391,11 +452,30 @@ int mlp_eval(Ctx *c, double *out) {
   }
   a.rowval = reinterpret_cast<float2 *>(P.eval);
   a.lda = eval_lda(P);
-  const int64_t groups = eval_groups(P, nr), n = groups * 64 * nr * a.lda;
-  bf16_t *act = reinterpret_cast<bf16_t *>(P.eval + ((size_t)P.total_rows * sizeof(float2) + 255) / 256 * 256);
+  a.zpart = nullptr;
+  a.row_pad = eval_act_rows(P, p);
+  const int64_t n = a.row_pad * a.lda;
+  bf16_t *act = reinterpret_cast<bf16_t *>(P.eval + eval_rowval_bytes(P));
   for (int i = 0; i < 4; ++i) a.act[i >> 1][i & 1] = act + (P.L > 3 ? i : (i & 1)) * n;
+  const EvalKernel kernel = eval_kernel(p, P.L);
+  const size_t lds = eval_lds(p.nr, p.nu);
   mlp_stage_weights(c);
-  hipLaunchKernelGGL(eval_kernel(nr, nu, P.L), dim3((unsigned)groups), dim3(512), eval_lds(nr, nu), c->stream, a);
+  if (p.by_layer) {
+    EvalArgs b = a;
+    b.L = 2;
+    for (int l = 1; l < P.L; ++l) {
+      const int ut = eval_unit_tiles(P, l, p.nu);
+      b.layer[0] = a.layer[l - 1]; b.layer[1] = a.layer[l];
+      if (l > 1) { b.Xh = a.act[l & 1][0]; b.Xl = a.act[l & 1][1]; b.ldx = a.lda; }
+      b.act[0][0] = a.act[(l - 1) & 1][0]; b.act[0][1] = a.act[(l - 1) & 1][1];
+      if (l == P.L - 1) b.zpart = reinterpret_cast<float *>(P.eval + eval_rowval_bytes(P) + eval_act_bytes(P, p));
+      const int64_t rows = min(eval_row_tiles(P, p.nr), (int64_t)max(1, kEvalGroups / ut));
+      hipLaunchKernelGGL(kernel, dim3((unsigned)rows, (unsigned)ut), dim3(512), lds, c->stream, b);
+    }
+    hipLaunchKernelGGL(k_eval_rows, dim3((unsigned)((P.total_rows + kBlock / 32 - 1) / (kBlock / 32))), dim3(kBlock), 0, c->stream, b, eval_unit_tiles(P, P.L - 1, p.nu));
+  } else {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)eval_groups(P, p.nr)), dim3(512), lds, c->stream, a);
+  }
   hipLaunchKernelGGL(k_eval_sums, dim3((unsigned)P.M), dim3(1024), 0, c->stream, a.s, a.rowval, c->eval_acc);
   eval_finish(c, out, 0);
   const hipError_t e = hipGetLastError();

@@ -79,3 +79,15 @@ def test_network_evaluation_at_tile_edges(dims, M, n):
     print(dims, got, loss, hits)
     assert abs(got[0] - loss) <= 2e-5 * abs(loss)
     assert abs(got[1] - hits) <= 2.0 / (M * n) + 1e-4      # rows whose two best classes differ by rounding
+
+
+# Few rows: a launch per hidden layer, a workgroup per tile of its units; every tile that this takes (64 to 256 rows, 128 or 256 units), with
+# activations passed on through memory from three layers on, and a last tile of rows and of units that is nearly empty.
+FEW_ROWS = [((300, 520, 10), 1, 1), ((300, 520, 32), 5, 13), ((300, 600, 10), 2, 2050), ((300, 520, 10), 1, 6100), ((301, 520, 10), 3, 2400), ((300, 601, 2), 2, 6050),
+            ((300, 513, 257, 5), 2, 50), ((301, 513, 257, 5), 1, 4100), ((200, 600, 300, 9), 1, 6100), ((200, 600, 300, 9), 1, 8200), ((200, 260, 140, 500, 9), 1, 130),
+            ((300, 400, 300, 500, 11), 1, 4100), ((64, 300, 40, 33, 257, 7), 2, 33)]
+
+
+@pytest.mark.parametrize("dims,M,n", FEW_ROWS, ids=lambda v: "-".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_network_evaluation_on_few_rows(dims, M, n):
+    test_network_evaluation_at_tile_edges(dims, M, n)
