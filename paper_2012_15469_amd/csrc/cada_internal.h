@@ -147,6 +147,9 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
   return (lane_f64(v, 0) + lane_f64(v, 16)) + (lane_f64(v, 32) + lane_f64(v, 48));
 }
 
+// (An asm block that sets m0 says so, as the compiler uses that register for LDS operations of its own; it warns that the register is reserved.)
+#pragma clang diagnostic ignored "-Winline-asm"
+
 // Workgroup barrier for data that is exchanged through LDS: it waits for this wavefront's LDS operations only, not, as
 // __syncthreads() does, for the acknowledgement of every global store issued before it (a microsecond each time).
 // Data that a thread loaded from memory and passes on through LDS is waited for where it is written to LDS.

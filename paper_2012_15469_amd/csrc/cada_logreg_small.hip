@@ -87,8 +87,8 @@ __device__ __forceinline__ float sigmoid_s(float a) { return 1.0f / (1.0f + expf
 template <int BYTES>
 __device__ __forceinline__ void lds_direct(const float *src, const float *dst) {
   const uint32_t off = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(const __attribute__((address_space(3))) float *)dst);
-  if constexpr (BYTES == 16) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(off), "v"(src) : "memory");
-  else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" :: "s"(off), "v"(src) : "memory");
+  if constexpr (BYTES == 16) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(off), "v"(src) : "memory", "m0");
+  else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" :: "s"(off), "v"(src) : "memory", "m0");
 }
 // every memory operation of this wavefront has completed, then the workgroup meets
 __device__ __forceinline__ void full_sync() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
