@@ -259,12 +259,14 @@ __global__ __launch_bounds__(R_NT) void k_rows(const RowsArgs a) {
       for (int q0 = 0; q0 < a.shares; q0 += 4) {
         v4s x[4], y[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {                  // (past the last share: reads as zero)
-          x[q] = load_far(part, (uint32_t)j * 4u, (uint32_t)((q0 + q) * 2 * ps) * 4u);
-          y[q] = load_far(part, (uint32_t)j * 4u, (uint32_t)(((q0 + q) * 2 + 1) * ps) * 4u);
+        for (int q = 0; q < 4; ++q) {                  // (past the last share: that one again, dropped)
+          const int at = min(q0 + q, a.shares - 1) * 2 * ps;
+          x[q] = load_far(part, (uint32_t)j * 4u, (uint32_t)at * 4u);
+          y[q] = load_far(part, (uint32_t)j * 4u, (uint32_t)(at + ps) * 4u);
         }
 #pragma unroll
-        for (int q = 0; q < 4; ++q) { gs += x[q]; is += y[q]; }
+        for (int q = 0; q < 4; ++q)
+          if (q0 + q < a.shares) { gs += x[q]; is += y[q]; }
       }
     } else {
       share_sums(j, gs, is);
