@@ -490,11 +490,12 @@ __device__ __forceinline__ void small_body(const SmallArgs &a, const uint32_t *s
   }
   // what a later launch, or reading the state out, adds up
   lds_sync();
-  if (tid < s.n_ring_part && (ONE || m == 0)) {
+  if (tid == 0 && (ONE || m == 0)) {
     float newest = red_q[0];
 #pragma unroll
     for (int i = 1; i < S_NW; ++i) newest += red_q[i];
-    at.ring_part[tid] = tid == 0 ? newest : 0.f;
+    at.ring_part[0] = newest;
+    for (int i = 1; i < at.n_ring_part; ++i) at.ring_part[i] = 0.f;
   }
 }
 
