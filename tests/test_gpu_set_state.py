@@ -9,7 +9,7 @@ import torch
 from cada_synth import configs, generators
 from oracle.cada_oracle import margins
 from oracle.driver import oracle_for
-from paper_2012_15469_amd.binding import Cada, CadaError, PATH_TWO_PASS, PATH_WHOLE_STEPS
+from paper_2012_15469_amd.binding import Cada, CadaError, PATH_SINGLE_PASS, PATH_TWO_PASS, PATH_WHOLE_STEPS
 
 from common import upload, to_dev, inject_oracle_state, library_state, rel_l2, MARGIN
 
@@ -21,6 +21,7 @@ CASES = [
     (configs.CFG2.scaled(K=70, N_m=300, D=20), 33, 1e-4, {"path": PATH_TWO_PASS}),       # two streaming passes, CADA1
     (configs.CFG2.scaled(name="cfg2_cada2", K=70, N_m=300, D=20, rule=configs.RULE_CADA2, c=0.05), 45, 1e-4, {}),
     (configs.CFG3.scaled(name="fused_cada2", layer_dims=(8192,), M=5, N_m=128, B=32, K=30, D=6, alpha=0.02, c=1e-4), 13, 1e-4, {}),
+    (configs.CFG3.scaled(name="single_pass_cada2", layer_dims=(8192,), M=5, N_m=128, B=32, K=30, D=6, alpha=0.02, c=1e-4), 13, 1e-4, {"path": PATH_SINGLE_PASS}),
     (configs.CFG4.scaled(name="mlp2_cada2", layer_dims=(150, 133, 10), M=5, N_m=300, B=70, K=40, D=8, c=20.0), 19, 2e-2, {}),
     (configs.CFG5.scaled(name="mlp3_cada1", layer_dims=(200, 136, 72, 7), M=4, N_m=300, B=130, K=30, D=8, c=2.0), 17, 2e-2, {}),
 ]
