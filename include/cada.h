@@ -267,12 +267,12 @@ int cada_eval(cada_ctx *ctx, double *out);
 #define CADA_EVAL_NOALLOC_MAX_M 256
 int cada_eval_noalloc(cada_ctx *ctx, double *out);
 
-/* Checkpoint / resume.  A checkpoint is the whole workspace (iterate, moments, stored
- * gradients, reference points, delays, ring, trace, ...) plus the host-side counters, as one
+/* Checkpoint / resume.  A checkpoint is the workspace's state (iterate, moments, stored
+ * gradients, reference points, delays, ring, trace, ...; not the scratch behind it) plus the host-side counters, as one
  * opaque block of cada_checkpoint_bytes(ctx) bytes of DEVICE memory owned by the caller.
  * cada_checkpoint_save enqueues the copy on the context's stream and then waits for it (this
  * call synchronises the stream).  cada_checkpoint_load validates the block against the
- * context (same configuration: shapes, rule, model, workspace size), restores the state and
+ * context (same configuration: shapes, rule, model, size of the state; `path` may differ), restores the state and
  * the step counter, and also waits for the stream; on a mismatch it returns CADA_EINVAL and
  * changes nothing.  A block saved by one context can be loaded into another context created
  * with an equal configuration (the data X, y are not part of it). */

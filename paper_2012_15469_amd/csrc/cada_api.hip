@@ -587,7 +587,7 @@ int cada_eval_noalloc(cada_ctx *ctx, double *out) {
   if (!ctx || !out) { set_error("ctx/out is NULL"); return CADA_EINVAL; }
   Ctx *c = &ctx->c;
   if (c->model != CADA_MODEL_LOGREG) {
-    set_error("cada_eval_noalloc serves the logistic model: the MLP evaluation stages a chunk's activations, far more than its fixed scratch array");
+    set_error("cada_eval_noalloc serves the logistic model: the MLP evaluation needs scratch for every row, far more than its fixed array");
     return CADA_EUNSUPPORTED;
   }
   return logreg_eval_noalloc(c, out);

@@ -1,6 +1,6 @@
 // Dual minibatch gradient, rule and (small states) server update of the logistic model for rows that one workgroup can
-// hold in its registers (p <= 8192): a step is ONE launch, or two where the state is too large for one workgroup's server
-// phase, and the rows cross the memory bus once.
+// hold in its registers (p <= 8192): a step is ONE launch, two where the state is too large for one workgroup's server
+// phase, three where the workers are too many for one workgroup's rule, and the rows cross the memory bus once.
 //
 // Workgroup (g, m) takes a share of worker m's minibatch rows.  The rows of a share are read into registers, many at a
 // time; z = x.theta and dz = x.d are summed over the lanes, turned into the residual and its difference (formulas as in
@@ -8,13 +8,13 @@
 //   p <= 1024: a wavefront holds whole rows (WC = 1), the eight wavefronts work on rows of their own and add their sums up
 //     through LDS at the end: no workgroup barrier per row;
 //   p <= 8192: a row lies across the eight wavefronts (WC = 8), which exchange their parts of z, dz through LDS, one barrier per
-//     batch of rows, with the next batch's loads in flight across it.
+//     batch of rows.  The next batch is asked for before a batch's products; in every other one the compiled loop waits for it as well.
 // Nothing waits for another workgroup: whoever finishes last continues.  The last workgroup of a worker adds the shares'
 // sums up in their order, forms the fresh gradient and the left-hand side; the last of those runs the rule for
-// all workers, and, where M p is small, the server update.  The partial sums, gradients and left-hand sides that are passed on
+// all workers (up to kRuleWorkers), and, where the state is small, the server update.  The partial sums, gradients and left-hand sides that are passed on
 // inside the launch are written and read at device scope (past the XCD's cache).
 //
-// Wider rows, up to 20480 columns: k_rows_wide and k_rows_sum below, two launches and the server's.
+// Wider rows, up to 20480 columns: k_rows_wide and k_rows_sum below, two launches, the rule's for more than a few workers, and the server's.
 //
 // Why: the path replaces four to five dependent launches (two passes over the rows, [left-hand side of the LAG rule],
 // rule, server), each about 5 us of fetching arguments, code and first operands for well under 1 us of work.
@@ -403,7 +403,8 @@ __global__ __launch_bounds__(R_NT) void k_rows(const RowsArgs a) {
 // kernel before: M = 37, B = 75, p = 20001, CADA1: 117 -> 79 us; p = 20000: 114 -> 77; M = 8, B = 256, p = 8196: 117 -> 39;
 // M = 100, B = 256, p = 20000 (2 GB of rows): 391 -> 387.  Rows without the non-temporal hint: 81, 79, 39, 433.
 // All workers' rows, one after the other, are cut into one share per workgroup (wide_split); a share that crosses from one worker to
-// the next starts new sums there (wide_slot), and k_rows_sum adds a worker's slots up, one block per 1024 columns.  RB rows are worked on together with the next RB in flight.
+// the next starts new sums there (wide_slot), and k_rows_sum adds a worker's slots up, one block per 1024 columns.  RB rows are worked on together, and the next RB asked for before;
+// the compiled loop waits for all loads once per two batches.
 // DL: theta - theta_ref lies in LDS (the registers of 512 threads hold four vectors of 20480 columns and the rows in flight, not
 // five).  SEG: shares may meet several workers (up to 14336 columns: the loop over them costs wider rows registers, 51 -> 59 us).
 // dynamic LDS: row offsets int64 [rows], labels [rows] (rounded up to four rows), with DL theta - theta_ref [CW][512] quads
