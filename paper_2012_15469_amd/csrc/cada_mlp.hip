@@ -32,8 +32,8 @@
 // orientation, (row, unit).  The weight-gradient contractions, which sum over the rows, read the
 // same chunks and transpose on the way from LDS into the registers (ds_read_b64_tr_b16).
 //
-// One kernel, k_mm5, serves all three contraction shapes (forward, weight gradient,
-// activation gradient).  For a 128 x 128 output tile of worker m it accumulates
+// k_mm5 serves the forward products and the activation gradients, k_dw the weight gradients.  For a 128 x 128
+// output tile of worker m they accumulate
 //     C1 = Ah Bh^T + Ah Bl^T + Al Bh^T          (evaluation at theta, split operands)
 //     C2 = Ad Bx^T + Ar Bd^T                    (difference to the reference evaluation)
 // from up to four A-side and four B-side bf16 tensors, all stored in chunks of 128 rows x 32
@@ -45,6 +45,7 @@
 // columns (the last layer).
 #include <cstdlib>
 #include <new>
+#include <type_traits>
 
 #include "cada_mlp.h"
 
@@ -52,16 +53,9 @@ namespace cada {
 
 enum { EPI_FWD_HIDDEN = 0, EPI_DW = 2, EPI_DA = 3, EPI_LOSS = 4 };
 
-// LDS: a ring of 8 KB slots (one chunk each); behind it a buffer per multiplying wavefront for the
-// way out: 32 rows x 64 floats for the weight gradients, 8 KB for the bf16 tensors of the forward
-// and activation-gradient variants.  The pitch of
-// 72 floats puts the two half-wavefronts of an accumulator store (rows 4 apart) into different
-// halves of the banks.
-constexpr int kDwPitch = 72;
+// k_mm5's LDS: a ring of 8 KB slots (one chunk each); behind it 8 KB per multiplying wavefront for the bf16 tensors on their way out.
 constexpr int kMm5Slots = 15;
-constexpr size_t mm5_lds_bytes(int epi) {
-  return (size_t)kMm5Slots * TILE * sizeof(bf16_t) + (epi == EPI_DW ? 4 * 32 * kDwPitch * sizeof(float) : 4 * 8192);
-}
+constexpr size_t kMm5Lds = (size_t)kMm5Slots * TILE * sizeof(bf16_t) + 4 * 8192;
 
 // Up to four tensors that share the row index of one side of the product.
 struct Side {
@@ -146,12 +140,6 @@ __device__ __forceinline__ u32x4 pack8(const bf16_t (&v)[8]) {
 // are free (NS more loads may go out).  The epilogues use no workgroup barrier, so both roles
 // execute the same number of them.  (With four wavefronts doing load, LDS write and multiply in
 // turn, the three phases of a step, each near 1000 cycles, ran one after the other.)
-//
-// Weight gradient (EPI_DW): the product sums over a worker's rows, and both operands are (row, unit)
-// tensors whose 128-row tiles hold the rows.  A tile step covers 32 rows; the operand of a side is the
-// 32 rows x 128 units block of them, which lies in four chunks (one per 32 units) as 2 KB of
-// consecutive memory each.  It is stored in its ring slot as [unit chunk][row][unit], and a fragment
-// (8 consecutive rows of one unit per lane) is read with two transposing LDS loads.
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 
 // Fragment of a transposed operand: 8 consecutive rows (k) of unit (lane % 32) from a [32 rows][32 units]
@@ -167,12 +155,15 @@ __device__ __forceinline__ bf16x8 tr_fragment(const bf16_t *blk, int lane_off) {
   return __builtin_bit_cast(bf16x8, v);
 }
 
+__device__ __forceinline__ void mm_load(const bf16_t *base, uint32_t byte_off, uint32_t lds) {      // 1 KB, 16 bytes per lane, to `lds` (uniform)
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(byte_off), "s"(base), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory", "m0");
+}
 template <int EPI, int NA, int NB, bool HAS_D>
 __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   bf16_t *lds = reinterpret_cast<bf16_t *>(smem_raw);
   constexpr int NS = NA + NB, NSLOT = kMm5Slots;
-  constexpr bool TR = EPI == EPI_DW;          // operands are (row, unit) tensors read across the rows
+  static_assert(EPI == EPI_FWD_HIDDEN || EPI == EPI_DA, "");
   constexpr bool PL = NB == 2;
   static_assert(NSLOT >= 2 * NS, "the ring must hold two tile steps");
   const DevState &s = g.s;
@@ -199,8 +190,7 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
     int goff[2];
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
-      if constexpr (TR) goff[c] = (lw << 12) + (c << 9) + lane * 8;    // kilobyte 2 w + c of the step's operand: half c of unit chunk w
-      else goff[c] = lds_piece((2 * lw + c) * 64 + lane) * 8;          // (the order is its own inverse)
+      goff[c] = lds_piece((2 * lw + c) * 64 + lane) * 8;          // (the order is its own inverse)
     }
     // issue cursor: tile ordinal, step in the tile, first chunk of the tile's rows in every tensor, ring slot
     int ord = 0, h = 0, slot = 0;
@@ -208,12 +198,11 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
     auto set_tile = [&](int o) __attribute__((always_inline)) {
       const int tix = t_first + o * nbx;
       const int bx = tix % gx, by = (tix / gx) % gy, bz = tix / (gx * gy);
-      // (TR: the worker's first row tile, chunk 4 by / 4 bx of its units; else row tile by / bx, first chunk)
 #pragma unroll
-      for (int sl = 0; sl < NA; ++sl) pa[sl] = g.A.ptr[sl] + (int64_t)bz * g.A.bstride[sl] + (((int64_t)by * (TR ? 4 : g.A.kt[sl])) << 12);
+      for (int sl = 0; sl < NA; ++sl) pa[sl] = g.A.ptr[sl] + (int64_t)bz * g.A.bstride[sl] + (((int64_t)by * g.A.kt[sl]) << 12);
       const int bzb = g.rep ? g.rep[bz] : bz;
 #pragma unroll
-      for (int sl = 0; sl < NB; ++sl) pb[sl] = g.B.ptr[sl] + (int64_t)bzb * g.B.bstride[sl] + (((int64_t)bx * (TR ? 4 : g.B.kt[sl])) << 12);
+      for (int sl = 0; sl < NB; ++sl) pb[sl] = g.B.ptr[sl] + (int64_t)bzb * g.B.bstride[sl] + (((int64_t)bx * g.B.kt[sl]) << 12);
     };
     // next tile step; past the last one the cursor stays (those loads re-read the last chunk into slots nobody reads)
     auto next_step = [&]() __attribute__((always_inline)) {
@@ -222,12 +211,7 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
     };
     auto load = [&](int sl) __attribute__((always_inline)) {
       const bf16_t *src = sl < NA ? pa[sl < NA ? sl : 0] : pb[sl < NA ? 0 : sl - NA];
-      if constexpr (TR) {      // rows 32 h .. 32 h + 31 of the worker: row tile h / 4, 32 rows of 32 units from row 32 (h % 4) on
-        const int64_t kt = sl < NA ? g.A.kt[sl < NA ? sl : 0] : g.B.kt[sl < NA ? 0 : sl - NA];
-        src += (((int64_t)(h >> 2) * kt) << 12) + ((h & 3) << 10);
-      } else {
-        src += (int64_t)h << 12;
-      }
+      src += (int64_t)h << 12;
       bf16_t *dst = lds + ((size_t)slot << 12) + (2 * lw << 9);
 #pragma unroll
       for (int c = 0; c < 2; ++c)
@@ -259,8 +243,6 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
 
   // fragment of this lane inside a 32-row band: row lane % 32, piece lane / 32 (+ 2 in the second half step)
   const int fro = lds_piece((lane & 31) * 4 + (lane >> 5)) * 8;
-  // transposed operands: this lane's source address inside a [32 rows][32 units] block (see tr_fragment)
-  const int fro_tr = (8 * (lane >> 5) + ((lane & 15) >> 2)) * 32 + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
   int sb = 0;                                  // ring slot of the current step's first tensor
   for (int ord = 0; ord < nt; ++ord) {
   const int tix = t_first + ord * nbx;
@@ -283,10 +265,8 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
 #pragma unroll
     for (int ks = 0; ks < BK; ks += 16) {
       bf16x8 ah[2], al[2], ad[2], ar[2], bh[2], bl[2], bx_[2], bd[2];
-      // (TR: unit block 2 wy + i of the step's [4][32 rows][32 units], rows ks .. ks + 15)
       auto frag = [&](const bf16_t *slot, int half, int blk) __attribute__((always_inline)) -> bf16x8 {
-        if constexpr (TR) return tr_fragment(slot + (half * 2 + blk) * 1024 + ks * 32, fro_tr);
-        else return *reinterpret_cast<const bf16x8 *>(slot + (half * 64 + blk * 32) * BK + (fro ^ ks));
+        return *reinterpret_cast<const bf16x8 *>(slot + (half * 64 + blk * 32) * BK + (fro ^ ks));
       };
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
@@ -327,7 +307,7 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
   const int rbase = m0 + wy * 64 + 4 * (lane >> 5);
   const int cbase = n0 + wx * 64 + (lane & 31);
   const int64_t rp0 = (int64_t)wk * g.Bp;            // first padded row of this worker
-  if constexpr (EPI == EPI_FWD_HIDDEN || EPI == EPI_DA) {
+  {
     // Forward: bias, ReLU of both evaluations.  Activation gradient: ReLU masks of the layer
     // below, bias-gradient partial sums.  Both: the result split into hi/lo, its difference and
     // its reference value, each written as a (row, column) tensor.
@@ -447,151 +427,195 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
       mb.x = (uint32_t)bit_on; mb.y = (uint32_t)(bit_on >> 32); mb.z = (uint32_t)bit_ref; mb.w = (uint32_t)(bit_ref >> 32);
       *reinterpret_cast<u32x4 *>(mbits) = mb;
     }
-  } else {   // EPI_DW
-    // A lane's accumulators are one column and 16 rows of the tile: stored from there, an
-    // instruction moves 4 bytes per lane, and the 192 such instructions of a wavefront kept the
-    // CU's address unit busy for longer than the contraction took.  Each wavefront instead passes
-    // its 64 x 64 part through an LDS buffer of its own, one 32-row band at a time, and writes it
-    // out row by row, 16 bytes per lane, 256 bytes per row.  (LDS operations of one wavefront are
-    // carried out in order, so the buffer needs no barrier.)
-    constexpr int SP = kDwPitch;
-    float *st = reinterpret_cast<float *>(smem_raw + (size_t)NSLOT * TILE * sizeof(bf16_t)) + w * (32 * SP);
-    const bool g16 = s.gbuf16 != nullptr;
-    float *gf = g16 ? nullptr : fresh_grad(s, wk) + g.offW;
-    bf16_t *gf16 = g16 ? fresh_grad16(s, wk) + g.offW : nullptr;
-    const bool cada1 = !PL && s.rule == CADA_RULE_CADA1;
-    bf16_t *ivf = cada1 ? fresh_innov(s, wk) + g.offW : nullptr;
-    const bf16_t *ivs = cada1 ? stored_innov(s, wk) + g.offW : nullptr;
-    // row-wise pass: this lane has columns c4 .. c4+3 of the band's rows rr + 4 it, it = 0..7
-    const int c4 = (lane & 15) * 4, rr = lane >> 4;
-    const int colg = n0 + wx * 64 + c4;
-    // A lane whose four columns exist takes 16 bytes at a time (8 bytes of bf16), whatever the rows' alignment; the lane at the
-    // matrix's edge that has fewer (`some`) goes element by element, but asks for all its stored values first, too.  (Whole
-    // wavefronts used to go element by element where their 64 columns overhang the matrix, one dependent read after the
-    // other with CADA1: 784-500-10, M = 30, B = 12: 148 -> 109 us per step.  Blocks of 32 x 128 with a wavefront per 32 columns were
-    // 2-6 % faster for odd widths and 5 % slower where a tile has more than four steps.)
-    const bool full = colg + 4 <= g.N, some = colg < g.N && !full;
-    const int colv = min(colg, g.N - 4);                     // (more than 32 columns)
-    auto put_band = [&](const f32x16 (&acc)[2]) __attribute__((always_inline)) {
+  }
+  }   // tiles
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");     // the movers' last barrier
+}
+
+// Weight gradient of a layer and its innovation: C1 = A^T G with split operands, C2 = A^T dG [+ dA^T Gref], summed over a worker's rows.  Both
+// operands are (row, unit) tensors; a step is 16 rows, 16 rows x 128 units of each of the NS tensors.
+//
+// What bounds it: a 128 x 128 tile has few steps (16 for B = 256) and then 64 KB of gradient to write (CADA1: 32 KB of innovation read and
+// written, too), so products and the way out have to overlap.  Two workgroups of four wavefronts share a CU, half of the register file and 80 KB of
+// LDS each: while one writes a tile out, the other has the matrix cores.  Every wavefront moves its part of the operands (LDS-direct), multiplies
+// 64 x 64 of the tile and writes them out; no wavefront is there for the moving alone, whose registers would be the second workgroup's.
+// With four moving and four multiplying wavefronts on a CU products and stores took turns: first layer of 3072-1024-1024-10, 16 workers of 256
+// rows, CADA1: 190 us, now 168; second layer 79, now 71; 784-512-10, 64 workers of 128 rows, CADA2: 51.5, now 44.5.  What is left: a step takes 880 cycles of
+// a CU without the way out (products alone 512 by count and 560 measured, loads alone 594), 1010 with it, at the 1.8 GHz that the products' power leaves.
+//
+// LDS: a ring of 20 slots of 4 KB, one tensor of a step each ([4 chunks of 32 units][16 rows][32 units]: 1 KB of consecutive memory per chunk, moved by
+// the wavefront of that number).  A step's fragments are read during the step before, each right after its register's last use, so a step's
+// slots are free at its own barrier, and the loads that refill them go out between its products.  A wavefront's loads land in the order of
+// issue: the barrier of a step waits until only what was asked for after the next step's operands is outstanding.  At a tile's end the last step's
+// freed slots (four of them) are the buffers of the way out, 4 KB per wavefront, and their refill waits until the next tile starts; everything
+// else that is in flight then has to land before the first store, so that the next tile's first steps need not wait for the stores behind.
+// Asked for in bursts after the barrier, the loads stalled the wavefronts: 1560 cycles per 1024 of products against 1142.
+//
+// The unit of A is the MFMA's column index: a lane's accumulators are one row of the matrix and groups of four consecutive
+// columns, which go through LDS 16 bytes (bf16: 8) at a time and leave as whole rows of 128 bytes.  (Plain stores: with the non-temporal hint, which
+// paid for rows of 256 bytes, 201 and 62 us where plain ones took 180 and 44.)
+typedef uint32_t u32x4h __attribute__((ext_vector_type(4), aligned(2)));   // eight bf16 values at any address
+constexpr int kDwRows = 16;                                    // rows per step
+constexpr int kDwSlots = 20;
+constexpr size_t kDwLds = kDwSlots * 4096;
+
+template <int NA, int NB, bool HAS_D, bool CADA1>
+__global__ __launch_bounds__(kBlock, 2) void k_dw(const Mm5Args g) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  constexpr int NS = NA + NB, NSLOT = kDwSlots, AHEAD = NSLOT / NS, R0 = NSLOT % NS;
+  constexpr int LANDED = (NSLOT - 4) / NS - 1;      // steps of a tile that need not wait for their loads: those had landed before the last tile's way out
+  constexpr bool PL = NB == 2;
+  static_assert(NS >= 4 && NSLOT >= 2 * NS + 4, "");
+  const DevState &s = g.s;
+  const int lane0 = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), wy = w >> 1, wx = w & 1;
+  // tiles of this workgroup: as in k_mm5
+  const int gx = (g.N + BN - 1) / BN, gy = (g.M + BM - 1) / BM;
+  const int total = gx * gy * g.workers, per = (total + 7) / 8, nbx = gridDim.x >> 3;
+  const int t_first = (blockIdx.x & 7) * per + (blockIdx.x >> 3), t_end = min(((int)(blockIdx.x & 7) + 1) * per, total);
+  if (t_first >= t_end) return;
+  const int nt = (t_end - t_first + nbx - 1) / nbx, nk = (g.K + kDwRows - 1) / kDwRows, nsteps = nt * nk;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem_raw;
+
+  // issue cursor: step, tile, step in the tile, slot; this wavefront's chunk of every operand of the tile, and the step's place in it
+  int i_step = 0, i_tix = t_first, i_h = 0, i_slot = 0;
+  const bf16_t *src[NS];
+  int64_t at_a = 0, at_b = 0;
+  auto set_tile = [&]() __attribute__((always_inline)) {
+    const int bx = i_tix % gx, by = (i_tix / gx) % gy, bz = i_tix / (gx * gy);
+#pragma unroll
+    for (int q = 0; q < NA; ++q) src[q] = g.A.ptr[q] + (int64_t)bz * g.A.bstride[q] + ((int64_t)(4 * by + w) << 12);
+#pragma unroll
+    for (int q = 0; q < NB; ++q) src[NA + q] = g.B.ptr[q] + (int64_t)bz * g.B.bstride[q] + ((int64_t)(4 * bx + w) << 12);
+  };
+  auto next_step = [&]() __attribute__((always_inline)) {
+    ++i_step;
+    if (++i_h == nk) { i_h = 0; i_tix += nbx; if (i_tix < t_end) set_tile(); }
+    at_a = (((int64_t)(i_h >> 3) * g.A.kt[0]) << 12) + ((i_h & 7) << 9);       // rows 16 i_h .. of the worker: eighth i_h % 8 of row tile i_h / 8
+    at_b = (((int64_t)(i_h >> 3) * g.B.kt[0]) << 12) + ((i_h & 7) << 9);
+  };
+  auto load = [&](int q) __attribute__((always_inline)) {        // tensor q of the cursor's step into the next slot (nothing past the last step)
+    if (i_step < nsteps) {
+      mm_load(src[q] + (q < NA ? at_a : at_b), lane0 * 16, lds0 + i_slot * 4096 + w * 1024);
+      i_slot = i_slot + 1 == NSLOT ? 0 : i_slot + 1;
+    }
+  };
+  auto more = [&](int i) __attribute__((always_inline)) {        // tensor i of the NS that take the slots of a step whose fragments have been read
+    if (i >= NS) return;
+    if ((R0 + i) % NS == 0) next_step();
+    load((R0 + i) % NS);
+  };
+  set_tile();
+#pragma unroll 1
+  for (int p = 0; p < AHEAD; ++p) {
+    if (p > 0) next_step();
+#pragma unroll
+    for (int q = 0; q < NS; ++q) load(q);
+  }
+  if constexpr (R0 > 0) next_step();
+#pragma unroll
+  for (int q = 0; q < R0; ++q) load(q);
+  // (the first step; all of them where there are few)
+  if (nsteps >= AHEAD) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((AHEAD - 1) * NS) : "memory");
+  else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+
+  // this lane's source address inside a [16 rows][32 units] block (see tr_fragment)
+  const int fro = (8 * (lane0 >> 5) + ((lane0 & 15) >> 2)) * 32 + 16 * ((lane0 >> 4) & 1) + 4 * (lane0 & 3);
+  int step = 0, sb = 0, landed = 0;             // sb: slot of the first tensor of the step whose fragments are read next
+  for (int tix = t_first; tix < t_end; tix += nbx) {
+    const int bx = tix % gx, by = (tix / gx) % gy, wk = tix / (gx * gy);     // wk: worker
+    f32x16 acc1[2][2], acc2[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) st[(8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * SP + j * 32 + (lane & 31)] = acc[j][r];
-      asm volatile("" ::: "memory");
-    };
-    // CADA1: the stored innovations of the part, all loads issued before anything waits for one
-    // (rows clamped into the matrix so that no load sits under a branch).  Gradients and innovations
-    // are written once and read once per step, megabytes apart in time: non-temporal accesses.
-    u32x2u old[2][8];        // four bf16 values each
-    if (cada1) {
+        for (int r = 0; r < 16; ++r) { acc1[i][j][r] = 0.f; acc2[i][j][r] = 0.f; }
+
+    auto slot_of = [&](int q) __attribute__((always_inline)) { const int p = sb + q; return smem_raw + (p >= NSLOT ? p - NSLOT : p) * 4096; };
+    auto frag = [&](int q, int blk) __attribute__((always_inline)) { return tr_fragment(reinterpret_cast<const bf16_t *>(slot_of(q) + blk * 1024), fro); };
+    bf16x8 ah[2], al[2], ad[2], bh[2], bl[2], bg[2], bd[2];
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (step > 0) {                              // the loads whose slots the last tile's way out lay over
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int it = 0; it < 8; ++it) {
-          const bf16_t *row = ivs + (int64_t)min(m0 + wy * 64 + i * 32 + rr + 4 * it, g.M - 1) * g.N;
-          old[i][it] = *reinterpret_cast<const u32x2u *>(row + colv);
-        }
-      if (n0 + wx * 64 + 64 > g.N && (g.N & 3) != 0) {       // (uniform: no branch among the loads of the other tiles)
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int it = 0; it < 8; ++it) {
-            const bf16_t *row = ivs + (int64_t)min(m0 + wy * 64 + i * 32 + rr + 4 * it, g.M - 1) * g.N;
-            uint32_t e[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) e[q] = row[min(colg + q, g.N - 1)];
-            if (some) { old[i][it].x = e[0] | (e[1] << 16); old[i][it].y = e[2] | (e[3] << 16); }
-          }
-      }
-    }
-    auto old_of = [&](int i, int it, int e) __attribute__((always_inline)) {      // value e of old[i][it]
-      const uint32_t o = e < 2 ? old[i][it].x : old[i][it].y;
-      return __uint_as_float((e & 1) ? o & 0xffff0000u : o << 16);
-    };
-    // The innovation first, the gradient last: the innovation's part waits for the loads of the stored
-    // innovations (and a wait for a load also waits for every store issued before it), whereas nothing
-    // in this tile waits behind the gradient's stores: they drain while the next tile's products run.
-    float sq = 0.f;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int rowb = m0 + wy * 64 + i * 32 + rr;
-      if constexpr (PL) break;
-      if (!cada1) {       // nothing to store or to subtract: the squared norm needs no particular order of the elements
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int row = m0 + wy * 64 + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), col = n0 + wx * 64 + j * 32 + (lane & 31);
-            const float v = (row < g.M && col < g.N) ? acc2[i][j][r] : 0.f;
-            sq = fmaf(v, v, sq);
-          }
-        continue;
-      }
-      put_band(acc2[i]);
-      if (full) {
-#pragma unroll
-        for (int it = 0; it < 8; ++it) {
-          f32x4u v = *reinterpret_cast<const f32x4u *>(st + (rr + 4 * it) * SP + c4);
-          if (rowb + 4 * it < g.M) {
-            u32x2u nw;
-            nw.x = f2bf_pk(v.x, v.y); nw.y = f2bf_pk(v.z, v.w);
-            *reinterpret_cast<u32x2u *>(ivf + (int64_t)(rowb + 4 * it) * g.N + colg) = nw;
-            const u32x2u o = old[i][it];
-            v.x -= bf2f((bf16_t)o.x); v.y -= bf2f((bf16_t)(o.x >> 16)); v.z -= bf2f((bf16_t)o.y); v.w -= bf2f((bf16_t)(o.y >> 16));
-            sq = fmaf(v.x, v.x, sq); sq = fmaf(v.y, v.y, sq); sq = fmaf(v.z, v.z, sq); sq = fmaf(v.w, v.w, sq);
-          }
-        }
-      } else if (some) {
-#pragma unroll
-        for (int it = 0; it < 8; ++it)
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (rowb + 4 * it < g.M && colg + e < g.N) {
-              const float iv = st[(rr + 4 * it) * SP + c4 + e];
-              ivf[(int64_t)(rowb + 4 * it) * g.N + colg + e] = f2bf(iv);
-              const float d = iv - old_of(i, it, e);
-              sq = fmaf(d, d, sq);
-            }
-      }
-      asm volatile("" ::: "memory");
+      for (int i = NS - 4; i < NS; ++i) more(i);
     }
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      const int rowb = m0 + wy * 64 + i * 32 + rr;
-      put_band(acc1[i]);
-      if (full) {
-#pragma unroll
-        for (int it = 0; it < 8; ++it) {
-          const f32x4u v = *reinterpret_cast<const f32x4u *>(st + (rr + 4 * it) * SP + c4);
-          if (rowb + 4 * it < g.M) {
-            if (g16) {
-              u32x2u nw;
-              nw.x = f2bf_pk(v.x, v.y); nw.y = f2bf_pk(v.z, v.w);
-              __builtin_nontemporal_store(nw, reinterpret_cast<u32x2u *>(gf16 + (int64_t)(rowb + 4 * it) * g.N + colg));
-            } else {
-              __builtin_nontemporal_store(v, reinterpret_cast<f32x4u *>(gf + (int64_t)(rowb + 4 * it) * g.N + colg));
-            }
-          }
-        }
-      } else if (some) {
-#pragma unroll
-        for (int it = 0; it < 8; ++it)
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (rowb + 4 * it < g.M && colg + e < g.N) {
-              const int64_t o = (int64_t)(rowb + 4 * it) * g.N + colg + e;
-              const float v = st[(rr + 4 * it) * SP + c4 + e];
-              if (g16) gf16[o] = f2bf(v); else gf[o] = v;
-            }
-      }
-      asm volatile("" ::: "memory");
+      al[i] = frag(1, 2 * wy + i); bh[i] = frag(NA, 2 * wx + i); ah[i] = frag(0, 2 * wy + i); bl[i] = frag(NA + 1, 2 * wx + i);
+      if constexpr (HAS_D) { ad[i] = frag(2, 2 * wy + i); bg[i] = frag(NA + 2, 2 * wx + i); }
+      if constexpr (!PL) bd[i] = frag(NS - 1, 2 * wx + i);
     }
+    const int rw = by * BM + wy * 64, cw = bx * BN + wx * 64;     // first row and column of this wavefront's part
+    int out_slot = 0;
+    u32x4 old[2][4] = {};
+    // Step by step each fragment is read for the next step right after its last use, and a load goes out between products.
+    for (int h = 0; h < nk; ++h, ++step) {
+      const bool last = h + 1 == nk;
+      if (last) {
+        out_slot = sb + (NS - 4) + w;
+        if constexpr (CADA1) {
+          // the stored innovations, 16 bytes of row lane / 8 + 8 it from column 8 (lane % 8) on (clamped into the matrix: no load under a branch)
+          int ln = lane0;
+          asm volatile("" : "+v"(ln));             // (addresses computed here, not kept in registers through the products)
+          const int r0 = min(rw, g.M - 1), c0 = min(cw, g.N - 8);
+          const bf16_t *ivs = stored_innov(s, wk) + g.offW + (int64_t)r0 * g.N + c0;
+          const uint32_t coff = min(cw + 8 * (ln & 7), g.N - 8) - c0;
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int it = 0; it < 4; ++it)
+              old[i][it] = *reinterpret_cast<const u32x4h *>(ivs + (uint32_t)min(32 * i + 8 * it + (ln >> 3), g.M - 1 - r0) * (uint32_t)g.N + coff);
+        }
+      }
+#define MM(a, b, c) c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, a, c, 0, 0, 0)
+#define KEEP() __builtin_amdgcn_sched_barrier(0)
+      auto ask = [&](int i) __attribute__((always_inline)) { if (i < NS - 4 || !last) more(i); };
+      sb = sb + NS >= NSLOT ? sb + NS - NSLOT : sb + NS;
+      KEEP();
+      MM(al[0], bh[0], acc1[0][0]); MM(al[0], bh[1], acc1[0][1]); MM(al[1], bh[0], acc1[1][0]); MM(al[1], bh[1], acc1[1][1]);
+      KEEP();
+      // this wavefront's part of the next step has landed, and every wavefront has this step's fragments in registers
+      const int later = nsteps - step - 2;
+      if (last || landed > 0) { --landed; asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+      else if (later * NS >= NSLOT - 2 * NS) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(NSLOT - 2 * NS) : "memory");
+      else if (later == 1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(NS) : "memory");
+      else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      __builtin_amdgcn_s_setprio(1);
+      al[0] = frag(1, 2 * wy); al[1] = frag(1, 2 * wy + 1); KEEP();
+      MM(ah[0], bl[0], acc1[0][0]); MM(ah[1], bl[0], acc1[1][0]); KEEP(); bl[0] = frag(NA + 1, 2 * wx); ask(0); KEEP();
+      MM(ah[0], bl[1], acc1[0][1]); MM(ah[1], bl[1], acc1[1][1]); KEEP(); bl[1] = frag(NA + 1, 2 * wx + 1); ask(1); KEEP();
+      MM(ah[0], bh[0], acc1[0][0]); MM(ah[1], bh[0], acc1[1][0]); KEEP(); bh[0] = frag(NA, 2 * wx); ask(2); KEEP();
+      MM(ah[0], bh[1], acc1[0][1]); MM(ah[1], bh[1], acc1[1][1]); KEEP(); bh[1] = frag(NA, 2 * wx + 1); ask(3); KEEP();
+      if constexpr (HAS_D) {
+        MM(ad[0], bg[0], acc2[0][0]); MM(ad[0], bg[1], acc2[0][1]); KEEP(); ad[0] = frag(2, 2 * wy); ask(4); KEEP();
+        MM(ad[1], bg[0], acc2[1][0]); MM(ad[1], bg[1], acc2[1][1]); KEEP(); ad[1] = frag(2, 2 * wy + 1); bg[0] = frag(NA + 2, 2 * wx); bg[1] = frag(NA + 2, 2 * wx + 1); ask(5); KEEP();
+      }
+      if constexpr (!PL) {
+        MM(ah[0], bd[0], acc2[0][0]); MM(ah[0], bd[1], acc2[0][1]); KEEP(); ah[0] = frag(0, 2 * wy); ask(HAS_D ? 6 : 4); KEEP();
+        MM(ah[1], bd[0], acc2[1][0]); MM(ah[1], bd[1], acc2[1][1]); KEEP(); ah[1] = frag(0, 2 * wy + 1); bd[0] = frag(NS - 1, 2 * wx); bd[1] = frag(NS - 1, 2 * wx + 1); KEEP();
+      } else {
+        ah[0] = frag(0, 2 * wy); ah[1] = frag(0, 2 * wy + 1); KEEP();
+      }
+      __builtin_amdgcn_s_setprio(0);
+#undef MM
+#undef KEEP
+    }
+    unsigned char *st = smem_raw + (out_slot >= NSLOT ? out_slot - NSLOT : out_slot) * 4096;
+
+    int lane = lane0;
+    asm volatile("" : "+v"(lane));
+    const int r32 = lane & 31, hf = lane >> 5;
+    // accumulator element (i, j, r): row rw + 32 i + lane % 32 of the matrix, column cw + 32 j + 8 (r / 4) + 4 (lane / 32) + r % 4
+    const bool g16 = s.gbuf16 != nullptr;
+    // On the way out a lane has 16 bytes of a row: floats 4 (lane % 8) .. of 32 columns, bf16 values 8 (lane % 8) .. of 64, of row lane / 8 + 8 it.
+    const int rl = lane >> 3;
+    const bool whole = rw + 64 <= g.M && cw + 64 <= g.N;        // (uniform) this wavefront's part lies in the matrix
     // The tiles of the first 128 units also form the layer's bias gradient and its innovation, from the sums that the
     // activation-gradient launch left per band of 64 rows: this wavefront's 64 columns, one per lane, and a partial sum of the left-hand
     // side of their own.  (A launch of its own cost 5 us.  One wavefront for 256 columns, with fewer partial sums: 784-500-10, B = 12:
     // 81.1 -> 82.8 us per step, 3072-1024-1024-10: 608 -> 615.)
-    if (g.nband > 0 && by == 0 && wy == 0 && n0 + wx * 64 < g.N) {
-      const int col = n0 + wx * 64 + lane;
+    if (g.nband > 0 && by == 0 && wy == 0 && cw < g.N) {
+      const int col = cw + lane;
       float dsum = 0.f;
       if (col < g.N) {
         const float *db = g.dbpart + (int64_t)wk * g.nband * g.N + col, *dd = g.ddbpart + (int64_t)wk * g.nband * g.N + col;
@@ -601,7 +625,7 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
           if constexpr (!PL) dsum += dd[(int64_t)i * g.N];
         }
         put_fresh_grad(s, wk, g.offb + col, gsum);
-        if (cada1) {
+        if (CADA1) {
           fresh_innov(s, wk)[g.offb + col] = f2bf(dsum);
           dsum -= bf2f(stored_innov(s, wk)[g.offb + col]);
         }
@@ -611,11 +635,126 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
         if (lane == 0) s.lhs_part[(int64_t)wk * s.n_lhs_part + g.lhs_slot_b + 2 * bx + wx] = totb;
       }
     }
-    const float tot = wave_sum(sq);           // one partial sum of the left-hand side per wavefront and tile
-    if (lane == 0) s.lhs_part[(int64_t)wk * s.n_lhs_part + g.lhs_slot0 + (by * gx + bx) * 4 + w] = tot;
-  }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    landed = LANDED;
+
+    // LDS positions: 16-byte piece p of row r at 128 r + 16 (p ^ r / 2 % 8) (rows 2 apart are one pass over the banks apart); the 8-byte halves of
+    // a bf16 piece change places in rows 16 to 31
+    auto pos16 = [&](int row, int piece) __attribute__((always_inline)) { return st + row * 128 + ((piece ^ ((row >> 1) & 7)) << 4); };
+    auto pos8 = [&](int j, int q) __attribute__((always_inline)) { return pos16(r32, 4 * j + q) + 8 * (hf ^ (r32 >> 4)); };
+    auto row16 = [&](int it, u32x4 v) __attribute__((always_inline)) { return it < 2 ? v : u32x4{v.z, v.w, v.x, v.y}; };
+    float sq = 0.f;
+    auto write_out = [&](auto whole_part) __attribute__((always_inline)) {
+      constexpr bool WHOLE = decltype(whole_part)::value;
+      const int rows = WHOLE ? 64 : g.M - rw, cols = WHOLE ? 64 : g.N - cw;       // of this wavefront's part (may be none)
+      const int64_t at = g.offW + (int64_t)rw * g.N + cw;
+      auto put_rows16 = [&](bf16_t *base, int i) __attribute__((always_inline)) {      // 32 rows of 64 bf16 values from LDS to memory
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+          const u32x4 v = row16(it, *reinterpret_cast<const u32x4 *>(pos16(8 * it + rl, lane & 7)));
+          const int row = 32 * i + 8 * it + rl, col = 8 * (lane & 7);
+          if (!WHOLE && row >= rows) continue;
+          bf16_t *q = base + (uint32_t)row * (uint32_t)g.N + col;
+          if (WHOLE || col + 8 <= cols) *reinterpret_cast<u32x4h *>(q) = v;
+          else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+              if (col + e < cols) q[e] = (bf16_t)(v[e >> 1] >> (16 * (e & 1)));
+          }
+        }
+      };
+      if constexpr (!PL) {
+        bf16_t *ivf = CADA1 ? fresh_innov(s, wk) + at : nullptr;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          if (CADA1) {
+#pragma unroll
+            for (int it = 0; it < 4; ++it) {
+              u32x4 o = old[i][it];
+              if constexpr (!WHOLE) {      // (a lane at the matrix's edge was moved back: its values lie that many places further up)
+                const int d = min(max(8 * (lane & 7) + 8 - cols, 0), 7);
+                uint64_t lo = (uint64_t)o.x | ((uint64_t)o.y << 32), hi = (uint64_t)o.z | ((uint64_t)o.w << 32);
+                if (d >= 4) { lo = hi; hi = 0; }
+                const int b = 16 * (d & 3);
+                if (b > 0) { lo = (lo >> b) | (hi << (64 - b)); hi >>= b; }
+                o = u32x4{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
+              }
+              *reinterpret_cast<u32x4 *>(pos16(8 * it + rl, lane & 7)) = row16(it, o);
+            }
+            asm volatile("" ::: "memory");
+          }
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              uint32_t o[2] = {0u, 0u}, nw[2];
+              if (CADA1) { const uint64_t x = *reinterpret_cast<const uint64_t *>(pos8(j, q)); o[0] = (uint32_t)x; o[1] = (uint32_t)(x >> 32); }
+#pragma unroll
+              for (int e = 0; e < 2; ++e) {
+                const float x = acc2[i][j][4 * q + 2 * e], y = acc2[i][j][4 * q + 2 * e + 1];
+                nw[e] = f2bf_pk(x, y);
+                const int row = 32 * i + r32, col = 32 * j + 8 * q + 4 * hf + 2 * e;
+                const float dx = WHOLE || (row < rows && col < cols) ? x - __uint_as_float(o[e] << 16) : 0.f;
+                const float dy = WHOLE || (row < rows && col + 1 < cols) ? y - __uint_as_float(o[e] & 0xffff0000u) : 0.f;
+                sq = fmaf(dx, dx, sq); sq = fmaf(dy, dy, sq);
+              }
+              if (CADA1) *reinterpret_cast<uint64_t *>(pos8(j, q)) = (uint64_t)nw[0] | ((uint64_t)nw[1] << 32);
+            }
+          if (CADA1) {
+            asm volatile("" ::: "memory");
+            put_rows16(ivf, i);
+            asm volatile("" ::: "memory");
+          }
+        }
+      }
+      if (g16) {
+        bf16_t *gf16 = fresh_grad16(s, wk) + at;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+              *reinterpret_cast<uint64_t *>(pos8(j, q)) = (uint64_t)f2bf_pk(acc1[i][j][4 * q], acc1[i][j][4 * q + 1]) |
+                                                          ((uint64_t)f2bf_pk(acc1[i][j][4 * q + 2], acc1[i][j][4 * q + 3]) << 32);
+          asm volatile("" ::: "memory");
+          put_rows16(gf16, i);
+          asm volatile("" ::: "memory");
+        }
+      } else {
+        float *gf = fresh_grad(s, wk) + at;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+              *reinterpret_cast<v4s *>(pos16(r32, 2 * q + hf)) = v4s{acc1[i][j][4 * q], acc1[i][j][4 * q + 1], acc1[i][j][4 * q + 2], acc1[i][j][4 * q + 3]};
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int it = 0; it < 4; ++it) {
+              const v4s v = *reinterpret_cast<const v4s *>(pos16(8 * it + rl, lane & 7));
+              const int row = 32 * i + 8 * it + rl, col = 32 * j + 4 * (lane & 7);
+              if (!WHOLE && row >= rows) continue;
+              float *q = gf + (uint32_t)row * (uint32_t)g.N + col;
+              if (WHOLE || col + 4 <= cols) *reinterpret_cast<f32x4u *>(q) = v;
+              else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                  if (col + e < cols) q[e] = v[e];
+              }
+            }
+            asm volatile("" ::: "memory");
+          }
+      }
+    };
+    if (whole) write_out(std::true_type{});
+    else write_out(std::false_type{});
+    if constexpr (!PL) {
+      const float tot = wave_sum(sq);           // one partial sum of the left-hand side per wavefront and tile
+      if (lane == 0) s.lhs_part[(int64_t)wk * s.n_lhs_part + g.lhs_slot0 + (by * gx + bx) * 4 + w] = tot;
+    }
   }   // tiles
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");     // the movers' last barrier
 }
 
 __device__ __forceinline__ float group16_sum(float x) {
@@ -1284,14 +1423,23 @@ void side_add(Side &sd, const bf16_t *p, int64_t kt, int64_t bstride) {
 // The (tensor count, product set) combinations the layers use.
 template <int EPI, int NA, int NB, bool HAS_D> hipError_t mm5_allow_lds() {
   return hipFuncSetAttribute(reinterpret_cast<const void *>(k_mm5<EPI, NA, NB, HAS_D>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)mm5_lds_bytes(EPI));
+                             (int)kMm5Lds);
 }
 template <int EPI, int NA, int NB, bool HAS_D> int launch_mm5_as(Ctx *c, const Mm5Args &g) {
   // one workgroup per CU at most (8 XCDs x 32 CUs), each XCD's tiles dealt over its workgroups
   const int total = ((g.N + BN - 1) / BN) * ((g.M + BM - 1) / BM) * g.workers, per = (total + 7) / 8;
   const dim3 grid(8 * (per < 32 ? per : 32));
-  hipLaunchKernelGGL((k_mm5<EPI, NA, NB, HAS_D>), grid, dim3(2 * kBlock), mm5_lds_bytes(EPI), c->stream, g);
+  hipLaunchKernelGGL((k_mm5<EPI, NA, NB, HAS_D>), grid, dim3(2 * kBlock), kMm5Lds, c->stream, g);
   return CADA_OK;
+}
+template <int NA, int NB, bool HAS_D, bool CADA1> int launch_dw_as(Ctx *c, const Mm5Args &g) {
+  // two workgroups per CU at most
+  const int total = ((g.N + BN - 1) / BN) * ((g.M + BM - 1) / BM) * g.workers, per = (total + 7) / 8;
+  hipLaunchKernelGGL((k_dw<NA, NB, HAS_D, CADA1>), dim3(8 * (per < 64 ? per : 64)), dim3(kBlock), kDwLds, c->stream, g);
+  return CADA_OK;
+}
+template <int NA, int NB, bool HAS_D, bool CADA1> hipError_t dw_allow_lds() {
+  return hipFuncSetAttribute(reinterpret_cast<const void *>(k_dw<NA, NB, HAS_D, CADA1>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kDwLds);
 }
 // first layer: two A tensors (hi, lo) and no propagated difference on the A side; deeper layers: all of them
 // per wavefront: its partial results (8 KB); weight gradient: the seven blocks it stages (14 KB), over which the partial results are laid later
@@ -1361,14 +1509,15 @@ template <int EPI> int launch_mm5(Ctx *c, Mm5Args &g, int workers) {
   for (int i = 0; i < g.B.n; ++i)
     if (g.B.kt[i] < needB) { set_error("internal: B tensor with fewer chunks than the tiles walk through"); return CADA_EUNSUPPORTED; }
   if (EPI == EPI_DW && (int64_t)((g.K + BK - 1) / BK) * BK > g.Bp) { set_error("internal: more rows than a worker's padded tile"); return CADA_EUNSUPPORTED; }
-  if (g.A.n == 2 && g.B.n == 2) return launch_mm5_as<EPI, 2, 2, false>(c, g);
   if constexpr (EPI == EPI_DW) {
-    if (!has_d && g.A.n == 2 && g.B.n == 3) return launch_mm5_as<EPI, 2, 3, false>(c, g);
-    if (has_d && g.A.n == 3 && g.B.n == 4) return launch_mm5_as<EPI, 3, 4, true>(c, g);
-  } else if constexpr (EPI == EPI_DA) {
-    if (has_d && g.A.n == 4 && g.B.n == 3) return launch_mm5_as<EPI, 4, 3, true>(c, g);
+    const bool cada1 = g.s.rule == CADA_RULE_CADA1;
+    if (g.A.n == 2 && g.B.n == 2) return launch_dw_as<2, 2, false, false>(c, g);
+    if (!has_d && g.A.n == 2 && g.B.n == 3) return cada1 ? launch_dw_as<2, 3, false, true>(c, g) : launch_dw_as<2, 3, false, false>(c, g);
+    if (has_d && g.A.n == 3 && g.B.n == 4) return cada1 ? launch_dw_as<3, 4, true, true>(c, g) : launch_dw_as<3, 4, true, false>(c, g);
   } else {
-    if (!has_d && g.A.n == 2 && g.B.n == 3) return launch_mm5_as<EPI, 2, 3, false>(c, g);
+    if (g.A.n == 2 && g.B.n == 2) return launch_mm5_as<EPI, 2, 2, false>(c, g);
+    if constexpr (EPI == EPI_FWD_HIDDEN)
+      if (!has_d && g.A.n == 2 && g.B.n == 3) return launch_mm5_as<EPI, 2, 3, false>(c, g);
     if (has_d && g.A.n == 4 && g.B.n == 3) return launch_mm5_as<EPI, 4, 3, true>(c, g);
   }
   set_error("internal: no MFMA kernel variant for %d + %d tensors", g.A.n, g.B.n);
@@ -1395,14 +1544,16 @@ int mlp_init_state(Ctx *c, const float *) {
   if (e == hipSuccess) e = mm5_allow_lds<EPI_FWD_HIDDEN, 4, 3, true>();
   if (e == hipSuccess) e = mm5_allow_lds<EPI_FWD_HIDDEN, 2, 2, false>();
   if (e == hipSuccess) e = mm5_allow_lds<EPI_DA, 2, 2, false>();
-  if (e == hipSuccess) e = mm5_allow_lds<EPI_DW, 2, 2, false>();
+  if (e == hipSuccess) e = dw_allow_lds<2, 2, false, false>();
   if (e == hipSuccess) e = skinny_allow_lds<EPI_FWD_HIDDEN, 2, 2, false>();
   if (e == hipSuccess) e = skinny_allow_lds<EPI_FWD_HIDDEN, 2, 3, false>();
   if (e == hipSuccess) e = skinny_allow_lds<EPI_FWD_HIDDEN, 4, 3, true>();
   if (e == hipSuccess) e = skinny_allow_lds<EPI_LOSS, 2, 2, false>();
   if (e == hipSuccess) e = skinny_allow_lds<EPI_DW, 2, 2, false>();
-  if (e == hipSuccess) e = mm5_allow_lds<EPI_DW, 2, 3, false>();
-  if (e == hipSuccess) e = mm5_allow_lds<EPI_DW, 3, 4, true>();
+  if (e == hipSuccess) e = dw_allow_lds<2, 3, false, false>();
+  if (e == hipSuccess) e = dw_allow_lds<2, 3, false, true>();
+  if (e == hipSuccess) e = dw_allow_lds<3, 4, true, false>();
+  if (e == hipSuccess) e = dw_allow_lds<3, 4, true, true>();
   if (e == hipSuccess) e = mm5_allow_lds<EPI_DA, 4, 3, true>();
   if (e == hipSuccess) e = skinny_allow_lds<EPI_LOSS, 2, 3, false>();
   if (e == hipSuccess) e = skinny_allow_lds<EPI_LOSS, 4, 3, true>();
