@@ -79,17 +79,23 @@ struct Mm5Args {
   bf16_t *o_h, *o_l, *o_d, *o_r;        // (padded row, column), kto chunks per tile
   int64_t kto;
   uint64_t *maskbits;                   // ReLU mask bits [workers][row tiles][column tiles][256 lanes][2]: written by EPI_FWD_HIDDEN, read by EPI_DA
-  float *dbpart, *ddbpart;              // EPI_DA: [M_workers][2 x row tiles][N], one partial sum per 64-row band
+  float *dbpart, *ddbpart;              // [workers][nband][units], one partial sum per band of 32 rows: written with the signals of a layer's units (EPI_DA, the last
+                                        // layer's EPI_DW), read by that layer's EPI_DW
   // EPI_DW
   int64_t offW;
   int lhs_slot0;
-  int nband;                            // k_mm5: 64-row bands of dbpart / ddbpart, of which the tiles of the first row band form the layer's bias gradient (0: not here)
+  int nband;                            // bands per worker
+  int bias_here;                        // k_dw: the tiles of the first 128 units form the layer's bias gradient from the bands' sums
   // EPI_LOSS (last layer's forward product with the loss in its epilogue; outputs o_h/o_l/o_d/o_r, bias at offb) and the
   // last layer's EPI_DW, which finishes that layer's bias gradient from the row blocks' sums
   const int64_t *grow;                  // global row of every padded minibatch row (its label)
   float *lastb;                         // [workers][nrb][32][2]: per block of 32 rows, sums over the rows of G and of dG
   int nrb;                              // blocks of 32 rows per worker
   int lhs_slot_b;                       // slot of the bias innovation's part of the left-hand side
+  // the last layer's EPI_DW also forms the activation gradient into the units below (null: a single-layer network): W of that layer, its lo part and its difference
+  // to the reference point as (unit, class) tensors of w_kt chunks; outputs o_h/o_l/o_d/o_r, maskbits and dbpart/ddbpart as for EPI_DA
+  const bf16_t *w_h, *w_l, *w_d;
+  int64_t w_kt, w_dstride;
 };
 
 __device__ __forceinline__ float delta_theta(const DevState &s, const RefPtr &ref, int64_t i) {
@@ -423,21 +429,15 @@ __global__ __launch_bounds__(2 * kBlock, 2) void k_mm5(const Mm5Args g) {
     }
     if constexpr (EPI == EPI_FWD_HIDDEN) { mbits[kh] = bit_on; mbits[2 + kh] = bit_ref; }
     if constexpr (EPI == EPI_DA) {
-      // one value per column and band of 64 rows (partial sum 2 by + wy of the column): the two wavefronts of the band
-      float *band = reinterpret_cast<float *>(smem_raw + 8 * 8192) + w * 128;
-      if (kh == 1 && lane < 32) {
-#pragma unroll
-        for (int j = 0; j < 2; ++j) { band[j * 32 + lane] = csum[j][0]; band[64 + j * 32 + lane] = csum[j][1]; }
-      }
-      lds_sync();
-      if (kh == 0 && lane < 32) {
+      // one value per column and band of 32 rows
+      if (lane < 32) {
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
           const int col = cbase + j * 32;
           if (col < g.N) {
-            const int64_t o = ((int64_t)wk * (2 * gy) + 2 * by + wy) * g.N + col;
-            g.dbpart[o] = csum[j][0] + band[j * 32 + lane];
-            if constexpr (!PL) g.ddbpart[o] = csum[j][1] + band[64 + j * 32 + lane];
+            const int64_t o = ((int64_t)wk * g.nband + 4 * by + 2 * wy + kh) * g.N + col;
+            g.dbpart[o] = csum[j][0];
+            if constexpr (!PL) g.ddbpart[o] = csum[j][1];
           }
         }
       }
@@ -627,16 +627,16 @@ __global__ __launch_bounds__(kBlock, 2) void k_dw(const Mm5Args g) {
     const int rl = lane >> 3;
     const bool whole = rw + 64 <= g.M && cw + 64 <= g.N;        // (uniform) this wavefront's part lies in the matrix
     // The tiles of the first 128 units also form the layer's bias gradient and its innovation, from the sums that the
-    // activation-gradient launch left per band of 64 rows: this wavefront's 64 columns, one per lane, and a partial sum of the left-hand
+    // activation gradients' launch left per band of 32 rows: this wavefront's 64 columns, one per lane, and a partial sum of the left-hand
     // side of their own.  (A launch of its own cost 5 us.  One wavefront for 256 columns, with fewer partial sums: 784-500-10, B = 12:
     // 81.1 -> 82.8 us per step, 3072-1024-1024-10: 608 -> 615.)
-    if (g.nband > 0 && by == 0 && wy == 0 && cw < g.N) {
+    if (g.bias_here && by == 0 && wy == 0 && cw < g.N) {
       const int col = cw + lane;
       float dsum = 0.f;
       if (col < g.N) {
         const float *db = g.dbpart + (int64_t)wk * g.nband * g.N + col, *dd = g.ddbpart + (int64_t)wk * g.nband * g.N + col;
         float gsum = 0.f;
-        for (int i = 0; i < g.nband; ++i) {
+        for (int i = 0; i < (g.K + 31) / 32; ++i) {
           gsum += db[(int64_t)i * g.N];
           if constexpr (!PL) dsum += dd[(int64_t)i * g.N];
         }
@@ -863,6 +863,19 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
 #pragma unroll
     for (int sl = 0; sl < NB; ++sl) pb[sl] = g.B.ptr[sl] + (int64_t)wk * g.B.bstride[sl];
     bf16_t *area = reinterpret_cast<bf16_t *>(smem_raw) + w * (7 * 1024);       // room for seven blocks per wavefront
+    u32x4 wh[2], wl[2], wd[2];                  // (activation gradient: 32 units x 32 classes of W, a unit per lane)
+    if constexpr (PL || HAS_D) {
+      if (g.w_h != nullptr) {
+        const int64_t o = (((int64_t)(m0 >> 7) * g.w_kt) << 12) + (((m0 & 127) + (lane & 31)) << 5) + ((lane >> 5) << 3);
+        const int64_t od = (int64_t)(g.rep ? g.rep[wk] : wk) * g.w_dstride + o;
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+          wh[half] = *reinterpret_cast<const u32x4 *>(g.w_h + o + 16 * half);
+          wl[half] = *reinterpret_cast<const u32x4 *>(g.w_l + o + 16 * half);
+          if constexpr (!PL) wd[half] = *reinterpret_cast<const u32x4 *>(g.w_d + od + 16 * half);
+        }
+      }
+    }
     const int fro_tr = (8 * (lane >> 5) + ((lane & 15) >> 2)) * 32 + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
     for (int kc = w; kc < nk; kc += nw) {
       u32x4 v[NA + NB][2];
@@ -891,6 +904,67 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
           acc2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ad, bx, acc2, 0, 0, 0);
         }
         if constexpr (!PL) acc2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bd, acc2, 0, 0, 0);
+      }
+      if constexpr (PL || HAS_D) {
+        if (g.w_h != nullptr) {
+          // activation gradient of these 32 rows into the units of this block: the signals' block lies in the area as it is, a row per lane
+          f32x16 c1, c2;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) { c1[r] = 0.f; c2[r] = 0.f; }
+#pragma unroll
+          for (int half = 0; half < 2; ++half) {
+            auto sig = [&](int sl) __attribute__((always_inline)) { return *reinterpret_cast<const bf16x8 *>(area + (NA + sl) * 1024 + (lane & 31) * 32 + half * 16 + 8 * (lane >> 5)); };
+            const bf16x8 gh = sig(0), gl = sig(1);
+            c1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(gl, __builtin_bit_cast(bf16x8, wh[half]), c1, 0, 0, 0);
+            c1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(gh, __builtin_bit_cast(bf16x8, wl[half]), c1, 0, 0, 0);
+            c1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(gh, __builtin_bit_cast(bf16x8, wh[half]), c1, 0, 0, 0);
+            if constexpr (!PL) {
+              c2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sig(NB - 1), __builtin_bit_cast(bf16x8, wh[half]), c2, 0, 0, 0);
+              c2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sig(2), __builtin_bit_cast(bf16x8, wd[half]), c2, 0, 0, 0);
+            }
+          }
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+          // masks as k_mm5 and this kernel's forward variant leave them: this block is quarter (i, j) of wavefront (wy, wx) of its 128 x 128 tile
+          const uint16_t *mb = reinterpret_cast<const uint16_t *>(g.maskbits + ((((int64_t)wk * ((g.K + BM - 1) / BM) + (kc >> 2)) * ((g.M + BN - 1) / BN) + (m0 >> 7)) * kBlock +
+                                                                                (((kc >> 1) & 1) * 2 + ((m0 >> 6) & 1)) * 64 + lane) * 2) + (kc & 1) * 2 + ((m0 >> 5) & 1);
+          const uint32_t on = mb[0], on_ref = PL ? 0u : mb[4];
+          float sum_g = 0.f, sum_d = 0.f;
+#pragma unroll
+          for (int r = 0; r < 16; r += 2) {
+            float x[2], xr[2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+              const bool live = m0 + (lane & 31) < g.M && 32 * kc + 8 * (r >> 2) + 4 * (lane >> 5) + ((r + e) & 3) < g.K;
+              x[e] = live && ((on >> (r + e)) & 1) ? c1[r + e] : 0.f;
+              xr[e] = live && ((on_ref >> (r + e)) & 1) ? c1[r + e] - c2[r + e] : 0.f;
+              sum_g += x[e]; sum_d += x[e] - xr[e];
+            }
+            const uint32_t vh = f2bf_pk(x[0], x[1]), vr = f2bf_pk(xr[0], xr[1]), vd = f2bf_pk(x[0] - xr[0], x[1] - xr[1]);
+            const uint32_t vl = f2bf_pk(x[0] - __uint_as_float(vh << 16), x[1] - __uint_as_float(vh & 0xffff0000u));
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+              const int o = (8 * (r >> 2) + 4 * (lane >> 5) + ((r + e) & 3)) * 32 + (lane & 31), sh = 16 * e;
+              area[o] = (bf16_t)(vh >> sh); area[1024 + o] = (bf16_t)(vl >> sh);
+              if constexpr (!PL) { area[2048 + o] = (bf16_t)(vd >> sh); area[3072 + o] = (bf16_t)(vr >> sh); }
+            }
+          }
+          asm volatile("" ::: "memory");
+          const int64_t out = tm((int64_t)wk * g.Bp + 32 * kc, m0, g.kto);
+          bf16_t *const dst[4] = {g.o_h, g.o_l, g.o_d, g.o_r};
+#pragma unroll
+          for (int b = 0; b < (PL ? 2 : 4); ++b)
+            if (dst[b] != nullptr) {
+#pragma unroll
+              for (int hh = 0; hh < 2; ++hh) *reinterpret_cast<u32x4 *>(dst[b] + out + (hh * 64 + lane) * 8) = *reinterpret_cast<const u32x4 *>(area + b * 1024 + (hh * 64 + lane) * 8);
+            }
+          sum_g += __shfl_xor(sum_g, 32, 64);
+          sum_d += __shfl_xor(sum_d, 32, 64);
+          if (lane < 32 && m0 + lane < g.M) {
+            const int64_t o = ((int64_t)wk * g.nband + kc) * g.M + m0 + lane;
+            g.dbpart[o] = sum_g;
+            if constexpr (!PL) g.ddbpart[o] = sum_d;
+          }
+        }
       }
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the fragments are in registers before the area is written again
     }
@@ -1170,8 +1244,8 @@ void layout(MlpPlan &P, const cada_config *cfg, int64_t total_rows, Carve &w) {
   }
   (void)w.take<float>(Rp * P.d[P.L]);             // (not used any more; the room keeps the layout of saved checkpoint blocks)
   (void)w.take<float>(Rp * P.d[P.L]);
-  P.dbpart = w.take<float>((size_t)cfg->M * 2 * P.RT * maxh);
-  P.ddbpart = w.take<float>((size_t)cfg->M * 2 * P.RT * maxh);
+  (void)w.take<float>((size_t)cfg->M * 2 * P.RT * maxh);     // (nor this)
+  (void)w.take<float>((size_t)cfg->M * 2 * P.RT * maxh);
   P.lastb = w.take<float>((size_t)cfg->M * (P.Bp / 32) * 32 * 2);
 }
 }  // namespace
@@ -1203,16 +1277,21 @@ size_t mlp_workspace_bytes(const cada_config *cfg, const int64_t total_rows) {
   return w.off + kAlignB;
 }
 
-// The partial sums of the left-hand side, in front of the evaluation's scratch.
+// Scratch: the partial sums of the left-hand side, the bands' sums of the signals and of their differences, the evaluation's.
 static size_t lhs_bytes(const cada_config *cfg) {
   return ((size_t)cfg->M * mlp_lhs_slots(cfg, mlp_bias_cols(cfg->rule)) * sizeof(float) + kAlignB - 1) / kAlignB * kAlignB;
+}
+static size_t band_bytes(const MlpPlan &P) {
+  int maxh = 1;
+  for (int l = 1; l < P.L; ++l) if (P.d[l] > maxh) maxh = P.d[l];
+  return ((size_t)P.M * 4 * P.RT * maxh * sizeof(float) + kAlignB - 1) / kAlignB * kAlignB;
 }
 
 size_t mlp_scratch_bytes(const cada_config *cfg, const int64_t total_rows) {
   MlpPlan P;
   Carve w{nullptr, 0};
   layout(P, cfg, total_rows, w);
-  return lhs_bytes(cfg) + mlp_eval_bytes(P) + kAlignB;
+  return lhs_bytes(cfg) + 2 * band_bytes(P) + mlp_eval_bytes(P) + kAlignB;
 }
 
 int mlp_plan(Ctx *c, const cada_config *cfg, char *base, size_t offset, size_t scratch, int64_t total_rows) {
@@ -1223,7 +1302,9 @@ int mlp_plan(Ctx *c, const cada_config *cfg, char *base, size_t offset, size_t s
   layout(*P, cfg, total_rows, w);
   scratch = (scratch + kAlignB - 1) / kAlignB * kAlignB;
   c->s.lhs_part = reinterpret_cast<float *>(base + scratch);
-  P->eval = base + scratch + lhs_bytes(cfg);
+  P->dbpart = reinterpret_cast<float *>(base + scratch + lhs_bytes(cfg));
+  P->ddbpart = P->dbpart + band_bytes(*P) / sizeof(float);
+  P->eval = reinterpret_cast<char *>(P->ddbpart) + band_bytes(*P);
   c->mlp = P;
   c->n_phases = 3;
   c->phase_names[0] = "mlp_gradients"; c->phase_names[1] = "rule"; c->phase_names[2] = "server_update";
@@ -1403,18 +1484,18 @@ __global__ __launch_bounds__(kBlock) void k_stage(const StageArgs a) {
   stage_weights(a, p, sm, (int)(r % p.gx), (int)(r / p.gx), (int)z, l == 0 && r == 0);
 }
 
-// Hidden-layer bias gradient and its innovation from the per-tile partial sums of k_mm5<EPI_DA>.
+// Hidden-layer bias gradient and its innovation from the sums per band of 32 rows.
 // grid (ceil(d / 64), M), one wavefront each
-__global__ __launch_bounds__(kWave) void k_bias_finish(const DevState s, const float *dbpart, const float *ddbpart, int RT, int d,
+__global__ __launch_bounds__(kWave) void k_bias_finish(const DevState s, const float *dbpart, const float *ddbpart, int nband, int bands, int d,
                                                        int64_t offb, int lhs_slot) {
   const int m = blockIdx.y;
   const int c = blockIdx.x * kWave + threadIdx.x;
   float sq = 0.f;
   if (c < d) {
     float gsum = 0.f, dsum = 0.f;
-    for (int rt = 0; rt < RT; ++rt) {
-      gsum += dbpart[((int64_t)m * RT + rt) * d + c];
-      if (ddbpart) dsum += ddbpart[((int64_t)m * RT + rt) * d + c];
+    for (int rb = 0; rb < bands; ++rb) {
+      gsum += dbpart[((int64_t)m * nband + rb) * d + c];
+      if (ddbpart) dsum += ddbpart[((int64_t)m * nband + rb) * d + c];
     }
     put_fresh_grad(s, m, offb + c, gsum);
     if (s.rule == CADA_RULE_CADA1) {
@@ -1669,6 +1750,14 @@ static bool bias_inside(int M, int din, int dout) {
   return dout > 32 && (int64_t)M * tiles128(dout) <= 512 && (int64_t)M * din < 65536;
 }
 
+// Where the signals of hidden layer q go, with their masks and the sums for its bias gradient.
+static void signals_below(Mm5Args &g, const MlpPlan &P, int q, bool plain) {
+  g.kto = P.kta[q];
+  g.o_h = P.Gh[q]; g.o_l = P.Gl[q]; g.o_d = plain ? nullptr : P.dG[q]; g.o_r = plain ? nullptr : P.Gref[q];     // (Gref: null for q = 1)
+  g.maskbits = P.maskbits[q];
+  g.dbpart = P.dbpart; g.ddbpart = P.ddbpart; g.nband = 4 * P.RT;
+}
+
 int mlp_gradients(Ctx *c, const int32_t *idx) {
   MlpPlan &P = *static_cast<MlpPlan *>(c->mlp);
   DevState s = c->s;
@@ -1709,12 +1798,17 @@ int mlp_gradients(Ctx *c, const int32_t *idx) {
       g.offW = P.offW[l - 1]; g.lhs_slot0 = P.lhs_w_slot[l - 1];
       if (l == L) {     // the last layer's launch also finishes its bias gradient from the forward launch's row-block sums
         g.lastb = P.lastb; g.nrb = Bp / 32; g.offb = P.offb[L - 1]; g.lhs_slot_b = P.lhs_b_slot[L - 1];
-      } else if (bias_inside(M, din, dout)) {       // and the other layers' from the activation-gradient launch's sums
-        g.dbpart = P.dbpart; g.ddbpart = P.ddbpart; g.nband = 2 * P.RT; g.offb = P.offb[l - 1]; g.lhs_slot_b = P.lhs_b_slot[l - 1];
+        if (l >= 2) {   // and forms the activation gradient into the layer below
+          g.w_h = P.WNh + P.wn_off[l - 1]; g.w_l = P.WNl + P.wn_off[l - 1]; g.w_d = P.dWN + P.wn_off[l - 1];
+          g.w_kt = P.kta[l]; g.w_dstride = dwn_stride; g.rep = per_worker ? P.rep : nullptr;
+          signals_below(g, P, l - 1, plain);
+        }
+      } else if (bias_inside(M, din, dout)) {       // and the other layers' from the sums of the launch that formed their signals
+        g.dbpart = P.dbpart; g.ddbpart = P.ddbpart; g.nband = 4 * P.RT; g.bias_here = 1; g.offb = P.offb[l - 1]; g.lhs_slot_b = P.lhs_b_slot[l - 1];
       }
       if (const int rc = launch_mm5<EPI_DW>(c, g, M)) return rc;
     }
-    if (l >= 2) {   // gradient w.r.t. the activations of layer l-1, masks, bias partials
+    if (l >= 2 && l < L) {   // gradient w.r.t. the activations of layer l-1, masks, bias partials
       Mm5Args g = blank(s, P);
       g.M = B; g.N = din; g.K = dout;
       const int64_t bs = (int64_t)Bp * P.kta[l] * 32;
@@ -1729,16 +1823,12 @@ int mlp_gradients(Ctx *c, const int32_t *idx) {
       g.b_h = 0; g.b_l = 1; g.b_x = 0; g.b_d = 1;
       if (!plain) { side_add(g.B, P.dWN + P.wn_off[l - 1], ktn, dwn_stride); g.b_d = 2; }
       g.rep = per_worker ? P.rep : nullptr;
-      const int q = l - 1;
-      g.offb = P.offb[q - 1]; g.kto = P.kta[q];
-      g.o_h = P.Gh[q]; g.o_l = P.Gl[q]; g.o_d = plain ? nullptr : P.dG[q]; g.o_r = plain ? nullptr : P.Gref[q];     // (Gref: null for q = 1)
-      g.maskbits = P.maskbits[q];
-      g.dbpart = P.dbpart; g.ddbpart = P.ddbpart;
+      signals_below(g, P, l - 1, plain);
       if (const int rc = launch_mm5<EPI_DA>(c, g, M)) return rc;
-      if (!bias_inside(M, P.d[q - 1], din))
-        hipLaunchKernelGGL(k_bias_finish, dim3((din + kWave - 1) / kWave, M), dim3(kWave), 0, st, s, P.dbpart, plain ? nullptr : P.ddbpart, 2 * P.RT, din,
-                         P.offb[q - 1], P.lhs_b_slot[q - 1]);
     }
+    if (l >= 2 && !bias_inside(M, P.d[l - 2], din))
+      hipLaunchKernelGGL(k_bias_finish, dim3((din + kWave - 1) / kWave, M), dim3(kWave), 0, st, s, P.dbpart, plain ? nullptr : P.ddbpart, 4 * P.RT, (B + 31) / 32, din,
+                         P.offb[l - 2], P.lhs_b_slot[l - 2]);
   }
   prof_mark(c);
   const hipError_t e = hipGetLastError();
