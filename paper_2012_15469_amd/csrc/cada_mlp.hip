@@ -57,6 +57,17 @@ enum { EPI_FWD_HIDDEN = 0, EPI_DW = 2, EPI_DA = 3, EPI_LOSS = 4 };
 constexpr int kMm5Slots = 20;
 constexpr size_t kMm5Lds = (size_t)kMm5Slots * TILE * sizeof(bf16_t);      // 160 KB
 
+// Division of 0 <= x < 2^31 by a divisor that the host knows: a product and a shift (as a division it takes the compiler some forty
+// instructions, and a tile's three indices two of them, each time at the head of a launch that may have one tile per workgroup).
+// With 2^(l-1) < d <= 2^l, m = floor(2^(31+l) / d) + 1 exceeds 2^(31+l) / d by e <= 1, and x e / 2^(31+l) < 2^-l <= 1 / d: the floor is x / d's.
+struct Divisor { uint32_t d, m, shift; };
+static Divisor divisor(uint32_t d) {
+  uint32_t l = 0;
+  while ((1u << l) < d) ++l;
+  return Divisor{d, (uint32_t)((1ull << (31 + l)) / d + 1), 31 + l};
+}
+__device__ __forceinline__ int quotient(int x, const Divisor &v) { return (int)(((uint64_t)(uint32_t)x * v.m) >> v.shift); }
+
 // Up to four tensors that share the row index of one side of the product.
 struct Side {
   const bf16_t *ptr[kMaxSlots];
@@ -72,6 +83,7 @@ struct Mm5Args {
   int b_h, b_l, b_x, b_d;       // role -> slot of B
   int M, N, K;                  // extents of the tile index spaces and of the contraction
   int workers;
+  Divisor gx, gy, nbx;          // k_mm5, k_dw: tiles per row and per column of tiles, workgroups per XCD
   const int32_t *rep;           // optional: the B side of worker m is read at worker rep[m]'s offset (shared reference points)
   int Bp;                       // padded rows per worker (multiple of 128)
   // EPI_FWD_HIDDEN / EPI_DA: bias offset, outputs
@@ -91,6 +103,7 @@ struct Mm5Args {
   const int64_t *grow;                  // global row of every padded minibatch row (its label)
   float *lastb;                         // [workers][nrb][32][2]: per block of 32 rows, sums over the rows of G and of dG
   int nrb;                              // blocks of 32 rows per worker
+  int step_waves;                       // k_skinny<EPI_DW>: wavefronts that take tile steps
   int lhs_slot_b;                       // slot of the bias innovation's part of the left-hand side
   // the last layer's EPI_DW also forms the activation gradient into the units below (null: a single-layer network): W of that layer, its lo part and its difference
   // to the reference point as (unit, class) tensors of w_kt chunks; outputs o_h/o_l/o_d/o_r, maskbits and dbpart/ddbpart as for EPI_DA
@@ -182,9 +195,9 @@ __global__ __launch_bounds__(2 * kBlock, 2) void k_mm5(const Mm5Args g) {
   // turn; XCD x takes the x-th eighth of the tiles (columns fastest, then rows, then workers), its
   // workgroups every nbx-th of those: an XCD's L2 then sees whole workers, or a few row tiles of
   // one worker with all their column tiles, instead of every worker's operands.
-  const int gx = (g.N + BN - 1) / BN, gy = (g.M + BM - 1) / BM;
+  const int gx = g.gx.d, gy = g.gy.d;
   const int total = gx * gy * g.workers, per = (total + 7) / 8;
-  const int nbx = gridDim.x >> 3;
+  const int nbx = g.nbx.d;
   const int t_first = (blockIdx.x & 7) * per + (blockIdx.x >> 3), t_end = min(((int)(blockIdx.x & 7) + 1) * per, total);
   const int nk = (g.K + BK - 1) / BK;
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem_raw;
@@ -193,7 +206,7 @@ __global__ __launch_bounds__(2 * kBlock, 2) void k_mm5(const Mm5Args g) {
   const uint32_t fro = (lds_piece((lane & 31) * 4 + (lane >> 5)) * 16) ^ (kh * 32);
 
   for (int tix = t_first; tix < t_end; tix += nbx) {
-    const int bx = tix % gx, by = (tix / gx) % gy, wk = tix / (gx * gy);     // wk: worker
+    const int trow = quotient(tix, g.gx), bx = tix - trow * gx, wk = quotient(trow, g.gy), by = trow - wk * gy;     // wk: worker
     const int m0 = by * BM, n0 = bx * BN;
     const bf16_t *src[NS];
     {
@@ -470,6 +483,8 @@ __global__ __launch_bounds__(2 * kBlock, 2) void k_mm5(const Mm5Args g) {
 // The unit of A is the MFMA's column index: a lane's accumulators are one row of the matrix and groups of four consecutive
 // columns, which go through LDS 16 bytes (bf16: 8) at a time and leave as whole rows of 128 bytes.  (Plain stores: with the non-temporal hint, which
 // paid for rows of 256 bytes, 201 and 62 us where plain ones took 180 and 44.)
+typedef uint32_t u32h __attribute__((aligned(2)));
+typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));
 typedef uint32_t u32x4h __attribute__((ext_vector_type(4), aligned(2)));   // eight bf16 values at any address
 constexpr int kDwRows = 16;                                    // rows per step
 constexpr int kDwSlots = 20;
@@ -485,11 +500,11 @@ __global__ __launch_bounds__(kBlock, 2) void k_dw(const Mm5Args g) {
   const DevState &s = g.s;
   const int lane0 = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), wy = w >> 1, wx = w & 1;
   // tiles of this workgroup: as in k_mm5
-  const int gx = (g.N + BN - 1) / BN, gy = (g.M + BM - 1) / BM;
-  const int total = gx * gy * g.workers, per = (total + 7) / 8, nbx = gridDim.x >> 3;
+  const int gx = g.gx.d, gy = g.gy.d;
+  const int total = gx * gy * g.workers, per = (total + 7) / 8, nbx = g.nbx.d;
   const int t_first = (blockIdx.x & 7) * per + (blockIdx.x >> 3), t_end = min(((int)(blockIdx.x & 7) + 1) * per, total);
   if (t_first >= t_end) return;
-  const int nt = (t_end - t_first + nbx - 1) / nbx, nk = (g.K + kDwRows - 1) / kDwRows, nsteps = nt * nk;
+  const int nt = quotient(t_end - t_first + nbx - 1, g.nbx), nk = (g.K + kDwRows - 1) / kDwRows, nsteps = nt * nk;
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem_raw;
 
   // issue cursor: step, tile, step in the tile, slot; this wavefront's chunk of every operand of the tile, and the step's place in it
@@ -497,7 +512,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_dw(const Mm5Args g) {
   const bf16_t *src[NS];
   int64_t at_a = 0, at_b = 0;
   auto set_tile = [&]() __attribute__((always_inline)) {
-    const int bx = i_tix % gx, by = (i_tix / gx) % gy, bz = i_tix / (gx * gy);
+    const int trow = quotient(i_tix, g.gx), bx = i_tix - trow * gx, bz = quotient(trow, g.gy), by = trow - bz * gy;
 #pragma unroll
     for (int q = 0; q < NA; ++q) src[q] = g.A.ptr[q] + (int64_t)bz * g.A.bstride[q] + ((int64_t)(4 * by + w) << 12);
 #pragma unroll
@@ -530,6 +545,38 @@ __global__ __launch_bounds__(kBlock, 2) void k_dw(const Mm5Args g) {
   if constexpr (R0 > 0) next_step();
 #pragma unroll
   for (int q = 0; q < R0; ++q) load(q);
+  // The tiles of the first 128 units also form the layer's bias gradient and its innovation, from the sums that the
+  // activation gradients' launch left per band of 32 rows: 64 columns from cw on, one per lane, and a partial sum of the left-hand
+  // side of their own.  (A launch of its own cost 5 us.  One wavefront for 256 columns, with fewer partial sums: 784-500-10, B = 12:
+  // 81.1 -> 82.8 us per step, 3072-1024-1024-10: 608 -> 615.)  A workgroup's first tile does it while its operands are on their way, a later one before
+  // its way out, when the stores of the tile before have drained.
+  auto bias_part = [&](int wk, int bx) __attribute__((always_inline)) {
+    const int cw = bx * BN + wx * 64;
+    if (cw >= g.N) return;
+    const int col = cw + lane0;
+    float dsum = 0.f;
+    if (col < g.N) {
+      const float *db = g.dbpart + (int64_t)wk * g.nband * g.N + col, *dd = g.ddbpart + (int64_t)wk * g.nband * g.N + col;
+      float gsum = 0.f;
+      for (int i = 0; i < (g.K + 31) / 32; ++i) {
+        gsum += db[(int64_t)i * g.N];
+        if constexpr (!PL) dsum += dd[(int64_t)i * g.N];
+      }
+      put_fresh_grad(s, wk, g.offb + col, gsum);
+      if (CADA1) {
+        fresh_innov(s, wk)[g.offb + col] = f2bf(dsum);
+        dsum -= bf2f(stored_innov(s, wk)[g.offb + col]);
+      }
+    }
+    if constexpr (!PL) {
+      const float totb = wave_sum(dsum * dsum);
+      if (lane0 == 0) s.lhs_part[(int64_t)wk * s.n_lhs_part + g.lhs_slot_b + 2 * bx + wx] = totb;
+    }
+  };
+  if (g.bias_here && wy == 0) {
+    const int trow = quotient(t_first, g.gx), wk = quotient(trow, g.gy);
+    if (trow == wk * gy) bias_part(wk, t_first - trow * gx);
+  }
   // (the first step; all of them where there are few)
   if (nsteps >= AHEAD) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((AHEAD - 1) * NS) : "memory");
   else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -538,7 +585,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_dw(const Mm5Args g) {
   const int fro = (8 * (lane0 >> 5) + ((lane0 & 15) >> 2)) * 32 + 16 * ((lane0 >> 4) & 1) + 4 * (lane0 & 3);
   int step = 0, sb = 0, landed = 0;             // sb: slot of the first tensor of the step whose fragments are read next
   for (int tix = t_first; tix < t_end; tix += nbx) {
-    const int bx = tix % gx, by = (tix / gx) % gy, wk = tix / (gx * gy);     // wk: worker
+    const int trow = quotient(tix, g.gx), bx = tix - trow * gx, wk = quotient(trow, g.gy), by = trow - wk * gy;     // wk: worker
     f32x16 acc1[2][2], acc2[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -626,31 +673,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_dw(const Mm5Args g) {
     // On the way out a lane has 16 bytes of a row: floats 4 (lane % 8) .. of 32 columns, bf16 values 8 (lane % 8) .. of 64, of row lane / 8 + 8 it.
     const int rl = lane >> 3;
     const bool whole = rw + 64 <= g.M && cw + 64 <= g.N;        // (uniform) this wavefront's part lies in the matrix
-    // The tiles of the first 128 units also form the layer's bias gradient and its innovation, from the sums that the
-    // activation gradients' launch left per band of 32 rows: this wavefront's 64 columns, one per lane, and a partial sum of the left-hand
-    // side of their own.  (A launch of its own cost 5 us.  One wavefront for 256 columns, with fewer partial sums: 784-500-10, B = 12:
-    // 81.1 -> 82.8 us per step, 3072-1024-1024-10: 608 -> 615.)
-    if (g.bias_here && by == 0 && wy == 0 && cw < g.N) {
-      const int col = cw + lane;
-      float dsum = 0.f;
-      if (col < g.N) {
-        const float *db = g.dbpart + (int64_t)wk * g.nband * g.N + col, *dd = g.ddbpart + (int64_t)wk * g.nband * g.N + col;
-        float gsum = 0.f;
-        for (int i = 0; i < (g.K + 31) / 32; ++i) {
-          gsum += db[(int64_t)i * g.N];
-          if constexpr (!PL) dsum += dd[(int64_t)i * g.N];
-        }
-        put_fresh_grad(s, wk, g.offb + col, gsum);
-        if (CADA1) {
-          fresh_innov(s, wk)[g.offb + col] = f2bf(dsum);
-          dsum -= bf2f(stored_innov(s, wk)[g.offb + col]);
-        }
-      }
-      if constexpr (!PL) {
-        const float totb = wave_sum(dsum * dsum);
-        if (lane == 0) s.lhs_part[(int64_t)wk * s.n_lhs_part + g.lhs_slot_b + 2 * bx + wx] = totb;
-      }
-    }
+    if (g.bias_here && by == 0 && wy == 0 && tix != t_first) bias_part(wk, bx);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     landed = LANDED;
 
@@ -672,10 +695,11 @@ __global__ __launch_bounds__(kBlock, 2) void k_dw(const Mm5Args g) {
           if (!WHOLE && row >= rows) continue;
           bf16_t *q = base + (uint32_t)row * (uint32_t)g.N + col;
           if (WHOLE || col + 8 <= cols) *reinterpret_cast<u32x4h *>(q) = v;
-          else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-              if (col + e < cols) q[e] = (bf16_t)(v[e >> 1] >> (16 * (e & 1)));
+          else if (col < cols) {               // the one lane at the matrix's edge: (uniform) cols % 8 values
+            uint32_t x = v.x, y = v.y;
+            if (cols & 4) { *reinterpret_cast<u32x2u *>(q) = u32x2u{x, y}; q += 4; x = v.z; y = v.w; }
+            if (cols & 2) { *reinterpret_cast<u32h *>(q) = x; q += 2; x = y; }
+            if (cols & 1) *q = (bf16_t)x;
           }
         }
       };
@@ -754,10 +778,10 @@ __global__ __launch_bounds__(kBlock, 2) void k_dw(const Mm5Args g) {
               if (!WHOLE && row >= rows) continue;
               float *q = gf + (uint32_t)row * (uint32_t)g.N + col;
               if (WHOLE || col + 4 <= cols) *reinterpret_cast<f32x4u *>(q) = v;
-              else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                  if (col + e < cols) q[e] = v[e];
+              else if (col < cols) {           // (cols % 4 values)
+                float x = v.x;
+                if (cols & 2) { *reinterpret_cast<f32x2u *>(q) = f32x2u{v.x, v.y}; q += 2; x = v.z; }
+                if (cols & 1) *q = x;
               }
             }
             asm volatile("" ::: "memory");
@@ -800,7 +824,8 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
   float *red = reinterpret_cast<float *>(smem_raw);                  // [8 wavefronts][2 accumulators][16][64]
   const DevState &s = g.s;
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  const int nw = blockDim.x >> 6;          // wavefronts of this launch (1..8): fewer for short contractions, so that more workgroups fit a CU
+  const int nw = blockDim.x >> 6;          // wavefronts of this launch (1..8)
+  const int nsw = EPI == EPI_DW ? g.step_waves : nw;       // those that take tile steps: fewer for short contractions, so that more workgroups fit a CU
   const int m0 = blockIdx.x * 32, wk = blockIdx.y;
   const int nk = (g.K + BK - 1) / BK;
   constexpr bool PL = NB == 2;
@@ -835,6 +860,16 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
       return;
     }
   }
+  const bool cada1 = !PL && s.rule == CADA_RULE_CADA1;
+  bf16_t old_iv[4] = {0, 0, 0, 0};              // EPI_DW: the stored innovations of four of the elements that this thread writes, from e0 on
+  auto ask_old = [&](int e0) __attribute__((always_inline)) {
+    const bf16_t *ivs = stored_innov(s, wk) + g.offW;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int e = min(e0 + i * (int)blockDim.x, 16 * 64 - 1), r = e >> 6, ln = e & 63;
+      old_iv[i] = ivs[(int64_t)min(m0 + 8 * (r >> 2) + 4 * (ln >> 5) + (r & 3), g.M - 1) * g.N + min(ln & 31, g.N - 1)];
+    }
+  };
   const bf16_t *pa[NA], *pb[NB];
   f32x16 acc1, acc2;
 #pragma unroll
@@ -863,6 +898,7 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
 #pragma unroll
     for (int sl = 0; sl < NB; ++sl) pb[sl] = g.B.ptr[sl] + (int64_t)wk * g.B.bstride[sl];
     bf16_t *area = reinterpret_cast<bf16_t *>(smem_raw) + w * (7 * 1024);       // room for seven blocks per wavefront
+    if (cada1) ask_old(t);                      // (used after the products)
     u32x4 wh[2], wl[2], wd[2];                  // (activation gradient: 32 units x 32 classes of W, a unit per lane)
     if constexpr (PL || HAS_D) {
       if (g.w_h != nullptr) {
@@ -877,7 +913,8 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
       }
     }
     const int fro_tr = (8 * (lane >> 5) + ((lane & 15) >> 2)) * 32 + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-    for (int kc = w; kc < nk; kc += nw) {
+    if (w < nsw)
+    for (int kc = w; kc < nk; kc += nsw) {
       u32x4 v[NA + NB][2];
 #pragma unroll
       for (int sl = 0; sl < NA + NB; ++sl) {
@@ -1002,10 +1039,12 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
     }
   }
   }
+  if (w < nsw) {
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    red[((w * 2 + 0) * 16 + r) * 64 + lane] = acc1[r];
-    if constexpr (!PL) red[((w * 2 + 1) * 16 + r) * 64 + lane] = acc2[r];
+    for (int r = 0; r < 16; ++r) {
+      red[((w * 2 + 0) * 16 + r) * 64 + lane] = acc1[r];
+      if constexpr (!PL) red[((w * 2 + 1) * 16 + r) * 64 + lane] = acc2[r];
+    }
   }
   __syncthreads();
   if constexpr (EPI == EPI_FWD_HIDDEN) {
@@ -1142,33 +1181,32 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
     }
     return;
   }
-  // 2 x 16 x 64 values over the threads, each the sum of the wavefronts' partial results in wavefront order
-  float *gf = nullptr;
-  bf16_t *gf16 = nullptr;
-  bf16_t *ivf = nullptr;
-  const bf16_t *ivs = nullptr;
-  const bool cada1 = !PL && s.rule == CADA_RULE_CADA1;
-  if constexpr (EPI == EPI_DW) {
-    if (s.gbuf16) gf16 = fresh_grad16(s, wk) + g.offW;
-    else gf = fresh_grad(s, wk) + g.offW;
-    if (cada1) {
-      ivf = fresh_innov(s, wk) + g.offW;
-      ivs = stored_innov(s, wk) + g.offW;
-    }
-  }
+  // The 16 x 64 sums over the threads, four at a time, each the sum of the wavefronts' partial results in wavefront order
   float sq = 0.f;
-  for (int e = t; e < (PL ? 1 : 2) * 16 * 64; e += (int)blockDim.x) {       // (accumulator, r, lane)
-    const int a = e >> 10, r = (e >> 6) & 15, ln = e & 63;
-    float v = 0.f;
-    for (int ww = 0; ww < nw; ++ww) v += red[((ww * 2 + a) * 16 + r) * 64 + ln];
-    const int row = m0 + 8 * (r >> 2) + 4 * (ln >> 5) + (r & 3), col = ln & 31;
-    if (row < g.M && col < g.N) {
-      const int64_t o = (int64_t)row * g.N + col;
-      if (a == 0) {
-        if (gf16) gf16[o] = f2bf(v); else gf[o] = v;
-      } else {
-        if (cada1) { ivf[o] = f2bf(v); v -= bf2f(ivs[o]); }
-        sq = fmaf(v, v, sq);
+  if constexpr (EPI == EPI_DW) {
+    float *gf = s.gbuf16 ? nullptr : fresh_grad(s, wk) + g.offW;
+    bf16_t *gf16 = s.gbuf16 ? fresh_grad16(s, wk) + g.offW : nullptr;
+    bf16_t *ivf = cada1 ? fresh_innov(s, wk) + g.offW : nullptr;
+    for (int e0 = t; e0 < 16 * 64; e0 += 4 * (int)blockDim.x) {
+      if (cada1 && e0 != t) ask_old(e0);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int e = e0 + i * (int)blockDim.x;
+        if (e >= 16 * 64) break;
+        float v = 0.f, iv = 0.f;
+        for (int ww = 0; ww < nsw; ++ww) {
+          v += red[(ww * 2 + 0) * 1024 + e];
+          if constexpr (!PL) iv += red[(ww * 2 + 1) * 1024 + e];
+        }
+        const int r = e >> 6, ln = e & 63, row = m0 + 8 * (r >> 2) + 4 * (ln >> 5) + (r & 3), col = ln & 31;
+        if (row < g.M && col < g.N) {
+          const int64_t o = (int64_t)row * g.N + col;
+          if (gf16) gf16[o] = f2bf(v); else gf[o] = v;
+          if constexpr (!PL) {
+            if (cada1) { ivf[o] = f2bf(iv); iv -= bf2f(old_iv[i]); }
+            sq = fmaf(iv, iv, sq);
+          }
+        }
       }
     }
   }
@@ -1517,22 +1555,26 @@ void side_add(Side &sd, const bf16_t *p, int64_t kt, int64_t bstride) {
   sd.ptr[sd.n] = p; sd.kt[sd.n] = kt; sd.bstride[sd.n] = bstride; sd.n += 1;
 }
 
+void set_tiles(Mm5Args &g, int per_xcd) { g.gx = divisor((g.N + BN - 1) / BN); g.gy = divisor((g.M + BM - 1) / BM); g.nbx = divisor(per_xcd); }
+
 // The (tensor count, product set) combinations the layers use.
 template <int EPI, int NA, int NB, bool HAS_D> hipError_t mm5_allow_lds() {
   return hipFuncSetAttribute(reinterpret_cast<const void *>(k_mm5<EPI, NA, NB, HAS_D>), hipFuncAttributeMaxDynamicSharedMemorySize,
                              (int)kMm5Lds);
 }
-template <int EPI, int NA, int NB, bool HAS_D> int launch_mm5_as(Ctx *c, const Mm5Args &g) {
+template <int EPI, int NA, int NB, bool HAS_D> int launch_mm5_as(Ctx *c, Mm5Args &g) {
   // one workgroup per CU at most (8 XCDs x 32 CUs), each XCD's tiles dealt over its workgroups
   const int total = ((g.N + BN - 1) / BN) * ((g.M + BM - 1) / BM) * g.workers, per = (total + 7) / 8;
-  const dim3 grid(8 * (per < 32 ? per : 32));
+  set_tiles(g, per < 32 ? per : 32);
+  const dim3 grid(8 * g.nbx.d);
   hipLaunchKernelGGL((k_mm5<EPI, NA, NB, HAS_D>), grid, dim3(2 * kBlock), kMm5Lds, c->stream, g);
   return CADA_OK;
 }
-template <int NA, int NB, bool HAS_D, bool CADA1> int launch_dw_as(Ctx *c, const Mm5Args &g) {
+template <int NA, int NB, bool HAS_D, bool CADA1> int launch_dw_as(Ctx *c, Mm5Args &g) {
   // two workgroups per CU at most
   const int total = ((g.N + BN - 1) / BN) * ((g.M + BM - 1) / BM) * g.workers, per = (total + 7) / 8;
-  hipLaunchKernelGGL((k_dw<NA, NB, HAS_D, CADA1>), dim3(8 * (per < 64 ? per : 64)), dim3(kBlock), kDwLds, c->stream, g);
+  set_tiles(g, per < 64 ? per : 64);
+  hipLaunchKernelGGL((k_dw<NA, NB, HAS_D, CADA1>), dim3(8 * g.nbx.d), dim3(kBlock), kDwLds, c->stream, g);
   return CADA_OK;
 }
 template <int NA, int NB, bool HAS_D, bool CADA1> hipError_t dw_allow_lds() {
@@ -1552,10 +1594,16 @@ template <int EPI, int NA, int NB, bool HAS_D> hipError_t skinny_allow_lds() {
   return hipFuncSetAttribute(reinterpret_cast<const void *>(k_skinny<EPI, NA, NB, HAS_D>), hipFuncAttributeMaxDynamicSharedMemorySize,
                              skinny_lds_bytes(EPI));
 }
-template <int EPI, int NA, int NB, bool HAS_D> int launch_skinny_as(Ctx *c, const Mm5Args &g) {
+template <int EPI, int NA, int NB, bool HAS_D> int launch_skinny_as(Ctx *c, Mm5Args &g) {
   const int nw = skinny_waves(EPI, g.K);
+  g.step_waves = nw;
   const unsigned extra = (EPI == EPI_DW && g.lastb != nullptr) ? 1u : 0u;      // (the workgroup that finishes the last layer's bias gradient)
-  hipLaunchKernelGGL((k_skinny<EPI, NA, NB, HAS_D>), dim3((unsigned)((g.M + 31) / 32) + extra, g.workers, EPI == EPI_FWD_HIDDEN ? (unsigned)((g.N + 31) / 32) : 1u), dim3(64 * nw), skinny_lds_bytes(EPI, nw), c->stream, g);
+  // A weight gradient's way out is spread over four wavefronts at least where the CUs have room for them (with one, 120-80-60-5, 8 workers of 40
+  // rows: 12.7 us, now 10.3); with more than two workgroups per CU, whose registers they take, over those of the products (784-512-10, 64 workers of 128 rows:
+  // 22.6 us with two, 24 with four).
+  const int wide = EPI == EPI_DW && nw < 4 && (int64_t)((g.M + 31) / 32 + extra) * g.workers <= 512 ? 4 : nw;
+  hipLaunchKernelGGL((k_skinny<EPI, NA, NB, HAS_D>), dim3((unsigned)((g.M + 31) / 32) + extra, g.workers, EPI == EPI_FWD_HIDDEN ? (unsigned)((g.N + 31) / 32) : 1u),
+                     dim3(64 * wide), skinny_lds_bytes(EPI, nw), c->stream, g);
   return CADA_OK;
 }
 // Hidden layers' forward products go through k_skinny while its 32 x 32 blocks fill the chip (two workgroups per CU) at most twice
