@@ -8,13 +8,16 @@
 // these registers are, as they are, the operand of the last layer's product (whose sum over the units may take them in any order, as
 // long as the weights follow it).  With one hidden layer nothing but the row's loss leaves the chip; deeper networks
 // pass activations on through rows of scratch that belong to the workgroup (L2-resident, never read by another).
-// Operands go straight to LDS, one step of 32 inputs ahead of the products, over the boundaries of unit and row tiles.
+// Operands go straight to LDS, weights one step of 32 inputs ahead of the products and rows, which come from HBM, two (one where the launch has several hidden
+// layers, whose inputs are written by the launch itself), over the boundaries of unit and row tiles.
 //
-// What bounds it: the MFMA issue (three products per weight and row; without any loads the launch below takes 630 us), then the
-// latency of the rows' loads (740 us when the rows lie in the L2).  It replaced a loop over chunks of M x B rows, each with five
-// launches that also staged the minibatch, the weights and their differences and evaluated the reference point.
-// Measured: 784-512-10 on 384000 rows 3.48 -> 0.90 ms (0.31 TFLOP, executed threefold: 1.04 PFLOP/s);
-// small minibatches, whose chunks were small too, 10.8 ms -> 73 us.
+// What bounds it: the MFMA issue (three products per weight and row; without any loads the launch below takes 630 us, and at the 1.2 PFLOP/s
+// that real operands leave the card 790), and the rows' way from HBM: 16 rows x 64 bytes a load, half a line each, of rows that start on no line.
+// Measured: 784-512-10 on 384000 rows 3.48 ms as a loop over chunks of M x B rows, 0.90 with the loads of a step in one burst before its products and rows one step
+// ahead, now 0.83 - 0.85 (0.31 TFLOP, executed threefold); small minibatches, whose chunks were small too, 10.8 ms -> 73 us.
+// Loads in a burst at the head of a step held the wavefronts up before their first product; rows two steps ahead in such a burst gained nothing (0.88), the same loads
+// among the first products 0.84 (one by one between all groups of products 0.86).  3072-1024-1024-10 on 50000 rows 2.27 -> 1.84 ms, with the weights at the head, the rows behind the
+// first products and the wavefronts that multiply raised over those that wait (either alone 1.94, 2.12; the other way round 1.96).
 #include <cstdlib>
 
 #include "cada_mlp.h"
@@ -53,12 +56,19 @@ __device__ __forceinline__ void to_lds(const bf16_t *base, uint32_t off, uint32_
 
 // HID: hidden layers (2: two or more), or kByLayer: one hidden layer a launch (layer[0]; layer[1] is the next one), one tile of its units a workgroup
 constexpr int kByLayer = 3;
+// Stages of rows in LDS: several hidden layers in a launch have two, as a layer's input is not there before its last step.
+constexpr int eval_row_stages(int hid) { return hid == 2 ? 2 : 3; }
+// Rows x units of 256 x 256 then leave no room for the logits.
+constexpr bool eval_lends(int NR, int NU, int hid) { return eval_row_stages(hid) == 3 && NR == 4 && NU == 2; }
+constexpr int eval_lds(int NR, int NU, int hid) { return 64 * NR * 128 * (eval_row_stages(hid) + (eval_lends(NR, NU, hid) ? 0 : 1)) + 2 * 128 * NU * 128; }
 template <int NR, int NU, int HID>
 __global__ __launch_bounds__(512) void k_eval_net(const EvalArgs a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   constexpr int RT = 64 * NR, UT = 128 * NU;
-  constexpr int STAGE = (RT + UT) * 128;                    // bytes: X hi, lo [RT][32], W hi, lo [UT][32]
-  float *logit_s = reinterpret_cast<float *>(smem_raw + 2 * STAGE);      // [RT][32], class c of row r at c ^ (r % 32)
+  // LDS: XS stages of rows (hi, lo [RT][32]), two of weights (hi, lo [UT][32]), the logits [RT][32] (class c of row r at c ^ (r % 32)), unless they take the
+  // stage of weights that is free between two tiles of units
+  constexpr int XS = eval_row_stages(HID), XB = RT * 128, WB = UT * 128;
+  constexpr bool LEND = eval_lends(NR, NU, HID);
   const DevState &s = a.s;
   const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
   const int wu = w & 3, wr = w >> 2;                        // this wavefront's units and rows
@@ -83,25 +93,29 @@ __global__ __launch_bounds__(512) void k_eval_net(const EvalArgs a) {
     for (int h = 0; h < 2; ++h)
       src[h] = first ? (h ? a.Xl : a.Xh) + (int64_t)ltile * RT * sld : a.act[(ll - 1) & 1][h] + (int64_t)blockIdx.x * RT * sld;
   };
-  auto load_step = [&](int buf) __attribute__((always_inline)) {
-    const uint32_t base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem_raw + (uint32_t)buf * STAGE;
-#pragma unroll
-    for (int i = 0; i < NR; ++i) {
-      const int id = w * NR + i, lo = id >= 4 * NR, blk = id & (4 * NR - 1);
-      const bf16_t *row = (lo ? src[1] : src[0]) + (int64_t)(blk * 16) * sld + lk * 32;
-      if ((int64_t)lk * 32 + 32 > sld) {                    // rows of X end at a multiple of 8 values: zeros from there on
-        const bf16_t *g = lk * 32 + pq * 8 < (int)sld ? reinterpret_cast<const bf16_t *>(reinterpret_cast<const char *>(row) + xoff) : a.zeros;
-        to_lds(g, base + (uint32_t)id * 1024u);
-      } else {
-        to_lds(row, xoff, base + (uint32_t)id * 1024u);
-      }
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem_raw;
+  auto load_row = [&](int stage, int i) __attribute__((always_inline)) {      // the i-th of this wavefront's NR loads of the cursor's rows
+    const int id = w * NR + i, lo = id >= 4 * NR, blk = id & (4 * NR - 1);
+    const bf16_t *row = (lo ? src[1] : src[0]) + (int64_t)(blk * 16) * sld + lk * 32;
+    const uint32_t to = lds0 + (uint32_t)(stage * XB + id * 1024);
+    if ((int64_t)lk * 32 + 32 > sld) {                      // rows of X end at a multiple of 8 values: zeros from there on
+      const bf16_t *g = lk * 32 + pq * 8 < (int)sld ? reinterpret_cast<const bf16_t *>(reinterpret_cast<const char *>(row) + xoff) : a.zeros;
+      to_lds(g, to);
+    } else {
+      to_lds(row, xoff, to);
     }
+  };
+  auto load_rows = [&](int stage) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < NR; ++i) load_row(stage, i);
+  };
+  auto load_weights = [&](int stage) __attribute__((always_inline)) {
     const int last = (le.N + 127) / 128 - 1;
 #pragma unroll
     for (int i = 0; i < 2 * NU; ++i) {
       const int id = w * 2 * NU + i, lo = id >= 8 * NU, blk = id & (8 * NU - 1);
       const int ut = min(lct * NU + (blk >> 3), last);      // (units past the last tile: any finite values)
-      to_lds((lo ? le.Wl : le.Wh) + (((int64_t)ut * le.kt + lk) << 12) + ((blk & 7) << 9), (uint32_t)piece * 16u, base + (uint32_t)(RT * 128 + id * 1024));
+      to_lds((lo ? le.Wl : le.Wh) + (((int64_t)ut * le.kt + lk) << 12) + ((blk & 7) << 9), (uint32_t)piece * 16u, lds0 + (uint32_t)(XS * XB + stage * WB + id * 1024));
     }
   };
   // next step; returns false where it is the first of a layer whose input is still being formed, or past the end
@@ -122,16 +136,33 @@ __global__ __launch_bounds__(512) void k_eval_net(const EvalArgs a) {
     set_source();
     return true;
   };
-  auto landed = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+  // everything has landed, or (rows of the step after the next are on their way) everything but the newest NR loads
+  auto landed = [&](bool rows_behind) __attribute__((always_inline)) {
+    if (rows_behind) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(NR) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  };
 
   if (ltile >= ntiles) return;
   bool done = false;
-  int buf = 0;
+  int xs = 0, ws = 0;                                       // stages of the step that is worked on
   set_source();
-  load_step(0);
-  landed();
+  load_rows(0);
+  load_weights(0);
+  bool next = true;                                         // XS == 3: the cursor stands at the next step (whose rows have been asked for)
+  if constexpr (XS == 3) {
+    next = advance(done);
+    if (next) load_rows(1);
+    landed(next);
+  } else {
+    landed(false);
+  }
   for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     const int64_t r0 = (int64_t)tile * RT;
+    float *logit_s = reinterpret_cast<float *>(smem_raw + XS * XB + 2 * WB);
+    constexpr int NSUM = LEND ? RT * 32 / 512 : 1;
+    float sums[NSUM];                                       // LEND: the logits between tiles of units, 512 threads apart
+#pragma unroll
+    for (int i = 0; i < NSUM; ++i) sums[i] = 0.f;
     for (int l = 0; l < nhid; ++l) {
       const EvalLayer e = a.layer[l];
       const int u1 = HID == kByLayer ? (int)blockIdx.y * UT : 0, u2 = HID == kByLayer ? u1 + 1 : e.N;
@@ -145,13 +176,17 @@ __global__ __launch_bounds__(512) void k_eval_net(const EvalArgs a) {
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
         bool ready = true;
         for (int k = 0; k < e.nk; ++k) {
-          ready = advance(done);
-          if (ready) load_step(buf ^ 1);
-          const bf16_t *st = reinterpret_cast<const bf16_t *>(smem_raw + buf * STAGE);
-          const bf16_t *sx = st + (wr * 32 * NR) * 32, *sw = st + RT * 64 + (wu * 32 * NU) * 32;
+          const int xn = xs + XS - 1 >= XS ? xs - 1 : xs + XS - 1;      // the stage of the rows that are asked for in this step
+          if constexpr (XS != 3) {
+            ready = advance(done);
+            if (ready) load_weights(ws ^ 1);
+          }
+          const bf16_t *sx = reinterpret_cast<const bf16_t *>(smem_raw + xs * XB) + (wr * 32 * NR) * 32;
+          const bf16_t *sw = reinterpret_cast<const bf16_t *>(smem_raw + XS * XB + ws * WB) + (wu * 32 * NU) * 32;
           const int fro = lds_piece(l32 * 4 + half) * 8;
 #pragma unroll
           for (int ks = 0; ks < 32; ks += 16) {
+            if constexpr (XS != 3) __builtin_amdgcn_s_setprio(1);
             bf16x8 wh[NU], wl[NU], xh[NR], xl[NR];
 #pragma unroll
             for (int j = 0; j < NR; ++j) {
@@ -164,15 +199,28 @@ __global__ __launch_bounds__(512) void k_eval_net(const EvalArgs a) {
               wl[i] = *reinterpret_cast<const bf16x8 *>(sw + UT * 32 + i * 1024 + (fro ^ ks));
             }
 #pragma unroll
-            for (int q = 0; q < 3; ++q)
+            for (int q = 0; q < 3; ++q) {
+              if (ks == 0 && q >= 1) {
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (XS == 3) {
+                  if (q == 1 && next) { load_weights(ws ^ 1); next = advance(done); }
+                  if (q == 2 && next) load_rows(xn);
+                } else if (ready) {
+                  if (q == 1) load_rows(xn);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+              }
 #pragma unroll
               for (int i = 0; i < NU; ++i)
 #pragma unroll
                 for (int j = 0; j < NR; ++j)
                   acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q == 1 ? wl[i] : wh[i], q == 0 ? xl[j] : xh[j], acc[i][j], 0, 0, 0);
+            }
           }
-          landed();
-          buf ^= 1;
+          if constexpr (XS != 3) __builtin_amdgcn_s_setprio(0);
+          landed(XS == 3 && next);
+          xs = xs + 1 == XS ? 0 : xs + 1;
+          ws ^= 1;
         }
         // accumulator element r of (i, j): unit ub + 32 i + 8 (r / 4) + r % 4, row 32 NR wr + 32 j + lane % 32
         const int ub = u0 + wu * 32 * NU + 4 * half;
@@ -269,7 +317,8 @@ __global__ __launch_bounds__(512) void k_eval_net(const EvalArgs a) {
               }
             }
             // added up over the four wavefronts of the same rows, one after the other
-            if (u0 == u1) {
+            if constexpr (LEND) logit_s = reinterpret_cast<float *>(smem_raw + XS * XB + (ws ^ 1) * WB);      // (the weights of the step that has just been worked on)
+            if (LEND || u0 == u1) {
               for (int i = t; i < RT * 32; i += 512) logit_s[i] = 0.f;
               lds_sync();
             }
@@ -284,12 +333,22 @@ __global__ __launch_bounds__(512) void k_eval_net(const EvalArgs a) {
               }
               lds_sync();
             }
+            if constexpr (LEND) {
+#pragma unroll
+              for (int i = 0; i < NSUM; ++i) sums[i] += logit_s[t + 512 * i];
+              if (u0 + UT >= u2) {
+#pragma unroll
+                for (int i = 0; i < NSUM; ++i) logit_s[t + 512 * i] = sums[i];
+              }
+              lds_sync();
+            }
           }
         }
         if (HID == 2 && !ready && !done) {       // the next layer reads what this one has just written
-          landed();
-          load_step(buf);
-          landed();
+          landed(false);
+          load_rows(xs);
+          load_weights(ws);
+          landed(false);
         }
       }
     }
@@ -312,7 +371,8 @@ __global__ __launch_bounds__(512) void k_eval_net(const EvalArgs a) {
       for (int c = 0; c < a.C; ++c) den += expf(z(c) - zmax);
       a.rowval[r] = make_float2(zmax + logf(den) - zl, arg == label ? 1.f : 0.f);
     }
-    // (the next write of the logits is a barrier away)
+    if constexpr (LEND) lds_sync();                         // (the next tile's first step loads weights to where they lie)
+    // (else the next write of the logits is a barrier away)
   }
 }
 
@@ -356,7 +416,6 @@ __global__ __launch_bounds__(1024) void k_eval_sums(const DevState s, const floa
 namespace {
 using EvalKernel = void (*)(const EvalArgs);
 constexpr int kEvalGroups = 256;        // workgroups of a launch (one per CU) at most
-constexpr int eval_lds(int NR, int NU) { return 2 * (64 * NR + 128 * NU) * 128 + 64 * NR * 128; }
 template <int NU, int HID> EvalKernel eval_kernel_of(int NR) { return NR == 4 ? k_eval_net<4, NU, HID> : NR == 2 ? k_eval_net<2, NU, HID> : k_eval_net<1, NU, HID>; }
 struct EvalPlan {
   int nr, nu;                // rows (64 nr) and units (128 nu) of a tile
@@ -372,6 +431,8 @@ EvalKernel eval_kernel(const EvalPlan &e, int L) {
   if (e.nu == 2) return e.nr == 2 ? k_eval_net<2, 2, 2> : k_eval_net<1, 2, 2>;
   return eval_kernel_of<1, 2>(e.nr);
 }
+
+int eval_hid(const EvalPlan &e, int L) { return e.by_layer ? kByLayer : min(L - 1, 2); }
 
 int64_t eval_row_tiles(const MlpPlan &P, int nr) { return (P.total_rows + 64 * nr - 1) / (64 * nr); }
 int eval_unit_tiles(const MlpPlan &P, int l, int nu) { return (int)((P.d[l] + 128 * nu - 1) / (128 * nu)); }
@@ -432,7 +493,7 @@ size_t mlp_eval_bytes(const MlpPlan &P) {
 int mlp_eval_init(Ctx *c) {
   const MlpPlan &P = *static_cast<MlpPlan *>(c->mlp);
   const EvalPlan p = eval_plan(P);
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(eval_kernel(p, P.L)), hipFuncAttributeMaxDynamicSharedMemorySize, eval_lds(p.nr, p.nu));
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(eval_kernel(p, P.L)), hipFuncAttributeMaxDynamicSharedMemorySize, eval_lds(p.nr, p.nu, eval_hid(p, P.L)));
   if (e != hipSuccess) { set_error("hipFuncSetAttribute(LDS size) failed: %s", hipGetErrorString(e)); return CADA_EHIP; }
   return CADA_OK;
 }
@@ -458,7 +519,7 @@ int mlp_eval(Ctx *c, double *out) {
   bf16_t *act = reinterpret_cast<bf16_t *>(P.eval + eval_rowval_bytes(P));
   for (int i = 0; i < 4; ++i) a.act[i >> 1][i & 1] = act + (P.L > 3 ? i : (i & 1)) * n;
   const EvalKernel kernel = eval_kernel(p, P.L);
-  const size_t lds = eval_lds(p.nr, p.nu);
+  const size_t lds = eval_lds(p.nr, p.nu, eval_hid(p, P.L));
   mlp_stage_weights(c);
   if (p.by_layer) {
     EvalArgs b = a;
