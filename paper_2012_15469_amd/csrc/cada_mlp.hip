@@ -53,9 +53,9 @@ namespace cada {
 
 enum { EPI_FWD_HIDDEN = 0, EPI_DW = 2, EPI_DA = 3, EPI_LOSS = 4 };
 
-// k_mm5's LDS: a ring of 8 KB slots, one chunk each.
-constexpr int kMm5Slots = 20;
-constexpr size_t kMm5Lds = (size_t)kMm5Slots * TILE * sizeof(bf16_t);      // 160 KB
+// k_mm5's LDS: a ring of 8 KB slots (one chunk each); behind it 8 KB per multiplying wavefront for the bf16 tensors on their way out.
+constexpr int kMm5Slots = 15;
+constexpr size_t kMm5Lds = (size_t)kMm5Slots * TILE * sizeof(bf16_t) + 4 * 8192;
 
 // Division of 0 <= x < 2^31 by a divisor that the host knows: a product and a shift (as a division it takes the compiler some forty
 // instructions, and a tile's three indices two of them, each time at the head of a launch that may have one tile per workgroup).
@@ -149,20 +149,20 @@ __device__ __forceinline__ u32x4 pack8(const bf16_t (&v)[8]) {
 // gradients read in this epilogue made it 12 us longer for the 10 us of that launch, and the server found nothing in the
 // caches, 7 -> 11 us; 617-301-150-26, 24 workers.)
 //
-// A workgroup of eight wavefronts has a CU and works through several 128 x 128 tiles.  Wavefronts w and w + 4 hold the same 64 x 64 part of the tile, one
-// for the first and one for the second 16 contraction indices of every step of 32, and add up at the end; each then has 32 of the part's rows to
-// write out.  So every SIMD has two wavefronts whose products and LDS reads overlap, and eight share the way out.  (Before, four
-// wavefronts moved the operands and four multiplied: a step of 1024 cycles of products took 1900, and the way out 19 k cycles on four wavefronts.)
-//
-// LDS is a ring of 20 slots of 8 KB, one chunk each, filled tensor by tensor in the order the steps read them, with LDS-direct loads (no registers, no
-// second pass through the LDS write port), one kilobyte of each chunk per wavefront.  A step's fragments are read during the step before, each right after
-// its register's last use; its slots are therefore free at its own barrier, and their refills go out one by one between its products (in a
-// burst after the barrier they held the wavefronts up: 1560 cycles per step against 1142 in a loop that does nothing else).  The barrier stands
-// behind the step's first four products, which cover the wait for the last fragments.
-//
-// What bounds it: forward product of layer 1, 3072-1024-1024-10, 16 workers of 256 rows, 96 steps: 1430 cycles per step at 1.54 - 1.7 GHz, the clock that
-// the power of the products leaves; that is 1.2 PFLOP/s executed, what a library product of 8192^3 reaches on this card (1.2 - 1.3).  Beside the loop a tile
-// takes 5 - 7 k cycles until its first step has landed and 13 k for the way out.
+// A workgroup has eight wavefronts in two roles and works through several tiles.  Wavefronts 4-7
+// move chunks from global memory straight into LDS (16-byte LDS-direct loads: no registers, no
+// second pass through the LDS write port); wavefronts 0-3 read fragments, issue MFMAs and run the
+// epilogue of each tile.  LDS is a ring of 8 KB slots, one chunk each, filled tensor by tensor in
+// the order the tile steps read them, across tile boundaries: while the multipliers write one
+// tile out, the first steps of the next are already landing.  One barrier per tile step: it
+// tells the multipliers that the step has landed, and the movers that the slots of the step before
+// are free (NS more loads may go out).  The epilogues use no workgroup barrier, so both roles
+// execute the same number of them.  (With four wavefronts doing load, LDS write and multiply in
+// turn, the three phases of a step, each near 1000 cycles, ran one after the other.)
+// (All eight wavefronts moving and multiplying, the contraction split in two halves of every step that are added up through LDS at the end, with the
+// fragments read a step ahead: 1430 instead of 1900 cycles per step, but at 1.54 GHz, what the products' power leaves, in place of 2: 3072-1024-1024-10 within 1 %,
+// 512-1024-1024-10 with 64 workers 2 % faster, 300-700-10 with 100 workers, several tiles per workgroup, 2 % slower.  And sums in another order move single units across zero
+// a few steps later.  Not kept.)
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 
 // Fragment of a transposed operand: 8 consecutive rows (k) of unit (lane % 32) from a [32 rows][32 units]
@@ -182,15 +182,17 @@ __device__ __forceinline__ void mm_load(const bf16_t *base, uint32_t byte_off, u
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(byte_off), "s"(base), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory", "m0");
 }
 template <int EPI, int NA, int NB, bool HAS_D>
-__global__ __launch_bounds__(2 * kBlock, 2) void k_mm5(const Mm5Args g) {
+__global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  constexpr int NS = NA + NB, NSLOT = kMm5Slots, AHEAD = NSLOT / NS, R0 = NSLOT % NS;
-  constexpr bool PL = NB == 2;
+  bf16_t *lds = reinterpret_cast<bf16_t *>(smem_raw);
+  constexpr int NS = NA + NB, NSLOT = kMm5Slots;
   static_assert(EPI == EPI_FWD_HIDDEN || EPI == EPI_DA, "");
-  static_assert((NA == 2 && !HAS_D) || (NA == 4 && NB == 3 && HAS_D), "hi, lo [, difference, reference] against hi, lo [, difference]");
+  constexpr bool PL = NB == 2;
+  static_assert(NSLOT >= 2 * NS, "the ring must hold two tile steps");
   const DevState &s = g.s;
-  const int lane = threadIdx.x & 63, w8 = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int kh = w8 >> 2, w = w8 & 3, wy = w >> 1, wx = w & 1;
+  const bool mover = __builtin_amdgcn_readfirstlane((int)threadIdx.x) >= kBlock;   // uniform per wavefront
+  const int t = threadIdx.x & (kBlock - 1), lane = t & 63, w = t >> 6;
+  const int wy = w >> 1, wx = w & 1;
   // Tiles of this workgroup.  Workgroups are dealt to the 8 XCDs (each with an L2 of its own) in
   // turn; XCD x takes the x-th eighth of the tiles (columns fastest, then rows, then workers), its
   // workgroups every nbx-th of those: an XCD's L2 then sees whole workers, or a few row tiles of
@@ -199,172 +201,148 @@ __global__ __launch_bounds__(2 * kBlock, 2) void k_mm5(const Mm5Args g) {
   const int total = gx * gy * g.workers, per = (total + 7) / 8;
   const int nbx = g.nbx.d;
   const int t_first = (blockIdx.x & 7) * per + (blockIdx.x >> 3), t_end = min(((int)(blockIdx.x & 7) + 1) * per, total);
+  if (t_first >= t_end) return;
+  const int nt = quotient(t_end - t_first + nbx - 1, g.nbx);
   const int nk = (g.K + BK - 1) / BK;
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem_raw;
-  const uint32_t goff = lds_piece(w8 * 64 + lane) * 16;        // the piece that the LDS order puts at this lane's place (the order is its own inverse)
-  // fragment of this lane inside a 32-row band: row lane % 32, piece lane / 32 (+ 2 in the second half step)
-  const uint32_t fro = (lds_piece((lane & 31) * 4 + (lane >> 5)) * 16) ^ (kh * 32);
+  const int nsteps = nt * nk;
 
-  for (int tix = t_first; tix < t_end; tix += nbx) {
-    const int trow = quotient(tix, g.gx), bx = tix - trow * gx, wk = quotient(trow, g.gy), by = trow - wk * gy;     // wk: worker
-    const int m0 = by * BM, n0 = bx * BN;
-    const bf16_t *src[NS];
-    {
-      const int wkb = g.rep ? g.rep[wk] : wk;
+  if (mover) {
+    // Instruction c of wavefront w fills the 64 pieces from position 64 (2 w + c) on of a slot;
+    // the lane at position P fetches the piece that the LDS order puts there.
+    const int lw = __builtin_amdgcn_readfirstlane(w);
+    int goff[2];
 #pragma unroll
-      for (int q = 0; q < NA; ++q) src[q] = g.A.ptr[q] + (int64_t)wk * g.A.bstride[q] + (((int64_t)by * g.A.kt[q]) << 12);
-#pragma unroll
-      for (int q = 0; q < NB; ++q) src[NA + q] = g.B.ptr[q] + (int64_t)wkb * g.B.bstride[q] + (((int64_t)bx * g.B.kt[q]) << 12);
+    for (int c = 0; c < 2; ++c) {
+      goff[c] = lds_piece((2 * lw + c) * 64 + lane) * 8;          // (the order is its own inverse)
     }
-    int in_slot = 0;
-    auto load = [&](int q, int step) __attribute__((always_inline)) {       // tensor q of a step into the next slot (nothing past the last step)
-      if (step < nk) {
-        mm_load(src[q] + ((int64_t)step << 12), goff, lds0 + in_slot * 8192 + w8 * 1024);
-        in_slot = in_slot + 1 == NSLOT ? 0 : in_slot + 1;
-      }
+    // issue cursor: tile ordinal, step in the tile, first chunk of the tile's rows in every tensor, ring slot
+    int ord = 0, h = 0, slot = 0;
+    const bf16_t *pa[NA], *pb[NB];
+    auto set_tile = [&](int o) __attribute__((always_inline)) {
+      const int tix = t_first + o * nbx;
+      const int trow = quotient(tix, g.gx), bx = tix - trow * gx, bz = quotient(trow, g.gy), by = trow - bz * gy;
+#pragma unroll
+      for (int sl = 0; sl < NA; ++sl) pa[sl] = g.A.ptr[sl] + (int64_t)bz * g.A.bstride[sl] + (((int64_t)by * g.A.kt[sl]) << 12);
+      const int bzb = g.rep ? g.rep[bz] : bz;
+#pragma unroll
+      for (int sl = 0; sl < NB; ++sl) pb[sl] = g.B.ptr[sl] + (int64_t)bzb * g.B.bstride[sl] + (((int64_t)bx * g.B.kt[sl]) << 12);
     };
-#pragma unroll 1
-    for (int p = 0; p < AHEAD; ++p) {
+    // next tile step; past the last one the cursor stays (those loads re-read the last chunk into slots nobody reads)
+    auto next_step = [&]() __attribute__((always_inline)) {
+      if (h + 1 < nk) ++h;
+      else if (ord + 1 < nt) { ++ord; h = 0; set_tile(ord); }
+    };
+    auto load = [&](int sl) __attribute__((always_inline)) {
+      const bf16_t *src = sl < NA ? pa[sl < NA ? sl : 0] : pb[sl < NA ? 0 : sl - NA];
+      src += (int64_t)h << 12;
+      bf16_t *dst = lds + ((size_t)slot << 12) + (2 * lw << 9);
 #pragma unroll
-      for (int q = 0; q < NS; ++q) load(q, p);
+      for (int c = 0; c < 2; ++c)
+        __builtin_amdgcn_global_load_lds(src + goff[c], (__attribute__((address_space(3))) void *)(dst + (c << 9)), 16, 0, 0);
+      slot = slot + 1 == NSLOT ? 0 : slot + 1;
+    };
+    set_tile(0);
+#pragma unroll
+    for (int q = 0; q < NSLOT; ++q) {          // fill the ring
+      if (q % NS == 0 && q > 0) next_step();
+      load(q % NS);
     }
+    // Barrier m: step m has landed when at most the NSLOT - 2 NS tensors issued after it are
+    // outstanding (two instructions each); then the NS slots of step m - 1 are free.
+    for (int m = 0; m < nsteps; ++m) {
+      asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"(2 * (NSLOT - 2 * NS)) : "memory");
+      if (m > 0) {
 #pragma unroll
-    for (int q = 0; q < R0; ++q) load(q, AHEAD);
-    if (nk >= AHEAD) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((AHEAD - 1) * NS) : "memory");
-    else asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+        for (int i = 0; i < NS; ++i) {
+          constexpr int r0 = NSLOT % NS;
+          if ((r0 + i) % NS == 0) next_step();
+          load((r0 + i) % NS);
+        }
+      }
+    }
+    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");     // nothing may land after the workgroup has gone
+    return;
+  }
 
-    // ReLU masks: one bit per accumulator element, set where the activation is positive (at theta,
-    // at the reference point).  The forward contraction of a layer and the activation-gradient
-    // contraction into it have the same tiles and the same element-to-lane map, so the forward
-    // epilogue leaves each lane's bits where the backward one finds them: per tile and lane of four wavefronts of 64 x 64
-    // two 64-bit words (theta, reference point), bit (i * 2 + j) * 16 + r; this wavefront has the 32 bits of i = kh.
-    uint32_t bit_on = 0, bit_ref = 0;
-    uint32_t *mbits = reinterpret_cast<uint32_t *>(g.maskbits + ((((int64_t)wk * gy + by) * gx + bx) * kBlock + w * 64 + lane) * 2);
-    if constexpr (EPI == EPI_DA) { bit_on = mbits[kh]; bit_ref = mbits[2 + kh]; }
-    // (asked for here, used in the epilogue: a chain of tau_m -> reference point -> four loads)
-    float b_th[2], b_tl[2], b_rh[2], b_rl[2];
-    if constexpr (EPI == EPI_FWD_HIDDEN) {
-      const RefPtr ref = theta_ref(s, wk, s.k);
+  // fragment of this lane inside a 32-row band: row lane % 32, piece lane / 32 (+ 2 in the second half step)
+  const int fro = lds_piece((lane & 31) * 4 + (lane >> 5)) * 8;
+  int sb = 0;                                  // ring slot of the current step's first tensor
+  for (int ord = 0; ord < nt; ++ord) {
+  const int tix = t_first + ord * nbx;
+  const int trow = quotient(tix, g.gx), bx = tix - trow * gx, wk = quotient(trow, g.gy), by = trow - wk * gy;     // wk: worker
+  const int m0 = by * BM, n0 = bx * BN;
+
+  f32x16 acc1[2][2], acc2[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) { acc1[i][j][r] = 0.f; acc2[i][j][r] = 0.f; }
+
+  for (int h = 0; h < nk; ++h) {
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    auto slot_of = [&](int idx) __attribute__((always_inline)) { const int p = sb + idx; return lds + ((size_t)(p >= NSLOT ? p - NSLOT : p) << 12); };
+    const bf16_t *tah = slot_of(g.a_h), *tal = slot_of(g.a_l), *tad = slot_of(HAS_D ? g.a_d : 0), *tar = slot_of(NA == 4 ? g.a_r : 0);
+    const bf16_t *tbh = slot_of(NA + g.b_h), *tbl = slot_of(NA + g.b_l), *tbx = slot_of(NA + (HAS_D && NB == 4 ? g.b_x : 0)), *tbd = slot_of(PL ? NA : NA + g.b_d);
+#pragma unroll
+    for (int ks = 0; ks < BK; ks += 16) {
+      bf16x8 ah[2], al[2], ad[2], ar[2], bh[2], bl[2], bx_[2], bd[2];
+      auto frag = [&](const bf16_t *slot, int half, int blk) __attribute__((always_inline)) -> bf16x8 {
+        return *reinterpret_cast<const bf16x8 *>(slot + (half * 64 + blk * 32) * BK + (fro ^ ks));
+      };
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        ah[i] = frag(tah, wy, i);
+        al[i] = frag(tal, wy, i);
+        if constexpr (HAS_D) ad[i] = frag(tad, wy, i);
+        // with fewer than four A tensors the reference operand is the hi part itself
+        if constexpr (NA == 4) ar[i] = frag(tar, wy, i);
+        else ar[i] = ah[i];
+      }
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
-        const int64_t o = g.offb + min(n0 + wx * 64 + j * 32 + (lane & 31), g.N - 1);
-        b_th[j] = s.theta[o];
-        if constexpr (!PL) { b_tl[j] = s.theta_lo[o]; b_rh[j] = ref.hi[o]; b_rl[j] = ref.lo[o]; }
-      }
-    }
-
-    f32x16 acc1[2][2], acc2[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) { acc1[i][j][r] = 0.f; acc2[i][j][r] = 0.f; }
-    int sb = 0;                                  // ring slot of the first tensor of the step whose fragments are read next
-    auto frag = [&](int q, int half, int blk) __attribute__((always_inline)) -> bf16x8 {
-      const int p = sb + q;
-      return *reinterpret_cast<const bf16x8 *>(smem_raw + (p >= NSLOT ? p - NSLOT : p) * 8192 + half * 4096 + blk * 2048 + fro);
-    };
-    bf16x8 ah[2], al[2], ad[2], ar[2], bh[2], bl[2], bd[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      al[i] = frag(1, wy, i); bh[i] = frag(NA, wx, i); ah[i] = frag(0, wy, i); bl[i] = frag(NA + 1, wx, i);
-      if constexpr (HAS_D) { ad[i] = frag(2, wy, i); ar[i] = frag(3, wy, i); }
-      if constexpr (!PL) bd[i] = frag(NS - 1, wx, i);
-    }
-    for (int h = 0; h < nk; ++h) {
-      sb = sb + NS >= NSLOT ? sb + NS - NSLOT : sb + NS;
-#define MM(a, b, c) c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0)
-#define KEEP() __builtin_amdgcn_sched_barrier(0)
-      MM(al[0], bh[0], acc1[0][0]); MM(al[0], bh[1], acc1[0][1]); MM(al[1], bh[0], acc1[1][0]); MM(al[1], bh[1], acc1[1][1]);
-      KEEP();
-      {   // step h + 1 has landed (everything but what was asked for after it); every wavefront has step h's fragments in registers
-        const int later = nk - h - 2;
-        if (later * NS >= NSLOT - 2 * NS) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(NSLOT - 2 * NS) : "memory");
-        else if (NS * 2 < NSLOT - 2 * NS && later == 2) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * NS) : "memory");
-        else if (later == 1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(NS) : "memory");
-        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-      }
-      auto more = [&](int i) __attribute__((always_inline)) { if (i < NS) load((R0 + i) % NS, h + AHEAD + (R0 + i >= NS ? 1 : 0)); };
-      __builtin_amdgcn_s_setprio(1);
-      al[0] = frag(1, wy, 0); al[1] = frag(1, wy, 1); KEEP();
-      MM(ah[0], bl[0], acc1[0][0]); MM(ah[1], bl[0], acc1[1][0]); KEEP(); bl[0] = frag(NA + 1, wx, 0); more(0); KEEP();
-      MM(ah[0], bl[1], acc1[0][1]); MM(ah[1], bl[1], acc1[1][1]); KEEP(); bl[1] = frag(NA + 1, wx, 1); more(1); KEEP();
-      if constexpr (HAS_D) {
-        MM(ah[0], bh[0], acc1[0][0]); MM(ah[0], bh[1], acc1[0][1]); KEEP(); ah[0] = frag(0, wy, 0); more(2); KEEP();
-        MM(ah[1], bh[0], acc1[1][0]); MM(ah[1], bh[1], acc1[1][1]); KEEP(); ah[1] = frag(0, wy, 1); more(3); KEEP();
-        MM(ad[0], bh[0], acc2[0][0]); MM(ad[1], bh[0], acc2[1][0]); KEEP(); bh[0] = frag(NA, wx, 0); more(4); KEEP();
-        MM(ad[0], bh[1], acc2[0][1]); MM(ad[1], bh[1], acc2[1][1]); KEEP(); bh[1] = frag(NA, wx, 1); ad[0] = frag(2, wy, 0); more(5); KEEP();
-        MM(ar[0], bd[0], acc2[0][0]); MM(ar[0], bd[1], acc2[0][1]); KEEP(); ad[1] = frag(2, wy, 1); ar[0] = frag(3, wy, 0); more(6); KEEP();
-        MM(ar[1], bd[0], acc2[1][0]); MM(ar[1], bd[1], acc2[1][1]); KEEP(); ar[1] = frag(3, wy, 1); bd[0] = frag(NS - 1, wx, 0); bd[1] = frag(NS - 1, wx, 1); KEEP();
-      } else if constexpr (!PL) {      // (the reference operand is the hi part itself)
-        MM(ah[0], bh[0], acc1[0][0]); MM(ah[1], bh[0], acc1[1][0]); KEEP(); bh[0] = frag(NA, wx, 0); more(2); KEEP();
-        MM(ah[0], bh[1], acc1[0][1]); MM(ah[1], bh[1], acc1[1][1]); KEEP(); bh[1] = frag(NA, wx, 1); more(3); KEEP();
-        MM(ah[0], bd[0], acc2[0][0]); MM(ah[0], bd[1], acc2[0][1]); KEEP(); ah[0] = frag(0, wy, 0); more(4); KEEP();
-        MM(ah[1], bd[0], acc2[1][0]); MM(ah[1], bd[1], acc2[1][1]); KEEP(); ah[1] = frag(0, wy, 1); bd[0] = frag(NS - 1, wx, 0); bd[1] = frag(NS - 1, wx, 1); KEEP();
-      } else {
-        MM(ah[0], bh[0], acc1[0][0]); MM(ah[0], bh[1], acc1[0][1]); KEEP(); ah[0] = frag(0, wy, 0); more(2); KEEP();
-        MM(ah[1], bh[0], acc1[1][0]); MM(ah[1], bh[1], acc1[1][1]); KEEP(); ah[1] = frag(0, wy, 1); bh[0] = frag(NA, wx, 0); bh[1] = frag(NA, wx, 1); more(3); KEEP();
-      }
-      __builtin_amdgcn_s_setprio(0);
-    }
-    // The two halves of the contraction: wavefronts w and w + 4 hold partial sums of the same 64 x 64 part.  Each takes 32 of its rows, and
-    // passes its sums of the other 32 through LDS (the ring is done with: every load has landed, every fragment has been read).
-    f32x16 c1[2], c2[2];
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    {
-      v4s *mine = reinterpret_cast<v4s *>(smem_raw) + w8 * 1024 + lane, *theirs = reinterpret_cast<v4s *>(smem_raw) + (w8 ^ 4) * 1024 + lane;
-      auto give = [&](const f32x16 (&p1)[2], const f32x16 (&p2)[2]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            mine[(j * 4 + q) * 64] = v4s{p1[j][4 * q], p1[j][4 * q + 1], p1[j][4 * q + 2], p1[j][4 * q + 3]};
-            if constexpr (!PL) mine[(8 + j * 4 + q) * 64] = v4s{p2[j][4 * q], p2[j][4 * q + 1], p2[j][4 * q + 2], p2[j][4 * q + 3]};
-          }
-      };
-      if (kh == 0) {
-        give(acc1[1], acc2[1]);
-#pragma unroll
-        for (int j = 0; j < 2; ++j) { c1[j] = acc1[0][j]; c2[j] = acc2[0][j]; }
-      } else {
-        give(acc1[0], acc2[0]);
-#pragma unroll
-        for (int j = 0; j < 2; ++j) { c1[j] = acc1[1][j]; c2[j] = acc2[1][j]; }
-      }
-      lds_sync();
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const v4s x = theirs[(j * 4 + q) * 64];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) c1[j][4 * q + e] += x[e];
-          if constexpr (!PL) {
-            const v4s y = theirs[(8 + j * 4 + q) * 64];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) c2[j][4 * q + e] += y[e];
-          }
+        bh[j] = frag(tbh, wx, j);
+        bl[j] = frag(tbl, wx, j);
+        // with fewer than four B tensors the single-bf16 operand is the hi part itself
+        if constexpr (HAS_D) {
+          if constexpr (NB == 4) bx_[j] = frag(tbx, wx, j);
+          else bx_[j] = bh[j];
         }
-      lds_sync();                                // (the buffers below lie over the sums)
+        if constexpr (!PL) bd[j] = frag(tbd, wx, j);
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          acc1[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[i], bh[j], acc1[i][j], 0, 0, 0);
+          acc1[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[i], bl[j], acc1[i][j], 0, 0, 0);
+          acc1[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[i], bh[j], acc1[i][j], 0, 0, 0);
+          if constexpr (HAS_D) acc2[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ad[i], bx_[j], acc2[i][j], 0, 0, 0);
+          if constexpr (!PL) acc2[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ar[i], bd[j], acc2[i][j], 0, 0, 0);
+        }
     }
+    sb = sb + NS >= NSLOT ? sb + NS - NSLOT : sb + NS;
+  }
 
-    // element (j, r) of the sums is output (row, col): row = m0 + wy*64 + kh*32 + 8*(r>>2) + 4*(lane>>5) + (r&3),  col = n0 + wx*64 + j*32 + (lane&31)
-    const int rbase = m0 + wy * 64 + kh * 32 + 4 * (lane >> 5);
-    const int cbase = n0 + wx * 64 + (lane & 31);
-    const int64_t rp0 = (int64_t)wk * g.Bp;            // first padded row of this worker
+  // accumulator element (i, j, r) is output (row, col):
+  //   row = m0 + wy*64 + i*32 + 8*(r>>2) + 4*(lane>>5) + (r&3),  col = n0 + wx*64 + j*32 + (lane&31)
+  const int rbase = m0 + wy * 64 + 4 * (lane >> 5);
+  const int cbase = n0 + wx * 64 + (lane & 31);
+  const int64_t rp0 = (int64_t)wk * g.Bp;            // first padded row of this worker
+  {
     // Forward: bias, ReLU of both evaluations.  Activation gradient: ReLU masks of the layer
     // below, bias-gradient partial sums.  Both: the result split into hi/lo, its difference and
     // its reference value, each written as a (row, column) tensor.
-    // A lane's sums are one column and 16 rows of a 32 x 32 quarter: written from there
+    // A lane's accumulators are one column and 16 rows of a 32 x 32 quarter: written from there
     // every store instruction would move 2 bytes per lane (some 300 instructions per wavefront and
     // tile; the CU's address unit then needs longer for them than the whole contraction took for
     // small K).  In the chunked layout a quarter is 2 KB of consecutive memory, so each wavefront puts
     // the quarter's values into an LDS buffer of its own in the layout of the destination and
     // copies it out 16 bytes per lane.  (LDS operations of one wavefront are carried out in
     // order, so the buffer needs no barrier.)
-    bf16_t *sg = reinterpret_cast<bf16_t *>(smem_raw) + w8 * 4096;   // 4 x 2 KB
-    const int wr0 = m0 + wy * 64 + kh * 32, wc0 = n0 + wx * 64;       // first row and column of this wavefront's 32 x 64 part
+    bf16_t *sg = reinterpret_cast<bf16_t *>(smem_raw + (size_t)NSLOT * TILE * sizeof(bf16_t)) + w * 4096;   // 4 x 2 KB
+    const int wr0 = m0 + wy * 64, wc0 = n0 + wx * 64;       // first row and column of this wavefront's 64 x 64 part
     bf16_t *const orow_t[4] = {g.o_h, g.o_l, g.o_d, g.o_r};
     auto copy_out = [&](bf16_t *const (&dst)[4], int64_t goff) __attribute__((always_inline)) {
       asm volatile("" ::: "memory");
@@ -380,85 +358,100 @@ __global__ __launch_bounds__(2 * kBlock, 2) void k_mm5(const Mm5Args g) {
       asm volatile("" ::: "memory");
     };
 
-    float csum[2][2];                            // EPI_DA: sums over the rows
+    // ReLU masks: one bit per accumulator element, set where the activation is positive (at theta,
+    // at the reference point).  The forward contraction of a layer and the activation-gradient
+    // contraction into it have the same tiles and the same element-to-lane map, so the forward
+    // epilogue leaves each lane's 2 x 64 bits where the backward one finds them: 16 bytes per lane.
+    uint64_t bit_on = 0, bit_ref = 0;
+    uint64_t *mbits = g.maskbits + ((((int64_t)wk * gy + by) * gx + bx) * kBlock + t) * 2;
+    if constexpr (EPI == EPI_DA) {
+      const u32x4 mb = *reinterpret_cast<const u32x4 *>(mbits);
+      bit_on = (uint64_t)mb.x | ((uint64_t)mb.y << 32);
+      bit_ref = (uint64_t)mb.z | ((uint64_t)mb.w << 32);
+    }
+
+    // (both columns' biases are asked for before either is used: one memory latency, not two)
+    float bias[2] = {0.f, 0.f}, dbias[2] = {0.f, 0.f};
+    if constexpr (EPI == EPI_FWD_HIDDEN) {
+      const RefPtr ref = theta_ref(s, wk, s.k);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int col = min(cbase + j * 32, g.N - 1);
+        bias[j] = s.theta[g.offb + col];
+        if constexpr (!PL) dbias[j] = delta_theta(s, ref, g.offb + col);
+      }
+    }
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       const int col = cbase + j * 32;
       const bool cok = col < g.N;
-      float b = 0.f, db = 0.f;
-      if constexpr (EPI == EPI_FWD_HIDDEN) {
-        b = b_th[j];
-        if constexpr (!PL) db = (b_th[j] - b_rh[j]) + (b_tl[j] - b_rl[j]);       // the same expression as delta_theta
-      }
-      float sg_sum = 0.f, sd_sum = 0.f;
-      // the quarter's four values per element, packed two rows to a register
-      uint32_t ph[8], pl[8], pd[8], pr[8];
+      const float b = bias[j], db = dbias[j];
 #pragma unroll
-      for (int rp = 0; rp < 8; ++rp) {
-        float x[2], xref[2];                      // value at theta, at the reference point; rows r, r + 1
+      for (int i = 0; i < 2; ++i) {
+        float sg_sum = 0.f, sd_sum = 0.f;
+        // the quarter's four values per element, packed two rows to a register
+        uint32_t ph[8], pl[8], pd[8], pr[8];
 #pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          const int r = 2 * rp + e;
-          const int row = rbase + 8 * (r >> 2) + (r & 3);
-          x[e] = 0.f; xref[e] = 0.f;
-          if (cok && row < g.M) {
-            if constexpr (EPI == EPI_FWD_HIDDEN) {
-              const float z = c1[j][r] + b;
-              x[e] = fmaxf(z, 0.f);
-              if constexpr (!PL) xref[e] = fmaxf(z - (c2[j][r] + db), 0.f);
-            } else {
-              const float ga = c1[j][r];
-              x[e] = (bit_on >> (j * 16 + r)) & 1 ? ga : 0.f;
-              if constexpr (!PL) xref[e] = (bit_ref >> (j * 16 + r)) & 1 ? (ga - c2[j][r]) : 0.f;
+        for (int rp = 0; rp < 8; ++rp) {
+          float x[2], xref[2];                      // value at theta, at the reference point; rows r, r + 1
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            const int r = 2 * rp + e;
+            const int row = rbase + i * 32 + 8 * (r >> 2) + (r & 3);
+            x[e] = 0.f; xref[e] = 0.f;
+            if (cok && row < g.M) {
+              if constexpr (EPI == EPI_FWD_HIDDEN) {
+                const float z = acc1[i][j][r] + b;
+                x[e] = fmaxf(z, 0.f);
+                if constexpr (!PL) xref[e] = fmaxf(z - (acc2[i][j][r] + db), 0.f);
+              } else {
+                const float ga = acc1[i][j][r];
+                x[e] = (bit_on >> ((i * 2 + j) * 16 + r)) & 1 ? ga : 0.f;
+                if constexpr (!PL) xref[e] = (bit_ref >> ((i * 2 + j) * 16 + r)) & 1 ? (ga - acc2[i][j][r]) : 0.f;
+              }
             }
+            sg_sum += x[e]; sd_sum += x[e] - xref[e];
           }
-          sg_sum += x[e]; sd_sum += x[e] - xref[e];
+          const uint32_t vh = f2bf_pk(x[0], x[1]), vr = f2bf_pk(xref[0], xref[1]);
+          ph[rp] = vh; pr[rp] = vr;
+          pl[rp] = f2bf_pk(x[0] - __uint_as_float(vh << 16), x[1] - __uint_as_float(vh & 0xffff0000u));
+          pd[rp] = f2bf_pk(x[0] - xref[0], x[1] - xref[1]);
+          if constexpr (EPI == EPI_FWD_HIDDEN) {      // (the sign of the stored, rounded value)
+            const int sh = (i * 2 + j) * 16 + 2 * rp;
+            bit_on |= (uint64_t)((__uint_as_float(vh << 16) > 0.f ? 1u : 0u) | (__uint_as_float(vh & 0xffff0000u) > 0.f ? 2u : 0u)) << sh;
+            if constexpr (!PL) bit_ref |= (uint64_t)((__uint_as_float(vr << 16) > 0.f ? 1u : 0u) | (__uint_as_float(vr & 0xffff0000u) > 0.f ? 2u : 0u)) << sh;
+          }
         }
-        const uint32_t vh = f2bf_pk(x[0], x[1]), vr = f2bf_pk(xref[0], xref[1]);
-        ph[rp] = vh; pr[rp] = vr;
-        pl[rp] = f2bf_pk(x[0] - __uint_as_float(vh << 16), x[1] - __uint_as_float(vh & 0xffff0000u));
-        pd[rp] = f2bf_pk(x[0] - xref[0], x[1] - xref[1]);
-        if constexpr (EPI == EPI_FWD_HIDDEN) {      // (the sign of the stored, rounded value)
-          const int sh = j * 16 + 2 * rp;
-          bit_on |= ((__uint_as_float(vh << 16) > 0.f ? 1u : 0u) | (__uint_as_float(vh & 0xffff0000u) > 0.f ? 2u : 0u)) << sh;
-          if constexpr (!PL) bit_ref |= ((__uint_as_float(vr << 16) > 0.f ? 1u : 0u) | (__uint_as_float(vr & 0xffff0000u) > 0.f ? 2u : 0u)) << sh;
-        }
-      }
-      // (row, column) layout: element (rl, cl) of the quarter at 32 rl + cl
-      if (g.o_h != nullptr && wc0 + j * 32 < (int)g.kto * 32) {
+        // (row, column) layout: element (rl, cl) of the quarter at 32 rl + cl
+        if (g.o_h != nullptr && wc0 + j * 32 < (int)g.kto * 32) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int e = (8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * 32 + (lane & 31), sh = 16 * (r & 1);
-          sg[e] = (bf16_t)(ph[r >> 1] >> sh); sg[1024 + e] = (bf16_t)(pl[r >> 1] >> sh);
-          if constexpr (!PL) { sg[2048 + e] = (bf16_t)(pd[r >> 1] >> sh); sg[3072 + e] = (bf16_t)(pr[r >> 1] >> sh); }
+          for (int r = 0; r < 16; ++r) {
+            const int e = (8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * 32 + (lane & 31), sh = 16 * (r & 1);
+            sg[e] = (bf16_t)(ph[r >> 1] >> sh); sg[1024 + e] = (bf16_t)(pl[r >> 1] >> sh);
+            if constexpr (!PL) { sg[2048 + e] = (bf16_t)(pd[r >> 1] >> sh); sg[3072 + e] = (bf16_t)(pr[r >> 1] >> sh); }
+          }
+          copy_out(orow_t, tm(rp0 + wr0 + i * 32, wc0 + j * 32, g.kto));
         }
-        copy_out(orow_t, tm(rp0 + wr0, wc0 + j * 32, g.kto));
-      }
-      if constexpr (EPI == EPI_DA) {
-        // the other half-wave holds the rows offset by 4: add it
-        csum[j][0] = sg_sum + __shfl_xor(sg_sum, 32, 64);
-        csum[j][1] = sd_sum + __shfl_xor(sd_sum, 32, 64);
-      }
-    }
-    if constexpr (EPI == EPI_FWD_HIDDEN) { mbits[kh] = bit_on; mbits[2 + kh] = bit_ref; }
-    if constexpr (EPI == EPI_DA) {
-      // one value per column and band of 32 rows
-      if (lane < 32) {
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const int col = cbase + j * 32;
-          if (col < g.N) {
-            const int64_t o = ((int64_t)wk * g.nband + 4 * by + 2 * wy + kh) * g.N + col;
-            g.dbpart[o] = csum[j][0];
-            if constexpr (!PL) g.ddbpart[o] = csum[j][1];
+        if constexpr (EPI == EPI_DA) {
+          // the other half-wave holds the rows offset by 4: add it, then one value per column and band of 32 rows
+          sg_sum += __shfl_xor(sg_sum, 32, 64);
+          sd_sum += __shfl_xor(sd_sum, 32, 64);
+          if (lane < 32 && cok) {
+            const int64_t o = ((int64_t)wk * g.nband + 4 * by + 2 * wy + i) * g.N + col;
+            g.dbpart[o] = sg_sum;
+            if constexpr (!PL) g.ddbpart[o] = sd_sum;
           }
         }
       }
     }
-    if (tix + nbx < t_end) lds_sync();           // the next tile's loads land where these buffers are
+    if constexpr (EPI == EPI_FWD_HIDDEN) {
+      u32x4 mb;
+      mb.x = (uint32_t)bit_on; mb.y = (uint32_t)(bit_on >> 32); mb.z = (uint32_t)bit_ref; mb.w = (uint32_t)(bit_ref >> 32);
+      *reinterpret_cast<u32x4 *>(mbits) = mb;
+    }
+  }
   }   // tiles
-#undef MM
-#undef KEEP
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");     // the movers' last barrier
 }
 
 // Weight gradient of a layer and its innovation: C1 = A^T G with split operands, C2 = A^T dG [+ dA^T Gref], summed over a worker's rows.  Both
