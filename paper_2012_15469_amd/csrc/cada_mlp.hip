@@ -542,7 +542,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_dw(const Mm5Args g) {
   // activation gradients' launch left per band of 32 rows: 64 columns from cw on, one per lane, and a partial sum of the left-hand
   // side of their own.  (A launch of its own cost 5 us.  One wavefront for 256 columns, with fewer partial sums: 784-500-10, B = 12:
   // 81.1 -> 82.8 us per step, 3072-1024-1024-10: 608 -> 615.)  A workgroup's first tile does it while its operands are on their way, a later one before
-  // its way out, when the stores of the tile before have drained.
+  // its way out, when the stores of the tile before have drained.  Bands are added in pairs: the order of sums per 64 rows.
   auto bias_part = [&](int wk, int bx) __attribute__((always_inline)) {
     const int cw = bx * BN + wx * 64;
     if (cw >= g.N) return;
@@ -551,9 +551,10 @@ __global__ __launch_bounds__(kBlock, 2) void k_dw(const Mm5Args g) {
     if (col < g.N) {
       const float *db = g.dbpart + (int64_t)wk * g.nband * g.N + col, *dd = g.ddbpart + (int64_t)wk * g.nband * g.N + col;
       float gsum = 0.f;
-      for (int i = 0; i < (g.K + 31) / 32; ++i) {
-        gsum += db[(int64_t)i * g.N];
-        if constexpr (!PL) dsum += dd[(int64_t)i * g.N];
+      for (int i = 0, n = (g.K + 31) / 32; i < n; i += 2) {
+        const int64_t at = (int64_t)i * g.N;
+        gsum += i + 1 < n ? db[at] + db[at + g.N] : db[at];
+        if constexpr (!PL) dsum += i + 1 < n ? dd[at] + dd[at + g.N] : dd[at];
       }
       put_fresh_grad(s, wk, g.offb + col, gsum);
       if (CADA1) {
@@ -1515,7 +1516,7 @@ __global__ __launch_bounds__(kBlock) void k_stage(const StageArgs a) {
   stage_weights(a, p, sm, (int)(r % p.gx), (int)(r / p.gx), (int)z, l == 0 && r == 0);
 }
 
-// Hidden-layer bias gradient and its innovation from the sums per band of 32 rows.
+// Hidden-layer bias gradient and its innovation from the sums per band of 32 rows, added in pairs as k_dw adds them.
 // grid (ceil(d / 64), M), one wavefront each
 __global__ __launch_bounds__(kWave) void k_bias_finish(const DevState s, const float *dbpart, const float *ddbpart, int nband, int bands, int d,
                                                        int64_t offb, int lhs_slot) {
@@ -1524,9 +1525,10 @@ __global__ __launch_bounds__(kWave) void k_bias_finish(const DevState s, const f
   float sq = 0.f;
   if (c < d) {
     float gsum = 0.f, dsum = 0.f;
-    for (int rb = 0; rb < bands; ++rb) {
-      gsum += dbpart[((int64_t)m * nband + rb) * d + c];
-      if (ddbpart) dsum += ddbpart[((int64_t)m * nband + rb) * d + c];
+    for (int rb = 0; rb < bands; rb += 2) {                
+      const int64_t at = ((int64_t)m * nband + rb) * d + c;
+      gsum += rb + 1 < bands ? dbpart[at] + dbpart[at + d] : dbpart[at];
+      if (ddbpart) dsum += rb + 1 < bands ? ddbpart[at] + ddbpart[at + d] : ddbpart[at];
     }
     put_fresh_grad(s, m, offb + c, gsum);
     if (s.rule == CADA_RULE_CADA1) {
