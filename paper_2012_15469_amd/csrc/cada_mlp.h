@@ -65,7 +65,7 @@ struct MlpPlan {
   bf16_t *Gh[CADA_MAX_LAYERS + 1], *Gl[CADA_MAX_LAYERS + 1], *dG[CADA_MAX_LAYERS + 1], *Gref[CADA_MAX_LAYERS + 1];       // layer l >= 1, (row, unit)
   uint64_t *maskbits[CADA_MAX_LAYERS];                    // hidden l: ReLU mask bits per tile and lane
   int32_t *rep;                                           // CADA2: first worker with the same reference point [M]
-  float *dbpart, *ddbpart;                                // [M][4 RT][max hidden width]: sums per band of 32 rows (scratch)
+  float *dbpart, *ddbpart;                                // [M][2 RT][max hidden width]: sums per band of 64 rows
   char *eval;                                             // scratch of the evaluation (mlp_eval_bytes)
   float *lastb;                                           // [M][Bp / 32][32][2]: last layer, sums of G and dG per block of 32 rows
 };

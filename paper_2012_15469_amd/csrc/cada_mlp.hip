@@ -91,8 +91,9 @@ struct Mm5Args {
   bf16_t *o_h, *o_l, *o_d, *o_r;        // (padded row, column), kto chunks per tile
   int64_t kto;
   uint64_t *maskbits;                   // ReLU mask bits [workers][row tiles][column tiles][256 lanes][2]: written by EPI_FWD_HIDDEN, read by EPI_DA
-  float *dbpart, *ddbpart;              // [workers][nband][units], one partial sum per band of 32 rows: written with the signals of a layer's units (EPI_DA, the last
-                                        // layer's EPI_DW), read by that layer's EPI_DW
+  float *dbpart, *ddbpart;              // [workers][nband][units], one partial sum per band of 64 rows: written with the signals of a layer's units (EPI_DA, the last
+                                        // layer's EPI_DW), read by that layer's EPI_DW.  The order of a band's sum is the same wherever it is formed: the rows with
+                                        // row / 4 even one after the other, the other rows one after the other, the one sum plus the other.
   // EPI_DW
   int64_t offW;
   int lhs_slot0;
@@ -386,9 +387,9 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
       const int col = cbase + j * 32;
       const bool cok = col < g.N;
       const float b = bias[j], db = dbias[j];
+      float sg_sum = 0.f, sd_sum = 0.f;
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        float sg_sum = 0.f, sd_sum = 0.f;
         // the quarter's four values per element, packed two rows to a register
         uint32_t ph[8], pl[8], pd[8], pr[8];
 #pragma unroll
@@ -432,15 +433,15 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
           }
           copy_out(orow_t, tm(rp0 + wr0 + i * 32, wc0 + j * 32, g.kto));
         }
-        if constexpr (EPI == EPI_DA) {
-          // the other half-wave holds the rows offset by 4: add it, then one value per column and band of 32 rows
-          sg_sum += __shfl_xor(sg_sum, 32, 64);
-          sd_sum += __shfl_xor(sd_sum, 32, 64);
-          if (lane < 32 && cok) {
-            const int64_t o = ((int64_t)wk * g.nband + 4 * by + 2 * wy + i) * g.N + col;
-            g.dbpart[o] = sg_sum;
-            if constexpr (!PL) g.ddbpart[o] = sd_sum;
-          }
+      }
+      if constexpr (EPI == EPI_DA) {
+        // the other half-wave holds the rows offset by 4: add it, then one value per column and band of 64 rows
+        sg_sum += __shfl_xor(sg_sum, 32, 64);
+        sd_sum += __shfl_xor(sd_sum, 32, 64);
+        if (lane < 32 && cok) {
+          const int64_t o = ((int64_t)wk * g.nband + 2 * by + wy) * g.N + col;
+          g.dbpart[o] = sg_sum;
+          if constexpr (!PL) g.ddbpart[o] = sd_sum;
         }
       }
     }
@@ -539,10 +540,10 @@ __global__ __launch_bounds__(kBlock, 2) void k_dw(const Mm5Args g) {
 #pragma unroll
   for (int q = 0; q < R0; ++q) load(q);
   // The tiles of the first 128 units also form the layer's bias gradient and its innovation, from the sums that the
-  // activation gradients' launch left per band of 32 rows: 64 columns from cw on, one per lane, and a partial sum of the left-hand
+  // signals' launch left per band of 64 rows: 64 columns from cw on, one per lane, and a partial sum of the left-hand
   // side of their own.  (A launch of its own cost 5 us.  One wavefront for 256 columns, with fewer partial sums: 784-500-10, B = 12:
   // 81.1 -> 82.8 us per step, 3072-1024-1024-10: 608 -> 615.)  A workgroup's first tile does it while its operands are on their way, a later one before
-  // its way out, when the stores of the tile before have drained.  Bands are added in pairs: the order of sums per 64 rows.
+  // its way out, when the stores of the tile before have drained.
   auto bias_part = [&](int wk, int bx) __attribute__((always_inline)) {
     const int cw = bx * BN + wx * 64;
     if (cw >= g.N) return;
@@ -551,10 +552,9 @@ __global__ __launch_bounds__(kBlock, 2) void k_dw(const Mm5Args g) {
     if (col < g.N) {
       const float *db = g.dbpart + (int64_t)wk * g.nband * g.N + col, *dd = g.ddbpart + (int64_t)wk * g.nband * g.N + col;
       float gsum = 0.f;
-      for (int i = 0, n = (g.K + 31) / 32; i < n; i += 2) {
-        const int64_t at = (int64_t)i * g.N;
-        gsum += i + 1 < n ? db[at] + db[at + g.N] : db[at];
-        if constexpr (!PL) dsum += i + 1 < n ? dd[at] + dd[at + g.N] : dd[at];
+      for (int i = 0; i < (g.K + 63) / 64; ++i) {
+        gsum += db[(int64_t)i * g.N];
+        if constexpr (!PL) dsum += dd[(int64_t)i * g.N];
       }
       put_fresh_grad(s, wk, g.offb + col, gsum);
       if (CADA1) {
@@ -803,8 +803,8 @@ __device__ __forceinline__ float group16_sum(float x) {
 // 32 rows x 32 columns; its wavefronts (eight; fewer for the few steps of a weight gradient) split the
 // tile steps (wavefront w takes steps w, w + nw, ...), read their fragments straight from the chunks in
 // global memory (a fragment is 16 consecutive bytes of a chunk row) and add their partial accumulators up
-// through LDS in a fixed order.  grid (ceil(M / 32), workers, blocks of 32 columns), 64 nw threads, 8 KB of dynamic LDS per
-// wavefront (EPI_DW: 14 KB).  EPI_FWD_HIDDEN: a hidden layer's forward product where the 128 x 128 tiles are few or mostly
+// through LDS in a fixed order.  grid (ceil(M / 32), workers, blocks of 32 columns), 64 threads per
+// wavefront (EPI_DW: and wavefronts for the way out alone, launch_skinny_as), 8 KB of dynamic LDS each (EPI_DW: 15.5 KB, for those that take steps).  EPI_FWD_HIDDEN: a hidden layer's forward product where the 128 x 128 tiles are few or mostly
 // padding (skinny_forward), with the outputs of k_mm5's.
 // EPI_LOSS: the logits stay in the workgroup, whose epilogue is the loss (the signals
 // the backward contractions read, and per-block sums for the bias gradient); EPI_DW: weight gradient, innovation, its
@@ -817,7 +817,7 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   float *red = reinterpret_cast<float *>(smem_raw);                  // [8 wavefronts][2 accumulators][16][64]
   const DevState &s = g.s;
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int t = threadIdx.x, lane = t & 63, w = EPI == EPI_DW ? __builtin_amdgcn_readfirstlane(t >> 6) : t >> 6;
   const int nw = blockDim.x >> 6;          // wavefronts of this launch (1..8)
   const int nsw = EPI == EPI_DW ? g.step_waves : nw;       // those that take tile steps: fewer for short contractions, so that more workgroups fit a CU
   const int m0 = blockIdx.x * 32, wk = blockIdx.y;
@@ -907,8 +907,23 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
       }
     }
     const int fro_tr = (8 * (lane >> 5) + ((lane & 15) >> 2)) * 32 + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-    if (w < nsw)
-    for (int kc = w; kc < nk; kc += nsw) {
+    // A band of 64 rows is two steps, which two wavefronts have (in the same round, or the last one and, a round later, the first): the one hands on its sums over
+    // the first 32 rows, and the other, whose values wait in its area, goes on from there.  What a round leaves is overwritten three rounds
+    // later, two barriers behind its reader.
+    float2 *const half_sums = reinterpret_cast<float2 *>(smem_raw + nsw * (7 * 2048));     // [3][nsw][64 lanes]
+    const bool signals = (PL || HAS_D) && g.w_h != nullptr;
+    auto put_band = [&](int kc, float2 v) __attribute__((always_inline)) {
+      v.x += __shfl_xor(v.x, 32, 64);            // (the other half-wave: the rows offset by 4)
+      v.y += __shfl_xor(v.y, 32, 64);
+      if (lane < 32 && m0 + lane < g.M) {
+        const int64_t o = ((int64_t)wk * g.nband + (kc >> 1)) * g.M + m0 + lane;
+        g.dbpart[o] = v.x;
+        if constexpr (!PL) g.ddbpart[o] = v.y;
+      }
+    };
+    for (int round = 0, kc = w; round * nsw < nk; ++round, kc += nsw) {
+      const bool mine = w < nsw && kc < nk;
+      if (mine) {
       u32x4 v[NA + NB][2];
 #pragma unroll
       for (int sl = 0; sl < NA + NB; ++sl) {
@@ -937,9 +952,9 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
         if constexpr (!PL) acc2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bd, acc2, 0, 0, 0);
       }
       if constexpr (PL || HAS_D) {
-        if (g.w_h != nullptr) {
+        if (signals) {
           // activation gradient of these 32 rows into the units of this block: the signals' block lies in the area as it is, a row per lane
-          f32x16 c1, c2;
+          f32x16 c1, c2;                        // at theta and its difference
 #pragma unroll
           for (int r = 0; r < 16; ++r) { c1[r] = 0.f; c2[r] = 0.f; }
 #pragma unroll
@@ -959,7 +974,6 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
           const uint16_t *mb = reinterpret_cast<const uint16_t *>(g.maskbits + ((((int64_t)wk * ((g.K + BM - 1) / BM) + (kc >> 2)) * ((g.M + BN - 1) / BN) + (m0 >> 7)) * kBlock +
                                                                                 (((kc >> 1) & 1) * 2 + ((m0 >> 6) & 1)) * 64 + lane) * 2) + (kc & 1) * 2 + ((m0 >> 5) & 1);
           const uint32_t on = mb[0], on_ref = PL ? 0u : mb[4];
-          float sum_g = 0.f, sum_d = 0.f;
 #pragma unroll
           for (int r = 0; r < 16; r += 2) {
             float x[2], xr[2];
@@ -968,7 +982,7 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
               const bool live = m0 + (lane & 31) < g.M && 32 * kc + 8 * (r >> 2) + 4 * (lane >> 5) + ((r + e) & 3) < g.K;
               x[e] = live && ((on >> (r + e)) & 1) ? c1[r + e] : 0.f;
               xr[e] = live && ((on_ref >> (r + e)) & 1) ? c1[r + e] - c2[r + e] : 0.f;
-              sum_g += x[e]; sum_d += x[e] - xr[e];
+              c1[r + e] = x[e]; c2[r + e] = x[e] - xr[e];
             }
             const uint32_t vh = f2bf_pk(x[0], x[1]), vr = f2bf_pk(xr[0], xr[1]), vd = f2bf_pk(x[0] - xr[0], x[1] - xr[1]);
             const uint32_t vl = f2bf_pk(x[0] - __uint_as_float(vh << 16), x[1] - __uint_as_float(vh & 0xffff0000u));
@@ -988,16 +1002,39 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
 #pragma unroll
               for (int hh = 0; hh < 2; ++hh) *reinterpret_cast<u32x4 *>(dst[b] + out + (hh * 64 + lane) * 8) = *reinterpret_cast<const u32x4 *>(area + b * 1024 + (hh * 64 + lane) * 8);
             }
-          sum_g += __shfl_xor(sum_g, 32, 64);
-          sum_d += __shfl_xor(sum_d, 32, 64);
-          if (lane < 32 && m0 + lane < g.M) {
-            const int64_t o = ((int64_t)wk * g.nband + kc) * g.M + m0 + lane;
-            g.dbpart[o] = sum_g;
-            if constexpr (!PL) g.ddbpart[o] = sum_d;
+          if (kc & 1) {
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              v4s *at = reinterpret_cast<v4s *>(area) + q * 64 + lane;
+              at[0] = v4s{c1[4 * q], c1[4 * q + 1], c1[4 * q + 2], c1[4 * q + 3]};
+              if constexpr (!PL) at[256] = v4s{c2[4 * q], c2[4 * q + 1], c2[4 * q + 2], c2[4 * q + 3]};
+            }
+          } else {
+            float2 v = make_float2(0.f, 0.f);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) { v.x += c1[r]; v.y += c2[r]; }
+            if (kc + 1 < nk) half_sums[((round % 3) * nsw + w) * 64 + lane] = v;
+            else put_band(kc, v);
           }
         }
       }
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the fragments are in registers before the area is written again
+      }
+      if (signals && nk > 1) {
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        if (mine && (kc & 1)) {
+          float2 v = half_sums[(w > 0 ? (round % 3) * nsw + w - 1 : ((round + 2) % 3) * nsw + nsw - 1) * 64 + lane];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const v4s *at = reinterpret_cast<const v4s *>(area) + q * 64 + lane;
+            const v4s x = at[0];
+            v.x += x.x; v.x += x.y; v.x += x.z; v.x += x.w;
+            if constexpr (!PL) { const v4s d = at[256]; v.y += d.x; v.y += d.y; v.y += d.z; v.y += d.w; }
+          }
+          put_band(kc, v);
+        }
+      }
     }
     __syncthreads();                                         // the areas are done with: `red` lies over them
   } else {
@@ -1276,8 +1313,8 @@ void layout(MlpPlan &P, const cada_config *cfg, int64_t total_rows, Carve &w) {
   }
   (void)w.take<float>(Rp * P.d[P.L]);             // (not used any more; the room keeps the layout of saved checkpoint blocks)
   (void)w.take<float>(Rp * P.d[P.L]);
-  (void)w.take<float>((size_t)cfg->M * 2 * P.RT * maxh);     // (nor this)
-  (void)w.take<float>((size_t)cfg->M * 2 * P.RT * maxh);
+  P.dbpart = w.take<float>((size_t)cfg->M * 2 * P.RT * maxh);
+  P.ddbpart = w.take<float>((size_t)cfg->M * 2 * P.RT * maxh);
   P.lastb = w.take<float>((size_t)cfg->M * (P.Bp / 32) * 32 * 2);
 }
 }  // namespace
@@ -1309,21 +1346,16 @@ size_t mlp_workspace_bytes(const cada_config *cfg, const int64_t total_rows) {
   return w.off + kAlignB;
 }
 
-// Scratch: the partial sums of the left-hand side, the bands' sums of the signals and of their differences, the evaluation's.
+// The partial sums of the left-hand side, in front of the evaluation's scratch.
 static size_t lhs_bytes(const cada_config *cfg) {
   return ((size_t)cfg->M * mlp_lhs_slots(cfg, mlp_bias_cols(cfg->rule)) * sizeof(float) + kAlignB - 1) / kAlignB * kAlignB;
-}
-static size_t band_bytes(const MlpPlan &P) {
-  int maxh = 1;
-  for (int l = 1; l < P.L; ++l) if (P.d[l] > maxh) maxh = P.d[l];
-  return ((size_t)P.M * 4 * P.RT * maxh * sizeof(float) + kAlignB - 1) / kAlignB * kAlignB;
 }
 
 size_t mlp_scratch_bytes(const cada_config *cfg, const int64_t total_rows) {
   MlpPlan P;
   Carve w{nullptr, 0};
   layout(P, cfg, total_rows, w);
-  return lhs_bytes(cfg) + 2 * band_bytes(P) + mlp_eval_bytes(P) + kAlignB;
+  return lhs_bytes(cfg) + mlp_eval_bytes(P) + kAlignB;
 }
 
 int mlp_plan(Ctx *c, const cada_config *cfg, char *base, size_t offset, size_t scratch, int64_t total_rows) {
@@ -1334,9 +1366,7 @@ int mlp_plan(Ctx *c, const cada_config *cfg, char *base, size_t offset, size_t s
   layout(*P, cfg, total_rows, w);
   scratch = (scratch + kAlignB - 1) / kAlignB * kAlignB;
   c->s.lhs_part = reinterpret_cast<float *>(base + scratch);
-  P->dbpart = reinterpret_cast<float *>(base + scratch + lhs_bytes(cfg));
-  P->ddbpart = P->dbpart + band_bytes(*P) / sizeof(float);
-  P->eval = reinterpret_cast<char *>(P->ddbpart) + band_bytes(*P);
+  P->eval = base + scratch + lhs_bytes(cfg);
   c->mlp = P;
   c->n_phases = 3;
   c->phase_names[0] = "mlp_gradients"; c->phase_names[1] = "rule"; c->phase_names[2] = "server_update";
@@ -1516,7 +1546,7 @@ __global__ __launch_bounds__(kBlock) void k_stage(const StageArgs a) {
   stage_weights(a, p, sm, (int)(r % p.gx), (int)(r / p.gx), (int)z, l == 0 && r == 0);
 }
 
-// Hidden-layer bias gradient and its innovation from the sums per band of 32 rows, added in pairs as k_dw adds them.
+// Hidden-layer bias gradient and its innovation from the sums per band of 64 rows.
 // grid (ceil(d / 64), M), one wavefront each
 __global__ __launch_bounds__(kWave) void k_bias_finish(const DevState s, const float *dbpart, const float *ddbpart, int nband, int bands, int d,
                                                        int64_t offb, int lhs_slot) {
@@ -1525,10 +1555,10 @@ __global__ __launch_bounds__(kWave) void k_bias_finish(const DevState s, const f
   float sq = 0.f;
   if (c < d) {
     float gsum = 0.f, dsum = 0.f;
-    for (int rb = 0; rb < bands; rb += 2) {                
+    for (int rb = 0; rb < bands; ++rb) {
       const int64_t at = ((int64_t)m * nband + rb) * d + c;
-      gsum += rb + 1 < bands ? dbpart[at] + dbpart[at + d] : dbpart[at];
-      if (ddbpart) dsum += rb + 1 < bands ? ddbpart[at] + ddbpart[at + d] : ddbpart[at];
+      gsum += dbpart[at];
+      if (ddbpart) dsum += ddbpart[at];
     }
     put_fresh_grad(s, m, offb + c, gsum);
     if (s.rule == CADA_RULE_CADA1) {
@@ -1575,9 +1605,9 @@ template <int NA, int NB, bool HAS_D, bool CADA1> int launch_dw_as(Ctx *c, Mm5Ar
 template <int NA, int NB, bool HAS_D, bool CADA1> hipError_t dw_allow_lds() {
   return hipFuncSetAttribute(reinterpret_cast<const void *>(k_dw<NA, NB, HAS_D, CADA1>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kDwLds);
 }
-// first layer: two A tensors (hi, lo) and no propagated difference on the A side; deeper layers: all of them
-// per wavefront: its partial results (8 KB); weight gradient: the seven blocks it stages (14 KB), over which the partial results are laid later
-constexpr int skinny_lds_bytes(int epi, int nw = 8) { return nw * (epi == EPI_DW ? 7 * 1024 * (int)sizeof(bf16_t) : 8192); }
+// per wavefront: its partial results (8 KB); weight gradient: the seven blocks it stages (14 KB), over which the partial results are laid later, and behind
+// them (1.5 KB) the sums that wavefronts hand on
+constexpr int skinny_lds_bytes(int epi, int nw = 8) { return nw * (epi == EPI_DW ? 7 * 1024 * (int)sizeof(bf16_t) + 3 * 64 * (int)sizeof(float2) : 8192); }
 // Wavefronts of a launch: one per two tile steps, eight at most.  A weight gradient sums over a worker's few rows (4-8
 // steps); with eight wavefronts half of them would idle while their LDS kept other workgroups off the CU.
 static int skinny_waves(int epi, int K) {
@@ -1798,7 +1828,7 @@ static void signals_below(Mm5Args &g, const MlpPlan &P, int q, bool plain) {
   g.kto = P.kta[q];
   g.o_h = P.Gh[q]; g.o_l = P.Gl[q]; g.o_d = plain ? nullptr : P.dG[q]; g.o_r = plain ? nullptr : P.Gref[q];     // (Gref: null for q = 1)
   g.maskbits = P.maskbits[q];
-  g.dbpart = P.dbpart; g.ddbpart = P.ddbpart; g.nband = 4 * P.RT;
+  g.dbpart = P.dbpart; g.ddbpart = P.ddbpart; g.nband = 2 * P.RT;
 }
 
 int mlp_gradients(Ctx *c, const int32_t *idx) {
@@ -1847,7 +1877,7 @@ int mlp_gradients(Ctx *c, const int32_t *idx) {
           signals_below(g, P, l - 1, plain);
         }
       } else if (bias_inside(M, din, dout)) {       // and the other layers' from the sums of the launch that formed their signals
-        g.dbpart = P.dbpart; g.ddbpart = P.ddbpart; g.nband = 4 * P.RT; g.bias_here = 1; g.offb = P.offb[l - 1]; g.lhs_slot_b = P.lhs_b_slot[l - 1];
+        g.dbpart = P.dbpart; g.ddbpart = P.ddbpart; g.nband = 2 * P.RT; g.bias_here = 1; g.offb = P.offb[l - 1]; g.lhs_slot_b = P.lhs_b_slot[l - 1];
       }
       if (const int rc = launch_mm5<EPI_DW>(c, g, M)) return rc;
     }
@@ -1870,7 +1900,7 @@ int mlp_gradients(Ctx *c, const int32_t *idx) {
       if (const int rc = launch_mm5<EPI_DA>(c, g, M)) return rc;
     }
     if (l >= 2 && !bias_inside(M, P.d[l - 2], din))
-      hipLaunchKernelGGL(k_bias_finish, dim3((din + kWave - 1) / kWave, M), dim3(kWave), 0, st, s, P.dbpart, plain ? nullptr : P.ddbpart, 4 * P.RT, (B + 31) / 32, din,
+      hipLaunchKernelGGL(k_bias_finish, dim3((din + kWave - 1) / kWave, M), dim3(kWave), 0, st, s, P.dbpart, plain ? nullptr : P.ddbpart, 2 * P.RT, (B + 63) / 64, din,
                          P.offb[l - 2], P.lhs_b_slot[l - 2]);
   }
   prof_mark(c);

@@ -6,7 +6,7 @@ import pytest
 
 from cada_synth import configs, generators
 
-from common import check_protocol, upload, run_library, oracle_run, rel_l2
+from common import check_protocol, to_dev, upload, run_library, oracle_run, rel_l2
 
 pytestmark = pytest.mark.gpu
 
@@ -54,3 +54,54 @@ def test_gradients_and_left_hand_sides(shape, rule):
     big = tr["lhs"] > 1e-9 * tr["lhs"].max()
     rel = np.abs(rep["trace_lhs"] - tr["lhs"])[big] / tr["lhs"][big]
     assert float(np.median(rel)) < 2.0 ** -7
+
+
+def _exact_network(dims, rows, rng):
+    """Small integers (times powers of two) throughout: every activation and logit is exact in any order of summation.  Row 0 of X is zero, and no
+    hidden unit is active there."""
+    X = rng.integers(0, 4, size=(rows + 1, dims[0])).astype(np.float32)
+    X[0] = 0.0
+    theta = []
+    for l, (a, b) in enumerate(zip(dims, dims[1:])):
+        theta.append(rng.integers(-2, 3, size=a * b) * 2.0 ** (-2 - l))
+        theta.append(np.full(b, -0.5 if l + 2 < len(dims) else 0.0))
+    return X, rng.integers(0, dims[-1], size=rows + 1).astype(np.int32), np.concatenate(theta).astype(np.float32)
+
+
+@pytest.mark.parametrize("rule", ["cada2", "always"])
+@pytest.mark.parametrize("dims", [(24, 45, 7), (24, 20, 5), (24, 150, 40, 5)], ids=lambda d: "-".join(map(str, d)))
+@pytest.mark.parametrize("B", [7, 33, 64, 100, 192, 224, 300, 513])
+def test_order_of_the_bias_gradients_sums(B, dims, rule):
+    """A hidden bias gradient is the sum of its signals over the rows in one order, whichever launch forms the signals: bands of 64 rows, in a band the rows with
+    row / 4 even one after the other, then the others, then the two sums; the bands one after the other.  float32 sums in that
+    order give the result bit for bit.  The signals come from workers that have one such row and otherwise rows on which no unit is active: zeros, which
+    leave a sum as it is."""
+    rng = np.random.default_rng(B)
+    X, y, theta = _exact_network(dims, B, rng)
+
+    def stored(M, n, X, y, sched):
+        cfg = configs.CFG4.scaled(name="bias_order", layer_dims=dims, M=M, N_m=n, B=B, K=1, D=3, rule=RULES[rule])
+        out = run_library(cfg, (to_dev(X), to_dev(y), to_dev(theta)), sched)
+        assert out["error_flags"][0] == 0 and out["trace_mask"].all()
+        return out["stored"]
+
+    pairs = np.stack([np.arange(1, B + 1), np.zeros(B, dtype=np.int64)], axis=1).reshape(-1)      # worker m: row m + 1, the zero row
+    one = np.ones((1, B, B), dtype=np.int32)
+    one[0, np.arange(B), np.arange(B)] = 0
+    single = stored(B, 2, X[pairs], y[pairs], one)
+    got = stored(1, B, X[1:], y[1:], np.arange(B, dtype=np.int32).reshape(1, 1, B))[0]
+
+    off = dims[0] * dims[1]
+    for a, b, c in zip(dims, dims[1:], dims[2:]):
+        x = single[:, off:off + b].astype(np.float32)
+        want, other = np.zeros(b, np.float32), np.zeros(b, np.float32)
+        for r0 in range(0, B, 64):
+            half = np.zeros((2, b), np.float32)
+            for r in range(r0, min(r0 + 64, B)):
+                half[(r >> 2) & 1] += x[r]
+            want += half[0] + half[1]
+        for r in range(B):
+            other += x[r]
+        assert np.abs(x).max() > 0 and (B < 33 or not np.array_equal(want, other)), "the case must tell orders apart"
+        assert np.array_equal(got[off:off + b], want), (b, np.abs(got[off:off + b] - want).max(), int((got[off:off + b] != want).sum()))
+        off += b + b * c
