@@ -54,11 +54,17 @@ __device__ __forceinline__ void to_lds(const bf16_t *base, uint32_t off, uint32_
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory", "m0");
 }
 
-// HID: hidden layers (2: two or more), or kByLayer: one hidden layer a launch (layer[0]; layer[1] is the next one), one tile of its units a workgroup
-constexpr int kByLayer = 3;
+// HID: hidden layers (2: two or more), or kByLayer: one hidden layer a launch (layer[0]; layer[1] is the next one), one tile of its units a workgroup, or
+// kFewSteps: one hidden layer of few inputs
+constexpr int kByLayer = 3, kFewSteps = 4;
 // Stages of rows in LDS: several hidden layers in a launch have two, as a layer's input is not there before its last step.
-constexpr int eval_row_stages(int hid) { return hid == 2 ? 2 : 3; }
-// Rows x units of 256 x 256 then leave no room for the logits.
+constexpr int eval_row_stages(int hid) { return hid == 2 || hid == kFewSteps ? 2 : 3; }
+// Rows x units of 256 x 256 then leave no room for the logits.  Lent out and taken back at the end of every tile of units, the stage of weights costs some
+// microseconds a row tile, which the third stage of rows earns back where a tile of units has many steps.  Where it has kFewStepsMost or fewer, k_eval_net<4, 2, kFewSteps>
+// has two stages, all loads of a step at its head and the logits in room of their own.  us, two stages / three, 60000 and 250000 rows: 64-1024-32 68.5, 239 / 72, 267;
+// 256-512-10 71, 237 / 73.5, 248; 512-1024-32 186, 738 / 192, 767; 640-512-10 117, 479 / 119, 473; 640-1024-32 216, 904 / 223, 912; 784-512-10 140, 603 / 139, 566;
+// 1024-1024-32 332, 1430 / 334, 1393.
+constexpr int kFewStepsMost = 20;
 constexpr bool eval_lends(int NR, int NU, int hid) { return eval_row_stages(hid) == 3 && NR == 4 && NU == 2; }
 constexpr int eval_lds(int NR, int NU, int hid) { return 64 * NR * 128 * (eval_row_stages(hid) + (eval_lends(NR, NU, hid) ? 0 : 1)) + 2 * 128 * NU * 128; }
 template <int NR, int NU, int HID>
@@ -179,6 +185,7 @@ __global__ __launch_bounds__(512) void k_eval_net(const EvalArgs a) {
           const int xn = xs + XS - 1 >= XS ? xs - 1 : xs + XS - 1;      // the stage of the rows that are asked for in this step
           if constexpr (XS != 3) {
             ready = advance(done);
+            if (HID == kFewSteps && ready) load_rows(xn);
             if (ready) load_weights(ws ^ 1);
           }
           const bf16_t *sx = reinterpret_cast<const bf16_t *>(smem_raw + xs * XB) + (wr * 32 * NR) * 32;
@@ -186,7 +193,7 @@ __global__ __launch_bounds__(512) void k_eval_net(const EvalArgs a) {
           const int fro = lds_piece(l32 * 4 + half) * 8;
 #pragma unroll
           for (int ks = 0; ks < 32; ks += 16) {
-            if constexpr (XS != 3) __builtin_amdgcn_s_setprio(1);
+            if constexpr (HID == 2) __builtin_amdgcn_s_setprio(1);
             bf16x8 wh[NU], wl[NU], xh[NR], xl[NR];
 #pragma unroll
             for (int j = 0; j < NR; ++j) {
@@ -205,7 +212,7 @@ __global__ __launch_bounds__(512) void k_eval_net(const EvalArgs a) {
                 if constexpr (XS == 3) {
                   if (q == 1 && next) { load_weights(ws ^ 1); next = advance(done); }
                   if (q == 2 && next) load_rows(xn);
-                } else if (ready) {
+                } else if (HID != kFewSteps && ready) {
                   if (q == 1) load_rows(xn);
                 }
                 __builtin_amdgcn_sched_barrier(0);
@@ -217,7 +224,7 @@ __global__ __launch_bounds__(512) void k_eval_net(const EvalArgs a) {
                   acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q == 1 ? wl[i] : wh[i], q == 0 ? xl[j] : xh[j], acc[i][j], 0, 0, 0);
             }
           }
-          if constexpr (XS != 3) __builtin_amdgcn_s_setprio(0);
+          if constexpr (HID == 2) __builtin_amdgcn_s_setprio(0);
           landed(XS == 3 && next);
           xs = xs + 1 == XS ? 0 : xs + 1;
           ws ^= 1;
@@ -421,7 +428,10 @@ struct EvalPlan {
   int nr, nu;                // rows (64 nr) and units (128 nu) of a tile
   bool by_layer;             // a launch per hidden layer
 };
-EvalKernel eval_kernel(const EvalPlan &e, int L) {
+bool eval_few_steps(const EvalPlan &e, const MlpPlan &P) { return P.L == 2 && !e.by_layer && e.nr == 4 && e.nu == 2 && (P.d[0] + 31) / 32 <= kFewStepsMost; }
+EvalKernel eval_kernel(const EvalPlan &e, const MlpPlan &P) {
+  const int L = P.L;
+  if (eval_few_steps(e, P)) return k_eval_net<4, 2, kFewSteps>;
   if (e.by_layer) {
     if (e.nu == 2) return e.nr == 2 ? k_eval_net<2, 2, kByLayer> : k_eval_net<1, 2, kByLayer>;
     return eval_kernel_of<1, kByLayer>(e.nr);
@@ -432,7 +442,7 @@ EvalKernel eval_kernel(const EvalPlan &e, int L) {
   return eval_kernel_of<1, 2>(e.nr);
 }
 
-int eval_hid(const EvalPlan &e, int L) { return e.by_layer ? kByLayer : min(L - 1, 2); }
+int eval_hid(const EvalPlan &e, const MlpPlan &P) { return eval_few_steps(e, P) ? kFewSteps : e.by_layer ? kByLayer : min(P.L - 1, 2); }
 
 int64_t eval_row_tiles(const MlpPlan &P, int nr) { return (P.total_rows + 64 * nr - 1) / (64 * nr); }
 int eval_unit_tiles(const MlpPlan &P, int l, int nu) { return (int)((P.d[l] + 128 * nu - 1) / (128 * nu)); }
@@ -493,7 +503,7 @@ size_t mlp_eval_bytes(const MlpPlan &P) {
 int mlp_eval_init(Ctx *c) {
   const MlpPlan &P = *static_cast<MlpPlan *>(c->mlp);
   const EvalPlan p = eval_plan(P);
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(eval_kernel(p, P.L)), hipFuncAttributeMaxDynamicSharedMemorySize, eval_lds(p.nr, p.nu, eval_hid(p, P.L)));
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(eval_kernel(p, P)), hipFuncAttributeMaxDynamicSharedMemorySize, eval_lds(p.nr, p.nu, eval_hid(p, P)));
   if (e != hipSuccess) { set_error("hipFuncSetAttribute(LDS size) failed: %s", hipGetErrorString(e)); return CADA_EHIP; }
   return CADA_OK;
 }
@@ -518,8 +528,8 @@ int mlp_eval(Ctx *c, double *out) {
   const int64_t n = a.row_pad * a.lda;
   bf16_t *act = reinterpret_cast<bf16_t *>(P.eval + eval_rowval_bytes(P));
   for (int i = 0; i < 4; ++i) a.act[i >> 1][i & 1] = act + (P.L > 3 ? i : (i & 1)) * n;
-  const EvalKernel kernel = eval_kernel(p, P.L);
-  const size_t lds = eval_lds(p.nr, p.nu, eval_hid(p, P.L));
+  const EvalKernel kernel = eval_kernel(p, P);
+  const size_t lds = eval_lds(p.nr, p.nu, eval_hid(p, P));
   mlp_stage_weights(c);
   if (p.by_layer) {
     EvalArgs b = a;

@@ -94,8 +94,9 @@ def test_network_evaluation_on_few_rows(dims, M, n):
 
 
 # More tiles of rows than workgroups, with one to three steps per tile: the loads that run ahead of the products cross tiles of units and of rows at every
-# step, end with the last tile, and (256 x 256) the logits lie in the weights' free stage between tiles of units.
-MANY_ROWS = [((20, 700, 5), 2, 40000), ((64, 512, 10), 2, 40000), ((96, 520, 32), 2, 33100), ((70, 20), 2, 40000), ((33, 260, 4), 2, 33100), ((40, 300, 200, 7), 2, 35000)]
+# step and end with the last tile.  The last two, 256 x 256 on either side of the line at 20 steps: with 21 the logits lie in the weights' free stage between tiles of units.
+MANY_ROWS = [((20, 700, 5), 2, 40000), ((64, 512, 10), 2, 40000), ((96, 520, 32), 2, 33100), ((70, 20), 2, 40000), ((33, 260, 4), 2, 33100), ((40, 300, 200, 7), 2, 35000),
+             ((640, 500, 4), 1, 100500), ((641, 500, 4), 1, 100500)]
 
 
 @pytest.mark.parametrize("dims,M,n", MANY_ROWS, ids=lambda v: "-".join(map(str, v)) if isinstance(v, tuple) else str(v))
