@@ -32,7 +32,7 @@
 // orientation, (row, unit).  The weight-gradient contractions, which sum over the rows, read the
 // same chunks and transpose on the way from LDS into the registers (ds_read_b64_tr_b16).
 //
-// k_mm5 serves the forward products and the activation gradients, k_dw the weight gradients.  For a 128 x 128
+// k_mm5 serves the forward products and the activation gradients, k_dw the weight gradients (where dw_past_caches says so, k_mm5).  For a 128 x 128
 // output tile of worker m they accumulate
 //     C1 = Ah Bh^T + Ah Bl^T + Al Bh^T          (evaluation at theta, split operands)
 //     C2 = Ad Bx^T + Ar Bd^T                    (difference to the reference evaluation)
@@ -53,9 +53,10 @@ namespace cada {
 
 enum { EPI_FWD_HIDDEN = 0, EPI_DW = 2, EPI_DA = 3, EPI_LOSS = 4 };
 
-// k_mm5's LDS: a ring of 8 KB slots (one chunk each); behind it 8 KB per multiplying wavefront for the bf16 tensors on their way out.
-constexpr int kMm5Slots = 15;
-constexpr size_t kMm5Lds = (size_t)kMm5Slots * TILE * sizeof(bf16_t) + 4 * 8192;
+// k_mm5's LDS: a ring of 8 KB slots (one chunk each); behind it 8 KB per multiplying wavefront for the bf16 tensors on their way out, or (weight gradients)
+// 32 rows x 64 floats with a pitch of 72: the two half-wavefronts of an accumulator store (rows 4 apart) come into different halves of the banks.
+constexpr int kMm5Slots = 15, kDwPitch = 72;
+constexpr size_t mm5_lds_bytes(int epi) { return (size_t)kMm5Slots * TILE * sizeof(bf16_t) + 4 * (epi == EPI_DW ? 32 * kDwPitch * sizeof(float) : 8192); }
 
 // Division of 0 <= x < 2^31 by a divisor that the host knows: a product and a shift (as a division it takes the compiler some forty
 // instructions, and a tile's three indices two of them, each time at the head of a launch that may have one tile per workgroup).
@@ -182,13 +183,41 @@ __device__ __forceinline__ bf16x8 tr_fragment(const bf16_t *blk, int lane_off) {
 __device__ __forceinline__ void mm_load(const bf16_t *base, uint32_t byte_off, uint32_t lds) {      // 1 KB, 16 bytes per lane, to `lds` (uniform)
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(byte_off), "s"(base), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory", "m0");
 }
+// Bias gradient of a hidden layer's units col .. (one per lane) and its innovation, from the sums that the signals' launch left per band of
+// 64 rows, and (not PL) the wavefront's 64 units' partial sum of the left-hand side: in the launch of the layer's weight gradient.
+template <bool PL, bool CADA1>
+__device__ __forceinline__ void hidden_bias(const Mm5Args &g, int wk, int col, int slot, int lane) {
+  const DevState &s = g.s;
+  float dsum = 0.f;
+  if (col < g.N) {
+    const float *db = g.dbpart + (int64_t)wk * g.nband * g.N + col, *dd = g.ddbpart + (int64_t)wk * g.nband * g.N + col;
+    float gsum = 0.f;
+    for (int i = 0; i < (g.K + 63) / 64; ++i) {
+      gsum += db[(int64_t)i * g.N];
+      if constexpr (!PL) dsum += dd[(int64_t)i * g.N];
+    }
+    put_fresh_grad(s, wk, g.offb + col, gsum);
+    if (CADA1) {
+      fresh_innov(s, wk)[g.offb + col] = f2bf(dsum);
+      dsum -= bf2f(stored_innov(s, wk)[g.offb + col]);
+    }
+  }
+  if constexpr (!PL) {
+    const float tot = wave_sum(dsum * dsum);
+    if (lane == 0) s.lhs_part[(int64_t)wk * s.n_lhs_part + slot] = tot;
+  }
+}
+
+// EPI_DW (rules without a second gradient, float32 store; dw_past_caches): both operands are (row, unit) tensors whose 128-row tiles hold the rows that the
+// product sums over.  A step is 32 rows; the operand of a side is the 32 rows x 128 units block of them, which lies in four chunks as 2 KB of
+// consecutive memory each, stored in its ring slot as [unit chunk][row][unit] and read with transposing LDS loads.
 template <int EPI, int NA, int NB, bool HAS_D>
 __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   bf16_t *lds = reinterpret_cast<bf16_t *>(smem_raw);
   constexpr int NS = NA + NB, NSLOT = kMm5Slots;
-  static_assert(EPI == EPI_FWD_HIDDEN || EPI == EPI_DA, "");
-  constexpr bool PL = NB == 2;
+  constexpr bool PL = NB == 2, TR = EPI == EPI_DW;
+  static_assert(EPI == EPI_FWD_HIDDEN || EPI == EPI_DA || (TR && PL), "");
   static_assert(NSLOT >= 2 * NS, "the ring must hold two tile steps");
   const DevState &s = g.s;
   const bool mover = __builtin_amdgcn_readfirstlane((int)threadIdx.x) >= kBlock;   // uniform per wavefront
@@ -214,7 +243,8 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
     int goff[2];
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
-      goff[c] = lds_piece((2 * lw + c) * 64 + lane) * 8;          // (the order is its own inverse)
+      if constexpr (TR) goff[c] = (lw << 12) + (c << 9) + lane * 8;    // kilobyte 2 w + c of the step's operand: half c of unit chunk w
+      else goff[c] = lds_piece((2 * lw + c) * 64 + lane) * 8;          // (the order is its own inverse)
     }
     // issue cursor: tile ordinal, step in the tile, first chunk of the tile's rows in every tensor, ring slot
     int ord = 0, h = 0, slot = 0;
@@ -223,10 +253,10 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
       const int tix = t_first + o * nbx;
       const int trow = quotient(tix, g.gx), bx = tix - trow * gx, bz = quotient(trow, g.gy), by = trow - bz * gy;
 #pragma unroll
-      for (int sl = 0; sl < NA; ++sl) pa[sl] = g.A.ptr[sl] + (int64_t)bz * g.A.bstride[sl] + (((int64_t)by * g.A.kt[sl]) << 12);
+      for (int sl = 0; sl < NA; ++sl) pa[sl] = g.A.ptr[sl] + (int64_t)bz * g.A.bstride[sl] + (((int64_t)by * (TR ? 4 : g.A.kt[sl])) << 12);
       const int bzb = g.rep ? g.rep[bz] : bz;
 #pragma unroll
-      for (int sl = 0; sl < NB; ++sl) pb[sl] = g.B.ptr[sl] + (int64_t)bzb * g.B.bstride[sl] + (((int64_t)bx * g.B.kt[sl]) << 12);
+      for (int sl = 0; sl < NB; ++sl) pb[sl] = g.B.ptr[sl] + (int64_t)bzb * g.B.bstride[sl] + (((int64_t)bx * (TR ? 4 : g.B.kt[sl])) << 12);
     };
     // next tile step; past the last one the cursor stays (those loads re-read the last chunk into slots nobody reads)
     auto next_step = [&]() __attribute__((always_inline)) {
@@ -235,7 +265,8 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
     };
     auto load = [&](int sl) __attribute__((always_inline)) {
       const bf16_t *src = sl < NA ? pa[sl < NA ? sl : 0] : pb[sl < NA ? 0 : sl - NA];
-      src += (int64_t)h << 12;
+      if constexpr (TR) src += (((int64_t)(h >> 2) * (sl < NA ? g.A.kt[0] : g.B.kt[0])) << 12) + ((h & 3) << 10);     // rows 32 h ...: quarter h % 4 of row tile h / 4
+      else src += (int64_t)h << 12;
       bf16_t *dst = lds + ((size_t)slot << 12) + (2 * lw << 9);
 #pragma unroll
       for (int c = 0; c < 2; ++c)
@@ -267,6 +298,7 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
 
   // fragment of this lane inside a 32-row band: row lane % 32, piece lane / 32 (+ 2 in the second half step)
   const int fro = lds_piece((lane & 31) * 4 + (lane >> 5)) * 8;
+  const int fro_tr = (8 * (lane >> 5) + ((lane & 15) >> 2)) * 32 + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);      // (TR: see tr_fragment)
   int sb = 0;                                  // ring slot of the current step's first tensor
   for (int ord = 0; ord < nt; ++ord) {
   const int tix = t_first + ord * nbx;
@@ -290,7 +322,8 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
     for (int ks = 0; ks < BK; ks += 16) {
       bf16x8 ah[2], al[2], ad[2], ar[2], bh[2], bl[2], bx_[2], bd[2];
       auto frag = [&](const bf16_t *slot, int half, int blk) __attribute__((always_inline)) -> bf16x8 {
-        return *reinterpret_cast<const bf16x8 *>(slot + (half * 64 + blk * 32) * BK + (fro ^ ks));
+        if constexpr (TR) return tr_fragment(slot + (half * 2 + blk) * 1024 + ks * 32, fro_tr);
+        else return *reinterpret_cast<const bf16x8 *>(slot + (half * 64 + blk * 32) * BK + (fro ^ ks));
       };
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
@@ -331,7 +364,7 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
   const int rbase = m0 + wy * 64 + 4 * (lane >> 5);
   const int cbase = n0 + wx * 64 + (lane & 31);
   const int64_t rp0 = (int64_t)wk * g.Bp;            // first padded row of this worker
-  {
+  if constexpr (!TR) {
     // Forward: bias, ReLU of both evaluations.  Activation gradient: ReLU masks of the layer
     // below, bias-gradient partial sums.  Both: the result split into hi/lo, its difference and
     // its reference value, each written as a (row, column) tensor.
@@ -450,6 +483,36 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
       mb.x = (uint32_t)bit_on; mb.y = (uint32_t)(bit_on >> 32); mb.z = (uint32_t)bit_ref; mb.w = (uint32_t)(bit_ref >> 32);
       *reinterpret_cast<u32x4 *>(mbits) = mb;
     }
+  } else {
+    // Each wavefront's 64 x 64 part passes through an LDS buffer of its own, 32 rows at a time, and leaves row by row, 16 bytes per lane, 256 bytes per
+    // row, past the caches; the stores drain while the next tile's products run.  A lane whose four columns are cut by the matrix's edge goes element by element.
+    float *st = reinterpret_cast<float *>(smem_raw + (size_t)NSLOT * TILE * sizeof(bf16_t)) + w * (32 * kDwPitch);
+    float *gf = fresh_grad(s, wk) + g.offW;
+    const int c4 = (lane & 15) * 4, rr = lane >> 4, colg = n0 + wx * 64 + c4;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int rowb = m0 + wy * 64 + i * 32 + rr;
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) st[(8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * kDwPitch + j * 32 + (lane & 31)] = acc1[i][j][r];
+      asm volatile("" ::: "memory");
+      if (colg + 4 <= g.N) {
+#pragma unroll
+        for (int it = 0; it < 8; ++it) {
+          const f32x4u v = *reinterpret_cast<const f32x4u *>(st + (rr + 4 * it) * kDwPitch + c4);
+          if (rowb + 4 * it < g.M) __builtin_nontemporal_store(v, reinterpret_cast<f32x4u *>(gf + (int64_t)(rowb + 4 * it) * g.N + colg));
+        }
+      } else {
+#pragma unroll
+        for (int it = 0; it < 8; ++it)
+#pragma unroll
+          for (int e = 0; e < 3; ++e)
+            if (rowb + 4 * it < g.M && colg + e < g.N) gf[(int64_t)(rowb + 4 * it) * g.N + colg + e] = st[(rr + 4 * it) * kDwPitch + c4 + e];
+      }
+      asm volatile("" ::: "memory");
+    }
+    if (g.bias_here && by == 0 && wy == 0 && n0 + wx * 64 < g.N) hidden_bias<true, false>(g, wk, n0 + wx * 64 + lane, 0, lane);
   }
   }   // tiles
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");     // the movers' last barrier
@@ -539,33 +602,12 @@ __global__ __launch_bounds__(kBlock, 2) void k_dw(const Mm5Args g) {
   if constexpr (R0 > 0) next_step();
 #pragma unroll
   for (int q = 0; q < R0; ++q) load(q);
-  // The tiles of the first 128 units also form the layer's bias gradient and its innovation, from the sums that the
-  // signals' launch left per band of 64 rows: 64 columns from cw on, one per lane, and a partial sum of the left-hand
-  // side of their own.  (A launch of its own cost 5 us.  One wavefront for 256 columns, with fewer partial sums: 784-500-10, B = 12:
+  // The tiles of the first 128 units also form the layer's bias gradient and its innovation.  (A launch of its own cost 5 us.  One wavefront for 256 columns, with fewer partial sums: 784-500-10, B = 12:
   // 81.1 -> 82.8 us per step, 3072-1024-1024-10: 608 -> 615.)  A workgroup's first tile does it while its operands are on their way, a later one before
   // its way out, when the stores of the tile before have drained.
   auto bias_part = [&](int wk, int bx) __attribute__((always_inline)) {
     const int cw = bx * BN + wx * 64;
-    if (cw >= g.N) return;
-    const int col = cw + lane0;
-    float dsum = 0.f;
-    if (col < g.N) {
-      const float *db = g.dbpart + (int64_t)wk * g.nband * g.N + col, *dd = g.ddbpart + (int64_t)wk * g.nband * g.N + col;
-      float gsum = 0.f;
-      for (int i = 0; i < (g.K + 63) / 64; ++i) {
-        gsum += db[(int64_t)i * g.N];
-        if constexpr (!PL) dsum += dd[(int64_t)i * g.N];
-      }
-      put_fresh_grad(s, wk, g.offb + col, gsum);
-      if (CADA1) {
-        fresh_innov(s, wk)[g.offb + col] = f2bf(dsum);
-        dsum -= bf2f(stored_innov(s, wk)[g.offb + col]);
-      }
-    }
-    if constexpr (!PL) {
-      const float totb = wave_sum(dsum * dsum);
-      if (lane0 == 0) s.lhs_part[(int64_t)wk * s.n_lhs_part + g.lhs_slot_b + 2 * bx + wx] = totb;
-    }
+    if (cw < g.N) hidden_bias<PL, CADA1>(g, wk, cw + lane0, g.lhs_slot_b + 2 * bx + wx, lane0);
   };
   if (g.bias_here && wy == 0) {
     const int trow = quotient(t_first, g.gx), wk = quotient(trow, g.gy);
@@ -1585,14 +1627,14 @@ void set_tiles(Mm5Args &g, int per_xcd) { g.gx = divisor((g.N + BN - 1) / BN); g
 // The (tensor count, product set) combinations the layers use.
 template <int EPI, int NA, int NB, bool HAS_D> hipError_t mm5_allow_lds() {
   return hipFuncSetAttribute(reinterpret_cast<const void *>(k_mm5<EPI, NA, NB, HAS_D>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)kMm5Lds);
+                             (int)mm5_lds_bytes(EPI));
 }
 template <int EPI, int NA, int NB, bool HAS_D> int launch_mm5_as(Ctx *c, Mm5Args &g) {
   // one workgroup per CU at most (8 XCDs x 32 CUs), each XCD's tiles dealt over its workgroups
   const int total = ((g.N + BN - 1) / BN) * ((g.M + BM - 1) / BM) * g.workers, per = (total + 7) / 8;
   set_tiles(g, per < 32 ? per : 32);
   const dim3 grid(8 * g.nbx.d);
-  hipLaunchKernelGGL((k_mm5<EPI, NA, NB, HAS_D>), grid, dim3(2 * kBlock), kMm5Lds, c->stream, g);
+  hipLaunchKernelGGL((k_mm5<EPI, NA, NB, HAS_D>), grid, dim3(2 * kBlock), mm5_lds_bytes(EPI), c->stream, g);
   return CADA_OK;
 }
 template <int NA, int NB, bool HAS_D, bool CADA1> int launch_dw_as(Ctx *c, Mm5Args &g) {
@@ -1641,6 +1683,18 @@ constexpr int64_t kSkinnyBlocks = 1024;
 static bool skinny_forward(const Mm5Args &g, int workers) {
   return g.M <= 32 || (int64_t)((g.M + 31) / 32) * ((g.N + 31) / 32) * workers <= kSkinnyBlocks;
 }
+// Weight gradients of the rules that read all of them back in the same step, stored ones beside fresh ones (k_lag_lhs).  When they outgrow the 256 MB of
+// memory-side cache it pays to write them past the caches: what k_dw's plain stores leave there is written back under that kernel's reads (3072-1024-10, 36 workers of 128
+// rows: 206 us, 175 with the other).  Stores of that kind keep k_dw's wavefronts, which load as well as store, waiting (163 us, 151 past the caches); in k_mm5
+// the moving wavefronts wait for nothing but loads (140).  Its way out costs more per tile, which few rows per tile do not make up for, least where
+// rows start on no line or no 16 bytes.  Measured, us per step, always-upload, k_dw / k_mm5: 3072-1024-10: 177 MB: 100 rows: 281 / 278; 215 MB: 64: 299 / 305, 100: 318 / 313;
+// 265 MB: 40: 342 / 343, 64: 347 / 344, 256: 503 / 474; 316 MB: 24: 392 / 394, 40: 392 / 388, 100: 427 / 397; 455 MB: 24: 517 / 518, 40: 575 / 552, 100: 629 / 565;
+// 100-1024-1024-10: 300 MB: 100: 552 / 506; 2000-1000-10: 320 MB: 64: 424 / 426, 100: 455 / 436; 450 MB: 40: 540 / 540, 100: 604 / 560; 1021-1021-1021-7:
+// 320 MB: 64: 481 / 489, 100: 507 / 490; 450 MB: 64: 611 / 626, 100: 657 / 619.  bf16 gradients (half the bytes, 8 instead of 16 per lane and row): k_dw.
+static bool dw_past_caches(const Mm5Args &g) {
+  const int64_t bytes = (int64_t)g.workers * g.s.ps * 4;
+  return g.s.gbuf16 == nullptr && bytes > 200000000 && bytes * g.K > (g.N % 32 == 0 ? 12000000000ll : 24000000000ll) && (g.N % 4 == 0 || g.K > 64);
+}
 // Returns CADA_OK after enqueueing the launch, CADA_EUNSUPPORTED (and launches nothing) when the
 // operands do not fit a compiled variant.
 template <int EPI> int launch_mm5(Ctx *c, Mm5Args &g, int workers) {
@@ -1681,7 +1735,7 @@ template <int EPI> int launch_mm5(Ctx *c, Mm5Args &g, int workers) {
   if (EPI == EPI_DW && (int64_t)((g.K + BK - 1) / BK) * BK > g.Bp) { set_error("internal: more rows than a worker's padded tile"); return CADA_EUNSUPPORTED; }
   if constexpr (EPI == EPI_DW) {
     const bool cada1 = g.s.rule == CADA_RULE_CADA1;
-    if (g.A.n == 2 && g.B.n == 2) return launch_dw_as<2, 2, false, false>(c, g);
+    if (g.A.n == 2 && g.B.n == 2) return dw_past_caches(g) ? launch_mm5_as<EPI, 2, 2, false>(c, g) : launch_dw_as<2, 2, false, false>(c, g);
     if (!has_d && g.A.n == 2 && g.B.n == 3) return cada1 ? launch_dw_as<2, 3, false, true>(c, g) : launch_dw_as<2, 3, false, false>(c, g);
     if (has_d && g.A.n == 3 && g.B.n == 4) return cada1 ? launch_dw_as<3, 4, true, true>(c, g) : launch_dw_as<3, 4, true, false>(c, g);
   } else {
@@ -1714,6 +1768,7 @@ int mlp_init_state(Ctx *c, const float *) {
   if (e == hipSuccess) e = mm5_allow_lds<EPI_FWD_HIDDEN, 4, 3, true>();
   if (e == hipSuccess) e = mm5_allow_lds<EPI_FWD_HIDDEN, 2, 2, false>();
   if (e == hipSuccess) e = mm5_allow_lds<EPI_DA, 2, 2, false>();
+  if (e == hipSuccess) e = mm5_allow_lds<EPI_DW, 2, 2, false>();
   if (e == hipSuccess) e = dw_allow_lds<2, 2, false, false>();
   if (e == hipSuccess) e = skinny_allow_lds<EPI_FWD_HIDDEN, 2, 2, false>();
   if (e == hipSuccess) e = skinny_allow_lds<EPI_FWD_HIDDEN, 2, 3, false>();

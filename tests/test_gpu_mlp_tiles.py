@@ -105,3 +105,25 @@ def test_order_of_the_bias_gradients_sums(B, dims, rule):
         assert np.abs(x).max() > 0 and (B < 33 or not np.array_equal(want, other)), "the case must tell orders apart"
         assert np.array_equal(got[off:off + b], want), (b, np.abs(got[off:off + b] - want).max(), int((got[off:off + b] != want).sum()))
         off += b + b * c
+
+
+@pytest.mark.parametrize("dims,B", [((100, 1024, 1000, 5), 90), ((100, 1021, 1003, 5), 180)], ids=["even", "odd"])
+def test_gradients_past_the_caches(dims, B):
+    """With 64 workers these 290 MB of gradients go past the caches (rules without a second gradient), with three they do not: another kernel, which adds the same
+    products up in the same order.  Forward products, whose order depends on the number of workers, are exact (see above)."""
+    M, some = 64, [0, 29, 63]
+    rng = np.random.default_rng(B)
+    X, y, theta = _exact_network(dims, M * B, rng)
+    X, y = X[1:].reshape(M, B, -1), y[1:].reshape(M, B)
+
+    def stored(X, y):
+        cfg = configs.CFG4.scaled(name="past_caches", layer_dims=dims, M=len(X), N_m=B, B=B, K=1, D=3, rule=configs.RULE_ALWAYS)
+        sched = np.tile(np.arange(B, dtype=np.int32), (1, len(X), 1))
+        out = run_library(cfg, (to_dev(X.reshape(-1, dims[0])), to_dev(y.reshape(-1)), to_dev(theta)), sched)
+        assert out["error_flags"][0] == 0
+        return out["stored"]
+
+    many, few = stored(X, y), stored(X[some], y[some])
+    assert np.isfinite(many).all() and all(np.abs(few[i]).max() > 0 for i in range(len(some)))
+    for i, m in enumerate(some):
+        assert np.array_equal(many[m], few[i]), (m, rel_l2(many[m], few[i]), int((many[m] != few[i]).sum()))
