@@ -83,5 +83,7 @@ def test_full_size_mlp_steps_match_stored_oracle(name):
         if 20.0 * probe[k] <= BF16_TOL:
             assert v <= BF16_TOL, (k, v)
     assert all(20.0 * probe[k] <= BF16_TOL for k in drift if k <= 8), "the bf16 tolerance must at least cover the first steps"
-    assert stats["theta_norm"] < 1e-2
+    # The norms of two vectors differ by no more than the vectors: where the oracle's own iterate moves by more than 1e-2 under that perturbation, no
+    # arithmetic keeps its norm to 1e-2 (the same sums in float32 in three orders and in double: 6e-4 to 2.3e-2 on the run whose yardstick is 0.47).
+    assert stats["theta_norm"] <= max(1e-2, probe[K])
     np.testing.assert_allclose(out["trace_rhs"][:9], g["rhs"][:9], rtol=BF16_TOL)      # (while the trajectories are still one)
