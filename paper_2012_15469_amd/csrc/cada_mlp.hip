@@ -217,7 +217,7 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
   bf16_t *lds = reinterpret_cast<bf16_t *>(smem_raw);
   constexpr int NS = NA + NB, NSLOT = kMm5Slots;
   constexpr bool PL = NB == 2, TR = EPI == EPI_DW;
-  static_assert(EPI == EPI_FWD_HIDDEN || EPI == EPI_DA || (TR && PL), "");
+  static_assert((EPI == EPI_FWD_HIDDEN || EPI == EPI_DA || (TR && PL)) && NB <= 3, "");
   static_assert(NSLOT >= 2 * NS, "the ring must hold two tile steps");
   const DevState &s = g.s;
   const bool mover = __builtin_amdgcn_readfirstlane((int)threadIdx.x) >= kBlock;   // uniform per wavefront
@@ -317,10 +317,10 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     auto slot_of = [&](int idx) __attribute__((always_inline)) { const int p = sb + idx; return lds + ((size_t)(p >= NSLOT ? p - NSLOT : p) << 12); };
     const bf16_t *tah = slot_of(g.a_h), *tal = slot_of(g.a_l), *tad = slot_of(HAS_D ? g.a_d : 0), *tar = slot_of(NA == 4 ? g.a_r : 0);
-    const bf16_t *tbh = slot_of(NA + g.b_h), *tbl = slot_of(NA + g.b_l), *tbx = slot_of(NA + (HAS_D && NB == 4 ? g.b_x : 0)), *tbd = slot_of(PL ? NA : NA + g.b_d);
+    const bf16_t *tbh = slot_of(NA + g.b_h), *tbl = slot_of(NA + g.b_l), *tbd = slot_of(PL ? NA : NA + g.b_d);
 #pragma unroll
     for (int ks = 0; ks < BK; ks += 16) {
-      bf16x8 ah[2], al[2], ad[2], ar[2], bh[2], bl[2], bx_[2], bd[2];
+      bf16x8 ah[2], al[2], ad[2], ar[2], bh[2], bl[2], bd[2];
       auto frag = [&](const bf16_t *slot, int half, int blk) __attribute__((always_inline)) -> bf16x8 {
         if constexpr (TR) return tr_fragment(slot + (half * 2 + blk) * 1024 + ks * 32, fro_tr);
         else return *reinterpret_cast<const bf16x8 *>(slot + (half * 64 + blk * 32) * BK + (fro ^ ks));
@@ -338,11 +338,6 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
       for (int j = 0; j < 2; ++j) {
         bh[j] = frag(tbh, wx, j);
         bl[j] = frag(tbl, wx, j);
-        // with fewer than four B tensors the single-bf16 operand is the hi part itself
-        if constexpr (HAS_D) {
-          if constexpr (NB == 4) bx_[j] = frag(tbx, wx, j);
-          else bx_[j] = bh[j];
-        }
         if constexpr (!PL) bd[j] = frag(tbd, wx, j);
       }
 #pragma unroll
@@ -352,7 +347,7 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
           acc1[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[i], bh[j], acc1[i][j], 0, 0, 0);
           acc1[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[i], bl[j], acc1[i][j], 0, 0, 0);
           acc1[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[i], bh[j], acc1[i][j], 0, 0, 0);
-          if constexpr (HAS_D) acc2[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ad[i], bx_[j], acc2[i][j], 0, 0, 0);
+          if constexpr (HAS_D) acc2[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ad[i], bh[j], acc2[i][j], 0, 0, 0);      // (against the hi part)
           if constexpr (!PL) acc2[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ar[i], bd[j], acc2[i][j], 0, 0, 0);
         }
     }
@@ -1361,8 +1356,8 @@ void layout(MlpPlan &P, const cada_config *cfg, int64_t total_rows, Carve &w) {
 }
 }  // namespace
 
-// Number of partial sums of the left-hand side per worker (one per weight-gradient tile and
-// per 256 biases).
+// Number of partial sums of the left-hand side per worker (four per weight-gradient tile, one per
+// bias_cols biases).
 int mlp_lhs_slots(const cada_config *cfg, int bias_cols) {
   int slot = 0;
   for (int l = 1; l <= cfg->n_layers; ++l)
@@ -1710,7 +1705,7 @@ template <int EPI> int launch_mm5(Ctx *c, Mm5Args &g, int workers) {
         return CADA_EUNSUPPORTED;
       }
       if (g.A.n == 2 && g.B.n == 2) return launch_skinny_as<EPI, 2, 2, false>(c, g);
-      if (EPI == EPI_DW) {
+      if constexpr (EPI == EPI_DW) {
         if (!has_d && g.A.n == 2 && g.B.n == 3) return launch_skinny_as<EPI, 2, 3, false>(c, g);
         if (has_d && g.A.n == 3 && g.B.n == 4) return launch_skinny_as<EPI, 3, 4, true>(c, g);
       } else {
