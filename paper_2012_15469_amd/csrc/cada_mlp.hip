@@ -1671,9 +1671,10 @@ template <int EPI, int NA, int NB, bool HAS_D> int launch_skinny_as(Ctx *c, Mm5A
 // Hidden layers' forward products go through k_skinny while its 32 x 32 blocks fill the chip (two workgroups per CU) at most twice
 // over, or a worker has a single block of rows (a 128 x 128 tile would then be three quarters padding).  Few tiles leave CUs
 // idle and run through the whole inner dimension one after the other, where k_skinny splits it over eight wavefronts.
-// Measured, us per step with k_skinny and with k_mm5: 784-500-10, M = 10, B = 12: 82, 103; M = 64: 149, 160; 617-301-150-26, M = 24,
-// B = 100: 160, 177; 3072-1024-1024-10, M = 16, B = 64: 468, 494; 3072-1024-10, M = 64, B = 12: 849, 889; above:
-// 784-512-10, M = 60, B = 60 (1920 blocks): 163, 157.
+// Measured, us per step with k_skinny and with k_mm5, CADA2: 784-500-10, M = 10: B = 33: 74.7, 89.1, 128 (640 blocks): 85.6, 95.0, 200 (1120): 105.0, 104.4;
+// M = 64: B = 20: 123, 131, 64 (2048): 152, 144; 784-512-10, M = 30: B = 64 (960): 101, 107, 96 (1440): 121, 116; 3072-1024-10, M = 16: B = 48 (1024): 354, 337, 64: 368,
+// 367, 96 (1536): 439, 389; 100-300-10, M = 60: B = 64 (1200): 74.0, 74.4, 96 (1800): 83.6, 79.3; 2000-130-10, M = 40: B = 128 (800): 168, 171, 200 (1400): 226, 203.
+// The always-upload rule: the same sides.
 constexpr int64_t kSkinnyBlocks = 1024;
 static bool skinny_forward(const Mm5Args &g, int workers) {
   return g.M <= 32 || (int64_t)((g.M + 31) / 32) * ((g.N + 31) / 32) * workers <= kSkinnyBlocks;
@@ -1864,11 +1865,12 @@ static int mlp_forward(Ctx *c, MlpPlan &P, const DevState &s, const int32_t *idx
   return CADA_OK;
 }
 
-// Whether a layer's weight-gradient launch also forms its bias gradient.  That saves a launch of 5 us, but a tile that does it waits for its own
-// stores first (some 8 us), which counts where a workgroup has several such tiles, or few workgroups have one and the others wait for them.
-// us per step inside / outside, CADA2, B = 128: 784-512-10: M = 64 (256 such tiles): 0.987, 200 (800): 1.017; 617-301-150-26:
-// M = 100 (300): 0.983; 1024-1024-32: M = 32 (256, M din = 32768): 0.992, 64: 1.016, 200: 1.049; 2000-64-5: M = 32 (32, 64000):
-// 0.989, 64: 1.012, 200: 1.035; 3072-1024-10: M = 16: 1.000, 64: 1.014.  (Up to 32 units k_skinny forms the weight gradient.)
+// Whether a layer's weight-gradient launch also forms its bias gradient.  That saves a launch of 5 us.  In k_dw a workgroup's first tile does it under its operands' way,
+// a later one in front of its way out, which then starts by the latency of those sums later; with many such tiles, or few workgroups that have
+// one, that costs as much as it saves.  us per step inside / outside (122 shapes, 12 to 256 rows, three rules): up to the lines below 0.955 to 1.002; beyond them 0.966 to 1.032:
+// 784-512-10: M = 64 (256 such tiles): 0.978 - 0.997, M = 200 (800): 0.986 - 0.999; 200-1000-10, M = 100 (800): 0.982 - 1.019; 1024-1024-32: M = 32 (256, M din = 32768):
+// 0.98 - 1.002, 64 (512, 65536): 0.997 - 1.013, 100: 1.005 - 1.032; 2000-64-5: M = 64 (64, 128000): 0.974 - 0.991, 200: 0.983 - 1.016; 300-128-10, M = 250 (250, 75000):
+// 0.966 - 0.999.  (Up to 32 units k_skinny forms the weight gradient.)
 static bool bias_inside(int M, int din, int dout) {
   return dout > 32 && (int64_t)M * tiles128(dout) <= 512 && (int64_t)M * din < 65536;
 }

@@ -457,9 +457,10 @@ int64_t eval_reads(const MlpPlan &P, int l, int u) { return P.total_rows * eval_
 
 // One launch takes a row through all layers; the choice of the tile minimises rounds of tiles over the CUs times the time of a tile.  But few
 // rows leave CUs idle and pass every tile of units one after the other: there a launch per layer (some 6000 cycles each) puts the tiles
-// of units side by side.  Measured, us in one launch / by layers (and the chunks of minibatches that both replaced): 3072-1024-1024-10: 100 rows:
-// 470 / 127 (330), 6000: 470 / 195, 20000: 855 / 618; 784-512-10: 64: 64 / 37 (101), 16000: 72 / 71, 40000: 130 / 160; 1024-1024-32: 100: 134 / 43
-// (70); 100-1000-10: 20000: 57 / 71.
+// of units side by side.  Measured, us in one launch / by layers, each with its best tile: 3072-1024-1024-10: 100 rows: 436 / 106, 5000: 439 / 164, 16000: 603 / 381, 40000:
+// 1575 / 948; 784-512-10: 100: 64 / 33, 16000: 66 / 55, 40000: 114 / -; 1024-1024-32: 100: 134 / 40, 16000: 139 / 110; 100-1000-10: 16000: 46 / 44; 64-1024-32: 5000: 40 / 30; a
+// network of few units: 57-193-470-12: 100: 40 / 31, 16000: 43 / 49.  The model takes the better one except near the line: 617-301-150-26, 40000 rows: 163 (136 by layers);
+// 1500-700-10, 16000: 145 (132); 2000-129-7, 5000: 69 (57); 57-193-470-12, 1500: 40 (31).
 EvalPlan eval_plan(const MlpPlan &P) {
   const int hidden = P.L > 1 ? P.L - 1 : 1;
   EvalPlan one{1, 1, false}, layers{1, 1, true};
