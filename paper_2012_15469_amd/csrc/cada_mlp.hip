@@ -944,9 +944,9 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
       }
     }
     const int fro_tr = (8 * (lane >> 5) + ((lane & 15) >> 2)) * 32 + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-    // A band of 64 rows is two steps, which two wavefronts have (in the same round, or the last one and, a round later, the first): the one hands on its sums over
-    // the first 32 rows, and the other, whose values wait in its area, goes on from there.  What a round leaves is overwritten three rounds
-    // later, two barriers behind its reader.
+    // A band of 64 rows is two steps, which two wavefronts have (in the same round, or the last one and, a round later, the first): the one hands its sums over
+    // the first 32 rows on, and the other goes on from there behind the round's barrier, under its conversions.  (Its values left in LDS until then and added up at the end: 784-512-10, 64 workers of
+    // 128 rows: 22.5 us, now 21.6; with sums per 32 rows, another order: 21.1.)  What a round leaves is overwritten three rounds later, two barriers behind its reader.
     float2 *const half_sums = reinterpret_cast<float2 *>(smem_raw + nsw * (7 * 2048));     // [3][nsw][64 lanes]
     const bool signals = (PL || HAS_D) && g.w_h != nullptr;
     auto put_band = [&](int kc, float2 v) __attribute__((always_inline)) {
@@ -959,8 +959,11 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
       }
     };
     for (int round = 0, kc = w; round * nsw < nk; ++round, kc += nsw) {
-      const bool mine = w < nsw && kc < nk;
-      if (mine) {
+      auto meet = [&]() __attribute__((always_inline)) { if (signals && nk > 1) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+      if (w >= nsw || kc >= nk) {               // (uniform: a wavefront without a step in this round)
+        meet();
+        continue;
+      }
       u32x4 v[NA + NB][2];
 #pragma unroll
       for (int sl = 0; sl < NA + NB; ++sl) {
@@ -1011,16 +1014,28 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
           const uint16_t *mb = reinterpret_cast<const uint16_t *>(g.maskbits + ((((int64_t)wk * ((g.K + BM - 1) / BM) + (kc >> 2)) * ((g.M + BN - 1) / BN) + (m0 >> 7)) * kBlock +
                                                                                 (((kc >> 1) & 1) * 2 + ((m0 >> 6) & 1)) * 64 + lane) * 2) + (kc & 1) * 2 + ((m0 >> 5) & 1);
           const uint32_t on = mb[0], on_ref = PL ? 0u : mb[4];
+          // the values at theta and at the reference point
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const bool live = m0 + (lane & 31) < g.M && 32 * kc + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3) < g.K;
+            const float x = live && ((on >> r) & 1) ? c1[r] : 0.f;
+            c2[r] = live && ((on_ref >> r) & 1) ? c1[r] - c2[r] : 0.f;
+            c1[r] = x;
+          }
+          float2 sum = make_float2(0.f, 0.f);
+          if (!(kc & 1)) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) { sum.x += c1[r]; sum.y += c1[r] - c2[r]; }
+            if (kc + 1 < nk) half_sums[((round % 3) * nsw + w) * 64 + lane] = sum;
+          }
+          meet();
+          if (kc & 1) sum = half_sums[(w > 0 ? (round % 3) * nsw + w - 1 : ((round + 2) % 3) * nsw + nsw - 1) * 64 + lane];
+          const float2 first = sum;
 #pragma unroll
           for (int r = 0; r < 16; r += 2) {
-            float x[2], xr[2];
+            const float x[2] = {c1[r], c1[r + 1]}, xr[2] = {c2[r], c2[r + 1]};
 #pragma unroll
-            for (int e = 0; e < 2; ++e) {
-              const bool live = m0 + (lane & 31) < g.M && 32 * kc + 8 * (r >> 2) + 4 * (lane >> 5) + ((r + e) & 3) < g.K;
-              x[e] = live && ((on >> (r + e)) & 1) ? c1[r + e] : 0.f;
-              xr[e] = live && ((on_ref >> (r + e)) & 1) ? c1[r + e] - c2[r + e] : 0.f;
-              c1[r + e] = x[e]; c2[r + e] = x[e] - xr[e];
-            }
+            for (int e = 0; e < 2; ++e) { sum.x += x[e]; sum.y += x[e] - xr[e]; }
             const uint32_t vh = f2bf_pk(x[0], x[1]), vr = f2bf_pk(xr[0], xr[1]), vd = f2bf_pk(x[0] - xr[0], x[1] - xr[1]);
             const uint32_t vl = f2bf_pk(x[0] - __uint_as_float(vh << 16), x[1] - __uint_as_float(vh & 0xffff0000u));
 #pragma unroll
@@ -1039,39 +1054,11 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
 #pragma unroll
               for (int hh = 0; hh < 2; ++hh) *reinterpret_cast<u32x4 *>(dst[b] + out + (hh * 64 + lane) * 8) = *reinterpret_cast<const u32x4 *>(area + b * 1024 + (hh * 64 + lane) * 8);
             }
-          if (kc & 1) {
-            asm volatile("" ::: "memory");
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              v4s *at = reinterpret_cast<v4s *>(area) + q * 64 + lane;
-              at[0] = v4s{c1[4 * q], c1[4 * q + 1], c1[4 * q + 2], c1[4 * q + 3]};
-              if constexpr (!PL) at[256] = v4s{c2[4 * q], c2[4 * q + 1], c2[4 * q + 2], c2[4 * q + 3]};
-            }
-          } else {
-            float2 v = make_float2(0.f, 0.f);
-#pragma unroll
-            for (int r = 0; r < 16; ++r) { v.x += c1[r]; v.y += c2[r]; }
-            if (kc + 1 < nk) half_sums[((round % 3) * nsw + w) * 64 + lane] = v;
-            else put_band(kc, v);
-          }
+          if (kc & 1) put_band(kc, sum);
+          else if (kc + 1 == nk) put_band(kc, first);
         }
       }
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the fragments are in registers before the area is written again
-      }
-      if (signals && nk > 1) {
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        if (mine && (kc & 1)) {
-          float2 v = half_sums[(w > 0 ? (round % 3) * nsw + w - 1 : ((round + 2) % 3) * nsw + nsw - 1) * 64 + lane];
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const v4s *at = reinterpret_cast<const v4s *>(area) + q * 64 + lane;
-            const v4s x = at[0];
-            v.x += x.x; v.x += x.y; v.x += x.z; v.x += x.w;
-            if constexpr (!PL) { const v4s d = at[256]; v.y += d.x; v.y += d.y; v.y += d.z; v.y += d.w; }
-          }
-          put_band(kc, v);
-        }
-      }
     }
     __syncthreads();                                         // the areas are done with: `red` lies over them
   } else {
@@ -1662,7 +1649,7 @@ template <int EPI, int NA, int NB, bool HAS_D> int launch_skinny_as(Ctx *c, Mm5A
   const unsigned extra = (EPI == EPI_DW && g.lastb != nullptr) ? 1u : 0u;      // (the workgroup that finishes the last layer's bias gradient)
   // A weight gradient's way out is spread over four wavefronts at least where the CUs have room for them (with one, 120-80-60-5, 8 workers of 40
   // rows: 12.7 us, now 10.3); with more than two workgroups per CU, whose registers they take, over those of the products (784-512-10, 64 workers of 128 rows:
-  // 22.6 us with two, 24 with four).
+  // four wavefronts 1.4 us slower than two).
   const int wide = EPI == EPI_DW && nw < 4 && (int64_t)((g.M + 31) / 32 + extra) * g.workers <= 512 ? 4 : nw;
   hipLaunchKernelGGL((k_skinny<EPI, NA, NB, HAS_D>), dim3((unsigned)((g.M + 31) / 32) + extra, g.workers, EPI == EPI_FWD_HIDDEN ? (unsigned)((g.N + 31) / 32) : 1u),
                      dim3(64 * wide), skinny_lds_bytes(EPI, nw), c->stream, g);
