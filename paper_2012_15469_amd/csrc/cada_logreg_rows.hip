@@ -399,12 +399,16 @@ __global__ __launch_bounds__(R_NT) void k_rows(const RowsArgs a) {
 
 // Rows of more than 8192 columns: a workgroup still takes whole rows (z and dz need no other workgroup, hence no cooperative launch and
 // no exchange, which cost the cluster kernel of cada_logreg_fused.hip some 50 us per step whatever the size), CW quads of each per lane.
-// What bounds it: HBM, at 4.2-5.3 TB/s, and 8 us of operands and sums at the two ends.  Measured per step, two passes or the cluster
-// kernel before: M = 37, B = 75, p = 20001, CADA1: 117 -> 79 us; p = 20000: 114 -> 77; M = 8, B = 256, p = 8196: 117 -> 39;
-// M = 100, B = 256, p = 20000 (2 GB of rows): 391 -> 387.  Rows without the non-temporal hint: 81, 79, 39, 433.
+// What bounds it: HBM, at 5.9 TB/s in long shares, and some 7 us of operands and sums at the two ends (a CU takes 64 bytes per cycle: 320 KB of theta,
+// theta_lo and the reference point for 20480 columns are 2.5 us).  Measured per step, two passes or the cluster
+// kernel in place of these launches: M = 37, B = 75, p = 20001, CADA1: 117 -> 66 us; M = 8, B = 256, p = 8196: 117 -> 35;
+// M = 100, B = 256, p = 20480 (2.1 GB of rows): 391 -> 356.  Rows without the non-temporal hint, the last of these: 433 (387 with it then).
+// The operands' latency is paid once: asked for piece by piece as the registers of the piece before fell free (with 28 to 40 bytes of them spilled, whose
+// reloads drained the rows in flight), p = 20001: 73.8 us, now 66.3; p = 12001: 57.5, 48.6; p = 20480, M = 100, B = 256: 381, 356.
 // All workers' rows, one after the other, are cut into one share per workgroup (wide_split); a share that crosses from one worker to
-// the next starts new sums there (wide_slot), and k_rows_sum adds a worker's slots up, one block per 1024 columns.  RB rows are worked on together, and the next RB asked for before;
-// the compiled loop waits for all loads once per two batches.
+// the next starts new sums there (wide_slot), and k_rows_sum adds a worker's slots up, one block per 1024 columns.  RB rows are worked on together, and the next RB asked for when
+// these have landed.  (Two batches in flight, a batch's registers asked for again right after its products: the rows of all CUs then share the memory and the one that is waited
+// for comes later: p = 20001: 69.4 us for 66.3, p = 15000, M = 100, B = 64: 96.4 for 88.1, p = 20480, M = 100, B = 256: 355 for 356.)
 // DL: theta - theta_ref lies in LDS (the registers of 512 threads hold four vectors of 20480 columns and the rows in flight, not
 // five).  SEG: shares may meet several workers (up to 14336 columns: the loop over them costs wider rows registers, 51 -> 59 us).
 // dynamic LDS: row offsets int64 [rows], labels [rows] (rounded up to four rows), with DL theta - theta_ref [CW][512] quads
@@ -421,63 +425,96 @@ __global__ __launch_bounds__(R_NT) void k_rows_wide(const RowsArgs a) {
   __shared__ float red_s[2][R_NW][NV];
 
   const int f0 = wide_first(a.wide, blockIdx.x), nr = wide_first(a.wide, blockIdx.x + 1) - f0;        // this share's rows
-  for (int b = tid; b < nr; b += R_NT) {
+  // Everything that depends on nothing is asked for at once: this thread's sampled row and its worker's first row, theta, theta_lo, the reference point.
+  struct Sample { int64_t base, n; int32_t r; };
+  auto ask_row = [&](int b) __attribute__((always_inline)) {
     const int m = (f0 + b) / s.B;
-    const int64_t base = s.row_off[m], n_m = s.row_off[m + 1] - base;
-    int64_t r = a.idx[f0 + b];
+    return Sample{s.row_off[m], s.row_off[m + 1], a.idx[f0 + b]};
+  };
+  auto row_of = [&](int b, const Sample &x) __attribute__((always_inline)) {          // global row of the share's b-th
+    const int64_t n_m = x.n - x.base;
+    int64_t r = x.r;
     if (r < 0 || r >= n_m) { atomicOr(s.err, 1u); r = r < 0 ? 0 : n_m - 1; }
-    off_s[b] = (base + r) * s.p;
-    y_s[b] = static_cast<const float *>(s.y)[base + r];
-  }
-  lds_sync();
+    off_s[b] = (x.base + r) * s.p;
+    return x.base + r;
+  };
+  const Sample first = ask_row(min(tid, nr - 1));
+  auto delay_of = [&](int m) __attribute__((always_inline)) { return s.rule == CADA_RULE_CADA2 ? s.tau[m] : 0; };
+  const int m_first = __builtin_amdgcn_readfirstlane(f0 / s.B);
+  const int32_t tau_first = delay_of(m_first);
   // columns as in k_rows: the quad that would reach past p ends at p, its first `dup` columns belong to the quad before
-  int j0 = (w * CW * kWave + lane) * 4;
-  uint32_t jb[CW];                                     // byte offsets
-  auto quad = [](const float *x, uint32_t off) __attribute__((always_inline)) { return *reinterpret_cast<const v4u *>(reinterpret_cast<const char *>(x) + off); };
+  // (buffer accesses: a uniform base and a 32-bit byte offset per lane, formed where it is used; as global accesses the compiled kernel kept
+  // 64-bit offsets of all pieces and spilled)
+  const uint32_t j_most = (uint32_t)(p - 4) * 4u;
+  auto here = [&]() __attribute__((always_inline)) { int ln = lane; asm volatile("" : "+v"(ln)); return (uint32_t)(w * CW * kWave + ln) * 16u; };
+  const uint32_t jl = here();
+  auto piece = [&](uint32_t j, int i) __attribute__((always_inline)) { return min(j + (uint32_t)i * (16u * kWave), j_most); };
+  auto vec = [&](const float *x) __attribute__((always_inline)) { return far_buffer(const_cast<float *>(x), p); };
+  auto quad = [](__amdgpu_buffer_rsrc_t x, uint32_t off) __attribute__((always_inline)) { return __builtin_bit_cast(v4s, __builtin_amdgcn_raw_buffer_load_b128(x, off, 0, 0)); };
+  constexpr int kNt = 2;                               // the non-temporal bit of a buffer access
   float th[CW][4], dd[DL ? 1 : CW][4], g[CW][4], iv[CW][4];
-  v4u x[2][RB][CW];
+  v4s x0[RB][CW], x1[RB][CW], lo[CW], rh[CW], rl[CW];
+  // theta_lo and the reference point of a worker, all asked for before the first is used, and before the rows: behind the first batch their data wait
+  // for its latency (p = 18000, M = 16, B = 64: 40.0 us for 39.2, and no better with half of them in front)
+  auto ask_operands = [&](int32_t tau) __attribute__((always_inline)) {
+    const RefPtr ref = theta_ref_at(s, tau, s.k);
+    const uint32_t j = here();
+#pragma unroll
+    for (int i = 0; i < CW; ++i) { lo[i] = quad(vec(s.theta_lo), piece(j, i)); rh[i] = quad(vec(ref.hi), piece(j, i)); rl[i] = quad(vec(ref.lo), piece(j, i)); }
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
 #pragma unroll
   for (int i = 0; i < CW; ++i) {
-    jb[i] = (uint32_t)min(j0 + i * (4 * kWave), p - 4) * 4u;
-    const v4u t4 = quad(s.theta, jb[i]);
+    const v4s t4 = quad(vec(s.theta), piece(jl, i));
 #pragma unroll
     for (int e = 0; e < 4; ++e) th[i][e] = t4[e];      // (zero in the columns of another quad: see below)
   }
+  // (labels are asked for behind the rows' offsets and put into LDS behind the first rows' loads: the products' barriers stand between that and their use)
+  ask_operands(__builtin_amdgcn_readfirstlane(tau_first));
+  int64_t row0 = first.base;
+  if (tid < nr) row0 = row_of(tid, first);
+  for (int b = tid + R_NT; b < nr; b += R_NT) y_s[b] = static_cast<const float *>(s.y)[row_of(b, ask_row(b))];
+  const float label = static_cast<const float *>(s.y)[row0];
+  lds_sync();
   int seg = 0, end;                                    // rows of the worker that is worked on
-  auto load = [&](v4u (&xb)[RB][CW], int b0) __attribute__((always_inline)) {      // rows b0 .. b0 + RB - 1 (past the end: theta, with weight zero)
+  auto load = [&](v4s (&xb)[RB][CW], int b0) __attribute__((always_inline)) {      // rows b0 .. b0 + RB - 1 (past the end: zeros, of a buffer without bytes)
+    const uint32_t j = here();
 #pragma unroll
     for (int q = 0; q < RB; ++q) {
       const int64_t o = off_s[min(b0 + q, end - 1)];
       const float *row = s.X + (((int64_t)__builtin_amdgcn_readfirstlane((uint32_t)(o >> 32)) << 32) | __builtin_amdgcn_readfirstlane((uint32_t)o));
-      if (b0 + q >= end) row = s.theta;
 #pragma unroll
-      for (int i = 0; i < CW; ++i) xb[q][i] = __builtin_nontemporal_load(reinterpret_cast<const v4u *>(reinterpret_cast<const char *>(row) + jb[i]));
+      for (int i = 0; i < CW; ++i) xb[q][i] = __builtin_bit_cast(v4s, __builtin_amdgcn_raw_buffer_load_b128(far_buffer(const_cast<float *>(row), b0 + q < end ? p : 0), piece(j, i), 0, kNt));
     }
   };
   const float invB = 1.0f / (float)s.B;
-  auto work = [&](v4u (&xb)[RB][CW], int b0, int it) __attribute__((always_inline)) {
+  auto work = [&](v4s (&xb)[RB][CW], int b0, int it) __attribute__((always_inline)) {
+    int ln = lane;
+    asm volatile("" : "+v"(ln));                       // (what follows from it is formed here each time: registers)
     float zd[NV];
 #pragma unroll
     for (int q = 0; q < NV; ++q) zd[q] = 0.f;
 #pragma unroll
     for (int i = 0; i < CW; ++i) {
       v4s d4;
-      if constexpr (DL) d4 = d_s[i * R_NT + tid];
+      if (CW >= 10 && i > 0 && i % 3 == 0) __builtin_amdgcn_sched_barrier(0);      // (three quads of the difference at a time: registers)
+      if constexpr (DL) d4 = d_s[i * R_NT + w * kWave + ln];
       else d4 = v4s{dd[i][0], dd[i][1], dd[i][2], dd[i][3]};
 #pragma unroll
       for (int q = 0; q < RB; ++q)
 #pragma unroll
         for (int e = 0; e < 4; ++e) { zd[2 * q] = fmaf(xb[q][i][e], th[i][e], zd[2 * q]); zd[2 * q + 1] = fmaf(xb[q][i][e], d4[e], zd[2 * q + 1]); }
     }
-    float mine = row_sums<NV>(zd, lane);
-    const int v = row_sums_index<NV>(lane);
-    if (row_sums_owner<NV>(lane)) red_s[it & 1][w][v] = mine;
+    float mine = row_sums<NV>(zd, ln);
+    const int v = row_sums_index<NV>(ln);
+    if (row_sums_owner<NV>(ln)) red_s[it & 1][w][v] = mine;
     lds_sync();
     mine = 0.f;
 #pragma unroll
     for (int i = 0; i < R_NW; ++i) mine += red_s[it & 1][i][v];
     const float other = dpp_of<0xB1>(mine);
-    const bool odd = lane & 1;
+    const bool odd = ln & 1;
     const int b = b0 + (v >> 1);
     const float z = odd ? other : mine, dz = odd ? mine : other;
     const float y = y_s[min(b, end - 1)];
@@ -497,51 +534,59 @@ __global__ __launch_bounds__(R_NT) void k_rows_wide(const RowsArgs a) {
   };
   int it = 0;
   do {
-    if constexpr (SEG) asm volatile("" : "+v"(j0));    // (what follows from it is formed here each time: registers)
-    const int m = (f0 + seg) / s.B;
+    const int m = __builtin_amdgcn_readfirstlane((f0 + seg) / s.B);
     end = min(nr, (m + 1) * s.B - f0);
-    const RefPtr ref = theta_ref(s, m, s.k);
-    load(x[0], seg);
+    int b = seg;
+    load(x0, b);
+    if (seg == 0 && tid < nr) y_s[tid] = label;
+    uint32_t j = here();
 #pragma unroll
     for (int i = 0; i < CW; ++i) {
-      if (SEG && i == (CW + 1) / 2) asm volatile("" ::: "memory");      // (half of the operands at a time: registers)
-      const v4u l4 = quad(s.theta_lo, jb[i]), rh = quad(ref.hi, jb[i]), rl = quad(ref.lo, jb[i]);
-      const int dup = j0 + i * (4 * kWave) - (int)(jb[i] >> 2);
+      const int dup = (int)(j + (uint32_t)i * (16u * kWave) - piece(j, i)) >> 2;
       v4s d4;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        d4[e] = e >= dup ? (th[i][e] - rh[e]) + (l4[e] - rl[e]) : 0.f;
+        d4[e] = e >= dup ? (th[i][e] - rh[i][e]) + (lo[i][e] - rl[i][e]) : 0.f;
         if (e < dup) th[i][e] = 0.f;
         if constexpr (!DL) dd[i][e] = d4[e];
         g[i][e] = iv[i][e] = 0.f;
       }
       if constexpr (DL) d_s[i * R_NT + tid] = d4;              // (read back by this lane only)
     }
-    // (no branch around the loads past the end: their registers then stay in place)
-    for (int b = seg; b < end; b += 2 * RB, it += 2) {
-      load(x[1], b + RB);
-      work(x[0], b, it);
+    // (no branch around the loads: their registers then stay in place)
+    for (;; b += 2 * RB) {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      load(x1, b + RB);
+      work(x0, b, it++);
+      load(x0, b + 2 * RB);
       if (b + RB >= end) break;
-      load(x[0], b + 2 * RB);
-      work(x[1], b + RB, it + 1);
+      work(x1, b + RB, it++);
+      if (b + 2 * RB >= end) break;
     }
-    float *pg = a.part + (int64_t)(SEG ? wide_slot(a.wide, blockIdx.x, m) : (int)blockIdx.x) * 2 * ps;
+    const __amdgpu_buffer_rsrc_t pg = far_buffer(a.part + (int64_t)(SEG ? wide_slot(a.wide, blockIdx.x, m) : (int)blockIdx.x) * 2 * ps, 2 * ps);
+    j = here();
 #pragma unroll
     for (int i = 0; i < CW; ++i) {
-      const int dup = j0 + i * (4 * kWave) - (int)(jb[i] >> 2);
-      float *q = reinterpret_cast<float *>(reinterpret_cast<char *>(pg) + jb[i]);
+      const uint32_t at = piece(j, i);
+      const int dup = (int)(j + (uint32_t)i * (16u * kWave) - at) >> 2;
       if (dup == 0) {
-        *reinterpret_cast<v4s *>(q) = v4s{g[i][0], g[i][1], g[i][2], g[i][3]};
-        *reinterpret_cast<v4s *>(q + ps) = v4s{iv[i][0], iv[i][1], iv[i][2], iv[i][3]};
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4s, v4s{g[i][0], g[i][1], g[i][2], g[i][3]}), pg, at, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4s, v4s{iv[i][0], iv[i][1], iv[i][2], iv[i][3]}), pg, at, ps * 4, 0);
       } else {
 #pragma unroll
         for (int e = 1; e < 4; ++e)
-          if (e >= dup) { q[e] = g[i][e]; q[ps + e] = iv[i][e]; }
+          if (e >= dup) {
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(g[i][e]), pg, at + 4 * e, 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(iv[i][e]), pg, at + 4 * e, ps * 4, 0);
+          }
       }
     }
     seg = end;
     // (the next worker's first rows may use the exchange buffer of this one's last ones, which a slower wavefront still reads)
-    if (SEG && seg < nr) lds_sync();
+    if (SEG && seg < nr) {
+      ask_operands(__builtin_amdgcn_readfirstlane(delay_of(m + 1)));
+      lds_sync();
+    }
   } while (SEG && seg < nr);
 }
 
