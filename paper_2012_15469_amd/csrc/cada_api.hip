@@ -200,7 +200,9 @@ size_t state_bytes(const cada_config *cfg, const Geometry &g) {
 void carve_logreg_scratch(Carver &w, const cada_config *cfg, Ctx *c) {
   float *rows_part = w.take<float>(rows_part_floats(cfg));
   uint32_t *rows_count = w.take<uint32_t>(kCountWords * (1 + (size_t)cfg->M));      // (zero between launches)
+  char *rule_room = w.take<char>(rule_in_bytes(cfg->M));
   if (!c) return;
+  c->rule_room = rule_room;
   c->rows_part = rows_part;
   c->rows_count = rows_count;
 }

@@ -43,6 +43,10 @@ struct DevState {
   float *lhs_part;        // [M][n_lhs_part] partial sums of the left-hand side
   uint8_t *mask;          // [M]
   float *ring;            // [d_max]
+  // Where an earlier launch of the step takes the rule's inputs down (rule_inputs, cada_rule.h; else null), so that the server's workgroups can all run the rule: the right-hand
+  // side, and the workers' delays and buffer selectors [2][M] as they were
+  double *rule_rhs;
+  int32_t *rule_in;
   float *ring_part;       // [n_ring_part] per-block partial sums of the last squared step,
                           // folded into ring[(k-1) mod d_max] by the next rule kernel
   uint64_t *uploads;
@@ -145,6 +149,29 @@ __device__ __forceinline__ double lane_f64(double x, int lane) {
 __device__ __forceinline__ double wave_sum_f64(double v) {
   v = dpp_add_f64<0xB1>(v); v = dpp_add_f64<0x4E>(v); v = dpp_add_f64<0x124>(v); v = dpp_add_f64<0x128>(v);
   return (lane_f64(v, 0) + lane_f64(v, 16)) + (lane_f64(v, 32) + lane_f64(v, 48));
+}
+
+// Sums over the 64 lanes of eight values at once (as row_sums below, in double): lane l receives the sum of value (l & 3) + 4 (l >> 5), lanes with
+// (l & 28) == 0 hold each value once.
+template <int CTRL>
+__device__ __forceinline__ double dpp_of_f64(double x) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xF, 0xF, true), hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xF, 0xF, true);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double eight_sums_f64(const double (&v)[8], int lane) {
+  const bool o1 = lane & 1, o2 = lane & 2, hf = lane & 32;
+  double a[4], b[2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) a[i] = (o1 ? v[2 * i + 1] : v[2 * i]) + dpp_of_f64<0xB1>(o1 ? v[2 * i] : v[2 * i + 1]);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    b[i] = (o2 ? a[2 * i + 1] : a[2 * i]) + dpp_of_f64<0x4E>(o2 ? a[2 * i] : a[2 * i + 1]);
+    b[i] = dpp_add_f64<0x124>(b[i]);
+    b[i] = dpp_add_f64<0x128>(b[i]);
+  }
+  const double c = (hf ? b[1] : b[0]) + __shfl_xor(hf ? b[0] : b[1], 32, 64);
+  return c + __shfl_xor(c, 16, 64);
 }
 
 // (An asm block that sets m0 says so, as the compiler uses that register for LDS operations of its own; it warns that the register is reserved.)
@@ -264,6 +291,7 @@ struct Ctx {
   int64_t chunk_cols;
   float *zpart;              // [M][B][n_col_chunks][2]
   int n_server_blocks;
+  int decide;                // the server's workgroups run the rule (k_server<., true>)
   int ring_cap;               // entries of ring_part in the workspace
   // single-pass (register-resident) logistic path, cada_logreg_fused.hip
   int fused, fused_Q, fused_clusters, fused_rs, fused_plain_launch;
@@ -285,6 +313,7 @@ struct Ctx {
   size_t rows_lds;
   float *rows_part;          // sums of the shares of a worker's rows
   uint32_t *rows_count;      // [1 + M] counters, kCountWords apart
+  char *rule_room;           // rule_in_bytes
   // full-data evaluation scratch (cada_eval)
   double *eval_part;         // [M][kEvalBlocks][2] per-block sums of (loss, correct)
   double *eval_acc;          // [M][2]
@@ -337,6 +366,9 @@ size_t mlp_scratch_bytes(const cada_config *cfg, const int64_t total_rows);     
 int mlp_plan(Ctx *c, const cada_config *cfg, char *base, size_t offset, size_t scratch, int64_t total_rows);
 int mlp_init_state(Ctx *c, const float *theta0);
 void mlp_free(Ctx *c);
+// Room for the rule's inputs, and whether the server's workgroups run the rule (cada_server.hip); s.rule_rhs and s.rule_in are then set.
+constexpr size_t rule_in_bytes(int M) { return 256 + (size_t)M * 2 * sizeof(int32_t); }
+void decide_plan(Ctx *c, char *room);
 // S3: rule, mask, tau.  S5-S7: aggregate, AMSGrad, ring push.
 int rule_and_server(Ctx *c, const uint8_t *replay);
 int rule_then_server(Ctx *c, const uint8_t *replay);      // the same, the left-hand side's partial sums being complete for every rule

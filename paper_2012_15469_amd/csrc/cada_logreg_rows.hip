@@ -599,6 +599,10 @@ __global__ __launch_bounds__(kBlock) void k_rows_sum(const RowsArgs a) {
   __shared__ uint32_t flag;
   const DevState &s = a.s;
   const int p = (int)s.p, ps = (p + 3) & ~3, m = blockIdx.y, rule = s.rule;
+  if (m == s.M) {                                    // (kTailNone: one more row of blocks)
+    if (blockIdx.x == 0) rule_inputs(s, rule_s);
+    return;
+  }
   const int64_t mp = (int64_t)s.M * s.p;
   const int j = (blockIdx.x * kBlock + threadIdx.x) * 4;
   float sq = 0.f;
@@ -715,8 +719,9 @@ bool rows_plan(Ctx *c, const cada_config *cfg) {
   c->s.n_lhs_part = wide ? (int)((cfg->p + 1023) / 1024) : 2;
   c->n_phases = 0;
   c->phase_names[c->n_phases++] = "logreg_rows";
-  if (c->rows_tail == kTailNone) c->phase_names[c->n_phases++] = "rule";
-  if (c->rows_tail != kTailServer) c->phase_names[c->n_phases++] = "server_update";
+  if (wide && c->rows_tail == kTailNone) decide_plan(c, c->rule_room);
+  if (c->rows_tail == kTailNone && !c->decide) c->phase_names[c->n_phases++] = "rule";
+  if (c->rows_tail != kTailServer) c->phase_names[c->n_phases++] = c->decide ? "rule_and_server_update" : "server_update";
   return true;
 }
 
@@ -737,7 +742,7 @@ int logreg_step_rows(Ctx *c, const int32_t *idx, const uint8_t *replay) {
   prof_mark(c);
   hipLaunchKernelGGL(c->rows == 2 ? wide_kernel(c->s.p) : rows_kernel(c->s.p, &wc), dim3((unsigned)a.shares, c->rows == 2 ? 1u : (unsigned)c->s.M), dim3(R_NT), c->rows_lds, c->stream, a);
   if (c->rows == 2)
-    hipLaunchKernelGGL(k_rows_sum, dim3((unsigned)((c->s.p + 1023) / 1024), (unsigned)c->s.M), dim3(kBlock), 0, c->stream, a);
+    hipLaunchKernelGGL(k_rows_sum, dim3((unsigned)((c->s.p + 1023) / 1024), (unsigned)c->s.M + (a.s.rule_rhs ? 1u : 0u)), dim3(kBlock), 0, c->stream, a);
   prof_mark(c);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) { set_error("logistic step launch failed: %s", hipGetErrorString(e)); return CADA_EHIP; }

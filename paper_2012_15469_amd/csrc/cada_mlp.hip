@@ -48,6 +48,7 @@
 #include <type_traits>
 
 #include "cada_mlp.h"
+#include "cada_rule.h"
 
 namespace cada {
 
@@ -1362,7 +1363,7 @@ size_t mlp_workspace_bytes(const cada_config *cfg, const int64_t total_rows) {
     int64_t nblk = ((int64_t)cfg->layer_dims[0] + 71) / 64 * ((cfg->B + 63) / 64) * cfg->M;
     for (int l = 1; l <= cfg->n_layers; ++l)
       nblk += ((int64_t)cfg->layer_dims[l] + 63) / 64 * ((cfg->layer_dims[l - 1] + 63) / 64) * nz;
-    if (nblk >= (1ll << 31)) { set_error("too many operand tiles for one launch (M x layer sizes / 4096 must stay below 2^31)"); return 0; }
+    if (nblk >= (1ll << 31) - 1) { set_error("too many operand tiles for one launch (M x layer sizes / 4096 must stay below 2^31)"); return 0; }
   }
   MlpPlan P;
   Carve w{nullptr, 0};
@@ -1370,9 +1371,10 @@ size_t mlp_workspace_bytes(const cada_config *cfg, const int64_t total_rows) {
   return w.off + kAlignB;
 }
 
-// The partial sums of the left-hand side, in front of the evaluation's scratch.
+// The partial sums of the left-hand side and the rule's inputs, in front of the evaluation's scratch.
+static size_t rule_room(const cada_config *cfg) { return (rule_in_bytes(cfg->M) + kAlignB - 1) / kAlignB * kAlignB; }
 static size_t lhs_bytes(const cada_config *cfg) {
-  return ((size_t)cfg->M * mlp_lhs_slots(cfg, mlp_bias_cols(cfg->rule)) * sizeof(float) + kAlignB - 1) / kAlignB * kAlignB;
+  return ((size_t)cfg->M * mlp_lhs_slots(cfg, mlp_bias_cols(cfg->rule)) * sizeof(float) + kAlignB - 1) / kAlignB * kAlignB + rule_room(cfg);
 }
 
 size_t mlp_scratch_bytes(const cada_config *cfg, const int64_t total_rows) {
@@ -1390,10 +1392,13 @@ int mlp_plan(Ctx *c, const cada_config *cfg, char *base, size_t offset, size_t s
   layout(*P, cfg, total_rows, w);
   scratch = (scratch + kAlignB - 1) / kAlignB * kAlignB;
   c->s.lhs_part = reinterpret_cast<float *>(base + scratch);
+  decide_plan(c, base + scratch + lhs_bytes(cfg) - rule_room(cfg));
   P->eval = base + scratch + lhs_bytes(cfg);
   c->mlp = P;
-  c->n_phases = 3;
-  c->phase_names[0] = "mlp_gradients"; c->phase_names[1] = "rule"; c->phase_names[2] = "server_update";
+  c->n_phases = 0;
+  c->phase_names[c->n_phases++] = "mlp_gradients";
+  if (!c->decide) c->phase_names[c->n_phases++] = "rule";
+  c->phase_names[c->n_phases++] = c->decide ? "rule_and_server_update" : "server_update";
   return CADA_OK;
 }
 
@@ -1447,6 +1452,7 @@ struct StageArgs {
   // out: rep[m] = the first worker with worker m's (clamped) tau.  Only that worker's difference is computed.
   int32_t *rep;
   uint32_t first[CADA_MAX_LAYERS + 2];   // first block of the minibatch part (0), of each layer, and the total
+  int rule_block;        // 1: one more block, in front of them, takes the rule's inputs down
 };
 
 // A 64 x 64 tile of the minibatch, moved 16 bytes (8 values) per lane: the sampled rows of X's bf16
@@ -1554,7 +1560,11 @@ __device__ __forceinline__ void stage_weights(const StageArgs &a, const PrepLaye
 
 __global__ __launch_bounds__(kBlock) void k_stage(const StageArgs a) {
   __shared__ __align__(16) unsigned char sm[64 * 65 * sizeof(float)];     // a weight tile on its way to the other orientation
-  const uint32_t blk = blockIdx.x;
+  if (a.rule_block && blockIdx.x == 0) {
+    rule_inputs(a.s, reinterpret_cast<double *>(sm));
+    return;
+  }
+  const uint32_t blk = blockIdx.x - a.rule_block;
   if (blk < a.first[1]) {
     const uint32_t per = (uint32_t)a.gx * a.gy;
     const uint32_t m = blk / per, r = blk - m * per;
@@ -1801,7 +1811,8 @@ static void stage(Ctx *c, const MlpPlan &P, const DevState &s, const int32_t *id
     nblk += (uint64_t)pl.gx * pl.gy * sa.nz;
   }
   for (int l = L + 1; l < CADA_MAX_LAYERS + 2; ++l) sa.first[l] = (uint32_t)nblk;
-  hipLaunchKernelGGL(k_stage, dim3((unsigned)nblk), dim3(kBlock), 0, c->stream, sa);
+  sa.rule_block = idx ? 1 : 0;
+  hipLaunchKernelGGL(k_stage, dim3((unsigned)(nblk + sa.rule_block)), dim3(kBlock), 0, c->stream, sa);
 }
 
 void mlp_stage_weights(Ctx *c) { stage(c, *static_cast<MlpPlan *>(c->mlp), c->s, nullptr); }

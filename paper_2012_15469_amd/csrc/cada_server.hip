@@ -4,32 +4,9 @@
 // of Section 1.2, fused with the squared step |theta^{k+1}-theta^k|^2 that the rules'
 // right-hand side needs (identity in the proof of Lemma 4 of the supplement:
 // |theta^{k+1}-theta^k|^2 = alpha^2 sum_i h_i^2 / (eps + vhat_i)).
-#include "cada_internal.h"
+#include "cada_rule.h"
 
 namespace cada {
-
-// Sum of the per-block partial sums of the squared step of iteration k-1 (the value of
-// ring[(k-1) mod d_max]), in a fixed order; called by the whole block, valid in every thread.
-__device__ float last_step_sq(const DevState &s, double *red /* [kBlock] LDS */) {
-  // (sixteen loads in flight per thread; the additions keep their order, a missing term adds 0)
-  double acc = 0.0;
-  for (int i0 = threadIdx.x; i0 < s.n_ring_part; i0 += 16 * kBlock) {
-    float v[16];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) { const int i = i0 + u * kBlock; v[u] = s.ring_part[min(i, s.n_ring_part - 1)]; if (i >= s.n_ring_part) v[u] = 0.f; }
-#pragma unroll
-    for (int u = 0; u < 16; ++u) acc += (double)v[u];
-  }
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int o = kBlock / 2; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-    __syncthreads();
-  }
-  const float r = (float)red[0];
-  __syncthreads();
-  return r;
-}
 
 // Left-hand side of condition (LAGrule), Section 2.1: |fresh gradient - stored gradient|^2 per
 // worker (the stored one was taken at another iterate on other samples).  grid (blocks, M);
@@ -69,10 +46,16 @@ __global__ __launch_bounds__(kBlock) void k_rule(const DevState s, const uint8_t
   __shared__ unsigned int cnt;
   const int64_t k = s.k;
   const int last = k > 0 ? (int)((k - 1) % s.d_max) : -1;
-  const float newest = k > 0 ? last_step_sq(s, red) : 0.f;
-  double sum = 0.0;
-  for (int j = 0; j < s.d_max; ++j) sum += (double)(j == last ? newest : s.ring[j]);
-  const double rhs = (s.c / (double)s.d_max) * sum;
+  const bool inputs = s.rule_rhs != nullptr;          // (taken down by an earlier launch of the step)
+  const float newest = k > 0 && !inputs ? last_step_sq(s, red) : 0.f;
+  double rhs;
+  if (inputs) {
+    rhs = *s.rule_rhs;
+  } else {
+    double sum = 0.0;
+    for (int j = 0; j < s.d_max; ++j) sum += (double)(j == last ? newest : s.ring[j]);
+    rhs = (s.c / (double)s.d_max) * sum;
+  }
   if (threadIdx.x == 0) cnt = 0;
   __syncthreads();
   const bool tr = k < s.trace_steps;
@@ -122,7 +105,7 @@ __global__ __launch_bounds__(kBlock) void k_rule(const DevState s, const uint8_t
       atomicAdd(s.n_up + (k & 1), cnt);
     }
     if (blockIdx.x == 0) {
-      if (last >= 0) s.ring[last] = newest;
+      if (last >= 0 && !inputs) s.ring[last] = newest;
       if (tr) s.t_rhs[k] = (float)rhs;
     }
   }
@@ -140,13 +123,20 @@ __global__ __launch_bounds__(kBlock) void k_ring_finalize(const DevState s) {
 // access when every row start is 16-byte aligned (VEC == 4), else the coordinates lane,
 // lane + 64, lane + 128, lane + 192 of the block's range (VEC == 1, coalesced scalar accesses).
 // Wavefront w sums the stored gradients of workers w, w+4, w+8, ... for them, the four sums
-// are combined through LDS in a fixed order, and wavefront 0 applies the update.
+// are combined through LDS in a fixed order, and each thread applies the update to one coordinate (its square root and two divisions are one chain, not
+// four in a wavefront that the others wait for).
 // grid = n_ring_part = ceil(p / 256) blocks.
-template <int VEC>
-__global__ __launch_bounds__(kBlock) void k_server(const DevState s) {
-  __shared__ float part[4][4][64];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int64_t base = (int64_t)blockIdx.x * 256;
+// DECIDE: S3 as well.  Every workgroup runs the rule for itself, from the left-hand sides' partial sums and the inputs that an earlier launch has taken down (rule_inputs: nothing
+// of what it reads is written in this launch); the first one keeps the books.  As many workgroups as are resident at once then take the coordinates in turn.
+constexpr int kDecideWorkers = 256, kDecideSerial = 24;
+template <int VEC, bool DECIDE>
+__global__ __launch_bounds__(kBlock, 7) void k_server(const DevState s, const uint8_t *replay) {
+  __shared__ __align__(16) float part[DECIDE ? 2 : 1][4][256];
+  __shared__ float sq_s[DECIDE ? 2 : 1][4];
+  __shared__ double lhs_s[DECIDE ? kDecideWorkers : 1];
+  __shared__ uint8_t dec_s[DECIDE ? kDecideWorkers : 1];       // buffer selector after the decision, 2: uploads
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  int64_t base = (int64_t)blockIdx.x * 256;
   const int64_t mp = (int64_t)s.M * s.ps;
   // coordinate of this lane's v-th value, and whether it exists
   auto coord = [&](int v) -> int64_t { return VEC == 4 ? base + lane * 4 + v : base + lane + 64 * v; };
@@ -162,123 +152,220 @@ __global__ __launch_bounds__(kBlock) void k_server(const DevState s) {
         if (coord(v) < s.p) o[v] = x[coord(v)];
     }
   };
-  auto put = [&](float *x, const float (&o)[4]) {
-    if constexpr (VEC == 4) {
-      if (coord(0) < s.p) *reinterpret_cast<float4 *>(x + coord(0)) = make_float4(o[0], o[1], o[2], o[3]);
-    } else {
+  uint32_t n_up = 0;
+  struct Bits { unsigned long long a, b, c, d; } sel64{}, up64{};      // DECIDE: the workers' decisions as bits of scalar registers
+  if constexpr (DECIDE) {
+    const int tid = threadIdx.x, M = s.M, n = s.n_lhs_part;
+    const int mine = min(tid, M - 1);
+    const int32_t tau = s.rule_in[mine], sel = s.rule_in[M + mine];
+    const uint8_t forced = replay != nullptr ? replay[mine] : (uint8_t)CADA_REPLAY_FREE;
+    const double rhs = *s.rule_rhs;
+    double lhs = 0.0;
+    if (n <= kDecideSerial) {            // few parts: each thread adds its worker's up
+      const float *lp = s.lhs_part + (int64_t)mine * n;
+      float v[kDecideSerial];
 #pragma unroll
-      for (int v = 0; v < 4; ++v)
-        if (coord(v) < s.p) x[coord(v)] = o[v];
+      for (int i = 0; i < kDecideSerial; ++i) v[i] = lp[min(i, n - 1)];
+#pragma unroll
+      for (int i = 0; i < kDecideSerial; ++i) lhs += i < n ? (double)v[i] : 0.0;
+    } else {
+      // a wavefront takes eight workers at a time, three loads of each in flight; up to sixteen workers, two or four wavefronts share their parts
+      const int sh = M <= 8 ? 2 : M <= 16 ? 1 : 0, per = (n + (1 << sh) - 1) >> sh, from = (w & ((1 << sh) - 1)) * per, to = min(n, from + per);
+      const int m0 = 8 * (w >> sh);
+      if (m0 < M) {                      // (M <= 32: decide_plan)
+        double l[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+        for (int t0 = from; t0 < to; t0 += 3 * kWave) {
+          float v[8][3];
+#pragma unroll
+          for (int u = 0; u < 3; ++u) {
+            const uint32_t at = min(t0 + u * kWave + lane, to - 1);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q][u] = (s.lhs_part + (int64_t)min(m0 + q, M - 1) * n)[at];
+          }
+#pragma unroll
+          for (int u = 0; u < 3; ++u)
+#pragma unroll
+            for (int q = 0; q < 8; ++q) l[q] += t0 + u * kWave + lane < to ? (double)v[q][u] : 0.0;
+        }
+        const double sum = eight_sums_f64(l, lane);
+        const int m = m0 + (lane & 3) + 4 * (lane >> 5);
+        if ((lane & 28) == 0 && m < M) lhs_s[(w & ((1 << sh) - 1)) * 64 + m] = sum;
+      }
+      lds_sync();
+      for (int q = 0; q < 1 << sh; ++q) lhs += lhs_s[64 * q + mine];
     }
+    const bool own = (s.rule == CADA_RULE_ALWAYS) || (lhs > rhs) || (tau >= s.D);
+    const bool up = forced != CADA_REPLAY_FREE ? forced != 0 : own;
+    dec_s[tid] = tid < M ? (uint8_t)((up ? sel ^ 1 : sel) | (up ? 2 : 0)) : (uint8_t)0;
+    lds_sync();
+    const uint32_t d0 = dec_s[lane], d1 = dec_s[64 + lane], d2 = dec_s[128 + lane], d3 = dec_s[192 + lane];
+    sel64 = Bits{__ballot(d0 & 1), __ballot(d1 & 1), __ballot(d2 & 1), __ballot(d3 & 1)};
+    up64 = Bits{__ballot(d0 & 2), __ballot(d1 & 2), __ballot(d2 & 2), __ballot(d3 & 2)};
+    n_up = (uint32_t)(__popcll(up64.a) + __popcll(up64.b) + __popcll(up64.c) + __popcll(up64.d));
+    if (blockIdx.x == 0 && tid < M) {      // the books
+      if (s.k < s.trace_steps) {
+        const int64_t o = s.k * M + tid;
+        s.t_mask[o] = up ? 1 : 0;
+        s.t_own[o] = own ? 1 : 0;
+        s.t_lhs[o] = (float)lhs;
+        s.t_tau[o] = tau;
+        if (tid == 0) s.t_rhs[s.k] = (float)rhs;
+      }
+      s.lhs[tid] = (float)lhs;
+      s.mask[tid] = up ? 1 : 0;
+      s.tau[tid] = up ? 1 : tau + 1;
+      s.sel[tid] = dec_s[tid] & 1;
+      // (only a replay mask can do this: the reference point theta^{k+1-(tau+1)} leaves the D+1 retained iterates)
+      if (!up && s.rule == CADA_RULE_CADA2 && tau >= s.D) atomicOr(s.err, 8u);
+      if (tid == 0) {
+        *s.uploads += n_up;
+        s.n_up[s.k & 1] = n_up;
+      }
+    }
+  } else {
+    n_up = s.n_up[s.k & 1];
+  }
+  auto bit = [](const Bits &x, int m) __attribute__((always_inline)) -> int {
+    const unsigned long long word = m < 64 ? x.a : m < 128 ? x.b : m < 192 ? x.c : x.d;
+    return (int)(word >> (m & 63)) & 1;
   };
+  auto sel_of = [&](int m) __attribute__((always_inline)) -> int { if constexpr (DECIDE) return bit(sel64, m); else return s.sel[m]; };
   // Aggregate.  Plain form: the sum of all M stored gradients (eq. (CADA-1)).  Incremental form of
   // Section 1.2, nabla^k = nabla^{k-1} + (1/M) sum over the uploading workers of (fresh gradient - the
   // gradient it replaces): taken when it reads fewer rows (2 per upload + 1 against M); the plain
   // sum is formed whenever the host asks for it (every D iterations, and when the stored nabla is not that
   // of the step before), so rounding differences between the two forms cannot pile up.  The choice is
   // the same in every block: it depends on the iteration's upload count alone.
-  const uint32_t n_up = s.n_up[s.k & 1];
   const bool incremental = !s.resum && 2 * (int64_t)n_up + 1 < (int64_t)s.M;
   if (blockIdx.x == 0 && threadIdx.x == 0) s.n_up[(s.k + 1) & 1] = 0u;      // (nobody reads that slot during this launch)
-  float nab[4] = {0.f, 0.f, 0.f, 0.f};
-  auto row_of = [&](int buf, int m) -> const float * { return s.gbuf + (int64_t)buf * mp + (int64_t)m * s.ps; };
-  // bf16 store (rows of ps16 elements, 16-byte aligned; VEC == 4 on that path): four coordinates are 8 bytes
-  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-  auto get16 = [&](int buf, int m, float (&o)[4]) {
-    if (coord(0) < s.p) {
-      const u32x2 t = __builtin_nontemporal_load(reinterpret_cast<const u32x2 *>(s.gbuf16 + ((int64_t)buf * s.M + m) * s.ps16 + coord(0)));
-      o[0] = __uint_as_float(t.x << 16); o[1] = __uint_as_float(t.x & 0xffff0000u);
-      o[2] = __uint_as_float(t.y << 16); o[3] = __uint_as_float(t.y & 0xffff0000u);
-    }
-  };
-  if (incremental) {
-    for (int m = w; m < s.M; m += 4) {
-      if (!s.mask[m]) continue;                       // (uniform in the wavefront)
-      const int cur = s.sel[m];                       // after the swap: cur holds the fresh gradient, 1 - cur the replaced one
-      float a4[4] = {0.f, 0.f, 0.f, 0.f}, b4[4] = {0.f, 0.f, 0.f, 0.f};
-      if (VEC == 4 && s.gbuf16) { get16(cur, m, a4); get16(1 - cur, m, b4); }
-      else { get(row_of(cur, m), a4); get(row_of(1 - cur, m), b4); }
-#pragma unroll
-      for (int v = 0; v < 4; ++v) nab[v] += a4[v] - b4[v];
-    }
-  } else if (VEC == 4 && s.gbuf16) {
-#pragma unroll 4
-    for (int m = w; m < s.M; m += 4) {
-      float t[4] = {0.f, 0.f, 0.f, 0.f};
-      get16(s.sel[m], m, t);
-#pragma unroll
-      for (int v = 0; v < 4; ++v) nab[v] += t[v];
-    }
-  } else if constexpr (VEC == 4) {
-    if (coord(0) < s.p) {
-#pragma unroll 5
+  int turn = 0;
+  do {
+    // (what the update of this thread's coordinate reads is asked for here)
+    const int64_t j = base + threadIdx.x, jr = min(j, s.p - 1);
+    float hh = s.h[jr], vh = s.vhat[jr], th = s.theta[jr], tl = s.theta_lo[jr];
+    const float prev = incremental ? s.nabla[jr] : 0.f;
+    float nab[4] = {0.f, 0.f, 0.f, 0.f};
+    auto row_of = [&](int buf, int m) -> const float * { return s.gbuf + (int64_t)buf * mp + (int64_t)m * s.ps; };
+    // bf16 store (rows of ps16 elements, 16-byte aligned; VEC == 4 on that path): four coordinates are 8 bytes
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    auto get16 = [&](int buf, int m, float (&o)[4]) {
+      if (coord(0) < s.p) {
+        const u32x2 t = __builtin_nontemporal_load(reinterpret_cast<const u32x2 *>(s.gbuf16 + ((int64_t)buf * s.M + m) * s.ps16 + coord(0)));
+        o[0] = __uint_as_float(t.x << 16); o[1] = __uint_as_float(t.x & 0xffff0000u);
+        o[2] = __uint_as_float(t.y << 16); o[3] = __uint_as_float(t.y & 0xffff0000u);
+      }
+    };
+    if (incremental) {
       for (int m = w; m < s.M; m += 4) {
-        typedef float f32x4 __attribute__((ext_vector_type(4)));
-        // (the stored gradients are read once per step: non-temporal loads, which stream from HBM faster)
-        const f32x4 t = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(s.gbuf + (int64_t)s.sel[m] * mp + (int64_t)m * s.ps + coord(0)));
-        nab[0] += t.x; nab[1] += t.y; nab[2] += t.z; nab[3] += t.w;
+        if (DECIDE ? !bit(up64, m) : !s.mask[m]) continue;      // (uniform in the wavefront)
+        const int cur = sel_of(m);                       // after the swap: cur holds the fresh gradient, 1 - cur the replaced one
+        float a4[4] = {0.f, 0.f, 0.f, 0.f}, b4[4] = {0.f, 0.f, 0.f, 0.f};
+        if (VEC == 4 && s.gbuf16) { get16(cur, m, a4); get16(1 - cur, m, b4); }
+        else { get(row_of(cur, m), a4); get(row_of(1 - cur, m), b4); }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) nab[v] += a4[v] - b4[v];
+      }
+    } else if (VEC == 4 && s.gbuf16) {
+#pragma unroll 4
+      for (int m = w; m < s.M; m += 4) {
+        float t[4] = {0.f, 0.f, 0.f, 0.f};
+        get16(sel_of(m), m, t);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) nab[v] += t[v];
+      }
+    } else if constexpr (VEC == 4) {
+      if (coord(0) < s.p) {
+#pragma unroll 5
+        for (int m = w; m < s.M; m += 4) {
+          typedef float f32x4 __attribute__((ext_vector_type(4)));
+          // (the stored gradients are read once per step: non-temporal loads, which stream from HBM faster)
+          const f32x4 t = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(s.gbuf + (int64_t)sel_of(m) * mp + (int64_t)m * s.ps + coord(0)));
+          nab[0] += t.x; nab[1] += t.y; nab[2] += t.z; nab[3] += t.w;
+        }
+      }
+    } else {
+#pragma unroll 4
+      for (int m = w; m < s.M; m += 4) {
+        float t[4] = {0.f, 0.f, 0.f, 0.f};
+        const float *gm = s.gbuf + (int64_t)sel_of(m) * mp + (int64_t)m * s.ps;
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (coord(v) < s.p) t[v] = __builtin_nontemporal_load(gm + coord(v));
+#pragma unroll
+        for (int v = 0; v < 4; ++v) nab[v] += t[v];
       }
     }
-  } else {
-#pragma unroll 4
-    for (int m = w; m < s.M; m += 4) {
-      float t[4] = {0.f, 0.f, 0.f, 0.f};
-      const float *gm = s.gbuf + (int64_t)s.sel[m] * mp + (int64_t)m * s.ps;
+    if constexpr (VEC == 4) {
+      *reinterpret_cast<v4s *>(&part[turn][w][4 * lane]) = v4s{nab[0], nab[1], nab[2], nab[3]};
+    } else {
 #pragma unroll
-      for (int v = 0; v < 4; ++v)
-        if (coord(v) < s.p) t[v] = __builtin_nontemporal_load(gm + coord(v));
-#pragma unroll
-      for (int v = 0; v < 4; ++v) nab[v] += t[v];
+      for (int v = 0; v < 4; ++v) part[turn][w][64 * v + lane] = nab[v];
     }
-  }
-#pragma unroll
-  for (int v = 0; v < 4; ++v) part[w][v][lane] = nab[v];
-  __syncthreads();
-  if (w != 0) return;
-  float sq = 0.f;
-  const float fM = (float)s.M;
-  float th[4] = {0.f, 0.f, 0.f, 0.f}, tl[4] = {0.f, 0.f, 0.f, 0.f}, hh[4] = {0.f, 0.f, 0.f, 0.f};
-  float vv[4], vh[4] = {0.f, 0.f, 0.f, 0.f};
-  float prev[4] = {0.f, 0.f, 0.f, 0.f};
-  get(s.h, hh); get(s.vhat, vh); get(s.theta, th); get(s.theta_lo, tl);
-  if (incremental) get(s.nabla, prev);
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    nab[v] = prev[v] + ((part[0][v][lane] + part[1][v][lane]) + (part[2][v][lane] + part[3][v][lane])) / fM;
-    const float to = th[v], lo = tl[v];
-    const float step = server_coordinate(s, s.alpha, nab[v], hh[v], vh[v], vv[v], th[v], tl[v]);
-    if (VEC == 4 && coord(v) >= s.p) { th[v] = to; tl[v] = lo; }   // (a coordinate of the 16-byte padding past p stays as it is, also with eps = 0)
-    if (coord(v) < s.p) sq = fmaf(step, step, sq);
-  }
-  put(s.nabla, nab); put(s.h, hh); put(s.v, vv); put(s.vhat, vh); put(s.theta, th); put(s.theta_lo, tl);
-  if (s.rule == CADA_RULE_CADA2) {
-    put(s.hist + ((s.k + 1) % s.R) * s.ps, th);
-    put(s.hist_lo + ((s.k + 1) % s.R) * s.ps, tl);
-  } else if (s.rule == CADA_RULE_CADA1 && (s.k + 1) % s.D == 0) {
-    put(s.snap, th);
-    put(s.snap_lo, tl);
-  }
-  const float tot = wave_sum(sq);
-  if (lane == 0) s.ring_part[blockIdx.x] = tot;
+    lds_sync();
+    const int i = threadIdx.x;
+    const float mean = prev + ((part[turn][0][i] + part[turn][1][i]) + (part[turn][2][i] + part[turn][3][i])) / (float)s.M;
+    float vv;
+    const float step = server_coordinate(s, s.alpha, mean, hh, vh, vv, th, tl);
+    if (j < s.p) {
+      s.nabla[j] = mean; s.h[j] = hh; s.v[j] = vv; s.vhat[j] = vh; s.theta[j] = th; s.theta_lo[j] = tl;
+      if (s.rule == CADA_RULE_CADA2) {
+        const int64_t o = ((s.k + 1) % s.R) * s.ps + j;
+        s.hist[o] = th;
+        s.hist_lo[o] = tl;
+      } else if (s.rule == CADA_RULE_CADA1 && (s.k + 1) % s.D == 0) {
+        s.snap[j] = th;
+        s.snap_lo[j] = tl;
+      }
+    }
+    const float sq = wave_sum_dpp(j < s.p ? step * step : 0.f);
+    if (lane == 0) sq_s[turn][w] = sq;
+    lds_sync();
+    if (i == 0) s.ring_part[base >> 8] = (sq_s[turn][0] + sq_s[turn][1]) + (sq_s[turn][2] + sq_s[turn][3]);
+    base += (int64_t)gridDim.x * 256;
+    turn ^= 1;             // (what a turn leaves in LDS is written again two turns later, a barrier behind its readers)
+  } while (DECIDE && base < s.p);
 }
 
-int server_step(Ctx *c) {
+// The rule in the server's launch saves one, and every workgroup reads all partial sums of the left-hand sides for it.  Measured, us per step with it / with a launch of
+// its own, M workers of n parts: p = 20001, M = 37, n = 20: 61.8 / 63.2; p = 10000, M = 250, n = 10: 65.1 / 67.7; 784-500-10, M = 10, n = 137: 65.1 / 65.9; 300-200-10, LAG, M = 30,
+// n = 34: 50.6 / 52.2; 400-300-10, M = 24, n = 66: 63.1 / 64.0; but 200-150-10, M = 64, n = 28: 68.4 / 67.6; 1000-800-10, M = 16, n = 267: 144.9 / 142.0;
+// 2000-500-10, M = 20, n = 281: 154.9 / 153.0; 784-300-10, M = 100: 130.1 / 127.6; 784-512-10, M = 64, n = 137: 174.2 / 171.3; 3072-1024-1024-10, M = 16: 580.9 / 577.1.
+// The launch of its own, with the squared step's parts added up and the inputs taken down in front: 3 us, before 5 to 11 (3072-1024-1024-10: 583 -> 577 us per step).
+constexpr int64_t kDecideParts = 3000;
+constexpr int kDecideBlocks = 7 * 256;           // seven workgroups of 68 registers per CU
+void decide_plan(Ctx *c, char *room) {
+  c->s.rule_rhs = reinterpret_cast<double *>(room);
+  c->s.rule_in = reinterpret_cast<int32_t *>(room + 256);
+  const int64_t M = c->s.M, n = c->s.n_lhs_part;
+  c->decide = M <= kDecideWorkers && (n <= kDecideSerial || (M <= 32 && M * n <= kDecideParts));
+}
+
+namespace {
+int launch_server(Ctx *c, bool decide, const uint8_t *replay) {
   DevState s = c->s;
   s.k = c->k;
   s.alpha = stepsize(s, s.k);
   s.resum = (c->force_resum || s.k % s.D == 0) ? 1 : 0;
-  if (c->vec == 4)
-    hipLaunchKernelGGL(k_server<4>, dim3(s.n_ring_part), dim3(kBlock), 0, c->stream, s);
-  else
-    hipLaunchKernelGGL(k_server<1>, dim3(s.n_ring_part), dim3(kBlock), 0, c->stream, s);
+  const dim3 grid(decide ? min(s.n_ring_part, kDecideBlocks) : s.n_ring_part);
+  if (c->vec == 4) {
+    if (decide) hipLaunchKernelGGL((k_server<4, true>), grid, dim3(kBlock), 0, c->stream, s, replay);
+    else hipLaunchKernelGGL((k_server<4, false>), grid, dim3(kBlock), 0, c->stream, s, nullptr);
+  } else {
+    if (decide) hipLaunchKernelGGL((k_server<1, true>), grid, dim3(kBlock), 0, c->stream, s, replay);
+    else hipLaunchKernelGGL((k_server<1, false>), grid, dim3(kBlock), 0, c->stream, s, nullptr);
+  }
   prof_mark(c);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) { set_error("server launch failed: %s", hipGetErrorString(e)); return CADA_EHIP; }
   c->force_resum = 0;
   return CADA_OK;
 }
+}  // namespace
+
+int server_step(Ctx *c) { return launch_server(c, false, nullptr); }
 
 int rule_then_server(Ctx *c, const uint8_t *replay) {
+  if (c->decide) return launch_server(c, true, replay);
   DevState s = c->s;
   s.k = c->k;
   hipLaunchKernelGGL(k_rule, dim3((unsigned)((s.M + 3) / 4)), dim3(kBlock), 0, c->stream, s, replay);

@@ -1,0 +1,58 @@
+"""The rule in the server's launch (cada_server.hip): which shapes take it, its sums over few and many parts of the left-hand sides at the edges of
+their groups of workers, the decisions and the books, and more coordinates than its workgroups take in one turn; against the oracle."""
+import numpy as np
+import pytest
+
+from cada_synth import configs, generators
+from paper_2012_15469_amd import binding
+
+from common import check_protocol, upload
+
+pytestmark = pytest.mark.gpu
+TOGETHER, APART = "rule_and_server_update", "server_update"
+
+
+def _check(cfg, phase, tol, lhs_rtol):
+    prob = generators.make_problem(cfg)
+    if cfg.model == "logreg":
+        prob.X *= np.float32(1.0 / np.sqrt(cfg.layer_dims[0]))
+    dev, sched = upload(prob), generators.make_schedule(cfg)
+    stats, o, tr, rep = check_protocol(cfg, prob, dev, sched, tol, lhs_rtol=lhs_rtol, own_mask_exact=lhs_rtol is not None,
+                                       free_margin=None if lhs_rtol is None else 1e-3, expect_phase=phase)
+    # The decisions follow from the recorded sides (float32 of the doubles that are compared: 2^-24 each), and the books agree with the trace.
+    lhs, rhs, tau = rep["trace_lhs"].astype(np.float64), rep["trace_rhs"].astype(np.float64)[:, None], rep["trace_tau"]
+    own = (lhs > rhs) | (tau >= cfg.D) | (cfg.rule == configs.RULE_ALWAYS)
+    clear = (abs(lhs - rhs) > 2.0 ** -22 * rhs) | (tau >= cfg.D)
+    assert np.array_equal(rep["trace_own_mask"][clear].astype(bool), own[clear])
+    assert np.array_equal(rep["lhs"], rep["trace_lhs"][-1]) and np.array_equal(rep["mask"], rep["trace_mask"][-1])
+    assert rep["uploads_total"][0] == rep["trace_mask"].sum()
+    # the right-hand side: squared steps of float32 updates whose gradients carry the path's own error (a step of Adam moves less than its gradient)
+    ok = tr["rhs"] > 0
+    assert ok.any() and (abs(rep["trace_rhs"] - tr["rhs"])[ok] <= 2e-2 * tr["rhs"][ok]).all()
+
+
+# layer sizes, workers, where the rule runs: 10 parts per worker (each thread adds its own worker's up), 28 parts (a wavefront takes eight workers; up to 8 and 16 of
+# them share their parts among four and two wavefronts), 180 parts and 498 thousand coordinates (two turns of 1792 workgroups)
+NETWORKS = [((100, 60, 5), 3, TOGETHER), ((100, 60, 5), 256, TOGETHER), ((100, 60, 5), 257, APART), ((130, 129, 5), 5, TOGETHER), ((130, 129, 5), 8, TOGETHER),
+            ((130, 129, 5), 9, TOGETHER), ((130, 129, 5), 16, TOGETHER), ((130, 129, 5), 17, TOGETHER), ((130, 129, 5), 32, TOGETHER), ((130, 129, 5), 33, APART),
+            ((700, 700, 10), 3, TOGETHER)]
+
+
+@pytest.mark.parametrize("rule", [configs.RULE_CADA1, configs.RULE_CADA2, configs.RULE_ALWAYS], ids=["cada1", "cada2", "always"])
+@pytest.mark.parametrize("dims,M,phase", NETWORKS)
+def test_networks(dims, M, phase, rule):
+    _check(configs.CFG5.scaled(name="rule", layer_dims=dims, M=M, N_m=30, B=6, K=6, D=3, c=20.0, rule=rule), phase, 2e-2, None)
+
+
+# rows of more than 8192 columns and more than 32 workers: 9 and 10 parts; a width that is no multiple of four
+@pytest.mark.parametrize("p,M,phase", [(8193, 33, TOGETHER), (9300, 256, TOGETHER), (8196, 257, APART)])
+def test_wide_rows(p, M, phase):
+    _check(configs.CFG1.scaled(name="rule", layer_dims=(p,), M=M, N_m=12, B=4, K=6, D=4, rule=configs.RULE_CADA2, c=2e-3), phase, 1e-4, 1e-4)
+
+
+def test_phase_names():
+    """Whole steps and the paths whose gradient launches run the rule keep the phases that they had."""
+    cfg = configs.CFG1.scaled(name="rule", layer_dims=(8193,), M=3, N_m=12, B=4, K=1)
+    eng = binding.Cada.from_config(cfg, *upload(generators.make_problem(cfg)))
+    assert binding.cada_profile_phase_names(eng.ctx) == ["logreg_rows", "server_update"]
+    eng.close()
