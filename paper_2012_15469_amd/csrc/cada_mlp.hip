@@ -1445,12 +1445,13 @@ struct StageArgs {
   int gx, gy;            // 64 x 64 tiles over (ldx, B)
   // weights
   PrepLayer layer[CADA_MAX_LAYERS];
-  int n_layers, nz;      // nz = 1 + number of workers with a difference of their own
+  int n_layers, nz;      // nz = 1 + groups of blocks for the differences (one for CADA1, none for the rules without)
   int64_t wt_total, wn_total;
   // CADA2 only, else null: workers whose last upload happened at the same iteration share their
   // reference point theta^{k - tau}, hence the difference theta - theta_ref and its bf16 copies;
   // out: rep[m] = the first worker with worker m's (clamped) tau.  Only that worker's difference is computed.
   int32_t *rep;
+  int z_groups;          // the groups that share these workers out (M > kBlock: a group for every worker, which finds out for itself whether it is a first one)
   uint32_t first[CADA_MAX_LAYERS + 2];   // first block of the minibatch part (0), of each layer, and the total
   int rule_block;        // 1: one more block, in front of them, takes the rule's inputs down
 };
@@ -1493,68 +1494,104 @@ __device__ __forceinline__ void stage_weights(const StageArgs &a, const PrepLaye
   const int o0 = bx * 64, i0 = by * 64;
   const int t = threadIdx.x;
   const bool is_w = z == 0;
-  const int m = is_w ? 0 : z - 1;
-  if (!is_w && a.rep) {
+  const int og = (t & 7) * 8;
+  auto one = [&](const int m) __attribute__((always_inline)) {
+    const RefPtr ref = theta_ref(s, m, s.k);
+#pragma unroll
+    for (int pass = 0; pass < 2; ++pass) {
+      const int r = (t >> 3) + 32 * pass, i = i0 + r, o = o0 + og;
+      float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      if (i < p.din && o < p.dout) {
+        const int64_t src = p.offW + (int64_t)i * p.dout + o;
+        if (o + 8 <= p.dout) {
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            f32x4u x = *reinterpret_cast<const f32x4u *>(s.theta + src + 4 * q);
+            if (!is_w) {
+              const f32x4u xl = *reinterpret_cast<const f32x4u *>(s.theta_lo + src + 4 * q);
+              const f32x4u rh = *reinterpret_cast<const f32x4u *>(ref.hi + src + 4 * q);
+              const f32x4u rl = *reinterpret_cast<const f32x4u *>(ref.lo + src + 4 * q);
+              x = (x - rh) + (xl - rl);             // the same expression as delta_theta
+            }
+            v[4 * q] = x.x; v[4 * q + 1] = x.y; v[4 * q + 2] = x.z; v[4 * q + 3] = x.w;
+          }
+        } else {
+          for (int e = 0; e < 8 && o + e < p.dout; ++e) v[e] = is_w ? s.theta[src + e] : delta_theta(s, ref, src + e);
+        }
+        if (p.want_n) {                             // (values past dout are zeros, like the padding they land in)
+          const int64_t dn = tm(i, o, p.ktn);
+          bf16_t h8[8], l8[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) { h8[e] = f2bf(v[e]); l8[e] = f2bf(v[e] - bf2f(h8[e])); }
+          if (is_w) { *reinterpret_cast<u32x4 *>(p.WNh + dn) = pack8(h8); *reinterpret_cast<u32x4 *>(p.WNl + dn) = pack8(l8); }
+          else *reinterpret_cast<u32x4 *>(p.dWN + (int64_t)m * a.wn_total + dn) = pack8(h8);
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) tile[r][og + e] = v[e];
+    }
+    __syncthreads();
+    const int oo = t & 63;
+    if (o0 + oo < p.dout) {
+#pragma unroll
+      for (int pass = 0; pass < 2; ++pass) {
+        const int ig = ((t >> 6) + 4 * pass) * 8;
+        if (i0 + ig < p.din) {                      // (rows past din are zeros in the tile)
+          bf16_t h8[8], l8[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) { const float x = tile[ig + e][oo]; h8[e] = f2bf(x); l8[e] = f2bf(x - bf2f(h8[e])); }
+          const int64_t dt = tm(o0 + oo, i0 + ig, p.ktt);
+          if (is_w) { *reinterpret_cast<u32x4 *>(p.WTh + dt) = pack8(h8); *reinterpret_cast<u32x4 *>(p.WTl + dt) = pack8(l8); }
+          else *reinterpret_cast<u32x4 *>(p.dWT + (int64_t)m * a.wt_total + dt) = pack8(h8);
+        }
+      }
+    }
+  };
+  // The first workers with each delay, dealt to the groups of blocks in turn.  (With a block for every worker and tile, most of which found that another one stood for
+  // their worker, 784-300-10 with 100 workers took 127.1 us per step, now 124.9; 784-512-10 with 64: the same.)
+  __shared__ int32_t tau_s[kBlock];
+  __shared__ unsigned long long first_s[kBlock / kWave];
+  const bool listed = !is_w && a.rep && s.M <= kBlock;
+  int m = 0;
+  if (listed) {
+    if (t < s.M) tau_s[t] = min(s.tau[t], s.D);
+    lds_sync();
+    int r = 0;
+    if (t < s.M) {
+      const int32_t mine = tau_s[t];
+      while (tau_s[r] != mine) ++r;                     // (r <= t)
+      if (first_tile && z == 1) a.rep[t] = r;
+    }
+    const unsigned long long firsts = __ballot(t < s.M && r == t);
+    if ((t & 63) == 0) first_s[t >> 6] = firsts;
+    lds_sync();
+  } else if (!is_w && a.rep) {
+    m = z - 1;
     const int tau_m = min(s.tau[m], s.D);
-    int r = m;                                        // (every wavefront finds it for itself)
+    int r = m;                                          // (every wavefront finds it for itself)
     for (int j0 = 0; j0 < m && r == m; j0 += kWave) {
       const int j = j0 + (t & 63);
       const unsigned long long same = __ballot(j < m && min(s.tau[j], s.D) == tau_m);
       if (same) r = j0 + __ffsll(same) - 1;
     }
     if (first_tile && t == 0) a.rep[m] = r;
-    if (r != m) return;                               // another worker with the same reference point stands for this one
+    if (r != m) return;                                 // another worker with the same reference point stands for this one
   }
-  const RefPtr ref = theta_ref(s, m, s.k);
-  const int og = (t & 7) * 8;
-#pragma unroll
-  for (int pass = 0; pass < 2; ++pass) {
-    const int r = (t >> 3) + 32 * pass, i = i0 + r, o = o0 + og;
-    float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    if (i < p.din && o < p.dout) {
-      const int64_t src = p.offW + (int64_t)i * p.dout + o;
-      if (o + 8 <= p.dout) {
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          f32x4u x = *reinterpret_cast<const f32x4u *>(s.theta + src + 4 * q);
-          if (!is_w) {
-            const f32x4u xl = *reinterpret_cast<const f32x4u *>(s.theta_lo + src + 4 * q);
-            const f32x4u rh = *reinterpret_cast<const f32x4u *>(ref.hi + src + 4 * q);
-            const f32x4u rl = *reinterpret_cast<const f32x4u *>(ref.lo + src + 4 * q);
-            x = (x - rh) + (xl - rl);             // the same expression as delta_theta
-          }
-          v[4 * q] = x.x; v[4 * q + 1] = x.y; v[4 * q + 2] = x.z; v[4 * q + 3] = x.w;
-        }
-      } else {
-        for (int e = 0; e < 8 && o + e < p.dout; ++e) v[e] = is_w ? s.theta[src + e] : delta_theta(s, ref, src + e);
+  unsigned long long left = listed ? first_s[0] : 0ull;
+  for (int i = 0, turn = 1;; ++turn) {
+    if (listed) {                                       // (uniform)
+      while (left == 0ull) {
+        if (++i == kBlock / kWave) return;
+        left = first_s[i];
       }
-      if (p.want_n) {                             // (values past dout are zeros, like the padding they land in)
-        const int64_t dn = tm(i, o, p.ktn);
-        bf16_t h8[8], l8[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) { h8[e] = f2bf(v[e]); l8[e] = f2bf(v[e] - bf2f(h8[e])); }
-        if (is_w) { *reinterpret_cast<u32x4 *>(p.WNh + dn) = pack8(h8); *reinterpret_cast<u32x4 *>(p.WNl + dn) = pack8(l8); }
-        else *reinterpret_cast<u32x4 *>(p.dWN + (int64_t)m * a.wn_total + dn) = pack8(h8);
-      }
+      m = __builtin_amdgcn_readfirstlane(i * kWave + __ffsll(left) - 1);
+      left &= left - 1;
+      if (turn != z) { if (turn == a.z_groups) turn = 0; continue; }
+      if (turn == a.z_groups) turn = 0;
     }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) tile[r][og + e] = v[e];
-  }
-  __syncthreads();
-  const int oo = t & 63;
-  if (o0 + oo < p.dout) {
-#pragma unroll
-    for (int pass = 0; pass < 2; ++pass) {
-      const int ig = ((t >> 6) + 4 * pass) * 8;
-      if (i0 + ig < p.din) {                      // (rows past din are zeros in the tile)
-        bf16_t h8[8], l8[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) { const float x = tile[ig + e][oo]; h8[e] = f2bf(x); l8[e] = f2bf(x - bf2f(h8[e])); }
-        const int64_t dt = tm(o0 + oo, i0 + ig, p.ktt);
-        if (is_w) { *reinterpret_cast<u32x4 *>(p.WTh + dt) = pack8(h8); *reinterpret_cast<u32x4 *>(p.WTl + dt) = pack8(l8); }
-        else *reinterpret_cast<u32x4 *>(p.dWT + (int64_t)m * a.wt_total + dt) = pack8(h8);
-      }
-    }
+    one(m);
+    if (!listed) return;
+    lds_sync();                                         // (the tile's room is written again)
   }
 }
 
@@ -1789,6 +1826,7 @@ int mlp_init_state(Ctx *c, const float *) {
 static bool plain_rule(const MlpPlan &P) { return P.rule == CADA_RULE_ALWAYS || P.rule == CADA_RULE_LAG; }
 
 // The bf16 copies of the weights, and with idx the minibatch's rows and the differences to the reference points.
+constexpr int kStageGroups = 8;
 static void stage(Ctx *c, const MlpPlan &P, const DevState &s, const int32_t *idx) {
   const int L = P.L, M = P.M, B = P.B;
   StageArgs sa;
@@ -1797,7 +1835,7 @@ static void stage(Ctx *c, const MlpPlan &P, const DevState &s, const int32_t *id
   sa.XGh = P.XGh; sa.XGl = P.XGl;
   sa.d0 = P.d[0]; sa.B = B; sa.Bp = P.Bp; sa.ktx = P.kta[0];
   sa.gx = (int)((P.ldx + 63) / 64); sa.gy = (B + 63) / 64;
-  sa.n_layers = L; sa.nz = idx && !plain_rule(P) ? P.nW + 1 : 1; sa.wt_total = P.wt_total; sa.wn_total = P.wn_total; sa.rep = P.rule == CADA_RULE_CADA2 ? P.rep : nullptr;
+  sa.n_layers = L; sa.z_groups = P.nW > kBlock ? P.nW : P.nW < kStageGroups ? P.nW : kStageGroups; sa.nz = idx && !plain_rule(P) ? sa.z_groups + 1 : 1; sa.wt_total = P.wt_total; sa.wn_total = P.wn_total; sa.rep = P.rule == CADA_RULE_CADA2 ? P.rep : nullptr;
   uint64_t nblk = idx ? (uint64_t)sa.gx * sa.gy * M : 0;
   sa.first[0] = 0;
   for (int l = 1; l <= L; ++l) {
