@@ -366,6 +366,8 @@ size_t mlp_scratch_bytes(const cada_config *cfg, const int64_t total_rows);     
 int mlp_plan(Ctx *c, const cada_config *cfg, char *base, size_t offset, size_t scratch, int64_t total_rows);
 int mlp_init_state(Ctx *c, const float *theta0);
 void mlp_free(Ctx *c);
+constexpr int kLagSpan = 4096;              // coordinates of a worker that a block of k_lag_lhs takes at a time
+inline int lag_parts(int64_t p) { return (int)((p + kLagSpan - 1) / kLagSpan); }
 // Room for the rule's inputs, and whether the server's workgroups run the rule (cada_server.hip); s.rule_rhs and s.rule_in are then set.
 constexpr size_t rule_in_bytes(int M) { return 256 + (size_t)M * 2 * sizeof(int32_t); }
 void decide_plan(Ctx *c, char *room);

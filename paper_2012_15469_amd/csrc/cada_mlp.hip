@@ -43,6 +43,7 @@
 // and the squared norm of the innovation, so no float32 intermediate except the logits
 // round-trips through HBM.  k_skinny computes the same products for outputs of at most 32
 // columns (the last layer).
+#include <algorithm>
 #include <cstdlib>
 #include <new>
 #include <type_traits>
@@ -888,7 +889,7 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
         sqb = iv * iv;
       }
       const float totb = wave_sum(sqb);
-      if (lane == 0) s.lhs_part[(int64_t)wk * s.n_lhs_part + g.lhs_slot_b] = totb;
+      if (!PL && lane == 0) s.lhs_part[(int64_t)wk * s.n_lhs_part + g.lhs_slot_b] = totb;
       return;
     }
   }
@@ -1266,7 +1267,7 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
       }
     }
   }
-  if constexpr (EPI == EPI_DW) {
+  if constexpr (EPI == EPI_DW && !PL) {
     const float ws = wave_sum(sq);
     __syncthreads();
     if (lane == 0) red[w] = ws;
@@ -1392,6 +1393,8 @@ int mlp_plan(Ctx *c, const cada_config *cfg, char *base, size_t offset, size_t s
   layout(*P, cfg, total_rows, w);
   scratch = (scratch + kAlignB - 1) / kAlignB * kAlignB;
   c->s.lhs_part = reinterpret_cast<float *>(base + scratch);
+  // (the rules without a second gradient: a part per block of k_lag_lhs)
+  if (cfg->rule == CADA_RULE_LAG || cfg->rule == CADA_RULE_ALWAYS) c->s.n_lhs_part = std::min(c->s.n_lhs_part, lag_parts(cfg->p));
   decide_plan(c, base + scratch + lhs_bytes(cfg) - rule_room(cfg));
   P->eval = base + scratch + lhs_bytes(cfg);
   c->mlp = P;

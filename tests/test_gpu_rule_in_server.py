@@ -41,6 +41,8 @@ NETWORKS = [((100, 60, 5), 3, TOGETHER), ((100, 60, 5), 256, TOGETHER), ((100, 6
 @pytest.mark.parametrize("rule", [configs.RULE_CADA1, configs.RULE_CADA2, configs.RULE_ALWAYS], ids=["cada1", "cada2", "always"])
 @pytest.mark.parametrize("dims,M,phase", NETWORKS)
 def test_networks(dims, M, phase, rule):
+    if rule == configs.RULE_ALWAYS and M <= 256:      # (a part per 4096 coordinates: few)
+        phase = TOGETHER
     _check(configs.CFG5.scaled(name="rule", layer_dims=dims, M=M, N_m=30, B=6, K=6, D=3, c=20.0, rule=rule), phase, 2e-2, None)
 
 
@@ -56,3 +58,13 @@ def test_phase_names():
     eng = binding.Cada.from_config(cfg, *upload(generators.make_problem(cfg)))
     assert binding.cada_profile_phase_names(eng.ctx) == ["logreg_rows", "server_update"]
     eng.close()
+
+
+# the LAG rule's left-hand side in a launch of its own: blocks of 4096 coordinates read 16 bytes at a time, rows that end inside a block, an access, or in the first
+@pytest.mark.parametrize("p,M,rule", [(1, 3, 3), (3, 2, 3), (7, 5, 0), (1023, 3, 3), (4095, 2, 3), (4096, 2, 0), (4099, 3, 3), (12290, 4, 3)])
+def test_lag_left_hand_sides(p, M, rule):
+    cfg = configs.CFG1.scaled(name="rule", layer_dims=(p,), M=M, N_m=60, B=9, K=8, D=4, rule=rule, c=0.5 if p < 100 else 2e-3, server=1 if rule == configs.RULE_LAG else 0)
+    prob = generators.make_problem(cfg)
+    prob.X *= np.float32(1.0 / np.sqrt(p))
+    dev, sched = upload(prob), generators.make_schedule(cfg)
+    check_protocol(cfg, prob, dev, sched, 1e-4, lhs_rtol=1e-4, path=binding.PATH_TWO_PASS, expect_phase="logreg_two_pass")
