@@ -185,6 +185,9 @@ __device__ __forceinline__ bf16x8 tr_fragment(const bf16_t *blk, int lane_off) {
 __device__ __forceinline__ void mm_load(const bf16_t *base, uint32_t byte_off, uint32_t lds) {      // 1 KB, 16 bytes per lane, to `lds` (uniform)
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(byte_off), "s"(base), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory", "m0");
 }
+// A value that earlier launches wrote and nobody changes in this one, at a uniform address.
+__device__ __forceinline__ int32_t scalar_load(const int32_t *p) { return *(const __attribute__((address_space(4))) int32_t *)(uintptr_t)p; }
+
 // Bias gradient of a hidden layer's units col .. (one per lane) and its innovation, from the sums that the signals' launch left per band of
 // 64 rows, and (not PL) the wavefront's 64 units' partial sum of the left-hand side: in the launch of the layer's weight gradient.
 template <bool PL, bool CADA1>
@@ -840,10 +843,9 @@ __device__ __forceinline__ float group16_sum(float x) {
 // 128 x 128 tile would leave nine tenths of its MFMAs and of its workgroups idle and the launch
 // would run on a few CUs (32 tiles for the logits of 16 workers).  Here a workgroup computes
 // 32 rows x 32 columns; its wavefronts (eight; fewer for the few steps of a weight gradient) split the
-// tile steps (wavefront w takes steps w, w + nw, ...), read their fragments straight from the chunks in
-// global memory (a fragment is 16 consecutive bytes of a chunk row) and add their partial accumulators up
+// tile steps (wavefront w takes steps w, w + nw, ...), each through an LDS area of its own, and add their partial accumulators up
 // through LDS in a fixed order.  grid (ceil(M / 32), workers, blocks of 32 columns), 64 threads per
-// wavefront (EPI_DW: and wavefronts for the way out alone, launch_skinny_as), 8 KB of dynamic LDS each (EPI_DW: 15.5 KB, for those that take steps).  EPI_FWD_HIDDEN: a hidden layer's forward product where the 128 x 128 tiles are few or mostly
+// wavefront (EPI_DW: and wavefronts for the way out alone, launch_skinny_as), 2 KB of dynamic LDS per tensor each (EPI_DW: 15.5 KB, for those that take steps).  EPI_FWD_HIDDEN: a hidden layer's forward product where the 128 x 128 tiles are few or mostly
 // padding (skinny_forward), with the outputs of k_mm5's.
 // EPI_LOSS: the logits stay in the workgroup, whose epilogue is the loss (the signals
 // the backward contractions read, and per-block sums for the bias gradient); EPI_DW: weight gradient, innovation, its
@@ -854,19 +856,19 @@ __device__ __forceinline__ float group16_sum(float x) {
 template <int EPI, int NA, int NB, bool HAS_D>
 __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  float *red = reinterpret_cast<float *>(smem_raw);                  // [8 wavefronts][2 accumulators][16][64]
+  float *red = reinterpret_cast<float *>(smem_raw);                  // EPI_DW: [8 wavefronts][2 accumulators][16][64]
   const DevState &s = g.s;
-  const int t = threadIdx.x, lane = t & 63, w = EPI == EPI_DW ? __builtin_amdgcn_readfirstlane(t >> 6) : t >> 6;
+  const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
   const int nw = blockDim.x >> 6;          // wavefronts of this launch (1..8)
   const int nsw = EPI == EPI_DW ? g.step_waves : nw;       // those that take tile steps: fewer for short contractions, so that more workgroups fit a CU
   const int m0 = blockIdx.x * 32, wk = blockIdx.y;
   const int nk = (g.K + BK - 1) / BK;
   constexpr bool PL = NB == 2;
-  // this lane's fragment in a chunk: row lane % 32 of the band (A) or of the first 32 rows (B), piece lane / 32 (+ 2)
-  const int64_t offa = (((int64_t)(m0 >> 7) * g.A.kt[0]) << 12) + (((m0 & 127) + (lane & 31)) << 5) + ((lane >> 5) << 3);
   // (EPI_FWD_HIDDEN: units 32 blockIdx.z ... of the layer; else the only block of columns)
   const int cb = EPI == EPI_FWD_HIDDEN ? (int)blockIdx.z : 0;
-  const int64_t offb = (((int64_t)(cb >> 2) * g.B.kt[0]) << 12) + ((cb & 3) << 10) + ((lane & 31) << 5) + ((lane >> 5) << 3);
+  // EPI_FWD_HIDDEN, EPI_LOSS: a wavefront's area of LDS: a step's 32 x 32 blocks, 2 KB each, later its partial results (4 KB, 8 KB with a difference) and a room behind them
+  constexpr int AREA = (NA + NB) * 2048, ROOM = PL ? 4096 : 8192;
+  auto part_of = [&](int ww, int q) __attribute__((always_inline)) { return reinterpret_cast<float *>(smem_raw + ww * AREA + q * 4096); };      // [16][64]
   if constexpr (EPI == EPI_DW) {
     // The last layer's launch has one workgroup more than tiles: it forms that layer's bias gradient, its innovation
     // and the innovation's part of the left-hand side from the sums that the forward launch left per block of 32 rows
@@ -907,22 +909,8 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
   f32x16 acc1, acc2;
 #pragma unroll
   for (int r = 0; r < 16; ++r) { acc1[r] = 0.f; acc2[r] = 0.f; }
-  // EPI_LOSS, EPI_FWD_HIDDEN: sixteen lanes share a row of the 32 x 32 result, each with two of the (at most 32) classes or units.
-  // The biases, their differences to the reference point and the row's label are asked for here, so that their
-  // latency passes under the products.
   float bz[2] = {0.f, 0.f}, dbz[2] = {0.f, 0.f};
   int label = 0;
-  if constexpr (EPI == EPI_LOSS || EPI == EPI_FWD_HIDDEN) {
-    const RefPtr ref = theta_ref(s, wk, s.k);
-    const int c0 = 32 * cb + 2 * (t & 15);
-#pragma unroll
-    for (int e = 0; e < 2; ++e)
-      if (c0 + e < g.N) {
-        bz[e] = s.theta[g.offb + c0 + e];
-        if constexpr (!PL) dbz[e] = delta_theta(s, ref, g.offb + c0 + e);
-      }
-    if constexpr (EPI == EPI_LOSS) label = static_cast<const int32_t *>(s.y)[g.grow[(int64_t)wk * g.Bp + min(m0 + (t >> 4), g.M - 1)]];
-  }
   if constexpr (EPI == EPI_DW) {
     // units m0 .. m0 + 31 of the A tensors are chunk m0 / 32 of every row tile, the (at most 32) output
     // columns chunk 0 of the B tensors; step kc covers the worker's rows 32 kc .. 32 kc + 31
@@ -1064,19 +1052,66 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
     }
     __syncthreads();                                         // the areas are done with: `red` lies over them
   } else {
+  // Step kc's block of a tensor is 2 KB of consecutive memory: moved straight to LDS, 1 KB per instruction, its 16-byte pieces in the order of lds_piece.  (Fragments
+  // read from memory are 16 bytes of a row each, 64 bytes apart: a wave-load of them took the CU's address unit some 70 cycles, 16300 for the four steps of a wavefront's
+  // 784 inputs.  Launches, us: 784-500-10 with 10 workers of 12 rows: hidden layer 10.9, now 9.1, loss 10.8, now 9.4; 617-301-150-26, always, 24 workers of 100: 11.4, now 9.1;
+  // loss of 3072-1024-1024-10 with 16 workers of 256: 19.6, now 16.6.)
+  const int64_t offa = (((int64_t)(m0 >> 7) * g.A.kt[0]) << 12) + ((m0 & 127) << 5), offb = (((int64_t)(cb >> 2) * g.B.kt[0]) << 12) + ((cb & 3) << 10);
+  // (scalar loads: a wait for a vector load's value would be one for all operands in flight)
+  const int rep_wk = g.rep ? scalar_load(g.rep + wk) : wk, tau_wk = s.rule == CADA_RULE_CADA2 ? scalar_load(s.tau + wk) : 0;
+  int64_t grow = 0;
+  if constexpr (EPI == EPI_LOSS) grow = g.grow[(int64_t)wk * g.Bp + min(m0 + (t >> 4), g.M - 1)];
 #pragma unroll
   for (int sl = 0; sl < NA; ++sl) pa[sl] = g.A.ptr[sl] + (int64_t)wk * g.A.bstride[sl] + offa;
+  const uint32_t area = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem_raw + w * AREA;
+  const uint32_t from[2] = {(uint32_t)lds_piece(lane) * 16u, (uint32_t)lds_piece(64 + lane) * 16u};
+  auto move = [&](const bf16_t *p, int kc, int sl) __attribute__((always_inline)) {
 #pragma unroll
-  for (int sl = 0; sl < NB; ++sl) pb[sl] = g.B.ptr[sl] + (int64_t)(g.rep ? g.rep[wk] : wk) * g.B.bstride[sl] + offb;
+    for (int c = 0; c < 2; ++c) mm_load(p + ((int64_t)kc << 12), from[c], area + sl * 2048 + c * 1024);
+  };
+  if (w < nk) {
+#pragma unroll
+    for (int sl = 0; sl < NA; ++sl) move(pa[sl], w, sl);
+  }
+#pragma unroll
+  for (int sl = 0; sl < NB; ++sl) pb[sl] = g.B.ptr[sl] + (int64_t)rep_wk * g.B.bstride[sl] + offb;
+  if (w < nk) {
+#pragma unroll
+    for (int sl = 0; sl < NB; ++sl) move(pb[sl], w, NA + sl);
+  }
+  // Sixteen lanes share a row of the 32 x 32 result, each with two of the (at most 32) classes or units.  The biases and their differences to the reference point are
+  // asked for behind the first step's operands, the row's label in its products, so that their latency passes under these.
+  const int c0 = 32 * cb + 2 * (t & 15);
+  {
+    const RefPtr ref = theta_ref_at(s, tau_wk, s.k);
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const int64_t i = g.offb + min(c0 + e, g.N - 1);           // (of an absent class: not used)
+      bz[e] = s.theta[i];
+      if constexpr (!PL) dbz[e] = delta_theta(s, ref, i);
+    }
+  }
+  auto ask_label = [&]() __attribute__((always_inline)) { if constexpr (EPI == EPI_LOSS) label = static_cast<const int32_t *>(s.y)[grow]; };
+  if (w >= nk) ask_label();
+  const unsigned char *mine = smem_raw + w * AREA;
+  const int fro = lds_piece((lane & 31) * 4 + (lane >> 5)) * 16;           // this lane's fragment of the first half step (the second: 32 bytes further, in lds_piece's order)
   for (int kc = w; kc < nk; kc += nw) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     u32x4 fa[2][NA], fb[2][NB];          // (kept as integer vectors: arrays of them stay in registers)
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
-      const int64_t o = ((int64_t)kc << 12) + half * 16;
 #pragma unroll
-      for (int sl = 0; sl < NA; ++sl) fa[half][sl] = *reinterpret_cast<const u32x4 *>(pa[sl] + o);
+      for (int sl = 0; sl < NA; ++sl) fa[half][sl] = *reinterpret_cast<const u32x4 *>(mine + sl * 2048 + (fro ^ (32 * half)));
 #pragma unroll
-      for (int sl = 0; sl < NB; ++sl) fb[half][sl] = *reinterpret_cast<const u32x4 *>(pb[sl] + o);
+      for (int sl = 0; sl < NB; ++sl) fb[half][sl] = *reinterpret_cast<const u32x4 *>(mine + (NA + sl) * 2048 + (fro ^ (32 * half)));
+    }
+    if (kc == w) ask_label();
+    if (kc + nw < nk) {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // (the fragments are in registers before the area is written again)
+#pragma unroll
+      for (int sl = 0; sl < NA; ++sl) move(pa[sl], kc + nw, sl);
+#pragma unroll
+      for (int sl = 0; sl < NB; ++sl) move(pb[sl], kc + nw, NA + sl);
     }
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
@@ -1097,16 +1132,18 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
   }
   }
   if (w < nsw) {
+    float *r1 = EPI == EPI_DW ? red + w * 2 * 1024 : part_of(w, 0), *r2 = EPI == EPI_DW ? r1 + 1024 : part_of(w, 1);      // (not EPI_DW: over this wavefront's own blocks)
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      red[((w * 2 + 0) * 16 + r) * 64 + lane] = acc1[r];
-      if constexpr (!PL) red[((w * 2 + 1) * 16 + r) * 64 + lane] = acc2[r];
+      r1[r * 64 + lane] = acc1[r];
+      if constexpr (!PL) r2[r * 64 + lane] = acc2[r];
     }
   }
-  __syncthreads();
+  lds_sync();
   if constexpr (EPI == EPI_FWD_HIDDEN) {
     // bias and ReLU of both evaluations; the block is 2 KB of consecutive memory of each output tensor
-    __shared__ uint8_t pos[2][32][33];              // value at theta, at the reference point is positive
+    uint8_t (*pos[2])[33];                          // [32]: value at theta, at the reference point is positive (in the room behind the partial results)
+    pos[0] = reinterpret_cast<uint8_t (*)[33]>(smem_raw + ROOM); pos[1] = reinterpret_cast<uint8_t (*)[33]>(smem_raw + AREA + ROOM);
     const int rl = t >> 4, c0 = 2 * (t & 15);
     const int ra = 4 * (rl >> 3) + (rl & 3), lb = 32 * ((rl >> 2) & 1);      // (accumulator element of a row: as below)
     float x[2], xref[2];
@@ -1114,21 +1151,14 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
     for (int e = 0; e < 2; ++e) {
       float zs = bz[e], ds = dbz[e];
       for (int ww = 0; ww < nw; ++ww) {
-        zs += red[((ww * 2 + 0) * 16 + ra) * 64 + lb + c0 + e];
-        if constexpr (!PL) ds += red[((ww * 2 + 1) * 16 + ra) * 64 + lb + c0 + e];
+        zs += part_of(ww, 0)[ra * 64 + lb + c0 + e];
+        if constexpr (!PL) ds += part_of(ww, 1)[ra * 64 + lb + c0 + e];
       }
       const bool live = m0 + rl < g.M && 32 * cb + c0 + e < g.N;             // (else padding: zero)
       x[e] = live ? fmaxf(zs, 0.f) : 0.f;
       xref[e] = live && !PL ? fmaxf(zs - ds, 0.f) : 0.f;
     }
     const uint32_t vh = f2bf_pk(x[0], x[1]), vr = f2bf_pk(xref[0], xref[1]);
-    const int64_t o = tm((int64_t)wk * g.Bp + m0 + rl, 32 * cb + c0, g.kto);
-    *reinterpret_cast<uint32_t *>(g.o_h + o) = vh;
-    *reinterpret_cast<uint32_t *>(g.o_l + o) = f2bf_pk(x[0] - __uint_as_float(vh << 16), x[1] - __uint_as_float(vh & 0xffff0000u));
-    if constexpr (!PL) {
-      *reinterpret_cast<uint32_t *>(g.o_d + o) = f2bf_pk(x[0] - xref[0], x[1] - xref[1]);
-      *reinterpret_cast<uint32_t *>(g.o_r + o) = vr;
-    }
     // ReLU masks where k_mm5's activation gradient looks for them (sign of the stored, rounded values): this block is quarter
     // (i, j) of wavefront (wy, wx) of its 128 x 128 tile, sixteen bits of each of the wavefront's lanes
 #pragma unroll
@@ -1136,7 +1166,14 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
       pos[0][rl][c0 + e] = __uint_as_float(e ? vh & 0xffff0000u : vh << 16) > 0.f;
       pos[1][rl][c0 + e] = __uint_as_float(e ? vr & 0xffff0000u : vr << 16) > 0.f;
     }
-    __syncthreads();
+    const int64_t o = tm((int64_t)wk * g.Bp + m0 + rl, 32 * cb + c0, g.kto);
+    *reinterpret_cast<uint32_t *>(g.o_h + o) = vh;
+    *reinterpret_cast<uint32_t *>(g.o_l + o) = f2bf_pk(x[0] - __uint_as_float(vh << 16), x[1] - __uint_as_float(vh & 0xffff0000u));
+    if constexpr (!PL) {
+      *reinterpret_cast<uint32_t *>(g.o_d + o) = f2bf_pk(x[0] - xref[0], x[1] - xref[1]);
+      *reinterpret_cast<uint32_t *>(g.o_r + o) = vr;
+    }
+    lds_sync();
     if (t < 2 * kWave) {
       const int ref = t >> 6;
       uint32_t bits = 0;
@@ -1160,7 +1197,7 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
     // maximum; the difference is then no longer small against its operands.
     // Also the sums over the tile's rows of G and dG: the last layer's bias gradient and its innovation, which the
     // weight-gradient launch of that layer adds up over the row blocks.
-    __shared__ float part[8][16][4];
+    auto part = [&](int ww, int cp_) __attribute__((always_inline)) { return reinterpret_cast<float *>(smem_raw + ww * AREA + ROOM) + cp_ * 4; };      // [16][4] per wavefront
     const int rl = t >> 4, cp = t & 15, c0 = 2 * cp;
     const bool on[2] = {c0 < g.N, c0 + 1 < g.N};
     const int row = m0 + rl;
@@ -1173,8 +1210,8 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
     for (int e = 0; e < 2; ++e) {
       float zs = 0.f, ds = 0.f;
       for (int ww = 0; ww < nw; ++ww) {
-        zs += red[((ww * 2 + 0) * 16 + ra) * 64 + lb + c0 + e];
-        if constexpr (!PL) ds += red[((ww * 2 + 1) * 16 + ra) * 64 + lb + c0 + e];
+        zs += part_of(ww, 0)[ra * 64 + lb + c0 + e];
+        if constexpr (!PL) ds += part_of(ww, 1)[ra * 64 + lb + c0 + e];
       }
       z[e] = on[e] ? zs + bz[e] : -INFINITY;
       ndz[e] = on[e] ? -(ds + dbz[e]) : 0.f;
@@ -1227,12 +1264,12 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
       sumG[e] += __shfl_xor(sumG[e], 16, 64); sumG[e] += __shfl_xor(sumG[e], 32, 64);
       sumD[e] += __shfl_xor(sumD[e], 16, 64); sumD[e] += __shfl_xor(sumD[e], 32, 64);
     }
-    if (lane < 16) { part[w][cp][0] = sumG[0]; part[w][cp][1] = sumG[1]; part[w][cp][2] = sumD[0]; part[w][cp][3] = sumD[1]; }
-    __syncthreads();
+    if (lane < 16) *reinterpret_cast<v4s *>(part(w, cp)) = v4s{sumG[0], sumG[1], sumD[0], sumD[1]};
+    lds_sync();
     if (w == 0 && lane < g.N) {
       const int c = lane;
       float gsum = 0.f, iv = 0.f;
-      for (int ww = 0; ww < nw; ++ww) { gsum += part[ww][c >> 1][c & 1]; iv += part[ww][c >> 1][2 + (c & 1)]; }
+      for (int ww = 0; ww < nw; ++ww) { gsum += part(ww, c >> 1)[c & 1]; iv += part(ww, c >> 1)[2 + (c & 1)]; }
       float *q = g.lastb + ((((int64_t)wk * g.nrb + blockIdx.x) * 32 + c) << 1);
       q[0] = gsum; q[1] = iv;
     }
@@ -1679,9 +1716,9 @@ template <int NA, int NB, bool HAS_D, bool CADA1> int launch_dw_as(Ctx *c, Mm5Ar
 template <int NA, int NB, bool HAS_D, bool CADA1> hipError_t dw_allow_lds() {
   return hipFuncSetAttribute(reinterpret_cast<const void *>(k_dw<NA, NB, HAS_D, CADA1>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kDwLds);
 }
-// per wavefront: its partial results (8 KB); weight gradient: the seven blocks it stages (14 KB), over which the partial results are laid later, and behind
+// per wavefront: the blocks of a step, over which its partial results (4 or 8 KB) are laid later, and a room of 2 KB at least behind those; weight gradient: the seven blocks it stages (14 KB), over which the partial results are laid later, and behind
 // them (1.5 KB) the sums that wavefronts hand on
-constexpr int skinny_lds_bytes(int epi, int nw = 8) { return nw * (epi == EPI_DW ? 7 * 1024 * (int)sizeof(bf16_t) + 3 * 64 * (int)sizeof(float2) : 8192); }
+constexpr int skinny_lds_bytes(int epi, int tensors, int nw = 8) { return nw * (epi == EPI_DW ? 7 * 1024 * (int)sizeof(bf16_t) + 3 * 64 * (int)sizeof(float2) : tensors * 2048); }
 // Wavefronts of a launch: one per two tile steps, eight at most.  A weight gradient sums over a worker's few rows (4-8
 // steps); with eight wavefronts half of them would idle while their LDS kept other workgroups off the CU.
 static int skinny_waves(int epi, int K) {
@@ -1691,7 +1728,7 @@ static int skinny_waves(int epi, int K) {
 }
 template <int EPI, int NA, int NB, bool HAS_D> hipError_t skinny_allow_lds() {
   return hipFuncSetAttribute(reinterpret_cast<const void *>(k_skinny<EPI, NA, NB, HAS_D>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                             skinny_lds_bytes(EPI));
+                             skinny_lds_bytes(EPI, NA + NB));
 }
 template <int EPI, int NA, int NB, bool HAS_D> int launch_skinny_as(Ctx *c, Mm5Args &g) {
   const int nw = skinny_waves(EPI, g.K);
@@ -1702,17 +1739,17 @@ template <int EPI, int NA, int NB, bool HAS_D> int launch_skinny_as(Ctx *c, Mm5A
   // four wavefronts 1.4 us slower than two).
   const int wide = EPI == EPI_DW && nw < 4 && (int64_t)((g.M + 31) / 32 + extra) * g.workers <= 512 ? 4 : nw;
   hipLaunchKernelGGL((k_skinny<EPI, NA, NB, HAS_D>), dim3((unsigned)((g.M + 31) / 32) + extra, g.workers, EPI == EPI_FWD_HIDDEN ? (unsigned)((g.N + 31) / 32) : 1u),
-                     dim3(64 * wide), skinny_lds_bytes(EPI, nw), c->stream, g);
+                     dim3(64 * wide), skinny_lds_bytes(EPI, NA + NB, nw), c->stream, g);
   return CADA_OK;
 }
-// Hidden layers' forward products go through k_skinny while its 32 x 32 blocks fill the chip (two workgroups per CU) at most twice
-// over, or a worker has a single block of rows (a 128 x 128 tile would then be three quarters padding).  Few tiles leave CUs
+// Hidden layers' forward products go through k_skinny while its 32 x 32 blocks fill the chip (two workgroups per CU) some two and a half
+// times over at most, or a worker has a single block of rows (a 128 x 128 tile would then be three quarters padding).  Few tiles leave CUs
 // idle and run through the whole inner dimension one after the other, where k_skinny splits it over eight wavefronts.
-// Measured, us per step with k_skinny and with k_mm5, CADA2: 784-500-10, M = 10: B = 33: 74.7, 89.1, 128 (640 blocks): 85.6, 95.0, 200 (1120): 105.0, 104.4;
-// M = 64: B = 20: 123, 131, 64 (2048): 152, 144; 784-512-10, M = 30: B = 64 (960): 101, 107, 96 (1440): 121, 116; 3072-1024-10, M = 16: B = 48 (1024): 354, 337, 64: 368,
-// 367, 96 (1536): 439, 389; 100-300-10, M = 60: B = 64 (1200): 74.0, 74.4, 96 (1800): 83.6, 79.3; 2000-130-10, M = 40: B = 128 (800): 168, 171, 200 (1400): 226, 203.
-// The always-upload rule: the same sides.
-constexpr int64_t kSkinnyBlocks = 1024;
+// Measured, us per step with k_skinny and with k_mm5 (blocks): 300-400-300-10, M = 20, B = 100 (1040): 132.0, 136.0; 784-500-10: M = 10, B = 200 (1120): 95.9, 101.3; LAG, M = 20,
+// B = 120 (1280): 86.4, 89.5; 784-512-10, M = 30, B = 96 (1440): 112.4, 114.0; 3072-1024-10, M = 16, B = 96 (1536): 346.8, 347.0; but 2000-130-10, M = 40, B = 200 (1400): 235.8, 226.7;
+// 100-300-10, M = 60, B = 96 (1800): 81.0, 78.8, always 60.5, 58.6; 1000-1000-10, M = 16, B = 128 (2048): 192.5, 188.2; 200-700-10, M = 40, B = 128 (3520): 106.8, 94.0; and
+// 784-500-10, M = 64, B = 64 (2048): 144.1, 146.8.
+constexpr int64_t kSkinnyBlocks = 1300;
 static bool skinny_forward(const Mm5Args &g, int workers) {
   return g.M <= 32 || (int64_t)((g.M + 31) / 32) * ((g.N + 31) / 32) * workers <= kSkinnyBlocks;
 }
