@@ -43,10 +43,6 @@ struct DevState {
   float *lhs_part;        // [M][n_lhs_part] partial sums of the left-hand side
   uint8_t *mask;          // [M]
   float *ring;            // [d_max]
-  // Where an earlier launch of the step takes the rule's inputs down (rule_inputs, cada_rule.h; else null), so that the server's workgroups can all run the rule: the right-hand
-  // side, and the workers' delays and buffer selectors [2][M] as they were
-  double *rule_rhs;
-  int32_t *rule_in;
   float *ring_part;       // [n_ring_part] per-block partial sums of the last squared step,
                           // folded into ring[(k-1) mod d_max] by the next rule kernel
   uint64_t *uploads;
@@ -70,6 +66,13 @@ struct DevState {
   double c;
   double alpha0;            // stepsize constant; alpha above is the stepsize of iteration k
   int64_t alpha_K0;         // 0: constant; else alpha_k = alpha0 K0 / (k + K0)
+};
+
+// Where an earlier launch of the step takes the rule's inputs down (rule_inputs, cada_rule.h; else null), so that the server's workgroups can all run the rule: the right-hand
+// side, and the workers' delays and buffer selectors [2][M] as they were.  (Not in DevState: 16 bytes more of it cost the whole-step kernel 2 % of a single step.)
+struct RuleInputs {
+  double *rhs;
+  int32_t *in;
 };
 
 // Reference point of worker m at iteration k (Algorithm 1: theta-tilde for CADA1,
@@ -291,6 +294,7 @@ struct Ctx {
   int64_t chunk_cols;
   float *zpart;              // [M][B][n_col_chunks][2]
   int n_server_blocks;
+  RuleInputs rule_in;
   int decide;                // the server's workgroups run the rule (k_server<., true>)
   int ring_cap;               // entries of ring_part in the workspace
   // single-pass (register-resident) logistic path, cada_logreg_fused.hip
@@ -368,7 +372,7 @@ int mlp_init_state(Ctx *c, const float *theta0);
 void mlp_free(Ctx *c);
 constexpr int kLagSpan = 4096;              // coordinates of a worker that a block of k_lag_lhs takes at a time
 inline int lag_parts(int64_t p) { return (int)((p + kLagSpan - 1) / kLagSpan); }
-// Room for the rule's inputs, and whether the server's workgroups run the rule (cada_server.hip); s.rule_rhs and s.rule_in are then set.
+// Room for the rule's inputs, and whether the server's workgroups run the rule (cada_server.hip).
 constexpr size_t rule_in_bytes(int M) { return 256 + (size_t)M * 2 * sizeof(int32_t); }
 void decide_plan(Ctx *c, char *room);
 // S3: rule, mask, tau.  S5-S7: aggregate, AMSGrad, ring push.

@@ -593,14 +593,14 @@ __global__ __launch_bounds__(R_NT) void k_rows_wide(const RowsArgs a) {
 // Adds up the shares of every worker in their order, adds the regulariser's terms, stores the fresh gradient (CADA1: and the fresh
 // innovation) and the left-hand side's partial sums; the block that finishes last runs the rule.  grid (ceil(p / 1024), M): four
 // columns per thread.  (The last quad may reach past p: it reads up to three floats of what follows in the workspace and drops them.)
-__global__ __launch_bounds__(kBlock) void k_rows_sum(const RowsArgs a) {
+__global__ __launch_bounds__(kBlock) void k_rows_sum(const RowsArgs a, const RuleInputs ri) {
   __shared__ float red[4];
   __shared__ double rule_s[rule_lds(kBlock) / sizeof(double)];
   __shared__ uint32_t flag;
   const DevState &s = a.s;
   const int p = (int)s.p, ps = (p + 3) & ~3, m = blockIdx.y, rule = s.rule;
   if (m == s.M) {                                    // (kTailNone: one more row of blocks)
-    if (blockIdx.x == 0) rule_inputs(s, rule_s);
+    if (blockIdx.x == 0) rule_inputs(s, ri, rule_s);
     return;
   }
   const int64_t mp = (int64_t)s.M * s.p;
@@ -742,7 +742,7 @@ int logreg_step_rows(Ctx *c, const int32_t *idx, const uint8_t *replay) {
   prof_mark(c);
   hipLaunchKernelGGL(c->rows == 2 ? wide_kernel(c->s.p) : rows_kernel(c->s.p, &wc), dim3((unsigned)a.shares, c->rows == 2 ? 1u : (unsigned)c->s.M), dim3(R_NT), c->rows_lds, c->stream, a);
   if (c->rows == 2)
-    hipLaunchKernelGGL(k_rows_sum, dim3((unsigned)((c->s.p + 1023) / 1024), (unsigned)c->s.M + (a.s.rule_rhs ? 1u : 0u)), dim3(kBlock), 0, c->stream, a);
+    hipLaunchKernelGGL(k_rows_sum, dim3((unsigned)((c->s.p + 1023) / 1024), (unsigned)c->s.M + (c->rule_in.rhs ? 1u : 0u)), dim3(kBlock), 0, c->stream, a, c->rule_in);
   prof_mark(c);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) { set_error("logistic step launch failed: %s", hipGetErrorString(e)); return CADA_EHIP; }

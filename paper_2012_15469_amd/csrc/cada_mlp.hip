@@ -1494,6 +1494,7 @@ struct StageArgs {
   int z_groups;          // the groups that share these workers out (M > kBlock: a group for every worker, which finds out for itself whether it is a first one)
   uint32_t first[CADA_MAX_LAYERS + 2];   // first block of the minibatch part (0), of each layer, and the total
   int rule_block;        // 1: one more block, in front of them, takes the rule's inputs down
+  RuleInputs rule_in;
 };
 
 // A 64 x 64 tile of the minibatch, moved 16 bytes (8 values) per lane: the sampled rows of X's bf16
@@ -1638,7 +1639,7 @@ __device__ __forceinline__ void stage_weights(const StageArgs &a, const PrepLaye
 __global__ __launch_bounds__(kBlock) void k_stage(const StageArgs a) {
   __shared__ __align__(16) unsigned char sm[64 * 65 * sizeof(float)];     // a weight tile on its way to the other orientation
   if (a.rule_block && blockIdx.x == 0) {
-    rule_inputs(a.s, reinterpret_cast<double *>(sm));
+    rule_inputs(a.s, a.rule_in, reinterpret_cast<double *>(sm));
     return;
   }
   const uint32_t blk = blockIdx.x - a.rule_block;
@@ -1890,6 +1891,7 @@ static void stage(Ctx *c, const MlpPlan &P, const DevState &s, const int32_t *id
   }
   for (int l = L + 1; l < CADA_MAX_LAYERS + 2; ++l) sa.first[l] = (uint32_t)nblk;
   sa.rule_block = idx ? 1 : 0;
+  sa.rule_in = c->rule_in;
   hipLaunchKernelGGL(k_stage, dim3((unsigned)(nblk + sa.rule_block)), dim3(kBlock), 0, c->stream, sa);
 }
 

@@ -47,14 +47,14 @@ __device__ inline float last_step_sq(const DevState &s, double *red /* [kBlock] 
 
 // The rule's inputs that no other workgroup of the step changes before the server's launch: the right-hand side (the newest squared step goes into the ring here), delays and
 // selectors.  By the kBlock threads of one workgroup of a launch in front.
-__device__ inline void rule_inputs(const DevState &s, double *red /* [kBlock] LDS */) {
+__device__ inline void rule_inputs(const DevState &s, const RuleInputs &ri, double *red /* [kBlock] LDS */) {
   const int last = s.k > 0 ? (int)((s.k - 1) % s.d_max) : -1;
-  for (int m = threadIdx.x; m < s.M; m += kBlock) { s.rule_in[m] = s.tau[m]; s.rule_in[s.M + m] = s.sel[m]; }
+  for (int m = threadIdx.x; m < s.M; m += kBlock) { ri.in[m] = s.tau[m]; ri.in[s.M + m] = s.sel[m]; }
   const float newest = s.k > 0 ? last_step_sq(s, red) : 0.f;
   if (threadIdx.x == 0) {
     double sum = 0.0;
     for (int j = 0; j < s.d_max; ++j) sum += (double)(j == last ? newest : s.ring[j]);
-    *s.rule_rhs = (s.c / (double)s.d_max) * sum;
+    *ri.rhs = (s.c / (double)s.d_max) * sum;
     if (last >= 0) s.ring[last] = newest;
   }
 }

@@ -58,16 +58,16 @@ __global__ __launch_bounds__(kBlock) void k_lag_lhs(const DevState s) {
 // S3 of the step: RHS, per-worker decision, tau, pointer swap, trace.  One wavefront per
 // worker, four workers per block; every block forms the RHS itself (same operations, same
 // value), block 0 records it.
-__global__ __launch_bounds__(kBlock) void k_rule(const DevState s, const uint8_t *replay) {
+__global__ __launch_bounds__(kBlock) void k_rule(const DevState s, const RuleInputs ri, const uint8_t *replay) {
   __shared__ double red[kBlock];
   __shared__ unsigned int cnt;
   const int64_t k = s.k;
   const int last = k > 0 ? (int)((k - 1) % s.d_max) : -1;
-  const bool inputs = s.rule_rhs != nullptr;          // (taken down by an earlier launch of the step)
+  const bool inputs = ri.rhs != nullptr;          // (taken down by an earlier launch of the step)
   const float newest = k > 0 && !inputs ? last_step_sq(s, red) : 0.f;
   double rhs;
   if (inputs) {
-    rhs = *s.rule_rhs;
+    rhs = *ri.rhs;
   } else {
     double sum = 0.0;
     for (int j = 0; j < s.d_max; ++j) sum += (double)(j == last ? newest : s.ring[j]);
@@ -147,7 +147,7 @@ __global__ __launch_bounds__(kBlock) void k_ring_finalize(const DevState s) {
 // of what it reads is written in this launch); the first one keeps the books.  As many workgroups as are resident at once then take the coordinates in turn.
 constexpr int kDecideWorkers = 256, kDecideSerial = 24;
 template <int VEC, bool DECIDE>
-__global__ __launch_bounds__(kBlock, 7) void k_server(const DevState s, const uint8_t *replay) {
+__global__ __launch_bounds__(kBlock, 7) void k_server(const DevState s, const RuleInputs ri, const uint8_t *replay) {
   __shared__ __align__(16) float part[DECIDE ? 2 : 1][4][256];
   __shared__ float sq_s[DECIDE ? 2 : 1][4];
   __shared__ double lhs_s[DECIDE ? kDecideWorkers : 1];
@@ -174,9 +174,9 @@ __global__ __launch_bounds__(kBlock, 7) void k_server(const DevState s, const ui
   if constexpr (DECIDE) {
     const int tid = threadIdx.x, M = s.M, n = s.n_lhs_part;
     const int mine = min(tid, M - 1);
-    const int32_t tau = s.rule_in[mine], sel = s.rule_in[M + mine];
+    const int32_t tau = ri.in[mine], sel = ri.in[M + mine];
     const uint8_t forced = replay != nullptr ? replay[mine] : (uint8_t)CADA_REPLAY_FREE;
-    const double rhs = *s.rule_rhs;
+    const double rhs = *ri.rhs;
     double lhs = 0.0;
     if (n <= kDecideSerial) {            // few parts: each thread adds its worker's up
       const float *lp = s.lhs_part + (int64_t)mine * n;
@@ -351,8 +351,7 @@ __global__ __launch_bounds__(kBlock, 7) void k_server(const DevState s, const ui
 constexpr int64_t kDecideParts = 3000;
 constexpr int kDecideBlocks = 7 * 256;           // seven workgroups of 68 registers per CU
 void decide_plan(Ctx *c, char *room) {
-  c->s.rule_rhs = reinterpret_cast<double *>(room);
-  c->s.rule_in = reinterpret_cast<int32_t *>(room + 256);
+  c->rule_in = RuleInputs{reinterpret_cast<double *>(room), reinterpret_cast<int32_t *>(room + 256)};
   const int64_t M = c->s.M, n = c->s.n_lhs_part;
   c->decide = M <= kDecideWorkers && (n <= kDecideSerial || (M <= 32 && M * n <= kDecideParts));
 }
@@ -365,11 +364,11 @@ int launch_server(Ctx *c, bool decide, const uint8_t *replay) {
   s.resum = (c->force_resum || s.k % s.D == 0) ? 1 : 0;
   const dim3 grid(decide ? min(s.n_ring_part, kDecideBlocks) : s.n_ring_part);
   if (c->vec == 4) {
-    if (decide) hipLaunchKernelGGL((k_server<4, true>), grid, dim3(kBlock), 0, c->stream, s, replay);
-    else hipLaunchKernelGGL((k_server<4, false>), grid, dim3(kBlock), 0, c->stream, s, nullptr);
+    if (decide) hipLaunchKernelGGL((k_server<4, true>), grid, dim3(kBlock), 0, c->stream, s, c->rule_in, replay);
+    else hipLaunchKernelGGL((k_server<4, false>), grid, dim3(kBlock), 0, c->stream, s, c->rule_in, nullptr);
   } else {
-    if (decide) hipLaunchKernelGGL((k_server<1, true>), grid, dim3(kBlock), 0, c->stream, s, replay);
-    else hipLaunchKernelGGL((k_server<1, false>), grid, dim3(kBlock), 0, c->stream, s, nullptr);
+    if (decide) hipLaunchKernelGGL((k_server<1, true>), grid, dim3(kBlock), 0, c->stream, s, c->rule_in, replay);
+    else hipLaunchKernelGGL((k_server<1, false>), grid, dim3(kBlock), 0, c->stream, s, c->rule_in, nullptr);
   }
   prof_mark(c);
   const hipError_t e = hipGetLastError();
@@ -385,7 +384,7 @@ int rule_then_server(Ctx *c, const uint8_t *replay) {
   if (c->decide) return launch_server(c, true, replay);
   DevState s = c->s;
   s.k = c->k;
-  hipLaunchKernelGGL(k_rule, dim3((unsigned)((s.M + 3) / 4)), dim3(kBlock), 0, c->stream, s, replay);
+  hipLaunchKernelGGL(k_rule, dim3((unsigned)((s.M + 3) / 4)), dim3(kBlock), 0, c->stream, s, c->rule_in, replay);
   prof_mark(c);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
