@@ -72,10 +72,26 @@ struct SmallVar {
   int64_t k;
   uint32_t bar_base;         // sequence number of this launch's first step (monotone over the life of the context)
 };
+// An iteration k where a launch of several steps needs it modulo something: k mod (D + 1) (slot of the iterate history), k mod D (CADA1's snapshots), k mod d_max (ring of
+// squared steps).  The host forms the first step's, the others follow: the modulo of a 64-bit k is some 130 instructions in the chain of every step.  Ten runs of 20 steps,
+// M = 10, B = 10, p = 54, side by side: 141.8 -> 139.8 us, 20 steps, M = 20, B = 32, p = 784: 234.6 -> 229.5.  (A single step forms them itself: as arguments they cost it 1 %.)
+struct Phase { int32_t R, D, d; };
+static Phase phase_of(const DevState &s, int64_t k) { return Phase{(int32_t)(k % s.R), (int32_t)(k % s.D), (int32_t)(k % s.d_max)}; }
+__device__ __forceinline__ Phase phase_after(const DevState &s, Phase ph) {
+  return Phase{ph.R + 1 == s.R ? 0 : ph.R + 1, ph.D + 1 == s.D ? 0 : ph.D + 1, ph.d + 1 == s.d_max ? 0 : ph.d + 1};
+}
+__device__ __forceinline__ RefPtr theta_ref_in(const DevState &s, int32_t tau_m, const Phase &ph) {       // theta_ref_at of an iteration in that phase
+  if (s.rule == CADA_RULE_CADA1) return RefPtr{s.snap, s.snap_lo};
+  if (s.rule != CADA_RULE_CADA2) return RefPtr{s.theta, s.theta_lo};
+  int32_t slot = ph.R - min(tau_m, s.D);
+  if (slot < 0) slot += s.R;
+  return RefPtr{s.hist + (int64_t)slot * s.ps, s.hist_lo + (int64_t)slot * s.ps};
+}
 // Several independent runs (blockIdx.y picks the run) or one.
 struct SmallLaunch {
   const SmallArgs *rep[CADA_MAX_REPLICAS];
   SmallVar var[CADA_MAX_REPLICAS];
+  Phase ph[CADA_MAX_REPLICAS];         // of the first step
   int64_t n_steps;
 };
 static_assert(sizeof(SmallLaunch) <= 4096, "kernel arguments");
@@ -101,7 +117,7 @@ __host__ __device__ inline size_t small_floats(int ps, int B, int rule, int grou
 }
 
 template <bool ONE>
-__device__ __forceinline__ void small_body(const SmallArgs &a, const uint32_t *state /* a.s in memory */, const SmallVar &v, int64_t n_steps) {
+__device__ __forceinline__ void small_body(const SmallArgs &a, const uint32_t *state /* a.s in memory */, const SmallVar &v, Phase ph, int64_t n_steps) {
   extern __shared__ __align__(16) unsigned char small_smem[];
   const DevState &s = a.s;
   const int p = (int)s.p, ps = a.ps, B = s.B, M = s.M, B4 = (s.B + 3) & ~3, nq = ps >> 2, rule = s.rule;
@@ -157,7 +173,7 @@ __device__ __forceinline__ void small_body(const SmallArgs &a, const uint32_t *s
       if (b0 + lane < B) lds_direct<4>(static_cast<const float *>(s.y) + base + row_n[b0 + lane], r_s + b0);
   };
   // Everything the start needs is asked for before anything is waited for; only the rows depend on their indices.
-  const RefPtr ref = theta_ref_at(s, tau_m, v.k);
+  const RefPtr ref = ONE ? theta_ref_at(s, tau_m, v.k) : theta_ref_in(s, tau_m, ph);
   const float *stored = (rule == CADA_RULE_CADA1 ? s.dtl : s.gbuf) + (int64_t)cur * mp + (int64_t)m * s.p;
   const int32_t idx0 = tid < B ? idx[tid] : 0;
   const uint32_t state0 = tid < (int)(sizeof(DevState) / 4) ? state[tid] : 0u;
@@ -199,6 +215,8 @@ __device__ __forceinline__ void small_body(const SmallArgs &a, const uint32_t *s
 
   for (int64_t step = 0; step < n_steps; ++step) {
     const int64_t k = v.k + step;
+    const Phase ph1 = phase_after(s, ph);      // of k + 1
+    const int newest_at = ONE ? k > 0 ? (int)((k - 1) % s.d_max) : 0 : ph.d == 0 ? s.d_max - 1 : ph.d - 1;
     const bool more = !ONE && step + 1 < n_steps;
     lds_sync();            // (the wavefronts waited for the rows before they came here)
     int32_t nidx = 0;
@@ -208,7 +226,7 @@ __device__ __forceinline__ void small_body(const SmallArgs &a, const uint32_t *s
       float newest = red_q[0];
 #pragma unroll
       for (int i = 1; i < S_NW; ++i) newest += red_q[i];
-      if (k > 0) ring_s[(k - 1) % s.d_max] = newest;
+      if (k > 0) ring_s[newest_at] = newest;
       double sum = 0.0;
 #pragma unroll 4
       for (int j = 0; j < s.d_max; ++j) sum += (double)ring_s[j];
@@ -406,10 +424,10 @@ __device__ __forceinline__ void small_body(const SmallArgs &a, const uint32_t *s
     const bool up_m = (int)dk_s[m] != cur;
     if (up_m) { tau_m = 1; cur ^= 1; } else tau_m += 1;
     // ------------------------------------------------------------ phase B
-    if ((ONE || m == 0) && tid == 0 && k > 0) at.ring[(k - 1) % s.d_max] = newest_s;   // (for the world outside: every workgroup has its own copy)
+    if ((ONE || m == 0) && tid == 0 && k > 0) at.ring[newest_at] = newest_s;   // (for the world outside: every workgroup has its own copy)
     float sqs = 0.f;
     const float alpha = stepsize(s, k);
-    const bool snap_now = rule == CADA_RULE_CADA1 && (k + 1) % s.D == 0;
+    const bool snap_now = rule == CADA_RULE_CADA1 && (ONE ? (k + 1) % s.D == 0 : ph1.D == 0);
     // the decisions as bits of scalar registers, 64 workers each (M <= 256)
     unsigned long long sel64[4];
 #pragma unroll
@@ -461,10 +479,10 @@ __device__ __forceinline__ void small_body(const SmallArgs &a, const uint32_t *s
       } else {
         d_s[j] = 0.f;
       }
-      if (ONE || (j / 256) % nb == m) {
+      if (ONE || (j < 256 * nb ? j / 256 : (j / 256) % nb) == m) {
         at.nabla[j] = nab; at.h[j] = hh; at.v[j] = vv; at.vhat[j] = vh; at.theta[j] = th; at.theta_lo[j] = tl;
         if (rule == CADA_RULE_CADA2) {      // (read by other workgroups of this launch below)
-          const int64_t o = ((k + 1) % s.R) * s.p + j;
+          const int64_t o = (ONE ? (k + 1) % s.R : ph1.R) * s.p + j;
           __hip_atomic_store(at.hist + o, th, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           __hip_atomic_store(at.hist_lo + o, tl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         } else if (snap_now) {
@@ -479,7 +497,7 @@ __device__ __forceinline__ void small_body(const SmallArgs &a, const uint32_t *s
       // only a replay mask does this: the worker's reference point has left the retained iterates and the
       // oldest of them, theta^{k + 1 - D}, stands for it (written D steps ago; with D = 1 by the step before)
       full_sync();
-      const RefPtr ref = theta_ref_at(at, tau_m, k + 1);
+      const RefPtr ref = theta_ref_in(at, tau_m, ph1);
       for (int j = tid; j < p; j += S_NT) {
         const float rf = __hip_atomic_load(ref.hi + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const float rl = __hip_atomic_load(ref.lo + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -487,6 +505,7 @@ __device__ __forceinline__ void small_body(const SmallArgs &a, const uint32_t *s
         d_s[j] = (th_s[j] - rf) + (tl_s[j] - rl);
       }
     }
+    ph = ph1;
   }
   // what a later launch, or reading the state out, adds up
   lds_sync();
@@ -509,11 +528,11 @@ __global__ __launch_bounds__(S_NT) void k_small(const SmallLaunch launch) {
   for (int i = 0; i < n; ++i) words[i] = src[i];
   SmallArgs a;
   __builtin_memcpy(&a, words, sizeof(a));
-  small_body<false>(a, reinterpret_cast<const uint32_t *>(&launch.rep[blockIdx.y]->s), launch.var[blockIdx.y], launch.n_steps);
+  small_body<false>(a, reinterpret_cast<const uint32_t *>(&launch.rep[blockIdx.y]->s), launch.var[blockIdx.y], launch.ph[blockIdx.y], launch.n_steps);
 }
 
 // grid M
-__global__ __launch_bounds__(S_NT) void k_small_one(const SmallArgs a, const SmallVar v) { small_body<true>(a, reinterpret_cast<const uint32_t *>(&a.s), v, 1); }
+__global__ __launch_bounds__(S_NT) void k_small_one(const SmallArgs a, const SmallVar v) { small_body<true>(a, reinterpret_cast<const uint32_t *>(&a.s), v, Phase{0, 0, 0}, 1); }
 
 // Whether the multi-step kernel serves this configuration.
 bool small_plan(Ctx *c, const cada_config *cfg) {
@@ -598,6 +617,7 @@ int small_steps_replicas(Ctx *const *cs, int n, const int32_t *const *idx, const
   for (int r = 0; r < n; ++r) {
     l.rep[r] = static_cast<const SmallArgs *>(cs[r]->small_args);
     l.var[r] = SmallVar{idx[r], replay ? replay[r] : nullptr, cs[r]->k, cs[r]->small_seq};
+    l.ph[r] = phase_of(cs[r]->s, cs[r]->k);
   }
   void *args[] = {&l};
   prof_mark(c0);
@@ -627,6 +647,7 @@ int small_steps(Ctx *c, const int32_t *idx, const uint8_t *replay, int64_t n_ste
   l.n_steps = n_steps;
   l.rep[0] = static_cast<const SmallArgs *>(c->small_args);
   l.var[0] = SmallVar{idx, replay, c->k, c->small_seq};
+  l.ph[0] = phase_of(c->s, c->k);
   void *args[] = {&l};
   prof_mark(c);
   hipError_t e;
