@@ -118,12 +118,16 @@ struct Mm5Args {
 __device__ __forceinline__ float delta_theta(const DevState &s, const RefPtr &ref, int64_t i) {
   return (s.theta[i] - ref.hi[i]) + (s.theta_lo[i] - ref.lo[i]);
 }
+// A value that earlier launches wrote and nobody changes in this one, at a uniform address.
+__device__ __forceinline__ int32_t scalar_load(const int32_t *p) { return *(const __attribute__((address_space(4))) int32_t *)(uintptr_t)p; }
+
+// (the selector by a scalar load: the compiler asks for it early, and no wait for it is one for the operands or stores in flight)
 __device__ __forceinline__ float *fresh_grad(const DevState &s, int m) {
-  return s.gbuf + ((int64_t)(1 - s.sel[m]) * s.M + m) * s.ps;
+  return s.gbuf + ((int64_t)(1 - scalar_load(s.sel + m)) * s.M + m) * s.ps;
 }
 // (bf16 gradient store: the same row of gbuf16; exactly one of the two stores exists)
 __device__ __forceinline__ uint16_t *fresh_grad16(const DevState &s, int m) {
-  return s.gbuf16 + ((int64_t)(1 - s.sel[m]) * s.M + m) * s.ps16;
+  return s.gbuf16 + ((int64_t)(1 - scalar_load(s.sel + m)) * s.M + m) * s.ps16;
 }
 // coordinate i of worker m's fresh gradient, into whichever store the context keeps
 __device__ __forceinline__ void put_fresh_grad(const DevState &s, int m, int64_t i, float v) {
@@ -133,10 +137,10 @@ __device__ __forceinline__ void put_fresh_grad(const DevState &s, int m, int64_t
 
 // CADA1's stored innovations (bf16): the row this step writes and the row of the last upload.
 __device__ __forceinline__ bf16_t *fresh_innov(const DevState &s, int m) {
-  return s.dtl16 + ((int64_t)(1 - s.sel[m]) * s.M + m) * s.ps16;
+  return s.dtl16 + ((int64_t)(1 - scalar_load(s.sel + m)) * s.M + m) * s.ps16;
 }
 __device__ __forceinline__ const bf16_t *stored_innov(const DevState &s, int m) {
-  return s.dtl16 + ((int64_t)s.sel[m] * s.M + m) * s.ps16;
+  return s.dtl16 + ((int64_t)scalar_load(s.sel + m) * s.M + m) * s.ps16;
 }
 
 __device__ __forceinline__ u32x4 pack8(const bf16_t (&v)[8]) {
@@ -185,9 +189,6 @@ __device__ __forceinline__ bf16x8 tr_fragment(const bf16_t *blk, int lane_off) {
 __device__ __forceinline__ void mm_load(const bf16_t *base, uint32_t byte_off, uint32_t lds) {      // 1 KB, 16 bytes per lane, to `lds` (uniform)
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(byte_off), "s"(base), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory", "m0");
 }
-// A value that earlier launches wrote and nobody changes in this one, at a uniform address.
-__device__ __forceinline__ int32_t scalar_load(const int32_t *p) { return *(const __attribute__((address_space(4))) int32_t *)(uintptr_t)p; }
-
 // Bias gradient of a hidden layer's units col .. (one per lane) and its innovation, from the sums that the signals' launch left per band of
 // 64 rows, and (not PL) the wavefront's 64 units' partial sum of the left-hand side: in the launch of the layer's weight gradient.
 template <bool PL, bool CADA1>
@@ -259,7 +260,7 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
       const int trow = quotient(tix, g.gx), bx = tix - trow * gx, bz = quotient(trow, g.gy), by = trow - bz * gy;
 #pragma unroll
       for (int sl = 0; sl < NA; ++sl) pa[sl] = g.A.ptr[sl] + (int64_t)bz * g.A.bstride[sl] + (((int64_t)by * (TR ? 4 : g.A.kt[sl])) << 12);
-      const int bzb = g.rep ? g.rep[bz] : bz;
+      const int bzb = g.rep ? scalar_load(g.rep + bz) : bz;
 #pragma unroll
       for (int sl = 0; sl < NB; ++sl) pb[sl] = g.B.ptr[sl] + (int64_t)bzb * g.B.bstride[sl] + (((int64_t)bx * (TR ? 4 : g.B.kt[sl])) << 12);
     };
@@ -309,6 +310,23 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
   const int tix = t_first + ord * nbx;
   const int trow = quotient(tix, g.gx), bx = tix - trow * gx, wk = quotient(trow, g.gy), by = trow - wk * gy;     // wk: worker
   const int m0 = by * BM, n0 = bx * BN;
+  const int rbase = m0 + wy * 64 + 4 * (lane >> 5);
+  const int cbase = n0 + wx * 64 + (lane & 31);
+  // What the epilogue starts with is asked for here: both columns' biases at theta and at the reference point, or the ReLU masks.
+  uint64_t *mbits = nullptr;
+  if constexpr (!TR) mbits = g.maskbits + ((((int64_t)wk * gy + by) * gx + bx) * kBlock + t) * 2;
+  float bias[2] = {0.f, 0.f}, bias_lo[2] = {0.f, 0.f}, ref_hi[2] = {0.f, 0.f}, ref_lo[2] = {0.f, 0.f};
+  u32x4 masks = {0u, 0u, 0u, 0u};
+  if constexpr (EPI == EPI_FWD_HIDDEN) {
+    const RefPtr ref = theta_ref_at(s, s.rule == CADA_RULE_CADA2 ? scalar_load(s.tau + wk) : 0, s.k);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int64_t i = g.offb + min(cbase + j * 32, g.N - 1);
+      bias[j] = s.theta[i];
+      if constexpr (!PL) { bias_lo[j] = s.theta_lo[i]; ref_hi[j] = ref.hi[i]; ref_lo[j] = ref.lo[i]; }
+    }
+  }
+  if constexpr (EPI == EPI_DA) masks = *reinterpret_cast<const u32x4 *>(mbits);
 
   f32x16 acc1[2][2], acc2[2][2];
 #pragma unroll
@@ -361,8 +379,6 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
 
   // accumulator element (i, j, r) is output (row, col):
   //   row = m0 + wy*64 + i*32 + 8*(r>>2) + 4*(lane>>5) + (r&3),  col = n0 + wx*64 + j*32 + (lane&31)
-  const int rbase = m0 + wy * 64 + 4 * (lane >> 5);
-  const int cbase = n0 + wx * 64 + (lane & 31);
   const int64_t rp0 = (int64_t)wk * g.Bp;            // first padded row of this worker
   if constexpr (!TR) {
     // Forward: bias, ReLU of both evaluations.  Activation gradient: ReLU masks of the layer
@@ -397,29 +413,15 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
     // contraction into it have the same tiles and the same element-to-lane map, so the forward
     // epilogue leaves each lane's 2 x 64 bits where the backward one finds them: 16 bytes per lane.
     uint64_t bit_on = 0, bit_ref = 0;
-    uint64_t *mbits = g.maskbits + ((((int64_t)wk * gy + by) * gx + bx) * kBlock + t) * 2;
     if constexpr (EPI == EPI_DA) {
-      const u32x4 mb = *reinterpret_cast<const u32x4 *>(mbits);
-      bit_on = (uint64_t)mb.x | ((uint64_t)mb.y << 32);
-      bit_ref = (uint64_t)mb.z | ((uint64_t)mb.w << 32);
-    }
-
-    // (both columns' biases are asked for before either is used: one memory latency, not two)
-    float bias[2] = {0.f, 0.f}, dbias[2] = {0.f, 0.f};
-    if constexpr (EPI == EPI_FWD_HIDDEN) {
-      const RefPtr ref = theta_ref(s, wk, s.k);
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int col = min(cbase + j * 32, g.N - 1);
-        bias[j] = s.theta[g.offb + col];
-        if constexpr (!PL) dbias[j] = delta_theta(s, ref, g.offb + col);
-      }
+      bit_on = (uint64_t)masks.x | ((uint64_t)masks.y << 32);
+      bit_ref = (uint64_t)masks.z | ((uint64_t)masks.w << 32);
     }
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       const int col = cbase + j * 32;
       const bool cok = col < g.N;
-      const float b = bias[j], db = dbias[j];
+      const float b = bias[j], db = (bias[j] - ref_hi[j]) + (bias_lo[j] - ref_lo[j]);       // (as delta_theta)
       float sg_sum = 0.f, sd_sum = 0.f;
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
@@ -924,7 +926,7 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
     if constexpr (PL || HAS_D) {
       if (g.w_h != nullptr) {
         const int64_t o = (((int64_t)(m0 >> 7) * g.w_kt) << 12) + (((m0 & 127) + (lane & 31)) << 5) + ((lane >> 5) << 3);
-        const int64_t od = (int64_t)(g.rep ? g.rep[wk] : wk) * g.w_dstride + o;
+        const int64_t od = (int64_t)(g.rep ? scalar_load(g.rep + wk) : wk) * g.w_dstride + o;
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
           wh[half] = *reinterpret_cast<const u32x4 *>(g.w_h + o + 16 * half);
