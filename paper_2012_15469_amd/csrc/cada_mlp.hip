@@ -549,9 +549,9 @@ constexpr int kDwRows = 16;                                    // rows per step
 constexpr int kDwSlots = 20;
 constexpr size_t kDwLds = kDwSlots * 4096;
 
+// at: the workgroup's place among its XCD's.
 template <int NA, int NB, bool HAS_D, bool CADA1>
-__global__ __launch_bounds__(kBlock, 2) void k_dw(const Mm5Args g) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
+__device__ __forceinline__ void weight_gradient(const Mm5Args &g, int at, unsigned char *smem_raw) {
   constexpr int NS = NA + NB, NSLOT = kDwSlots, AHEAD = NSLOT / NS, R0 = NSLOT % NS;
   constexpr int LANDED = (NSLOT - 4) / NS - 1;      // steps of a tile that need not wait for their loads: those had landed before the last tile's way out
   constexpr bool PL = NB == 2;
@@ -561,7 +561,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_dw(const Mm5Args g) {
   // tiles of this workgroup: as in k_mm5
   const int gx = g.gx.d, gy = g.gy.d;
   const int total = gx * gy * g.workers, per = (total + 7) / 8, nbx = g.nbx.d;
-  const int t_first = (blockIdx.x & 7) * per + (blockIdx.x >> 3), t_end = min(((int)(blockIdx.x & 7) + 1) * per, total);
+  const int t_first = (blockIdx.x & 7) * per + at, t_end = min(((int)(blockIdx.x & 7) + 1) * per, total);
   if (t_first >= t_end) return;
   const int nt = quotient(t_end - t_first + nbx - 1, g.nbx), nk = (g.K + kDwRows - 1) / kDwRows, nsteps = nt * nk;
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem_raw;
@@ -833,6 +833,25 @@ __global__ __launch_bounds__(kBlock, 2) void k_dw(const Mm5Args g) {
       if (lane == 0) s.lhs_part[(int64_t)wk * s.n_lhs_part + g.lhs_slot0 + (by * gx + bx) * 4 + w] = tot;
     }
   }   // tiles
+}
+
+template <int NA, int NB, bool HAS_D, bool CADA1>
+__global__ __launch_bounds__(kBlock, 2) void k_dw(const Mm5Args g) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  weight_gradient<NA, NB, HAS_D, CADA1>(g, blockIdx.x >> 3, smem_raw);
+}
+// The second layer's and the first layer's in one launch (the same number of workgroups per XCD for both; the first layer's tiles are dealt from the other end, so that where
+// the tiles are few the two layers have workgroups of their own).  It saves a launch and the first one's last wave.  us per step, two launches / one: 617-301-150-26, always,
+// 24 workers of 100 rows: 87.6 / 84.5; 784-512-512-10, LAG, 10 of 12: 82.6 / 78.9; 300-400-300-10, 64 of 60: 174.9 / 167.6; 3072-1024-1024-10, 16 of 256: 572.4 / 562.0.
+template <bool PL, bool CADA1>
+__global__ __launch_bounds__(kBlock, 2) void k_dw_two(const Mm5Args g2, const Mm5Args g1) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const int at = blockIdx.x >> 3, last = g1.nbx.d - 1;
+  if constexpr (PL) weight_gradient<2, 2, false, false>(g2, at, smem_raw);
+  else weight_gradient<3, 4, true, CADA1>(g2, at, smem_raw);
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");      // (the ring's slots are written again; every load into them has landed)
+  if constexpr (PL) weight_gradient<2, 2, false, false>(g1, last - at, smem_raw);
+  else weight_gradient<2, 3, false, CADA1>(g1, last - at, smem_raw);
 }
 
 __device__ __forceinline__ float group16_sum(float x) {
@@ -1378,8 +1397,9 @@ void layout(MlpPlan &P, const cada_config *cfg, int64_t total_rows, Carve &w) {
   }
   (void)w.take<float>(Rp * P.d[P.L]);             // (not used any more; the room keeps the layout of saved checkpoint blocks)
   (void)w.take<float>(Rp * P.d[P.L]);
-  P.dbpart = w.take<float>((size_t)cfg->M * 2 * P.RT * maxh);
-  P.ddbpart = w.take<float>((size_t)cfg->M * 2 * P.RT * maxh);
+  P.dbpart[0] = w.take<float>((size_t)cfg->M * 2 * P.RT * maxh);
+  P.ddbpart[0] = w.take<float>((size_t)cfg->M * 2 * P.RT * maxh);
+  P.band_floats = (size_t)cfg->M * 2 * P.RT * maxh;
   P.lastb = w.take<float>((size_t)cfg->M * (P.Bp / 32) * 32 * 2);
 }
 }  // namespace
@@ -1417,11 +1437,14 @@ static size_t lhs_bytes(const cada_config *cfg) {
   return ((size_t)cfg->M * mlp_lhs_slots(cfg, mlp_bias_cols(cfg->rule)) * sizeof(float) + kAlignB - 1) / kAlignB * kAlignB + rule_room(cfg);
 }
 
+// The sums per band of the odd layers' signals (two arrays), behind them.
+static size_t bands_bytes(const MlpPlan &P) { return 2 * ((P.band_floats * sizeof(float) + kAlignB - 1) / kAlignB * kAlignB); }
+
 size_t mlp_scratch_bytes(const cada_config *cfg, const int64_t total_rows) {
   MlpPlan P;
   Carve w{nullptr, 0};
   layout(P, cfg, total_rows, w);
-  return lhs_bytes(cfg) + mlp_eval_bytes(P) + kAlignB;
+  return lhs_bytes(cfg) + bands_bytes(P) + mlp_eval_bytes(P) + kAlignB;
 }
 
 int mlp_plan(Ctx *c, const cada_config *cfg, char *base, size_t offset, size_t scratch, int64_t total_rows) {
@@ -1435,7 +1458,9 @@ int mlp_plan(Ctx *c, const cada_config *cfg, char *base, size_t offset, size_t s
   // (the rules without a second gradient: a part per block of k_lag_lhs)
   if (cfg->rule == CADA_RULE_LAG || cfg->rule == CADA_RULE_ALWAYS) c->s.n_lhs_part = std::min(c->s.n_lhs_part, lag_parts(cfg->p));
   decide_plan(c, base + scratch + lhs_bytes(cfg) - rule_room(cfg));
-  P->eval = base + scratch + lhs_bytes(cfg);
+  P->dbpart[1] = reinterpret_cast<float *>(base + scratch + lhs_bytes(cfg));
+  P->ddbpart[1] = reinterpret_cast<float *>(base + scratch + lhs_bytes(cfg) + bands_bytes(*P) / 2);
+  P->eval = base + scratch + lhs_bytes(cfg) + bands_bytes(*P);
   c->mlp = P;
   c->n_phases = 0;
   c->phase_names[c->n_phases++] = "mlp_gradients";
@@ -1716,6 +1741,16 @@ template <int NA, int NB, bool HAS_D, bool CADA1> int launch_dw_as(Ctx *c, Mm5Ar
   hipLaunchKernelGGL((k_dw<NA, NB, HAS_D, CADA1>), dim3(8 * g.nbx.d), dim3(kBlock), kDwLds, c->stream, g);
   return CADA_OK;
 }
+template <bool PL, bool CADA1> int launch_dw_two(Ctx *c, Mm5Args &g2, Mm5Args &g1) {
+  int most = 0;
+  for (const Mm5Args *g : {&g2, &g1}) most = std::max(most, (((g->N + BN - 1) / BN) * ((g->M + BM - 1) / BM) * g->workers + 7) / 8);
+  set_tiles(g2, std::min(most, 64)); set_tiles(g1, std::min(most, 64));
+  hipLaunchKernelGGL((k_dw_two<PL, CADA1>), dim3(8 * g1.nbx.d), dim3(kBlock), kDwLds, c->stream, g2, g1);
+  return CADA_OK;
+}
+template <bool PL, bool CADA1> hipError_t dw_two_allow_lds() {
+  return hipFuncSetAttribute(reinterpret_cast<const void *>(k_dw_two<PL, CADA1>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kDwLds);
+}
 template <int NA, int NB, bool HAS_D, bool CADA1> hipError_t dw_allow_lds() {
   return hipFuncSetAttribute(reinterpret_cast<const void *>(k_dw<NA, NB, HAS_D, CADA1>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kDwLds);
 }
@@ -1768,9 +1803,23 @@ static bool dw_past_caches(const Mm5Args &g) {
   const int64_t bytes = (int64_t)g.workers * g.s.ps * 4;
   return g.s.gbuf16 == nullptr && bytes > 200000000 && bytes * g.K > (g.N % 32 == 0 ? 12000000000ll : 24000000000ll) && (g.N % 4 == 0 || g.K > 64);
 }
+template <int EPI> bool tiles_fit(const Mm5Args &g) {
+  // every tensor must hold the chunks the tile steps walk through: the contraction indices along a row
+  // tile, or (weight gradient: units are output rows, the steps walk down the worker's rows) whole
+  // 128-unit tiles and the worker's padded rows
+  const int64_t needA = EPI == EPI_DW ? 4 * ((g.M + BM - 1) / BM) : (g.K + BK - 1) / BK;
+  const int64_t needB = EPI == EPI_DW ? 4 * ((g.N + BN - 1) / BN) : (g.K + BK - 1) / BK;
+  for (int i = 0; i < g.A.n; ++i)
+    if (g.A.kt[i] < needA) { set_error("internal: A tensor with fewer chunks than the tiles walk through"); return false; }
+  for (int i = 0; i < g.B.n; ++i)
+    if (g.B.kt[i] < needB) { set_error("internal: B tensor with fewer chunks than the tiles walk through"); return false; }
+  if (EPI == EPI_DW && (int64_t)((g.K + BK - 1) / BK) * BK > g.Bp) { set_error("internal: more rows than a worker's padded tile"); return false; }
+  return true;
+}
 // Returns CADA_OK after enqueueing the launch, CADA_EUNSUPPORTED (and launches nothing) when the
 // operands do not fit a compiled variant.
-template <int EPI> int launch_mm5(Ctx *c, Mm5Args &g, int workers) {
+// first (EPI_DW): arguments of the layer above's weight gradient, kept back to be launched together with this one's.
+template <int EPI> int launch_mm5(Ctx *c, Mm5Args &g, int workers, Mm5Args *first = nullptr) {
   g.workers = workers;
   const bool has_d = g.a_d >= 0;
   if constexpr (EPI == EPI_DW || EPI == EPI_LOSS || EPI == EPI_FWD_HIDDEN) {
@@ -1796,18 +1845,14 @@ template <int EPI> int launch_mm5(Ctx *c, Mm5Args &g, int workers) {
     set_error("internal: the loss epilogue serves at most 32 classes");
     return CADA_EUNSUPPORTED;
   } else {
-  // every tensor must hold the chunks the tile steps walk through: the contraction indices along a row
-  // tile, or (weight gradient: units are output rows, the steps walk down the worker's rows) whole
-  // 128-unit tiles and the worker's padded rows
-  const int64_t needA = EPI == EPI_DW ? 4 * ((g.M + BM - 1) / BM) : (g.K + BK - 1) / BK;
-  const int64_t needB = EPI == EPI_DW ? 4 * ((g.N + BN - 1) / BN) : (g.K + BK - 1) / BK;
-  for (int i = 0; i < g.A.n; ++i)
-    if (g.A.kt[i] < needA) { set_error("internal: A tensor with fewer chunks than the tiles walk through"); return CADA_EUNSUPPORTED; }
-  for (int i = 0; i < g.B.n; ++i)
-    if (g.B.kt[i] < needB) { set_error("internal: B tensor with fewer chunks than the tiles walk through"); return CADA_EUNSUPPORTED; }
-  if (EPI == EPI_DW && (int64_t)((g.K + BK - 1) / BK) * BK > g.Bp) { set_error("internal: more rows than a worker's padded tile"); return CADA_EUNSUPPORTED; }
+  if (!tiles_fit<EPI>(g) || (first != nullptr && !tiles_fit<EPI>(*first))) return CADA_EUNSUPPORTED;
   if constexpr (EPI == EPI_DW) {
     const bool cada1 = g.s.rule == CADA_RULE_CADA1;
+    if (first != nullptr) {
+      if (g.A.n == 2 && g.B.n == 2 && first->A.n == 2 && first->B.n == 2) return launch_dw_two<true, false>(c, *first, g);
+      if (!has_d && g.A.n == 2 && g.B.n == 3 && first->a_d >= 0 && first->A.n == 3 && first->B.n == 4)
+        return cada1 ? launch_dw_two<false, true>(c, *first, g) : launch_dw_two<false, false>(c, *first, g);
+    }
     if (g.A.n == 2 && g.B.n == 2) return dw_past_caches(g) ? launch_mm5_as<EPI, 2, 2, false>(c, g) : launch_dw_as<2, 2, false, false>(c, g);
     if (!has_d && g.A.n == 2 && g.B.n == 3) return cada1 ? launch_dw_as<2, 3, false, true>(c, g) : launch_dw_as<2, 3, false, false>(c, g);
     if (has_d && g.A.n == 3 && g.B.n == 4) return cada1 ? launch_dw_as<3, 4, true, true>(c, g) : launch_dw_as<3, 4, true, false>(c, g);
@@ -1852,6 +1897,9 @@ int mlp_init_state(Ctx *c, const float *) {
   if (e == hipSuccess) e = dw_allow_lds<2, 3, false, true>();
   if (e == hipSuccess) e = dw_allow_lds<3, 4, true, false>();
   if (e == hipSuccess) e = dw_allow_lds<3, 4, true, true>();
+  if (e == hipSuccess) e = dw_two_allow_lds<true, false>();
+  if (e == hipSuccess) e = dw_two_allow_lds<false, false>();
+  if (e == hipSuccess) e = dw_two_allow_lds<false, true>();
   if (e == hipSuccess) e = mm5_allow_lds<EPI_DA, 4, 3, true>();
   if (e == hipSuccess) e = skinny_allow_lds<EPI_LOSS, 2, 3, false>();
   if (e == hipSuccess) e = skinny_allow_lds<EPI_LOSS, 4, 3, true>();
@@ -1960,7 +2008,7 @@ static void signals_below(Mm5Args &g, const MlpPlan &P, int q, bool plain) {
   g.kto = P.kta[q];
   g.o_h = P.Gh[q]; g.o_l = P.Gl[q]; g.o_d = plain ? nullptr : P.dG[q]; g.o_r = plain ? nullptr : P.Gref[q];     // (Gref: null for q = 1)
   g.maskbits = P.maskbits[q];
-  g.dbpart = P.dbpart; g.ddbpart = P.ddbpart; g.nband = 2 * P.RT;
+  g.dbpart = P.dbpart[q & 1]; g.ddbpart = P.ddbpart[q & 1]; g.nband = 2 * P.RT;
 }
 
 int mlp_gradients(Ctx *c, const int32_t *idx) {
@@ -1976,6 +2024,8 @@ int mlp_gradients(Ctx *c, const int32_t *idx) {
   if (const int rc = mlp_forward(c, P, s, idx)) return rc;
 
   // ---- backward
+  Mm5Args second;          // the second layer's weight gradient, where it waits for the first layer's
+  bool waits = false;
   for (int l = L; l >= 1; --l) {
     const int din = P.d[l - 1], dout = P.d[l];
     {   // weight gradient and its innovation: contraction over the worker's rows, both operands (row, unit) tensors
@@ -2009,9 +2059,16 @@ int mlp_gradients(Ctx *c, const int32_t *idx) {
           signals_below(g, P, l - 1, plain);
         }
       } else if (bias_inside(M, din, dout)) {       // and the other layers' from the sums of the launch that formed their signals
-        g.dbpart = P.dbpart; g.ddbpart = P.ddbpart; g.nband = 2 * P.RT; g.bias_here = 1; g.offb = P.offb[l - 1]; g.lhs_slot_b = P.lhs_b_slot[l - 1];
+        g.dbpart = P.dbpart[l & 1]; g.ddbpart = P.ddbpart[l & 1]; g.nband = 2 * P.RT; g.bias_here = 1; g.offb = P.offb[l - 1]; g.lhs_slot_b = P.lhs_b_slot[l - 1];
       }
-      if (const int rc = launch_mm5<EPI_DW>(c, g, M)) return rc;
+      if (l == 2 && l < L && dout > 32 && din > 32) {
+        g.workers = M;
+        Mm5Args g1 = g;      // (of the first layer, as far as the choice of its kernel goes)
+        g1.M = P.d[0]; g1.N = din;
+        waits = !(plain && (dw_past_caches(g) || dw_past_caches(g1)));
+      }
+      if (l == 2 && waits) second = g;
+      else if (const int rc = launch_mm5<EPI_DW>(c, g, M, l == 1 && waits ? &second : nullptr)) return rc;
     }
     if (l >= 2 && l < L) {   // gradient w.r.t. the activations of layer l-1, masks, bias partials
       Mm5Args g = blank(s, P);
@@ -2032,7 +2089,7 @@ int mlp_gradients(Ctx *c, const int32_t *idx) {
       if (const int rc = launch_mm5<EPI_DA>(c, g, M)) return rc;
     }
     if (l >= 2 && !bias_inside(M, P.d[l - 2], din))
-      hipLaunchKernelGGL(k_bias_finish, dim3((din + kWave - 1) / kWave, M), dim3(kWave), 0, st, s, P.dbpart, plain ? nullptr : P.ddbpart, 2 * P.RT, (B + 63) / 64, din,
+      hipLaunchKernelGGL(k_bias_finish, dim3((din + kWave - 1) / kWave, M), dim3(kWave), 0, st, s, P.dbpart[(l - 1) & 1], plain ? nullptr : P.ddbpart[(l - 1) & 1], 2 * P.RT, (B + 63) / 64, din,
                          P.offb[l - 2], P.lhs_b_slot[l - 2]);
   }
   prof_mark(c);
