@@ -14,7 +14,7 @@
 // all workers (up to kRuleWorkers), and, where the state is small, the server update.  The partial sums, gradients and left-hand sides that are passed on
 // inside the launch are written and read at device scope (past the XCD's cache).
 //
-// Wider rows, up to 20480 columns: k_rows_wide and k_rows_sum below, two launches, the rule's for more than a few workers, and the server's.
+// Wider rows, up to 20480 columns: k_rows_wide and k_rows_sum below, two launches, and the server's with the rule in it (more than 256 workers: a launch of its own).
 //
 // Why: the path replaces four to five dependent launches (two passes over the rows, [left-hand side of the LAG rule],
 // rule, server), each about 5 us of fetching arguments, code and first operands for well under 1 us of work.
@@ -34,16 +34,15 @@ enum { kTailNone = 0, kTailRule = 1, kTailServer = 2 };      // what the workgro
 constexpr int kServerColumns = 2 * R_NT, kServerState = 16384, kServerWorkers = 32;      // p, M p and M up to here
 // The rule in the last workgroup saves a launch as well; the workgroups count themselves in one after the other for it.  Measured, us with
 // and without it: B = 65, p = 22: M = 100: 17.2, 19.9; 256: 23.3, 24.1; 400: 28.6, 30.0; 512: 32.3, 32.4; 1024: 54.9, 53.8; p = 8191, M = 512: 215, 219;
-// 1024: 414, 416.  k_rows_sum, whose blocks are many: p = 8193, M = 16, B = 8: 23.0, 23.9; 64: 32.5, 30.7; 256: 62.8, 47.5; 1024: 207, 134; p = 20480,
-// M = 16, B = 64: 49.6, 50.1; M = 64: 94.0, 91.7.
-constexpr int kRuleWorkers = 512, kWideRuleWorkers = 32;
+// 1024: 414, 416. 
+constexpr int kRuleWorkers = 512;
 
 struct RowsArgs {
   DevState s;
   const int32_t *idx;        // [M][B]
   const uint8_t *replay;     // [M] or nullptr
   float *part;               // sums of the shares: k_rows [M][shares][2][p rounded up to 4] (shares > 1), k_rows_wide [wide_slots][2][the same]
-  uint32_t *count;           // [1 + M], kCountWords apart: workers done; shares (k_rows_sum: blocks) done of each worker (zero between launches)
+  uint32_t *count;           // [1 + M], kCountWords apart: workers done; shares done of each worker (zero between launches)
   int shares;                // k_rows: workgroups per worker
   int rows;                  // rows per share (at most)
   int tail;                  // kTail*
@@ -591,15 +590,15 @@ __global__ __launch_bounds__(R_NT) void k_rows_wide(const RowsArgs a) {
 }
 
 // Adds up the shares of every worker in their order, adds the regulariser's terms, stores the fresh gradient (CADA1: and the fresh
-// innovation) and the left-hand side's partial sums; the block that finishes last runs the rule.  grid (ceil(p / 1024), M): four
-// columns per thread.  (The last quad may reach past p: it reads up to three floats of what follows in the workspace and drops them.)
+// innovation) and the left-hand side's partial sums; one block more takes the rule's inputs down.  grid (ceil(p / 1024), M + 1): four
+// columns per thread.  (The rule in the block that finishes last, up to 32 workers, cost two trips to counters, the stores' drain and the rule's own reads; in the server's launch it costs less.
+// us per step so / now: p = 8193, M = 16, B = 8: 20.2 / 17.8; p = 20480, M = 4, B = 64: 29.1 / 26.7; p = 20001, M = 32: 54.7 / 50.8; p = 14000, LAG, M = 24: 36.8 / 34.0.)  (The last quad may reach past p: it reads up to three floats of what follows in the workspace and drops them.)
 __global__ __launch_bounds__(kBlock) void k_rows_sum(const RowsArgs a, const RuleInputs ri) {
   __shared__ float red[4];
-  __shared__ double rule_s[rule_lds(kBlock) / sizeof(double)];
-  __shared__ uint32_t flag;
+  __shared__ double rule_s[kBlock];
   const DevState &s = a.s;
   const int p = (int)s.p, ps = (p + 3) & ~3, m = blockIdx.y, rule = s.rule;
-  if (m == s.M) {                                    // (kTailNone: one more row of blocks)
+  if (m == s.M) {                                    // (one more row of blocks)
     if (blockIdx.x == 0) rule_inputs(s, ri, rule_s);
     return;
   }
@@ -648,10 +647,7 @@ __global__ __launch_bounds__(kBlock) void k_rows_sum(const RowsArgs a, const Rul
     }
   }
   sq = block_sum_lds(sq, red);
-  if (threadIdx.x == 0) put_far(s.lhs_part + (int64_t)m * s.n_lhs_part + blockIdx.x, sq);
-  // (counted per worker first: a counter takes one arrival at a time)
-  if (a.tail == kTailNone) return;
-  if (last_of(a.count + kCountWords * (1 + m), gridDim.x, &flag) && last_of(a.count, gridDim.y, &flag)) rule_all<kBlock>(s, a.replay, rule_s);
+  if (threadIdx.x == 0) s.lhs_part[(int64_t)m * s.n_lhs_part + blockIdx.x] = sq;
 }
 
 namespace {
@@ -695,7 +691,7 @@ bool rows_plan(Ctx *c, const cada_config *cfg) {
   const bool wide = cfg->p > 8192;
   const size_t ps = (size_t)((cfg->p + 3) / 4 * 4);
   int wc;
-  c->rows_tail = cfg->M <= (wide ? kWideRuleWorkers : kRuleWorkers) ? kTailRule : kTailNone;
+  c->rows_tail = !wide && cfg->M <= kRuleWorkers ? kTailRule : kTailNone;
   RowsKernel fn;
   if (wide) {
     const WideSplit w = wide_split(cfg->M, cfg->B, cfg->p);
@@ -719,7 +715,7 @@ bool rows_plan(Ctx *c, const cada_config *cfg) {
   c->s.n_lhs_part = wide ? (int)((cfg->p + 1023) / 1024) : 2;
   c->n_phases = 0;
   c->phase_names[c->n_phases++] = "logreg_rows";
-  if (wide && c->rows_tail == kTailNone) decide_plan(c, c->rule_room);
+  if (wide) decide_plan(c, c->rule_room);
   if (c->rows_tail == kTailNone && !c->decide) c->phase_names[c->n_phases++] = "rule";
   if (c->rows_tail != kTailServer) c->phase_names[c->n_phases++] = c->decide ? "rule_and_server_update" : "server_update";
   return true;

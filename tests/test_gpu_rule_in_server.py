@@ -46,15 +46,15 @@ def test_networks(dims, M, phase, rule):
     _check(configs.CFG5.scaled(name="rule", layer_dims=dims, M=M, N_m=30, B=6, K=6, D=3, c=20.0, rule=rule), phase, 2e-2, None)
 
 
-# rows of more than 8192 columns and more than 32 workers: 9 and 10 parts; a width that is no multiple of four
-@pytest.mark.parametrize("p,M,phase", [(8193, 33, TOGETHER), (9300, 256, TOGETHER), (8196, 257, APART)])
+# rows of more than 8192 columns: 9, 10 and 20 parts; widths that are no multiple of four
+@pytest.mark.parametrize("p,M,phase", [(8193, 1, TOGETHER), (20479, 5, TOGETHER), (8193, 33, TOGETHER), (9300, 256, TOGETHER), (8196, 257, APART)])
 def test_wide_rows(p, M, phase):
     _check(configs.CFG1.scaled(name="rule", layer_dims=(p,), M=M, N_m=12, B=4, K=6, D=4, rule=configs.RULE_CADA2, c=2e-3), phase, 1e-4, 1e-4)
 
 
 def test_phase_names():
     """Whole steps and the paths whose gradient launches run the rule keep the phases that they had."""
-    cfg = configs.CFG1.scaled(name="rule", layer_dims=(8193,), M=3, N_m=12, B=4, K=1)
+    cfg = configs.CFG1.scaled(name="rule", layer_dims=(8192,), M=3, N_m=12, B=4, K=1)
     eng = binding.Cada.from_config(cfg, *upload(generators.make_problem(cfg)))
     assert binding.cada_profile_phase_names(eng.ctx) == ["logreg_rows", "server_update"]
     eng.close()
