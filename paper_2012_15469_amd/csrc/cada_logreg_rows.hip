@@ -21,6 +21,8 @@
 // Measured per step, against those launches: M = 10, p = 784, B = 60: 23.8 -> 16.2 us (15.5 in the kernel: operands and indices 3.3,
 // rows 2.9, share's sums 2.6, gradient 1.5, count 0.7, rule 1.0, aggregate 2.1, update 1.3); M = 10, p = 22, B = 92, LAG:
 // 23.8 -> 13.2 us; M = 100, B = 256, p = 4000 (410 MB of rows): 147 -> 87 us; p = 8192: 308 -> 164 us (5.1 TB/s).
+#include <type_traits>
+
 #include "cada_rows_split.h"
 #include "cada_rule.h"
 
@@ -35,7 +37,10 @@ constexpr int kServerColumns = 2 * R_NT, kServerState = 16384, kServerWorkers = 
 // The rule in the last workgroup saves a launch as well; the workgroups count themselves in one after the other for it.  Measured, us with
 // and without it: B = 65, p = 22: M = 100: 17.2, 19.9; 256: 23.3, 24.1; 400: 28.6, 30.0; 512: 32.3, 32.4; 1024: 54.9, 53.8; p = 8191, M = 512: 215, 219;
 // 1024: 414, 416. 
-constexpr int kRuleWorkers = 512;
+// In the server's launch (cada_server.hip) it needs neither: up to 256 workers.  us per step there / in the last workgroup: p = 54, M = 200, B = 100: 21.6 / 33.7; p = 300,
+// M = 100, B = 80: 20.8 / 24.4; p = 784, M = 256, B = 40: 31.8 / 41.9; M = 64, B = 60: 20.7 / 23.7; p = 1500, M = 10, B = 64: 16.6 / 17.7; p = 8192, LAG, M = 16: 34.6 / 36.4;
+// p = 4000, M = 100, B = 256: 93.8 / 96.4.  (The server update in the last workgroup stays where it is: p = 784, M = 16, B = 100: 17.0 for 18.0, p = 100, M = 10: 12.1 for 13.8.)
+constexpr int kRuleWorkers = 512, kRuleInServer = 256;
 
 struct RowsArgs {
   DevState s;
@@ -49,12 +54,16 @@ struct RowsArgs {
   WideSplit wide;            // k_rows_wide, k_rows_sum
 };
 
+struct RowsInArgs : RowsArgs { RuleInputs ri; };
+
 __device__ __forceinline__ float sigmoid_r(float a) { return 1.0f / (1.0f + expf(-a)); }
 
 // CW: 16-byte pieces of a row per lane; WC: wavefronts a row lies across; RB: rows per batch.
 // dynamic LDS: row offsets int64 [rows], labels [rows] (rounded up to four rows), sums [R_NW / WC][2][p]
-template <int CW, int WC, int RB>
-__global__ __launch_bounds__(R_NT) void k_rows(const RowsArgs a) {
+// Args RowsInArgs: the launch ends with the left-hand sides and takes the rule's inputs down for the server's launch (a kernel of its own: the code at the end of the
+// other one costs that 1 to 3 % of a step of few workers).
+template <int CW, int WC, int RB, class Args>
+__global__ __launch_bounds__(R_NT) void k_rows(const Args a) {
   extern __shared__ __align__(16) unsigned char rows_smem[];
   const DevState &s = a.s;
   const int p = (int)s.p, ps = (p + 3) & ~3, M = s.M, m = blockIdx.y, share = blockIdx.x, rule = s.rule;
@@ -300,6 +309,17 @@ __global__ __launch_bounds__(R_NT) void k_rows(const RowsArgs a) {
     const float hi = (float)l, lo = (float)(l - (double)hi);
     put_far(lhs_far + m, ((uint64_t)__float_as_uint(lo) << 32) | __float_as_uint(hi));
     up_s = 0u;
+  }
+  if constexpr (std::is_same_v<Args, RowsInArgs>) {
+    const RuleInputs ri = a.ri;
+    if (m == 0) {                                      // (one workgroup comes here for each worker; M <= R_NT) the rule's inputs for the server's launch
+      if (tid < M) { ri.in[tid] = tau0; ri.in[M + tid] = sel0; }
+      if (tid == 0) {
+        *ri.rhs = rhs;
+        if (last >= 0) s.ring[last] = newest;          // (others read this slot too, and put their own sum in its place)
+      }
+    }
+    return;
   }
   if (a.tail == kTailNone) return;
   if (!last_of(a.count, (uint32_t)M, &flag_s)) return;
@@ -652,15 +672,23 @@ __global__ __launch_bounds__(kBlock) void k_rows_sum(const RowsArgs a, const Rul
 
 namespace {
 using RowsKernel = void (*)(const RowsArgs);
+using RowsInKernel = void (*)(const RowsInArgs);
 // the variant for rows of p columns: pieces per lane, wavefronts per row, rows per batch
-RowsKernel rows_kernel(int64_t p, int *wc) {
-  *wc = p <= 1024 ? 1 : 8;
-  if (p <= 256) return k_rows<1, 1, 8>;
-  if (p <= 512) return k_rows<2, 1, 4>;
-  if (p <= 1024) return k_rows<4, 1, 4>;
-  if (p <= 2048) return k_rows<1, 8, 8>;
-  if (p <= 4096) return k_rows<2, 8, 4>;
-  return k_rows<4, 8, 2>;
+RowsKernel rows_kernel(int64_t p) {
+  if (p <= 256) return k_rows<1, 1, 8, RowsArgs>;
+  if (p <= 512) return k_rows<2, 1, 4, RowsArgs>;
+  if (p <= 1024) return k_rows<4, 1, 4, RowsArgs>;
+  if (p <= 2048) return k_rows<1, 8, 8, RowsArgs>;
+  if (p <= 4096) return k_rows<2, 8, 4, RowsArgs>;
+  return k_rows<4, 8, 2, RowsArgs>;
+}
+RowsInKernel rows_in_kernel(int64_t p) {
+  if (p <= 256) return k_rows<1, 1, 8, RowsInArgs>;
+  if (p <= 512) return k_rows<2, 1, 4, RowsInArgs>;
+  if (p <= 1024) return k_rows<4, 1, 4, RowsInArgs>;
+  if (p <= 2048) return k_rows<1, 8, 8, RowsInArgs>;
+  if (p <= 4096) return k_rows<2, 8, 4, RowsInArgs>;
+  return k_rows<4, 8, 2, RowsInArgs>;
 }
 RowsKernel wide_kernel(int64_t p) {
   if (p <= 5 * 2048) return k_rows_wide<5, 2, false, true>;
@@ -702,20 +730,23 @@ bool rows_plan(Ctx *c, const cada_config *cfg) {
     const RowsSplit r = rows_split(cfg->M, cfg->B, cfg->p);
     c->rows_shares = r.shares; c->rows_per_share = r.rows;
     if (cfg->p <= kServerColumns && cfg->M <= kServerWorkers && (int64_t)cfg->M * cfg->p <= kServerState) c->rows_tail = kTailServer;
-    fn = rows_kernel(cfg->p, &wc);
+    fn = rows_kernel(cfg->p);
+    wc = cfg->p <= 1024 ? 1 : 8;
     const size_t server = (size_t)((cfg->M + 15) & ~15) + ps * sizeof(float);
     c->rows_lds = (size_t)((c->rows_per_share + 3) & ~3) * 12 + (size_t)(R_NW / wc) * 2 * ps * sizeof(float);
     if (c->rows_tail == kTailServer && c->rows_lds < server) c->rows_lds = server;
   }
-  if (hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024) != hipSuccess) {
-    (void)hipGetLastError();
-    return false;
-  }
+  for (const void *k : {reinterpret_cast<const void *>(fn), reinterpret_cast<const void *>(rows_in_kernel(cfg->p))})
+    if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024) != hipSuccess) {
+      (void)hipGetLastError();
+      return false;
+    }
   c->rows = wide ? 2 : 1;
   c->s.n_lhs_part = wide ? (int)((cfg->p + 1023) / 1024) : 2;
   c->n_phases = 0;
   c->phase_names[c->n_phases++] = "logreg_rows";
-  if (wide) decide_plan(c, c->rule_room);
+  if (wide || (c->rows_tail == kTailRule && cfg->M <= kRuleInServer)) decide_plan(c, c->rule_room);
+  if (c->decide) c->rows_tail = kTailNone;
   if (c->rows_tail == kTailNone && !c->decide) c->phase_names[c->n_phases++] = "rule";
   if (c->rows_tail != kTailServer) c->phase_names[c->n_phases++] = c->decide ? "rule_and_server_update" : "server_update";
   return true;
@@ -734,9 +765,10 @@ int logreg_step_rows(Ctx *c, const int32_t *idx, const uint8_t *replay) {
   a.rows = c->rows_per_share;
   a.wide = WideSplit{c->s.M, c->s.B, c->rows_shares, c->rows_per_share, c->rows_per_worker};
   a.tail = c->rows_tail;
-  int wc;
   prof_mark(c);
-  hipLaunchKernelGGL(c->rows == 2 ? wide_kernel(c->s.p) : rows_kernel(c->s.p, &wc), dim3((unsigned)a.shares, c->rows == 2 ? 1u : (unsigned)c->s.M), dim3(R_NT), c->rows_lds, c->stream, a);
+  const dim3 grid((unsigned)a.shares, c->rows == 2 ? 1u : (unsigned)c->s.M);
+  if (c->rows == 1 && c->decide) hipLaunchKernelGGL(rows_in_kernel(c->s.p), grid, dim3(R_NT), c->rows_lds, c->stream, RowsInArgs{a, c->rule_in});
+  else hipLaunchKernelGGL(c->rows == 2 ? wide_kernel(c->s.p) : rows_kernel(c->s.p), grid, dim3(R_NT), c->rows_lds, c->stream, a);
   if (c->rows == 2)
     hipLaunchKernelGGL(k_rows_sum, dim3((unsigned)((c->s.p + 1023) / 1024), (unsigned)c->s.M + (c->rule_in.rhs ? 1u : 0u)), dim3(kBlock), 0, c->stream, a, c->rule_in);
   prof_mark(c);

@@ -54,7 +54,7 @@ def test_wide_rows(p, M, phase):
 
 def test_phase_names():
     """Whole steps and the paths whose gradient launches run the rule keep the phases that they had."""
-    cfg = configs.CFG1.scaled(name="rule", layer_dims=(8192,), M=3, N_m=12, B=4, K=1)
+    cfg = configs.CFG1.scaled(name="rule", layer_dims=(8192,), M=257, N_m=4, B=4, K=1)
     eng = binding.Cada.from_config(cfg, *upload(generators.make_problem(cfg)))
     assert binding.cada_profile_phase_names(eng.ctx) == ["logreg_rows", "server_update"]
     eng.close()
