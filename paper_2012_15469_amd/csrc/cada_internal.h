@@ -355,7 +355,7 @@ constexpr size_t kFusedTailFloatsPerP = 2 * 32;     // room for the parts of 32 
 constexpr size_t kFusedPostWords = 1024 * 4 * 16;   // upper bound: 1024 workgroups x 4 buffers x 16 values
 // S1+S2 for the MLP.
 int mlp_gradients(Ctx *c, const int32_t *idx);
-// Partial sums of the left-hand side, with one per so many columns of a bias innovation (the plain rules have none: k_lag_lhs uses the slots).
+// Partial sums of the left-hand side, with one per so many columns of a bias innovation (the rules without a second gradient have none of these: k_lag_lhs leaves theirs).
 constexpr int kBiasColsState = 256;
 inline int mlp_bias_cols(int rule) { return rule == CADA_RULE_CADA1 || rule == CADA_RULE_CADA2 ? 64 : kBiasColsState; }
 int mlp_lhs_slots(const cada_config *cfg, int bias_cols);
@@ -370,8 +370,8 @@ size_t mlp_scratch_bytes(const cada_config *cfg, const int64_t total_rows);     
 int mlp_plan(Ctx *c, const cada_config *cfg, char *base, size_t offset, size_t scratch, int64_t total_rows);
 int mlp_init_state(Ctx *c, const float *theta0);
 void mlp_free(Ctx *c);
-constexpr int kLagSpan = 4096;              // coordinates of a worker that a block of k_lag_lhs takes at a time
-inline int lag_parts(int64_t p) { return (int)((p + kLagSpan - 1) / kLagSpan); }
+constexpr int kLagSpan = 4096;              // coordinates of a worker that a block of k_lag_lhs takes at a time; it leaves two parts
+inline int lag_blocks(int64_t p) { return (int)((p + kLagSpan - 1) / kLagSpan); }
 // Room for the rule's inputs, and whether the server's workgroups run the rule (cada_server.hip).
 constexpr size_t rule_in_bytes(int M) { return 256 + (size_t)M * 2 * sizeof(int32_t); }
 void decide_plan(Ctx *c, char *room);

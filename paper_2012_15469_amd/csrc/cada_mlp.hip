@@ -1431,10 +1431,13 @@ size_t mlp_workspace_bytes(const cada_config *cfg, const int64_t total_rows) {
   return w.off + kAlignB;
 }
 
-// The partial sums of the left-hand side and the rule's inputs, in front of the evaluation's scratch.
+// The partial sums of the left-hand side (the rules without a second gradient: two per block of k_lag_lhs) and the rule's inputs, in front of the evaluation's scratch.
+static int lhs_parts(const cada_config *cfg) {
+  return cfg->rule == CADA_RULE_LAG || cfg->rule == CADA_RULE_ALWAYS ? 2 * lag_blocks(cfg->p) : mlp_lhs_slots(cfg, mlp_bias_cols(cfg->rule));
+}
 static size_t rule_room(const cada_config *cfg) { return (rule_in_bytes(cfg->M) + kAlignB - 1) / kAlignB * kAlignB; }
 static size_t lhs_bytes(const cada_config *cfg) {
-  return ((size_t)cfg->M * mlp_lhs_slots(cfg, mlp_bias_cols(cfg->rule)) * sizeof(float) + kAlignB - 1) / kAlignB * kAlignB + rule_room(cfg);
+  return ((size_t)cfg->M * lhs_parts(cfg) * sizeof(float) + kAlignB - 1) / kAlignB * kAlignB + rule_room(cfg);
 }
 
 // The sums per band of the odd layers' signals (two arrays), behind them.
@@ -1455,8 +1458,7 @@ int mlp_plan(Ctx *c, const cada_config *cfg, char *base, size_t offset, size_t s
   layout(*P, cfg, total_rows, w);
   scratch = (scratch + kAlignB - 1) / kAlignB * kAlignB;
   c->s.lhs_part = reinterpret_cast<float *>(base + scratch);
-  // (the rules without a second gradient: a part per block of k_lag_lhs)
-  if (cfg->rule == CADA_RULE_LAG || cfg->rule == CADA_RULE_ALWAYS) c->s.n_lhs_part = std::min(c->s.n_lhs_part, lag_parts(cfg->p));
+  c->s.n_lhs_part = lhs_parts(cfg);
   decide_plan(c, base + scratch + lhs_bytes(cfg) - rule_room(cfg));
   P->dbpart[1] = reinterpret_cast<float *>(base + scratch + lhs_bytes(cfg));
   P->ddbpart[1] = reinterpret_cast<float *>(base + scratch + lhs_bytes(cfg) + bands_bytes(*P) / 2);

@@ -10,18 +10,19 @@ namespace cada {
 
 // Left-hand side of condition (LAGrule), Section 2.1: |fresh gradient - stored gradient|^2 per
 // worker (the stored one was taken at another iterate on other samples).  grid (blocks, M);
-// block b of worker m writes lhs_part[m][b]; the remaining slots are cleared.
+// block b of worker m leaves its sum in lhs_part[m][2 b] and [2 b + 1], the second what the first is rounded by (one part in all: rounded); the
+// remaining parts are cleared.  Squares and sums are in double, as the rule compares in double: in float32 over a block a square of 1 swallows all of 2^-25.
 // What bounds it: reading, and one round trip: a block takes kLagSpan coordinates at a time, 16 bytes per access, all of them asked for before the first is used (with 2 or 4 bytes per
 // access and a block for every 1024 coordinates, 617-301-150-26 with 24 workers and bf16 gradients: 9.7 us in the kernel and 96.0 per step, now 6.3 and 92.5; float32, 300-200-10 with 30 workers: 50.0 us
 // per step, now 46.8; 3072-1024-10, always, 36 workers of 128 rows: 572, now 555).
 template <bool BF16>
-__device__ __forceinline__ float lag_part(const DevState &s, int m) {
+__device__ __forceinline__ double lag_part(const DevState &s, int m) {
   constexpr int E = BF16 ? 8 : 4, ROUNDS = kLagSpan / (E * kBlock);
   typedef uint32_t u4 __attribute__((ext_vector_type(4), aligned(4)));
   const int cur = s.sel[m];
   const char *gs = BF16 ? reinterpret_cast<const char *>(s.gbuf16 + ((int64_t)cur * s.M + m) * s.ps16) : reinterpret_cast<const char *>(s.gbuf + ((int64_t)cur * s.M + m) * s.ps);
   const char *gf = BF16 ? reinterpret_cast<const char *>(s.gbuf16 + ((int64_t)(1 - cur) * s.M + m) * s.ps16) : reinterpret_cast<const char *>(s.gbuf + ((int64_t)(1 - cur) * s.M + m) * s.ps);
-  float sq[4] = {0.f, 0.f, 0.f, 0.f};
+  double sq[4] = {0.0, 0.0, 0.0, 0.0};
   auto value = [](const u4 &x, int e) __attribute__((always_inline)) { return __uint_as_float(!BF16 ? x[e] : (e & 1) ? x[e >> 1] & 0xffff0000u : x[e >> 1] << 16); };
   for (int64_t i0 = (int64_t)blockIdx.x * kLagSpan + threadIdx.x * E; i0 < s.p; i0 += (int64_t)gridDim.x * kLagSpan) {
     u4 x[ROUNDS], y[ROUNDS];
@@ -37,22 +38,33 @@ __device__ __forceinline__ float lag_part(const DevState &s, int m) {
       const int64_t want = i0 + r * E * kBlock, i = BF16 ? min(want, s.ps16 - E) : max(min(want, s.p - E), (int64_t)0);
 #pragma unroll
       for (int e = 0; e < E; ++e) {
-        const float d = i + e >= want && i + e < s.p ? value(x[r], e) - value(y[r], e) : 0.f;
-        sq[e & 3] = fmaf(d, d, sq[e & 3]);
+        const double d = i + e >= want && i + e < s.p ? value(x[r], e) - value(y[r], e) : 0.f;
+        sq[e & 3] = fma(d, d, sq[e & 3]);
       }
     }
   }
   return (sq[0] + sq[1]) + (sq[2] + sq[3]);
 }
 __global__ __launch_bounds__(kBlock) void k_lag_lhs(const DevState s) {
-  __shared__ float red[4];
+  __shared__ double red[kBlock / kWave];
   const int m = blockIdx.y;
-  const float sq = s.gbuf16 ? lag_part<true>(s, m) : lag_part<false>(s, m);      // (bf16 store, always-upload rule, which only records this value: the rows as they are kept)
-  const float tot = block_sum_lds(sq, red);
+  const double sq = wave_sum_f64(s.gbuf16 ? lag_part<true>(s, m) : lag_part<false>(s, m));      // (bf16 store, always-upload rule, which only records this value: the rows as they are kept)
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = sq;
+  lds_sync();
+  const bool two = 2 * (int)gridDim.x <= s.n_lhs_part;
   float *lp = s.lhs_part + (int64_t)m * s.n_lhs_part;
-  if (threadIdx.x == 0) lp[blockIdx.x] = tot;
+  if (threadIdx.x == 0) {
+    const double tot = (red[0] + red[1]) + (red[2] + red[3]);
+    const float hi = (float)tot;
+    if (two) {
+      lp[2 * blockIdx.x] = hi;
+      lp[2 * blockIdx.x + 1] = isinf(hi) ? 0.f : (float)(tot - (double)hi);
+    } else {
+      lp[blockIdx.x] = hi;
+    }
+  }
   if (blockIdx.x == 0)
-    for (int t = gridDim.x + threadIdx.x; t < s.n_lhs_part; t += kBlock) lp[t] = 0.f;
+    for (int t = (two ? 2 : 1) * gridDim.x + threadIdx.x; t < s.n_lhs_part; t += kBlock) lp[t] = 0.f;
 }
 
 // S3 of the step: RHS, per-worker decision, tau, pointer swap, trace.  One wavefront per
@@ -398,8 +410,8 @@ int rule_and_server(Ctx *c, const uint8_t *replay) {
   DevState s = c->s;
   s.k = c->k;
   if (s.rule == CADA_RULE_LAG || s.rule == CADA_RULE_ALWAYS) {   // (the always-upload rule only records it)
-    const int nb = min(s.n_lhs_part, lag_parts(s.p));
-    hipLaunchKernelGGL(k_lag_lhs, dim3((unsigned)max(nb, 1), (unsigned)s.M), dim3(kBlock), 0, c->stream, s);
+    const int nb = min(max(s.n_lhs_part / 2, 1), lag_blocks(s.p));      // (two parts each; the logistic model: one, of at most 1024 coordinates, or room for two for every 4096)
+    hipLaunchKernelGGL(k_lag_lhs, dim3((unsigned)nb, (unsigned)s.M), dim3(kBlock), 0, c->stream, s);
   }
   return rule_then_server(c, replay);
 }

@@ -2,11 +2,12 @@
 their groups of workers, the decisions and the books, and more coordinates than its workgroups take in one turn; against the oracle."""
 import numpy as np
 import pytest
+import torch
 
 from cada_synth import configs, generators
 from paper_2012_15469_amd import binding
 
-from common import check_protocol, upload
+from common import check_protocol, to_dev, upload
 
 pytestmark = pytest.mark.gpu
 TOGETHER, APART = "rule_and_server_update", "server_update"
@@ -68,3 +69,38 @@ def test_lag_left_hand_sides(p, M, rule):
     prob.X *= np.float32(1.0 / np.sqrt(p))
     dev, sched = upload(prob), generators.make_schedule(cfg)
     check_protocol(cfg, prob, dev, sched, 1e-4, lhs_rtol=1e-4, path=binding.PATH_TWO_PASS, expect_phase="logreg_two_pass")
+
+
+def test_lag_sums_keep_small_terms():
+    """The rule compares sums of squares in double, and so are they added up inside a block of 4096 coordinates and handed on: two blocks of 1024 + 2^-14 (a float32 sum
+    loses what it adds to a square of 1, and a float32 part half a unit in its last place) and one of 2^-14.  All values are powers of two, every gradient is exact."""
+    p, M, B = 12288, 3, 128
+    x = torch.zeros(p, device="cuda")
+    x[:1024] = x[4096:5120] = 2.0
+    x[1024:2048] = x[5120:6144] = x[8192:9216] = 2.0 ** -11
+    eng = binding.Cada(model="logreg", layer_dims=[p], M=M, B=B, n_samples=[B] * M, X=x.repeat(M * B, 1).contiguous(), y=torch.ones(M * B, device="cuda"),
+                       theta0=torch.zeros(p, device="cuda"), rule=configs.RULE_LAG, D=50, d_max=10, c=0.5, alpha=1.0, beta1=0.9, beta2=0.999, eps=1e-8, server=1,
+                       trace_steps=1, path=binding.PATH_TWO_PASS)
+    assert "logreg_two_pass" in binding.cada_profile_phase_names(eng.ctx)
+    eng.step(torch.arange(B, dtype=torch.int32, device="cuda").repeat(M, 1).contiguous())
+    lhs = eng.state()["trace_lhs"].cpu().numpy().ravel()
+    eng.close()
+    assert (lhs == np.float32(2048 + 3 * 2.0 ** -14)).all()
+
+
+@pytest.mark.parametrize("dims,rule,store", [((617, 301, 150, 26), configs.RULE_LAG, 0), ((617, 301, 150, 26), configs.RULE_ALWAYS, 1), ((20, 33, 3), configs.RULE_LAG, 0),
+                                             ((5, 3, 2), configs.RULE_ALWAYS, 1), ((200, 181, 7), configs.RULE_LAG, 0)])
+def test_lag_left_hand_sides_of_networks(dims, rule, store):
+    """Everybody uploads at every step: a left-hand side is then |gradient now - gradient of the step before|^2 of the stored rows, and float32 of a sum in double."""
+    cfg = configs.CFG5.scaled(name="lag", layer_dims=dims, M=24, N_m=60, B=10, K=8, D=50, rule=rule, server=1 if rule == configs.RULE_LAG else 0)
+    eng = binding.Cada.from_config(cfg, *upload(generators.make_problem(cfg)), trace_steps=cfg.K, gradient_store=store)
+    everybody, before = torch.ones(cfg.M, dtype=torch.uint8, device="cuda"), np.zeros((cfg.M, cfg.p), np.float32)
+    for k, idx in enumerate(generators.make_schedule(cfg)):
+        eng.step(to_dev(idx.astype(np.int32)), everybody)
+        now = eng.stored_gradients().cpu().numpy()
+        got = eng.state()["trace_lhs"][k].cpu().numpy()
+        want = ((now - before).astype(np.float64) ** 2).sum(axis=1)      # (the differences are float32, as in the kernel)
+        # two sums in double of up to 240 thousand terms, and a pair of float32 per block: 2^-40 covers them
+        assert ((got == np.float32(want * (1 - 2.0 ** -40))) | (got == np.float32(want * (1 + 2.0 ** -40)))).all(), (k, got, want)
+        before = now
+    eng.close()
