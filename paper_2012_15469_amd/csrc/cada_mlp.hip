@@ -1520,7 +1520,8 @@ struct StageArgs {
   // reference point theta^{k - tau}, hence the difference theta - theta_ref and its bf16 copies;
   // out: rep[m] = the first worker with worker m's (clamped) tau.  Only that worker's difference is computed.
   int32_t *rep;
-  int z_groups;          // the groups that share these workers out (M > kBlock: a group for every worker, which finds out for itself whether it is a first one)
+  int z_groups;          // groups of blocks that share these workers out
+  int z_listed;          // 1: every block makes the list of them; else a group for every worker, which finds out for itself whether it is a first one
   uint32_t first[CADA_MAX_LAYERS + 2];   // first block of the minibatch part (0), of each layer, and the total
   int rule_block;        // 1: one more block, in front of them, takes the rule's inputs down
   RuleInputs rule_in;
@@ -1554,19 +1555,21 @@ __device__ __forceinline__ void stage_minibatch(const StageArgs &a, int bx, int 
   }
 }
 
-// A 64 x 64 tile of one layer's weights (z = 0: hi and lo parts of W) or of their difference to
-// worker z - 1's reference point, 8 values per lane: rows of W are read (4-byte aligned 16-byte
-// loads) and written as they are, and turned through LDS for the other orientation.
+constexpr int kStageDelays = 64 * 65;            // delays that the list's table has room for (it lies where a tile does later)
+// A 64 x 64 tile of one layer's weights (z = 0: hi and lo parts of W) or of their differences to the
+// reference points of group z (worker z - 1's where there is no list), 8 values per lane: rows of W are read (4-byte aligned
+// 16-byte loads) and written as they are, and turned through LDS for the other orientation.
 __device__ __forceinline__ void stage_weights(const StageArgs &a, const PrepLayer &p, unsigned char *sm, int bx, int by, int z, bool first_tile) {
   const DevState &s = a.s;
   typedef float tile_t[64][65];
+  static_assert(sizeof(tile_t) >= kStageDelays * sizeof(int32_t), "");
   tile_t &tile = *reinterpret_cast<tile_t *>(sm);
   const int o0 = bx * 64, i0 = by * 64;
   const int t = threadIdx.x;
   const bool is_w = z == 0;
   const int og = (t & 7) * 8;
-  auto one = [&](const int m) __attribute__((always_inline)) {
-    const RefPtr ref = theta_ref(s, m, s.k);
+  auto one = [&](const int m, const int32_t tau) __attribute__((always_inline)) {
+    const RefPtr ref = theta_ref_at(s, tau, s.k);
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
       const int r = (t >> 3) + 32 * pass, i = i0 + r, o = o0 + og;
@@ -1617,52 +1620,50 @@ __device__ __forceinline__ void stage_weights(const StageArgs &a, const PrepLaye
       }
     }
   };
-  // The first workers with each delay, dealt to the groups of blocks in turn.  (With a block for every worker and tile, most of which found that another one stood for
-  // their worker, 784-300-10 with 100 workers took 127.1 us per step, now 124.9; 784-512-10 with 64: the same.)
+  // The first workers with each delay, from a table of the delays (in the tile's room), are dealt to the groups of blocks in turn.
   __shared__ int32_t tau_s[kBlock];
-  __shared__ unsigned long long first_s[kBlock / kWave];
-  const bool listed = !is_w && a.rep && s.M <= kBlock;
-  int m = 0;
-  if (listed) {
-    if (t < s.M) tau_s[t] = min(s.tau[t], s.D);
+  __shared__ unsigned long long mine_s[kBlock / kWave];
+  if (!is_w && a.z_listed) {
+    int32_t *first_of = reinterpret_cast<int32_t *>(sm);
+    const int32_t tau = t < s.M ? min(max(s.tau[t], 0), s.D) : 0;
+    for (int j = t; j <= s.D; j += kBlock) first_of[j] = kBlock;
     lds_sync();
-    int r = 0;
-    if (t < s.M) {
-      const int32_t mine = tau_s[t];
-      while (tau_s[r] != mine) ++r;                     // (r <= t)
-      if (first_tile && z == 1) a.rep[t] = r;
-    }
-    const unsigned long long firsts = __ballot(t < s.M && r == t);
-    if ((t & 63) == 0) first_s[t >> 6] = firsts;
+    if (t < s.M) atomicMin(&first_of[tau], t);
     lds_sync();
-  } else if (!is_w && a.rep) {
+    const int r = t < s.M ? first_of[tau] : kBlock;
+    if (first_tile && z == 1 && t < s.M) a.rep[t] = r;
+    const unsigned long long firsts = __ballot(r == t);
+    tau_s[t] = tau;
+    if ((t & 63) == 0) mine_s[t >> 6] = firsts;
+    lds_sync();
+    int turn = __popcll(firsts & ((1ull << (t & 63)) - 1));
+    for (int i = 0; i < t >> 6; ++i) turn += __popcll(mine_s[i]);
+    const unsigned long long mine = __ballot(r == t && turn % a.z_groups == z - 1);
+    lds_sync();
+    if ((t & 63) == 0) mine_s[t >> 6] = mine;
+    lds_sync();
+    for (int i = 0; i < kBlock / kWave; ++i)
+      for (unsigned long long left = mine_s[i]; left; left &= left - 1) {
+        const int m = __builtin_amdgcn_readfirstlane(i * kWave + __ffsll(left) - 1);
+        one(m, __builtin_amdgcn_readfirstlane(tau_s[m]));
+        lds_sync();                                     // (the tile's room is written again)
+      }
+    return;
+  }
+  int m = 0, tau = 0;
+  if (!is_w && a.rep) {
     m = z - 1;
-    const int tau_m = min(s.tau[m], s.D);
+    tau = min(s.tau[m], s.D);
     int r = m;                                          // (every wavefront finds it for itself)
     for (int j0 = 0; j0 < m && r == m; j0 += kWave) {
       const int j = j0 + (t & 63);
-      const unsigned long long same = __ballot(j < m && min(s.tau[j], s.D) == tau_m);
+      const unsigned long long same = __ballot(j < m && min(s.tau[j], s.D) == tau);
       if (same) r = j0 + __ffsll(same) - 1;
     }
     if (first_tile && t == 0) a.rep[m] = r;
     if (r != m) return;                                 // another worker with the same reference point stands for this one
   }
-  unsigned long long left = listed ? first_s[0] : 0ull;
-  for (int i = 0, turn = 1;; ++turn) {
-    if (listed) {                                       // (uniform)
-      while (left == 0ull) {
-        if (++i == kBlock / kWave) return;
-        left = first_s[i];
-      }
-      m = __builtin_amdgcn_readfirstlane(i * kWave + __ffsll(left) - 1);
-      left &= left - 1;
-      if (turn != z) { if (turn == a.z_groups) turn = 0; continue; }
-      if (turn == a.z_groups) turn = 0;
-    }
-    one(m);
-    if (!listed) return;
-    lds_sync();                                         // (the tile's room is written again)
-  }
+  one(m, tau);
 }
 
 __global__ __launch_bounds__(kBlock) void k_stage(const StageArgs a) {
@@ -1919,7 +1920,12 @@ int mlp_init_state(Ctx *c, const float *) {
 static bool plain_rule(const MlpPlan &P) { return P.rule == CADA_RULE_ALWAYS || P.rule == CADA_RULE_LAG; }
 
 // The bf16 copies of the weights, and with idx the minibatch's rows and the differences to the reference points.
-constexpr int kStageGroups = 8;
+// The differences of CADA2 are formed by groups of blocks that share the distinct reference points out, so many groups as make the blocks fill the chip (eight per CU), eight at
+// least.  Every group's blocks start with the list of those points, and more groups than points leave the others' blocks nothing else to do.  Measured, us per step with a group per worker whose blocks
+// look for an equal delay before theirs / these groups / 8: every worker at another delay: 784-300-10, 100 workers of 12 rows: 192.2, 193.6, 270; 784-512-10, 64 of 128: 216.4, 217.6, 255; 100-32-10,
+// 256 of 8: 51.0, 50.5, 154 (8: with a list made by a walk over the workers as well); 3072-1024-1024-10, 16 of 256: 728.7, 717.3, 738; all workers at one: 113.0, 109.7, 108.5; 165.1, 162.5, 161.7;
+// 60.2, 60.5, 60.2; 559, 555, 554.  784-300-10 with 1024 / 4096 blocks: 212.8 / 188.5 and 108.8 / 113.0.
+constexpr int kStageBlocks = 2048, kStageGroups = 8;
 static void stage(Ctx *c, const MlpPlan &P, const DevState &s, const int32_t *idx) {
   const int L = P.L, M = P.M, B = P.B;
   StageArgs sa;
@@ -1928,7 +1934,11 @@ static void stage(Ctx *c, const MlpPlan &P, const DevState &s, const int32_t *id
   sa.XGh = P.XGh; sa.XGl = P.XGl;
   sa.d0 = P.d[0]; sa.B = B; sa.Bp = P.Bp; sa.ktx = P.kta[0];
   sa.gx = (int)((P.ldx + 63) / 64); sa.gy = (B + 63) / 64;
-  sa.n_layers = L; sa.z_groups = P.nW > kBlock ? P.nW : P.nW < kStageGroups ? P.nW : kStageGroups; sa.nz = idx && !plain_rule(P) ? sa.z_groups + 1 : 1; sa.wt_total = P.wt_total; sa.wn_total = P.wn_total; sa.rep = P.rule == CADA_RULE_CADA2 ? P.rep : nullptr;
+  int64_t tiles = 0;
+  for (int l = 1; l <= L; ++l) tiles += (int64_t)((P.d[l] + 63) / 64) * ((P.d[l - 1] + 63) / 64);
+  sa.z_listed = P.rule == CADA_RULE_CADA2 && M <= kBlock && c->s.D < kStageDelays;
+  sa.z_groups = sa.z_listed ? (int)std::min<int64_t>(P.nW, std::max<int64_t>(kStageGroups, (kStageBlocks + tiles - 1) / tiles)) : P.nW;
+  sa.n_layers = L; sa.nz = idx && !plain_rule(P) ? sa.z_groups + 1 : 1; sa.wt_total = P.wt_total; sa.wn_total = P.wn_total; sa.rep = P.rule == CADA_RULE_CADA2 ? P.rep : nullptr;
   uint64_t nblk = idx ? (uint64_t)sa.gx * sa.gy * M : 0;
   sa.first[0] = 0;
   for (int l = 1; l <= L; ++l) {
