@@ -104,3 +104,12 @@ def test_lag_left_hand_sides_of_networks(dims, rule, store):
         assert ((got == np.float32(want * (1 - 2.0 ** -40))) | (got == np.float32(want * (1 + 2.0 ** -40)))).all(), (k, got, want)
         before = now
     eng.close()
+
+
+# the right-hand side over rings that a wavefront takes in one round, in two, and in sixteen, before and after they have gone round
+@pytest.mark.parametrize("dims,d_max,K", [((8193,), 1, 8), ((8193,), 64, 70), ((8196,), 65, 70), ((8193,), 1024, 20), ((60, 40, 5), 1, 6), ((60, 40, 5), 65, 70)])
+def test_ring_lengths(dims, d_max, K):
+    if len(dims) > 1:
+        _check(configs.CFG5.scaled(name="ring", layer_dims=dims, M=3, N_m=30, B=6, K=K, D=9, d_max=d_max, c=20.0, rule=configs.RULE_CADA2), TOGETHER, 2e-2, None)
+    else:
+        _check(configs.CFG1.scaled(name="ring", layer_dims=dims, M=2, N_m=12, B=4, K=K, D=9, d_max=d_max, rule=configs.RULE_CADA2, c=2e-3), TOGETHER, 1e-4, 1e-4)

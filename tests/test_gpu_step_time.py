@@ -40,3 +40,14 @@ def test_distinct_reference_points():
     t = _shortest([binding.Cada.from_config(cfg, *dev) for _ in range(2)], sched, [apart, all_])
     print(t)
     assert t[0] < 1.4 * t[1], t
+
+
+@pytest.mark.parametrize("dims,M,B", [((8193,), 4, 64), ((100, 60, 5), 8, 12)])
+def test_long_ring(dims, M, B):
+    """A ring of 1024 squared steps against one of 64: 22 and 22, 44 and 44 us per step (added up by one thread: 95 and 23, 114 and 45)."""
+    base = configs.CFG5.scaled(name="time", layer_dims=dims, rule=configs.RULE_CADA1) if len(dims) > 1 else configs.CFG1.scaled(name="time", layer_dims=dims)
+    cfg = base.scaled(M=M, N_m=80, B=B, K=STEPS)
+    dev, sched = upload(generators.make_problem(cfg)), torch.from_numpy(generators.make_schedule(cfg).astype("int32")).cuda()
+    t = _shortest([binding.Cada.from_config(cfg.scaled(d_max=d), *dev) for d in (1024, 64)], sched, [None, None])
+    print(t)
+    assert t[0] < 1.6 * t[1], t
