@@ -1783,16 +1783,23 @@ template <int EPI, int NA, int NB, bool HAS_D> int launch_skinny_as(Ctx *c, Mm5A
                      dim3(64 * wide), skinny_lds_bytes(EPI, NA + NB, nw), c->stream, g);
   return CADA_OK;
 }
-// Hidden layers' forward products go through k_skinny while its 32 x 32 blocks fill the chip (two workgroups per CU) some two and a half
-// times over at most, or a worker has a single block of rows (a 128 x 128 tile would then be three quarters padding).  Few tiles leave CUs
+// Hidden layers' forward products go through k_skinny while its 32 x 32 blocks fill the chip (two workgroups per CU) at most twice
+// over, or a worker has a single block of rows (a 128 x 128 tile would then be three quarters padding).  Few tiles leave CUs
 // idle and run through the whole inner dimension one after the other, where k_skinny splits it over eight wavefronts.
-// Measured, us per step with k_skinny and with k_mm5 (blocks): 300-400-300-10, M = 20, B = 100 (1040): 132.0, 136.0; 784-500-10: M = 10, B = 200 (1120): 95.9, 101.3; LAG, M = 20,
-// B = 120 (1280): 86.4, 89.5; 784-512-10, M = 30, B = 96 (1440): 112.4, 114.0; 3072-1024-10, M = 16, B = 96 (1536): 346.8, 347.0; but 2000-130-10, M = 40, B = 200 (1400): 235.8, 226.7;
-// 100-300-10, M = 60, B = 96 (1800): 81.0, 78.8, always 60.5, 58.6; 1000-1000-10, M = 16, B = 128 (2048): 192.5, 188.2; 200-700-10, M = 40, B = 128 (3520): 106.8, 94.0; and
-// 784-500-10, M = 64, B = 64 (2048): 144.1, 146.8.
-constexpr int64_t kSkinnyBlocks = 1300;
+// Some two and a half times over as well, where the rows that an XCD meets stay in its L2 (4 MB) from one block of columns to the next: they are read again for each.  They are the same rows
+// each time where the row blocks are a multiple of the eight XCDs; where they are not, the products of a second gradient hide what that costs up to half as many rows.
+// Measured, us per step with k_skinny and with k_mm5 (inner dimension x units, row blocks), all workers uploading.  CADA2, rows in L2: 3072 x 1024, 40: 215.4, 237.1; 2000 x 500, 80: 145.9, 163.5; 784 x 512, 72:
+// 101.9, 110.5; 784 x 500, 70: 90.9, 95.7; 784 x 260, 144: 104.6, 109.7; 784 x 300, 130: 107.3, 107.5; past that: 2000 x 400, 95: 170.0, 169.9 (all delays different: 225.6, 218.8); 3072 x 130, 259: 241.4, 233.6
+// (279, 257); 2000 x 130, 259: 183.6, 181.3; 3072 x 257, 140: 207.8, 206.2; but 2000 x 256, 160: 141.8, 155.2.  Always, LAG: 2000 x 500, 80: 129.9, 141.7; 784 x 512, 72: 87.7, 91.8; 64 x 500, 80: 54.0, 54.0;
+// no multiple: 784 x 300, 130: 97.2, 93.1; 2000 x 400, 95: 158.7, 147.4; 784 x 500, 70: 77.9, 79.4; past it: 3072 x 128, 320: 214.1, 199.7; 2000 x 64, 640: 205.9, 200.4.
+// More blocks, CADA2: 2000-130-10, M = 40, B = 200 (1400): 235.8, 226.7; 100-300-10, M = 60, B = 96 (1800): 81.0, 78.8; 1000-1000-10, M = 16, B = 128 (2048): 192.5, 188.2.
+constexpr int64_t kSkinnyBlocks = 1024, kSkinnyBlocksInL2 = 1300, kL2Bytes = 4 << 20;
 static bool skinny_forward(const Mm5Args &g, int workers) {
-  return g.M <= 32 || (int64_t)((g.M + 31) / 32) * ((g.N + 31) / 32) * workers <= kSkinnyBlocks;
+  const int64_t row_blocks = (int64_t)((g.M + 31) / 32) * workers, blocks = row_blocks * ((g.N + 31) / 32);
+  if (g.M <= 32 || blocks <= kSkinnyBlocks) return true;
+  const bool plain = g.s.rule == CADA_RULE_ALWAYS || g.s.rule == CADA_RULE_LAG;
+  const int64_t row_bytes = row_blocks * 32 * g.K * g.A.n * (int64_t)sizeof(bf16_t), room = row_blocks % 8 == 0 ? 8 * kL2Bytes : plain ? 0 : 4 * kL2Bytes;
+  return blocks <= kSkinnyBlocksInL2 && row_bytes <= room;
 }
 // Weight gradients of the rules that read all of them back in the same step, stored ones beside fresh ones (k_lag_lhs).  When they outgrow the 256 MB of
 // memory-side cache it pays to write them past the caches: what k_dw's plain stores leave there is written back under that kernel's reads (3072-1024-10, 36 workers of 128

@@ -155,11 +155,11 @@ def test_reference_point_far_from_the_iterate():
     assert rel_l2(out["theta64"], o.theta) < BF16_TOL
 
 
-# Hidden layers' forward products on either side of the 32 x 32 blocks' range (one block of rows; 1024 blocks and more), odd widths
-# on both sides of 32, the rules with and without a second gradient.  Tolerances as in the reduced cases above.
+# Hidden layers' forward products on either side of the 32 x 32 blocks' range (one block of rows; 1024 blocks; from there to 1300 with row blocks that are a
+# multiple of eight and not; more), odd widths on both sides of 32, the rules with and without a second gradient.  Tolerances as in the reduced cases above.
 @pytest.mark.parametrize("dims,M,B,rule", [
     ((61, 133, 10), 3, 5, 1), ((61, 133, 10), 3, 33, 2), ((77, 67, 45, 7), 4, 32, 2), ((77, 67, 31, 7), 4, 40, 0), ((45, 33, 129, 5), 3, 130, 1),
-    ((50, 515, 10), 40, 33, 2), ((50, 515, 10), 61, 20, 3), ((50, 515, 9), 21, 64, 2), ((77, 131, 67, 7), 5, 100, 3), ((40, 31, 10), 3, 50, 3)])
+    ((50, 515, 10), 40, 33, 2), ((50, 515, 10), 61, 20, 3), ((50, 515, 9), 21, 64, 2), ((50, 515, 9), 38, 33, 2), ((50, 515, 10), 36, 33, 3), ((50, 515, 10), 37, 33, 0), ((77, 131, 67, 7), 5, 100, 3), ((40, 31, 10), 3, 50, 3)])
 def test_forward_blocks_and_odd_widths(dims, M, B, rule):
     lag = rule == configs.RULE_LAG
     cfg = configs.CFG4.scaled(name="blocks", layer_dims=dims, M=M, N_m=B + 60, B=B, K=12, D=5, rule=rule, c=20.0,

@@ -98,6 +98,13 @@ def test_every_column_of_every_workers_gradients(shape, rule):
             off += rows * b
 
 
+# 1200 to 1300 forward blocks of 32 x 32: row blocks that are a multiple of eight and not, rows that fit an XCD's L2 and do not
+@pytest.mark.parametrize("rule", list(RULES))
+@pytest.mark.parametrize("shape", [((100, 130, 5), 40, 200), ((100, 130, 5), 36, 200), ((100, 130, 5), 37, 200), ((700, 65, 10), 40, 320)], ids=lambda s: "-".join(map(str, s[0])) + "_M%d_B%d" % s[1:])
+def test_forward_blocks_in_and_past_the_l2(shape, rule):
+    test_every_column_of_every_workers_gradients(shape, rule)
+
+
 @pytest.mark.parametrize("rule", ["cada2", "always"])
 @pytest.mark.parametrize("dims", [(24, 45, 7), (24, 20, 5), (24, 150, 40, 5)], ids=lambda d: "-".join(map(str, d)))
 @pytest.mark.parametrize("B", [7, 33, 64, 100, 192, 224, 300, 513])
