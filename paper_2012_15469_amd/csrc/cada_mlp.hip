@@ -1828,8 +1828,7 @@ template <int EPI> bool tiles_fit(const Mm5Args &g) {
 }
 // Returns CADA_OK after enqueueing the launch, CADA_EUNSUPPORTED (and launches nothing) when the
 // operands do not fit a compiled variant.
-// first (EPI_DW): arguments of the layer above's weight gradient, kept back to be launched together with this one's.
-template <int EPI> int launch_mm5(Ctx *c, Mm5Args &g, int workers, Mm5Args *first = nullptr) {
+template <int EPI> int launch_mm5(Ctx *c, Mm5Args &g, int workers) {
   g.workers = workers;
   const bool has_d = g.a_d >= 0;
   if constexpr (EPI == EPI_DW || EPI == EPI_LOSS || EPI == EPI_FWD_HIDDEN) {
@@ -1855,14 +1854,9 @@ template <int EPI> int launch_mm5(Ctx *c, Mm5Args &g, int workers, Mm5Args *firs
     set_error("internal: the loss epilogue serves at most 32 classes");
     return CADA_EUNSUPPORTED;
   } else {
-  if (!tiles_fit<EPI>(g) || (first != nullptr && !tiles_fit<EPI>(*first))) return CADA_EUNSUPPORTED;
+  if (!tiles_fit<EPI>(g)) return CADA_EUNSUPPORTED;
   if constexpr (EPI == EPI_DW) {
     const bool cada1 = g.s.rule == CADA_RULE_CADA1;
-    if (first != nullptr) {
-      if (g.A.n == 2 && g.B.n == 2 && first->A.n == 2 && first->B.n == 2) return launch_dw_two<true, false>(c, *first, g);
-      if (!has_d && g.A.n == 2 && g.B.n == 3 && first->a_d >= 0 && first->A.n == 3 && first->B.n == 4)
-        return cada1 ? launch_dw_two<false, true>(c, *first, g) : launch_dw_two<false, false>(c, *first, g);
-    }
     if (g.A.n == 2 && g.B.n == 2) return dw_past_caches(g) ? launch_mm5_as<EPI, 2, 2, false>(c, g) : launch_dw_as<2, 2, false, false>(c, g);
     if (!has_d && g.A.n == 2 && g.B.n == 3) return cada1 ? launch_dw_as<2, 3, false, true>(c, g) : launch_dw_as<2, 3, false, false>(c, g);
     if (has_d && g.A.n == 3 && g.B.n == 4) return cada1 ? launch_dw_as<3, 4, true, true>(c, g) : launch_dw_as<3, 4, true, false>(c, g);
@@ -1875,6 +1869,17 @@ template <int EPI> int launch_mm5(Ctx *c, Mm5Args &g, int workers, Mm5Args *firs
   set_error("internal: no MFMA kernel variant for %d + %d tensors", g.A.n, g.B.n);
   return CADA_EUNSUPPORTED;
   }
+}
+
+// The weight gradients of the second layer (g2) and the first (g1) in one launch.  (As above: both or none.)
+int launch_weight_gradients_of_two(Ctx *c, Mm5Args &g2, Mm5Args &g1, int workers) {
+  g2.workers = g1.workers = workers;
+  if (!tiles_fit<EPI_DW>(g2) || !tiles_fit<EPI_DW>(g1)) return CADA_EUNSUPPORTED;
+  const bool cada1 = g1.s.rule == CADA_RULE_CADA1;
+  if (g1.A.n == 2 && g1.B.n == 2 && g2.A.n == 2 && g2.B.n == 2) return launch_dw_two<true, false>(c, g2, g1);
+  if (g1.a_d < 0 && g1.A.n == 2 && g1.B.n == 3 && g2.a_d >= 0 && g2.A.n == 3 && g2.B.n == 4) return cada1 ? launch_dw_two<false, true>(c, g2, g1) : launch_dw_two<false, false>(c, g2, g1);
+  set_error("internal: no kernel variant for the weight gradients of %d + %d and %d + %d tensors", g2.A.n, g2.B.n, g1.A.n, g1.B.n);
+  return CADA_EUNSUPPORTED;
 }
 
 Mm5Args blank(const DevState &s, const MlpPlan &P) {
@@ -2087,7 +2092,7 @@ int mlp_gradients(Ctx *c, const int32_t *idx) {
         waits = !(plain && (dw_past_caches(g) || dw_past_caches(g1)));
       }
       if (l == 2 && waits) second = g;
-      else if (const int rc = launch_mm5<EPI_DW>(c, g, M, l == 1 && waits ? &second : nullptr)) return rc;
+      else if (const int rc = l == 1 && waits ? launch_weight_gradients_of_two(c, second, g, M) : launch_mm5<EPI_DW>(c, g, M)) return rc;
     }
     if (l >= 2 && l < L) {   // gradient w.r.t. the activations of layer l-1, masks, bias partials
       Mm5Args g = blank(s, P);
