@@ -65,7 +65,7 @@ struct MlpPlan {
   bf16_t *Gh[CADA_MAX_LAYERS + 1], *Gl[CADA_MAX_LAYERS + 1], *dG[CADA_MAX_LAYERS + 1], *Gref[CADA_MAX_LAYERS + 1];       // layer l >= 1, (row, unit)
   uint64_t *maskbits[CADA_MAX_LAYERS];                    // hidden l: ReLU mask bits per tile and lane
   int32_t *rep;                                           // CADA2: first worker with the same reference point [M]
-  float *dbpart[2], *ddbpart[2];                          // [M][2 RT][max hidden width]: sums per band of 64 rows; those of hidden layer l in l mod 2
+  float *dbpart[2], *ddbpart[2];                          // [M][2 RT][max hidden width]: sums per band of 64 rows; those of hidden layer l in (l - 1) mod 2
   size_t band_floats;                                     // of one of them
   char *eval;                                             // scratch of the evaluation (mlp_eval_bytes)
   float *lastb;                                           // [M][Bp / 32][32][2]: last layer, sums of G and dG per block of 32 rows

@@ -1440,8 +1440,8 @@ static size_t lhs_bytes(const cada_config *cfg) {
   return ((size_t)cfg->M * lhs_parts(cfg) * sizeof(float) + kAlignB - 1) / kAlignB * kAlignB + rule_room(cfg);
 }
 
-// The sums per band of the odd layers' signals (two arrays), behind them.
-static size_t bands_bytes(const MlpPlan &P) { return 2 * ((P.band_floats * sizeof(float) + kAlignB - 1) / kAlignB * kAlignB); }
+// The sums per band of the signals of the second, fourth, ... hidden layer (two arrays), behind them.
+static size_t bands_bytes(const MlpPlan &P) { return P.L < 3 ? 0 : 2 * ((P.band_floats * sizeof(float) + kAlignB - 1) / kAlignB * kAlignB); }
 
 size_t mlp_scratch_bytes(const cada_config *cfg, const int64_t total_rows) {
   MlpPlan P;
@@ -1460,8 +1460,10 @@ int mlp_plan(Ctx *c, const cada_config *cfg, char *base, size_t offset, size_t s
   c->s.lhs_part = reinterpret_cast<float *>(base + scratch);
   c->s.n_lhs_part = lhs_parts(cfg);
   decide_plan(c, base + scratch + lhs_bytes(cfg) - rule_room(cfg));
-  P->dbpart[1] = reinterpret_cast<float *>(base + scratch + lhs_bytes(cfg));
-  P->ddbpart[1] = reinterpret_cast<float *>(base + scratch + lhs_bytes(cfg) + bands_bytes(*P) / 2);
+  if (P->L >= 3) {
+    P->dbpart[1] = reinterpret_cast<float *>(base + scratch + lhs_bytes(cfg));
+    P->ddbpart[1] = reinterpret_cast<float *>(base + scratch + lhs_bytes(cfg) + bands_bytes(*P) / 2);
+  }
   P->eval = base + scratch + lhs_bytes(cfg) + bands_bytes(*P);
   c->mlp = P;
   c->n_phases = 0;
@@ -2032,7 +2034,7 @@ static void signals_below(Mm5Args &g, const MlpPlan &P, int q, bool plain) {
   g.kto = P.kta[q];
   g.o_h = P.Gh[q]; g.o_l = P.Gl[q]; g.o_d = plain ? nullptr : P.dG[q]; g.o_r = plain ? nullptr : P.Gref[q];     // (Gref: null for q = 1)
   g.maskbits = P.maskbits[q];
-  g.dbpart = P.dbpart[q & 1]; g.ddbpart = P.ddbpart[q & 1]; g.nband = 2 * P.RT;
+  g.dbpart = P.dbpart[(q - 1) & 1]; g.ddbpart = P.ddbpart[(q - 1) & 1]; g.nband = 2 * P.RT;
 }
 
 int mlp_gradients(Ctx *c, const int32_t *idx) {
@@ -2083,7 +2085,7 @@ int mlp_gradients(Ctx *c, const int32_t *idx) {
           signals_below(g, P, l - 1, plain);
         }
       } else if (bias_inside(M, din, dout)) {       // and the other layers' from the sums of the launch that formed their signals
-        g.dbpart = P.dbpart[l & 1]; g.ddbpart = P.ddbpart[l & 1]; g.nband = 2 * P.RT; g.bias_here = 1; g.offb = P.offb[l - 1]; g.lhs_slot_b = P.lhs_b_slot[l - 1];
+        g.dbpart = P.dbpart[(l - 1) & 1]; g.ddbpart = P.ddbpart[(l - 1) & 1]; g.nband = 2 * P.RT; g.bias_here = 1; g.offb = P.offb[l - 1]; g.lhs_slot_b = P.lhs_b_slot[l - 1];
       }
       if (l == 2 && l < L && dout > 32 && din > 32) {
         g.workers = M;
@@ -2113,7 +2115,7 @@ int mlp_gradients(Ctx *c, const int32_t *idx) {
       if (const int rc = launch_mm5<EPI_DA>(c, g, M)) return rc;
     }
     if (l >= 2 && !bias_inside(M, P.d[l - 2], din))
-      hipLaunchKernelGGL(k_bias_finish, dim3((din + kWave - 1) / kWave, M), dim3(kWave), 0, st, s, P.dbpart[(l - 1) & 1], plain ? nullptr : P.ddbpart[(l - 1) & 1], 2 * P.RT, (B + 63) / 64, din,
+      hipLaunchKernelGGL(k_bias_finish, dim3((din + kWave - 1) / kWave, M), dim3(kWave), 0, st, s, P.dbpart[l & 1], plain ? nullptr : P.ddbpart[l & 1], 2 * P.RT, (B + 63) / 64, din,
                          P.offb[l - 2], P.lhs_b_slot[l - 2]);
   }
   prof_mark(c);
