@@ -306,7 +306,7 @@ __global__ __launch_bounds__(R_NT) void k_rows(const Args a) {
     double l = red_l[0];
 #pragma unroll
     for (int i = 1; i < R_NW; ++i) l += red_l[i];
-    const float hi = (float)l, lo = (float)(l - (double)hi);
+    const float hi = (float)l, lo = isinf(hi) ? 0.f : (float)(l - (double)hi);
     put_far(lhs_far + m, ((uint64_t)__float_as_uint(lo) << 32) | __float_as_uint(hi));
     up_s = 0u;
   }

@@ -112,3 +112,23 @@ def test_sums_of_the_rule_keep_small_terms(p, M):
     assert st["lhs"].cpu().numpy().tolist() == [want] * M
     assert st["ring"].cpu().numpy()[0] == want
     eng.close()
+
+
+@pytest.mark.parametrize("p,M,path,phase", [(784, 10, binding.PATH_AUTO, "logreg_rows"), (1025, 4, binding.PATH_AUTO, "logreg_rows"), (54, 300, binding.PATH_AUTO, "logreg_rows"),
+                                            (8192, 3, binding.PATH_AUTO, "logreg_rows"), (8193, 3, binding.PATH_AUTO, "logreg_rows"), (1025, 4, binding.PATH_TWO_PASS, "logreg_two_pass")])
+def test_left_hand_side_past_float32(p, M, path, phase):
+    """A left-hand side past float32's range is infinite, which is more than any right-hand side: the worker uploads.  (Not a number, and the worker silent, where what
+    infinity is rounded by was added to it.)"""
+    B = 70
+    X = torch.full((2 * M * B, p), 1e20, device="cuda")
+    y = torch.ones(2, B, device="cuda")
+    y[1] = -1.0
+    eng = binding.Cada(model="logreg", layer_dims=[p], M=M, B=B, n_samples=[2 * B] * M, X=X, y=y.reshape(-1).repeat(M).contiguous(), theta0=torch.zeros(p, device="cuda"),
+                       rule=configs.RULE_LAG, D=50, d_max=10, c=0.5, alpha=1e-30, beta1=0.9, beta2=0.999, eps=1e-8, server=1, trace_steps=2, path=path)
+    assert phase in binding.cada_profile_phase_names(eng.ctx)
+    rows = torch.arange(2 * B, dtype=torch.int32, device="cuda").view(2, 1, B).repeat(1, M, 1).contiguous()      # a gradient, then its opposite
+    eng.run(rows)
+    st = {name: t.cpu().numpy().copy() for name, t in eng.state().items() if name.startswith("trace")}
+    eng.close()
+    assert np.isposinf(st["trace_lhs"]).all() and np.isfinite(st["trace_rhs"]).all(), (st["trace_lhs"], st["trace_rhs"])
+    assert st["trace_own_mask"].all() and st["trace_mask"].all()
