@@ -356,16 +356,20 @@ __global__ __launch_bounds__(kBlock, 7) void k_server(const DevState s, const Ru
 }
 
 // The rule in the server's launch saves one, and every workgroup reads all partial sums of the left-hand sides for it.  Measured, us per step with it / with a launch of
-// its own, M workers of n parts: p = 20001, M = 37, n = 20: 61.8 / 63.2; p = 10000, M = 250, n = 10: 65.1 / 67.7; 784-500-10, M = 10, n = 137: 65.1 / 65.9; 300-200-10, LAG, M = 30,
-// n = 34: 50.6 / 52.2; 400-300-10, M = 24, n = 66: 63.1 / 64.0; but 200-150-10, M = 64, n = 28: 68.4 / 67.6; 1000-800-10, M = 16, n = 267: 144.9 / 142.0;
+// its own, M workers of n parts.  Few parts (rows that are read 16 bytes at a time): p = 20480, n = 20: M = 64: 33.5 / 34.8; 128: 41.3 / 42.2; 256: 58.9 / 59.2; p = 10000, n = 10: M = 64: 24.7 / 25.9; 128: 33.6 /
+// 33.5; 256: 47.6 / 45.9; 4 bytes at a time, p = 10001, n = 10: M = 64: 24.7 / 32.2; 256: 47.4 / 69.9; 512-128-10, n = 23: M = 64: 52.0 / 53.5; 256: 106.1 / 106.7; 384-128-10, n = 19: M = 256: 94.9 / 94.0;
+// 100-60-5, n = 11: M = 256: 63.2 / 63.1.  LAG and always: 384-120-10, n = 24: M = 64: 46.1 / 47.5; 128: 58.4 / 58.5; 256: 86.2 / 83.7; 150-100-10, n = 8: M = 64: 41.9 / 43.4; 128: 51.8 / 51.5; 256: 67.8 / 64.5;
+// 100-60-5, n = 4: M = 256: 54.4 / 54.3.  More parts: 784-500-10, n = 137: M = 10: 58.5 / 60.1; 21: 73.0 / 74.1; 400-300-10, n = 66: M = 32: 58.4 / 60.9; 700-700-10, LAG, n = 246: M = 3: 46.9 / 45.9;
+// but 200-150-10, M = 64, n = 28: 68.4 / 67.6; 1000-800-10, M = 16, n = 267: 144.9 / 142.0;
 // 2000-500-10, M = 20, n = 281: 154.9 / 153.0; 784-300-10, M = 100: 130.1 / 127.6; 784-512-10, M = 64, n = 137: 174.2 / 171.3; 3072-1024-1024-10, M = 16: 580.9 / 577.1.
-// The launch of its own, with the squared step's parts added up and the inputs taken down in front: 3 us, before 5 to 11 (3072-1024-1024-10: 583 -> 577 us per step).
+// The launch of its own takes 5 to 7 us where the squared step's parts are added up and the inputs taken down in front, 11 where it does that itself.
 constexpr int64_t kDecideParts = 3000;
 constexpr int kDecideBlocks = 7 * 256;           // seven workgroups of 68 registers per CU
 void decide_plan(Ctx *c, char *room) {
   c->rule_in = RuleInputs{reinterpret_cast<double *>(room), reinterpret_cast<int32_t *>(room + 256)};
   const int64_t M = c->s.M, n = c->s.n_lhs_part;
-  c->decide = M <= kDecideWorkers && (n <= kDecideSerial || (M <= 32 && M * n <= kDecideParts));
+  const bool one_gradient = c->s.rule == CADA_RULE_ALWAYS || c->s.rule == CADA_RULE_LAG;
+  c->decide = M <= (c->model == CADA_MODEL_MLP && one_gradient && n > 4 ? kDecideWorkers / 2 : kDecideWorkers) && (n <= kDecideSerial || (M <= 32 && M * n <= kDecideParts));
 }
 
 namespace {

@@ -47,6 +47,12 @@ def test_networks(dims, M, phase, rule):
     _check(configs.CFG5.scaled(name="rule", layer_dims=dims, M=M, N_m=30, B=6, K=6, D=3, c=20.0, rule=rule), phase, 2e-2, None)
 
 
+# networks without a second gradient, whose parts are two per 4096 coordinates: 10 parts up to 128 workers, 4 up to 256
+@pytest.mark.parametrize("dims,M,phase", [((130, 129, 5), 128, TOGETHER), ((130, 129, 5), 129, APART), ((100, 60, 5), 256, TOGETHER), ((100, 60, 5), 257, APART)])
+def test_networks_with_one_gradient(dims, M, phase):
+    _check(configs.CFG5.scaled(name="rule", layer_dims=dims, M=M, N_m=60, B=6, K=6, D=3, rule=configs.RULE_LAG, c=20.0, server=1), phase, 2e-2, None)
+
+
 # rows of more than 8192 columns: 9, 10 and 20 parts; widths that are no multiple of four
 @pytest.mark.parametrize("p,M,phase", [(8193, 1, TOGETHER), (20479, 5, TOGETHER), (8193, 33, TOGETHER), (9300, 256, TOGETHER), (8196, 257, APART)])
 def test_wide_rows(p, M, phase):
