@@ -53,10 +53,38 @@ def test_networks_with_one_gradient(dims, M, phase):
     _check(configs.CFG5.scaled(name="rule", layer_dims=dims, M=M, N_m=60, B=6, K=6, D=3, rule=configs.RULE_LAG, c=20.0, server=1), phase, 2e-2, None)
 
 
+# The sums of 28 and 180 parts above, and of 765, 770 and 924, which four wavefronts take in one round of 192, in two of which the last holds one part, and in two; against the
+# oracle's left-hand sides, so that no part is left out, counted twice or another worker's.  (Bounds as in test_gpu_mlp_tiles.)
+@pytest.mark.parametrize("rule", [configs.RULE_CADA1, configs.RULE_CADA2], ids=["cada1", "cada2"])
+@pytest.mark.parametrize("dims,M", [(d, m) for d, m, phase in NETWORKS if phase == TOGETHER] + [((12032, 200, 10), 3), ((24448, 40, 10), 3), ((24448, 40, 10), 1), ((1800, 1700, 10), 2)])
+def test_left_hand_sides_of_networks(dims, M, rule):
+    cfg = configs.CFG5.scaled(name="rule", layer_dims=dims, M=M, N_m=30, B=6, K=5, D=3, c=20.0, rule=rule)
+    prob = generators.make_problem(cfg)
+    stats, o, tr, rep = check_protocol(cfg, prob, upload(prob), generators.make_schedule(cfg), 2e-2, lhs_rtol=None, own_mask_exact=False, free_margin=None, expect_phase=TOGETHER)
+    big = tr["lhs"] > 1e-9 * tr["lhs"].max()
+    rel = np.abs(rep["trace_lhs"] - tr["lhs"]) / np.maximum(tr["lhs"], 1e-300)
+    assert float(np.median(rel[big])) < 2.0 ** -7 and float(np.quantile(rel[big], 0.99)) < 0.2
+    assert all(float(np.median(rel[big[:, m], m])) < 0.05 for m in range(M) if big[:, m].any())
+
+
 # rows of more than 8192 columns: 9, 10 and 20 parts; widths that are no multiple of four
 @pytest.mark.parametrize("p,M,phase", [(8193, 1, TOGETHER), (20479, 5, TOGETHER), (8193, 33, TOGETHER), (9300, 256, TOGETHER), (8196, 257, APART)])
 def test_wide_rows(p, M, phase):
     _check(configs.CFG1.scaled(name="rule", layer_dims=(p,), M=M, N_m=12, B=4, K=6, D=4, rule=configs.RULE_CADA2, c=2e-3), phase, 1e-4, 1e-4)
+
+
+# rows of up to 8192 columns whose server has a launch of its own: every variant, a share per worker and several, up to 256 workers; above, the last workgroup runs the rule
+@pytest.mark.parametrize("rule", [configs.RULE_CADA1, configs.RULE_CADA2, configs.RULE_LAG], ids=["cada1", "cada2", "lag"])
+@pytest.mark.parametrize("p,M,B,phase", [(54, 33, 130, TOGETHER), (256, 256, 65, TOGETHER), (300, 64, 130, TOGETHER), (512, 65, 130, TOGETHER), (512, 255, 33, TOGETHER), (784, 33, 130, TOGETHER),
+                                         (784, 256, 40, TOGETHER), (1024, 64, 66, TOGETHER), (1024, 256, 33, TOGETHER), (1025, 256, 12, TOGETHER), (2049, 255, 12, TOGETHER), (4100, 256, 10, TOGETHER),
+                                         (54, 257, 65, APART), (300, 512, 33, APART), (784, 257, 40, APART), (1025, 257, 12, APART), (2049, 512, 12, APART), (8191, 257, 10, APART)])
+def test_rows(p, M, B, phase, rule):
+    cfg = configs.CFG1.scaled(name="rule", layer_dims=(p,), M=M, N_m=B + 40, B=B, K=6, D=4, rule=rule, c=0.5 if p < 100 else 2e-3, server=1 if rule == configs.RULE_LAG else 0)
+    prob = generators.make_problem(cfg)
+    eng = binding.Cada.from_config(cfg, *upload(prob))
+    assert binding.cada_profile_phase_names(eng.ctx) == ["logreg_rows", phase]
+    eng.close()
+    _check(cfg, phase, 1e-4, 1e-4)
 
 
 def test_phase_names():
