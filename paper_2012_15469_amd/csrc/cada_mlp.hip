@@ -1630,9 +1630,11 @@ __device__ __forceinline__ void stage_weights(const StageArgs &a, const PrepLaye
     const int32_t tau = t < s.M ? min(max(s.tau[t], 0), s.D) : 0;
     for (int j = t; j <= s.D; j += kBlock) first_of[j] = kBlock;
     lds_sync();
-    if (t < s.M) atomicMin(&first_of[tau], t);
+    // (equal delays take their turns at the table's entry: a wavefront's first worker, often one of many with the same, stands for those of its wavefront)
+    const int32_t lead = __builtin_amdgcn_readlane(tau, 0);
+    if (t < s.M && ((t & 63) == 0 || tau != lead)) atomicMin(&first_of[tau], t);
     lds_sync();
-    const int r = t < s.M ? first_of[tau] : kBlock;
+    const int r = t < s.M ? min(first_of[tau], t) : kBlock;
     if (first_tile && z == 1 && t < s.M) a.rep[t] = r;
     const unsigned long long firsts = __ballot(r == t);
     tau_s[t] = tau;
