@@ -372,7 +372,8 @@ int mlp_init_state(Ctx *c, const float *theta0);
 void mlp_free(Ctx *c);
 constexpr int kLagSpan = 4096;              // coordinates of a worker that a block of k_lag_lhs takes at a time; it leaves two parts
 inline int lag_blocks(int64_t p) { return (int)((p + kLagSpan - 1) / kLagSpan); }
-// Room for the rule's inputs, and whether the server's workgroups run the rule (cada_server.hip).
+// Room for the rule's inputs, and whether the server's workgroups run the rule (cada_server.hip: at most so many workers).
+constexpr int kDecideWorkers = 256;
 constexpr size_t rule_in_bytes(int M) { return 256 + (size_t)M * 2 * sizeof(int32_t); }
 void decide_plan(Ctx *c, char *room);
 // S3: rule, mask, tau.  S5-S7: aggregate, AMSGrad, ring push.

@@ -1,6 +1,9 @@
 // Dual minibatch gradient, rule and (small states) server update of the logistic model for rows that one workgroup can
-// hold in its registers (p <= 8192): a step is ONE launch, two where the state is too large for one workgroup's server
-// phase, three where the workers are too many for one workgroup's rule, and the rows cross the memory bus once.
+// hold in its registers (p <= 8192), and the rows cross the memory bus once.  A step is
+//   ONE launch where the state is small (kServerColumns, kServerState, kServerWorkers): its last workgroup runs rule and server;
+//   two, up to kRuleInServer workers: the server's launch runs the rule (cada_server.hip), from inputs that this one takes down;
+//   two, up to kRuleWorkers: the last workgroup runs the rule;
+//   three with more workers: the rule has a launch of its own.
 //
 // Workgroup (g, m) takes a share of worker m's minibatch rows.  The rows of a share are read into registers, many at a
 // time; z = x.theta and dz = x.d are summed over the lanes, turned into the residual and its difference (formulas as in
@@ -11,7 +14,7 @@
 //     batch of rows.  The next batch is asked for before a batch's products; in every other one the compiled loop waits for it as well.
 // Nothing waits for another workgroup: whoever finishes last continues.  The last workgroup of a worker adds the shares'
 // sums up in their order, forms the fresh gradient and the left-hand side; the last of those runs the rule for
-// all workers (up to kRuleWorkers), and, where the state is small, the server update.  The partial sums, gradients and left-hand sides that are passed on
+// all workers, and the server update, where the list above says so.  The partial sums, gradients and left-hand sides that are passed on
 // inside the launch are written and read at device scope (past the XCD's cache).
 //
 // Wider rows, up to 20480 columns: k_rows_wide and k_rows_sum below, two launches, and the server's with the rule in it (more than 256 workers: a launch of its own).
@@ -36,11 +39,11 @@ enum { kTailNone = 0, kTailRule = 1, kTailServer = 2 };      // what the workgro
 constexpr int kServerColumns = 2 * R_NT, kServerState = 16384, kServerWorkers = 32;      // p, M p and M up to here
 // The rule in the last workgroup saves a launch as well; the workgroups count themselves in one after the other for it.  Measured, us with
 // and without it: B = 65, p = 22: M = 100: 17.2, 19.9; 256: 23.3, 24.1; 400: 28.6, 30.0; 512: 32.3, 32.4; 1024: 54.9, 53.8; p = 8191, M = 512: 215, 219;
-// 1024: 414, 416. 
+// 1024: 414, 416.
 // In the server's launch (cada_server.hip) it needs neither: up to 256 workers.  us per step there / in the last workgroup: p = 54, M = 200, B = 100: 21.6 / 33.7; p = 300,
 // M = 100, B = 80: 20.8 / 24.4; p = 784, M = 256, B = 40: 31.8 / 41.9; M = 64, B = 60: 20.7 / 23.7; p = 1500, M = 10, B = 64: 16.6 / 17.7; p = 8192, LAG, M = 16: 34.6 / 36.4;
 // p = 4000, M = 100, B = 256: 93.8 / 96.4.  (The server update in the last workgroup stays where it is: p = 784, M = 16, B = 100: 17.0 for 18.0, p = 100, M = 10: 12.1 for 13.8.)
-constexpr int kRuleWorkers = 512, kRuleInServer = 256;
+constexpr int kRuleWorkers = 512, kRuleInServer = kDecideWorkers;
 
 struct RowsArgs {
   DevState s;
@@ -420,7 +423,7 @@ __global__ __launch_bounds__(R_NT) void k_rows(const Args a) {
 // no exchange, which cost the cluster kernel of cada_logreg_fused.hip some 50 us per step whatever the size), CW quads of each per lane.
 // What bounds it: HBM, at 5.9 TB/s in long shares, and some 7 us of operands and sums at the two ends (a CU takes 64 bytes per cycle: 320 KB of theta,
 // theta_lo and the reference point for 20480 columns are 2.5 us).  Measured per step, two passes or the cluster
-// kernel in place of these launches: M = 37, B = 75, p = 20001, CADA1: 117 -> 66 us; M = 8, B = 256, p = 8196: 117 -> 35;
+// kernel in place of these launches: M = 37, B = 75, p = 20001, CADA1: 117 -> 62 us; M = 8, B = 256, p = 8196: 117 -> 35;
 // M = 100, B = 256, p = 20480 (2.1 GB of rows): 391 -> 356.  Rows without the non-temporal hint, the last of these: 433 (387 with it then).
 // The operands' latency is paid once: asked for piece by piece as the registers of the piece before fell free (with 28 to 40 bytes of them spilled, whose
 // reloads drained the rows in flight), p = 20001: 73.8 us, now 66.3; p = 12001: 57.5, 48.6; p = 20480, M = 100, B = 256: 381, 356.

@@ -1,4 +1,4 @@
-// The rule's decisions for all workers without a launch of their own, which costs some 3 to 5 us for under 1 us of work: by the workgroup of a gradient
+// The rule's decisions for all workers without a launch of their own, which takes 5 to 7 us for under 1 us of work: by the workgroup of a gradient
 // kernel that finishes last (last_of), or by every workgroup of the server's launch from inputs taken down in front (rule_inputs).
 #pragma once
 

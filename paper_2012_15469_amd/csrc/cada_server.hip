@@ -157,7 +157,7 @@ __global__ __launch_bounds__(kBlock) void k_ring_finalize(const DevState s) {
 // grid = n_ring_part = ceil(p / 256) blocks.
 // DECIDE: S3 as well.  Every workgroup runs the rule for itself, from the left-hand sides' partial sums and the inputs that an earlier launch has taken down (rule_inputs: nothing
 // of what it reads is written in this launch); the first one keeps the books.  As many workgroups as are resident at once then take the coordinates in turn.
-constexpr int kDecideWorkers = 256, kDecideSerial = 24;
+constexpr int kDecideSerial = 24;
 template <int VEC, bool DECIDE>
 __global__ __launch_bounds__(kBlock, 7) void k_server(const DevState s, const RuleInputs ri, const uint8_t *replay) {
   __shared__ __align__(16) float part[DECIDE ? 2 : 1][4][256];
@@ -362,7 +362,7 @@ __global__ __launch_bounds__(kBlock, 7) void k_server(const DevState s, const Ru
 // 100-60-5, n = 4: M = 256: 54.4 / 54.3.  More parts: 784-500-10, n = 137: M = 10: 58.5 / 60.1; 21: 73.0 / 74.1; 400-300-10, n = 66: M = 32: 58.4 / 60.9; 700-700-10, LAG, n = 246: M = 3: 46.9 / 45.9;
 // but 200-150-10, M = 64, n = 28: 68.4 / 67.6; 1000-800-10, M = 16, n = 267: 144.9 / 142.0;
 // 2000-500-10, M = 20, n = 281: 154.9 / 153.0; 784-300-10, M = 100: 130.1 / 127.6; 784-512-10, M = 64, n = 137: 174.2 / 171.3; 3072-1024-1024-10, M = 16: 580.9 / 577.1.
-// The launch of its own takes 5 to 7 us where the squared step's parts are added up and the inputs taken down in front, 11 where it does that itself.
+// The launch of its own: 784-512-10, M = 64: 4.8 us, 5.9 where it adds the squared step's parts up itself; 3072-1024-1024-10, M = 16: 6.7, 10.7.
 constexpr int64_t kDecideParts = 3000;
 constexpr int kDecideBlocks = 7 * 256;           // seven workgroups of 68 registers per CU
 void decide_plan(Ctx *c, char *room) {

@@ -46,7 +46,8 @@ def test_wide_rows_path_shares_of_several_workers(p, M, B, rule):
     test_rows_path(p, M, B, rule, K=8, spare=40 if rule == configs.RULE_LAG else 3)
 
 
-# the rule in the last workgroup up to 512 workers (more than 8192 columns: in the server's launch up to 256), in a launch of its own for more
+# the rule in the server's launch up to 256 workers (or, with the server, in the last workgroup), in the last workgroup up to 512, in a launch of its own for more; more than 8192
+# columns: in the server's launch up to 256, in a launch of its own for more
 @pytest.mark.parametrize("p,M,B,rule", [(54, 512, 33, 2), (54, 513, 33, 1), (257, 530, 40, 3), (1025, 513, 8, 2), (2050, 513, 9, 0), (8193, 32, 5, 1), (8200, 33, 5, 2),
                                         (10241, 40, 9, 0)])
 def test_rows_path_many_workers(p, M, B, rule):
