@@ -1522,8 +1522,7 @@ struct StageArgs {
   // reference point theta^{k - tau}, hence the difference theta - theta_ref and its bf16 copies;
   // out: rep[m] = the first worker with worker m's (clamped) tau.  Only that worker's difference is computed.
   int32_t *rep;
-  int z_groups;          // groups of blocks that share these workers out
-  int z_listed;          // 1: every block makes the list of them; else a group for every worker, which finds out for itself whether it is a first one
+  int z_groups;          // groups of blocks that share these workers out: k_stage<true>, every block makes the list of them; else a group for every worker, which finds out for itself whether it is a first one
   uint32_t first[CADA_MAX_LAYERS + 2];   // first block of the minibatch part (0), of each layer, and the total
   int rule_block;        // 1: one more block, in front of them, takes the rule's inputs down
   RuleInputs rule_in;
@@ -1561,6 +1560,8 @@ constexpr int kStageDelays = 64 * 65;            // delays that the list's table
 // A 64 x 64 tile of one layer's weights (z = 0: hi and lo parts of W) or of their differences to the
 // reference points of group z (worker z - 1's where there is no list), 8 values per lane: rows of W are read (4-byte aligned
 // 16-byte loads) and written as they are, and turned through LDS for the other orientation.
+// LIST: the differences go by the list of distinct reference points (CADA2, up to 256 workers and 4159 delays); an instance of its own, whose registers the others need not pay for.
+template <bool LIST>
 __device__ __forceinline__ void stage_weights(const StageArgs &a, const PrepLayer &p, unsigned char *sm, int bx, int by, int z, bool first_tile) {
   const DevState &s = a.s;
   typedef float tile_t[64][65];
@@ -1568,9 +1569,8 @@ __device__ __forceinline__ void stage_weights(const StageArgs &a, const PrepLaye
   tile_t &tile = *reinterpret_cast<tile_t *>(sm);
   const int o0 = bx * 64, i0 = by * 64;
   const int t = threadIdx.x;
-  const bool is_w = z == 0;
   const int og = (t & 7) * 8;
-  auto one = [&](const int m, const int32_t tau) __attribute__((always_inline)) {
+  auto one = [&](const bool is_w, const int m, const int32_t tau) __attribute__((always_inline)) {
     const RefPtr ref = theta_ref_at(s, tau, s.k);
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
@@ -1623,9 +1623,10 @@ __device__ __forceinline__ void stage_weights(const StageArgs &a, const PrepLaye
     }
   };
   // The first workers with each delay, from a table of the delays (in the tile's room), are dealt to the groups of blocks in turn.
-  __shared__ int32_t tau_s[kBlock];
-  __shared__ unsigned long long mine_s[kBlock / kWave];
-  if (!is_w && a.z_listed) {
+  if constexpr (LIST) {
+    __shared__ int32_t tau_s[kBlock];
+    __shared__ unsigned long long mine_s[kBlock / kWave];
+    if (z == 0) { one(true, 0, 0); return; }
     int32_t *first_of = reinterpret_cast<int32_t *>(sm);
     const int32_t tau = t < s.M ? min(max(s.tau[t], 0), s.D) : 0;
     for (int j = t; j <= s.D; j += kBlock) first_of[j] = kBlock;
@@ -1649,28 +1650,29 @@ __device__ __forceinline__ void stage_weights(const StageArgs &a, const PrepLaye
     for (int i = 0; i < kBlock / kWave; ++i)
       for (unsigned long long left = mine_s[i]; left; left &= left - 1) {
         const int m = __builtin_amdgcn_readfirstlane(i * kWave + __ffsll(left) - 1);
-        one(m, __builtin_amdgcn_readfirstlane(tau_s[m]));
+        one(false, m, __builtin_amdgcn_readfirstlane(tau_s[m]));
         lds_sync();                                     // (the tile's room is written again)
       }
-    return;
-  }
-  int m = 0, tau = 0;
-  if (!is_w && a.rep) {
-    m = z - 1;
-    tau = min(s.tau[m], s.D);
-    int r = m;                                          // (every wavefront finds it for itself)
-    for (int j0 = 0; j0 < m && r == m; j0 += kWave) {
-      const int j = j0 + (t & 63);
-      const unsigned long long same = __ballot(j < m && min(s.tau[j], s.D) == tau);
-      if (same) r = j0 + __ffsll(same) - 1;
+  } else {
+    int m = 0, tau = 0;
+    if (z != 0 && a.rep) {
+      m = z - 1;
+      tau = min(s.tau[m], s.D);
+      int r = m;                                          // (every wavefront finds it for itself)
+      for (int j0 = 0; j0 < m && r == m; j0 += kWave) {
+        const int j = j0 + (t & 63);
+        const unsigned long long same = __ballot(j < m && min(s.tau[j], s.D) == tau);
+        if (same) r = j0 + __ffsll(same) - 1;
+      }
+      if (first_tile && t == 0) a.rep[m] = r;
+      if (r != m) return;                                 // another worker with the same reference point stands for this one
     }
-    if (first_tile && t == 0) a.rep[m] = r;
-    if (r != m) return;                                 // another worker with the same reference point stands for this one
+    one(z == 0, m, tau);
   }
-  one(m, tau);
 }
 
-__global__ __launch_bounds__(kBlock) void k_stage(const StageArgs a) {
+template <bool LIST>
+__global__ __launch_bounds__(kBlock, LIST ? 5 : 8) void k_stage(const StageArgs a) {
   __shared__ __align__(16) unsigned char sm[64 * 65 * sizeof(float)];     // a weight tile on its way to the other orientation
   if (a.rule_block && blockIdx.x == 0) {
     rule_inputs(a.s, a.rule_in, reinterpret_cast<double *>(sm));
@@ -1689,7 +1691,7 @@ __global__ __launch_bounds__(kBlock) void k_stage(const StageArgs a) {
   const uint32_t rel = blk - a.first[l + 1];
   const uint32_t per = (uint32_t)p.gx * p.gy;
   const uint32_t z = rel / per, r = rel - z * per;
-  stage_weights(a, p, sm, (int)(r % p.gx), (int)(r / p.gx), (int)z, l == 0 && r == 0);
+  stage_weights<LIST>(a, p, sm, (int)(r % p.gx), (int)(r / p.gx), (int)z, l == 0 && r == 0);
 }
 
 // Hidden-layer bias gradient and its innovation from the sums per band of 64 rows.
@@ -1952,8 +1954,8 @@ static void stage(Ctx *c, const MlpPlan &P, const DevState &s, const int32_t *id
   sa.gx = (int)((P.ldx + 63) / 64); sa.gy = (B + 63) / 64;
   int64_t tiles = 0;
   for (int l = 1; l <= L; ++l) tiles += (int64_t)((P.d[l] + 63) / 64) * ((P.d[l - 1] + 63) / 64);
-  sa.z_listed = P.rule == CADA_RULE_CADA2 && M <= kBlock && c->s.D < kStageDelays;
-  sa.z_groups = sa.z_listed ? (int)std::min<int64_t>(P.nW, std::max<int64_t>(kStageGroups, (kStageBlocks + tiles - 1) / tiles)) : P.nW;
+  const bool z_listed = P.rule == CADA_RULE_CADA2 && M <= kBlock && c->s.D < kStageDelays;
+  sa.z_groups = z_listed ? (int)std::min<int64_t>(P.nW, std::max<int64_t>(kStageGroups, (kStageBlocks + tiles - 1) / tiles)) : P.nW;
   sa.n_layers = L; sa.nz = idx && !plain_rule(P) ? sa.z_groups + 1 : 1; sa.wt_total = P.wt_total; sa.wn_total = P.wn_total; sa.rep = P.rule == CADA_RULE_CADA2 ? P.rep : nullptr;
   uint64_t nblk = idx ? (uint64_t)sa.gx * sa.gy * M : 0;
   sa.first[0] = 0;
@@ -1970,7 +1972,9 @@ static void stage(Ctx *c, const MlpPlan &P, const DevState &s, const int32_t *id
   for (int l = L + 1; l < CADA_MAX_LAYERS + 2; ++l) sa.first[l] = (uint32_t)nblk;
   sa.rule_block = idx ? 1 : 0;
   sa.rule_in = c->rule_in;
-  hipLaunchKernelGGL(k_stage, dim3((unsigned)(nblk + sa.rule_block)), dim3(kBlock), 0, c->stream, sa);
+  const dim3 grid((unsigned)(nblk + sa.rule_block));
+  if (z_listed && idx) hipLaunchKernelGGL(k_stage<true>, grid, dim3(kBlock), 0, c->stream, sa);
+  else hipLaunchKernelGGL(k_stage<false>, grid, dim3(kBlock), 0, c->stream, sa);
 }
 
 void mlp_stage_weights(Ctx *c) { stage(c, *static_cast<MlpPlan *>(c->mlp), c->s, nullptr); }
