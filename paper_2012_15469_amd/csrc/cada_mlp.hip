@@ -1075,7 +1075,7 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
   } else {
   // Step kc's block of a tensor is 2 KB of consecutive memory: moved straight to LDS, 1 KB per instruction, its 16-byte pieces in the order of lds_piece.  (Fragments
   // read from memory are 16 bytes of a row each, 64 bytes apart: a wave-load of them took the CU's address unit some 70 cycles, 16300 for the four steps of a wavefront's
-  // 784 inputs.  Launches, us: 784-500-10 with 10 workers of 12 rows: hidden layer 10.9, now 8.9, loss 10.8, now 9.1; 617-301-150-26, always, 24 workers of 100: 11.4, now 9.2;
+  // 784 inputs.  Launches, us: 784-500-10 with 10 workers of 12 rows: hidden layer 10.9, now 9.1, loss 10.8, now 9.0; 617-301-150-26, always, 24 workers of 100: 11.4, now 9.2;
   // loss of 3072-1024-1024-10 with 16 workers of 256: 19.6, now 16.2.)
   const int64_t offa = (((int64_t)(m0 >> 7) * g.A.kt[0]) << 12) + ((m0 & 127) << 5), offb = (((int64_t)(cb >> 2) * g.B.kt[0]) << 12) + ((cb & 3) << 10);
   // (scalar loads: a wait for a vector load's value would be one for all operands in flight)
