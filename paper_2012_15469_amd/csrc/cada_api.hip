@@ -201,7 +201,10 @@ void carve_logreg_scratch(Carver &w, const cada_config *cfg, Ctx *c) {
   float *rows_part = w.take<float>(rows_part_floats(cfg));
   uint32_t *rows_count = w.take<uint32_t>(kCountWords * (1 + (size_t)cfg->M));      // (zero between launches)
   char *rule_room = w.take<char>(rule_in_bytes(cfg->M));
+  const size_t steps = steps_rows_floats(cfg);
+  float *steps_rows = w.take<float>(steps);
   if (!c) return;
+  c->steps_rows = steps ? steps_rows : nullptr;
   c->rule_room = rule_room;
   c->rows_part = rows_part;
   c->rows_count = rows_count;
@@ -454,6 +457,7 @@ int cada_init(const cada_config *cfg, const float *theta0, cada_ctx **out) {
     int rc = logreg_init(c);
     if (rc == CADA_OK) rc = eval_scratch_init();
     if (rc == CADA_OK) rc = small_publish_args(c);
+    if (rc == CADA_OK) rc = steps_clear(c);
     if (rc != CADA_OK) { small_free(c); delete h; return rc; }
   }
   *out = h;
@@ -574,6 +578,7 @@ int cada_set_state(cada_ctx *ctx, const cada_state_in *in) {
   hipLaunchKernelGGL(k_set_rows, dim3(std::min(pb, 1024u), (unsigned)s.M), dim3(kBlock), 0, c->stream, a);
   hipLaunchKernelGGL(k_set_small, dim3(1), dim3(kBlock), 0, c->stream, a, c->ring_cap);
   HIP_TRY(hipGetLastError());
+  if (const int rc = steps_clear(c)) return rc;
   c->k = in->k;
   c->force_resum = 1;       // (the aggregate of the step before is not part of the state handed over)
   return CADA_OK;
@@ -649,7 +654,8 @@ int cada_checkpoint_load(cada_ctx *ctx, const void *src) {
   c->small_seq = h.small_seq;
   c->force_resum = h.force_resum;
   // (the image holds the saving context's launch arguments, which point into its workspace)
-  const int rc = small_publish_args(c);
+  int rc = small_publish_args(c);
+  if (rc == CADA_OK) rc = steps_clear(c);
   if (rc != CADA_OK) return rc;
   HIP_TRY(hipStreamSynchronize(c->stream));
   return CADA_OK;

@@ -279,6 +279,7 @@ __device__ __forceinline__ float server_coordinate(const DevState &s, float alph
 
 constexpr int kCountWords = 32;      // a counter that workgroups count in has a 128-byte line of its own
 
+struct SmallArgs; struct SmallVar; struct Phase; struct SmallLaunch;      // cada_small.h
 // Host context.
 struct Ctx {
   DevState s;
@@ -310,11 +311,16 @@ struct Ctx {
   int small_plain_launch;    // launch it as an ordinary grid (profilers that cannot trace cooperative dispatches)
   uint32_t *small_bar;       // the whole-step kernel's barrier words in the workspace
   uint32_t small_seq;        // its value after everything enqueued so far
+  void (*small_one)(const SmallArgs, const SmallVar, const Phase);      // its kernels: of a single step, of launches of several (cada_logreg_small.hip or cada_logreg_steps.hip)
+  void (*small_several)(const SmallLaunch);
+  float *steps_rows;         // the gradients that the workgroups of cada_logreg_steps.hip pass on (scratch; null: its kernels do not serve the shape)
+  int32_t steps_turn;        // turn of the next step of a launch of several
   void *small_args;          // room in the workspace for this context's launch-invariant arguments (launches of several steps)
   void *small_args_host;     // their host copy (owned by the context)
   // one or two launches per step for rows of up to 8192 columns, cada_logreg_rows.hip
   int rows, rows_shares, rows_per_share, rows_per_worker, rows_tail;      // (rows: 1, or 2 for more than 8192 columns, whose shares are WideSplit's)
   size_t rows_lds;
+  void (*rows_one)(const SmallArgs, const SmallVar, const Phase);      // small states: the whole step in the single-step kernel of cada_logreg_steps.hip (null: not this shape)
   float *rows_part;          // sums of the shares of a worker's rows
   uint32_t *rows_count;      // [1 + M] counters, kCountWords apart
   char *rule_room;           // rule_in_bytes
@@ -348,6 +354,8 @@ int small_steps_replicas(Ctx *const *cs, int n, const int32_t *const *idx, const
 constexpr size_t kSmallArgsBytes = 1024;    // >= sizeof(SmallArgs), checked where it is defined
 bool small_plan(Ctx *c, const cada_config *cfg);
 int small_publish_args(Ctx *c);             // after the state pointers are final, and after a checkpoint was loaded
+int steps_clear(Ctx *c);                    // at init, and where the state is replaced: whatever ended before that, the steps to come start clean
+size_t steps_rows_floats(const cada_config *cfg);
 void small_free(Ctx *c);
 int logreg_init(Ctx *c);                    // LDS allowance of the two-pass kernels
 constexpr int kFusedWaves = 8;                      // streaming wavefronts of a single-pass workgroup: one partial sum of the left-hand side each

@@ -1,6 +1,7 @@
 // Dual minibatch gradient, rule and (small states) server update of the logistic model for rows that one workgroup can
 // hold in its registers (p <= 8192), and the rows cross the memory bus once.  A step is
-//   ONE launch where the state is small (kServerColumns, kServerState, kServerWorkers): its last workgroup runs rule and server;
+//   ONE launch where the state is small (kServerColumns, kServerState, kServerWorkers): its last workgroup runs rule and server (minibatches that a workgroup's registers hold
+//   take the single-step kernel of cada_logreg_steps.hip for it);
 //   two, up to kRuleInServer workers: the server's launch runs the rule (cada_server.hip), from inputs that this one takes down;
 //   two, up to kRuleWorkers: the last workgroup runs the rule;
 //   three with more workers: the rule has a launch of its own.
@@ -22,12 +23,12 @@
 // Why: the path replaces four to five dependent launches (two passes over the rows, [left-hand side of the LAG rule],
 // rule, server), each about 5 us of fetching arguments, code and first operands for well under 1 us of work.
 // Measured per step, against those launches: M = 10, p = 784, B = 60: 23.8 -> 16.2 us (15.5 in the kernel: operands and indices 3.3,
-// rows 2.9, share's sums 2.6, gradient 1.5, count 0.7, rule 1.0, aggregate 2.1, update 1.3); M = 10, p = 22, B = 92, LAG:
-// 23.8 -> 13.2 us; M = 100, B = 256, p = 4000 (410 MB of rows): 147 -> 87 us; p = 8192: 308 -> 164 us (5.1 TB/s).
+// rows 2.9, share's sums 2.6, gradient 1.5, count 0.7, rule 1.0, aggregate 2.1, update 1.3; in cada_logreg_steps.hip 14.6); M = 100, B = 256, p = 4000 (410 MB of rows): 147 -> 87 us; p = 8192: 308 -> 164 us (5.1 TB/s).
 #include <type_traits>
 
 #include "cada_rows_split.h"
 #include "cada_rule.h"
+#include "cada_small.h"
 
 namespace cada {
 
@@ -744,6 +745,11 @@ bool rows_plan(Ctx *c, const cada_config *cfg) {
       (void)hipGetLastError();
       return false;
     }
+  c->rows_one = c->rows_tail == kTailServer ? steps_one_kernel(cfg->p, cfg->B) : nullptr;
+  if (c->rows_one && hipFuncSetAttribute(reinterpret_cast<const void *>(c->rows_one), hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024) != hipSuccess) {
+    (void)hipGetLastError();
+    c->rows_one = nullptr;
+  }
   c->rows = wide ? 2 : 1;
   c->s.n_lhs_part = wide ? (int)((cfg->p + 1023) / 1024) : 2;
   c->n_phases = 0;
@@ -769,6 +775,15 @@ int logreg_step_rows(Ctx *c, const int32_t *idx, const uint8_t *replay) {
   a.wide = WideSplit{c->s.M, c->s.B, c->rows_shares, c->rows_per_share, c->rows_per_worker};
   a.tail = c->rows_tail;
   prof_mark(c);
+  if (c->rows_one) {
+    hipLaunchKernelGGL(c->rows_one, dim3((unsigned)c->s.M), dim3(R_NT), steps_lds(c->s.p), c->stream, SmallArgs{a.s, c->rows_count, 0u, (int)((c->s.p + 3) / 4 * 4), 0, 0, nullptr},
+                       SmallVar{idx, replay, c->k, 0u, 0}, phase_of(c->s, c->k));
+    prof_mark(c);
+    const hipError_t e1 = hipGetLastError();
+    if (e1 != hipSuccess) { set_error("logistic step launch failed: %s", hipGetErrorString(e1)); return CADA_EHIP; }
+    c->force_resum = 0;
+    return CADA_OK;
+  }
   const dim3 grid((unsigned)a.shares, c->rows == 2 ? 1u : (unsigned)c->s.M);
   if (c->rows == 1 && c->decide) hipLaunchKernelGGL(rows_in_kernel(c->s.p), grid, dim3(R_NT), c->rows_lds, c->stream, RowsInArgs{a, c->rule_in});
   else hipLaunchKernelGGL(c->rows == 2 ? wide_kernel(c->s.p) : rows_kernel(c->s.p), grid, dim3(R_NT), c->rows_lds, c->stream, a);

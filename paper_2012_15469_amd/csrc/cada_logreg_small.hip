@@ -1,4 +1,5 @@
-// Whole iterations of Algorithm 1 in one kernel launch, for logistic workloads so small that a
+// Whole iterations of Algorithm 1 in one kernel launch, with the rows in LDS: for minibatches that the registers of cada_logreg_steps.hip do not hold (more than 1024 columns or fewer than 4,
+// more than 64 rows, or 32 of more than 512 columns); the host side serves both.  Logistic workloads so small that a
 // step is bound by launch and dependency latency rather than by memory (tens of workers, a few
 // hundred coordinates): four dependent launches per step cost 20-40 us, the arithmetic well
 // under one.  One workgroup per worker:
@@ -39,62 +40,17 @@
 //     the right-hand side is formed by a wavefront under the products, the next step's rows are asked for while the
 //     others arrive (LDS-direct loads into buffers that are free by then);
 //   - four workgroup barriers per step, which wait for LDS only; the wait for the gradient's stores is the one exception.
-// Measured (before: 256 threads, whole-cache release and acquire per step, a cooperative launch for a single step too):
-// one step per call, M = 10, B = 10, p = 54: 34.6 -> 11.5 us (of 8.8 us in the kernel: indices 1.6, rows and vectors 1.1,
-// products 1.0, gradient 1.4, count 1.1, rows of the aggregate 1.5, update 0.9; the phases' code comes from memory each
-// time); twenty steps per call, M = 20, B = 32, p = 784 (CADA1): 18.2 -> 11.9 us per step; ten runs of the first
-// workload side by side: 12.1 -> 7.2 us per step.
+// Measured: twenty steps per call, M = 8, B = 5, p = 2500 (CADA1): 10.9 us per step.  (Shapes that cada_logreg_steps.hip serves now took here: one step per call, M = 10, B = 10, p = 54: 11.2 us; twenty
+// steps per call, M = 20, B = 32, p = 784 (CADA1): 11.4 us per step; ten runs of the first side by side: 7.0.)
 #include <cstring>
 #include <new>
 #include <type_traits>
 
-#include "cada_internal.h"
+#include "cada_small.h"
 
 namespace cada {
 
 constexpr int S_NT = 512, S_NW = S_NT / kWave;      // threads and wavefronts of a workgroup
-
-// What does not change from launch to launch; kept in the context's workspace for the launches of several steps.
-struct SmallArgs {
-  DevState s;
-  uint32_t *bar;             // [64]: counter of a single-step launch (first 8 bytes); then [2][M] words {tag, selector} of the last two steps
-  uint32_t spin_limit;
-  int ps;                    // floats from one row to the next in LDS: p rounded up to a multiple of 4
-  int groups;                // row groups of the gradient pass (1, 2, 4, 8), each of all columns
-  int dts;                   // the worker's stored innovation (CADA1) or gradient (LAG, always) is kept in LDS
-};
-static_assert(sizeof(SmallArgs) <= kSmallArgsBytes && sizeof(SmallArgs) % 8 == 0, "room kept in the workspace");
-
-// What does: schedules, iteration, tag of the first step.
-struct SmallVar {
-  const int32_t *idx;        // [n_steps][M][B]
-  const uint8_t *replay;     // [n_steps][M] or nullptr
-  int64_t k;
-  uint32_t bar_base;         // sequence number of this launch's first step (monotone over the life of the context)
-};
-// An iteration k where a launch of several steps needs it modulo something: k mod (D + 1) (slot of the iterate history), k mod D (CADA1's snapshots), k mod d_max (ring of
-// squared steps).  The host forms the first step's, the others follow: the modulo of a 64-bit k is some 130 instructions in the chain of every step.  Ten runs of 20 steps,
-// M = 10, B = 10, p = 54, side by side: 141.8 -> 139.8 us, 20 steps, M = 20, B = 32, p = 784: 234.6 -> 229.5.  (A single step forms them itself: as arguments they cost it 1 %.)
-struct Phase { int32_t R, D, d; };
-static Phase phase_of(const DevState &s, int64_t k) { return Phase{(int32_t)(k % s.R), (int32_t)(k % s.D), (int32_t)(k % s.d_max)}; }
-__device__ __forceinline__ Phase phase_after(const DevState &s, Phase ph) {
-  return Phase{ph.R + 1 == s.R ? 0 : ph.R + 1, ph.D + 1 == s.D ? 0 : ph.D + 1, ph.d + 1 == s.d_max ? 0 : ph.d + 1};
-}
-__device__ __forceinline__ RefPtr theta_ref_in(const DevState &s, int32_t tau_m, const Phase &ph) {       // theta_ref_at of an iteration in that phase
-  if (s.rule == CADA_RULE_CADA1) return RefPtr{s.snap, s.snap_lo};
-  if (s.rule != CADA_RULE_CADA2) return RefPtr{s.theta, s.theta_lo};
-  int32_t slot = ph.R - min(tau_m, s.D);
-  if (slot < 0) slot += s.R;
-  return RefPtr{s.hist + (int64_t)slot * s.ps, s.hist_lo + (int64_t)slot * s.ps};
-}
-// Several independent runs (blockIdx.y picks the run) or one.
-struct SmallLaunch {
-  const SmallArgs *rep[CADA_MAX_REPLICAS];
-  SmallVar var[CADA_MAX_REPLICAS];
-  Phase ph[CADA_MAX_REPLICAS];         // of the first step
-  int64_t n_steps;
-};
-static_assert(sizeof(SmallLaunch) <= 4096, "kernel arguments");
 
 __device__ __forceinline__ float sigmoid_s(float a) { return 1.0f / (1.0f + expf(-a)); }
 
@@ -532,7 +488,7 @@ __global__ __launch_bounds__(S_NT) void k_small(const SmallLaunch launch) {
 }
 
 // grid M
-__global__ __launch_bounds__(S_NT) void k_small_one(const SmallArgs a, const SmallVar v) { small_body<true>(a, reinterpret_cast<const uint32_t *>(&a.s), v, Phase{0, 0, 0}, 1); }
+__global__ __launch_bounds__(S_NT) void k_small_one(const SmallArgs a, const SmallVar v, const Phase) { small_body<true>(a, reinterpret_cast<const uint32_t *>(&a.s), v, Phase{0, 0, 0}, 1); }
 
 // Whether the multi-step kernel serves this configuration.
 bool small_plan(Ctx *c, const cada_config *cfg) {
@@ -540,7 +496,7 @@ bool small_plan(Ctx *c, const cada_config *cfg) {
   const int64_t p = cfg->p;
   const int B = cfg->B, M = cfg->M;
   if (p >= 8192) return false;
-  // Measured against the rows path (cada_logreg_rows.hip), us per step of a 16-step run here / of a single step here / there: M = 10, B = 10,
+  // Measured with the rows in LDS against the rows path (cada_logreg_rows.hip), us per step of a 16-step run here / of a single step here / there: M = 10, B = 10,
   // p = 54: 7 / 11.5 / 13; M = 20, B = 32, p = 784: 12 / 17 / 15; M = 64: 15 / 20 / 17; but M = 128: 21 / 26 / 19, M = 200 tiny workers 19 / 23 / 22 (the
   // server phase and the barrier grow with the workers), B = 100 rows of p = 54: 12 / 17 / 13, B = 300: 24 / 28 / 17 (one CU
   // has all rows of a worker): the path is taken by itself up to 64 workers of up to 64 rows.
@@ -561,7 +517,11 @@ bool small_plan(Ctx *c, const cada_config *cfg) {
   while (c->small_groups > 1 && (ps / 4 * c->small_groups > S_NT || (B + c->small_groups - 1) / c->small_groups < 8 ||
                                  small_floats(ps, B, cfg->rule, c->small_groups, c->small_dts) * sizeof(float) > kRoom)) c->small_groups /= 2;
   c->small_lds = small_floats(ps, B, cfg->rule, c->small_groups, c->small_dts) * sizeof(float);
-  for (const void *fn : {reinterpret_cast<const void *>(k_small), reinterpret_cast<const void *>(k_small_one)})
+  const StepsKernels steps = steps_kernels(p, B);
+  c->small_one = k_small_one; c->small_several = k_small;
+  if (steps.one) { c->small_one = steps.one; c->small_several = steps.several; c->small_lds = steps_lds(p); }
+  else c->steps_rows = nullptr;
+  for (const void *fn : {reinterpret_cast<const void *>(c->small_several), reinterpret_cast<const void *>(c->small_one)})
     if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRoom) != hipSuccess) {
       (void)hipGetLastError();
       return false;
@@ -581,6 +541,7 @@ static SmallArgs small_args_of(Ctx *c) {
   a.ps = (int)((c->s.p + 3) / 4 * 4);
   a.groups = c->small_groups;
   a.dts = c->small_dts;
+  a.rows = c->steps_rows;
   return a;
 }
 
@@ -616,12 +577,12 @@ int small_steps_replicas(Ctx *const *cs, int n, const int32_t *const *idx, const
   l.n_steps = n_steps;
   for (int r = 0; r < n; ++r) {
     l.rep[r] = static_cast<const SmallArgs *>(cs[r]->small_args);
-    l.var[r] = SmallVar{idx[r], replay ? replay[r] : nullptr, cs[r]->k, cs[r]->small_seq};
+    l.var[r] = SmallVar{idx[r], replay ? replay[r] : nullptr, cs[r]->k, cs[r]->small_seq, cs[r]->steps_turn};
     l.ph[r] = phase_of(cs[r]->s, cs[r]->k);
   }
   void *args[] = {&l};
   prof_mark(c0);
-  const hipError_t e = hipLaunchCooperativeKernel(reinterpret_cast<const void *>(k_small), dim3((unsigned)c0->s.M, (unsigned)n), dim3(S_NT), args,
+  const hipError_t e = hipLaunchCooperativeKernel(reinterpret_cast<const void *>(c0->small_several), dim3((unsigned)c0->s.M, (unsigned)n), dim3(S_NT), args,
                                                   (unsigned)c0->small_lds, c0->stream);
   prof_mark(c0);
   if (e != hipSuccess) {
@@ -629,15 +590,18 @@ int small_steps_replicas(Ctx *const *cs, int n, const int32_t *const *idx, const
     return CADA_EHIP;
   }
   // (the barrier counters advance only with a launch that was accepted)
-  for (int r = 0; r < n; ++r) cs[r]->small_seq += (uint32_t)(n_steps * cs[r]->s.M);
+  for (int r = 0; r < n; ++r) {
+    cs[r]->small_seq += (uint32_t)(n_steps * cs[r]->s.M);
+    cs[r]->steps_turn = (int32_t)((cs[r]->steps_turn + n_steps) % kStepsTurns);
+  }
   return CADA_OK;
 }
 
 int small_steps(Ctx *c, const int32_t *idx, const uint8_t *replay, int64_t n_steps) {
   if (n_steps == 1) {
     prof_mark(c);
-    hipLaunchKernelGGL(k_small_one, dim3((unsigned)c->s.M), dim3(S_NT), c->small_lds, c->stream, small_args_of(c),
-                       SmallVar{idx, replay, c->k, 0u});
+    hipLaunchKernelGGL(c->small_one, dim3((unsigned)c->s.M), dim3(S_NT), c->small_lds, c->stream, small_args_of(c),
+                       SmallVar{idx, replay, c->k, 0u, 0}, phase_of(c->s, c->k));
     prof_mark(c);
     const hipError_t e1 = hipGetLastError();
     if (e1 != hipSuccess) { set_error("single-step logistic launch failed: %s", hipGetErrorString(e1)); return CADA_EHIP; }
@@ -646,16 +610,16 @@ int small_steps(Ctx *c, const int32_t *idx, const uint8_t *replay, int64_t n_ste
   SmallLaunch l{};
   l.n_steps = n_steps;
   l.rep[0] = static_cast<const SmallArgs *>(c->small_args);
-  l.var[0] = SmallVar{idx, replay, c->k, c->small_seq};
+  l.var[0] = SmallVar{idx, replay, c->k, c->small_seq, c->steps_turn};
   l.ph[0] = phase_of(c->s, c->k);
   void *args[] = {&l};
   prof_mark(c);
   hipError_t e;
   if (c->small_plain_launch) {      // (at most as many workgroups as CUs: all resident at once on an idle device)
-    hipLaunchKernelGGL(k_small, dim3((unsigned)c->s.M), dim3(S_NT), c->small_lds, c->stream, l);
+    hipLaunchKernelGGL(c->small_several, dim3((unsigned)c->s.M), dim3(S_NT), c->small_lds, c->stream, l);
     e = hipGetLastError();
   } else {
-    e = hipLaunchCooperativeKernel(reinterpret_cast<const void *>(k_small), dim3((unsigned)c->s.M), dim3(S_NT), args,
+    e = hipLaunchCooperativeKernel(reinterpret_cast<const void *>(c->small_several), dim3((unsigned)c->s.M), dim3(S_NT), args,
                                    (unsigned)c->small_lds, c->stream);
   }
   prof_mark(c);
@@ -664,6 +628,7 @@ int small_steps(Ctx *c, const int32_t *idx, const uint8_t *replay, int64_t n_ste
     return CADA_EHIP;
   }
   c->small_seq += (uint32_t)(n_steps * c->s.M);
+  c->steps_turn = (int32_t)((c->steps_turn + n_steps) % kStepsTurns);
   return CADA_OK;
 }
 
