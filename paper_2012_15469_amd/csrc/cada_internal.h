@@ -49,6 +49,7 @@ struct DevState {
   uint32_t *n_up;          // [2]: uploads of iteration k in slot k mod 2 (the server kernel clears the other slot)
   int32_t resum;           // this launch: form the aggregate as the plain sum over all workers (0: the kernel may
                            // take the incremental form of Section 1.2 when few workers uploaded)
+  int32_t snap_next;        // theta^{k+1} is CADA1's next snapshot
   uint32_t *err;
   // trace
   uint8_t *t_mask, *t_own;
@@ -60,6 +61,7 @@ struct DevState {
   const void *y;
   const int64_t *row_off;   // device [M+1], prefix sums of N_m
   int32_t M, B, d_max, D, R, rule, server_sgd, n_lhs_part, n_ring_part;
+  int32_t kR;               // k mod R (the modulo of a 64-bit k is some 130 instructions at the head of a launch)
   int64_t p;
   int64_t k;                // iteration of the launch this copy is passed to
   float alpha, beta1, beta2, omb1, omb2, eps, lam;   // omb = 1 - beta, rounded once from double
@@ -81,17 +83,19 @@ struct RuleInputs {
 // gradient kernels carry is exactly zero.
 struct RefPtr { const float *hi, *lo; };
 // (for a caller that already holds the worker's delay tau_m^k)
-__device__ __forceinline__ RefPtr theta_ref_at(const DevState &s, int32_t tau_m, int64_t k) {
+__device__ __forceinline__ RefPtr theta_ref_at(const DevState &s, int32_t tau_m) {
   if (s.rule == CADA_RULE_CADA1) return RefPtr{s.snap, s.snap_lo};
   if (s.rule != CADA_RULE_CADA2) return RefPtr{s.theta, s.theta_lo};
-  int64_t j = k - (int64_t)min(tau_m, s.D);      // tau <= D unless a replay kept m silent longer
-  int64_t slot = j % s.R;
+  int32_t slot = s.kR - min(tau_m, s.D);         // tau <= D unless a replay kept m silent longer
   if (slot < 0) slot += s.R;
-  return RefPtr{s.hist + slot * s.ps, s.hist_lo + slot * s.ps};
+  return RefPtr{s.hist + (int64_t)slot * s.ps, s.hist_lo + (int64_t)slot * s.ps};
 }
-__device__ __forceinline__ RefPtr theta_ref(const DevState &s, int m, int64_t k) {
-  return theta_ref_at(s, s.rule == CADA_RULE_CADA2 ? s.tau[m] : 0, k);
+__device__ __forceinline__ RefPtr theta_ref(const DevState &s, int m) {
+  return theta_ref_at(s, s.rule == CADA_RULE_CADA2 ? s.tau[m] : 0);
 }
+
+// The copy of iteration k.
+inline void set_iteration(DevState &s, int64_t k) { s.k = k; s.kR = (int32_t)(k % s.R); s.snap_next = s.rule == CADA_RULE_CADA1 && (k + 1) % s.D == 0; }
 
 // Stepsize of iteration k (constant, or the decaying 2/(mu(k+K0)) of Theorem 2).
 __host__ __device__ __forceinline__ float stepsize(const DevState &s, int64_t k) {

@@ -66,7 +66,7 @@ __global__ __launch_bounds__(kBlock) void k_dots(const LogregArgs a) {
   const int64_t k = s.k;
   const float *__restrict__ th = s.theta;
   const float *__restrict__ tl = s.theta_lo;
-  const RefPtr ref = theta_ref(s, m, k);
+  const RefPtr ref = theta_ref(s, m);
   const int32_t *idx = a.idx + (int64_t)m * s.B;
 
   const float *xrow[kRowsPerBlock];
@@ -190,7 +190,7 @@ __global__ __launch_bounds__(kBlock) void k_grad(const LogregArgs a) {
       }
     }
     float t[VEC], d[VEC], lo[VEC], rlo[VEC];
-    const RefPtr ref = theta_ref(s, m, k);
+    const RefPtr ref = theta_ref(s, m);
     load_vec<VEC>(s.theta + j, t);
     load_vec<VEC>(ref.hi + j, d);
     load_vec<VEC>(s.theta_lo + j, lo);
@@ -233,7 +233,7 @@ int logreg_init(Ctx *) {
 int logreg_gradients(Ctx *c, const int32_t *idx) {
   LogregArgs a;
   a.s = c->s;
-  a.s.k = c->k;
+  set_iteration(a.s, c->k);
   a.idx = idx;
   a.zpart = c->zpart;
   a.nc = c->n_col_chunks;

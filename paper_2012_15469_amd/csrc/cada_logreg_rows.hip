@@ -84,7 +84,7 @@ __global__ __launch_bounds__(R_NT) void k_rows(const Args a) {
   const int r0 = share * a.rows, nr = min(a.rows, s.B - r0);        // this share's rows
   const int64_t base = s.row_off[m], n_m = s.row_off[m + 1] - base;
   const int64_t mp = (int64_t)M * s.p;
-  const RefPtr ref = theta_ref(s, m, s.k);
+  const RefPtr ref = theta_ref(s, m);
   // this lane's columns: CW quads; the quad that would reach past p is moved back to end at p, `dup` of its columns belong
   // to the quad before (weight zero here, not stored from here); a quad beyond p has dup >= 4
   int jb[CW], dup[CW];
@@ -480,7 +480,7 @@ __global__ __launch_bounds__(R_NT) void k_rows_wide(const RowsArgs a) {
   // theta_lo and the reference point of a worker, all asked for before the first is used, and before the rows: behind the first batch their data wait
   // for its latency (p = 18000, M = 16, B = 64: 40.0 us for 39.2, and no better with half of them in front)
   auto ask_operands = [&](int32_t tau) __attribute__((always_inline)) {
-    const RefPtr ref = theta_ref_at(s, tau, s.k);
+    const RefPtr ref = theta_ref_at(s, tau);
     const uint32_t j = here();
 #pragma unroll
     for (int i = 0; i < CW; ++i) { lo[i] = quad(vec(s.theta_lo), piece(j, i)); rh[i] = quad(vec(ref.hi), piece(j, i)); rl[i] = quad(vec(ref.lo), piece(j, i)); }
@@ -630,7 +630,7 @@ __global__ __launch_bounds__(kBlock) void k_rows_sum(const RowsArgs a, const Rul
   const int j = (blockIdx.x * kBlock + threadIdx.x) * 4;
   float sq = 0.f;
   if (j < ps) {
-    const RefPtr ref = theta_ref(s, m, s.k);
+    const RefPtr ref = theta_ref(s, m);
     const int cur = s.sel[m];
     const int64_t o = (int64_t)m * s.p + j, of = (int64_t)(1 - cur) * mp + o, oc = (int64_t)cur * mp + o;
     const v4u t4 = *reinterpret_cast<const v4u *>(s.theta + j), l4 = *reinterpret_cast<const v4u *>(s.theta_lo + j);
@@ -764,7 +764,7 @@ bool rows_plan(Ctx *c, const cada_config *cfg) {
 int logreg_step_rows(Ctx *c, const int32_t *idx, const uint8_t *replay) {
   RowsArgs a;
   a.s = c->s;
-  a.s.k = c->k;
+  set_iteration(a.s, c->k);
   a.s.alpha = stepsize(a.s, c->k);
   a.idx = idx;
   a.replay = replay;

@@ -129,7 +129,7 @@ __device__ __forceinline__ void small_body(const SmallArgs &a, const uint32_t *s
       if (b0 + lane < B) lds_direct<4>(static_cast<const float *>(s.y) + base + row_n[b0 + lane], r_s + b0);
   };
   // Everything the start needs is asked for before anything is waited for; only the rows depend on their indices.
-  const RefPtr ref = ONE ? theta_ref_at(s, tau_m, v.k) : theta_ref_in(s, tau_m, ph);
+  const RefPtr ref = theta_ref_in(s, tau_m, ph);
   const float *stored = (rule == CADA_RULE_CADA1 ? s.dtl : s.gbuf) + (int64_t)cur * mp + (int64_t)m * s.p;
   const int32_t idx0 = tid < B ? idx[tid] : 0;
   const uint32_t state0 = tid < (int)(sizeof(DevState) / 4) ? state[tid] : 0u;
@@ -488,7 +488,7 @@ __global__ __launch_bounds__(S_NT) void k_small(const SmallLaunch launch) {
 }
 
 // grid M
-__global__ __launch_bounds__(S_NT) void k_small_one(const SmallArgs a, const SmallVar v, const Phase) { small_body<true>(a, reinterpret_cast<const uint32_t *>(&a.s), v, Phase{0, 0, 0}, 1); }
+__global__ __launch_bounds__(S_NT) void k_small_one(const SmallArgs a, const SmallVar v, const Phase ph) { small_body<true>(a, reinterpret_cast<const uint32_t *>(&a.s), v, ph, 1); }
 
 // Whether the multi-step kernel serves this configuration.
 bool small_plan(Ctx *c, const cada_config *cfg) {

@@ -318,7 +318,7 @@ __global__ __launch_bounds__(2 * kBlock, 1) void k_mm5(const Mm5Args g) {
   float bias[2] = {0.f, 0.f}, bias_lo[2] = {0.f, 0.f}, ref_hi[2] = {0.f, 0.f}, ref_lo[2] = {0.f, 0.f};
   u32x4 masks = {0u, 0u, 0u, 0u};
   if constexpr (EPI == EPI_FWD_HIDDEN) {
-    const RefPtr ref = theta_ref_at(s, s.rule == CADA_RULE_CADA2 ? scalar_load(s.tau + wk) : 0, s.k);
+    const RefPtr ref = theta_ref_at(s, s.rule == CADA_RULE_CADA2 ? scalar_load(s.tau + wk) : 0);
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       const int64_t i = g.offb + min(cbase + j * 32, g.N - 1);
@@ -1104,7 +1104,7 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
   // asked for behind the first step's operands, the row's label in its products, so that their latency passes under these.
   const int c0 = 32 * cb + 2 * (t & 15);
   {
-    const RefPtr ref = theta_ref_at(s, tau_wk, s.k);
+    const RefPtr ref = theta_ref_at(s, tau_wk);
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
       const int64_t i = g.offb + min(c0 + e, g.N - 1);           // (of an absent class: not used)
@@ -1571,7 +1571,7 @@ __device__ __forceinline__ void stage_weights(const StageArgs &a, const PrepLaye
   const int t = threadIdx.x;
   const int og = (t & 7) * 8;
   auto one = [&](const bool is_w, const int m, const int32_t tau) __attribute__((always_inline)) {
-    const RefPtr ref = theta_ref_at(s, tau, s.k);
+    const RefPtr ref = theta_ref_at(s, tau);
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
       const int r = (t >> 3) + 32 * pass, i = i0 + r, o = o0 + og;
@@ -1591,7 +1591,16 @@ __device__ __forceinline__ void stage_weights(const StageArgs &a, const PrepLaye
             v[4 * q] = x.x; v[4 * q + 1] = x.y; v[4 * q + 2] = x.z; v[4 * q + 3] = x.w;
           }
         } else {
-          for (int e = 0; e < 8 && o + e < p.dout; ++e) v[e] = is_w ? s.theta[src + e] : delta_theta(s, ref, src + e);
+          // (all asked for at once: element by element as far as the row goes, each waited for the one before, up to 8 us of a launch of 11 in 617-301-150-26)
+          float x[8], y[8] = {}, z[8] = {}, u[8] = {};
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const int64_t at = src + min(e, p.dout - 1 - o);
+            x[e] = s.theta[at];
+            if (!is_w) { y[e] = ref.hi[at]; z[e] = s.theta_lo[at]; u[e] = ref.lo[at]; }
+          }
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v[e] = o + e < p.dout ? is_w ? x[e] : (x[e] - y[e]) + (z[e] - u[e]) : 0.f;
         }
         if (p.want_n) {                             // (values past dout are zeros, like the padding they land in)
           const int64_t dn = tm(i, o, p.ktn);
@@ -1627,6 +1636,28 @@ __device__ __forceinline__ void stage_weights(const StageArgs &a, const PrepLaye
     __shared__ int32_t tau_s[kBlock];
     __shared__ unsigned long long mine_s[kBlock / kWave];
     if (z == 0) { one(true, 0, 0); return; }
+    if (s.M <= kWave) {
+      // up to 64 workers: every wavefront makes the list for itself, a ballot per distinct delay (with the table below, which takes six barriers: 784-500-10, 10 workers of 12
+      // rows: 2 us more)
+      const int lane = t & 63;
+      const int32_t mine_tau = lane < s.M ? min(max(s.tau[lane], 0), s.D) : -1;
+      unsigned long long left = s.M == kWave ? ~0ull : (1ull << s.M) - 1, mine = 0;
+      int r = lane;
+      for (int turn = 0; left; turn = turn + 1 == a.z_groups ? 0 : turn + 1) {
+        const int i = __ffsll(left) - 1;
+        const unsigned long long same = __ballot(mine_tau == __builtin_amdgcn_readlane(mine_tau, i));
+        if ((same >> lane) & 1) r = i;
+        if (turn == z - 1) mine |= 1ull << i;
+        left &= ~same;
+      }
+      if (first_tile && z == 1 && t < s.M) a.rep[t] = r;
+      for (; mine; mine &= mine - 1) {
+        const int m = __ffsll(mine) - 1;
+        one(false, m, __builtin_amdgcn_readlane(mine_tau, m));
+        lds_sync();                                     // (the tile's room is written again)
+      }
+      return;
+    }
     int32_t *first_of = reinterpret_cast<int32_t *>(sm);
     const int32_t tau = t < s.M ? min(max(s.tau[t], 0), s.D) : 0;
     for (int j = t; j <= s.D; j += kBlock) first_of[j] = kBlock;
@@ -2046,7 +2077,7 @@ static void signals_below(Mm5Args &g, const MlpPlan &P, int q, bool plain) {
 int mlp_gradients(Ctx *c, const int32_t *idx) {
   MlpPlan &P = *static_cast<MlpPlan *>(c->mlp);
   DevState s = c->s;
-  s.k = c->k;
+  set_iteration(s, c->k);
   hipStream_t st = c->stream;
   const int L = P.L, M = P.M, B = P.B, Bp = P.Bp;
   const bool per_worker = (P.rule == CADA_RULE_CADA2), plain = plain_rule(P);

@@ -514,7 +514,7 @@ int mlp_eval(Ctx *c, double *out) {
   const EvalPlan p = eval_plan(P);
   EvalArgs a;
   a.s = c->s;
-  a.s.k = c->k;
+  set_iteration(a.s, c->k);
   a.Xh = P.Xh; a.Xl = P.Xl; a.ldx = P.ldx; a.rows = P.total_rows;
   a.zeros = P.XGh + tm(0, P.ldx, P.kta[0]);      // (columns from ldx on; not read where a row fills its chunks)
   a.L = P.L; a.C = P.d[P.L];

@@ -207,14 +207,17 @@ __global__ __launch_bounds__(kBlock, 7) void k_server(const DevState s, const Ru
           float v[8][3];
 #pragma unroll
           for (int u = 0; u < 3; ++u) {
+            if (t0 + u * kWave >= to) break;           // (uniform)
             const uint32_t at = min(t0 + u * kWave + lane, to - 1);
 #pragma unroll
             for (int q = 0; q < 8; ++q) v[q][u] = (s.lhs_part + (int64_t)min(m0 + q, M - 1) * n)[at];
           }
 #pragma unroll
-          for (int u = 0; u < 3; ++u)
+          for (int u = 0; u < 3; ++u) {
+            if (t0 + u * kWave >= to) break;
 #pragma unroll
             for (int q = 0; q < 8; ++q) l[q] += t0 + u * kWave + lane < to ? (double)v[q][u] : 0.0;
+          }
         }
         const double sum = eight_sums_f64(l, lane);
         const int m = m0 + (lane & 3) + 4 * (lane >> 5);
@@ -338,10 +341,10 @@ __global__ __launch_bounds__(kBlock, 7) void k_server(const DevState s, const Ru
     if (j < s.p) {
       s.nabla[j] = mean; s.h[j] = hh; s.v[j] = vv; s.vhat[j] = vh; s.theta[j] = th; s.theta_lo[j] = tl;
       if (s.rule == CADA_RULE_CADA2) {
-        const int64_t o = ((s.k + 1) % s.R) * s.ps + j;
+        const int64_t o = (int64_t)(s.kR + 1 == s.R ? 0 : s.kR + 1) * s.ps + j;
         s.hist[o] = th;
         s.hist_lo[o] = tl;
-      } else if (s.rule == CADA_RULE_CADA1 && (s.k + 1) % s.D == 0) {
+      } else if (s.snap_next) {
         s.snap[j] = th;
         s.snap_lo[j] = tl;
       }
@@ -375,7 +378,7 @@ void decide_plan(Ctx *c, char *room) {
 namespace {
 int launch_server(Ctx *c, bool decide, const uint8_t *replay) {
   DevState s = c->s;
-  s.k = c->k;
+  set_iteration(s, c->k);
   s.alpha = stepsize(s, s.k);
   s.resum = (c->force_resum || s.k % s.D == 0) ? 1 : 0;
   const dim3 grid(decide ? min(s.n_ring_part, kDecideBlocks) : s.n_ring_part);
@@ -399,7 +402,7 @@ int server_step(Ctx *c) { return launch_server(c, false, nullptr); }
 int rule_then_server(Ctx *c, const uint8_t *replay) {
   if (c->decide) return launch_server(c, true, replay);
   DevState s = c->s;
-  s.k = c->k;
+  set_iteration(s, c->k);
   hipLaunchKernelGGL(k_rule, dim3((unsigned)((s.M + 3) / 4)), dim3(kBlock), 0, c->stream, s, c->rule_in, replay);
   prof_mark(c);
   const hipError_t e = hipGetLastError();
@@ -412,7 +415,7 @@ int rule_then_server(Ctx *c, const uint8_t *replay) {
 
 int rule_and_server(Ctx *c, const uint8_t *replay) {
   DevState s = c->s;
-  s.k = c->k;
+  set_iteration(s, c->k);
   if (s.rule == CADA_RULE_LAG || s.rule == CADA_RULE_ALWAYS) {   // (the always-upload rule only records it)
     const int nb = min(max(s.n_lhs_part / 2, 1), lag_blocks(s.p));      // (two parts each; the logistic model: one, of at most 1024 coordinates, or room for two for every 4096)
     hipLaunchKernelGGL(k_lag_lhs, dim3((unsigned)nb, (unsigned)s.M), dim3(kBlock), 0, c->stream, s);
@@ -422,7 +425,7 @@ int rule_and_server(Ctx *c, const uint8_t *replay) {
 
 int ring_finalize(Ctx *c) {
   DevState s = c->s;
-  s.k = c->k;
+  set_iteration(s, c->k);
   hipLaunchKernelGGL(k_ring_finalize, dim3(1), dim3(kBlock), 0, c->stream, s);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
