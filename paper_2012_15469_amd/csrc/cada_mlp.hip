@@ -557,6 +557,7 @@ __device__ __forceinline__ void weight_gradient(const Mm5Args &g, int at, unsign
   constexpr bool PL = NB == 2;
   static_assert(NS >= 4 && NSLOT >= 2 * NS + 4, "");
   const DevState &s = g.s;
+  // (one stride and one number of chunks for all tensors of a side: tiles_fit)
   const int lane0 = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), wy = w >> 1, wx = w & 1;
   // tiles of this workgroup: as in k_mm5
   const int gx = g.gx.d, gy = g.gy.d;
@@ -573,9 +574,9 @@ __device__ __forceinline__ void weight_gradient(const Mm5Args &g, int at, unsign
   auto set_tile = [&]() __attribute__((always_inline)) {
     const int trow = quotient(i_tix, g.gx), bx = i_tix - trow * gx, bz = quotient(trow, g.gy), by = trow - bz * gy;
 #pragma unroll
-    for (int q = 0; q < NA; ++q) src[q] = g.A.ptr[q] + (int64_t)bz * g.A.bstride[q] + ((int64_t)(4 * by + w) << 12);
+    for (int q = 0; q < NA; ++q) src[q] = g.A.ptr[q] + (int64_t)bz * g.A.bstride[0] + ((int64_t)(4 * by + w) << 12);
 #pragma unroll
-    for (int q = 0; q < NB; ++q) src[NA + q] = g.B.ptr[q] + (int64_t)bz * g.B.bstride[q] + ((int64_t)(4 * bx + w) << 12);
+    for (int q = 0; q < NB; ++q) src[NA + q] = g.B.ptr[q] + (int64_t)bz * g.B.bstride[0] + ((int64_t)(4 * bx + w) << 12);
   };
   auto next_step = [&]() __attribute__((always_inline)) {
     ++i_step;
@@ -838,6 +839,11 @@ __device__ __forceinline__ void weight_gradient(const Mm5Args &g, int at, unsign
 template <int NA, int NB, bool HAS_D, bool CADA1>
 __global__ __launch_bounds__(kBlock, 2) void k_dw(const Mm5Args g) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
+  // The arguments of the head and of the way out in one round trip, as in k_skinny.  (784-512-10, 64 workers of 128 rows, with the last layer's launch and the server's: 159.7 -> 157.0 us per step, 784-500-10, 10 of
+  // 12: 52.3 -> 51.1.  In k_dw_two and k_mm5 it costs scalar registers that the loop wants: 3072-1024-1024-10: 592.7 -> 594.5, 784-500-500-10, 10 of 12: 104.3 -> 105.3.)
+  asm volatile("" ::"s"(g.A.ptr[0]), "s"(g.A.ptr[1]), "s"(g.A.ptr[NA - 1]), "s"(g.B.ptr[0]), "s"(g.B.ptr[1]), "s"(g.B.ptr[NB - 2]), "s"(g.B.ptr[NB - 1]), "s"(g.A.kt[0]), "s"(g.B.kt[0]),
+               "s"(g.A.bstride[0]), "s"(g.B.bstride[0]), "s"(g.gx.d), "s"(g.gx.m), "s"(g.gx.shift), "s"(g.gy.d), "s"(g.gy.m), "s"(g.gy.shift), "s"(g.nbx.d), "s"(g.nbx.m), "s"(g.nbx.shift),
+               "s"(g.workers), "s"(g.K), "s"(g.M), "s"(g.N), "s"(g.bias_here), "s"(g.s.gbuf), "s"(g.s.gbuf16), "s"(g.s.sel), "s"(g.s.M));
   weight_gradient<NA, NB, HAS_D, CADA1>(g, blockIdx.x >> 3, smem_raw);
 }
 // The second layer's and the first layer's in one launch (the same number of workgroups per XCD for both; the first layer's tiles are dealt from the other end, so that where
@@ -926,6 +932,16 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
       old_iv[i] = ivs[(int64_t)min(m0 + 8 * (r >> 2) + 4 * (ln >> 5) + (r & 3), g.M - 1) * g.N + min(ln & 31, g.N - 1)];
     }
   };
+  if constexpr (EPI != EPI_DW) {
+    // The arguments that the head needs, in one round trip (left to itself the compiled kernel asks for each where it is used: seven of 0.2 us in a row before the last operands are on their way).
+    asm volatile("" ::"s"(g.A.ptr[0]), "s"(g.A.ptr[1]), "s"(g.A.ptr[NA - 2]), "s"(g.A.ptr[NA - 1]), "s"(g.B.ptr[0]), "s"(g.B.ptr[1]), "s"(g.B.ptr[NB - 1]), "s"(g.A.kt[0]), "s"(g.B.kt[0]),
+                 "s"(g.A.bstride[0]), "s"(g.B.bstride[NB - 1]), "s"(g.rep), "s"(s.tau), "s"(s.rule), "s"(g.K), "s"(g.M), "s"(g.N), "s"(g.offb), "s"(s.theta), "s"(s.theta_lo), "s"(s.hist), "s"(s.hist_lo),
+                 "s"(s.kR), "s"(s.D), "s"(s.R), "s"(s.ps), "s"(EPI == EPI_LOSS ? g.grow : nullptr), "s"(g.Bp));
+  } else {
+    asm volatile("" ::"s"(g.A.ptr[0]), "s"(g.A.ptr[1]), "s"(g.A.ptr[NA - 1]), "s"(g.B.ptr[0]), "s"(g.B.ptr[1]), "s"(g.B.ptr[NB - 2]), "s"(g.B.ptr[NB - 1]), "s"(g.A.kt[0]), "s"(g.B.kt[0]),
+                 "s"(g.A.bstride[0]), "s"(g.B.bstride[0]), "s"(g.rep), "s"(s.rule), "s"(g.K), "s"(g.M), "s"(g.N), "s"(g.step_waves), "s"(g.lastb), "s"(g.w_h), "s"(g.w_l), "s"(g.w_d), "s"(g.w_kt),
+                 "s"(g.w_dstride), "s"(g.maskbits), "s"(s.sel), "s"(s.M), "s"(s.dtl16), "s"(s.ps16));
+  }
   const bf16_t *pa[NA], *pb[NB];
   f32x16 acc1, acc2;
 #pragma unroll
@@ -936,9 +952,9 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
     // units m0 .. m0 + 31 of the A tensors are chunk m0 / 32 of every row tile, the (at most 32) output
     // columns chunk 0 of the B tensors; step kc covers the worker's rows 32 kc .. 32 kc + 31
 #pragma unroll
-    for (int sl = 0; sl < NA; ++sl) pa[sl] = g.A.ptr[sl] + (int64_t)wk * g.A.bstride[sl] + ((int64_t)(m0 >> 5) << 12);
+    for (int sl = 0; sl < NA; ++sl) pa[sl] = g.A.ptr[sl] + (int64_t)wk * g.A.bstride[0] + ((int64_t)(m0 >> 5) << 12);
 #pragma unroll
-    for (int sl = 0; sl < NB; ++sl) pb[sl] = g.B.ptr[sl] + (int64_t)wk * g.B.bstride[sl];
+    for (int sl = 0; sl < NB; ++sl) pb[sl] = g.B.ptr[sl] + (int64_t)wk * g.B.bstride[0];
     bf16_t *area = reinterpret_cast<bf16_t *>(smem_raw) + w * (7 * 1024);       // room for seven blocks per wavefront
     if (cada1) ask_old(t);                      // (used after the products)
     u32x4 wh[2], wl[2], wd[2];                  // (activation gradient: 32 units x 32 classes of W, a unit per lane)
@@ -978,8 +994,8 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
       u32x4 v[NA + NB][2];
 #pragma unroll
       for (int sl = 0; sl < NA + NB; ++sl) {
-        const bf16_t *src = (sl < NA ? pa[sl < NA ? sl : 0] + (((int64_t)(kc >> 2) * g.A.kt[sl < NA ? sl : 0]) << 12)
-                                     : pb[sl < NA ? 0 : sl - NA] + (((int64_t)(kc >> 2) * g.B.kt[sl < NA ? 0 : sl - NA]) << 12)) + ((kc & 3) << 10);
+        const bf16_t *src = (sl < NA ? pa[sl < NA ? sl : 0] + (((int64_t)(kc >> 2) * g.A.kt[0]) << 12)
+                                     : pb[sl < NA ? 0 : sl - NA] + (((int64_t)(kc >> 2) * g.B.kt[0]) << 12)) + ((kc & 3) << 10);
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh) v[sl][hh] = *reinterpret_cast<const u32x4 *>(src + (hh * 64 + lane) * 8);
       }
@@ -1079,11 +1095,12 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
   // loss of 3072-1024-1024-10 with 16 workers of 256: 19.6, now 16.2.)
   const int64_t offa = (((int64_t)(m0 >> 7) * g.A.kt[0]) << 12) + ((m0 & 127) << 5), offb = (((int64_t)(cb >> 2) * g.B.kt[0]) << 12) + ((cb & 3) << 10);
   // (scalar loads: a wait for a vector load's value would be one for all operands in flight)
-  const int rep_wk = g.rep ? scalar_load(g.rep + wk) : wk, tau_wk = s.rule == CADA_RULE_CADA2 ? scalar_load(s.tau + wk) : 0;
+  // (and without a branch around them: one round trip for both, where a branch each waited for the arguments that it looks at, then for its value)
+  const int32_t rep_there = scalar_load((g.rep ? g.rep : s.tau) + wk), tau_there = scalar_load(s.tau + wk);
   int64_t grow = 0;
   if constexpr (EPI == EPI_LOSS) grow = g.grow[(int64_t)wk * g.Bp + min(m0 + (t >> 4), g.M - 1)];
 #pragma unroll
-  for (int sl = 0; sl < NA; ++sl) pa[sl] = g.A.ptr[sl] + (int64_t)wk * g.A.bstride[sl] + offa;
+  for (int sl = 0; sl < NA; ++sl) pa[sl] = g.A.ptr[sl] + (int64_t)wk * g.A.bstride[0] + offa;      // (one stride for all of A, none for W: launch_mm5)
   const uint32_t area = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem_raw + w * AREA;
   const uint32_t from[2] = {(uint32_t)lds_piece(lane) * 16u, (uint32_t)lds_piece(64 + lane) * 16u};
   auto move = [&](const bf16_t *p, int kc, int sl) __attribute__((always_inline)) {
@@ -1094,8 +1111,9 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
 #pragma unroll
     for (int sl = 0; sl < NA; ++sl) move(pa[sl], w, sl);
   }
+  const int rep_wk = g.rep ? rep_there : wk, tau_wk = s.rule == CADA_RULE_CADA2 ? tau_there : 0;
 #pragma unroll
-  for (int sl = 0; sl < NB; ++sl) pb[sl] = g.B.ptr[sl] + (int64_t)rep_wk * g.B.bstride[sl] + offb;
+  for (int sl = 0; sl < NB; ++sl) pb[sl] = g.B.ptr[sl] + (!PL && sl == NB - 1 ? (int64_t)rep_wk * g.B.bstride[sl] : 0) + offb;
   if (w < nk) {
 #pragma unroll
     for (int sl = 0; sl < NB; ++sl) move(pb[sl], w, NA + sl);
@@ -1856,6 +1874,10 @@ template <int EPI> bool tiles_fit(const Mm5Args &g) {
   // 128-unit tiles and the worker's padded rows
   const int64_t needA = EPI == EPI_DW ? 4 * ((g.M + BM - 1) / BM) : (g.K + BK - 1) / BK;
   const int64_t needB = EPI == EPI_DW ? 4 * ((g.N + BN - 1) / BN) : (g.K + BK - 1) / BK;
+  for (int i = 1; i < g.A.n; ++i)
+    if (g.A.kt[i] != g.A.kt[0] || g.A.bstride[i] != g.A.bstride[0]) { set_error("internal: A tensors with different chunk counts or strides"); return false; }
+  for (int i = 1; i < g.B.n; ++i)
+    if (EPI == EPI_DW && (g.B.kt[i] != g.B.kt[0] || g.B.bstride[i] != g.B.bstride[0])) { set_error("internal: B tensors with different chunk counts or strides"); return false; }
   for (int i = 0; i < g.A.n; ++i)
     if (g.A.kt[i] < needA) { set_error("internal: A tensor with fewer chunks than the tiles walk through"); return false; }
   for (int i = 0; i < g.B.n; ++i)
@@ -1871,7 +1893,12 @@ template <int EPI> int launch_mm5(Ctx *c, Mm5Args &g, int workers) {
   if constexpr (EPI == EPI_DW || EPI == EPI_LOSS || EPI == EPI_FWD_HIDDEN) {
     if (EPI == EPI_FWD_HIDDEN ? skinny_forward(g, workers) : g.N <= 32) {            // (at most 32 output columns: the last layer)
       for (int i = 1; i < g.A.n; ++i)
-        if (g.A.kt[i] != g.A.kt[0]) { set_error("internal: A tensors with different chunk counts"); return CADA_EUNSUPPORTED; }
+        if (g.A.kt[i] != g.A.kt[0] || g.A.bstride[i] != g.A.bstride[0]) { set_error("internal: A tensors with different chunk counts or strides"); return CADA_EUNSUPPORTED; }
+      if constexpr (EPI == EPI_DW) {
+        for (int i = 1; i < g.B.n; ++i)
+          if (g.B.kt[i] != g.B.kt[0] || g.B.bstride[i] != g.B.bstride[0]) { set_error("internal: B tensors with different chunk counts or strides"); return CADA_EUNSUPPORTED; }
+      } else
+        if (g.B.bstride[0] != 0 || g.B.bstride[1] != 0) { set_error("internal: weights of a worker's own"); return CADA_EUNSUPPORTED; }
       if (g.a_h != 0 || g.a_l != 1 || (has_d && g.a_d != 2) || g.a_r != (g.A.n == 4 ? 3 : 0) || g.b_h != 0 || g.b_l != 1 ||
           (has_d && g.b_x != (g.B.n == 4 ? 2 : 0)) || g.b_d != g.B.n - 1) {
         set_error("internal: unexpected tensor roles");

@@ -165,6 +165,9 @@ __global__ __launch_bounds__(kBlock, 7) void k_server(const DevState s, const Ru
   __shared__ double lhs_s[DECIDE ? kDecideWorkers : 1];
   __shared__ uint8_t dec_s[DECIDE ? kDecideWorkers : 1];       // buffer selector after the decision, 2: uploads
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  // (what the launch reads of its arguments, in one round trip)
+  asm volatile("" ::"s"(s.h), "s"(s.vhat), "s"(s.theta), "s"(s.theta_lo), "s"(s.gbuf), "s"(s.gbuf16), "s"(s.sel), "s"(s.n_up), "s"(s.lhs_part), "s"(s.M), "s"(s.p), "s"(s.ps), "s"(s.k), "s"(s.rule),
+               "s"(s.D), "s"(s.n_lhs_part), "s"(s.resum), "s"(ri.in), "s"(ri.rhs), "s"(replay));
   int64_t base = (int64_t)blockIdx.x * 256;
   const int64_t mp = (int64_t)s.M * s.ps;
   // coordinate of this lane's v-th value, and whether it exists
