@@ -1183,34 +1183,36 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
     // bias and ReLU of both evaluations; the block is 2 KB of consecutive memory of each output tensor
     uint8_t (*pos[2])[33];                          // [32]: value at theta, at the reference point is positive (in the room behind the partial results)
     pos[0] = reinterpret_cast<uint8_t (*)[33]>(smem_raw + ROOM); pos[1] = reinterpret_cast<uint8_t (*)[33]>(smem_raw + AREA + ROOM);
-    const int rl = t >> 4, c0 = 2 * (t & 15);
-    const int ra = 4 * (rl >> 3) + (rl & 3), lb = 32 * ((rl >> 2) & 1);      // (accumulator element of a row: as below)
-    float x[2], xref[2];
+    const int c0 = 2 * (t & 15);
+    for (int rl = t >> 4; rl < 32; rl += 4 * nw) {
+      const int ra = 4 * (rl >> 3) + (rl & 3), lb = 32 * ((rl >> 2) & 1);      // (accumulator element of a row: as below)
+      float x[2], xref[2];
 #pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      float zs = bz[e], ds = dbz[e];
-      for (int ww = 0; ww < nw; ++ww) {
-        zs += part_of(ww, 0)[ra * 64 + lb + c0 + e];
-        if constexpr (!PL) ds += part_of(ww, 1)[ra * 64 + lb + c0 + e];
+      for (int e = 0; e < 2; ++e) {
+        float zs = bz[e], ds = dbz[e];
+        for (int ww = 0; ww < nw; ++ww) {
+          zs += part_of(ww, 0)[ra * 64 + lb + c0 + e];
+          if constexpr (!PL) ds += part_of(ww, 1)[ra * 64 + lb + c0 + e];
+        }
+        const bool live = m0 + rl < g.M && 32 * cb + c0 + e < g.N;             // (else padding: zero)
+        x[e] = live ? fmaxf(zs, 0.f) : 0.f;
+        xref[e] = live && !PL ? fmaxf(zs - ds, 0.f) : 0.f;
       }
-      const bool live = m0 + rl < g.M && 32 * cb + c0 + e < g.N;             // (else padding: zero)
-      x[e] = live ? fmaxf(zs, 0.f) : 0.f;
-      xref[e] = live && !PL ? fmaxf(zs - ds, 0.f) : 0.f;
-    }
-    const uint32_t vh = f2bf_pk(x[0], x[1]), vr = f2bf_pk(xref[0], xref[1]);
-    // ReLU masks where k_mm5's activation gradient looks for them (sign of the stored, rounded values): this block is quarter
-    // (i, j) of wavefront (wy, wx) of its 128 x 128 tile, sixteen bits of each of the wavefront's lanes
+      const uint32_t vh = f2bf_pk(x[0], x[1]), vr = f2bf_pk(xref[0], xref[1]);
+      // ReLU masks where k_mm5's activation gradient looks for them (sign of the stored, rounded values): this block is quarter
+      // (i, j) of wavefront (wy, wx) of its 128 x 128 tile, sixteen bits of each of the wavefront's lanes
 #pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      pos[0][rl][c0 + e] = __uint_as_float(e ? vh & 0xffff0000u : vh << 16) > 0.f;
-      pos[1][rl][c0 + e] = __uint_as_float(e ? vr & 0xffff0000u : vr << 16) > 0.f;
-    }
-    const int64_t o = tm((int64_t)wk * g.Bp + m0 + rl, 32 * cb + c0, g.kto);
-    *reinterpret_cast<uint32_t *>(g.o_h + o) = vh;
-    *reinterpret_cast<uint32_t *>(g.o_l + o) = f2bf_pk(x[0] - __uint_as_float(vh << 16), x[1] - __uint_as_float(vh & 0xffff0000u));
-    if constexpr (!PL) {
-      *reinterpret_cast<uint32_t *>(g.o_d + o) = f2bf_pk(x[0] - xref[0], x[1] - xref[1]);
-      *reinterpret_cast<uint32_t *>(g.o_r + o) = vr;
+      for (int e = 0; e < 2; ++e) {
+        pos[0][rl][c0 + e] = __uint_as_float(e ? vh & 0xffff0000u : vh << 16) > 0.f;
+        pos[1][rl][c0 + e] = __uint_as_float(e ? vr & 0xffff0000u : vr << 16) > 0.f;
+      }
+      const int64_t o = tm((int64_t)wk * g.Bp + m0 + rl, 32 * cb + c0, g.kto);
+      *reinterpret_cast<uint32_t *>(g.o_h + o) = vh;
+      *reinterpret_cast<uint32_t *>(g.o_l + o) = f2bf_pk(x[0] - __uint_as_float(vh << 16), x[1] - __uint_as_float(vh & 0xffff0000u));
+      if constexpr (!PL) {
+        *reinterpret_cast<uint32_t *>(g.o_d + o) = f2bf_pk(x[0] - xref[0], x[1] - xref[1]);
+        *reinterpret_cast<uint32_t *>(g.o_r + o) = vr;
+      }
     }
     lds_sync();
     if (t < 2 * kWave) {
@@ -1817,6 +1819,10 @@ template <int NA, int NB, bool HAS_D, bool CADA1> hipError_t dw_allow_lds() {
 constexpr int skinny_lds_bytes(int epi, int tensors, int nw = 8) { return nw * (epi == EPI_DW ? 7 * 1024 * (int)sizeof(bf16_t) + 3 * 64 * (int)sizeof(float2) : tensors * 2048); }
 // Wavefronts of a launch: one per two tile steps, eight at most.  A weight gradient sums over a worker's few rows (4-8
 // steps); with eight wavefronts half of them would idle while their LDS kept other workgroups off the CU.
+// A hidden layer's forward product of more blocks than two workgroups of eight wavefronts per CU: four wavefronts, so that more workgroups are there at once and one's head and way out pass under
+// another's products, unless the inner dimension is long.  us per step, eight / four: 300-400-300-10, 30 workers of 60 rows, CADA2: 114.2 / 110.5; 64-1000-10, 32 of 16: 61.8 / 59.9; 617-301-150-26, always, 24 of
+// 100: 81.5 / 81.0; 784-1024-10, 40 of 24: 148.4 / 147.2; but 3072-1024-10, 20 of 64: 363 / 372; and 784-500-10, 10 of 12 (160 blocks): 51.6 / 52.4.
+constexpr int kSkinnyFewWaves = 512, kSkinnyShort = 1024;
 static int skinny_waves(int epi, int K) {
   const int nk = (K + BK - 1) / BK;
   if (epi != EPI_DW) return 8;
@@ -1827,7 +1833,8 @@ template <int EPI, int NA, int NB, bool HAS_D> hipError_t skinny_allow_lds() {
                              skinny_lds_bytes(EPI, NA + NB));
 }
 template <int EPI, int NA, int NB, bool HAS_D> int launch_skinny_as(Ctx *c, Mm5Args &g) {
-  const int nw = skinny_waves(EPI, g.K);
+  const int blocks = ((g.M + 31) / 32) * g.workers * ((g.N + 31) / 32);
+  const int nw = EPI == EPI_FWD_HIDDEN && blocks > kSkinnyFewWaves && g.K <= kSkinnyShort ? 4 : skinny_waves(EPI, g.K);
   g.step_waves = nw;
   const unsigned extra = (EPI == EPI_DW && g.lastb != nullptr) ? 1u : 0u;      // (the workgroup that finishes the last layer's bias gradient)
   // A weight gradient's way out is spread over four wavefronts at least where the CUs have room for them (with one, 120-80-60-5, 8 workers of 40
