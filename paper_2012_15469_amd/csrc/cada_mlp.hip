@@ -881,14 +881,13 @@ __device__ __forceinline__ float group16_sum(float x) {
 // one is a [32 rows][32 units] block (2 KB of consecutive memory), which the wavefront copies into an
 // LDS area of its own and reads back transposed (tr_fragment).
 template <int EPI, int NA, int NB, bool HAS_D>
-__global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
+__device__ __forceinline__ void skinny(const Mm5Args &g, unsigned char *smem_raw, int bx /* block of 32 rows of the result */) {
   float *red = reinterpret_cast<float *>(smem_raw);                  // EPI_DW: [8 wavefronts][2 accumulators][16][64]
   const DevState &s = g.s;
   const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
   const int nw = blockDim.x >> 6;          // wavefronts of this launch (1..8)
   const int nsw = EPI == EPI_DW ? g.step_waves : nw;       // those that take tile steps: fewer for short contractions, so that more workgroups fit a CU
-  const int m0 = blockIdx.x * 32, wk = blockIdx.y;
+  const int m0 = bx * 32, wk = blockIdx.y;
   const int nk = (g.K + BK - 1) / BK;
   constexpr bool PL = NB == 2;
   // (EPI_FWD_HIDDEN: units 32 blockIdx.z ... of the layer; else the only block of columns)
@@ -900,7 +899,7 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
     // The last layer's launch has one workgroup more than tiles: it forms that layer's bias gradient, its innovation
     // and the innovation's part of the left-hand side from the sums that the forward launch left per block of 32 rows
     // (added up in the order of the rows).
-    if (g.lastb != nullptr && (int)blockIdx.x == (g.M + 31) / 32) {
+    if (g.lastb != nullptr && bx == (g.M + 31) / 32) {
       if (w != 0) return;
       const bool cada1 = s.rule == CADA_RULE_CADA1;
       float sqb = 0.f;
@@ -1311,7 +1310,7 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
       const int c = lane;
       float gsum = 0.f, iv = 0.f;
       for (int ww = 0; ww < nw; ++ww) { gsum += part(ww, c >> 1)[c & 1]; iv += part(ww, c >> 1)[2 + (c & 1)]; }
-      float *q = g.lastb + ((((int64_t)wk * g.nrb + blockIdx.x) * 32 + c) << 1);
+      float *q = g.lastb + ((((int64_t)wk * g.nrb + bx) * 32 + c) << 1);
       q[0] = gsum; q[1] = iv;
     }
     return;
@@ -1353,9 +1352,27 @@ __global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
     if (t == 0) {
       float tot = 0.f;
       for (int ww = 0; ww < nw; ++ww) tot += red[ww];
-      s.lhs_part[(int64_t)wk * s.n_lhs_part + g.lhs_slot0 + blockIdx.x] = tot;
+      s.lhs_part[(int64_t)wk * s.n_lhs_part + g.lhs_slot0 + bx] = tot;
     }
   }
+}
+
+template <int EPI, int NA, int NB, bool HAS_D>
+__global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  skinny<EPI, NA, NB, HAS_D>(g, smem_raw, blockIdx.x);
+}
+
+// The loss and the last layer's weight gradient in one launch, where a worker's rows are one block and the workgroups are all there at once: each of a worker's workgroups forms the
+// worker's signals for itself and takes them up again where it has put them (every one the same values to the same place), which costs what the loss costs alone and saves a launch.
+template <bool PL>
+__global__ __launch_bounds__(2 * kBlock) void k_loss_dw(const Mm5Args loss, const Mm5Args dw) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  if constexpr (PL) skinny<EPI_LOSS, 2, 2, false>(loss, smem_raw, 0);
+  else skinny<EPI_LOSS, 4, 3, true>(loss, smem_raw, 0);
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");      // (signals and sums have arrived; the areas are written again)
+  if constexpr (PL) skinny<EPI_DW, 2, 2, false>(dw, smem_raw, blockIdx.x);
+  else skinny<EPI_DW, 3, 4, true>(dw, smem_raw, blockIdx.x);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1845,6 +1862,16 @@ template <int EPI, int NA, int NB, bool HAS_D> int launch_skinny_as(Ctx *c, Mm5A
                      dim3(64 * wide), skinny_lds_bytes(EPI, NA + NB, nw), c->stream, g);
   return CADA_OK;
 }
+template <bool PL> hipError_t loss_dw_allow_lds() {
+  return hipFuncSetAttribute(reinterpret_cast<const void *>(k_loss_dw<PL>), hipFuncAttributeMaxDynamicSharedMemorySize, skinny_lds_bytes(EPI_LOSS, PL ? 4 : 7));
+}
+// (M rows of the result and one more workgroup, for each worker)
+static int loss_dw_blocks(int units, int workers) { return ((units + 31) / 32 + 1) * workers; }
+template <bool PL> int launch_loss_dw(Ctx *c, Mm5Args &loss, Mm5Args &dw) {
+  dw.step_waves = 1;                       // (at most 32 rows: one step)
+  hipLaunchKernelGGL(k_loss_dw<PL>, dim3((unsigned)((dw.M + 31) / 32 + 1), (unsigned)dw.workers), dim3(2 * kBlock), skinny_lds_bytes(EPI_LOSS, PL ? 4 : 7), c->stream, loss, dw);
+  return CADA_OK;
+}
 // Hidden layers' forward products go through k_skinny while its 32 x 32 blocks fill the chip (two workgroups per CU) at most twice
 // over, or a worker has a single block of rows (a 128 x 128 tile would then be three quarters padding).  Few tiles leave CUs
 // idle and run through the whole inner dimension one after the other, where k_skinny splits it over eight wavefronts.
@@ -1991,6 +2018,8 @@ int mlp_init_state(Ctx *c, const float *) {
   if (e == hipSuccess) e = skinny_allow_lds<EPI_LOSS, 4, 3, true>();
   if (e == hipSuccess) e = skinny_allow_lds<EPI_DW, 2, 3, false>();
   if (e == hipSuccess) e = skinny_allow_lds<EPI_DW, 3, 4, true>();
+  if (e == hipSuccess) e = loss_dw_allow_lds<true>();
+  if (e == hipSuccess) e = loss_dw_allow_lds<false>();
   if (e != hipSuccess) { set_error("hipFuncSetAttribute(LDS size) failed: %s", hipGetErrorString(e)); return CADA_EHIP; }
   const int64_t n = P.total_rows * P.ldx;
   hipLaunchKernelGGL(k_x_to_bf16, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, c->s.X, P.Xh, P.Xl, P.total_rows, P.d[0], P.ldx);
@@ -2045,7 +2074,12 @@ static void stage(Ctx *c, const MlpPlan &P, const DevState &s, const int32_t *id
 void mlp_stage_weights(Ctx *c) { stage(c, *static_cast<MlpPlan *>(c->mlp), c->s, nullptr); }
 
 // Gathers the minibatch rows, prepares the bf16 weights and runs the forward contractions, whose last one evaluates the loss.
-static int mlp_forward(Ctx *c, MlpPlan &P, const DevState &s, const int32_t *idx) {
+// One launch for the loss and the last layer's weight gradient: one block of rows per worker, at most a workgroup per CU (their LDS).  us per step, two launches / one: 784-500-10, 10 workers of 12 rows (170
+// workgroups): 51.4 / 49.3; 784-500-500-10: 102.0 / 100.0; 617-301-150-26, always, 24 of 30 (144): 68.7 / 67.5; 784-300-10, 23 of 16 (253): 57.1 / 56.3; but 40 of 16 (440): 73.0 / 81.8.
+constexpr int kLossDwBlocks = 256;
+static bool loss_with_dw(const MlpPlan &P) { return P.L >= 2 && P.B <= 32 && loss_dw_blocks(P.d[P.L - 1], P.M) <= kLossDwBlocks; }
+
+static int mlp_forward(Ctx *c, MlpPlan &P, const DevState &s, const int32_t *idx, Mm5Args &loss /* out: where it has no launch of its own */) {
   const int L = P.L, M = P.M, B = P.B, Bp = P.Bp;
   const bool per_worker = (P.rule == CADA_RULE_CADA2), plain = plain_rule(P);
   const int64_t dwt_stride = per_worker ? P.wt_total : 0;
@@ -2084,7 +2118,8 @@ static int mlp_forward(Ctx *c, MlpPlan &P, const DevState &s, const int32_t *idx
       g.offb = P.offb[L - 1]; g.kto = P.kta[L];
       g.o_h = P.Gh[L]; g.o_l = P.Gl[L]; g.o_d = P.dG[L]; g.o_r = P.Gref[L];     // (Gref: null for a single-layer network)
       g.grow = P.grow; g.lastb = P.lastb; g.nrb = Bp / 32;
-      if (const int rc = launch_mm5<EPI_LOSS>(c, g, M)) return rc;
+      if (loss_with_dw(P)) { g.workers = M; loss = g; }
+      else if (const int rc = launch_mm5<EPI_LOSS>(c, g, M)) return rc;
     }
   }
   return CADA_OK;
@@ -2118,7 +2153,8 @@ int mlp_gradients(Ctx *c, const int32_t *idx) {
   const int64_t dwn_stride = per_worker ? P.wn_total : 0;
 
   prof_mark(c);
-  if (const int rc = mlp_forward(c, P, s, idx)) return rc;
+  Mm5Args loss;
+  if (const int rc = mlp_forward(c, P, s, idx, loss)) return rc;
 
   // ---- backward
   Mm5Args second;          // the second layer's weight gradient, where it waits for the first layer's
@@ -2164,7 +2200,10 @@ int mlp_gradients(Ctx *c, const int32_t *idx) {
         g1.M = P.d[0]; g1.N = din;
         waits = !(plain && (dw_past_caches(g) || dw_past_caches(g1)));
       }
-      if (l == 2 && waits) second = g;
+      if (l == L && loss_with_dw(P)) {
+        g.workers = M;
+        if (const int rc = plain ? launch_loss_dw<true>(c, loss, g) : launch_loss_dw<false>(c, loss, g)) return rc;
+      } else if (l == 2 && waits) second = g;
       else if (const int rc = l == 1 && waits ? launch_weight_gradients_of_two(c, second, g, M) : launch_mm5<EPI_DW>(c, g, M)) return rc;
     }
     if (l >= 2 && l < L) {   // gradient w.r.t. the activations of layer l-1, masks, bias partials
