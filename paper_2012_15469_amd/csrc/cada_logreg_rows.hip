@@ -445,9 +445,6 @@ __global__ __launch_bounds__(R_NT) void k_rows_wide(const RowsArgs a) {
   float *y_s = reinterpret_cast<float *>(off_s + ((a.rows + 3) & ~3));
   v4s *d_s = reinterpret_cast<v4s *>(y_s + ((a.rows + 3) & ~3));
   constexpr int NV = 2 * RB;
-  // (the arguments of the head in one round trip: see k_rows_sum)
-  asm volatile("" ::"s"(s.p), "s"(s.rule), "s"(s.B), "s"(s.tau), "s"(s.row_off), "s"(a.idx), "s"(s.theta), "s"(s.theta_lo), "s"(s.hist), "s"(s.hist_lo), "s"(s.snap), "s"(s.snap_lo), "s"(s.kR), "s"(s.D), "s"(s.R),
-               "s"(s.ps), "s"(a.rows), "s"(a.wide.shares), "s"(a.wide.rows), "s"(a.wide.per), "s"(s.X), "s"(s.y));
   __shared__ float red_s[2][R_NW][NV];
 
   const int f0 = wide_first(a.wide, blockIdx.x), nr = wide_first(a.wide, blockIdx.x + 1) - f0;        // this share's rows
@@ -624,10 +621,6 @@ __global__ __launch_bounds__(kBlock) void k_rows_sum(const RowsArgs a, const Rul
   __shared__ float red[4];
   __shared__ double rule_s[kBlock];
   const DevState &s = a.s;
-  // The arguments in one round trip, here and at the head of k_rows_wide (left to itself the compiled kernel asks for each where it is used, one after the other): p = 8196, M = 8, B = 64: 24.0 -> 23.0 us
-  // per step, p = 20001, M = 37, B = 75: 62.6 -> 62.0.  (At the head of the staging launch and of single whole steps it costs 0.3 and 0.2 us instead: scalar registers.)
-  asm volatile("" ::"s"(s.p), "s"(s.M), "s"(s.rule), "s"(s.B), "s"(s.tau), "s"(s.sel), "s"(s.theta), "s"(s.theta_lo), "s"(s.hist), "s"(s.hist_lo), "s"(s.snap), "s"(s.snap_lo), "s"(s.gbuf), "s"(s.dtl), "s"(s.kR),
-               "s"(s.D), "s"(s.R), "s"(s.ps), "s"(a.part), "s"(a.wide.shares), "s"(a.wide.rows), "s"(a.wide.per), "s"(s.lhs_part), "s"(s.n_lhs_part), "s"(s.lam));
   const int p = (int)s.p, ps = (p + 3) & ~3, m = blockIdx.y, rule = s.rule;
   if (m == s.M) {                                    // (one more row of blocks)
     if (blockIdx.x == 0) rule_inputs(s, ri, rule_s);

@@ -1121,7 +1121,7 @@ __device__ __forceinline__ void skinny(const Mm5Args &g, unsigned char *smem_raw
   // asked for behind the first step's operands, the row's label in its products, so that their latency passes under these.
   const int c0 = 32 * cb + 2 * (t & 15);
   {
-    const RefPtr ref = theta_ref_at(s, tau_wk);
+    const RefPtr ref = theta_ref_of(s, tau_wk);
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
       const int64_t i = g.offb + min(c0 + e, g.N - 1);           // (of an absent class: not used)
