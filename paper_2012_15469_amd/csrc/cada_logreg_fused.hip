@@ -673,7 +673,7 @@ __global__ __launch_bounds__(128) void k_fused_tail(const FusedArgs a) {
   const int64_t c0 = ((int64_t)blockIdx.x * 128 + threadIdx.x) * 4;
   float sq = 0.f;
   if (c0 < s.p) {
-    const RefPtr ref = theta_ref(s, m);
+    const RefPtr ref = theta_ref(s, m, s.k);
     const float4 tt = *reinterpret_cast<const float4 *>(s.theta + c0), tl = *reinterpret_cast<const float4 *>(s.theta_lo + c0);
     const float4 rh = *reinterpret_cast<const float4 *>(ref.hi + c0), rl = *reinterpret_cast<const float4 *>(ref.lo + c0);
     const float4 d = make_float4((tt.x - rh.x) + (tl.x - rl.x), (tt.y - rh.y) + (tl.y - rl.y), (tt.z - rh.z) + (tl.z - rl.z), (tt.w - rh.w) + (tl.w - rl.w));
@@ -760,7 +760,7 @@ bool fused_plan(Ctx *c, const cada_config *cfg) {
 int logreg_gradients_fused(Ctx *c, const int32_t *idx) {
   FusedArgs a;
   a.s = c->s;
-  set_iteration(a.s, c->k);
+  a.s.k = c->k;
   a.idx = idx;
   a.zpost = c->fused_post;
   a.Q = c->fused_Q;
