@@ -183,7 +183,7 @@ def measure(cfg, K: int, W: int, plain_launch: bool = False, bf16_store: bool = 
         grad_ms = prof["logreg_single_pass"] if single else sum(v for k, v in prof.items() if k.startswith("logreg_"))
         alg = kernel_bytes_per_launch(cfg) if not whole else algorithmic_bytes_per_step(cfg)
         achieved = alg / (grad_ms * 1e-3) / 1e9
-        name = "k_fused" if single else ("k_small (whole iterations; latency-bound)" if whole else "k_dots+k_grad")
+        name = "k_fused" if single else ("k_steps (whole iterations; latency-bound)" if whole else "k_dots+k_grad")
         rec["roofline"] = {"bound": "hbm", "kernel": name, "achieved": achieved,
                            "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                            "traffic": stored_traffic(cfg.name) if single else None,
