@@ -871,7 +871,7 @@ __device__ __forceinline__ float group16_sum(float x) {
 // would run on a few CUs (32 tiles for the logits of 16 workers).  Here a workgroup computes
 // 32 rows x 32 columns; its wavefronts (eight; fewer for the few steps of a weight gradient) split the
 // tile steps (wavefront w takes steps w, w + nw, ...), each through an LDS area of its own, and add their partial accumulators up
-// through LDS in a fixed order.  grid (ceil(M / 32), workers, blocks of 32 columns), 64 threads per
+// through LDS in a fixed order, the same for any number of workers.  grid (ceil(M / 32), workers, blocks of 32 columns), 64 threads per
 // wavefront (EPI_DW: and wavefronts for the way out alone, launch_skinny_as), 2 KB of dynamic LDS per tensor each (EPI_DW: 15.5 KB, for those that take steps).  EPI_FWD_HIDDEN: a hidden layer's forward product where the 128 x 128 tiles are few or mostly
 // padding (skinny_forward), with the outputs of k_mm5's.
 // EPI_LOSS: the logits stay in the workgroup, whose epilogue is the loss (the signals
@@ -880,8 +880,10 @@ __device__ __forceinline__ float group16_sum(float x) {
 // The weight gradient sums over the worker's rows: its operands are (row, unit) tensors, a step's part of
 // one is a [32 rows][32 units] block (2 KB of consecutive memory), which the wavefront copies into an
 // LDS area of its own and reads back transposed (tr_fragment).
-template <int EPI, int NA, int NB, bool HAS_D>
+// TWICE (EPI_FWD_HIDDEN): four wavefronts that do the work of eight, each the steps and the partial accumulators of two of them, so that a result does not depend on their number.
+template <int EPI, int NA, int NB, bool HAS_D, bool TWICE = false>
 __device__ __forceinline__ void skinny(const Mm5Args &g, unsigned char *smem_raw, int bx /* block of 32 rows of the result */) {
+  static_assert(EPI == EPI_FWD_HIDDEN || !TWICE, "");
   float *red = reinterpret_cast<float *>(smem_raw);                  // EPI_DW: [8 wavefronts][2 accumulators][16][64]
   const DevState &s = g.s;
   const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -945,6 +947,7 @@ __device__ __forceinline__ void skinny(const Mm5Args &g, unsigned char *smem_raw
   f32x16 acc1, acc2;
 #pragma unroll
   for (int r = 0; r < 16; ++r) { acc1[r] = 0.f; acc2[r] = 0.f; }
+  f32x16 later1 = acc1, later2 = acc2;            // TWICE: of the wavefront's second share of the steps
   float bz[2] = {0.f, 0.f}, dbz[2] = {0.f, 0.f};
   int label = 0;
   if constexpr (EPI == EPI_DW) {
@@ -1133,69 +1136,99 @@ __device__ __forceinline__ void skinny(const Mm5Args &g, unsigned char *smem_raw
   if (w >= nk) ask_label();
   const unsigned char *mine = smem_raw + w * AREA;
   const int fro = lds_piece((lane & 31) * 4 + (lane >> 5)) * 16;           // this lane's fragment of the first half step (the second: 32 bytes further, in lds_piece's order)
-  for (int kc = w; kc < nk; kc += nw) {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    u32x4 fa[2][NA], fb[2][NB];          // (kept as integer vectors: arrays of them stay in registers)
+  // steps first, first + stride, ...; then the steps from `then` on are next (nk: none)
+  const int stride = TWICE ? 2 * nw : nw;
+  auto walk = [&](int first, int then, f32x16 &acc1, f32x16 &acc2) __attribute__((always_inline)) {
+    for (int kc = first; kc < nk; kc += stride) {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      u32x4 fa[2][NA], fb[2][NB];          // (kept as integer vectors: arrays of them stay in registers)
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
+      for (int half = 0; half < 2; ++half) {
 #pragma unroll
-      for (int sl = 0; sl < NA; ++sl) fa[half][sl] = *reinterpret_cast<const u32x4 *>(mine + sl * 2048 + (fro ^ (32 * half)));
+        for (int sl = 0; sl < NA; ++sl) fa[half][sl] = *reinterpret_cast<const u32x4 *>(mine + sl * 2048 + (fro ^ (32 * half)));
 #pragma unroll
-      for (int sl = 0; sl < NB; ++sl) fb[half][sl] = *reinterpret_cast<const u32x4 *>(mine + (NA + sl) * 2048 + (fro ^ (32 * half)));
-    }
-    if (kc == w) ask_label();
-    if (kc + nw < nk) {
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // (the fragments are in registers before the area is written again)
-#pragma unroll
-      for (int sl = 0; sl < NA; ++sl) move(pa[sl], kc + nw, sl);
-#pragma unroll
-      for (int sl = 0; sl < NB; ++sl) move(pb[sl], kc + nw, NA + sl);
-    }
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      // (the roles of the tensors follow from their number: hi, lo, [difference, [reference]] on the A
-      // side, hi, lo, [reference,] difference on the B side; the host checks it)
-      auto fr = [&](const u32x4 &v) __attribute__((always_inline)) { return __builtin_bit_cast(bf16x8, v); };
-      const bf16x8 ah = fr(fa[half][0]), al = fr(fa[half][1]), bh = fr(fb[half][0]), bl = fr(fb[half][1]), bd = fr(fb[half][NB - 1]);
-      const bf16x8 ar = NA == 4 ? fr(fa[half][NA - 1]) : ah;
-      acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bh, acc1, 0, 0, 0);
-      acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bl, acc1, 0, 0, 0);
-      acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bh, acc1, 0, 0, 0);
-      if constexpr (HAS_D) {
-        const bf16x8 ad = fr(fa[half][2]), bx = NB == 4 ? fr(fb[half][2]) : bh;
-        acc2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ad, bx, acc2, 0, 0, 0);
+        for (int sl = 0; sl < NB; ++sl) fb[half][sl] = *reinterpret_cast<const u32x4 *>(mine + (NA + sl) * 2048 + (fro ^ (32 * half)));
       }
-      if constexpr (!PL) acc2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ar, bd, acc2, 0, 0, 0);
+      if (kc == w) ask_label();
+      const int next = kc + stride < nk ? kc + stride : then;
+      if (next < nk) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // (the fragments are in registers before the area is written again)
+#pragma unroll
+        for (int sl = 0; sl < NA; ++sl) move(pa[sl], next, sl);
+#pragma unroll
+        for (int sl = 0; sl < NB; ++sl) move(pb[sl], next, NA + sl);
+      }
+#pragma unroll
+      for (int half = 0; half < 2; ++half) {
+        // (the roles of the tensors follow from their number: hi, lo, [difference, [reference]] on the A
+        // side, hi, lo, [reference,] difference on the B side; the host checks it)
+        auto fr = [&](const u32x4 &v) __attribute__((always_inline)) { return __builtin_bit_cast(bf16x8, v); };
+        const bf16x8 ah = fr(fa[half][0]), al = fr(fa[half][1]), bh = fr(fb[half][0]), bl = fr(fb[half][1]), bd = fr(fb[half][NB - 1]);
+        const bf16x8 ar = NA == 4 ? fr(fa[half][NA - 1]) : ah;
+        acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bh, acc1, 0, 0, 0);
+        acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bl, acc1, 0, 0, 0);
+        acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bh, acc1, 0, 0, 0);
+        if constexpr (HAS_D) {
+          const bf16x8 ad = fr(fa[half][2]), bx = NB == 4 ? fr(fb[half][2]) : bh;
+          acc2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ad, bx, acc2, 0, 0, 0);
+        }
+        if constexpr (!PL) acc2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ar, bd, acc2, 0, 0, 0);
+      }
     }
+  };
+  walk(w, TWICE ? w + nw : nk, acc1, acc2);
+  if constexpr (TWICE) walk(w + nw, nk, later1, later2);
   }
-  }
-  if (w < nsw) {
+  auto put_part = [&](const f32x16 &acc1, const f32x16 &acc2) __attribute__((always_inline)) {
     float *r1 = EPI == EPI_DW ? red + w * 2 * 1024 : part_of(w, 0), *r2 = EPI == EPI_DW ? r1 + 1024 : part_of(w, 1);      // (not EPI_DW: over this wavefront's own blocks)
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       r1[r * 64 + lane] = acc1[r];
       if constexpr (!PL) r2[r * 64 + lane] = acc2[r];
     }
-  }
+  };
+  if (w < nsw) put_part(acc1, acc2);
   lds_sync();
   if constexpr (EPI == EPI_FWD_HIDDEN) {
     // bias and ReLU of both evaluations; the block is 2 KB of consecutive memory of each output tensor
     uint8_t (*pos[2])[33];                          // [32]: value at theta, at the reference point is positive (in the room behind the partial results)
     pos[0] = reinterpret_cast<uint8_t (*)[33]>(smem_raw + ROOM); pos[1] = reinterpret_cast<uint8_t (*)[33]>(smem_raw + AREA + ROOM);
+    constexpr int ROWS = TWICE ? 2 : 1, NW = 8 / ROWS;      // rows of a thread; wavefronts of the launch (launch_skinny_as)
     const int c0 = 2 * (t & 15);
-    for (int rl = t >> 4; rl < 32; rl += 4 * nw) {
-      const int ra = 4 * (rl >> 3) + (rl & 3), lb = 32 * ((rl >> 2) & 1);      // (accumulator element of a row: as below)
+    float zs[ROWS][2], ds[ROWS][2];
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i)
+#pragma unroll
+      for (int e = 0; e < 2; ++e) { zs[i][e] = bz[e]; ds[i][e] = dbz[e]; }
+    auto add_parts = [&]() __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < ROWS; ++i) {
+        const int rl = (t >> 4) + 16 * i, ra = 4 * (rl >> 3) + (rl & 3), lb = 32 * ((rl >> 2) & 1);      // (accumulator element of a row: as below)
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+#pragma unroll
+          for (int ww = 0; ww < NW; ++ww) {
+            zs[i][e] += part_of(ww, 0)[ra * 64 + lb + c0 + e];
+            if constexpr (!PL) ds[i][e] += part_of(ww, 1)[ra * 64 + lb + c0 + e];
+          }
+      }
+    };
+    add_parts();
+    if (TWICE && nk > nw) {                          // (else the second shares are empty)
+      lds_sync();
+      put_part(later1, later2);
+      lds_sync();
+      add_parts();
+    }
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) {
+      const int rl = (t >> 4) + 16 * i;
       float x[2], xref[2];
 #pragma unroll
       for (int e = 0; e < 2; ++e) {
-        float zs = bz[e], ds = dbz[e];
-        for (int ww = 0; ww < nw; ++ww) {
-          zs += part_of(ww, 0)[ra * 64 + lb + c0 + e];
-          if constexpr (!PL) ds += part_of(ww, 1)[ra * 64 + lb + c0 + e];
-        }
         const bool live = m0 + rl < g.M && 32 * cb + c0 + e < g.N;             // (else padding: zero)
-        x[e] = live ? fmaxf(zs, 0.f) : 0.f;
-        xref[e] = live && !PL ? fmaxf(zs - ds, 0.f) : 0.f;
+        x[e] = live ? fmaxf(zs[i][e], 0.f) : 0.f;
+        xref[e] = live && !PL ? fmaxf(zs[i][e] - ds[i][e], 0.f) : 0.f;
       }
       const uint32_t vh = f2bf_pk(x[0], x[1]), vr = f2bf_pk(xref[0], xref[1]);
       // ReLU masks where k_mm5's activation gradient looks for them (sign of the stored, rounded values): this block is quarter
@@ -1357,10 +1390,10 @@ __device__ __forceinline__ void skinny(const Mm5Args &g, unsigned char *smem_raw
   }
 }
 
-template <int EPI, int NA, int NB, bool HAS_D>
-__global__ __launch_bounds__(2 * kBlock) void k_skinny(const Mm5Args g) {
+template <int EPI, int NA, int NB, bool HAS_D, bool TWICE = false>
+__global__ __launch_bounds__(TWICE ? kBlock : 2 * kBlock) void k_skinny(const Mm5Args g) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  skinny<EPI, NA, NB, HAS_D>(g, smem_raw, blockIdx.x);
+  skinny<EPI, NA, NB, HAS_D, TWICE>(g, smem_raw, blockIdx.x);
 }
 
 // The loss and the last layer's weight gradient in one launch, where a worker's rows are one block and the workgroups are all there at once: each of a worker's workgroups forms the
@@ -1836,30 +1869,41 @@ template <int NA, int NB, bool HAS_D, bool CADA1> hipError_t dw_allow_lds() {
 constexpr int skinny_lds_bytes(int epi, int tensors, int nw = 8) { return nw * (epi == EPI_DW ? 7 * 1024 * (int)sizeof(bf16_t) + 3 * 64 * (int)sizeof(float2) : tensors * 2048); }
 // Wavefronts of a launch: one per two tile steps, eight at most.  A weight gradient sums over a worker's few rows (4-8
 // steps); with eight wavefronts half of them would idle while their LDS kept other workgroups off the CU.
-// A hidden layer's forward product of more blocks than two workgroups of eight wavefronts per CU: four wavefronts, so that more workgroups are there at once and one's head and way out pass under
-// another's products, unless the inner dimension is long.  us per step, eight / four: 300-400-300-10, 30 workers of 60 rows, CADA2: 114.2 / 110.5; 64-1000-10, 32 of 16: 61.8 / 59.9; 617-301-150-26, always, 24 of
-// 100: 81.5 / 81.0; 784-1024-10, 40 of 24: 148.4 / 147.2; but 3072-1024-10, 20 of 64: 363 / 372; and 784-500-10, 10 of 12 (160 blocks): 51.6 / 52.4.
-constexpr int kSkinnyFewWaves = 512, kSkinnyShort = 1024;
+// A hidden layer's forward product of more blocks than two workgroups of eight wavefronts per CU: four wavefronts with the shares of two each, so that more workgroups are there at once and one's head and
+// way out pass under another's products; an inner dimension of more than 512 leaves nothing of that, since the second shares cross LDS after the first.  us per step of inner dimension-400-10, eight / four, CADA2,
+// 30 workers of 60 rows, then 40 of 24, always, 30 of 60: 64: 53.8 / 52.5, 51.9 / 50.6, 47.7 / 45.9; 200: 55.9 / 55.8, 57.6 / 57.5, 50.5 / 49.1; 400: 64.1 / 63.7, 68.8 / 68.4, 58.3 / 57.1; 512: 66.3 / 65.7, 71.2 /
+// 71.6, 64.0 / 63.8; 700: 80.9 / 80.8, 77.4 / 78.0, 72.7 / 72.5; 1000: 103.1 / 103.0, 103.1 / 104.1, 86.3 / 86.9; 300-400-300-10, 30 of 60: 111.3 / 110.1; 100-300-300-300-10, CADA1, 40 of 50: 170.2 / 162.9.  784-500-10,
+// 10 of 12 (160 blocks): 51.6 / 52.4.  (With four shares in all, whose sums are others, 0.2 to 1.3 less from 200 on.)
+constexpr int kSkinnyFewWaves = 512, kSkinnyShort = 512;
 static int skinny_waves(int epi, int K) {
   const int nk = (K + BK - 1) / BK;
   if (epi != EPI_DW) return 8;
   return nk >= 16 ? 8 : nk >= 2 ? nk / 2 : 1;
 }
 template <int EPI, int NA, int NB, bool HAS_D> hipError_t skinny_allow_lds() {
+  if constexpr (EPI == EPI_FWD_HIDDEN) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_skinny<EPI, NA, NB, HAS_D, true>), hipFuncAttributeMaxDynamicSharedMemorySize, skinny_lds_bytes(EPI, NA + NB, 4));
+    if (e != hipSuccess) return e;
+  }
   return hipFuncSetAttribute(reinterpret_cast<const void *>(k_skinny<EPI, NA, NB, HAS_D>), hipFuncAttributeMaxDynamicSharedMemorySize,
                              skinny_lds_bytes(EPI, NA + NB));
 }
 template <int EPI, int NA, int NB, bool HAS_D> int launch_skinny_as(Ctx *c, Mm5Args &g) {
-  const int blocks = ((g.M + 31) / 32) * g.workers * ((g.N + 31) / 32);
-  const int nw = EPI == EPI_FWD_HIDDEN && blocks > kSkinnyFewWaves && g.K <= kSkinnyShort ? 4 : skinny_waves(EPI, g.K);
+  if constexpr (EPI == EPI_FWD_HIDDEN) {
+    const dim3 grid((unsigned)((g.M + 31) / 32), (unsigned)g.workers, (unsigned)((g.N + 31) / 32));
+    if ((int64_t)grid.x * grid.y * grid.z > kSkinnyFewWaves && g.K <= kSkinnyShort)
+      hipLaunchKernelGGL((k_skinny<EPI, NA, NB, HAS_D, true>), grid, dim3(kBlock), skinny_lds_bytes(EPI, NA + NB, 4), c->stream, g);
+    else hipLaunchKernelGGL((k_skinny<EPI, NA, NB, HAS_D>), grid, dim3(2 * kBlock), skinny_lds_bytes(EPI, NA + NB), c->stream, g);
+    return CADA_OK;
+  }
+  const int nw = skinny_waves(EPI, g.K);
   g.step_waves = nw;
   const unsigned extra = (EPI == EPI_DW && g.lastb != nullptr) ? 1u : 0u;      // (the workgroup that finishes the last layer's bias gradient)
   // A weight gradient's way out is spread over four wavefronts at least where the CUs have room for them (with one, 120-80-60-5, 8 workers of 40
   // rows: 12.7 us, now 10.3); with more than two workgroups per CU, whose registers they take, over those of the products (784-512-10, 64 workers of 128 rows:
   // four wavefronts 1.4 us slower than two).
   const int wide = EPI == EPI_DW && nw < 4 && (int64_t)((g.M + 31) / 32 + extra) * g.workers <= 512 ? 4 : nw;
-  hipLaunchKernelGGL((k_skinny<EPI, NA, NB, HAS_D>), dim3((unsigned)((g.M + 31) / 32) + extra, g.workers, EPI == EPI_FWD_HIDDEN ? (unsigned)((g.N + 31) / 32) : 1u),
-                     dim3(64 * wide), skinny_lds_bytes(EPI, NA + NB, nw), c->stream, g);
+  hipLaunchKernelGGL((k_skinny<EPI, NA, NB, HAS_D>), dim3((unsigned)((g.M + 31) / 32) + extra, g.workers), dim3(64 * wide), skinny_lds_bytes(EPI, NA + NB, nw), c->stream, g);
   return CADA_OK;
 }
 template <bool PL> hipError_t loss_dw_allow_lds() {
