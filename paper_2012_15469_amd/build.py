@@ -2,6 +2,7 @@
 from __future__ import annotations
 
 import os
+import re
 import subprocess
 import sys
 
@@ -9,7 +10,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 HIP_FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-shared", "-fPIC",
-             "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument"]
+             "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument",
+             "-Werror=align-mismatch"]
 
 LIBCADA = os.path.join(HERE, "libcada.so")
 LIBCADA_SRC = [os.path.join(HERE, "csrc", f) for f in
@@ -19,9 +21,11 @@ LIBCADA_SRC = [os.path.join(HERE, "csrc", f) for f in
 
 def _run(cmd):
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-    out = "\n".join(l for l in r.stdout.splitlines() if "packed-fp32-ops" not in l)
+    out = "\n".join(l for l in r.stdout.splitlines() if "packed-fp32-ops" not in l and not re.fullmatch(r"\d+ warnings? generated.*", l))
     if r.returncode != 0:
         raise RuntimeError("build failed: %s\n%s" % (" ".join(cmd), out))
+    if out:
+        print(out, file=sys.stderr, flush=True)      # warnings
     return out
 
 

@@ -38,7 +38,14 @@ __device__ __forceinline__ float sigmoid_t(float a) { return 1.0f / (1.0f + expf
 template <typename T> __device__ __forceinline__ T uniform_load(const T *p) { return *(const __attribute__((address_space(4))) T *)(uintptr_t)p; }
 
 // Memory through a pointer that itself comes from memory: said to be global (the compiler would make flat accesses of it, for which a wait for LDS waits too).
-template <typename T> __device__ __forceinline__ __attribute__((address_space(1))) T *far_of(T *p) { return (__attribute__((address_space(1))) T *)p; }
+template <typename T> __device__ __forceinline__ __attribute__((address_space(1))) T *far_of(T *p) {
+  static_assert(std::is_arithmetic<std::remove_const_t<T>>::value, "a template's parameter drops the alignment of v4u: far_quad");
+  return (__attribute__((address_space(1))) T *)p;
+}
+// Four floats at any 4-byte aligned address (rows of 54 or 1021 columns, the last quad of a row).
+typedef __attribute__((address_space(1))) v4u far_v4u;
+__device__ __forceinline__ const far_v4u &far_quad(const float *p) { return *(const far_v4u *)p; }
+__device__ __forceinline__ far_v4u &far_quad(float *p) { return *(far_v4u *)p; }
 
 // What seldom happens is laid out behind what does: a jump to code that no workgroup of the CU has run in this launch waits for memory, code in line is fetched ahead.
 __device__ __forceinline__ bool rare(bool x) { return __builtin_expect(x, false); }
@@ -91,7 +98,7 @@ __device__ __forceinline__ void steps_body(const SmallArgs &a, const uint32_t *s
   v4u x[NB][RW][CW];
   auto ask_quads = [&](const Rows &r, int t, int i) __attribute__((always_inline)) {
 #pragma unroll
-    for (int q = 0; q < RW; ++q) x[t][q][i] = *far_of(reinterpret_cast<const v4u *>(r.row[q] + jb(i)));
+    for (int q = 0; q < RW; ++q) x[t][q][i] = far_quad(r.row[q] + jb(i));
   };
   int32_t idx[NB];
 #pragma unroll
@@ -265,7 +272,7 @@ __device__ __forceinline__ void steps_body(const SmallArgs &a, const uint32_t *s
         if (jq + 4 <= p) store_far(store, (uint32_t)jq * 4u, (uint32_t)(((int64_t)(1 - cur) * mp + (int64_t)m * s.p) * 4), sum);
         else for (int e = 0; jq + e < p; ++e) __hip_atomic_store(far_of(at.gbuf) + of + e, sum[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       } else if (is_iv && rule == CADA_RULE_CADA1) {
-        if (jq + 4 <= p) *far_of(reinterpret_cast<v4u *>(at.dtl + of)) = sum;
+        if (jq + 4 <= p) far_quad(at.dtl + of) = sum;
         else for (int e = 0; jq + e < p; ++e) far_of(at.dtl)[of + e] = sum[e];
       }
     };
