@@ -158,6 +158,12 @@ __device__ __forceinline__ void steps_body(const SmallArgs &a, const uint32_t *s
   const __amdgpu_buffer_rsrc_t rows = far_buffer(a.rows, (int64_t)kStepsTurns * M * ps);
   const uint32_t row4 = (uint32_t)ps * 4u;     // bytes of a row of `rows`
   int turn = v.turn;
+  if constexpr (!ONE) {
+    // h and vhat of this thread's columns are here before the workgroup's first gradient can be (behind the barrier below): with it all others may update them and write them
+    // back, and a wavefront without rows, under a rule without reference points, waits for nothing else until its own update.
+#pragma unroll
+    for (int e = 0; e < W; ++e) asm volatile("; server state %0 %1" ::"v"(hh[e]), "v"(vh[e]) : "memory");
+  }
 
   for (int64_t step = 0; step < n_steps; ++step) {
     const int64_t k = v.k + step;
