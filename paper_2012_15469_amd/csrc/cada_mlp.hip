@@ -938,7 +938,9 @@ __device__ __forceinline__ void skinny(const Mm5Args &g, unsigned char *smem_raw
     asm volatile("" ::"s"(g.A.ptr[0]), "s"(g.A.ptr[1]), "s"(g.A.ptr[NA - 2]), "s"(g.A.ptr[NA - 1]), "s"(g.B.ptr[0]), "s"(g.B.ptr[1]), "s"(g.B.ptr[NB - 1]), "s"(g.A.kt[0]), "s"(g.B.kt[0]),
                  "s"(g.A.bstride[0]), "s"(g.B.bstride[NB - 1]), "s"(g.rep), "s"(s.tau), "s"(s.rule), "s"(g.K), "s"(g.M), "s"(g.N), "s"(g.offb), "s"(s.theta), "s"(s.theta_lo), "s"(s.hist), "s"(s.hist_lo),
                  "s"(s.kR), "s"(s.D), "s"(s.R), "s"(s.ps), "s"(EPI == EPI_LOSS ? g.grow : nullptr), "s"(g.Bp));
-  } else {
+  } else if constexpr (NB == 4) {
+    // (not under the rules without reference points: without / with it 784-500-10, always, 10 workers of 12 rows: 41.8 / 42.5 us per step,
+    // 784-512-10, always, 64 of 128: 164.5 / 164.5; CADA2, 784-500-10, 10 of 12: 50.7 / 50.4, 200-150-5, 8 of 200: 55.1 / 55.2, 300-400-300-10, 30 of 60: 111.2 / 111.2)
     asm volatile("" ::"s"(g.A.ptr[0]), "s"(g.A.ptr[1]), "s"(g.A.ptr[NA - 1]), "s"(g.B.ptr[0]), "s"(g.B.ptr[1]), "s"(g.B.ptr[NB - 2]), "s"(g.B.ptr[NB - 1]), "s"(g.A.kt[0]), "s"(g.B.kt[0]),
                  "s"(g.A.bstride[0]), "s"(g.B.bstride[0]), "s"(g.rep), "s"(s.rule), "s"(g.K), "s"(g.M), "s"(g.N), "s"(g.step_waves), "s"(g.lastb), "s"(g.w_h), "s"(g.w_l), "s"(g.w_d), "s"(g.w_kt),
                  "s"(g.w_dstride), "s"(g.maskbits), "s"(s.sel), "s"(s.M), "s"(s.dtl16), "s"(s.ps16));
