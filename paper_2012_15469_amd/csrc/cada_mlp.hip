@@ -1650,29 +1650,18 @@ __device__ __forceinline__ void stage_weights(const StageArgs &a, const PrepLaye
       float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
       if (i < p.din && o < p.dout) {
         const int64_t src = p.offW + (int64_t)i * p.dout + o;
-        if (o + 8 <= p.dout) {
+        // (whole quads also where the row ends inside them: up to seven floats past it, of the next row, the bias or what follows in the workspace, which are not used)
 #pragma unroll
-          for (int q = 0; q < 2; ++q) {
-            f32x4u x = *reinterpret_cast<const f32x4u *>(s.theta + src + 4 * q);
-            if (!is_w) {
-              const f32x4u xl = *reinterpret_cast<const f32x4u *>(s.theta_lo + src + 4 * q);
-              const f32x4u rh = *reinterpret_cast<const f32x4u *>(ref.hi + src + 4 * q);
-              const f32x4u rl = *reinterpret_cast<const f32x4u *>(ref.lo + src + 4 * q);
-              x = (x - rh) + (xl - rl);             // the same expression as delta_theta
-            }
-            v[4 * q] = x.x; v[4 * q + 1] = x.y; v[4 * q + 2] = x.z; v[4 * q + 3] = x.w;
-          }
-        } else {
-          // (all asked for at once: element by element as far as the row goes, each waited for the one before, up to 8 us of a launch of 11 in 617-301-150-26)
-          float x[8], y[8] = {}, z[8] = {}, u[8] = {};
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const int64_t at = src + min(e, p.dout - 1 - o);
-            x[e] = s.theta[at];
-            if (!is_w) { y[e] = ref.hi[at]; z[e] = s.theta_lo[at]; u[e] = ref.lo[at]; }
+        for (int q = 0; q < 2; ++q) {
+          f32x4u x = *reinterpret_cast<const f32x4u *>(s.theta + src + 4 * q);
+          if (!is_w) {
+            const f32x4u xl = *reinterpret_cast<const f32x4u *>(s.theta_lo + src + 4 * q);
+            const f32x4u rh = *reinterpret_cast<const f32x4u *>(ref.hi + src + 4 * q);
+            const f32x4u rl = *reinterpret_cast<const f32x4u *>(ref.lo + src + 4 * q);
+            x = (x - rh) + (xl - rl);               // the same expression as delta_theta
           }
 #pragma unroll
-          for (int e = 0; e < 8; ++e) v[e] = o + e < p.dout ? is_w ? x[e] : (x[e] - y[e]) + (z[e] - u[e]) : 0.f;
+          for (int e = 0; e < 4; ++e) v[4 * q + e] = o + 4 * q + e < p.dout ? x[e] : 0.f;
         }
         if (p.want_n) {                             // (values past dout are zeros, like the padding they land in)
           const int64_t dn = tm(i, o, p.ktn);
