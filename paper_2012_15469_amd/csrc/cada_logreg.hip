@@ -63,7 +63,6 @@ __global__ __launch_bounds__(kBlock) void k_dots(const LogregArgs a) {
   const DevState &s = a.s;
   const int m = a.m0 + blockIdx.z;
   const int r0 = blockIdx.y * kRowsPerBlock;
-  const int64_t k = s.k;
   const float *__restrict__ th = s.theta;
   const float *__restrict__ tl = s.theta_lo;
   const RefPtr ref = theta_ref(s, m);
@@ -136,7 +135,6 @@ __global__ __launch_bounds__(kBlock) void k_grad(const LogregArgs a) {
   __shared__ float red[4];
 
   const int m = a.m0 + blockIdx.y;
-  const int64_t k = s.k;
   const int32_t *idx = a.idx + (int64_t)m * s.B;
   const float *yv = static_cast<const float *>(s.y);
   const float invB = 1.0f / (float)s.B;

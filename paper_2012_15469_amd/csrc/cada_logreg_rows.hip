@@ -401,9 +401,10 @@ __global__ __launch_bounds__(R_NT) void k_rows(const Args a) {
     sqs = fma((double)step, (double)step, sqs);
     s.nabla[j] = nab; s.h[j] = hh; s.v[j] = vv; s.vhat[j] = vh; s.theta[j] = t; s.theta_lo[j] = tl;
     if (rule == CADA_RULE_CADA2) {
-      s.hist[((k + 1) % s.R) * s.ps + j] = t;
-      s.hist_lo[((k + 1) % s.R) * s.ps + j] = tl;
-    } else if (rule == CADA_RULE_CADA1 && (k + 1) % s.D == 0) {
+      const int64_t o = (int64_t)(s.kR + 1 == s.R ? 0 : s.kR + 1) * s.ps + j;
+      s.hist[o] = t;
+      s.hist_lo[o] = tl;
+    } else if (s.snap_next) {
       s.snap[j] = t;
       s.snap_lo[j] = tl;
     }

@@ -172,7 +172,7 @@ __device__ __forceinline__ void small_body(const SmallArgs &a, const uint32_t *s
   for (int64_t step = 0; step < n_steps; ++step) {
     const int64_t k = v.k + step;
     const Phase ph1 = phase_after(s, ph);      // of k + 1
-    const int newest_at = ONE ? k > 0 ? (int)((k - 1) % s.d_max) : 0 : ph.d == 0 ? s.d_max - 1 : ph.d - 1;
+    const int newest_at = ph.d == 0 ? s.d_max - 1 : ph.d - 1;
     const bool more = !ONE && step + 1 < n_steps;
     lds_sync();            // (the wavefronts waited for the rows before they came here)
     int32_t nidx = 0;
@@ -383,7 +383,7 @@ __device__ __forceinline__ void small_body(const SmallArgs &a, const uint32_t *s
     if ((ONE || m == 0) && tid == 0 && k > 0) at.ring[newest_at] = newest_s;   // (for the world outside: every workgroup has its own copy)
     float sqs = 0.f;
     const float alpha = stepsize(s, k);
-    const bool snap_now = rule == CADA_RULE_CADA1 && (ONE ? (k + 1) % s.D == 0 : ph1.D == 0);
+    const bool snap_now = rule == CADA_RULE_CADA1 && ph1.D == 0;
     // the decisions as bits of scalar registers, 64 workers each (M <= 256)
     unsigned long long sel64[4];
 #pragma unroll
@@ -438,7 +438,7 @@ __device__ __forceinline__ void small_body(const SmallArgs &a, const uint32_t *s
       if (ONE || (j < 256 * nb ? j / 256 : (j / 256) % nb) == m) {
         at.nabla[j] = nab; at.h[j] = hh; at.v[j] = vv; at.vhat[j] = vh; at.theta[j] = th; at.theta_lo[j] = tl;
         if (rule == CADA_RULE_CADA2) {      // (read by other workgroups of this launch below)
-          const int64_t o = (ONE ? (k + 1) % s.R : ph1.R) * s.p + j;
+          const int64_t o = (int64_t)ph1.R * s.p + j;
           __hip_atomic_store(at.hist + o, th, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           __hip_atomic_store(at.hist_lo + o, tl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         } else if (snap_now) {

@@ -25,11 +25,11 @@ struct SmallVar {
   uint32_t bar_base;         // sequence number of this launch's first step (monotone over the life of the context)
   int32_t turn;              // cada_logreg_steps.hip: turn of the first step of a launch of several
 };
-// An iteration k where a launch of several steps needs it modulo something: k mod (D + 1) (slot of the iterate history), k mod D (CADA1's snapshots), k mod d_max (ring of
+// An iteration k where a launch needs it modulo something: k mod (D + 1) (slot of the iterate history), k mod D (CADA1's snapshots), k mod d_max (ring of
 // squared steps).  The host forms the first step's, the others follow: the modulo of a 64-bit k is some 130 instructions in the chain of every step.  Ten runs of 20 steps,
-// M = 10, B = 10, p = 54, side by side: 141.8 -> 139.8 us, 20 steps, M = 20, B = 32, p = 784: 234.6 -> 229.5.  (A single step forms them itself: as arguments they cost it 1 %.)
+// M = 10, B = 10, p = 54, side by side: 141.8 -> 139.8 us, 20 steps, M = 20, B = 32, p = 784: 234.6 -> 229.5. 
 struct Phase { int32_t R, D, d; };
-static Phase phase_of(const DevState &s, int64_t k) { return Phase{(int32_t)(k % s.R), (int32_t)(k % s.D), (int32_t)(k % s.d_max)}; }
+inline Phase phase_of(const DevState &s, int64_t k) { return Phase{(int32_t)(k % s.R), (int32_t)(k % s.D), (int32_t)(k % s.d_max)}; }
 __device__ __forceinline__ Phase phase_after(const DevState &s, Phase ph) {
   return Phase{ph.R + 1 == s.R ? 0 : ph.R + 1, ph.D + 1 == s.D ? 0 : ph.D + 1, ph.d + 1 == s.d_max ? 0 : ph.d + 1};
 }
