@@ -129,7 +129,7 @@ __device__ __forceinline__ void small_body(const SmallArgs &a, const uint32_t *s
       if (b0 + lane < B) lds_direct<4>(static_cast<const float *>(s.y) + base + row_n[b0 + lane], r_s + b0);
   };
   // Everything the start needs is asked for before anything is waited for; only the rows depend on their indices.
-  const RefPtr ref = theta_ref_in(s, tau_m, ph);
+  const RefPtr ref = !ONE || rule != CADA_RULE_CADA2 ? theta_ref_in(s, tau_m, ph) : theta_ref_in(s, tau_m, Phase{(int32_t)(v.k % s.R), 0, 0});
   const float *stored = (rule == CADA_RULE_CADA1 ? s.dtl : s.gbuf) + (int64_t)cur * mp + (int64_t)m * s.p;
   const int32_t idx0 = tid < B ? idx[tid] : 0;
   const uint32_t state0 = tid < (int)(sizeof(DevState) / 4) ? state[tid] : 0u;
@@ -172,7 +172,7 @@ __device__ __forceinline__ void small_body(const SmallArgs &a, const uint32_t *s
   for (int64_t step = 0; step < n_steps; ++step) {
     const int64_t k = v.k + step;
     const Phase ph1 = phase_after(s, ph);      // of k + 1
-    const int newest_at = ph.d == 0 ? s.d_max - 1 : ph.d - 1;
+    const int newest_at = ONE ? k > 0 ? (int)((k - 1) % s.d_max) : 0 : ph.d == 0 ? s.d_max - 1 : ph.d - 1;
     const bool more = !ONE && step + 1 < n_steps;
     lds_sync();            // (the wavefronts waited for the rows before they came here)
     int32_t nidx = 0;
@@ -383,7 +383,7 @@ __device__ __forceinline__ void small_body(const SmallArgs &a, const uint32_t *s
     if ((ONE || m == 0) && tid == 0 && k > 0) at.ring[newest_at] = newest_s;   // (for the world outside: every workgroup has its own copy)
     float sqs = 0.f;
     const float alpha = stepsize(s, k);
-    const bool snap_now = rule == CADA_RULE_CADA1 && ph1.D == 0;
+    const bool snap_now = rule == CADA_RULE_CADA1 && (ONE ? (k + 1) % s.D == 0 : ph1.D == 0);
     // the decisions as bits of scalar registers, 64 workers each (M <= 256)
     unsigned long long sel64[4];
 #pragma unroll
@@ -438,7 +438,7 @@ __device__ __forceinline__ void small_body(const SmallArgs &a, const uint32_t *s
       if (ONE || (j < 256 * nb ? j / 256 : (j / 256) % nb) == m) {
         at.nabla[j] = nab; at.h[j] = hh; at.v[j] = vv; at.vhat[j] = vh; at.theta[j] = th; at.theta_lo[j] = tl;
         if (rule == CADA_RULE_CADA2) {      // (read by other workgroups of this launch below)
-          const int64_t o = (int64_t)ph1.R * s.p + j;
+          const int64_t o = (ONE ? (k + 1) % s.R : ph1.R) * s.p + j;
           __hip_atomic_store(at.hist + o, th, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           __hip_atomic_store(at.hist_lo + o, tl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         } else if (snap_now) {
@@ -488,6 +488,7 @@ __global__ __launch_bounds__(S_NT) void k_small(const SmallLaunch launch) {
 }
 
 // grid M
+// (ph is not looked at: the single step forms the remainders that its rule needs itself.  With them off the arguments p = 2500, M = 8, B = 5, CADA1: 17.95 -> 18.16 us; p = 700, M = 20, B = 40: 16.69 -> 16.93.)
 __global__ __launch_bounds__(S_NT) void k_small_one(const SmallArgs a, const SmallVar v, const Phase ph) { small_body<true>(a, reinterpret_cast<const uint32_t *>(&a.s), v, ph, 1); }
 
 // Whether the multi-step kernel serves this configuration.
