@@ -1,5 +1,5 @@
 """Networks whose loss and last weight gradient share a launch (at most 32 rows per worker, at most 256 workgroups of 32 units, one more per worker), at both sides of both lines, and hidden
-layers whose small forward products take four wavefronts per workgroup (more than 512 blocks of 32 x 32, at most 1024 inputs), against the oracle."""
+layers whose small forward products take four wavefronts per workgroup (more than 512 blocks of 32 x 32, at most 512 inputs), against the oracle."""
 import numpy as np
 import pytest
 
@@ -9,8 +9,8 @@ from common import check_protocol, upload
 
 pytestmark = pytest.mark.gpu
 
-# 1, 31, 32 and 33 rows; one unit and no multiple of 32 of them; 256 workgroups and 264; 512 blocks of the forward product and 520, 1024 inputs and 1025
-SHAPES = [((40, 33, 5), 3, 1), ((50, 1, 2), 4, 31), ((60, 70, 32), 5, 32), ((60, 70, 32), 5, 33), ((30, 97, 6), 51, 9), ((30, 225, 3), 32, 9), ((30, 225, 3), 33, 9), ((40, 50, 65, 7), 8, 20),
+# 1, 31, 32 and 33 rows; one unit and no multiple of 32 of them; 255 workgroups (51 workers), 256 and 264 (193 and 224 units), 288 and 297; 512 blocks of the forward product and 544, 1024 inputs and 1025
+SHAPES = [((40, 33, 5), 3, 1), ((50, 1, 2), 4, 31), ((60, 70, 32), 5, 32), ((60, 70, 32), 5, 33), ((30, 97, 6), 51, 9), ((30, 225, 3), 32, 9), ((30, 225, 3), 33, 9), ((30, 193, 3), 32, 9), ((30, 224, 3), 32, 9), ((30, 224, 3), 33, 9), ((40, 50, 65, 7), 8, 20),
           ((64, 512, 4), 32, 12), ((64, 513, 4), 32, 12), ((1024, 256, 4), 65, 8), ((1025, 256, 4), 65, 8)]
 
 
