@@ -102,7 +102,7 @@ __device__ __forceinline__ RefPtr theta_ref(const DevState &s, int m) {
   return theta_ref_at(s, s.rule == CADA_RULE_CADA2 ? s.tau[m] : 0);
 }
 
-// (for a launch whose copy of the state was not made by set_iteration)
+// (the single-pass kernel)
 __device__ __forceinline__ RefPtr theta_ref(const DevState &s, int m, int64_t k) {
   if (s.rule != CADA_RULE_CADA2) return theta_ref_at(s, 0);
   int64_t slot = (k - (int64_t)min(s.tau[m], s.D)) % s.R;
@@ -110,7 +110,8 @@ __device__ __forceinline__ RefPtr theta_ref(const DevState &s, int m, int64_t k)
   return RefPtr{s.hist + slot * s.ps, s.hist_lo + slot * s.ps};
 }
 
-// The copy of iteration k.
+// The copy of iteration k.  Every launch of a kernel that looks for a reference point or writes one passes such a copy; not the single-pass kernel, which forms the remainders itself, and the evaluation's
+// staging, which has no differences to form.
 inline void set_iteration(DevState &s, int64_t k) { s.k = k; s.kR = (int32_t)(k % s.R); s.snap_next = s.rule == CADA_RULE_CADA1 && (k + 1) % s.D == 0; }
 
 // Stepsize of iteration k (constant, or the decaying 2/(mu(k+K0)) of Theorem 2).

@@ -37,6 +37,8 @@ enum { kTailNone = 0, kTailRule = 1, kTailServer = 2 };      // what the workgro
 // The server update in the launch's last workgroup saves a launch, and costs a pass over the state by one CU.  Measured, us per step with and
 // without it, B = 65: M = 10, p = 22: 12.5, 15.0; M = 32, p = 256: 14.0, 15.5; M = 32, p = 500: 14.5, 15.5; M = 48: 15.6, 16.1; M = 64: 16.8,
 // 16.7; M = 16, p = 784: 16.5, 17.1; M = 24: 18.1, 17.2; M = 16, p = 1024: 16.4, 17.0; M = 1, p = 1500: 16.5, 16.3; 3000: 22.0, 18.9; 8000: 40.7, 26.6.
+// Minibatches that the single-step kernel of cada_logreg_steps.hip takes, in it / with a launch for rule and server: M = 33, p = 22, B = 92, LAG: 13.0, 13.8; M = 48: 13.4, 13.9; M = 64: 15.5, 14.7; M = 48,
+// p = 200, B = 100: 13.8, 14.3; M = 64, p = 256: 16.1, 15.0; M = 21, p = 784, B = 60: 16.2, 14.5; M = 17, p = 1024: 16.4, 14.7: the same line for M p; for few columns M could go to 48.
 constexpr int kServerColumns = 2 * R_NT, kServerState = 16384, kServerWorkers = 32;      // p, M p and M up to here
 // The rule in the last workgroup saves a launch as well; the workgroups count themselves in one after the other for it.  Measured, us with
 // and without it: B = 65, p = 22: M = 100: 17.2, 19.9; 256: 23.3, 24.1; 400: 28.6, 30.0; 512: 32.3, 32.4; 1024: 54.9, 53.8; p = 8191, M = 512: 215, 219;

@@ -1,5 +1,5 @@
 // Whole iterations of Algorithm 1 in one kernel launch, with the rows in LDS: for minibatches that the registers of cada_logreg_steps.hip do not hold (more than 1024 columns or fewer than 4,
-// more than 64 rows, or 32 of more than 512 columns); the host side serves both.  Logistic workloads so small that a
+// more than 64 rows, or 32 of more than 512 columns); the host side serves both, and asks for both that the rows would fit LDS.  Logistic workloads so small that a
 // step is bound by launch and dependency latency rather than by memory (tens of workers, a few
 // hundred coordinates): four dependent launches per step cost 20-40 us, the arithmetic well
 // under one.  One workgroup per worker:

@@ -1,5 +1,5 @@
 // Whole iterations of Algorithm 1 in one kernel launch, as in cada_logreg_small.hip, for minibatches that a workgroup's registers hold: one workgroup per worker, rows of up to
-// 1024 columns.  A wavefront holds whole rows, four columns per lane and quad, and asks for its rows of the next step at the head of this one: neither the products nor the
+// 1024 columns.  (small_plan still asks that the rows would fit LDS: 32 rows under the CADA rules have up to 1008 columns here.)  A wavefront holds whole rows, four columns per lane and quad, and asks for its rows of the next step at the head of this one: neither the products nor the
 // sums of the gradient pass through LDS, and no fetch stands between a step and the next.
 //
 // What bounds a step is a chain, which has three workgroup barriers and one exchange among the workgroups (each wavefront's instructions count: a dependent one takes 8 cycles):

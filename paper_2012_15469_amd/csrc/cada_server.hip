@@ -165,7 +165,8 @@ __global__ __launch_bounds__(kBlock, 7) void k_server(const DevState s, const Ru
   __shared__ double lhs_s[DECIDE ? kDecideWorkers : 1];
   __shared__ uint8_t dec_s[DECIDE ? kDecideWorkers : 1];       // buffer selector after the decision, 2: uploads
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  // (what the launch reads of its arguments, in one round trip)
+  // What the launch reads of its arguments, in one round trip.  us per step without / with it: 128-64-10, always, 50 workers of 40 rows 41.6 / 41.2; 200-150-5, CADA2, 8 of 200 55.7 / 55.2; 20001 columns, LAG,
+  // 37 of 75 60.7 / 60.4; but 784-512-10, 64 of 128 164.2 / 164.7 (always), 155.6 / 156.0 (CADA2, bf16 store); 784-1024-10, LAG, 20 of 200 154.9 / 155.4.  (67 / 69 vector registers with the rule.)
   asm volatile("" ::"s"(s.h), "s"(s.vhat), "s"(s.theta), "s"(s.theta_lo), "s"(s.gbuf), "s"(s.gbuf16), "s"(s.sel), "s"(s.n_up), "s"(s.lhs_part), "s"(s.M), "s"(s.p), "s"(s.ps), "s"(s.k), "s"(s.rule),
                "s"(s.D), "s"(s.n_lhs_part), "s"(s.resum), "s"(ri.in), "s"(ri.rhs), "s"(replay));
   int64_t base = (int64_t)blockIdx.x * 256;
@@ -370,7 +371,7 @@ __global__ __launch_bounds__(kBlock, 7) void k_server(const DevState s, const Ru
 // 2000-500-10, M = 20, n = 281: 154.9 / 153.0; 784-300-10, M = 100: 130.1 / 127.6; 784-512-10, M = 64, n = 137: 174.2 / 171.3; 3072-1024-1024-10, M = 16: 580.9 / 577.1.
 // The launch of its own: 784-512-10, M = 64: 4.8 us, 5.9 where it adds the squared step's parts up itself; 3072-1024-1024-10, M = 16: 6.7, 10.7.
 constexpr int64_t kDecideParts = 3000;
-constexpr int kDecideBlocks = 7 * 256;           // seven workgroups of 68 registers per CU
+constexpr int kDecideBlocks = 7 * 256;           // seven workgroups of up to 73 registers per CU
 void decide_plan(Ctx *c, char *room) {
   c->rule_in = RuleInputs{reinterpret_cast<double *>(room), reinterpret_cast<int32_t *>(room + 256)};
   const int64_t M = c->s.M, n = c->s.n_lhs_part;
