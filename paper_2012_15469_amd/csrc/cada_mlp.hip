@@ -1650,18 +1650,22 @@ __device__ __forceinline__ void stage_weights(const StageArgs &a, const PrepLaye
       float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
       if (i < p.din && o < p.dout) {
         const int64_t src = p.offW + (int64_t)i * p.dout + o;
-        // (whole quads also where the row ends inside them: up to seven floats past it, of the next row, the bias or what follows in the workspace, which are not used)
+        // (whole quads also where the row ends inside them: up to seven floats past it, of the next row, the bias or what follows in the workspace, which are not used; the two quads of a tensor
+        // one after the other: they share a line, and with the first quads of all four tensors in front 784-512-10, 64 workers of 128 rows, takes 1 us more per step, 23.4 for 22.2 in this launch)
+        auto both = [&](const float *from, f32x4u (&x)[2]) __attribute__((always_inline)) { x[0] = *reinterpret_cast<const f32x4u *>(from + src); x[1] = *reinterpret_cast<const f32x4u *>(from + src + 4); __builtin_amdgcn_sched_barrier(0); };
+        f32x4u x[2];
+        both(s.theta, x);
+        if (!is_w) {
+          f32x4u xl[2], rh[2], rl[2];
+          both(ref.hi, rh); both(s.theta_lo, xl); both(ref.lo, rl);
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          f32x4u x = *reinterpret_cast<const f32x4u *>(s.theta + src + 4 * q);
-          if (!is_w) {
-            const f32x4u xl = *reinterpret_cast<const f32x4u *>(s.theta_lo + src + 4 * q);
-            const f32x4u rh = *reinterpret_cast<const f32x4u *>(ref.hi + src + 4 * q);
-            const f32x4u rl = *reinterpret_cast<const f32x4u *>(ref.lo + src + 4 * q);
-            x = (x - rh) + (xl - rl);               // the same expression as delta_theta
-          }
+          for (int q = 0; q < 2; ++q) x[q] = (x[q] - rh[q]) + (xl[q] - rl[q]);      // the same expression as delta_theta
+        }
 #pragma unroll
-          for (int e = 0; e < 4; ++e) v[4 * q + e] = o + 4 * q + e < p.dout ? x[e] : 0.f;
+        for (int e = 0; e < 8; ++e) v[e] = x[e >> 2][e & 3];
+        if (o + 8 > p.dout) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v[e] = o + e < p.dout ? v[e] : 0.f;
         }
         if (p.want_n) {                             // (values past dout are zeros, like the padding they land in)
           const int64_t dn = tm(i, o, p.ktn);
