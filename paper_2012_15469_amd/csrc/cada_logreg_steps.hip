@@ -341,8 +341,9 @@ __device__ __forceinline__ void steps_body(const SmallArgs &a, const uint32_t *s
         for (int mm = tid; mm < M; mm += T_NT) dk_s[mm] = (unsigned char)__hip_atomic_load(at.sel + mm, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         lds_sync();
       }
-      if (tid * W < p) {
-        const uint32_t mp4 = (uint32_t)mp * 4u, p4 = (uint32_t)p * 4u;
+      // (whole wavefronts come here: the ballot below takes all lanes; those past the row's end read its last columns once more, and drop them)
+      if (w * kWave * W < p) {
+        const uint32_t mp4 = (uint32_t)mp * 4u, p4 = (uint32_t)p * 4u, col4 = (uint32_t)min(tid * W, (p - 1) / W * W) * 4u;
         constexpr int NG = 16;
         for (int m0 = 0; m0 < M; m0 += NG) {           // sixteen rows asked for before the first is added
           uint32_t bits = (uint32_t)(last >> (m0 & 63));
@@ -353,9 +354,9 @@ __device__ __forceinline__ void steps_body(const SmallArgs &a, const uint32_t *s
           for (int q = 0; q < NG; ++q) {
             const int qq = min(q, M - 1 - m0);         // (past the last worker: its row again, dropped)
             const uint32_t off = ((bits >> qq) & 1u) * mp4 + (uint32_t)(m0 + qq) * p4;
-            if constexpr (W == 1) gq[q][0] = __builtin_amdgcn_raw_buffer_load_b32(store, (uint32_t)tid * 4u, off, kFar);
+            if constexpr (W == 1) gq[q][0] = __builtin_amdgcn_raw_buffer_load_b32(store, col4, off, kFar);
             else {                                     // (the second may lie past the row: dropped)
-              const u2s u = __builtin_bit_cast(u2s, __builtin_amdgcn_raw_buffer_load_b64(store, (uint32_t)tid * 8u, off, kFar));
+              const u2s u = __builtin_bit_cast(u2s, __builtin_amdgcn_raw_buffer_load_b64(store, col4, off, kFar));
               gq[q][0] = u.x; gq[q][W - 1] = u.y;
             }
           }

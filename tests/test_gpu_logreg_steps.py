@@ -40,8 +40,10 @@ def test_against_the_oracle(p, M, B, rule):
 
 
 @pytest.mark.parametrize("rule", [configs.RULE_ALWAYS, configs.RULE_CADA1, configs.RULE_CADA2, configs.RULE_LAG], ids=["always", "cada1", "cada2", "lag"])
-# (511 columns and 10 rows, 1021 and 5: wavefronts that have columns and no rows)
-@pytest.mark.parametrize("p,M,B", [(5, 3, 8), (54, 57, 10), (256, 25, 64), (511, 33, 24), (511, 33, 10), (784, 20, 32), (1021, 2, 17), (1021, 24, 5)])
+# (511 columns and 10 rows, 1021 and 5: wavefronts that have columns and no rows; 5, 65, 260, 513 and 650 columns with more than 56 workers, whose selectors do not travel with the count of a single step: wavefronts
+# with columns for fewer than 16 lanes)
+@pytest.mark.parametrize("p,M,B", [(5, 3, 8), (54, 57, 10), (256, 25, 64), (511, 33, 24), (511, 33, 10), (784, 20, 32), (1021, 2, 17), (1021, 24, 5), (5, 58, 9), (65, 57, 8), (260, 60, 17), (513, 64, 9),
+                                   (650, 130, 8), (1021, 61, 8)])
 def test_single_steps_end_where_a_launch_of_several_does(p, M, B, rule):
     cfg = _cfg(p, M, B, rule)
     prob = _problem(cfg)
